@@ -24,7 +24,7 @@
 // Shares of at most 64 rows (bf16) take a pair of weight-streaming kernels instead (gemm_bf16_skinny_kernel):
 // 32- or 64-row tiles, 256-byte bursts per weight row, the LDS ring given to loads in flight.
 //
-// fp32 path (correctness configuration): plain 64x64x16 LDS-tiled vector-ALU GEMM.
+// fp32 path: 64 x 64 tiles on the fp32 matrix cores (gemm_f32_kernel).
 #include "common.h"
 #include <algorithm>
 #include <cstddef>
@@ -477,61 +477,129 @@ __host__ __device__ __forceinline__ TailPlan plan_tail(int total, int ncu, int n
 constexpr size_t kPartialBytes = (size_t)256 * 256 * sizeof(float);   // one fp32 partial tile
 
 // ------------------------------------------------------------------------------------ fp32
-// C[r, n] = epi( sum_k A[r,k] * B0[n,k], sum_k A[r,k] * B1[n,k] ), 64x64 tile, 4x4 per thread.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// C[r, n] = epi( sum_k A[r,k] * B0[n,k], sum_k A[r,k] * B1[n,k] ) on v_mfma_f32_32x32x2_f32 (fp32 operands and
+// accumulation, like a chain of fmaf).  64 x 64 block tile, 4 waves 2 x 2 of one 32 x 32 tile each, k-tiles of 32.
+// The matrix core's fp32 rate (256 flop per clock and CU, twice the vector unit's without packed instructions) is
+// the bound, and operand delivery is cheap against it: a wave reads 2 KB of LDS per 256 clocks of MFMA.  So the
+// tile is small: several blocks share a CU (32 KB of LDS each), which hides the global loads and the epilogues and
+// keeps the last round short.  A k-tile goes through registers (a row's last chunks may lie past K and are
+// zeroed there), one k-tile ahead, into one of two LDS buffers; one barrier per k-tile.
+//
+// Operands: the order of the sum over k is free, so lane half h takes k-chunk 2 s + h (four floats, one
+// ds_read_b128) of k-step s and feeds float v of both operands to MFMA v.  LDS: 8 chunks of 16 bytes per row,
+// slot(r, c) = 8 r + (c ^ ((r >> 1) & 7)): the 16 consecutive rows that a read serves at a time fall on all 64 banks.
+// SwiGLU: a wave's 32 weight rows are 16 gate rows and the 16 up rows of the same columns (accumulator elements
+// 0-7 and 8-15), so the activation needs no exchange.  D = B . A^T: a lane ends with 4 consecutive columns of a row.
+constexpr int FM = 64, FN = 64, FK = 32;
+constexpr int kF32TileBytes = FM * FK * 4;     // one operand tile: 8 KB
+__device__ __forceinline__ int f32_slot(int r, int c) { return (r << 3) + (c ^ ((r >> 1) & 7)); }
+
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int lda, TileMap m,
                                                        ExpertTable tab, int which0, int which1, int N, int K,
                                                        float* __restrict__ C, int ldc, int tiles_n) {
-    __shared__ float As[16][65], B0s[16][65], B1s[(EPI == EPI_SWIGLU) ? 16 : 1][65];
-    const int tile_m = blockIdx.x / tiles_n, tile_n = blockIdx.x % tiles_n;
-    if (tile_m >= *m.n_tiles) return;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[2][2 * kF32TileBytes];
+    constexpr int NOUT = (EPI == EPI_SWIGLU) ? FN / 2 : FN;                 // output columns per block
+    const int n_tiles_m = *m.n_tiles;
+    const int total = n_tiles_m * tiles_n;
+    if ((int)blockIdx.x >= total) return;
+    int tile_m, tile_n;
+    tile_of_block(blockIdx.x, total, n_tiles_m, tiles_n, &tile_m, &tile_n);
     const int row0 = m.row0[tile_m], nrows = m.nrows[tile_m], ex = m.expert[tile_m];
+    const int32_t* rel = m.gather[tile_m] ? m.rel + (size_t)tile_m * kRelPitch : nullptr;
     auto pick = [&](int which) -> const float* {
         return reinterpret_cast<const float*>(which == 0 ? tab.w1[ex] : which == 1 ? tab.w_up[ex] : tab.w_down[ex]);
     };
     const float* B0 = pick(which0);
-    const float* B1 = (EPI == EPI_SWIGLU) ? pick(which1) : nullptr;
-    const int n0 = tile_n * 64;
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    float acc0[4][4] = {}, acc1[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        for (int q = threadIdx.x; q < 64 * 16; q += 256) {
-            const int r = q / 16, kk = q % 16;
-            const int gr = row0 + min(r, nrows - 1);
-            As[kk][r] = (k0 + kk < K) ? A[(size_t)gr * lda + k0 + kk] : 0.f;
-            const int gn = n0 + r;
-            const bool ok = gn < N && k0 + kk < K;
-            B0s[kk][r] = ok ? B0[(size_t)gn * K + k0 + kk] : 0.f;
-            if (EPI == EPI_SWIGLU) B1s[kk][r] = ok ? B1[(size_t)gn * K + k0 + kk] : 0.f;
+    const float* B1 = (EPI == EPI_SWIGLU) ? pick(which1) : B0;
+    const int n0 = tile_n * NOUT;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+
+    // what this thread fetches: chunk tid % 8 of rows tid / 8 and tid / 8 + 32 of both operand tiles
+    const int c = tid & 7;
+    const f32x4* a_ptr[2];
+    const f32x4* b_ptr[2];
+    int dst[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = (tid >> 3) + 32 * i;
+        int ar = min(r, nrows - 1);
+        if (rel) ar = rel[ar];
+        a_ptr[i] = reinterpret_cast<const f32x4*>(A + (size_t)(row0 + ar) * lda);
+        int col;
+        const float* base = B0;
+        if (EPI == EPI_SWIGLU) {
+            if (r & 16) base = B1;
+            col = n0 + (r >> 5) * 16 + (r & 15);
+        } else {
+            col = n0 + r;
         }
-        __syncthreads();
+        b_ptr[i] = reinterpret_cast<const f32x4*>(base + (size_t)min(col, N - 1) * K);
+        dst[i] = f32_slot(r, c) * 16;
+    }
+    const int nchunk = K / 4;                      // K is a multiple of 4
+    f32x4 av[2], bv[2];
+    auto fetch = [&](int kt) {
+        const int ch = kt * (FK / 4) + c;
+        const int cc = min(ch, nchunk - 1);
 #pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b0[4], b1[4];
+        for (int i = 0; i < 2; ++i) { av[i] = a_ptr[i][cc]; bv[i] = b_ptr[i][cc]; }
+        if (ch >= nchunk) {                        // past K: zero in both (0 * a stray infinity would be a NaN)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { a[i] = As[kk][ty * 4 + i]; b0[i] = B0s[kk][tx * 4 + i]; }
-            if (EPI == EPI_SWIGLU)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) b1[i] = B1s[kk][tx * 4 + i];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    acc0[i][j] = fmaf(a[i], b0[j], acc0[i][j]);
-                    if (EPI == EPI_SWIGLU) acc1[i][j] = fmaf(a[i], b1[j], acc1[i][j]);
-                }
+            for (int i = 0; i < 2; ++i) av[i] = bv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
+    };
+    auto park = [&](unsigned char* st) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            *reinterpret_cast<f32x4*>(st + dst[i]) = av[i];
+            *reinterpret_cast<f32x4*>(st + kF32TileBytes + dst[i]) = bv[i];
+        }
+    };
+    const int fr = lane & 31, fk = lane >> 5;
+    int a_off[4], b_off[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        a_off[s] = f32_slot(wm * 32 + fr, 2 * s + fk) * 16;
+        b_off[s] = kF32TileBytes + f32_slot(wn * 32 + fr, 2 * s + fk) * 16;
+    }
+    f32x16 acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    const int nk = (K + FK - 1) / FK;
+    fetch(0);
+    park(lds[0]);
+    __syncthreads();
+    for (int kt = 0; kt < nk; ++kt) {
+        const unsigned char* st = lds[kt & 1];
+        if (kt + 1 < nk) fetch(kt + 1);
+        f32x4 af[4], bf[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            af[s] = *reinterpret_cast<const f32x4*>(st + a_off[s]);
+            bf[s] = *reinterpret_cast<const f32x4*>(st + b_off[s]);
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf[s][v], af[s][v], acc, 0, 0, 0);
+        if (kt + 1 < nk) park(lds[(kt + 1) & 1]);  // the buffer read in trip kt - 1: everybody passed the barrier since
         __syncthreads();
     }
+    const int gr = wm * 32 + fr;
+    if (gr >= nrows) return;
+    float* crow = C + (size_t)(row0 + (rel ? rel[gr] : gr)) * ldc;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = ty * 4 + i;
-        if (r >= nrows) continue;
+    for (int g = 0; g < ((EPI == EPI_SWIGLU) ? 2 : 4); ++g) {
+        f32x4 v;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx * 4 + j;
-            if (n < N) C[(size_t)(row0 + r) * ldc + n] = epilogue<EPI>(acc0[i][j], acc1[i][j]);
-        }
+        for (int t = 0; t < 4; ++t) v[t] = epilogue<EPI>(acc[4 * g + t], (EPI == EPI_SWIGLU) ? acc[4 * (g + 2) + t] : 0.f);
+        const int col = n0 + wn * (NOUT / 2) + g * 8 + fk * 4;
+        if (col < N) *reinterpret_cast<f32x4*>(crow + col) = v;            // N is a multiple of 4
     }
 }
 
@@ -539,8 +607,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int BM = 256, BN = 256, BK = 32, STAGES = 5;
@@ -1268,8 +1334,9 @@ int launch_bf16_skinny(const void* A, int lda, const TileMap& m, const ExpertTab
 template <int EPI>
 int launch_f32(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
                void* C, int ldc, int R, int nseg, hipStream_t st) {
-    const int tiles_n = (N + 63) / 64;
-    const int max_tiles_m = (R + 63) / 64 + nseg;
+    const int nout = (EPI == EPI_SWIGLU) ? FN / 2 : FN;
+    const int tiles_n = (N + nout - 1) / nout;
+    const int max_tiles_m = (R + FM - 1) / FM + nseg;
     hipLaunchKernelGGL((gemm_f32_kernel<EPI>), dim3(max_tiles_m * tiles_n), dim3(256), 0, st,
                        reinterpret_cast<const float*>(A), lda, m, tab, which0, which1, N, K,
                        reinterpret_cast<float*>(C), ldc, tiles_n);
@@ -1440,10 +1507,10 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     const bool skinny = dtype == MOE_BF16 && R <= kSkinnyRows;
     if (timed_gemm != 0 && (dtype != MOE_BF16 || skinny))
         return moe_set_error(MOE_ESHAPE, "moe_diag_ffn_phases: bf16 and more than %d rows needed", kSkinnyRows);
-    const int bm = skinny ? skinny_tile_rows(R) : (dtype == MOE_BF16) ? BM : 64;
+    const int bm = skinny ? skinny_tile_rows(R) : (dtype == MOE_BF16) ? BM : FM;
     if (ev) MOE_HIP(hipEventRecord(ev[0], st));
-    // gathered tiles address their rows by 32-bit byte offsets from the tile's first row
-    const int gather = (dtype == MOE_BF16 && (size_t)R * (size_t)std::max(H, F) * 2 <= 0xFFFFFFFFull) ? 1 : 0;
+    // gathered bf16 tiles address their rows by 32-bit byte offsets from the tile's first row
+    const int gather = (dtype == MOE_F32 || (size_t)R * (size_t)std::max(H, F) * 2 <= 0xFFFFFFFFull) ? 1 : 0;
     // A thread per segment, and whole waves write the row-offset tables of the gathered tiles.  With a handful of
     // segments a quarter of the block does it as fast and its barriers are cheaper (10 against 12.7 us with 8
     // segments); one wave alone was too few for the tables (18 against 12 us with 64 segments, 10 k table rows).
