@@ -247,6 +247,11 @@ int moe_combine(moe_ctx* ctx, const void* ret, const int32_t* slot_to_row, const
  * moe_status. */
 int moe_selfcheck_tile_order(int32_t tiles_m, int32_t tiles_n, int32_t ncu, int32_t nk);
 
+/* Rows per tile (128, 192 or 256) that a bf16 FFN GEMM of R rows over n_used experts takes on ncu compute units:
+ * N output columns, K the inner dimension (a multiple of 64), act the activation of a first GEMM, -1 for a second.
+ * (Shares of at most 64 rows take the weight-streaming kernels whatever this says.) */
+int moe_selfcheck_tile_shape(int32_t R, int32_t n_used, int32_t N, int32_t K, int32_t act, int32_t ncu);
+
 /* Plan of the weight-streaming FFN kernels (shares of at most 64 rows) for `total` tiles of `ns` stages of K on
  * ncu compute units: checks that the pieces cover the stages exactly once, are at least two stages long and fit
  * the launch.  Returns the number of pieces per tile (1 = whole tiles), or a negative moe_status. */

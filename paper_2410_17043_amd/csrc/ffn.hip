@@ -9,7 +9,8 @@
 // turns the segment list into a list of M-tiles (adjacent segments of the same
 // expert are merged, tiles never straddle experts), so nothing waits for the host.
 //
-// bf16 path: 256x256 block tile, 32-wide k-tiles, 4 waves in 2x2, each wave 128x128 = 4x4
+// bf16 path: 256x256 block tile (192x256 or 128x128 where that fills the chip better, see choose_shape), 32-wide
+// k-tiles, 4 waves in 2x2, each wave 128x128 = 4x4
 // tiles of v_mfma_f32_32x32x16_bf16 with fp32 accumulators (256 accumulator registers per
 // lane); operands go global -> LDS directly (no register staging) through a 5-stage ring that
 // fills the whole 160 KB LDS, in an XOR-swizzled layout that makes every ds_read_b128 of an
@@ -56,18 +57,22 @@ inline size_t tilemap_bytes(int R) {
     return align256(256 + 4 * sizeof(int32_t) * (size_t)max_tiles_for(R)) + (size_t)max_tiles_for(R) * kRelPitch * sizeof(int32_t);
 }
 
-TileMap tilemap_at(void* ws, int R) {
+// the map whose tiles are the workspace's records from `first` on; `which` (0, 1) has a tile count of its own
+TileMap tilemap_at(void* ws, int R, int which = 0, int first = 0) {
     TileMap m;
     char* p = reinterpret_cast<char*>(ws);
     const size_t n = (size_t)max_tiles_for(R);
-    m.n_tiles = reinterpret_cast<int32_t*>(p);
+    m.n_tiles = reinterpret_cast<int32_t*>(p) + which;
     m.row0 = reinterpret_cast<int32_t*>(p + 256);
     m.nrows = m.row0 + n;
     m.expert = m.nrows + n;
     m.gather = m.expert + n;
     m.rel = reinterpret_cast<int32_t*>(p + align256(256 + 4 * sizeof(int32_t) * n));
+    m.row0 += first; m.nrows += first; m.expert += first; m.gather += first;
+    m.rel += (size_t)first * kRelPitch;
     return m;
 }
+inline int max_tiles_of(int R, int bm, int nseg) { return (R + bm - 1) / bm + nseg; }
 
 // Tile map.  The received rows come as segments (rows seg_offset[i] .. seg_offset[i+1] - 1 belong to local
 // expert seg_expert[i]); with several sources and several local experts the segments of one expert are not
@@ -259,13 +264,17 @@ __device__ __forceinline__ Int3 block_scan3(Int3 v, Int3* excl, int* wave_tot /*
     return total;
 }
 
-// One block, a thread per segment.  The segment list is read into LDS in one round trip; the stable order
+// One block per map, a thread per segment.  The segment list is read into LDS in one round trip; the stable order
 // by expert comes from wave ballots (segments of the same expert inside a wave) plus a scan over the 16
 // waves; groups, positions inside the groups and the tiles of the groups come from two block-wide prefix
 // sums; then one thread per tile writes the tile records and the items fill the offset tables.
+struct MapJob { int bm, max_tiles; TileMap m; };
+struct MapJobs { MapJob job[2]; };          // the two GEMMs may take tiles of different heights: a block per map
 __global__ __launch_bounds__(kMapThreads) void tilemap_kernel(const int32_t* __restrict__ seg_offset,
                                                               const int32_t* __restrict__ seg_expert, int nseg, int R,
-                                                              int BM, int n_local, int gather, int max_tiles, TileMap m) {
+                                                              int n_local, int gather, MapJobs jobs) {
+    const int BM = jobs.job[blockIdx.x].bm, max_tiles = jobs.job[blockIdx.x].max_tiles;
+    const TileMap m = jobs.job[blockIdx.x].m;
     __shared__ SegWork w;
     __shared__ int wave_cnt[kMapThreads / 64][MOE_MAX_LOCAL];
     __shared__ int wave_tot[3 * 16];
@@ -474,7 +483,6 @@ __host__ __device__ __forceinline__ TailPlan plan_tail(int total, int ncu, int n
     p.n_full = total - rem;
     return p;
 }
-constexpr size_t kPartialBytes = (size_t)256 * 256 * sizeof(float);   // one fp32 partial tile
 
 // ------------------------------------------------------------------------------------ fp32
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -609,12 +617,23 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int BM = 256, BN = 256, BK = 32, STAGES = 5;
-constexpr int kTileBytes = BM * BK * 2;        // one 256 x 32 bf16 operand tile: 16 KB
-constexpr int kStageBytes = 2 * kTileBytes;    // A tile then B tile
-constexpr int kLdsBytes = STAGES * kStageBytes;   // 160 KB: the whole LDS of a CU
+constexpr int BK = 32, STAGES = 5;
+// Block tile of MI x NJ: the 4 waves are 2 x 2, a wave holds MI x NJ tiles of 32 x 32.
+//   4 x 4  256 x 256, all 160 KB of LDS, one block per CU: the fewest operand bytes per flop
+//   3 x 4  192 x 256, 140 KB, one block per CU
+//   2 x 2  128 x 128, 80 KB, two blocks per CU
+// The last two are for grids that 256 x 256 tiles do not fill (see choose_shape).
+template <int MI, int NJ> struct TileGeom {
+    static constexpr int BM = 64 * MI, BN = 64 * NJ;
+    static constexpr int A_BYTES = BM * BK * 2;              // A tile of a stage (one 32-wide k-tile); the B tile follows
+    static constexpr int STAGE = A_BYTES + BN * BK * 2;
+    static constexpr int LDS = STAGES * STAGE;
+    static constexpr int PER_CU = (160 * 1024) / LDS;        // blocks that share a CU
+    static constexpr size_t PARTIAL = (size_t)BM * BN * sizeof(float);   // one fp32 partial tile
+};
+constexpr int BM = TileGeom<4, 4>::BM;         // rows of the largest tile
 
-// An operand tile is stored as 16 blocks of 16 rows; a block is 1 KB = 64 slots of
+// An operand tile is stored as blocks of 16 rows; a block is 1 KB = 64 slots of
 // 16 bytes and is filled by ONE wave-wide direct-to-LDS load (lane l fills slot l).
 // Inside a block the rows are kept row-major (4 slots per row, so 4 neighbouring
 // lanes fetch 64 contiguous bytes of one row from memory), with the 16-byte chunk
@@ -629,7 +648,7 @@ __device__ __forceinline__ void rc_of_slot(int l, int* r, int* c) {
     *r = l >> 2;
     *c = (l & 3) ^ (l >> 4);
 }
-// byte offset of (row, chunk) inside a 256-row tile
+// byte offset of (row, chunk) inside an operand tile
 __device__ __forceinline__ int tile_off(int row, int c) { return ((row >> 4) << 10) + (slot_of(row & 15, c) << 4); }
 
 __device__ __forceinline__ float fast_silu(float a) {
@@ -657,40 +676,41 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 // Epilogue of a tile in two steps: activation on registers, pack to bf16 and write to LDS (which
 // must be idle) for one 32-row tile i of every wave; then whole-line stores of row tiles
 // [i_lo, i_hi).  acc_i[j][e] is output row  i*32 + lane%32  and output column
-// j*32 + (e/4)*8 + (lane/32)*4 + e%4  of the wave's 128 x (NJ*32) block.
-template <int EPI> struct EpiGeom {
-    static constexpr int NOUT = (EPI == EPI_SWIGLU) ? 128 : 256;   // output columns per block
+// j*32 + (e/4)*8 + (lane/32)*4 + e%4  of the wave's (32 MI) x NW block.
+template <int EPI, int MI, int NJ> struct EpiGeom {
+    static constexpr int NOUT = (EPI == EPI_SWIGLU) ? 32 * NJ : 64 * NJ;   // output columns per block
     static constexpr int NW = NOUT / 2;                            // output columns per wave
-    static constexpr int NJ = NW / 32;                             // 32-wide output column tiles per wave
+    static constexpr int NJO = NW / 32;                            // 32-wide output column tiles per wave
+    static constexpr int ROWS = 32 * MI;                           // rows per wave
     static constexpr int PITCH = NW * 2 + 8;                       // bytes; the +8 spreads the 32 rows of a write over all banks
 };
-template <int EPI>
-__device__ __forceinline__ void stage_rows(const f32x16 (&acc_i)[4], int i, unsigned char* lds) {
-    using G = EpiGeom<EPI>;
+template <int EPI, int MI, int NJ>
+__device__ __forceinline__ void stage_rows(const f32x16 (&acc_i)[NJ], int i, unsigned char* lds) {
+    using G = EpiGeom<EPI, MI, NJ>;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int fr = lane & 31, fk = lane >> 5;
-    unsigned char* region = lds + wave * (128 * G::PITCH);
+    unsigned char* region = lds + wave * (G::ROWS * G::PITCH);
 #pragma unroll
-    for (int j = 0; j < G::NJ; ++j)
+    for (int j = 0; j < G::NJO; ++j)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             float v[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const float up = (EPI == EPI_SWIGLU) ? acc_i[j + 2][4 * g + t] : 0.f;
+                const float up = (EPI == EPI_SWIGLU) ? acc_i[(j + NJ / 2) % NJ][4 * g + t] : 0.f;
                 v[t] = epilogue_bf16<EPI>(acc_i[j][4 * g + t], up);
             }
             const u32x2 p = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
             *reinterpret_cast<u32x2*>(region + (i * 32 + fr) * G::PITCH + (j * 32 + g * 8 + fk * 4) * 2) = p;
         }
 }
-template <int EPI, bool GATHER>
+template <int EPI, int MI, int NJ, bool GATHER>
 __device__ __forceinline__ void flush_rows_impl(int i_lo, int i_hi, const unsigned char* lds, int row0, int nrows,
                                                 const int32_t* __restrict__ rel, int n0, int N, uint16_t* __restrict__ C, int ldc) {
-    using G = EpiGeom<EPI>;
+    using G = EpiGeom<EPI, MI, NJ>;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
-    const unsigned char* region = lds + wave * (128 * G::PITCH);
+    const unsigned char* region = lds + wave * (G::ROWS * G::PITCH);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // a wave reads back only what it wrote itself
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -700,11 +720,11 @@ __device__ __forceinline__ void flush_rows_impl(int i_lo, int i_hi, const unsign
     const int col = n0 + wn * G::NW + sub_c * 8;
 #pragma unroll 4
     for (int it = i_lo * 32 / RPI; it < i_hi * 32 / RPI; ++it) {
-        const int r = it * RPI + sub_r;            // row inside this wave's 128
+        const int r = it * RPI + sub_r;            // row inside this wave's rows
         const unsigned char* src = region + r * G::PITCH + sub_c * 16;
         const u32x2 lo = *reinterpret_cast<const u32x2*>(src);
         const u32x2 hi = *reinterpret_cast<const u32x2*>(src + 8);
-        const int gr = wm * 128 + r;
+        const int gr = wm * G::ROWS + r;
         if (gr < nrows && col < N) {
             const u32x4 q = {lo.x, lo.y, hi.x, hi.y};
             const int orow = row0 + (GATHER ? rel[gr] : gr);   // gathered tile: its rows are not consecutive
@@ -713,19 +733,19 @@ __device__ __forceinline__ void flush_rows_impl(int i_lo, int i_hi, const unsign
     }
 }
 // two copies of the store loop: the common one keeps its plain row arithmetic
-template <int EPI>
+template <int EPI, int MI, int NJ>
 __device__ __forceinline__ void flush_rows(int i_lo, int i_hi, const unsigned char* lds, int row0, int nrows,
                                            const int32_t* __restrict__ rel, int n0, int N, uint16_t* __restrict__ C, int ldc) {
-    if (rel) flush_rows_impl<EPI, true>(i_lo, i_hi, lds, row0, nrows, rel, n0, N, C, ldc);
-    else flush_rows_impl<EPI, false>(i_lo, i_hi, lds, row0, nrows, rel, n0, N, C, ldc);
+    if (rel) flush_rows_impl<EPI, MI, NJ, true>(i_lo, i_hi, lds, row0, nrows, rel, n0, N, C, ldc);
+    else flush_rows_impl<EPI, MI, NJ, false>(i_lo, i_hi, lds, row0, nrows, rel, n0, N, C, ldc);
 }
 
-// C[r, n] = epi(sum_k A[r,k] B0[n,k] , sum_k A[r,k] B1[n,k]) for one 256-row M-tile and one
-// N-tile.  SwiGLU: the B tile's 256 rows are, per wave-column wn (64 output columns), 64 rows
-// of W1 followed by the 64 rows of Wu for the same columns, so the gate and the up product of
+// C[r, n] = epi(sum_k A[r,k] B0[n,k] , sum_k A[r,k] B1[n,k]) for one M-tile of 64 MI rows and one
+// N-tile of 64 NJ weight rows.  SwiGLU: the B tile's rows are, per wave-column wn (16 NJ output columns), 16 NJ rows
+// of W1 followed by the 16 NJ rows of Wu for the same columns, so the gate and the up product of
 // a column live in the same lane and the activation needs no exchange.
 //
-// Pipeline: 5 LDS stages of one 32-wide k-tile each (160 KB).  Loads are direct-to-LDS and
+// Pipeline: 5 LDS stages of one 32-wide k-tile each (160 KB at 4 x 4).  Loads are direct-to-LDS and
 // issued in PAIRS of k-tiles (2q, 2q+1) every second iteration, interleaved so that the two
 // halves of every 128-byte memory line are requested back to back: half-line requests that
 // come a whole k-tile apart cost about twice the L2 bandwidth.  The pair (kt+4, kt+5) is issued
@@ -737,19 +757,21 @@ __device__ __forceinline__ void flush_rows(int i_lo, int i_hi, const unsigned ch
 // TIMED (diagnostics, moe_diag_ffn_phases): the same kernel with the 100 MHz wall clock read by lane 0 of every wave
 // into marks[block][wave][4]: 0 start, 1 first operands in LDS (loop about to start), 2 loop done, 3 end.  The
 // ordinary instantiation contains none of it.
-template <int EPI, bool TIMED>
-__global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const uint16_t* __restrict__ A, int lda, TileMap m,
+template <int EPI, int MI, int NJ, bool TIMED>
+__global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_kernel(const uint16_t* __restrict__ A, int lda, TileMap m,
                                                            ExpertTable tab, int which0, int which1, int N, int K,
                                                            uint16_t* __restrict__ C, int ldc, int tiles_n, int ncu,
-                                                           float* __restrict__ partial, long long* __restrict__ marks) {
+                                                           float* __restrict__ partial, long long* __restrict__ marks,
+                                                           uint32_t mark_blocks) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
 #define MOE_MARK(i)                                                                                                 \
     do {                                                                                                            \
-        if (TIMED && (threadIdx.x & 63) == 0)                                                                       \
+        if (TIMED && blockIdx.x < mark_blocks && (threadIdx.x & 63) == 0)                                           \
             marks[((size_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 4 + (i)] = (long long)wall_clock64();              \
     } while (0)
     MOE_MARK(0);
-    constexpr int NOUT = (EPI == EPI_SWIGLU) ? 128 : 256;                  // output columns per block
+    using TG = TileGeom<MI, NJ>;
+    constexpr int NOUT = EpiGeom<EPI, MI, NJ>::NOUT;                       // output columns per block
     const int n_tiles_m = *m.n_tiles;
     const int total = n_tiles_m * tiles_n;
     const TailPlan plan = plan_tail(total, ncu, K / BK);
@@ -778,8 +800,8 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const uint16_t* __res
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform by construction; tell the compiler
     const int wm = wave >> 1, wn = wave & 1;
 
-    // Direct-to-LDS staging.  A stage is 32 blocks of 1 KB (16 of A, 16 of B); wave w
-    // fills blocks w, w+4, ...: 4 of A and 4 of B per stage.  Addresses are kept as a wave-uniform
+    // Direct-to-LDS staging.  A stage is 4 (MI + NJ) blocks of 1 KB (4 MI of A, 4 NJ of B); wave w
+    // fills blocks w, w+4, ...: MI of A and NJ of B per stage.  Addresses are kept as a wave-uniform
     // 64-bit base (advanced with k by scalar adds) plus a fixed 32-bit byte offset per lane, so a
     // load costs no vector address arithmetic.
     int lr, lc;
@@ -788,115 +810,133 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const uint16_t* __res
     const int kt_lo = (piece < 0) ? 0 : piece * plan.pairs_per * 2;
     const int nk = (piece < 0) ? K / BK : min(plan.pairs_per * 2, K / BK - kt_lo);   // even: K is a multiple of 64
     const char* a_base = reinterpret_cast<const char*>(A + (size_t)row0 * lda) + (size_t)kt_lo * BK * 2;
-    const char* b_base[4];
-    uint32_t a_voff[4], b_voff[4];
-    int a_row[4];                                            // row (relative to row0) of the tile rows this lane fetches
+    const char* b_base[NJ];
+    uint32_t a_voff[MI], b_voff[NJ];
+    int a_row[MI];                                           // row (relative to row0) of the tile rows this lane fetches
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a_row[i] = min((wave + 4 * i) * 16 + lr, nrows - 1);
+    for (int i = 0; i < MI; ++i) a_row[i] = min((wave + 4 * i) * 16 + lr, nrows - 1);
     if (rel) {                                               // gathered tile: offsets from row0, below 2^32 bytes (checked
-        int t[4];                                            // on the host); the four loads go out together
+        int t[MI];                                           // on the host); the loads go out together
 #pragma unroll
-        for (int i = 0; i < 4; ++i) t[i] = rel[a_row[i]];
+        for (int i = 0; i < MI; ++i) t[i] = rel[a_row[i]];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) a_row[i] = t[i];
+        for (int i = 0; i < MI; ++i) a_row[i] = t[i];
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < MI; ++i) {
+        a_voff[i] = (uint32_t)a_row[i] * (uint32_t)lda * 2u + (uint32_t)lc * 16u;
+        asm volatile("" : "+v"(a_voff[i]));                  // (see below)
+    }
+#pragma unroll
+    for (int i = 0; i < NJ; ++i) {
         const int blk = wave + 4 * i;                        // 16-row block of the tile (wave-uniform)
         const int r = blk * 16 + lr;                         // tile row this lane fetches
-        const int ar = a_row[i];
-        a_voff[i] = (uint32_t)ar * (uint32_t)lda * 2u + (uint32_t)lc * 16u;
         int col;
         if (EPI == EPI_SWIGLU) {
-            const int w = r >> 7, sub = r & 127;
-            b_base[i] = reinterpret_cast<const char*>(((blk * 16) & 64) ? B1 : B0) + (size_t)kt_lo * BK * 2;   // sub >= 64 for the whole block or not at all
-            col = n0 + w * 64 + (sub & 63);
+            constexpr int WB = 32 * NJ;                      // weight rows per wave-column, the first half gate, the second up
+            const int w = r / WB, sub = r % WB;
+            b_base[i] = reinterpret_cast<const char*>(((blk * 16) & (WB / 2)) ? B1 : B0) + (size_t)kt_lo * BK * 2;   // sub >= WB / 2 for the whole block or not at all
+            col = n0 + w * (WB / 2) + sub % (WB / 2);
         } else {
             b_base[i] = reinterpret_cast<const char*>(B0) + (size_t)kt_lo * BK * 2;
             col = n0 + r;
         }
         b_voff[i] = (uint32_t)min(col, N - 1) * (uint32_t)K * 2u + (uint32_t)lc * 16u;
         // opaque to the optimiser from here on: it must stay a 32-bit lane offset next to a scalar base
-        asm volatile("" : "+v"(a_voff[i]), "+v"(b_voff[i]));
+        asm volatile("" : "+v"(b_voff[i]));
     }
-    // k-tiles t and t+1 (t even) into the stages at LDS byte offsets so0 and so1; past the end the last pair is fetched again (into stages nobody reads any more) so that
-    // the count of outstanding loads stays uniform
+    // The loads of k-tiles t and t+1 (t even) into the stages at LDS byte offsets so0 and so1, items [i_lo, i_hi): the
+    // MI + NJ 16-row blocks this wave fetches, A and B in turn, each for both k-tiles.  Past the end the last pair is
+    // fetched again (into stages nobody reads any more) so that the count of outstanding loads stays uniform.
     auto issue_part = [&](int t, int so0, int so1, int i_lo, int i_hi) {
         t = min(t, nk - 2);
         unsigned char* s0 = lds + so0;
         unsigned char* s1 = lds + so1;
         const size_t kb = (size_t)t * BK * 2;                // byte offset of k-tile t inside a row
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (i < i_lo || i >= i_hi) continue;
-            const int blk = (wave + 4 * i) * 1024;
-            const char* ak = a_base + kb;
-            const char* bk = b_base[i] + kb;
-            uint32_t &av = a_voff[i], &bv = b_voff[i];
+        for (int it = 0; it < MI + NJ; ++it) {
+            if (it < i_lo || it >= i_hi) continue;
+            static_assert(MI <= NJ, "A and B blocks alternate while there are A blocks");
+            const bool is_a = it < 2 * MI && (it & 1) == 0;
+            const int i = it < 2 * MI ? it >> 1 : it - MI;
+            const int blk = (wave + 4 * i) * 1024 + (is_a ? 0 : TG::A_BYTES);
+            const char* p = (is_a ? a_base : b_base[i]) + kb;
+            uint32_t& v = is_a ? a_voff[i] : b_voff[i];
             // opaque here, so that scalar base + zero-extended 32-bit lane offset is still visible when the
             // load is selected (saddr form: half the address registers, no 64-bit vector add per load)
-            const char* ak1 = ak + BK * 2;
-            const char* bk1 = bk + BK * 2;
-            asm volatile("" : "+s"(ak), "+s"(bk), "+s"(ak1), "+s"(bk1), "+v"(av), "+v"(bv));
-            __builtin_amdgcn_global_load_lds(ak + av, (__attribute__((address_space(3))) void*)(s0 + blk), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds(ak1 + av, (__attribute__((address_space(3))) void*)(s1 + blk), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds(bk + bv, (__attribute__((address_space(3))) void*)(s0 + kTileBytes + blk), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds(bk1 + bv, (__attribute__((address_space(3))) void*)(s1 + kTileBytes + blk), 16, 0, 0);
+            const char* p1 = p + BK * 2;
+            asm volatile("" : "+s"(p), "+s"(p1), "+v"(v));
+            __builtin_amdgcn_global_load_lds(p + v, (__attribute__((address_space(3))) void*)(s0 + blk), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(p1 + v, (__attribute__((address_space(3))) void*)(s1 + blk), 16, 0, 0);
         }
     };
+    constexpr int GI = (MI + NJ + 3) / 4;                    // items per group (the last may have fewer): four groups per pair of k-tiles
+    constexpr int LAST = MI + NJ - 3 * GI;
+    static_assert(LAST >= 1, "");
 
-    f32x16 acc[4][4];                                        // [m-tile i][n-tile j], holds D^T: rows n, columns m
+    f32x16 acc[MI][NJ];                                      // [m-tile i][n-tile j], holds D^T: rows n, columns m
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-    issue_part(0, 0, kStageBytes, 0, 4);
-    issue_part(2, 2 * kStageBytes, 3 * kStageBytes, 0, 3);   // its last group goes out in the first trip below
+    issue_part(0, 0, TG::STAGE, 0, 4 * GI);
+    issue_part(2, 2 * TG::STAGE, 3 * TG::STAGE, 0, 3 * GI);  // its last group goes out in the first trip below
 
     const int fr = lane & 31, fk = lane >> 5;      // fragment row within a 32-row tile, which k-half
     int a_off[2], b_off[2];                        // byte offsets inside a stage of 32-row tile 0, per k-step;
 #pragma unroll                                     // tile i lies 2 KB further (two 16-row blocks)
     for (int s = 0; s < 2; ++s) {
-        a_off[s] = tile_off(wm * 128 + fr, 2 * s + fk);
-        b_off[s] = kTileBytes + tile_off(wn * 128 + fr, 2 * s + fk);
+        a_off[s] = tile_off(wm * 32 * MI + fr, 2 * s + fk);
+        b_off[s] = TG::A_BYTES + tile_off(wn * 32 * NJ + fr, 2 * s + fk);
     }
 
-    auto load_frags = [&](bf16x8 (&af)[4], bf16x8 (&bfr)[4], const unsigned char* st, int s) {
+    auto load_frags = [&](bf16x8 (&af)[MI], bf16x8 (&bfr)[NJ], const unsigned char* st, int s) {
         const unsigned char* pa = st + a_off[s];
         const unsigned char* pb = st + b_off[s];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) af[i] = *reinterpret_cast<const bf16x8*>(pa + i * 2048);
+        for (int i = 0; i < MI; ++i) af[i] = *reinterpret_cast<const bf16x8*>(pa + i * 2048);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) bfr[j] = *reinterpret_cast<const bf16x8*>(pb + j * 2048);
+        for (int j = 0; j < NJ; ++j) bfr[j] = *reinterpret_cast<const bf16x8*>(pb + j * 2048);
     };
-    auto mma = [&](const bf16x8 (&af)[4], const bf16x8 (&bfr)[4]) {
+    auto mma = [&](const bf16x8 (&af)[MI], const bf16x8 (&bfr)[NJ]) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < NJ; ++j)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
     };
 
-    // Software pipeline, two k-tiles per trip, four phases of 16 MFMAs each:
+    // Software pipeline, two k-tiles per trip, four phases of MI x NJ MFMAs each:
     //   A(kt)   read fragments (kt, k-step 1)     | MFMAs (kt, step 0)   | load group 3 of pair (kt+2, kt+3)
     //   barrier: every wave is done with the stages of tiles kt-1 and kt
     //   B(kt)   read fragments (kt+1, step 0)     | MFMAs (kt, step 1)   | load group 0 of pair (kt+4, kt+5)
     //   A(kt+1) read fragments (kt+1, step 1)     | MFMAs (kt+1, step 0) | load group 1
-    //   wait until only groups 0 and 1 (8 loads per wave) are outstanding: pair (kt+2, kt+3) is in LDS; barrier
+    //   wait until only groups 0 and 1 (4 GI loads per wave) are outstanding: pair (kt+2, kt+3) is in LDS; barrier
     //   B(kt+1) read fragments (kt+2, step 0)     | MFMAs (kt+1, step 1) | load group 2
-    // A group is 4 loads per wave (one 16-row block of A and of B, both k-tiles of the pair).  The
-    // loads are spread evenly, one per four MFMAs: a CU sustains roughly one wave-load per 40 clocks
+    // A group is GI 16-row blocks, both k-tiles of the pair: 4 loads per wave at 4 x 4, 2 at 2 x 2.  The
+    // loads are spread evenly, at 4 x 4 one per four MFMAs: a CU sustains roughly one wave-load per 40 clocks
     // when the lines come from HBM, and a load that cannot be accepted stalls the wave's MFMA issue too.
     // A bare s_barrier is used: __syncthreads() would add a fence that waits for ALL outstanding loads.
-    bf16x8 a0[4], b0[4], a1[4], b1[4];
-    __builtin_amdgcn_s_waitcnt(0x0F7C);            // vmcnt(12): pair (0, 1) is in LDS
+    bf16x8 a0[MI], b0[NJ], a1[MI], b1[NJ];
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (6 * GI)); // vmcnt(three groups): pair (0, 1) is in LDS
     __builtin_amdgcn_s_barrier();
     MOE_MARK(1);
     load_frags(a0, b0, lds, 0);
 #define MOE_PHASE_SCHED()                                                                      \
+    if (MI * NJ == 12) {                                                                       \
+    _Pragma("unroll") for (int q = 0; q < 7; ++q) {   /* (MFMA, LDS read) x 7 */                \
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                     \
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                     \
+    }                                                                                          \
+    _Pragma("unroll") for (int q = 0; q < 4; ++q) {   /* (MFMA, global->LDS load) x 4, MFMA */  \
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                     \
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                     \
+    }                                                                                          \
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                         \
+    } else if (MI * NJ == 16) {                                                                \
     _Pragma("unroll") for (int q = 0; q < 8; ++q) {   /* (MFMA, LDS read) x 8 */                \
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                     \
         __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                     \
@@ -904,36 +944,44 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const uint16_t* __res
     _Pragma("unroll") for (int q = 0; q < 4; ++q) {   /* (MFMA, MFMA, global->LDS load) x 4 */  \
         __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                                     \
         __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                     \
+    }                                                                                          \
+    } else {                                                                                   \
+    _Pragma("unroll") for (int q = 0; q < 2; ++q) {   /* (MFMA, 2 LDS reads, MFMA, load) x 2 */ \
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                     \
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);                                     \
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                     \
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                     \
+    }                                                                                          \
     }
     // so[j] is the LDS byte offset of the stage that holds k-tile kt + j; the five values rotate by two per
     // trip, which keeps modulo arithmetic out of the instruction stream
     int so[STAGES];
 #pragma unroll
-    for (int j = 0; j < STAGES; ++j) so[j] = j * kStageBytes;
+    for (int j = 0; j < STAGES; ++j) so[j] = j * TG::STAGE;
     for (int kt = 0; kt < nk; kt += 2) {
         __builtin_amdgcn_sched_barrier(0);
         load_frags(a1, b1, lds + so[0], 1);
-        issue_part(kt + 2, so[2], so[3], 3, 4);
+        issue_part(kt + 2, so[2], so[3], 3 * GI, 4 * GI);
         mma(a0, b0);
         MOE_PHASE_SCHED()
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         load_frags(a0, b0, lds + so[1], 0);
-        issue_part(kt + 4, so[4], so[0], 0, 1);
+        issue_part(kt + 4, so[4], so[0], 0, GI);
         mma(a1, b1);
         MOE_PHASE_SCHED()
         __builtin_amdgcn_sched_barrier(0);
         load_frags(a1, b1, lds + so[1], 1);
-        issue_part(kt + 4, so[4], so[0], 1, 2);
+        issue_part(kt + 4, so[4], so[0], GI, 2 * GI);
         mma(a0, b0);
         MOE_PHASE_SCHED()
         __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0x0F78);        // vmcnt(8): only groups 0 and 1 of the next pair may be outstanding
+        __builtin_amdgcn_s_waitcnt(0x0F70 | (4 * GI));   // only groups 0 and 1 of the next pair may be outstanding
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         load_frags(a0, b0, lds + so[2], 0);
-        issue_part(kt + 4, so[4], so[0], 2, 3);
+        issue_part(kt + 4, so[4], so[0], 2 * GI, 3 * GI);
         mma(a1, b1);
         MOE_PHASE_SCHED()
         __builtin_amdgcn_sched_barrier(0);
@@ -949,72 +997,82 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_kernel(const uint16_t* __res
     if (piece >= 0) {
         // a piece of a tail tile: the raw accumulators, 16 bytes per lane and store (whole 4 KB per store)
         f32x4* dst = reinterpret_cast<f32x4*>(reinterpret_cast<char*>(partial) +
-                                              ((size_t)(tile_id - plan.n_full) * plan.parts + piece) * kPartialBytes);
+                                              ((size_t)(tile_id - plan.n_full) * plan.parts + piece) * TG::PARTIAL);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < NJ; ++j)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                    dst[((i * 4 + j) * 4 + q) * 256 + tid] = v;
+                    dst[((i * NJ + j) * 4 + q) * 256 + tid] = v;
                 }
         MOE_MARK(3);
         return;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) stage_rows<EPI>(acc[i], i, lds);
-    flush_rows<EPI>(0, 4, lds, row0, nrows, rel, n0, N, C, ldc);
+    for (int i = 0; i < MI; ++i) stage_rows<EPI, MI, NJ>(acc[i], i, lds);
+    flush_rows<EPI, MI, NJ>(0, MI, lds, row0, nrows, rel, n0, N, C, ldc);
     MOE_MARK(3);
 #undef MOE_MARK
 }
 
-// Adds the pieces of one 32-row tile per wave (blockIdx.x % 4) of tail tile blockIdx.x / 4 in piece
-// order and finishes those rows like a whole tile's.
-template <int EPI>
+// Adds the pieces of a tail tile in piece order and finishes it.  A block takes one 32 x 32 tile of outputs per wave
+// (of UNITS = MI x NJO per wave and tile), so that even a few tail tiles make hundreds of blocks; four pieces are
+// requested before the first is added, without conditions (past the last piece the last one is read again and not
+// added): a load under a condition waits for the one before it.
+template <int EPI, int MI, int NJ>
 __global__ __launch_bounds__(256) void gemm_bf16_tail_kernel(TileMap m, int N, int K, uint16_t* __restrict__ C, int ldc,
                                                              int tiles_n, int ncu, const float* __restrict__ partial) {
-    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    using G = EpiGeom<EPI, MI, NJ>;
+    using TG = TileGeom<MI, NJ>;
+    constexpr int UNITS = MI * G::NJO, NP = (EPI == EPI_SWIGLU) ? 2 : 1;    // NP: products behind an output
     const int n_tiles_m = *m.n_tiles;
     const int total = n_tiles_m * tiles_n;
     const TailPlan plan = plan_tail(total, ncu, K / BK);
-    const int tt = blockIdx.x >> 2, i = blockIdx.x & 3;
+    const int tt = blockIdx.x / UNITS, unit = blockIdx.x % UNITS;
     if (tt >= plan.n_tail) return;
+    const int i = unit / G::NJO, jo = unit % G::NJO;
     int tile_m, tile_n;
     tile_of_block(plan.n_full + tt, total, n_tiles_m, tiles_n, &tile_m, &tile_n);
     const int row0 = m.row0[tile_m], nrows = m.nrows[tile_m];
     const int32_t* rel = m.gather[tile_m] ? m.rel + (size_t)tile_m * kRelPitch : nullptr;
-    const int tid = threadIdx.x;
-    const f32x4* src = reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(partial) +
-                                                      (size_t)tt * plan.parts * kPartialBytes) + (size_t)i * 16 * 256 + tid;
-    // all pieces of four accumulator quads are requested before the first is added (plan_tail makes at most
-    // 8 pieces): the pass is a latency-bound stream otherwise
-    f32x4 sum[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const f32x4* src = reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(partial) + (size_t)tt * plan.parts * TG::PARTIAL) + tid;
+    f32x4 sum[NP][4];
 #pragma unroll
-    for (int q0 = 0; q0 < 16; q0 += 4) {
-        f32x4 v[8][4];
+    for (int n = 0; n < NP; ++n)
 #pragma unroll
-        for (int p = 0; p < 8; ++p)
+        for (int q = 0; q < 4; ++q) sum[n][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int p0 = 0; p0 < plan.parts; p0 += 4) {
+        f32x4 v[4][NP][4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                v[p][u] = (p < plan.parts) ? src[(size_t)p * (kPartialBytes / 16) + (q0 + u) * 256] : f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            sum[q0 + u] = v[0][u];
+            for (int n = 0; n < NP; ++n)
 #pragma unroll
-            for (int p = 1; p < 8; ++p)
-                if (p < plan.parts) sum[q0 + u] += v[p][u];
-        }
+                for (int q = 0; q < 4; ++q)
+                    v[u][n][q] = src[(size_t)min(p0 + u, plan.parts - 1) * (TG::PARTIAL / 16) + ((i * NJ + jo + n * (NJ / 2)) * 4 + q) * 256];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (p0 + u < plan.parts) {
+#pragma unroll
+                for (int n = 0; n < NP; ++n)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) sum[n][q] += v[u][n][q];
+            }
     }
-    f32x16 acc_i[4];
+    const int gr = (wave >> 1) * G::ROWS + i * 32 + (lane & 31);
+    if (gr >= nrows) return;
+    uint16_t* crow = C + (size_t)(row0 + (rel ? rel[gr] : gr)) * ldc;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int q = 0; q < 4; ++q) {
+        float v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) acc_i[j][4 * q + t] = sum[j * 4 + q][t];
-    stage_rows<EPI>(acc_i, i, lds);
-    flush_rows<EPI>(i, i + 1, lds, row0, nrows, rel, tile_n * EpiGeom<EPI>::NOUT, N, C, ldc);
+        for (int t = 0; t < 4; ++t) v[t] = epilogue_bf16<EPI>(sum[0][q][t], sum[NP - 1][q][t]);
+        const int col = tile_n * G::NOUT + (wave & 1) * G::NW + jo * 32 + q * 8 + (lane >> 5) * 4;
+        if (col < N) *reinterpret_cast<u32x2*>(crow + col) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1047,7 +1105,6 @@ template <int MT> struct SkinnyGeom {
     static constexpr int LOADS = 2 * MT + 8;             // wave-loads per stage and wave
     static constexpr size_t PARTIAL = (size_t)BM_ * SBN * sizeof(float);   // one fp32 partial tile
 };
-constexpr int kSkinnyRows = 64;                          // shares up to this many rows take this path
 
 struct SkinnyPlan {
     int parts;     // pieces per tile
@@ -1061,6 +1118,13 @@ __host__ __device__ __forceinline__ SkinnyPlan plan_skinny(int total, int ncu, i
     p.per = (ns + parts - 1) / parts;
     p.parts = (ns + p.per - 1) / p.per;
     return p;
+}
+
+// Block `id` of `total` -> tile (M fastest).  Blocks go to the 8 XCDs round-robin; every XCD gets a run of consecutive
+// tiles, so that the M-tiles of an expert which share weight rows find them in one L2.
+__host__ __device__ __forceinline__ int skinny_tile(int id, int total) {
+    const int x = id % 8, base = total / 8, extra = total % 8;
+    return x * base + (x < extra ? x : extra) + id / 8;
 }
 
 // byte offset of (row, 16-byte chunk c of the stage's 256 bytes) inside a tile region
@@ -1107,7 +1171,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_skinny_kernel(const uint16_t
     const int ns_all = K / SKW;
     const SkinnyPlan plan = plan_skinny(total, ncu, ns_all);
     if ((int)blockIdx.x >= total * plan.parts) return;
-    const int tile_id = blockIdx.x % total, piece = blockIdx.x / total;
+    const int piece = blockIdx.x / total, tile_id = skinny_tile(blockIdx.x % total, total);
     const int tile_m = tile_id % n_tiles_m, tile_n = tile_id / n_tiles_m;
     const int row0 = __builtin_amdgcn_readfirstlane(m.row0[tile_m]);
     const int nrows = __builtin_amdgcn_readfirstlane(m.nrows[tile_m]);
@@ -1259,40 +1323,97 @@ int round_size() {
     return ncu;
 }
 
-template <int EPI, bool TIMED = false>
+template <int EPI, int MI, int NJ, bool TIMED>
 int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
-                void* C, int ldc, int R, int nseg, float* partial, hipStream_t st, long long* marks = nullptr,
-                size_t marks_len = 0) {
-    const int nout = (EPI == EPI_SWIGLU) ? 128 : 256;
-    const int tiles_n = (N + nout - 1) / nout;
-    const int max_tiles_m = (R + BM - 1) / BM + nseg;
-    const int ncu = round_size();
-    const size_t lds = (size_t)kLdsBytes;
+                void* C, int ldc, int R, int nseg, float* partial, hipStream_t st, long long* marks,
+                size_t marks_len) {
+    using TG = TileGeom<MI, NJ>;
+    using G = EpiGeom<EPI, MI, NJ>;
+    const int tiles_n = (N + G::NOUT - 1) / G::NOUT;
+    const int max_tiles_m = max_tiles_of(R, TG::BM, nseg);
+    const int ncu = round_size() * TG::PER_CU;             // tiles per round of the grid
     static bool attr_done = false;
     if (!attr_done) {
-        MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<EPI, TIMED>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_tail_kernel<EPI>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<EPI, MI, NJ, TIMED>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, TG::LDS));
         attr_done = true;
     }
     // whole tiles first, then at most ncu pieces of tail tiles; blocks past the real tile count exit at once
-    if (TIMED && marks_len < (size_t)(max_tiles_m * tiles_n + ncu) * 16)
-        return moe_set_error(MOE_ESHAPE, "moe_diag_ffn_phases: marks needs %zu elements", (size_t)(max_tiles_m * tiles_n + ncu) * 16);
-    hipLaunchKernelGGL((gemm_bf16_kernel<EPI, TIMED>), dim3(max_tiles_m * tiles_n + ncu), dim3(256), lds, st,
+    if (TIMED) {
+        const int out44 = EpiGeom<EPI, 4, 4>::NOUT;
+        const size_t need = ((size_t)max_tiles_of(R, TileGeom<4, 4>::BM, nseg) * ((N + out44 - 1) / out44) + round_size()) * 16;
+        if (marks_len < need) return moe_set_error(MOE_ESHAPE, "moe_diag_ffn_phases: marks needs %zu elements", need);
+    }
+    hipLaunchKernelGGL((gemm_bf16_kernel<EPI, MI, NJ, TIMED>), dim3(max_tiles_m * tiles_n + ncu), dim3(256), TG::LDS, st,
                        reinterpret_cast<const uint16_t*>(A), lda, m, tab, which0, which1, N, K,
-                       reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, partial, marks);
+                       reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, partial, marks,
+                       (uint32_t)std::min<size_t>(marks_len / 16, 0xFFFFFFFFu));
     MOE_LAUNCH_CHECK("gemm_bf16_kernel");
     // the tile count is only known on the device, but with a short K no count at all gives a tail (plan_tail
     // wants pieces of a minimum length): then there is nothing to add up and the launch is left out
-    bool tail_possible = false;
-    for (int rem = 1; rem < ncu && !tail_possible; ++rem) tail_possible = plan_tail(rem, ncu, K / BK).n_tail > 0;
-    if (tail_possible) {
-        hipLaunchKernelGGL((gemm_bf16_tail_kernel<EPI>), dim3(2 * ncu), dim3(256), lds, st, m, N, K,   // ncu / 2 tiles at most, 4 blocks each
+    int most_tail = 0;
+    for (int rem = 1; rem < ncu; ++rem) most_tail = std::max(most_tail, plan_tail(rem, ncu, K / BK).n_tail);
+    most_tail = std::min(most_tail, max_tiles_m * tiles_n);
+    if (most_tail > 0) {
+        hipLaunchKernelGGL((gemm_bf16_tail_kernel<EPI, MI, NJ>), dim3(most_tail * MI * G::NJO), dim3(256), 0, st, m, N, K,
                            reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, partial);
         MOE_LAUNCH_CHECK("gemm_bf16_tail_kernel");
     }
     return MOE_OK;
+}
+
+enum TileShape { TS_128, TS_192, TS_256 };
+template <int EPI>
+int launch_bf16_shape(TileShape t, const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
+                      void* C, int ldc, int R, int nseg, float* partial, hipStream_t st, bool timed, long long* marks, size_t marks_len) {
+#define MOE_GEMM(...) launch_bf16<EPI, __VA_ARGS__>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, partial, st, marks, marks_len)
+    if (t == TS_128) return timed ? MOE_GEMM(2, 2, true) : MOE_GEMM(2, 2, false);
+    if (t == TS_192) return timed ? MOE_GEMM(3, 4, true) : MOE_GEMM(3, 4, false);
+    return timed ? MOE_GEMM(4, 4, true) : MOE_GEMM(4, 4, false);
+#undef MOE_GEMM
+}
+
+// Which tiles a bf16 GEMM takes.  The number of tiles is only known on the device, so the choice is made from an
+// estimate of it: half a tile of padding per expert.  Every shape's time is modelled as rounds of the grid, a round
+// costing a + b * (k-tiles of 32), and a tail as plan_tail cuts it; the shape with the least time is taken.  The
+// constants (microseconds) are from GEMMs of K = 1024 ... 14336 with whole rounds: 256 x 256 100 us per round at
+// K = 4096, 37 at 1024; 192 x 256 80 us at 4096; 128 x 128, two blocks per CU, 66 us at 4096 and 36 at 2048, and
+// about two thirds of that when the round has one block per CU.  So 256 x 256 is the best rate (1.35 PFLOP/s against
+// 1.3 and 1.0) and the others win where it leaves CUs idle or rows empty: at 2048 -> 1408 -> 2048 with four experts
+// and 400 rows 35 + 33 us against 27 + 18 for 128 x 128; at 1024 -> 4096 -> 1024 and 10199 rows the second GEMM 93
+// against 80 us for 192 x 256 (220 tiles for 256 CUs instead of 160).
+constexpr int kShapeRows[] = {TileGeom<2, 2>::BM, TileGeom<3, 4>::BM, TileGeom<4, 4>::BM};
+constexpr int kSkinnyRows = 64;                          // shares up to this many rows take the streaming kernels
+inline double estimated_tiles_m(int R, int bm, int n_used) {
+    if (n_used <= 1) return (R + bm - 1) / bm;
+    return std::max((double)n_used, (double)R / bm + 0.5 * n_used);
+}
+double modelled_us(TileShape t, int R, int n_used, int N, int K, int act, int cus) {
+    struct Cost { double a, b, a1, b1, piece; };           // round, round of at most one block per CU, pass over a partial tile
+    static const Cost cost[] = {{6.5, 0.467, 6.0, 0.33, 0.026}, {7.6, 0.565, 7.6, 0.565, 0.079}, {9.6, 0.71, 9.6, 0.71, 0.105}};
+    Cost c = cost[t];
+    if (act == MOE_ACT_GELU_MLP) c.a += (t == TS_128) ? 1.0 : 4.0;   // its exp2 and rcp of twice SwiGLU's columns, hidden where two blocks share a CU
+    const int per_cu = (t == TS_128) ? TileGeom<2, 2>::PER_CU : 1, slots = cus * per_cu;
+    const int out_cols = ((t == TS_128) ? TileGeom<2, 2>::BN : TileGeom<4, 4>::BN) / (act == MOE_ACT_SWIGLU ? 2 : 1);
+    const int tiles = (int)(estimated_tiles_m(R, kShapeRows[t], n_used) * ((N + out_cols - 1) / out_cols) + 0.5);
+    const TailPlan p = plan_tail(tiles, slots, K / BK);
+    const int rest = p.n_full % slots;                     // tiles of a last round that is not cut
+    double us = (double)(p.n_full / slots) * (c.a + c.b * (K / BK));
+    if (rest > 0) us += (rest <= cus) ? c.a1 + c.b1 * (K / BK) : c.a + c.b * (K / BK);
+    if (p.n_tail > 0) {
+        const int pieces = p.n_tail * p.parts;
+        us += ((pieces <= cus) ? c.a1 + c.b1 * 2 * p.pairs_per : c.a + c.b * 2 * p.pairs_per) + 5.0 + pieces * c.piece;
+    }
+    return us;
+}
+TileShape choose_shape(int R, int n_used, int N, int K, int act, int cus) {
+    TileShape best = TS_256;
+    double best_us = modelled_us(TS_256, R, n_used, N, K, act, cus);
+    for (TileShape t : {TS_192, TS_128}) {
+        const double us = modelled_us(t, R, n_used, N, K, act, cus);
+        if (us < best_us) { best = t; best_us = us; }
+    }
+    return best;
 }
 
 // Shares of at most kSkinnyRows rows (the tile map is then made of 32 MT-row tiles).
@@ -1303,7 +1424,7 @@ int launch_bf16_skinny_mt(const void* A, int lda, const TileMap& m, const Expert
     using G = SkinnyGeom<MT>;
     const int nout = (EPI == EPI_SWIGLU) ? SBN / 2 : SBN;
     const int tiles_n = (N + nout - 1) / nout;
-    const int max_total = ((R + G::BM_ - 1) / G::BM_ + nseg) * tiles_n;
+    const int max_total = max_tiles_of(R, G::BM_, nseg) * tiles_n;
     const int ncu = round_size();
     static bool attr_done = false;
     if (!attr_done) {
@@ -1336,7 +1457,7 @@ int launch_f32(const void* A, int lda, const TileMap& m, const ExpertTable& tab,
                void* C, int ldc, int R, int nseg, hipStream_t st) {
     const int nout = (EPI == EPI_SWIGLU) ? FN / 2 : FN;
     const int tiles_n = (N + nout - 1) / nout;
-    const int max_tiles_m = (R + FM - 1) / FM + nseg;
+    const int max_tiles_m = max_tiles_of(R, FM, nseg);
     hipLaunchKernelGGL((gemm_f32_kernel<EPI>), dim3(max_tiles_m * tiles_n), dim3(256), 0, st,
                        reinterpret_cast<const float*>(A), lda, m, tab, which0, which1, N, K,
                        reinterpret_cast<float*>(C), ldc, tiles_n);
@@ -1379,6 +1500,11 @@ extern "C" int moe_selfcheck_tile_order(int32_t tiles_m, int32_t tiles_n, int32_
 // segment of a known expert lies in exactly one tile of that expert, that tile rows increase, that exactly
 // the tiles with gaps are marked as gathered and that their offset tables are complete.  Returns the
 // number of tiles, or a negative status.
+extern "C" int moe_selfcheck_tile_shape(int32_t R, int32_t n_used, int32_t N, int32_t K, int32_t act, int32_t ncu) {
+    if (R < 1 || n_used < 1 || N < 1 || K < 64 || K % 64 != 0 || ncu < 1) return moe_set_error(MOE_EINVAL, "moe_selfcheck_tile_shape: bad argument");
+    return kShapeRows[choose_shape(R, n_used, N, K, act, ncu)];
+}
+
 extern "C" int moe_selfcheck_skinny_plan(int32_t total, int32_t ncu, int32_t ns) {
     if (total < 1 || ncu < 1 || ns < 1) return moe_set_error(MOE_EINVAL, "moe_selfcheck_skinny_plan: total, ncu and ns must be positive");
     const SkinnyPlan p = plan_skinny(total, ncu, ns);
@@ -1460,7 +1586,7 @@ extern "C" int moe_selfcheck_tile_map(const int32_t* seg_offset, const int32_t* 
 
 extern "C" size_t moe_ffn_workspace_bytes(int32_t R_max, int32_t H, int32_t F, int32_t act, int32_t dtype) {
     if (R_max < 0 || H <= 0 || F <= 0 || act < 0 || act > 2 || (dtype != MOE_F32 && dtype != MOE_BF16)) return 0;
-    const size_t partial = (dtype == MOE_BF16) ? (size_t)kMaxCU * kPartialBytes : 0;   // pieces of tail tiles
+    const size_t partial = (dtype == MOE_BF16) ? (size_t)kMaxCU * TileGeom<4, 4>::PARTIAL : 0;   // pieces of tail tiles
     return tilemap_bytes(R_max) + align256((size_t)R_max * F * elem_size(dtype)) + partial + 256;
 }
 
@@ -1501,22 +1627,38 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         if (ev) for (int i = 0; i < 4; ++i) MOE_HIP(hipEventRecord(ev[i], st));
         return MOE_OK;
     }
-    TileMap m = tilemap_at(workspace, R);
     void* hmid = reinterpret_cast<char*>(workspace) + tilemap_bytes(R);
     float* partial = reinterpret_cast<float*>(reinterpret_cast<char*>(hmid) + align256((size_t)R * F * elem_size(dtype)));
     const bool skinny = dtype == MOE_BF16 && R <= kSkinnyRows;
     if (timed_gemm != 0 && (dtype != MOE_BF16 || skinny))
         return moe_set_error(MOE_ESHAPE, "moe_diag_ffn_phases: bf16 and more than %d rows needed", kSkinnyRows);
-    const int bm = skinny ? skinny_tile_rows(R) : (dtype == MOE_BF16) ? BM : FM;
-    if (ev) MOE_HIP(hipEventRecord(ev[0], st));
     // gathered bf16 tiles address their rows by 32-bit byte offsets from the tile's first row
     const int gather = (dtype == MOE_F32 || (size_t)R * (size_t)std::max(H, F) * 2 <= 0xFFFFFFFFull) ? 1 : 0;
+    TileShape shape[2] = {TS_256, TS_256};
+    int bm[2] = {FM, FM};
+    if (skinny) {
+        bm[0] = bm[1] = skinny_tile_rows(R);
+    } else if (dtype == MOE_BF16) {
+        const int n_used = std::min(std::min(n_local, nseg), R);
+        shape[0] = choose_shape(R, n_used, F, H, act, round_size());
+        shape[1] = choose_shape(R, n_used, H, F, -1, round_size());
+        for (int i = 0; i < 2; ++i) bm[i] = kShapeRows[shape[i]];
+        // two maps share the records of the workspace, which are made for one map of 64-row tiles
+        if (bm[0] != bm[1] && max_tiles_of(R, bm[0], nseg) + max_tiles_of(R, bm[1], nseg) > max_tiles_for(R)) {
+            shape[1] = shape[0];
+            bm[1] = bm[0];
+        }
+    }
+    if (ev) MOE_HIP(hipEventRecord(ev[0], st));
+    MapJobs jobs;
+    jobs.job[0] = MapJob{bm[0], max_tiles_of(R, bm[0], nseg), tilemap_at(workspace, R)};
+    jobs.job[1] = (bm[1] == bm[0]) ? jobs.job[0] : MapJob{bm[1], max_tiles_of(R, bm[1], nseg), tilemap_at(workspace, R, 1, jobs.job[0].max_tiles)};
+    const TileMap &m = jobs.job[0].m, &m2 = jobs.job[1].m;
     // A thread per segment, and whole waves write the row-offset tables of the gathered tiles.  With a handful of
     // segments a quarter of the block does it as fast and its barriers are cheaper (10 against 12.7 us with 8
     // segments); one wave alone was too few for the tables (18 against 12 us with 64 segments, 10 k table rows).
     const int map_threads = (nseg <= 16) ? 256 : kMapThreads;
-    hipLaunchKernelGGL(tilemap_kernel, dim3(1), dim3(map_threads), 0, st, seg_offset, seg_expert, nseg, R, bm, n_local, gather,
-                       (R + bm - 1) / bm + nseg, m);
+    hipLaunchKernelGGL(tilemap_kernel, dim3(bm[1] == bm[0] ? 1 : 2), dim3(map_threads), 0, st, seg_offset, seg_expert, nseg, R, n_local, gather, jobs);
     MOE_LAUNCH_CHECK("tilemap_kernel");
     if (ev) MOE_HIP(hipEventRecord(ev[1], st));
     int rc;
@@ -1528,17 +1670,15 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         if (ev) MOE_HIP(hipEventRecord(ev[2], st));
         rc = launch_bf16_skinny<EPI_PLAIN>(hmid, F, m, tab, 2, 2, H, F, out, H, R, nseg, partial, st);
     } else if (dtype == MOE_BF16) {
-        if (timed_gemm == 1) {
-            if (act == MOE_ACT_SWIGLU) rc = launch_bf16<EPI_SWIGLU, true>(recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, partial, st, marks, marks_len);
-            else if (act == MOE_ACT_GELU_MLP) rc = launch_bf16<EPI_GELU, true>(recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, partial, st, marks, marks_len);
-            else rc = launch_bf16<EPI_SILU, true>(recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, partial, st, marks, marks_len);
-        } else if (act == MOE_ACT_SWIGLU) rc = launch_bf16<EPI_SWIGLU>(recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, partial, st);
-        else if (act == MOE_ACT_GELU_MLP) rc = launch_bf16<EPI_GELU>(recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, partial, st);
-        else rc = launch_bf16<EPI_SILU>(recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, partial, st);
+        if (act == MOE_ACT_SWIGLU)
+            rc = launch_bf16_shape<EPI_SWIGLU>(shape[0], recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, partial, st, timed_gemm == 1, marks, marks_len);
+        else if (act == MOE_ACT_GELU_MLP)
+            rc = launch_bf16_shape<EPI_GELU>(shape[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, partial, st, timed_gemm == 1, marks, marks_len);
+        else
+            rc = launch_bf16_shape<EPI_SILU>(shape[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, partial, st, timed_gemm == 1, marks, marks_len);
         if (rc != MOE_OK) return rc;
         if (ev) MOE_HIP(hipEventRecord(ev[2], st));
-        if (timed_gemm == 2) rc = launch_bf16<EPI_PLAIN, true>(hmid, F, m, tab, 2, 2, H, F, out, H, R, nseg, partial, st, marks, marks_len);
-        else rc = launch_bf16<EPI_PLAIN>(hmid, F, m, tab, 2, 2, H, F, out, H, R, nseg, partial, st);
+        rc = launch_bf16_shape<EPI_PLAIN>(shape[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, partial, st, timed_gemm == 2, marks, marks_len);
     } else {
         if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, st);
         else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, st);

@@ -513,3 +513,36 @@ def test_combine(H, cfg, with_shared):
     sh.combine(H.dev(ret, cfg.dtype), None if shared is None else H.dev(shared, cfg.dtype))
     torch.cuda.synchronize()
     assert H.rel_err(H.host(sh.y), ref) < (1e-6 if cfg.dtype == "fp32" else 2 ** -8)
+
+
+# The tile heights (first GEMM, second GEMM) a share takes, with rows just past a tile edge, gathered tiles, two maps in
+# one workspace, and too many segments for two maps (then both GEMMs take the first one's height).
+TILE_SHAPE_CASES = [(129, 256, 1408, 1, 1, 2, (128, 128)), (385, 128, 9216, 1, 2, 2, (192, 128)), (513, 128, 9216, 2, 9, 2, (256, 128)),
+                    (2000, 1024, 4608, 2, 7, 0, (192, 192)), (1151, 2048, 4608, 1, 3, 1, (128, 192)), (2500, 1024, 4608, 3, 40, 0, (256, 192)),
+                    (2500, 1024, 4608, 3, 600, 0, (256, 192))]
+
+
+@pytest.mark.parametrize("R,Hd,F,n_local,nseg,act,rows", TILE_SHAPE_CASES)
+def test_expert_ffn_tile_heights(H, R, Hd, F, n_local, nseg, act, rows):
+    from paper_2410_17043_amd import _lib
+    shape_of = _lib.load().moe_selfcheck_tile_shape
+    assert (shape_of(R, n_local, F, Hd, act, 256), shape_of(R, n_local, Hd, F, -1, 256)) == rows
+    cfg = small("c2_mixtral", H=Hd, F=F, act=act)
+    r = np.random.default_rng(R + nseg)
+    recv = W.to_bf16_grid(r.standard_normal((R, Hd)).astype(np.float32))
+    experts = [W.make_expert_weights(cfg, e) for e in range(n_local)]
+    off, exp = make_segments(r, R, nseg, n_local)
+    out = H.run_ffn(H.dev(recv, "bf16"), off, exp, [H.weights_to_dev(w, "bf16") for w in experts], Hd, F, act, "bf16")
+    H.assert_close(H.host(out), O.expert_ffn(recv, off, exp, experts, act), "bf16")
+
+
+# fp32 tiles of 64 x 64: one row past a tile, a K that is no multiple of the 32-wide k-tile, gathered tiles, N below a tile
+@pytest.mark.parametrize("act,R,Hd,F,n_local,nseg", [(2, 65, 100, 68, 1, 1), (0, 129, 36, 260, 2, 9), (1, 64, 4, 4, 1, 1), (2, 300, 128, 96, 3, 64)])
+def test_expert_ffn_fp32_tiles(H, act, R, Hd, F, n_local, nseg):
+    cfg = small("c1_tiny_fp32", H=Hd, F=F, act=act)
+    r = np.random.default_rng(R + F)
+    recv = r.standard_normal((R, Hd)).astype(np.float32)
+    experts = [W.make_expert_weights(cfg, e) for e in range(n_local)]
+    off, exp = make_segments(r, R, nseg, n_local)
+    out = H.run_ffn(H.dev(recv, "fp32"), off, exp, [H.weights_to_dev(w, "fp32") for w in experts], Hd, F, act, "fp32")
+    H.assert_close(H.host(out), O.expert_ffn(recv, off, exp, experts, act), "fp32")
