@@ -42,7 +42,9 @@ struct TileMap {
     int32_t* expert;    // [max_tiles] local expert
     int32_t* gather;    // [max_tiles] 0: the tile is rows row0 .. row0 + nrows - 1; 1: row r is row0 + rel[tile][r]
     int32_t* rel;       // [max_tiles][kRelPitch] row offsets of the gathered tiles (written for those only)
+    int32_t* done;      // [kMaxSplitTiles] pieces that have arrived, per tile cut along K (zeroed with the map); NULL: no tile is cut
 };
+constexpr int kMaxSplitTiles = 256;
 constexpr int kRelPitch = 256;
 
 struct ExpertTable {
@@ -70,6 +72,7 @@ TileMap tilemap_at(void* ws, int R, int which = 0, int first = 0) {
     m.rel = reinterpret_cast<int32_t*>(p + align256(256 + 4 * sizeof(int32_t) * n));
     m.row0 += first; m.nrows += first; m.expert += first; m.gather += first;
     m.rel += (size_t)first * kRelPitch;
+    m.done = nullptr;
     return m;
 }
 inline int max_tiles_of(int R, int bm, int nseg) { return (R + bm - 1) / bm + nseg; }
@@ -269,12 +272,102 @@ __device__ __forceinline__ Int3 block_scan3(Int3 v, Int3* excl, int* wave_tot /*
 // waves; groups, positions inside the groups and the tiles of the groups come from two block-wide prefix
 // sums; then one thread per tile writes the tile records and the items fill the offset tables.
 struct MapJob { int bm, max_tiles; TileMap m; };
-struct MapJobs { MapJob job[2]; };          // the two GEMMs may take tiles of different heights: a block per map
+struct MapJobs { MapJob job[2]; int32_t* done; };   // the two GEMMs may take tiles of different heights; done: both GEMMs' counters or NULL
+__device__ __forceinline__ void zero_done(int32_t* done, int tid, int nth) {
+    if (done)
+        for (int i = tid; i < 2 * kMaxSplitTiles; i += nth) done[i] = 0;
+}
+
+// Up to 64 segments (every local expert of every source of a layer of up to 64 experts): lane k of EVERY wave holds
+// segment k and works out the whole list for itself with ballots, lane permutations and prefix sums - no LDS, no
+// barrier - and the waves share out the tiles.  10 -> 4 us at 64 segments against the block-wide kernel below.
+__device__ __forceinline__ int wave_prefix(int v, int lane) {          // inclusive
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(v, o, 64);
+        if (lane >= o) v += up;
+    }
+    return v;
+}
+constexpr int kSmallMapSegs = 64;
+__global__ __launch_bounds__(256) void tilemap_small_kernel(const int32_t* __restrict__ seg_offset,
+                                                            const int32_t* __restrict__ seg_expert, int nseg, int R,
+                                                            int n_local, int gather, MapJobs jobs) {
+    const MapJob& job = jobs.job[blockIdx.y];
+    const int BM = job.bm;
+    const TileMap m = job.m;
+    const int lane = threadIdx.x & 63, wave_id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i = min(lane, nseg - 1);
+    const int off0 = seg_offset[i], off1 = seg_offset[i + 1];
+    int e = seg_expert[i];
+    if (blockIdx.x == 0 && blockIdx.y == 0) zero_done(jobs.done, threadIdx.x, 256);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int lo = max(off0, 0), len = min(off1, R) - lo;
+    const bool ok = lane < nseg && e >= 0 && e < n_local && len > 0;   // others are skipped
+    // items: the segments by (expert, index) - without gathering by index - first, the skipped ones behind them
+    const unsigned long long okm = __ballot(ok);
+    unsigned long long eq = okm, lt = 0;
+#pragma unroll
+    for (int b = 5; b >= 0; --b) {                                     // MOE_MAX_LOCAL = 64 experts: six bits
+        const bool one = (e >> b) & 1;
+        const unsigned long long mb = __ballot(ok && one);
+        if (one) { lt |= eq & ~mb; eq &= mb; }
+        else eq &= ~mb;
+    }
+    const int ni = __popcll(okm);
+    int rank = gather ? __popcll(lt) + __popcll(eq & below) : __popcll(okm & below);
+    if (!ok) { rank = ni + __popcll(~okm & below); len = 0; e = -1; }
+    lo = __builtin_amdgcn_ds_permute(rank * 4, lo);
+    len = __builtin_amdgcn_ds_permute(rank * 4, len);
+    e = __builtin_amdgcn_ds_permute(rank * 4, e);
+    // groups: chains of items of one expert whose rows increase (without gathering: follow each other)
+    const int incl = wave_prefix(len, lane), excl = incl - len, total = __builtin_amdgcn_readlane(incl, 63);
+    const int prev_e = __shfl_up(e, 1, 64), prev_hi = __shfl_up(lo + len, 1, 64);
+    const bool live = lane < ni;
+    const bool opens = live && (lane == 0 || e != prev_e || (gather ? lo < prev_hi : lo != prev_hi));
+    const unsigned long long heads = __ballot(opens), gaps = __ballot(live && !opens && lo != prev_hi);
+    const unsigned long long upto = below | (1ull << lane);
+    const int head = 63 - __clzll((heads & upto) | 1ull);              // bit 0 is set whenever there is an item
+    const int v0 = excl - __shfl(excl, head, 64);                      // position of the item's first row in its group
+    const unsigned long long above = heads & ~upto;
+    const int end = above ? __builtin_ctzll(above) : ni;               // one past the last item of the group
+    const int excl_end = __shfl(excl, min(end, 63), 64);
+    const int rows_g = (end < ni ? excl_end : total) - excl;           // of the group this item opens
+    const int tiles_g = opens ? (rows_g + BM - 1) / BM : 0;
+    const int tincl = wave_prefix(tiles_g, lane), tile0 = tincl - tiles_g;
+    // a well-formed list (non-decreasing offsets) stays below the bound; overlapping segments are cut off here
+    const int nt = min(__builtin_amdgcn_readlane(tincl, 63), job.max_tiles);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *m.n_tiles = nt;
+    for (int t = wave_id; t < nt; t += gridDim.x * 4) {
+        const int g = 63 - __clzll(__ballot(opens && tile0 <= t));
+        const int v_lo = (t - __builtin_amdgcn_readlane(tile0, g)) * BM;
+        const int v_hi = min(__builtin_amdgcn_readlane(rows_g, g), v_lo + BM), g_end = __builtin_amdgcn_readlane(end, g);
+        unsigned long long in = __ballot(lane >= g && lane < g_end && v0 < v_hi && v0 + len > v_lo);
+        const int f = __builtin_ctzll(in);
+        const int row0 = __builtin_amdgcn_readlane(lo, f) + v_lo - __builtin_amdgcn_readlane(v0, f);
+        const bool gat = (gaps & in & ~(1ull << f)) != 0;              // a gap in front of an item that starts inside the tile
+        if (lane == 0) {
+            m.row0[t] = row0;
+            m.nrows[t] = v_hi - v_lo;
+            m.expert[t] = __builtin_amdgcn_readlane(e, f);
+            m.gather[t] = gat ? 1 : 0;
+        }
+        if (!gat) continue;
+        for (; in; in &= in - 1) {
+            const int k = __builtin_ctzll(in);
+            const int v0k = __builtin_amdgcn_readlane(v0, k), first = __builtin_amdgcn_readlane(lo, k) - v0k - row0;
+            const int b = min(v0k + __builtin_amdgcn_readlane(len, k), v_hi);
+            for (int v = max(v0k, v_lo) + lane; v < b; v += 64) m.rel[(size_t)t * kRelPitch + v - v_lo] = first + v;
+        }
+    }
+}
+
 __global__ __launch_bounds__(kMapThreads) void tilemap_kernel(const int32_t* __restrict__ seg_offset,
                                                               const int32_t* __restrict__ seg_expert, int nseg, int R,
                                                               int n_local, int gather, MapJobs jobs) {
     const int BM = jobs.job[blockIdx.x].bm, max_tiles = jobs.job[blockIdx.x].max_tiles;
     const TileMap m = jobs.job[blockIdx.x].m;
+    if (blockIdx.x == 0) zero_done(jobs.done, threadIdx.x, blockDim.x);
     __shared__ SegWork w;
     __shared__ int wave_cnt[kMapThreads / 64][MOE_MAX_LOCAL];
     __shared__ int wave_tot[3 * 16];
@@ -458,8 +551,8 @@ __host__ __device__ __forceinline__ void tile_of_block(int id, int total, int ti
 // Tail splitting.  The grid runs in rounds of `ncu` tiles (one block per CU); the tiles of a last,
 // mostly empty round would leave most CUs idle for a whole tile time.  When that round has at most
 // ncu / 2 tiles, each of them is cut along K into `parts` pieces that run as separate blocks
-// (1/parts of a tile time) and write fp32 partial tiles; a second small kernel adds the pieces
-// of a tile in piece order and applies the epilogue.  Everything here depends
+// (1/parts of a tile time) and write fp32 partial tiles; the last piece of a tile to arrive adds them
+// in piece order and applies the epilogue (see last_piece).  Everything here depends
 // only on the shapes, so results do not vary from run to run.
 struct TailPlan {
     int n_full;        // tiles handled whole: ids [0, n_full)
@@ -482,6 +575,11 @@ __host__ __device__ __forceinline__ TailPlan plan_tail(int total, int ncu, int n
     p.n_tail = rem;
     p.n_full = total - rem;
     return p;
+}
+// ... with a tail of at most `most_tail` tiles, which the launch has made room for; else none
+__host__ __device__ __forceinline__ TailPlan plan_tail_upto(int most_tail, int total, int ncu, int nk) {
+    const TailPlan p = plan_tail(total, ncu, nk);
+    return p.n_tail <= most_tail ? p : TailPlan{total, 0, 1, nk / 2};
 }
 
 // ------------------------------------------------------------------------------------ fp32
@@ -630,6 +728,7 @@ template <int MI, int NJ> struct TileGeom {
     static constexpr int LDS = STAGES * STAGE;
     static constexpr int PER_CU = (160 * 1024) / LDS;        // blocks that share a CU
     static constexpr size_t PARTIAL = (size_t)BM * BN * sizeof(float);   // one fp32 partial tile
+    static constexpr bool SUM_IN_PLACE = PARTIAL <= 64 * 1024;           // how the pieces of a cut tile are added (see last_piece)
 };
 constexpr int BM = TileGeom<4, 4>::BM;         // rows of the largest tile
 
@@ -740,6 +839,88 @@ __device__ __forceinline__ void flush_rows(int i_lo, int i_hi, const unsigned ch
     else flush_rows_impl<EPI, MI, NJ, false>(i_lo, i_hi, lds, row0, nrows, rel, n0, N, C, ldc);
 }
 
+// The pieces of a tile that is cut along K.  Every piece writes its fp32 accumulators; at 128 x 128 (and in the
+// weight-streaming kernels) the block that arrives last (a counter per tile, nobody waits) adds all pieces in piece
+// order - its own is read back like the others, so the result does not depend on who was last - and finishes the
+// tile.  A kernel of its own for the sums costs 4.5 us where there is nothing to add and 5-16 us where there is, each
+// time behind a launch gap; the last block reads up to half a megabyte in about as long, without the gap.  The larger
+// tiles have 0.8 to 2 MB of pieces, which take one block 20 us and more (93 against 108 us for the second GEMM at 4096
+// -> 14336 -> 4096 and 701 rows): those are added by gemm_bf16_tail_kernel, spread over the chip.
+// The writers may sit on other XCDs, whose L2s do not see each other: pieces are stored and read with accesses of
+// agent scope (sc1: written through, read past the L2), the counter is an agent-scope atomic, and a wave's stores have
+// completed (vmcnt(0)) before its block counts.  The same with plain accesses between __threadfence()s was far
+// slower: every fence writes back the whole L2 (54 against 17 us at 110 tiles of four pieces).
+constexpr int kAgentScope = 16;                              // cache policy bits of a buffer access: sc1
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t pieces_rsrc(const float* partial, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(partial), 0, bytes, 0x00027000);
+}
+__device__ __forceinline__ void store_piece(__amdgpu_buffer_rsrc_t r, int quad, const f32x4& v) {   // 16 bytes at quad * 16
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, quad * 16, 0, kAgentScope);
+}
+__device__ __forceinline__ f32x4 load_piece(__amdgpu_buffer_rsrc_t r, int quad) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, quad * 16, 0, kAgentScope));
+}
+__device__ __forceinline__ bool last_piece(int32_t* done, int parts, int* lds_flag) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070);                        // vmcnt(0) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    if (threadIdx.x == 0) *lds_flag = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
+    __syncthreads();
+    asm volatile("" ::: "memory");
+    return *lds_flag != 0;
+}
+
+// Sum of the pieces of one tile and its epilogue for units [unit_lo, unit_hi) of 32 x 32 outputs per wave.  Four pieces are requested before
+// the first is added, without conditions (past the last piece the last one is read again and not added): a load under
+// a condition waits for the one before it.
+template <int EPI, int MI, int NJ>
+__device__ __forceinline__ void sum_pieces(int unit_lo, int unit_hi, const float* partial, int parts, int row0, int nrows,
+                                           const int32_t* __restrict__ rel, int n0, int N, uint16_t* __restrict__ C, int ldc) {
+    using G = EpiGeom<EPI, MI, NJ>;
+    using TG = TileGeom<MI, NJ>;
+    constexpr int NP = (EPI == EPI_SWIGLU) ? 2 : 1;            // products behind an output
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const __amdgpu_buffer_rsrc_t src = pieces_rsrc(partial, (uint32_t)(parts * TG::PARTIAL));
+#pragma unroll 1
+    for (int unit = unit_lo; unit < unit_hi; ++unit) {
+        const int i = unit / G::NJO, jo = unit % G::NJO;
+        f32x4 sum[NP][4];
+#pragma unroll
+        for (int n = 0; n < NP; ++n)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) sum[n][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int p0 = 0; p0 < parts; p0 += 4) {
+            f32x4 v[4][NP][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int n = 0; n < NP; ++n)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        v[u][n][q] = load_piece(src, min(p0 + u, parts - 1) * (int)(TG::PARTIAL / 16) + ((i * NJ + jo + n * (NJ / 2)) * 4 + q) * 256 + (int)threadIdx.x);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (p0 + u < parts) {
+#pragma unroll
+                    for (int n = 0; n < NP; ++n)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) sum[n][q] += v[u][n][q];
+                }
+        }
+        const int gr = (wave >> 1) * G::ROWS + i * 32 + (lane & 31);
+        if (gr >= nrows) continue;
+        uint16_t* crow = C + (size_t)(row0 + (rel ? rel[gr] : gr)) * ldc;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float v[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) v[t] = epilogue_bf16<EPI>(sum[0][q][t], sum[NP - 1][q][t]);
+            const int col = n0 + (wave & 1) * G::NW + jo * 32 + q * 8 + (lane >> 5) * 4;
+            if (col < N) *reinterpret_cast<u32x2*>(crow + col) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+        }
+    }
+}
+
 // C[r, n] = epi(sum_k A[r,k] B0[n,k] , sum_k A[r,k] B1[n,k]) for one M-tile of 64 MI rows and one
 // N-tile of 64 NJ weight rows.  SwiGLU: the B tile's rows are, per wave-column wn (16 NJ output columns), 16 NJ rows
 // of W1 followed by the 16 NJ rows of Wu for the same columns, so the gate and the up product of
@@ -760,8 +941,8 @@ __device__ __forceinline__ void flush_rows(int i_lo, int i_hi, const unsigned ch
 template <int EPI, int MI, int NJ, bool TIMED>
 __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_kernel(const uint16_t* __restrict__ A, int lda, TileMap m,
                                                            ExpertTable tab, int which0, int which1, int N, int K,
-                                                           uint16_t* __restrict__ C, int ldc, int tiles_n, int ncu,
-                                                           float* __restrict__ partial, long long* __restrict__ marks,
+                                                           uint16_t* __restrict__ C, int ldc, int tiles_n, int ncu, int most_tail,
+                                                           float* partial, long long* __restrict__ marks,
                                                            uint32_t mark_blocks) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
 #define MOE_MARK(i)                                                                                                 \
@@ -774,7 +955,7 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     constexpr int NOUT = EpiGeom<EPI, MI, NJ>::NOUT;                       // output columns per block
     const int n_tiles_m = *m.n_tiles;
     const int total = n_tiles_m * tiles_n;
-    const TailPlan plan = plan_tail(total, ncu, K / BK);
+    const TailPlan plan = plan_tail_upto(most_tail, total, ncu, K / BK);
     int tile_id = blockIdx.x, piece = -1;                                   // piece < 0: the whole K range
     if ((int)blockIdx.x >= plan.n_full) {
         const int j = blockIdx.x - plan.n_full;
@@ -996,8 +1177,8 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
 
     if (piece >= 0) {
         // a piece of a tail tile: the raw accumulators, 16 bytes per lane and store (whole 4 KB per store)
-        f32x4* dst = reinterpret_cast<f32x4*>(reinterpret_cast<char*>(partial) +
-                                              ((size_t)(tile_id - plan.n_full) * plan.parts + piece) * TG::PARTIAL);
+        float* pieces = partial + (size_t)(tile_id - plan.n_full) * plan.parts * (TG::PARTIAL / 4);   // of this tile
+        const __amdgpu_buffer_rsrc_t dst = pieces_rsrc(pieces, (uint32_t)(plan.parts * TG::PARTIAL));
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -1005,8 +1186,10 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                    dst[((i * NJ + j) * 4 + q) * 256 + tid] = v;
+                    store_piece(dst, piece * (int)(TG::PARTIAL / 16) + ((i * NJ + j) * 4 + q) * 256 + tid, v);
                 }
+        if (TG::SUM_IN_PLACE && last_piece(m.done + (tile_id - plan.n_full), plan.parts, reinterpret_cast<int*>(lds)))
+            sum_pieces<EPI, MI, NJ>(0, MI * EpiGeom<EPI, MI, NJ>::NJO, pieces, plan.parts, row0, nrows, rel, n0, N, C, ldc);
         MOE_MARK(3);
         return;
     }
@@ -1017,62 +1200,23 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
 #undef MOE_MARK
 }
 
-// Adds the pieces of a tail tile in piece order and finishes it.  A block takes one 32 x 32 tile of outputs per wave
-// (of UNITS = MI x NJO per wave and tile), so that even a few tail tiles make hundreds of blocks; four pieces are
-// requested before the first is added, without conditions (past the last piece the last one is read again and not
-// added): a load under a condition waits for the one before it.
+// Adds and finishes the tail tiles of the larger shapes: a block per unit of a tile, so that a few tail tiles make
+// hundreds of blocks.
 template <int EPI, int MI, int NJ>
 __global__ __launch_bounds__(256) void gemm_bf16_tail_kernel(TileMap m, int N, int K, uint16_t* __restrict__ C, int ldc,
-                                                             int tiles_n, int ncu, const float* __restrict__ partial) {
+                                                             int tiles_n, int ncu, int most_tail, const float* __restrict__ partial) {
     using G = EpiGeom<EPI, MI, NJ>;
-    using TG = TileGeom<MI, NJ>;
-    constexpr int UNITS = MI * G::NJO, NP = (EPI == EPI_SWIGLU) ? 2 : 1;    // NP: products behind an output
+    constexpr int UNITS = MI * G::NJO;
     const int n_tiles_m = *m.n_tiles;
     const int total = n_tiles_m * tiles_n;
-    const TailPlan plan = plan_tail(total, ncu, K / BK);
+    const TailPlan plan = plan_tail_upto(most_tail, total, ncu, K / BK);
     const int tt = blockIdx.x / UNITS, unit = blockIdx.x % UNITS;
     if (tt >= plan.n_tail) return;
-    const int i = unit / G::NJO, jo = unit % G::NJO;
     int tile_m, tile_n;
     tile_of_block(plan.n_full + tt, total, n_tiles_m, tiles_n, &tile_m, &tile_n);
-    const int row0 = m.row0[tile_m], nrows = m.nrows[tile_m];
     const int32_t* rel = m.gather[tile_m] ? m.rel + (size_t)tile_m * kRelPitch : nullptr;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const f32x4* src = reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(partial) + (size_t)tt * plan.parts * TG::PARTIAL) + tid;
-    f32x4 sum[NP][4];
-#pragma unroll
-    for (int n = 0; n < NP; ++n)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) sum[n][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int p0 = 0; p0 < plan.parts; p0 += 4) {
-        f32x4 v[4][NP][4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int n = 0; n < NP; ++n)
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    v[u][n][q] = src[(size_t)min(p0 + u, plan.parts - 1) * (TG::PARTIAL / 16) + ((i * NJ + jo + n * (NJ / 2)) * 4 + q) * 256];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (p0 + u < plan.parts) {
-#pragma unroll
-                for (int n = 0; n < NP; ++n)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) sum[n][q] += v[u][n][q];
-            }
-    }
-    const int gr = (wave >> 1) * G::ROWS + i * 32 + (lane & 31);
-    if (gr >= nrows) return;
-    uint16_t* crow = C + (size_t)(row0 + (rel ? rel[gr] : gr)) * ldc;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        float v[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = epilogue_bf16<EPI>(sum[0][q][t], sum[NP - 1][q][t]);
-        const int col = tile_n * G::NOUT + (wave & 1) * G::NW + jo * 32 + q * 8 + (lane >> 5) * 4;
-        if (col < N) *reinterpret_cast<u32x2*>(crow + col) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-    }
+    sum_pieces<EPI, MI, NJ>(unit, unit + 1, partial + (size_t)tt * plan.parts * (TileGeom<MI, NJ>::PARTIAL / 4), plan.parts, m.row0[tile_m],
+                            m.nrows[tile_m], rel, tile_n * G::NOUT, N, C, ldc);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1085,8 +1229,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_tail_kernel(TileMap m, int N, i
 // Wave w owns weight rows 32 w .. 32 w + 31 of the tile (SwiGLU: 16 gate rows, then the 16 up rows of the
 // same output columns) and all rows of A: MT x 1 tiles of v_mfma_f32_32x32x16_bf16, eight k-steps per stage.
 // A wave loads the weight rows it reads itself; the A tile is shared (one barrier per stage).  With fewer
-// tiles than CUs every tile is cut along K into `parts` pieces (fp32 partial tiles, added in piece order by a
-// second kernel: results do not depend on the run).
+// tiles than CUs every tile is cut along K into `parts` pieces (fp32 partial tiles, added in piece order by the last
+// block to arrive: results do not depend on the run).
 //
 // LDS layout of a stage: blocks of 1 KB = 4 rows x 16 chunks of 16 bytes, filled by ONE wave-wide
 // direct-to-LDS load (lane l fills slot l).  Inside a block slot(r, c) = 16 r + (c ^ (4 r + blk % 4)):
@@ -1162,14 +1306,14 @@ template <int EPI, int MT>
 __global__ __launch_bounds__(256, 1) void gemm_bf16_skinny_kernel(const uint16_t* __restrict__ A, int lda, TileMap m,
                                                                   ExpertTable tab, int which0, int which1, int N, int K,
                                                                   uint16_t* __restrict__ C, int ldc, int tiles_n, int ncu,
-                                                                  float* __restrict__ partial) {
+                                                                  float* partial) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     using G = SkinnyGeom<MT>;
     constexpr int NOUT = (EPI == EPI_SWIGLU) ? SBN / 2 : SBN;
     const int n_tiles_m = *m.n_tiles;
     const int total = n_tiles_m * tiles_n;
     const int ns_all = K / SKW;
-    const SkinnyPlan plan = plan_skinny(total, ncu, ns_all);
+    const SkinnyPlan plan = m.done ? plan_skinny(total, ncu, ns_all) : SkinnyPlan{1, ns_all};
     if ((int)blockIdx.x >= total * plan.parts) return;
     const int piece = blockIdx.x / total, tile_id = skinny_tile(blockIdx.x % total, total);
     const int tile_m = tile_id % n_tiles_m, tile_n = tile_id / n_tiles_m;
@@ -1262,51 +1406,38 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_skinny_kernel(const uint16_t
     }
     __builtin_amdgcn_s_waitcnt(0x0070);                      // no load may still be on its way to LDS when the block ends
     if (plan.parts > 1) {
-        f32x4* dst = reinterpret_cast<f32x4*>(reinterpret_cast<char*>(partial) + ((size_t)tile_id * plan.parts + piece) * G::PARTIAL);
+        const __amdgpu_buffer_rsrc_t pieces = pieces_rsrc(partial + (size_t)tile_id * plan.parts * (G::PARTIAL / 4), (uint32_t)(plan.parts * G::PARTIAL));
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                dst[(i * 4 + q) * 256 + tid] = f32x4{acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
-        return;
+                store_piece(pieces, piece * (int)(G::PARTIAL / 16) + (i * 4 + q) * 256 + tid,
+                            f32x4{acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]});
+        if (!last_piece(m.done + tile_id, plan.parts, reinterpret_cast<int*>(lds))) return;
+        f32x4 sum[4 * MT];
+#pragma unroll
+        for (int q = 0; q < 4 * MT; ++q) sum[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int p0 = 0; p0 < plan.parts; p0 += 4) {         // four pieces in flight; past the last one it is read again and not added
+            f32x4 v[4][4 * MT];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int q = 0; q < 4 * MT; ++q) v[u][q] = load_piece(pieces, min(p0 + u, plan.parts - 1) * (int)(G::PARTIAL / 16) + q * 256 + tid);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (p0 + u < plan.parts) {
+#pragma unroll
+                    for (int q = 0; q < 4 * MT; ++q) sum[q] += v[u][q];
+                }
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[i][4 * q + t] = sum[i * 4 + q][t];
     }
     skinny_store<EPI, MT>(acc, wave, lane, row0, nrows, rel, n0, N, C, ldc);
-}
-
-// Adds the pieces of a tile in piece order (a block per tile, a thread per lane of the GEMM block) and finishes it.
-template <int EPI, int MT>
-__global__ __launch_bounds__(256) void gemm_bf16_skinny_sum_kernel(TileMap m, int N, int K, uint16_t* __restrict__ C, int ldc,
-                                                                   int tiles_n, int ncu, const float* __restrict__ partial) {
-    constexpr int NOUT = (EPI == EPI_SWIGLU) ? SBN / 2 : SBN;
-    const int n_tiles_m = *m.n_tiles;
-    const int total = n_tiles_m * tiles_n;
-    const SkinnyPlan plan = plan_skinny(total, ncu, K / SKW);
-    const int tile_id = blockIdx.x;
-    if (plan.parts < 2 || tile_id >= total) return;
-    const int tile_m = tile_id % n_tiles_m, tile_n = tile_id / n_tiles_m;
-    const int row0 = m.row0[tile_m], nrows = m.nrows[tile_m];
-    const int32_t* rel = m.gather[tile_m] ? m.rel + (size_t)tile_m * kRelPitch : nullptr;
-    const int tid = threadIdx.x;
-    using G = SkinnyGeom<MT>;
-    const f32x4* src = reinterpret_cast<const f32x4*>(reinterpret_cast<const char*>(partial) + (size_t)tile_id * plan.parts * G::PARTIAL) + tid;
-    f32x4 sum[4 * MT];
-#pragma unroll
-    for (int q = 0; q < 4 * MT; ++q) sum[q] = src[q * 256];
-    for (int p = 1; p < plan.parts; ++p) {
-        f32x4 v[4 * MT];
-#pragma unroll
-        for (int q = 0; q < 4 * MT; ++q) v[q] = src[(size_t)p * (G::PARTIAL / 16) + q * 256];
-#pragma unroll
-        for (int q = 0; q < 4 * MT; ++q) sum[q] += v[q];
-    }
-    f32x16 acc[MT];
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) acc[i][4 * q + t] = sum[i * 4 + q][t];
-    skinny_store<EPI, MT>(acc, tid >> 6, tid & 63, row0, nrows, rel, tile_n * NOUT, N, C, ldc);
 }
 
 constexpr int kMaxCU = 256;                    // tail pieces per launch, at most: sizes the partial-tile workspace
@@ -1325,7 +1456,7 @@ int round_size() {
 
 template <int EPI, int MI, int NJ, bool TIMED>
 int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
-                void* C, int ldc, int R, int nseg, float* partial, hipStream_t st, long long* marks,
+                void* C, int ldc, int R, int nseg, int n_used, float* partial, hipStream_t st, long long* marks,
                 size_t marks_len) {
     using TG = TileGeom<MI, NJ>;
     using G = EpiGeom<EPI, MI, NJ>;
@@ -1344,19 +1475,20 @@ int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab
         const size_t need = ((size_t)max_tiles_of(R, TileGeom<4, 4>::BM, nseg) * ((N + out44 - 1) / out44) + round_size()) * 16;
         if (marks_len < need) return moe_set_error(MOE_ESHAPE, "moe_diag_ffn_phases: marks needs %zu elements", need);
     }
+    // The tile count is only known on the device: the most tail tiles over every count that n_used runs of rows which
+    // share no tile can give.  A list that leaves rows out may have fewer tiles; its tail is cut if it fits as well.
+    int most_tail = 0;
+    if (!TG::SUM_IN_PLACE || m.done)
+        for (int t = (R + TG::BM - 1) / TG::BM, hi = (R + n_used * (TG::BM - 1)) / TG::BM; t <= hi; ++t)
+            most_tail = std::max(most_tail, plan_tail(t * tiles_n, ncu, K / BK).n_tail);
     hipLaunchKernelGGL((gemm_bf16_kernel<EPI, MI, NJ, TIMED>), dim3(max_tiles_m * tiles_n + ncu), dim3(256), TG::LDS, st,
                        reinterpret_cast<const uint16_t*>(A), lda, m, tab, which0, which1, N, K,
-                       reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, partial, marks,
+                       reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, most_tail, partial, marks,
                        (uint32_t)std::min<size_t>(marks_len / 16, 0xFFFFFFFFu));
     MOE_LAUNCH_CHECK("gemm_bf16_kernel");
-    // the tile count is only known on the device, but with a short K no count at all gives a tail (plan_tail
-    // wants pieces of a minimum length): then there is nothing to add up and the launch is left out
-    int most_tail = 0;
-    for (int rem = 1; rem < ncu; ++rem) most_tail = std::max(most_tail, plan_tail(rem, ncu, K / BK).n_tail);
-    most_tail = std::min(most_tail, max_tiles_m * tiles_n);
-    if (most_tail > 0) {
+    if (most_tail > 0 && !TG::SUM_IN_PLACE) {
         hipLaunchKernelGGL((gemm_bf16_tail_kernel<EPI, MI, NJ>), dim3(most_tail * MI * G::NJO), dim3(256), 0, st, m, N, K,
-                           reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, partial);
+                           reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, most_tail, partial);
         MOE_LAUNCH_CHECK("gemm_bf16_tail_kernel");
     }
     return MOE_OK;
@@ -1365,8 +1497,8 @@ int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab
 enum TileShape { TS_128, TS_192, TS_256 };
 template <int EPI>
 int launch_bf16_shape(TileShape t, const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
-                      void* C, int ldc, int R, int nseg, float* partial, hipStream_t st, bool timed, long long* marks, size_t marks_len) {
-#define MOE_GEMM(...) launch_bf16<EPI, __VA_ARGS__>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, partial, st, marks, marks_len)
+                      void* C, int ldc, int R, int nseg, int n_used, float* partial, hipStream_t st, bool timed, long long* marks, size_t marks_len) {
+#define MOE_GEMM(...) launch_bf16<EPI, __VA_ARGS__>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, n_used, partial, st, marks, marks_len)
     if (t == TS_128) return timed ? MOE_GEMM(2, 2, true) : MOE_GEMM(2, 2, false);
     if (t == TS_192) return timed ? MOE_GEMM(3, 4, true) : MOE_GEMM(3, 4, false);
     return timed ? MOE_GEMM(4, 4, true) : MOE_GEMM(4, 4, false);
@@ -1437,12 +1569,6 @@ int launch_bf16_skinny_mt(const void* A, int lda, const TileMap& m, const Expert
                        reinterpret_cast<const uint16_t*>(A), lda, m, tab, which0, which1, N, K,
                        reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, partial);
     MOE_LAUNCH_CHECK("gemm_bf16_skinny_kernel");
-    // with more than ncu / 2 tiles along N alone no tile is ever cut (plan_skinny): nothing to add up
-    if (2 * tiles_n <= ncu) {
-        hipLaunchKernelGGL((gemm_bf16_skinny_sum_kernel<EPI, MT>), dim3(std::min(max_total, ncu)), dim3(256), 0, st, m, N, K,
-                           reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, partial);
-        MOE_LAUNCH_CHECK("gemm_bf16_skinny_sum_kernel");
-    }
     return MOE_OK;
 }
 template <int EPI>
@@ -1635,11 +1761,12 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     // gathered bf16 tiles address their rows by 32-bit byte offsets from the tile's first row
     const int gather = (dtype == MOE_F32 || (size_t)R * (size_t)std::max(H, F) * 2 <= 0xFFFFFFFFull) ? 1 : 0;
     TileShape shape[2] = {TS_256, TS_256};
+    int n_used = 1;
     int bm[2] = {FM, FM};
     if (skinny) {
         bm[0] = bm[1] = skinny_tile_rows(R);
     } else if (dtype == MOE_BF16) {
-        const int n_used = std::min(std::min(n_local, nseg), R);
+        n_used = std::min(gather ? std::min(n_local, nseg) : nseg, R);   // runs of rows that share no tile
         shape[0] = choose_shape(R, n_used, F, H, act, round_size());
         shape[1] = choose_shape(R, n_used, H, F, -1, round_size());
         for (int i = 0; i < 2; ++i) bm[i] = kShapeRows[shape[i]];
@@ -1653,12 +1780,23 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     MapJobs jobs;
     jobs.job[0] = MapJob{bm[0], max_tiles_of(R, bm[0], nseg), tilemap_at(workspace, R)};
     jobs.job[1] = (bm[1] == bm[0]) ? jobs.job[0] : MapJob{bm[1], max_tiles_of(R, bm[1], nseg), tilemap_at(workspace, R, 1, jobs.job[0].max_tiles)};
+    // the counters of the tiles that are cut along K lie behind the maps, in the room of two more tiles (2 x 256
+    // counters); with hundreds of segments for a handful of rows there is no such room and no tile is cut
+    const int n_records = jobs.job[0].max_tiles + (bm[1] == bm[0] ? 0 : jobs.job[1].max_tiles);
+    static_assert(2 * kMaxSplitTiles == 2 * kRelPitch, "two rows of the offset table");
+    jobs.done = (dtype == MOE_BF16 && n_records + 2 <= max_tiles_for(R)) ? tilemap_at(workspace, R, 0, max_tiles_for(R) - 2).rel : nullptr;
+    if (jobs.done) {
+        jobs.job[0].m.done = jobs.done;
+        jobs.job[1].m.done = jobs.done + kMaxSplitTiles;
+    }
     const TileMap &m = jobs.job[0].m, &m2 = jobs.job[1].m;
-    // A thread per segment, and whole waves write the row-offset tables of the gathered tiles.  With a handful of
-    // segments a quarter of the block does it as fast and its barriers are cheaper (10 against 12.7 us with 8
-    // segments); one wave alone was too few for the tables (18 against 12 us with 64 segments, 10 k table rows).
-    const int map_threads = (nseg <= 16) ? 256 : kMapThreads;
-    hipLaunchKernelGGL(tilemap_kernel, dim3(bm[1] == bm[0] ? 1 : 2), dim3(map_threads), 0, st, seg_offset, seg_expert, nseg, R, n_local, gather, jobs);
+    const int n_maps = bm[1] == bm[0] ? 1 : 2;
+    if (nseg <= kSmallMapSegs) {                           // about a tile per wave
+        const int blocks = std::min(64, (R / std::min(bm[0], bm[1]) + std::min(nseg, n_local) + 3) / 4);
+        hipLaunchKernelGGL(tilemap_small_kernel, dim3(blocks, n_maps), dim3(256), 0, st, seg_offset, seg_expert, nseg, R, n_local, gather, jobs);
+    } else {
+        hipLaunchKernelGGL(tilemap_kernel, dim3(n_maps), dim3(kMapThreads), 0, st, seg_offset, seg_expert, nseg, R, n_local, gather, jobs);
+    }
     MOE_LAUNCH_CHECK("tilemap_kernel");
     if (ev) MOE_HIP(hipEventRecord(ev[1], st));
     int rc;
@@ -1668,17 +1806,17 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         else rc = launch_bf16_skinny<EPI_SILU>(recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, partial, st);
         if (rc != MOE_OK) return rc;
         if (ev) MOE_HIP(hipEventRecord(ev[2], st));
-        rc = launch_bf16_skinny<EPI_PLAIN>(hmid, F, m, tab, 2, 2, H, F, out, H, R, nseg, partial, st);
+        rc = launch_bf16_skinny<EPI_PLAIN>(hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, partial, st);
     } else if (dtype == MOE_BF16) {
         if (act == MOE_ACT_SWIGLU)
-            rc = launch_bf16_shape<EPI_SWIGLU>(shape[0], recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, partial, st, timed_gemm == 1, marks, marks_len);
+            rc = launch_bf16_shape<EPI_SWIGLU>(shape[0], recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
         else if (act == MOE_ACT_GELU_MLP)
-            rc = launch_bf16_shape<EPI_GELU>(shape[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, partial, st, timed_gemm == 1, marks, marks_len);
+            rc = launch_bf16_shape<EPI_GELU>(shape[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
         else
-            rc = launch_bf16_shape<EPI_SILU>(shape[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, partial, st, timed_gemm == 1, marks, marks_len);
+            rc = launch_bf16_shape<EPI_SILU>(shape[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
         if (rc != MOE_OK) return rc;
         if (ev) MOE_HIP(hipEventRecord(ev[2], st));
-        rc = launch_bf16_shape<EPI_PLAIN>(shape[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, partial, st, timed_gemm == 2, marks, marks_len);
+        rc = launch_bf16_shape<EPI_PLAIN>(shape[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, partial, st, timed_gemm == 2, marks, marks_len);
     } else {
         if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, st);
         else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, st);

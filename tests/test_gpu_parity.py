@@ -546,3 +546,27 @@ def test_expert_ffn_fp32_tiles(H, act, R, Hd, F, n_local, nseg):
     off, exp = make_segments(r, R, nseg, n_local)
     out = H.run_ffn(H.dev(recv, "fp32"), off, exp, [H.weights_to_dev(w, "fp32") for w in experts], Hd, F, act, "fp32")
     H.assert_close(H.host(out), O.expert_ffn(recv, off, exp, experts, act), "fp32")
+
+
+@pytest.mark.parametrize("R,nseg", [(60, 5), (300, 63), (300, 64), (300, 65), (1000, 64)])
+def test_expert_ffn_tile_map_skips_what_it_must(H, R, nseg):
+    """Empty segments, segments of no local expert, rows before the first and after the last segment, on both sides of
+    the segment count where the map kernel changes."""
+    Hd, F, n_local = 128, 256, 3
+    cfg = small("c2_mixtral", H=Hd, F=F)
+    r = np.random.default_rng(nseg)
+    recv = W.to_bf16_grid(r.standard_normal((R, Hd)).astype(np.float32))
+    experts = [W.make_expert_weights(cfg, e) for e in range(n_local)]
+    off = np.sort(r.integers(3, R - 4, size=nseg + 1))
+    off[1] = off[0]                                                   # an empty one for certain
+    exp = r.integers(-1, n_local + 1, size=nseg)
+    out = H.host(H.run_ffn(H.dev(recv, "bf16"), off, exp, [H.weights_to_dev(w, "bf16") for w in experts], Hd, F, 2, "bf16"))
+    done = np.zeros(R, dtype=bool)
+    ref = np.zeros((R, Hd))
+    for i in range(nseg):
+        if 0 <= exp[i] < n_local and off[i + 1] > off[i]:
+            w = experts[exp[i]]
+            done[off[i]:off[i + 1]] = True
+            ref[off[i]:off[i + 1]] = O.ffn(recv[off[i]:off[i + 1]], w["w1"], w["w_up"], w["w_down"], 2)
+    assert np.isnan(out[~done]).all()
+    H.assert_close(out[done], ref[done], "bf16")
