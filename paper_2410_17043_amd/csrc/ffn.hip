@@ -588,26 +588,30 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // C[r, n] = epi( sum_k A[r,k] * B0[n,k], sum_k A[r,k] * B1[n,k] ) on v_mfma_f32_32x32x2_f32 (fp32 operands and
 // accumulation, like a chain of fmaf).  64 x 64 block tile, 4 waves 2 x 2 of one 32 x 32 tile each, k-tiles of 32.
-// The matrix core's fp32 rate (256 flop per clock and CU, twice the vector unit's without packed instructions) is
-// the bound, and operand delivery is cheap against it: a wave reads 2 KB of LDS per 256 clocks of MFMA.  So the
-// tile is small: several blocks share a CU (32 KB of LDS each), which hides the global loads and the epilogues and
-// keeps the last round short.  A k-tile goes through registers (a row's last chunks may lie past K and are
-// zeroed there), one k-tile ahead, into one of two LDS buffers; one barrier per k-tile.
+// The matrix core's fp32 rate (256 flop per clock and CU; 155 TFLOP/s from registers alone) is the bound, and the tile
+// is small so that three blocks (48 KB of LDS each) share a CU, which hides prologues and epilogues and keeps the last
+// round short: 3001 rows of 1024 -> 2816 -> 1024 SwiGLU are 16.5 + 3 tiles per CU.  Operands go global -> LDS directly
+// through a ring of three k-tiles, one wave-load per k-step between the MFMAs, fragments are read one k-step ahead,
+// one barrier per k-tile.  The pair of GEMMs of that layer: 500 us with the operands staged through registers one
+// k-tile ahead, 475 with direct loads issued together, 415 with them spread over the k-steps on scalar bases
+// (125 TFLOP/s); tiles of 128 x 64 and 128 x 128 take 455 and 480 (4.1 rounds, and 0.75 of one).
 //
 // Operands: the order of the sum over k is free, so lane half h takes k-chunk 2 s + h (four floats, one
 // ds_read_b128) of k-step s and feeds float v of both operands to MFMA v.  LDS: 8 chunks of 16 bytes per row,
-// slot(r, c) = 8 r + (c ^ ((r >> 1) & 7)): the 16 consecutive rows that a read serves at a time fall on all 64 banks.
+// slot(r, c) = 8 r + (c ^ ((r >> 1) & 7)): the 16 consecutive rows that a read serves at a time fall on all 64 banks,
+// and a wave-load fills 8 rows with 128 contiguous bytes each.
 // SwiGLU: a wave's 32 weight rows are 16 gate rows and the 16 up rows of the same columns (accumulator elements
 // 0-7 and 8-15), so the activation needs no exchange.  D = B . A^T: a lane ends with 4 consecutive columns of a row.
 constexpr int FM = 64, FN = 64, FK = 32;
 constexpr int kF32TileBytes = FM * FK * 4;     // one operand tile: 8 KB
+constexpr int kF32Stages = 3;
 __device__ __forceinline__ int f32_slot(int r, int c) { return (r << 3) + (c ^ ((r >> 1) & 7)); }
 
 template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, int lda, TileMap m,
-                                                       ExpertTable tab, int which0, int which1, int N, int K,
-                                                       float* __restrict__ C, int ldc, int tiles_n) {
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[2][2 * kF32TileBytes];
+__global__ __launch_bounds__(256, 3) void gemm_f32_kernel(const float* __restrict__ A, int lda, TileMap m,
+                                                          ExpertTable tab, int which0, int which1, int N, int K,
+                                                          float* __restrict__ C, int ldc, int tiles_n) {
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[kF32Stages * 2 * kF32TileBytes];
     constexpr int NOUT = (EPI == EPI_SWIGLU) ? FN / 2 : FN;                 // output columns per block
     const int n_tiles_m = *m.n_tiles;
     const int total = n_tiles_m * tiles_n;
@@ -622,50 +626,48 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     const float* B0 = pick(which0);
     const float* B1 = (EPI == EPI_SWIGLU) ? pick(which1) : B0;
     const int n0 = tile_n * NOUT;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1;
 
-    // what this thread fetches: chunk tid % 8 of rows tid / 8 and tid / 8 + 32 of both operand tiles
-    const int c = tid & 7;
-    const f32x4* a_ptr[2];
-    const f32x4* b_ptr[2];
-    int dst[2];
+    // wave-load i (of 2 per operand) fills rows 8 (wave + 4 i) .. + 7: this lane fetches one chunk of one row.  Addresses
+    // are a scalar base plus a 32-bit offset per lane.  Chunks past K are fetched clamped to the row's last one and
+    // zeroed when they are read.
+    const int nchunk = K / 4, nk = (K + FK - 1) / FK;   // K is a multiple of 4
+    // byte offset of the lane's chunk inside a k-tile's 128 bytes: row r = 8 (wave + 4 i) + lane / 8, so (r >> 1) & 7 does not depend on i
+    const uint32_t chunk = (uint32_t)(((lane & 7) ^ (((wave & 1) << 2) + (lane >> 4))) * 16);
+    const uint32_t chunk_last = min(chunk, (uint32_t)((nchunk - 1) * 16 - (nk - 1) * (FK * 4)));
+    const char* a_base = reinterpret_cast<const char*>(A + (size_t)row0 * lda);
+    const char* b_base[2];
+    uint32_t a_voff[2], b_voff[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const int r = (tid >> 3) + 32 * i;
-        int ar = min(r, nrows - 1);
-        if (rel) ar = rel[ar];
-        a_ptr[i] = reinterpret_cast<const f32x4*>(A + (size_t)(row0 + ar) * lda);
-        int col;
-        const float* base = B0;
-        if (EPI == EPI_SWIGLU) {
-            if (r & 16) base = B1;
-            col = n0 + (r >> 5) * 16 + (r & 15);
-        } else {
-            col = n0 + r;
-        }
-        b_ptr[i] = reinterpret_cast<const f32x4*>(base + (size_t)min(col, N - 1) * K);
-        dst[i] = f32_slot(r, c) * 16;
+        const int r0 = (wave + 4 * i) * 8;         // wave-uniform
+        int ar = min(r0 + (lane >> 3), nrows - 1);
+        if (rel) ar = rel[ar];                     // gathered tile: offsets below 2^32 bytes (checked on the host)
+        a_voff[i] = (uint32_t)ar * (uint32_t)lda * 4u;
+        const int col0 = (EPI == EPI_SWIGLU) ? (r0 >> 5) * 16 + (r0 & 15) : r0;
+        b_base[i] = reinterpret_cast<const char*>(((EPI == EPI_SWIGLU && (r0 & 16)) ? B1 : B0) + (size_t)n0 * K);
+        b_voff[i] = (uint32_t)min(col0 + (lane >> 3), N - 1 - n0) * (uint32_t)K * 4u;
+        asm volatile("" : "+v"(a_voff[i]), "+v"(b_voff[i]));   // stay 32-bit lane offsets next to a scalar base
     }
-    const int nchunk = K / 4;                      // K is a multiple of 4
-    f32x4 av[2], bv[2];
-    auto fetch = [&](int kt) {
-        const int ch = kt * (FK / 4) + c;
-        const int cc = min(ch, nchunk - 1);
+    // loads [lo, hi) of the four of k-tile kt; past the end the last k-tile is fetched again: their count stays uniform
+    auto issue = [&](int kt, int stage, int lo, int hi) {
+        kt = min(kt, nk - 1);
+        const uint32_t ch = kt == nk - 1 ? chunk_last : chunk;
+        unsigned char* st = lds + stage * 2 * kF32TileBytes + wave * 1024;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) { av[i] = a_ptr[i][cc]; bv[i] = b_ptr[i][cc]; }
-        if (ch >= nchunk) {                        // past K: zero in both (0 * a stray infinity would be a NaN)
-#pragma unroll
-            for (int i = 0; i < 2; ++i) av[i] = bv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int it = 0; it < 4; ++it) {
+            if (it < lo || it >= hi) continue;
+            const bool is_a = it < 2;
+            const int i = it & 1;
+            const char* p = (is_a ? a_base : b_base[i]) + (size_t)kt * (FK * 4);
+            uint32_t v = (is_a ? a_voff[i] : b_voff[i]) + ch;
+            asm volatile("" : "+s"(p), "+v"(v));
+            __builtin_amdgcn_global_load_lds(p + v, (__attribute__((address_space(3))) void*)(st + (is_a ? 0 : kF32TileBytes) + i * 4096), 16, 0, 0);
         }
     };
-    auto park = [&](unsigned char* st) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            *reinterpret_cast<f32x4*>(st + dst[i]) = av[i];
-            *reinterpret_cast<f32x4*>(st + kF32TileBytes + dst[i]) = bv[i];
-        }
-    };
+    issue(0, 0, 0, 4);
+    issue(1, 1, 0, 3);                             // the fourth goes out in the first k-step below
     const int fr = lane & 31, fk = lane >> 5;
     int a_off[4], b_off[4];
 #pragma unroll
@@ -676,26 +678,48 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     f32x16 acc;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-    const int nk = (K + FK - 1) / FK;
-    fetch(0);
-    park(lds[0]);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const unsigned char* st = lds[kt & 1];
-        if (kt + 1 < nk) fetch(kt + 1);
-        f32x4 af[4], bf[4];
+    f32x4 af[2], bf[2];
+    auto read = [&](const unsigned char* st, int s) {
+        af[s & 1] = *reinterpret_cast<const f32x4*>(st + a_off[s]);
+        bf[s & 1] = *reinterpret_cast<const f32x4*>(st + b_off[s]);
+    };
+    // the MFMAs of k-step s of k-tile kt; behind the first the fragments of the next k-step are read, behind the second
+    // load `it` of k-tile t_load goes out
+    auto step = [&](const unsigned char* st_next, int kt, int s, bool ragged, int t_load, int slot, int it) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (ragged && kt * (FK / 4) + 2 * s + fk >= nchunk)   // zero in both: 0 * a stray infinity would be a NaN
+            af[s & 1] = bf[s & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        read(st_next, (s + 1) & 3);
+        issue(t_load, slot, it, it + 1);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            af[s] = *reinterpret_cast<const f32x4*>(st + a_off[s]);
-            bf[s] = *reinterpret_cast<const f32x4*>(st + b_off[s]);
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf[s][v], af[s][v], acc, 0, 0, 0);
-        if (kt + 1 < nk) park(lds[(kt + 1) & 1]);  // the buffer read in trip kt - 1: everybody passed the barrier since
-        __syncthreads();
-    }
+        for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf[s & 1][v], af[s & 1][v], acc, 0, 0, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int cur = 0;                                   // ring slot of k-tile kt
+    auto trip = [&](int kt, bool ragged) {
+        const int nxt = cur == kF32Stages - 1 ? 0 : cur + 1, prev = cur == 0 ? kF32Stages - 1 : cur - 1;
+        const unsigned char* st = lds + cur * 2 * kF32TileBytes;
+        // slot `prev` was last read in trip kt - 1, whose barrier every wave has passed: k-tile kt + 2 goes there
+        step(st, kt, 0, ragged, kt + 1, nxt, 3);
+        step(st, kt, 1, ragged, kt + 2, prev, 0);
+        step(st, kt, 2, ragged, kt + 2, prev, 1);
+        __builtin_amdgcn_s_waitcnt(0x0070 | 2);    // vmcnt(2) lgkmcnt(0): k-tile kt + 1 is in LDS, this wave has read all of kt
+        __builtin_amdgcn_s_barrier();
+        step(lds + nxt * 2 * kF32TileBytes, kt, 3, ragged, kt + 2, prev, 2);
+        cur = nxt;
+    };
+    __builtin_amdgcn_s_waitcnt(0x0F70 | 3);        // vmcnt(3): k-tile 0 is in LDS
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    read(lds, 0);
+    for (int kt = 0; kt < K / FK; ++kt) trip(kt, false);
+    if (K % FK != 0) trip(nk - 1, true);
+    __builtin_amdgcn_s_waitcnt(0x0070);            // no load may still target LDS when the block ends
     const int gr = wm * 32 + fr;
     if (gr >= nrows) return;
     float* crow = C + (size_t)(row0 + (rel ? rel[gr] : gr)) * ldc;
@@ -703,7 +727,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
     for (int g = 0; g < ((EPI == EPI_SWIGLU) ? 2 : 4); ++g) {
         f32x4 v;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = epilogue<EPI>(acc[4 * g + t], (EPI == EPI_SWIGLU) ? acc[4 * (g + 2) + t] : 0.f);
+        for (int t = 0; t < 4; ++t) v[t] = epilogue<EPI>(acc[4 * g + t], (EPI == EPI_SWIGLU) ? acc[4 * (g & 1) + 8 + t] : 0.f);
         const int col = n0 + wn * (NOUT / 2) + g * 8 + fk * 4;
         if (col < N) *reinterpret_cast<f32x4*>(crow + col) = v;            // N is a multiple of 4
     }
@@ -1758,8 +1782,8 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     const bool skinny = dtype == MOE_BF16 && R <= kSkinnyRows;
     if (timed_gemm != 0 && (dtype != MOE_BF16 || skinny))
         return moe_set_error(MOE_ESHAPE, "moe_diag_ffn_phases: bf16 and more than %d rows needed", kSkinnyRows);
-    // gathered bf16 tiles address their rows by 32-bit byte offsets from the tile's first row
-    const int gather = (dtype == MOE_F32 || (size_t)R * (size_t)std::max(H, F) * 2 <= 0xFFFFFFFFull) ? 1 : 0;
+    // gathered tiles address their rows by 32-bit byte offsets from the tile's first row
+    const int gather = (size_t)R * (size_t)std::max(H, F) * elem_size(dtype) <= 0xFFFFFFFFull ? 1 : 0;
     TileShape shape[2] = {TS_256, TS_256};
     int n_used = 1;
     int bm[2] = {FM, FM};

@@ -335,6 +335,10 @@ FFN_CASES = [
     ("fp32", 0, 300, 64, 128, 2, 5),
     ("fp32", 1, 77, 36, 52, 3, 4),
     ("fp32", 2, 130, 64, 128, 2, 6),
+    # several turns of the fp32 ring of k-tiles, with and without a partial last one; K shorter than the ring
+    ("fp32", 2, 131, 164, 228, 2, 6),
+    ("fp32", 0, 65, 160, 96, 1, 1),
+    ("fp32", 1, 64, 8, 40, 2, 3),
     ("bf16", 2, 700, 256, 384, 2, 5),
     ("bf16", 2, 1, 128, 128, 1, 1),
     ("bf16", 1, 523, 256, 512, 3, 7),
