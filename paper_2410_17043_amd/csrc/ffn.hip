@@ -29,6 +29,7 @@
 #include "common.h"
 #include <algorithm>
 #include <cstddef>
+#include <type_traits>
 #include <vector>
 
 namespace {
@@ -796,71 +797,77 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     return *reinterpret_cast<const uint32_t*>(&b);
 }
 
-// Epilogue of a tile in two steps: activation on registers, pack to bf16 and write to LDS (which
-// must be idle) for one 32-row tile i of every wave; then whole-line stores of row tiles
-// [i_lo, i_hi).  acc_i[j][e] is output row  i*32 + lane%32  and output column
-// j*32 + (e/4)*8 + (lane/32)*4 + e%4  of the wave's (32 MI) x NW block.
 template <int EPI, int MI, int NJ> struct EpiGeom {
     static constexpr int NOUT = (EPI == EPI_SWIGLU) ? 32 * NJ : 64 * NJ;   // output columns per block
     static constexpr int NW = NOUT / 2;                            // output columns per wave
     static constexpr int NJO = NW / 32;                            // 32-wide output column tiles per wave
     static constexpr int ROWS = 32 * MI;                           // rows per wave
-    static constexpr int PITCH = NW * 2 + 8;                       // bytes; the +8 spreads the 32 rows of a write over all banks
 };
-template <int EPI, int MI, int NJ>
-__device__ __forceinline__ void stage_rows(const f32x16 (&acc_i)[NJ], int i, unsigned char* lds) {
-    using G = EpiGeom<EPI, MI, NJ>;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// Activation and store of a wave's part of a tile: acc[i][j][e] is output row 32 i + lane % 32 and output column
+// j * 32 + (e / 4) * 8 + (lane / 32) * 4 + e % 4.  Up to 64 columns at a time are packed to bf16, transposed through
+// `region` (4 KB of LDS of this wave's own; LDS accesses of a wave execute in order) and stored as whole lines: stores
+// of 32 bytes per row straight from the registers took 13 us per 256 x 256 tile instead of 4.
+// Region: rows of CH 16-byte chunks, chunk c of row r at slot c ^ (r / (16 / CH)) % CH, the 8-byte halves of a chunk
+// exchanged in rows 16-31: both the 8-byte writes (32 rows, one chunk) and the 16-byte reads touch all 64 banks once.
+// An accumulator element on its way to the vector unit.  The large tiles' accumulators fill the accumulation registers;
+// left to itself the register allocator moves whole 16-element tuples out of them at every use and spills.
+template <bool IN_AGPR> __device__ __forceinline__ float read_acc(float a) {
+    if (!IN_AGPR) return a;
+    float v;
+    asm("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(a));
+    return v;
+}
+template <int EPI, int MI, int NJ, bool IN_AGPR, bool GATHER>
+__device__ __forceinline__ void store_tile(const f32x16 (&acc)[MI][NJ], int lane0, unsigned char* region, __amdgpu_buffer_rsrc_t dst,
+                                           int first_row, int nrows, const int32_t* __restrict__ rel, int ldc) {
+    constexpr int NJO = EpiGeom<EPI, MI, NJ>::NJO;
+    constexpr int JP = NJO == 1 ? 1 : 2, CH = 4 * JP, RPI = 64 / CH, STEPS = 32 / RPI;   // column tiles per pass, chunks per row, rows per store
+    constexpr int PER_ROW = NJO / JP;                        // passes per 32-row tile
+    static_assert(TileGeom<MI, NJ>::STAGE / 4 >= 32 * CH * 16, "32 rows of a pass");
+    int lane = lane0;                                        // opaque: what follows from it is not worth registers during the loop
+    asm volatile("" : "+v"(lane));
     const int fr = lane & 31, fk = lane >> 5;
-    unsigned char* region = lds + wave * (G::ROWS * G::PITCH);
+    unsigned char* wr = region + fr * (CH * 16) + ((fk ^ (fr >> 4)) * 8);
+    const int w_swz = (fr / (16 / CH)) % CH;
+    auto write = [&](int p) {
+        const int i = p / PER_ROW, j0 = p % PER_ROW * JP;
 #pragma unroll
-    for (int j = 0; j < G::NJO; ++j)
+        for (int j = j0; j < j0 + JP; ++j)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            float v[4];
+            for (int g = 0; g < 4; ++g) {
+                float v[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const float up = (EPI == EPI_SWIGLU) ? acc_i[(j + NJ / 2) % NJ][4 * g + t] : 0.f;
-                v[t] = epilogue_bf16<EPI>(acc_i[j][4 * g + t], up);
+                for (int t = 0; t < 4; ++t)
+                    v[t] = epilogue_bf16<EPI>(read_acc<IN_AGPR>(acc[i][j][4 * g + t]),
+                                              (EPI == EPI_SWIGLU) ? read_acc<IN_AGPR>(acc[i][(j + NJ / 2) % NJ][4 * g + t]) : 0.f);
+                *reinterpret_cast<u32x2*>(wr + (((j - j0) * 4 + g) ^ w_swz) * 16) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
             }
-            const u32x2 p = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-            *reinterpret_cast<u32x2*>(region + (i * 32 + fr) * G::PITCH + (j * 32 + g * 8 + fk * 4) * 2) = p;
+    };
+    write(0);
+#pragma unroll
+    for (int p = 0; p < MI * PER_ROW; ++p) {
+        // the wave's LDS accesses execute in order, so the region can be written again behind the reads: what the next
+        // pass computes hides their latency
+        asm volatile("" ::: "memory");
+        u32x4 q[STEPS];
+        uint32_t row_off[STEPS];
+#pragma unroll
+        for (int it = 0; it < STEPS; ++it) {
+            const int r = it * RPI + lane / CH;
+            const u32x4 v = *reinterpret_cast<const u32x4*>(region + r * (CH * 16) + ((lane % CH) ^ ((r / (16 / CH)) % CH)) * 16);
+            q[it] = it >= STEPS / 2 ? u32x4{v.z, v.w, v.x, v.y} : v;
+            const int gr = first_row + p / PER_ROW * 32 + r;
+            const int mr = GATHER ? rel[min(gr, nrows - 1)] : gr;
+            row_off[it] = gr < nrows ? (uint32_t)mr * (uint32_t)ldc * 2u + (uint32_t)(lane % CH) * 16u : 0xFFFFFF00u;   // else past the end of dst: not stored
         }
-}
-template <int EPI, int MI, int NJ, bool GATHER>
-__device__ __forceinline__ void flush_rows_impl(int i_lo, int i_hi, const unsigned char* lds, int row0, int nrows,
-                                                const int32_t* __restrict__ rel, int n0, int N, uint16_t* __restrict__ C, int ldc) {
-    using G = EpiGeom<EPI, MI, NJ>;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const unsigned char* region = lds + wave * (G::ROWS * G::PITCH);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");     // a wave reads back only what it wrote itself
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    constexpr int LPR = G::NW * 2 / 16;            // lanes per output row (16 bytes each)
-    constexpr int RPI = 64 / LPR;                  // rows per store instruction
-    const int sub_r = lane / LPR, sub_c = lane % LPR;
-    const int col = n0 + wn * G::NW + sub_c * 8;
-#pragma unroll 4
-    for (int it = i_lo * 32 / RPI; it < i_hi * 32 / RPI; ++it) {
-        const int r = it * RPI + sub_r;            // row inside this wave's rows
-        const unsigned char* src = region + r * G::PITCH + sub_c * 16;
-        const u32x2 lo = *reinterpret_cast<const u32x2*>(src);
-        const u32x2 hi = *reinterpret_cast<const u32x2*>(src + 8);
-        const int gr = wm * G::ROWS + r;
-        if (gr < nrows && col < N) {
-            const u32x4 q = {lo.x, lo.y, hi.x, hi.y};
-            const int orow = row0 + (GATHER ? rel[gr] : gr);   // gathered tile: its rows are not consecutive
-            *reinterpret_cast<u32x4*>(C + (size_t)orow * ldc + col) = q;
-        }
+        asm volatile("" ::: "memory");
+        if (p + 1 < MI * PER_ROW) write(p + 1);
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int it = 0; it < STEPS; ++it)
+            __builtin_amdgcn_raw_buffer_store_b128(q[it], dst, row_off[it] + p % PER_ROW * JP * 64, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
     }
-}
-// two copies of the store loop: the common one keeps its plain row arithmetic
-template <int EPI, int MI, int NJ>
-__device__ __forceinline__ void flush_rows(int i_lo, int i_hi, const unsigned char* lds, int row0, int nrows,
-                                           const int32_t* __restrict__ rel, int n0, int N, uint16_t* __restrict__ C, int ldc) {
-    if (rel) flush_rows_impl<EPI, MI, NJ, true>(i_lo, i_hi, lds, row0, nrows, rel, n0, N, C, ldc);
-    else flush_rows_impl<EPI, MI, NJ, false>(i_lo, i_hi, lds, row0, nrows, rel, n0, N, C, ldc);
 }
 
 // The pieces of a tile that is cut along K.  Every piece writes its fp32 accumulators; at 128 x 128 (and in the
@@ -956,50 +963,52 @@ __device__ __forceinline__ void sum_pieces(int unit_lo, int unit_hi, const float
 // come a whole k-tile apart cost about twice the L2 bandwidth.  The pair (kt+4, kt+5) is issued
 // in iteration kt (kt even) and first needed 2.5 iterations later.
 // The MFMAs are issued as D = B . A^T (operands swapped), so a lane ends up with 4 consecutive
-// output COLUMNS of one row: the epilogue packs them to 8 bytes, transposes through LDS and
-// writes whole 128-byte lines.
+// output COLUMNS of one row (see store_rows).
+//
+// A block walks through several tiles, and the pipeline runs across them: the loads that go out in a tile's last two
+// trips are the next tile's first k-tiles (its addresses are prepared during the epilogue before), and the last
+// fragment reads are its first fragments.  So a tile costs its loop and its epilogue; with a block per tile each also
+// paid 3.4 us from the block's start to its first operands and 1.3 us of launch.  Per 256 x 256 tile at K = 1408: 41.6
+// -> 39.5 us, at K = 2048 SwiGLU 54.6 -> 53; 612329 rows of 2048 -> 1408 -> 2048 with shared experts, the whole share:
+// 9.33 -> 9.13 ms; 10199 rows of 1024 -> 4096 -> 1024 238 -> 233 us; two models at once 1.75 -> 1.70 ms.  (A tile whose
+// loop is long is bound by power instead: K = 14336 is unchanged.)
 //
 // TIMED (diagnostics, moe_diag_ffn_phases): the same kernel with the 100 MHz wall clock read by lane 0 of every wave
-// into marks[block][wave][4]: 0 start, 1 first operands in LDS (loop about to start), 2 loop done, 3 end.  The
-// ordinary instantiation contains none of it.
+// into marks[item][wave][4]: 0 start, 1 first operands in LDS (loop about to start), 2 loop done, 3 end; an item is a
+// tile or a piece of one.  The ordinary instantiation contains none of it.
+struct WorkItem {
+    int tile_id, piece;      // piece < 0: the whole K range
+    int nk;                  // k-tiles (even: K is a multiple of 64)
+    int row0, nrows, n0;     // output rows and first output column
+    const int32_t* rel;      // row offsets of a gathered tile, else NULL
+};
 template <int EPI, int MI, int NJ, bool TIMED>
 __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_kernel(const uint16_t* __restrict__ A, int lda, TileMap m,
                                                            ExpertTable tab, int which0, int which1, int N, int K,
                                                            uint16_t* __restrict__ C, int ldc, int tiles_n, int ncu, int most_tail,
                                                            float* partial, long long* __restrict__ marks,
-                                                           uint32_t mark_blocks) {
+                                                           uint32_t mark_items) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
 #define MOE_MARK(i)                                                                                                 \
     do {                                                                                                            \
-        if (TIMED && blockIdx.x < mark_blocks && (threadIdx.x & 63) == 0)                                           \
-            marks[((size_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 4 + (i)] = (long long)wall_clock64();              \
+        if (TIMED && (uint32_t)item < mark_items && (threadIdx.x & 63) == 0)                                        \
+            marks[((size_t)item * 4 + (threadIdx.x >> 6)) * 4 + (i)] = (long long)wall_clock64();                    \
     } while (0)
+    int item = blockIdx.x;
     MOE_MARK(0);
     using TG = TileGeom<MI, NJ>;
-    constexpr int NOUT = EpiGeom<EPI, MI, NJ>::NOUT;                       // output columns per block
-    const int n_tiles_m = *m.n_tiles;
+    using EG = EpiGeom<EPI, MI, NJ>;
+    constexpr int NOUT = EG::NOUT;                                          // output columns per block
+    const int n_tiles_m = *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(m.n_tiles));
     const int total = n_tiles_m * tiles_n;
-    const TailPlan plan = plan_tail_upto(most_tail, total, ncu, K / BK);
-    int tile_id = blockIdx.x, piece = -1;                                   // piece < 0: the whole K range
-    if ((int)blockIdx.x >= plan.n_full) {
-        const int j = blockIdx.x - plan.n_full;
-        if (j >= plan.n_tail * plan.parts) return;
-        tile_id = plan.n_full + j % plan.n_tail;
-        piece = j / plan.n_tail;
-    }
-    int tile_m, tile_n;
-    tile_of_block(tile_id, total, n_tiles_m, tiles_n, &tile_m, &tile_n);
-    // everything read from the tile map is the same for the whole block: keep it in scalar registers
-    const int row0 = __builtin_amdgcn_readfirstlane(m.row0[tile_m]);
-    const int nrows = __builtin_amdgcn_readfirstlane(m.nrows[tile_m]);
-    const int ex = __builtin_amdgcn_readfirstlane(m.expert[tile_m]);
-    const int32_t* rel = __builtin_amdgcn_readfirstlane(m.gather[tile_m]) ? m.rel + (size_t)tile_m * kRelPitch : nullptr;
-    auto pick = [&](int which) -> const uint16_t* {
-        return reinterpret_cast<const uint16_t*>(which == 0 ? tab.w1[ex] : which == 1 ? tab.w_up[ex] : tab.w_down[ex]);
-    };
-    const uint16_t* B0 = pick(which0);
-    const uint16_t* B1 = (EPI == EPI_SWIGLU) ? pick(which1) : B0;
-    const int n0 = tile_n * NOUT;
+    TailPlan plan = plan_tail_upto(most_tail, total, ncu, K / BK);
+    // the same for all blocks; the compiler does not see it through the divisions
+    plan.n_full = __builtin_amdgcn_readfirstlane(plan.n_full);
+    plan.n_tail = __builtin_amdgcn_readfirstlane(plan.n_tail);
+    plan.parts = __builtin_amdgcn_readfirstlane(plan.parts);
+    plan.pairs_per = __builtin_amdgcn_readfirstlane(plan.pairs_per);
+    const int n_items = plan.n_full + (plan.parts > 1 ? plan.n_tail * plan.parts : 0);
+    if (item >= n_items) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform by construction; tell the compiler
@@ -1009,52 +1018,81 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     // fills blocks w, w+4, ...: MI of A and NJ of B per stage.  Addresses are kept as a wave-uniform
     // 64-bit base (advanced with k by scalar adds) plus a fixed 32-bit byte offset per lane, so a
     // load costs no vector address arithmetic.
-    int lr, lc;
-    rc_of_slot(lane, &lr, &lc);
-    // k-tiles [kt_lo, kt_lo + nk) of the row: everything for a whole tile, one piece for a tail tile
-    const int kt_lo = (piece < 0) ? 0 : piece * plan.pairs_per * 2;
-    const int nk = (piece < 0) ? K / BK : min(plan.pairs_per * 2, K / BK - kt_lo);   // even: K is a multiple of 64
-    const char* a_base = reinterpret_cast<const char*>(A + (size_t)row0 * lda) + (size_t)kt_lo * BK * 2;
-    const char* b_base[NJ];
-    uint32_t a_voff[MI], b_voff[NJ];
-    int a_row[MI];                                           // row (relative to row0) of the tile rows this lane fetches
-#pragma unroll
-    for (int i = 0; i < MI; ++i) a_row[i] = min((wave + 4 * i) * 16 + lr, nrows - 1);
-    if (rel) {                                               // gathered tile: offsets from row0, below 2^32 bytes (checked
-        int t[MI];                                           // on the host); the loads go out together
-#pragma unroll
-        for (int i = 0; i < MI; ++i) t[i] = rel[a_row[i]];
-#pragma unroll
-        for (int i = 0; i < MI; ++i) a_row[i] = t[i];
-    }
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-        a_voff[i] = (uint32_t)a_row[i] * (uint32_t)lda * 2u + (uint32_t)lc * 16u;
-        asm volatile("" : "+v"(a_voff[i]));                  // (see below)
-    }
-#pragma unroll
-    for (int i = 0; i < NJ; ++i) {
-        const int blk = wave + 4 * i;                        // 16-row block of the tile (wave-uniform)
-        const int r = blk * 16 + lr;                         // tile row this lane fetches
-        int col;
-        if (EPI == EPI_SWIGLU) {
-            constexpr int WB = 32 * NJ;                      // weight rows per wave-column, the first half gate, the second up
-            const int w = r / WB, sub = r % WB;
-            b_base[i] = reinterpret_cast<const char*>(((blk * 16) & (WB / 2)) ? B1 : B0) + (size_t)kt_lo * BK * 2;   // sub >= WB / 2 for the whole block or not at all
-            col = n0 + w * (WB / 2) + sub % (WB / 2);
-        } else {
-            b_base[i] = reinterpret_cast<const char*>(B0) + (size_t)kt_lo * BK * 2;
-            col = n0 + r;
+    struct Source { const char *a, *b0, *b1; uint32_t a_voff[MI], b_voff[NJ]; };
+    // in two parts, so that the loads of the first are under way during an epilogue
+    auto describe = [&](int id, WorkItem& w, Source& src, int (&a_row)[MI]) {
+        int lr, lc, ln = lane;
+        asm volatile("" : "+v"(ln));                         // (opaque: not worth registers during the loop)
+        rc_of_slot(ln, &lr, &lc);
+        w.tile_id = id;
+        w.piece = -1;
+        int kt_lo = 0;
+        w.nk = K / BK;
+        if (id >= plan.n_full) {
+            const int j = id - plan.n_full;
+            w.tile_id = plan.n_full + j % plan.n_tail;
+            w.piece = j / plan.n_tail;
+            kt_lo = w.piece * plan.pairs_per * 2;
+            w.nk = min(plan.pairs_per * 2, K / BK - kt_lo);
         }
-        b_voff[i] = (uint32_t)min(col, N - 1) * (uint32_t)K * 2u + (uint32_t)lc * 16u;
-        // opaque to the optimiser from here on: it must stay a 32-bit lane offset next to a scalar base
-        asm volatile("" : "+v"(b_voff[i]));
-    }
+        int tile_m, tile_n;
+        tile_of_block(w.tile_id, total, n_tiles_m, tiles_n, &tile_m, &tile_n);
+        tile_m = __builtin_amdgcn_readfirstlane(tile_m);
+        // the same for the whole block, written by an earlier kernel: scalar loads, which do not queue behind the operands
+        auto rec = [&](const int32_t* p) { return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p))[tile_m]; };
+        w.row0 = rec(m.row0);
+        w.nrows = rec(m.nrows);
+        const int ex = rec(m.expert);
+        w.rel = rec(m.gather) ? m.rel + (size_t)tile_m * kRelPitch : nullptr;
+        w.n0 = __builtin_amdgcn_readfirstlane(tile_n * NOUT);
+        auto pick = [&](int which) -> const char* {
+            return reinterpret_cast<const char*>(which == 0 ? tab.w1[ex] : which == 1 ? tab.w_up[ex] : tab.w_down[ex]) + (size_t)kt_lo * BK * 2;
+        };
+        src.b0 = pick(which0);
+        src.b1 = (EPI == EPI_SWIGLU) ? pick(which1) : src.b0;
+        // SwiGLU: the second half of a wave-column's 2 NJ 16-row blocks are up rows; this wave fetches blocks wave + 4 i
+        if (NJ == 2 && (wave & 2)) src.b0 = src.b1;
+        src.a = reinterpret_cast<const char*>(A + (size_t)w.row0 * lda) + (size_t)kt_lo * BK * 2;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) a_row[i] = min((wave + 4 * i) * 16 + lr, w.nrows - 1);   // row (relative to row0) of the tile rows this lane fetches
+        if (w.rel) {                                         // gathered tile: offsets from row0, below 2^32 bytes (checked
+            int t[MI];                                       // on the host); the loads go out together
+#pragma unroll
+            for (int i = 0; i < MI; ++i) t[i] = w.rel[a_row[i]];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) a_row[i] = t[i];
+        }
+    };
+    auto describe_lanes = [&](const WorkItem& w, Source& src, const int (&a_row)[MI]) {
+        int lr, lc, ln = lane;
+        asm volatile("" : "+v"(ln));
+        rc_of_slot(ln, &lr, &lc);
+#pragma unroll
+        for (int i = 0; i < MI; ++i) src.a_voff[i] = (uint32_t)a_row[i] * (uint32_t)lda * 2u + (uint32_t)lc * 16u;
+#pragma unroll
+        for (int i = 0; i < NJ; ++i) {
+            const int r = (wave + 4 * i) * 16 + lr;          // tile row this lane fetches
+            int col = w.n0 + r;
+            if (EPI == EPI_SWIGLU) {
+                constexpr int WB = 32 * NJ;                  // weight rows per wave-column, the first half gate, the second up
+                col = w.n0 + r / WB * (WB / 2) + r % (WB / 2);
+            }
+            src.b_voff[i] = (uint32_t)min(col, N - 1) * (uint32_t)K * 2u + (uint32_t)lc * 16u;
+        }
+        // opaque to the optimiser from here on: these must stay 32-bit lane offsets next to scalar bases
+#pragma unroll
+        for (int i = 0; i < MI; ++i) asm volatile("" : "+v"(src.a_voff[i]));
+#pragma unroll
+        for (int i = 0; i < NJ; ++i) asm volatile("" : "+v"(src.b_voff[i]));
+    };
+    WorkItem cur, next;
+    Source src, src_next;
+    int t_first = 0, t_last = 0;                             // loads: the k-tile number at which `src` starts, and the last pair it has
     // The loads of k-tiles t and t+1 (t even) into the stages at LDS byte offsets so0 and so1, items [i_lo, i_hi): the
-    // MI + NJ 16-row blocks this wave fetches, A and B in turn, each for both k-tiles.  Past the end the last pair is
-    // fetched again (into stages nobody reads any more) so that the count of outstanding loads stays uniform.
+    // MI + NJ 16-row blocks this wave fetches, A and B in turn, each for both k-tiles.  Past the end of the last tile its
+    // last pair is fetched again (into stages nobody reads any more) so that the count of outstanding loads stays uniform.
     auto issue_part = [&](int t, int so0, int so1, int i_lo, int i_hi) {
-        t = min(t, nk - 2);
+        t = min(t - t_first, t_last);
         unsigned char* s0 = lds + so0;
         unsigned char* s1 = lds + so1;
         const size_t kb = (size_t)t * BK * 2;                // byte offset of k-tile t inside a row
@@ -1065,8 +1103,9 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
             const bool is_a = it < 2 * MI && (it & 1) == 0;
             const int i = it < 2 * MI ? it >> 1 : it - MI;
             const int blk = (wave + 4 * i) * 1024 + (is_a ? 0 : TG::A_BYTES);
-            const char* p = (is_a ? a_base : b_base[i]) + kb;
-            uint32_t& v = is_a ? a_voff[i] : b_voff[i];
+            const char* b = (EPI == EPI_SWIGLU && (i & (NJ / 4))) ? src.b1 : src.b0;
+            const char* p = (is_a ? src.a : b) + kb;
+            uint32_t& v = is_a ? src.a_voff[i] : src.b_voff[i];
             // opaque here, so that scalar base + zero-extended 32-bit lane offset is still visible when the
             // load is selected (saddr form: half the address registers, no 64-bit vector add per load)
             const char* p1 = p + BK * 2;
@@ -1079,17 +1118,6 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     constexpr int LAST = MI + NJ - 3 * GI;
     static_assert(LAST >= 1, "");
 
-    f32x16 acc[MI][NJ];                                      // [m-tile i][n-tile j], holds D^T: rows n, columns m
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-    issue_part(0, 0, TG::STAGE, 0, 4 * GI);
-    issue_part(2, 2 * TG::STAGE, 3 * TG::STAGE, 0, 3 * GI);  // its last group goes out in the first trip below
-
     const int fr = lane & 31, fk = lane >> 5;      // fragment row within a 32-row tile, which k-half
     int a_off[2], b_off[2];                        // byte offsets inside a stage of 32-row tile 0, per k-step;
 #pragma unroll                                     // tile i lies 2 KB further (two 16-row blocks)
@@ -1097,7 +1125,7 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
         a_off[s] = tile_off(wm * 32 * MI + fr, 2 * s + fk);
         b_off[s] = TG::A_BYTES + tile_off(wn * 32 * NJ + fr, 2 * s + fk);
     }
-
+    f32x16 acc[MI][NJ];                                      // [m-tile i][n-tile j], holds D^T: rows n, columns m
     auto load_frags = [&](bf16x8 (&af)[MI], bf16x8 (&bfr)[NJ], const unsigned char* st, int s) {
         const unsigned char* pa = st + a_off[s];
         const unsigned char* pb = st + b_off[s];
@@ -1106,12 +1134,15 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
 #pragma unroll
         for (int j = 0; j < NJ; ++j) bfr[j] = *reinterpret_cast<const bf16x8*>(pb + j * 2048);
     };
-    auto mma = [&](const bf16x8 (&af)[MI], const bf16x8 (&bfr)[NJ]) {
+    auto mma = [&](const bf16x8 (&af)[MI], const bf16x8 (&bfr)[NJ], auto from_zero) {
+        f32x16 zero;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) zero[e] = 0.f;
 #pragma unroll
         for (int i = 0; i < MI; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], decltype(from_zero)::value ? zero : acc[i][j], 0, 0, 0);
     };
 
     // Software pipeline, two k-tiles per trip, four phases of MI x NJ MFMAs each:
@@ -1125,11 +1156,6 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     // loads are spread evenly, at 4 x 4 one per four MFMAs: a CU sustains roughly one wave-load per 40 clocks
     // when the lines come from HBM, and a load that cannot be accepted stalls the wave's MFMA issue too.
     // A bare s_barrier is used: __syncthreads() would add a fence that waits for ALL outstanding loads.
-    bf16x8 a0[MI], b0[NJ], a1[MI], b1[NJ];
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (6 * GI)); // vmcnt(three groups): pair (0, 1) is in LDS
-    __builtin_amdgcn_s_barrier();
-    MOE_MARK(1);
-    load_frags(a0, b0, lds, 0);
 #define MOE_PHASE_SCHED()                                                                      \
     if (MI * NJ == 12) {                                                                       \
     _Pragma("unroll") for (int q = 0; q < 7; ++q) {   /* (MFMA, LDS read) x 7 */                \
@@ -1163,63 +1189,120 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     int so[STAGES];
 #pragma unroll
     for (int j = 0; j < STAGES; ++j) so[j] = j * TG::STAGE;
-    for (int kt = 0; kt < nk; kt += 2) {
+    bf16x8 a0[MI], b0[NJ], a1[MI], b1[NJ];
+
+    int a_row[MI];
+    describe(item, cur, src, a_row);
+    describe_lanes(cur, src, a_row);
+    t_last = cur.nk - 2;
+    issue_part(0, so[0], so[1], 0, 4 * GI);
+    issue_part(2, so[2], so[3], 0, 3 * GI);        // its last group goes out in the first trip below
+    bool more = item + ncu < n_items;
+    if (more) {
+        describe(item + ncu, next, src_next, a_row);
+        describe_lanes(next, src_next, a_row);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (6 * GI)); // vmcnt(three groups): pair (0, 1) is in LDS
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    load_frags(a0, b0, lds + so[0], 0);
+    // One trip.  FIRST: of a tile (the products start from zero); SWITCH: the loads of this tile end with phase A, those
+    // of the next one follow.
+    auto trip = [&](int kt, auto first, auto switches) {
+        constexpr bool FIRST = decltype(first)::value, SWITCH = decltype(switches)::value;
         __builtin_amdgcn_sched_barrier(0);
         load_frags(a1, b1, lds + so[0], 1);
         issue_part(kt + 2, so[2], so[3], 3 * GI, 4 * GI);
-        mma(a0, b0);
+        mma(a0, b0, first);
         MOE_PHASE_SCHED()
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
+        if ((SWITCH || (FIRST && cur.nk == 4)) && more) { src = src_next; t_first = cur.nk; t_last = next.nk - 2; }
         load_frags(a0, b0, lds + so[1], 0);
         issue_part(kt + 4, so[4], so[0], 0, GI);
-        mma(a1, b1);
+        mma(a1, b1, std::false_type{});
         MOE_PHASE_SCHED()
         __builtin_amdgcn_sched_barrier(0);
         load_frags(a1, b1, lds + so[1], 1);
         issue_part(kt + 4, so[4], so[0], GI, 2 * GI);
-        mma(a0, b0);
+        mma(a0, b0, std::false_type{});
         MOE_PHASE_SCHED()
         __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0x0F70 | (4 * GI));   // only groups 0 and 1 of the next pair may be outstanding
+        __builtin_amdgcn_s_waitcnt(0x0F70 | (4 * GI));       // only groups 0 and 1 of the next pair may be outstanding
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         load_frags(a0, b0, lds + so[2], 0);
         issue_part(kt + 4, so[4], so[0], 2 * GI, 3 * GI);
-        mma(a1, b1);
+        mma(a1, b1, std::false_type{});
         MOE_PHASE_SCHED()
         __builtin_amdgcn_sched_barrier(0);
         const int t0 = so[0], t1 = so[1];
         so[0] = so[2]; so[1] = so[3]; so[2] = so[4]; so[3] = t0; so[4] = t1;
+    };
+    while (true) {
+        MOE_MARK(1);
+        trip(0, std::true_type{}, std::false_type{});
+        if (cur.nk > 2) {                                    // (a tile that another one follows is whole: at least four k-tiles)
+            int kt = 2;
+            for (; kt < cur.nk - 4; kt += 2) trip(kt, std::false_type{}, std::false_type{});
+            if (cur.nk > 4) {
+                trip(kt, std::false_type{}, std::true_type{});
+                kt += 2;
+            }
+            trip(kt, std::false_type{}, std::false_type{});
+        }
+        if (TG::PER_CU == 1) {                               // the accumulators stay where they are until they are stored
+            asm volatile("s_nop 15\n\ts_nop 15");            // the last product has left the matrix core before read_acc
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) asm volatile("" : "+a"(acc[i][j]));
+        }
+        MOE_MARK(2);
+        if (cur.piece >= 0) break;                           // the last item of its block: a round holds all pieces
+        const WorkItem done = cur;
+        const bool had_next = more;
+        if (more) {
+            cur = next;
+            t_first = 0;
+            more = item + 2 * ncu < n_items;
+            if (more) describe(item + 2 * ncu, next, src_next, a_row);
+        }
+        const int col0 = __builtin_amdgcn_readfirstlane(done.n0 + wn * EG::NW);
+        if (col0 < N) {                                      // N is a multiple of 128: all columns of the wave or none
+            const __amdgpu_buffer_rsrc_t dst = __builtin_amdgcn_make_buffer_rsrc(C + (size_t)__builtin_amdgcn_readfirstlane(done.row0) * ldc + col0, 0, 0xFFFFFF00u, 0x00027000);
+            unsigned char* region = lds + so[4] + wave * (TG::STAGE / 4);   // the only stage that no load is on its way to
+            // two copies: the common one keeps its plain row arithmetic
+            if (done.rel) store_tile<EPI, MI, NJ, TG::PER_CU == 1, true>(acc, lane, region, dst, wm * EG::ROWS, done.nrows, done.rel, ldc);
+            else store_tile<EPI, MI, NJ, TG::PER_CU == 1, false>(acc, lane, region, dst, wm * EG::ROWS, done.nrows, nullptr, ldc);
+        }
+        if (more) describe_lanes(next, src_next, a_row);
+        MOE_MARK(3);
+        if (!had_next) {
+            __builtin_amdgcn_s_waitcnt(0x0070);              // no load may still target LDS when the block ends
+            return;
+        }
+        item += ncu;
+        MOE_MARK(0);
     }
 #undef MOE_PHASE_SCHED
-    // no load may still target LDS, and no wave may still read operands, when LDS is reused below
-    __builtin_amdgcn_s_waitcnt(0x0070);            // vmcnt(0) lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-    MOE_MARK(2);
-
-    if (piece >= 0) {
-        // a piece of a tail tile: the raw accumulators, 16 bytes per lane and store (whole 4 KB per store)
-        float* pieces = partial + (size_t)(tile_id - plan.n_full) * plan.parts * (TG::PARTIAL / 4);   // of this tile
-        const __amdgpu_buffer_rsrc_t dst = pieces_rsrc(pieces, (uint32_t)(plan.parts * TG::PARTIAL));
+    // a piece of a tail tile: the raw accumulators, 16 bytes per lane and store (whole 4 KB per store)
+    __builtin_amdgcn_s_waitcnt(0x0070);                      // vmcnt(0) lgkmcnt(0): no load may still target LDS below
+    const int tail = __builtin_amdgcn_readfirstlane(cur.tile_id - plan.n_full), piece = __builtin_amdgcn_readfirstlane(cur.piece);
+    float* pieces = partial + (size_t)tail * plan.parts * (TG::PARTIAL / 4);   // of this tile
+    const __amdgpu_buffer_rsrc_t dst = pieces_rsrc(pieces, (uint32_t)(plan.parts * TG::PARTIAL));
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-            for (int j = 0; j < NJ; ++j)
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                    store_piece(dst, piece * (int)(TG::PARTIAL / 16) + ((i * NJ + j) * 4 + q) * 256 + tid, v);
-                }
-        if (TG::SUM_IN_PLACE && last_piece(m.done + (tile_id - plan.n_full), plan.parts, reinterpret_cast<int*>(lds)))
-            sum_pieces<EPI, MI, NJ>(0, MI * EpiGeom<EPI, MI, NJ>::NJO, pieces, plan.parts, row0, nrows, rel, n0, N, C, ldc);
-        MOE_MARK(3);
-        return;
-    }
-#pragma unroll
-    for (int i = 0; i < MI; ++i) stage_rows<EPI, MI, NJ>(acc[i], i, lds);
-    flush_rows<EPI, MI, NJ>(0, MI, lds, row0, nrows, rel, n0, N, C, ldc);
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                store_piece(dst, piece * (int)(TG::PARTIAL / 16) + ((i * NJ + j) * 4 + q) * 256 + tid, v);
+            }
+    if (TG::SUM_IN_PLACE && last_piece(m.done + tail, plan.parts, reinterpret_cast<int*>(lds)))
+        sum_pieces<EPI, MI, NJ>(0, MI * EG::NJO, pieces, plan.parts, cur.row0, cur.nrows, cur.rel, cur.n0, N, C, ldc);
     MOE_MARK(3);
 #undef MOE_MARK
 }
@@ -1485,7 +1568,6 @@ int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab
     using TG = TileGeom<MI, NJ>;
     using G = EpiGeom<EPI, MI, NJ>;
     const int tiles_n = (N + G::NOUT - 1) / G::NOUT;
-    const int max_tiles_m = max_tiles_of(R, TG::BM, nseg);
     const int ncu = round_size() * TG::PER_CU;             // tiles per round of the grid
     static bool attr_done = false;
     if (!attr_done) {
@@ -1493,7 +1575,8 @@ int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab
                                     hipFuncAttributeMaxDynamicSharedMemorySize, TG::LDS));
         attr_done = true;
     }
-    // whole tiles first, then at most ncu pieces of tail tiles; blocks past the real tile count exit at once
+    // one block per place: it walks through the tiles and pieces blockIdx, blockIdx + ncu, ... (the count is known on the
+    // device), the pieces last
     if (TIMED) {
         const int out44 = EpiGeom<EPI, 4, 4>::NOUT;
         const size_t need = ((size_t)max_tiles_of(R, TileGeom<4, 4>::BM, nseg) * ((N + out44 - 1) / out44) + round_size()) * 16;
@@ -1505,7 +1588,7 @@ int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab
     if (!TG::SUM_IN_PLACE || m.done)
         for (int t = (R + TG::BM - 1) / TG::BM, hi = (R + n_used * (TG::BM - 1)) / TG::BM; t <= hi; ++t)
             most_tail = std::max(most_tail, plan_tail(t * tiles_n, ncu, K / BK).n_tail);
-    hipLaunchKernelGGL((gemm_bf16_kernel<EPI, MI, NJ, TIMED>), dim3(max_tiles_m * tiles_n + ncu), dim3(256), TG::LDS, st,
+    hipLaunchKernelGGL((gemm_bf16_kernel<EPI, MI, NJ, TIMED>), dim3(ncu), dim3(256), TG::LDS, st,
                        reinterpret_cast<const uint16_t*>(A), lda, m, tab, which0, which1, N, K,
                        reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, most_tail, partial, marks,
                        (uint32_t)std::min<size_t>(marks_len / 16, 0xFFFFFFFFu));
@@ -1531,7 +1614,8 @@ int launch_bf16_shape(TileShape t, const void* A, int lda, const TileMap& m, con
 
 // Which tiles a bf16 GEMM takes.  The number of tiles is only known on the device, so the choice is made from an
 // estimate of it: half a tile of padding per expert.  Every shape's time is modelled as rounds of the grid, a round
-// costing a + b * (k-tiles of 32), and a tail as plan_tail cuts it; the shape with the least time is taken.  The
+// costing a + b * (k-tiles of 32), and a tail as plan_tail cuts it; the first round of the large shapes starts cold; the
+// shape with the least time is taken.  The
 // constants (microseconds) are from GEMMs of K = 1024 ... 14336 with whole rounds: 256 x 256 100 us per round at
 // K = 4096, 37 at 1024; 192 x 256 80 us at 4096; 128 x 128, two blocks per CU, 66 us at 4096 and 36 at 2048, and
 // about two thirds of that when the round has one block per CU.  So 256 x 256 is the best rate (1.35 PFLOP/s against
@@ -1545,8 +1629,8 @@ inline double estimated_tiles_m(int R, int bm, int n_used) {
     return std::max((double)n_used, (double)R / bm + 0.5 * n_used);
 }
 double modelled_us(TileShape t, int R, int n_used, int N, int K, int act, int cus) {
-    struct Cost { double a, b, a1, b1, piece; };           // round, round of at most one block per CU, pass over a partial tile
-    static const Cost cost[] = {{6.5, 0.467, 6.0, 0.33, 0.026}, {7.6, 0.565, 7.6, 0.565, 0.079}, {9.6, 0.71, 9.6, 0.71, 0.105}};
+    struct Cost { double first, a, b, a1, b1, piece; };    // start, round, round of at most one block per CU, pass over a partial tile
+    static const Cost cost[] = {{0.0, 6.5, 0.467, 6.0, 0.33, 0.026}, {3.0, 4.6, 0.565, 4.6, 0.565, 0.079}, {3.0, 6.6, 0.71, 6.6, 0.71, 0.105}};
     Cost c = cost[t];
     if (act == MOE_ACT_GELU_MLP) c.a += (t == TS_128) ? 1.0 : 4.0;   // its exp2 and rcp of twice SwiGLU's columns, hidden where two blocks share a CU
     const int per_cu = (t == TS_128) ? TileGeom<2, 2>::PER_CU : 1, slots = cus * per_cu;
@@ -1554,7 +1638,7 @@ double modelled_us(TileShape t, int R, int n_used, int N, int K, int act, int cu
     const int tiles = (int)(estimated_tiles_m(R, kShapeRows[t], n_used) * ((N + out_cols - 1) / out_cols) + 0.5);
     const TailPlan p = plan_tail(tiles, slots, K / BK);
     const int rest = p.n_full % slots;                     // tiles of a last round that is not cut
-    double us = (double)(p.n_full / slots) * (c.a + c.b * (K / BK));
+    double us = c.first + (double)(p.n_full / slots) * (c.a + c.b * (K / BK));
     if (rest > 0) us += (rest <= cus) ? c.a1 + c.b1 * (K / BK) : c.a + c.b * (K / BK);
     if (p.n_tail > 0) {
         const int pieces = p.n_tail * p.parts;

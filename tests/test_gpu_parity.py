@@ -540,6 +540,15 @@ def test_expert_ffn_tile_heights(H, R, Hd, F, n_local, nseg, act, rows):
     H.assert_close(H.host(out), O.expert_ffn(recv, off, exp, experts, act), "bf16")
 
 
+# Several tiles per block: the pipeline runs from one tile into the next.  K of four k-tiles (the first trip of a tile is
+# the one before its last), gathered rows and ragged last tiles in every position, N of half a tile, pieces behind whole tiles.
+@pytest.mark.parametrize("R,Hd,F,n_local,nseg,act,rows", [(9001, 128, 3200, 3, 40, 2, (192, 128)), (17000, 1152, 128, 5, 20, 0, (128, 192)),
+                                                          (70000, 128, 256, 2, 9, 1, (192, 128)), (2217, 512, 5248, 2, 7, 2, (256, 128)),
+                                                          (5623, 512, 2176, 2, 2, 2, (256, 128))])
+def test_expert_ffn_blocks_walk_through_tiles(H, R, Hd, F, n_local, nseg, act, rows):
+    test_expert_ffn_tile_heights(H, R, Hd, F, n_local, nseg, act, rows)
+
+
 # fp32 tiles of 64 x 64: one row past a tile, a K that is no multiple of the 32-wide k-tile, gathered tiles, N below a tile
 @pytest.mark.parametrize("act,R,Hd,F,n_local,nseg", [(2, 65, 100, 68, 1, 1), (0, 129, 36, 260, 2, 9), (1, 64, 4, 4, 1, 1), (2, 300, 128, 96, 3, 64)])
 def test_expert_ffn_fp32_tiles(H, act, R, Hd, F, n_local, nseg):
