@@ -315,11 +315,11 @@ def aurora_order(D, B=None):
         nr = s.n_rounds
         out = {
             "n": n, "n_rounds": nr,
-            "duration": np.array([s.duration[r] for r in range(nr)], dtype=np.float64),
-            "dst": np.array([s.dst[i] for i in range(nr * n)], dtype=np.int32).reshape(nr, n),
-            "dest_order": np.array([s.dest_order[i] for i in range(n * n)], dtype=np.int32).reshape(n, n),
-            "alg1_order": np.array([s.alg1_order[i] for i in range(n * n)], dtype=np.int32).reshape(n, n),
-            "start": np.array([s.start[i] for i in range(n * n)], dtype=np.float64).reshape(n, n),
+            "duration": np.ctypeslib.as_array(s.duration, (nr,)).copy(),
+            "dst": np.ctypeslib.as_array(s.dst, (nr, n)).copy(),
+            "dest_order": np.ctypeslib.as_array(s.dest_order, (n, n)).copy(),
+            "alg1_order": np.ctypeslib.as_array(s.alg1_order, (n, n)).copy(),
+            "start": np.ctypeslib.as_array(s.start, (n, n)).copy(),
             "bmax": s.bmax, "port_bound": s.port_bound, "makespan_rounds": s.makespan_rounds,
             "makespan_order": s.makespan_order, "order_time": s.order_time,
             "candidate_time": [s.candidate_time[c] for c in range(4)], "order_source": s.order_source,

@@ -395,3 +395,24 @@ def test_skinny_plan_and_row_geometry_self_checks():
         assert lib.moe_selfcheck_row_geometry(row16, k, out) == 0
         assert (out[0], out[2]) == (tpw, pieces), (row16, k, list(out))
     assert lib.moe_selfcheck_row_geometry(0, 2, out) < 0 and lib.moe_selfcheck_row_geometry(64, 17, out) < 0
+
+
+@pytest.mark.parametrize("n,hi,hetero", [(2, 9, False), (5, 3, True), (7, 40, False), (16, 200, True), (17, 5, False), (33, 1000, True)])
+def test_send_order_time_is_that_of_playing_the_order_and_no_exchange_improves_it(n, hi, hetero):
+    """The hill climbing resumes recorded runs; playing the order it returns from the start gives the same time to the
+    bit, and while its budget of 64 n tries lasts it ends where no exchange of neighbouring flows gains more than 1e-9."""
+    r = np.random.default_rng(100 * n + hi)
+    for _ in range(3):
+        D = random_D(r, n, hi)
+        np.fill_diagonal(D, 0)
+        B = r.uniform(0.3, 1.0, size=n) if hetero else None
+        p = P.aurora_order(D, B)
+        assert P.aurora_simulate(D, B, p["dest_order"]) == p["order_time"]
+        tries = sum(max(0, int((D[i] > 0).sum()) - 1) for i in range(n))
+        if tries > 12 * n:                                       # several sweeps might not fit into the budget
+            continue
+        for i in range(n):
+            for q in range(int((D[i] > 0).sum()) - 1):
+                o = p["dest_order"].copy()
+                o[i, [q, q + 1]] = o[i, [q + 1, q]]
+                assert P.aurora_simulate(D, B, o) >= p["order_time"] * (1 - 1e-9)
