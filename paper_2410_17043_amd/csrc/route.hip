@@ -14,6 +14,7 @@
 //       the k-th largest - no other expert can be among the true k largest - and selects once more.
 //   route_mfma_kernel   every token in fp64 on the fp64 matrix cores: fp32 inputs and any H.
 #include "common.h"
+#include <algorithm>
 
 namespace {
 
@@ -105,15 +106,27 @@ template <int L> __device__ __forceinline__ float group_max(float v) {
     return v;
 }
 
+// LDS written by a wave and read back by it: its accesses execute in order, the compiler has to keep them so
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Selection for one token by a group of L neighbouring lanes (sub = 0..L-1; lane `sub` looks after experts sub,
 // sub + L, ..., at most NC of them, read once from zr[0..E) in LDS): the k + 1 largest, ties to the lower index;
 // softmax weights; returns whether every gap between consecutive ones exceeds min_gap (a negative min_gap: only
-// the k largest are extracted and the answer means nothing), and the k-th largest in *kth.  selw: LDS scratch
-// [k] of this token.
+// the k largest are extracted and the answer means nothing), and the k-th largest in *kth.  sel: LDS scratch of this
+// token, kSelPitch bytes.  The extraction is a chain of k + 1 reductions and only that; what follows from its result
+// (exponentials, divisions, stores) is done for all k at once behind it.
+constexpr int kSelPitch = MOE_MAX_K * 16;                  // values, then indices and weights
 template <int NC, int L>
 __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int E, int k, int renorm, int t, int sub,
-                                             double min_gap, float* __restrict__ selw, int32_t* __restrict__ topk_idx,
+                                             double min_gap, unsigned char* sel, int32_t* __restrict__ topk_idx,
                                              float* __restrict__ topk_w, double* kth) {
+    double* sz = reinterpret_cast<double*>(sel);
+    int* se = reinterpret_cast<int*>(sz + MOE_MAX_K);
+    float* sw = reinterpret_cast<float*>(se + MOE_MAX_K);
     double cv[NC];
     bool live[NC];
 #pragma unroll
@@ -123,7 +136,6 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
     }
     const int n_take = min(min_gap >= 0.0 ? k + 1 : k, E);   // a negative min_gap: no gaps wanted, the k largest only
     double zmax = 0.0, prev = 0.0;
-    float den = 1.f, wsum = 0.f;
     bool safe = true;
     for (int j = 0; j < n_take; ++j) {
         double best = 0.0;
@@ -150,31 +162,39 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
 #pragma unroll
         for (int i = 0; i < NC; ++i)
             if (sub + L * i == best_e) live[i] = false;
-        if (j == 0) {
-            zmax = best;
-            float part = 0.f;
-#pragma unroll
-            for (int i = 0; i < NC; ++i)
-                if (sub + L * i < E) part += __expf((float)(cv[i] - zmax));
-            den = group_sum<L>(part);
-        } else if (!(prev - best > min_gap)) {
-            safe = false;
-        }
+        if (j == 0) zmax = best;
+        else if (!(prev - best > min_gap)) safe = false;
         prev = best;
         if (j == k - 1) *kth = best;
+        if (j < k && sub == 0) { sz[j] = best; se[j] = best_e; }
+    }
+    float part = 0.f;
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+        if (sub + L * i < E) part += __expf((float)(cv[i] - zmax));
+    const float den = group_sum<L>(part);
+    wave_lds_order();                                    // the group lies inside one wave
+    float wj[MOE_MAX_K / L];
+#pragma unroll
+    for (int m = 0; m < MOE_MAX_K / L; ++m) {
+        const int j = sub + L * m;
+        wj[m] = 0.f;
         if (j < k) {
-            const float wj = __expf((float)(best - zmax)) / den;
-            wsum += wj;
-            if (sub == 0) {
-                topk_idx[(size_t)t * k + j] = best_e;
-                selw[j] = wj;
-            }
+            wj[m] = __expf((float)(sz[j] - zmax)) / den;
+            topk_idx[(size_t)t * k + j] = se[j];
+            sw[j] = wj[m];
         }
     }
-    if (sub == 0) {
-        const float scale = renorm ? 1.f / wsum : 1.f;
-        for (int j = 0; j < k; ++j) topk_w[(size_t)t * k + j] = selw[j] * scale;
+    float scale = 1.f;
+    if (renorm) {
+        wave_lds_order();
+        float wsum = 0.f;
+        for (int j = 0; j < k; ++j) wsum += sw[j];
+        scale = 1.f / wsum;
     }
+#pragma unroll
+    for (int m = 0; m < MOE_MAX_K / L; ++m)
+        if (sub + L * m < k) topk_w[(size_t)t * k + sub + L * m] = wj[m] * scale;
     return safe;
 }
 
@@ -207,12 +227,13 @@ __global__ __launch_bounds__(MAXT) void route_bf16_kernel(const uint16_t* __rest
     const int ngrp = H / 32;                             // groups of 32 hidden values = 64 bytes per row
     const int per = (ngrp + S - 1) / S;
     const int b_lo = wave * per, b_hi = min(b_lo + per, ngrp);
-    // LDS: [ring: S x R x PIECES KB | aliased after the loop by the partial tiles and norm parts]
-    //      [zl] [bias] [thresholds] [xn2] [wn2] [selw] [tokens to evaluate again] [(token, expert) pairs] [2 counters]
+    // LDS: [ring: S x R x PIECES KB | aliased after the loop by the partial tiles and norm parts, then by the selection's scratch]
+    //      [zl] [bias] [thresholds] [xn2] [wn2] [tokens to evaluate again] [(token, expert) pairs] [2 counters]
     const size_t ring_bytes = (size_t)S * R * PIECES * 1024;
     unsigned char* my_ring = lds + (size_t)wave * R * PIECES * 1024;
-    double* zpart = reinterpret_cast<double*>(lds);                               // [S][TP][16]
-    float* xn_part = reinterpret_cast<float*>(lds + (size_t)S * TP * 16 * 8);     // [S][TP]
+    constexpr int NG = (2048 * MT * NT + 64 * (MT + NT) <= 1024 * R * (MT + NT)) ? NT : 1;   // expert tiles whose partial tiles fit into the ring
+    double* zpart = reinterpret_cast<double*>(lds);                               // [S][NG][TP][16]
+    float* xn_part = reinterpret_cast<float*>(lds + (size_t)S * NG * TP * 16 * 8);   // [S][TP]
     float* wn_part = xn_part + (size_t)S * TP;                                    // [S][EP]
     const int ZP = E + 4;                                                         // row pitch of zl: spreads the rows over the banks
     double* zl = reinterpret_cast<double*>(lds + ring_bytes);                     // [TP][ZP]
@@ -220,8 +241,7 @@ __global__ __launch_bounds__(MAXT) void route_bf16_kernel(const uint16_t* __rest
     double* redo_thr = bias_l + E;                                                // [TP] (k-th largest logit) - 2B of a token
     float* xn2 = reinterpret_cast<float*>(redo_thr + TP);                         // [TP]
     float* wn2 = xn2 + TP;                                                        // [E]
-    float* selw = wn2 + E;                                                        // [TP][MOE_MAX_K]
-    int* redo_tok = reinterpret_cast<int*>(selw + TP * MOE_MAX_K);                // [TP] tokens to evaluate again
+    int* redo_tok = reinterpret_cast<int*>(wn2 + E);                              // [TP] tokens to evaluate again
     int* pairs = redo_tok + TP;                                                   // [TP * E] (token << 16) | expert to evaluate exactly
     int* counters = pairs + TP * E;                                               // [2] how many of each
     if (threadIdx.x < 2) counters[threadIdx.x] = 0;
@@ -329,26 +349,29 @@ __global__ __launch_bounds__(MAXT) void route_bf16_kernel(const uint16_t* __rest
             for (int m = 0; m < MT; ++m)
                 if ((r >> 2) == g) xn_part[(size_t)wave * TP + m * 16 + r] = xacc[m][r & 3];
         }
+        // partial tiles of NG expert tiles at a time: 2 barriers instead of 2 NT where the ring has the room
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
+        for (int n0 = 0; n0 < NT; n0 += NG) {
 #pragma unroll
-            for (int m = 0; m < MT; ++m)
+            for (int n = n0; n < n0 + NG; ++n)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) zpart[((size_t)wave * TP + m * 16 + 4 * g + i) * 16 + r] = acc[m][n][i];
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) zpart[((size_t)(wave * NG + n - n0) * TP + m * 16 + 4 * g + i) * 16 + r] = acc[m][n][i];
             __syncthreads();
             // the S parts of an element: all reads first (a loop over S would wait for each in turn), sum in wave order
-            for (int q = threadIdx.x; q < TP * 16; q += blockDim.x) {
-                const int tt = q >> 4, e = e0 + n * 16 + (q & 15);
+            for (int q = threadIdx.x; q < NG * TP * 16; q += blockDim.x) {
+                const int tt = (q >> 4) % TP, e = e0 + (n0 + (q >> 4) / TP) * 16 + (q & 15);
                 double part[kRouteMaxWaves];
 #pragma unroll
-                for (int w = 0; w < kRouteMaxWaves; ++w) part[w] = (w < S) ? zpart[(size_t)w * TP * 16 + q] : 0.0;
+                for (int w = 0; w < kRouteMaxWaves; ++w) part[w] = (w < S) ? zpart[(size_t)w * NG * TP * 16 + q] : 0.0;
                 double sum = part[0];
 #pragma unroll
                 for (int w = 1; w < kRouteMaxWaves; ++w)
                     if (w < S) sum += part[w];
                 if (e < E) zl[(size_t)tt * ZP + e] = sum + bias_l[e];
             }
-            if (n == 0) {
+            if (n0 == 0) {
                 for (int q = threadIdx.x; q < EP + (e0 == 0 ? TP : 0); q += blockDim.x) {
                     const bool is_w = q < EP;
                     const float* src = is_w ? wn_part + q : xn_part + (q - EP);
@@ -375,8 +398,8 @@ __global__ __launch_bounds__(MAXT) void route_bf16_kernel(const uint16_t* __rest
         wmax = group_max<L>(wmax);
         const double min_gap = 2.0 * (double)((float)RUN * kLogitErr * sqrtf(xn2[tsel] * wmax));
         double kth = 0.0;
-        const bool safe = select_group<NC, L>(zl + (size_t)tsel * ZP, E, k, renorm, tok0 + tsel, sub, min_gap,
-                                              selw + tsel * MOE_MAX_K, topk_idx, topk_w, &kth);
+        const bool safe = select_group<NC, L>(zl + (size_t)tsel * ZP, E, k, renorm, tok0 + tsel, sub, min_gap, lds + tsel * kSelPitch,
+                                              topk_idx, topk_w, &kth);
         if (!safe && sub == 0) {                         // the order of this list does not reach any result
             redo_thr[tsel] = kth - min_gap;
             redo_tok[atomicAdd(&counters[0], 1)] = tsel;
@@ -453,7 +476,7 @@ __global__ __launch_bounds__(MAXT) void route_bf16_kernel(const uint16_t* __rest
     for (int f = threadIdx.x / L; f < n_redo; f += blockDim.x / L) {
         const int tsel = redo_tok[f];
         double kth = 0.0;
-        select_group<NC, L>(zl + (size_t)tsel * ZP, E, k, renorm, tok0 + tsel, sub, -1.0, selw + tsel * MOE_MAX_K, topk_idx, topk_w, &kth);
+        select_group<NC, L>(zl + (size_t)tsel * ZP, E, k, renorm, tok0 + tsel, sub, -1.0, lds + tsel * kSelPitch, topk_idx, topk_w, &kth);
     }
     MOE_MARK(5);
 #undef MOE_MARK
@@ -546,10 +569,10 @@ __global__ __launch_bounds__(NT == 1 ? 1024 : 512) void route_mfma_kernel(const 
         }
         __syncthreads();
     }
-    float* selw = reinterpret_cast<float*>(zpart);       // [16][MOE_MAX_K]
+    unsigned char* sel = reinterpret_cast<unsigned char*>(zpart);   // [16][kSelPitch]
     for (int tt = threadIdx.x >> 4; tt < 16 && tok0 + tt < T; tt += blockDim.x >> 4) {
         double kth = 0.0;
-        select_group<NC, 16>(zl + (size_t)tt * ZP, E, k, renorm, tok0 + tt, threadIdx.x & 15, -1.0, selw + tt * MOE_MAX_K, topk_idx, topk_w, &kth);
+        select_group<NC, 16>(zl + (size_t)tt * ZP, E, k, renorm, tok0 + tt, threadIdx.x & 15, -1.0, sel + tt * kSelPitch, topk_idx, topk_w, &kth);
     }
 }
 
@@ -562,7 +585,7 @@ int launch_route_mfma(const moe_ctx* c, const void* x, const void* wg, const flo
     int S = 1;                                            // waves per block: about 2048 waves in all (4096 with one expert tile), at most 8 (16)
     const int s_max = (NT == 1) ? 16 : 8, waves = (NT == 1) ? 4096 : 2048;
     while (S < s_max && blocks * S < waves && 2 * S <= ngrp) S *= 2;
-    const size_t lds = ((size_t)16 * (s.E + 1) + (size_t)S * 16 * NT * 16) * sizeof(double);   // at most 97 KB
+    const size_t lds = (size_t)16 * (s.E + 1) * sizeof(double) + std::max((size_t)S * 16 * NT * 16 * sizeof(double), (size_t)16 * kSelPitch);   // at most 97 KB
     static bool attr_done = false;
     if (!attr_done) {
         MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&route_mfma_kernel<DT, NT, PF, NC>),
@@ -583,7 +606,7 @@ int launch_route_bf16(const moe_ctx* c, const void* x, const void* wg, const flo
     int S = MAXT / 64;                                    // waves per block: no more than there are groups to share out
     while (S > 1 && S > ngrp) S >>= 1;
     const size_t lds = (size_t)S * R * (MT + NT) * 1024 + ((size_t)TP * (s.E + 4) + s.E + TP) * sizeof(double) +
-                       (size_t)(TP + s.E + TP * MOE_MAX_K) * sizeof(float) + ((size_t)TP + (size_t)TP * s.E + 2) * sizeof(int);
+                       (size_t)(TP + s.E) * sizeof(float) + ((size_t)TP + (size_t)TP * s.E + 2) * sizeof(int);
     static bool attr_done = false;
     if (!attr_done) {
         MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&route_bf16_kernel<NT, MT, R, RUN, NC, L, MAXT, TIMED>),
@@ -624,6 +647,13 @@ int route_dispatch(const moe_ctx* c, const void* x, const void* wg, const float*
     // other waits for its fragments; with many tokens four tiles per block (the gate rows are fetched from L2 once
     // per 64 tokens instead of once per 32) and one wave per SIMD
     const bool few = (s.T + 63) / 64 < 200;
+    // ... but while tiles of one token each find a CU, one per block: half the fragments, sums and selections behind each
+    // other, and the ring has room for all partial tiles at once.  E = 64, k = 6, H = 2048: 14.0 -> 11.0 us at 64 tokens,
+    // 24.7 -> 21.8 at 4096; E = 24, k = 3, H = 1152: 7.9 -> 6.7 and 12.7 -> 10.8
+    if ((s.T + 15) / 16 <= 256) {
+        if (s.E <= 32) return MOE_ROUTE(2, 1, 4, 2, 2, 16, 512);
+        if (s.E <= 64) return MOE_ROUTE(4, 1, 3, 2, 4, 16, 512);
+    }
     if (s.E <= 32) return few ? MOE_ROUTE(2, 2, 2, 2, 2, 16, 512) : MOE_ROUTE(2, 4, 3, 2, 8, 4, 256);
     if (s.E <= 64) return few ? MOE_ROUTE(4, 2, 2, 2, 4, 16, 512) : MOE_ROUTE(4, 4, 3, 2, 16, 4, 256);
     return MOE_ROUTE(4, 1, 2, 2, 16, 16, 512);

@@ -45,6 +45,13 @@ ROUTE_CASES = [
     small("c2_mixtral", T=17, H=8, E=17, k=2, G=1),              # one 16-byte chunk per row, one expert past a tile
     small("c5_finegrained", T=100, H=520, E=65, k=6, G=5),       # second pass of 64 experts holds a single expert
     small("c3_switch", T=40, H=1024, E=256, k=16, G=64),         # the limits of E, k and G
+    # both sides of where two token tiles share a block; k = E; more choices than lanes of the four-lane selection
+    small("c2_mixtral", T=4096, H=96, E=24, k=4, G=8),
+    small("c2_mixtral", T=4097, H=96, E=24, k=4, G=8),
+    small("c3_switch", T=4113, H=64, E=33, k=1, G=3),
+    small("c5_finegrained", T=20, H=64, E=33, k=16, G=3),
+    small("c2_mixtral", T=12801, H=32, E=18, k=16, G=6),
+    small("c2_mixtral", T=12801, H=32, E=40, k=9, G=8),
 ]
 
 
