@@ -473,10 +473,12 @@ __global__ __launch_bounds__(MAXT) void route_bf16_kernel(const uint16_t* __rest
         }
     }
     __syncthreads();
-    for (int f = threadIdx.x / L; f < n_redo; f += blockDim.x / L) {
+    // few tokens: 16 lanes each, where the selection of all tokens has four (a shorter chain per extraction)
+    for (int f = threadIdx.x >> 4; f < n_redo; f += blockDim.x >> 4) {
         const int tsel = redo_tok[f];
         double kth = 0.0;
-        select_group<NC, L>(zl + (size_t)tsel * ZP, E, k, renorm, tok0 + tsel, sub, -1.0, lds + tsel * kSelPitch, topk_idx, topk_w, &kth);
+        select_group<(NC * L + 15) / 16, 16>(zl + (size_t)tsel * ZP, E, k, renorm, tok0 + tsel, threadIdx.x & 15, -1.0, lds + tsel * kSelPitch,
+                                             topk_idx, topk_w, &kth);
     }
     MOE_MARK(5);
 #undef MOE_MARK
