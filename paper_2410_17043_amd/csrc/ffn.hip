@@ -1364,7 +1364,9 @@ struct SkinnyPlan {
 __host__ __device__ __forceinline__ SkinnyPlan plan_skinny(int total, int ncu, int ns) {
     SkinnyPlan p{1, ns};
     if (total <= 0 || total >= ncu) return p;
-    int parts = min(min(ncu / total, ns / 2), 32);       // at least 2 stages per piece
+    // At least 4 stages per piece: the last block adds the pieces at about 0.4 us each, half a stage's time.  64 rows of
+    // 2048 -> 2816 -> 2048 30.0 us (pieces of 2 stages: 32.3, of 6: 32.8), 60 of 1152 -> 2304 -> 1152 25.6 (28.7, 26.5)
+    int parts = min(min(ncu / total, ns / 4), 32);
     if (parts < 2) return p;
     p.per = (ns + parts - 1) / parts;
     p.parts = (ns + p.per - 1) / p.per;
