@@ -1155,7 +1155,9 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     // A group is GI 16-row blocks, both k-tiles of the pair: 4 loads per wave at 4 x 4, 2 at 2 x 2.  The
     // loads are spread evenly, at 4 x 4 one per four MFMAs: a CU sustains roughly one wave-load per 40 clocks
     // when the lines come from HBM, and a load that cannot be accepted stalls the wave's MFMA issue too.
-    // A bare s_barrier is used: __syncthreads() would add a fence that waits for ALL outstanding loads.
+    // A bare s_barrier is used: __syncthreads() would add a fence that waits for ALL outstanding loads.  In front of it a
+    // wave waits for its own LDS reads: a read that is only issued is not ordered against what other waves write behind
+    // the barrier.  The phase behind it starts with MFMAs on those fragments, so the wait costs nothing.
 #define MOE_PHASE_SCHED()                                                                      \
     if (MI * NJ == 12) {                                                                       \
     _Pragma("unroll") for (int q = 0; q < 7; ++q) {   /* (MFMA, LDS read) x 7 */                \
@@ -1216,6 +1218,7 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
         mma(a0, b0, first);
         MOE_PHASE_SCHED()
         __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xC07F);                  // lgkmcnt(0): this wave has read stage so[0], which is refilled below
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         if ((SWITCH || (FIRST && cur.nk == 4)) && more) { src = src_next; t_first = cur.nk; t_last = next.nk - 2; }
@@ -1229,7 +1232,9 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
         mma(a0, b0, std::false_type{});
         MOE_PHASE_SCHED()
         __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0x0F70 | (4 * GI));       // only groups 0 and 1 of the next pair may be outstanding
+        // vmcnt(4 GI): only groups 0 and 1 of the next pair may be outstanding; lgkmcnt(0): this wave has read stage so[1],
+        // which the epilogue writes behind a tile's last trip
+        __builtin_amdgcn_s_waitcnt(0x0070 | (4 * GI));
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         load_frags(a0, b0, lds + so[2], 0);
