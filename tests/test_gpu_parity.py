@@ -78,6 +78,31 @@ def test_route(H, cfg):
     assert np.max(np.abs(H.host(sh.w) / w_ref - 1.0)) < 1e-5
 
 
+def lane_tree(v):
+    """fp32 sum along the last axis (up to 16 values) in the order of 16 lanes that exchange at distances 8, 4, 2, 1."""
+    v = np.concatenate([v, np.zeros(v.shape[:-1] + (16 - v.shape[-1],), np.float32)], axis=-1)
+    while v.shape[-1] > 1:
+        h = v.shape[-1] // 2
+        v = v[..., :h] + v[..., h:]
+    return v
+
+
+@pytest.mark.parametrize("E,k,dtype,H_", [(16, 4, "fp32", 64), (5, 5, "fp32", 36), (64, 16, "fp32", 100), (200, 9, "fp32", 36), (24, 3, "bf16", 40)])
+def test_renormalised_weights_of_the_fp32_gate_are_quotients_rounded_once(H, E, k, dtype, H_):
+    """With the probabilities p (renorm = 0) of the same inputs: w = fl(p / sum p), to the bit."""
+    cfg = small("c1_tiny_fp32", T=333, H=H_, E=E, k=k, G=1)
+    cfg = dataclasses.replace(cfg, dtype=dtype, renorm=0)
+    r = np.random.default_rng(E)
+    x, wg = H.dev(r.standard_normal((cfg.T, H_)), dtype), H.dev(0.2 * r.standard_normal((E, H_)), dtype)
+    got = {}
+    for renorm in (0, 1):
+        sh = H.Share(dataclasses.replace(cfg, renorm=renorm))
+        sh.route(x, wg, None)
+        torch.cuda.synchronize()
+        got[renorm] = H.host(sh.w)
+    assert np.array_equal(got[1], got[0] / lane_tree(got[0]))
+
+
 @pytest.mark.parametrize("cfg", [small("c2_mixtral", T=203, H=1024), small("c5_finegrained", T=301, H=512),
                                  small("c3_switch", T=40, H=1024, E=256, k=16, G=64), small("c1_tiny_fp32", T=37, H=100, E=5, k=3, G=5)],
                          ids=lambda c: "%s-T%d-E%d-k%d" % (c.name, c.T, c.E, c.k))
