@@ -89,7 +89,8 @@ inline int max_tiles_of(int R, int bm, int nseg) { return (R + bm - 1) / bm + ns
 //
 // Items are the clamped, non-empty segments in processing order; a group is a maximal chain of items of
 // one expert whose rows increase (so offsets from the tile's first row are never negative); tiles never
-// straddle groups.  The construction is written once for the device kernel and for the host self check.
+// straddle groups.  Both constructions - this one, and the one of lists of up to 64 segments below - are written once
+// for the device kernel and for the host self check.
 struct SegWork {
     int lo[kMaxSeg], hi[kMaxSeg], exp[kMaxSeg];                            // items (rows lo .. hi - 1 of one expert)
     int v0[kMaxSeg];                                                       // position of the item's first row in its group
@@ -281,84 +282,171 @@ __device__ __forceinline__ void zero_done(int32_t* done, int tid, int nth) {
 
 // Up to 64 segments (every local expert of every source of a layer of up to 64 experts): lane k of EVERY wave holds
 // segment k and works out the whole list for itself with ballots, lane permutations and prefix sums - no LDS, no
-// barrier - and the waves share out the tiles.  10 -> 4 us at 64 segments against the block-wide kernel below.
-__device__ __forceinline__ int wave_prefix(int v, int lane) {          // inclusive
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int up = __shfl_up(v, o, 64);
-        if (lane >= o) v += up;
-    }
-    return v;
-}
+// barrier - and the waves share out the tiles.  10 -> 4.7 us at 64 segments against the block-wide kernel below.
+// The steps are written once over W, the 64 lanes: WaveLanes on the device, ArrayLanes in the host self check.
 constexpr int kSmallMapSegs = 64;
+struct SmallItem {
+    int off0, off1, e;               // in: seg_offset[k], seg_offset[k + 1], seg_expert[k]; e: then the item's expert
+    int lo, len, hi;                 // rows lo .. hi - 1
+    int rank;                        // position of the segment among the items
+    int incl, excl;                  // rows of the items up to and in front of this one
+    int prev_e, prev_hi;
+    int v0;                          // position of the item's first row in its group
+    int end, rows, tiles, tincl;     // of the group that the item opens: one past its last item, rows, tiles; tiles up to it
+    bool ok, opens;
+};
+struct WaveLanes {
+    SmallItem mine;
+    int lane;
+    template <class F> __device__ __forceinline__ void each(F f) { f(mine, lane); }
+    template <class F> __device__ __forceinline__ unsigned long long ballot(F f) const { return __ballot(f(mine, lane)); }
+    __device__ __forceinline__ int at(int SmallItem::*v, int k) const { return __builtin_amdgcn_readlane(mine.*v, k); }
+    __device__ __forceinline__ void move_to_rank(int SmallItem::*v) { mine.*v = __builtin_amdgcn_ds_permute(mine.rank * 4, mine.*v); }
+    __device__ __forceinline__ int from(int SmallItem::*v, int l, const SmallItem&) const { return __shfl(mine.*v, l, 64); }
+    __device__ __forceinline__ void from_below(int SmallItem::*v, int SmallItem::*to) { mine.*to = __shfl_up(mine.*v, 1, 64); }
+    __device__ __forceinline__ void prefix(int SmallItem::*v, int SmallItem::*to) {   // inclusive
+        int x = mine.*v;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int up = __shfl_up(x, o, 64);
+            if (lane >= o) x += up;
+        }
+        mine.*to = x;
+    }
+};
+struct ArrayLanes {
+    SmallItem it[64];
+    template <class F> void each(F f) { for (int l = 0; l < 64; ++l) f(it[l], l); }
+    template <class F> unsigned long long ballot(F f) const {
+        unsigned long long m = 0;
+        for (int l = 0; l < 64; ++l) m |= (unsigned long long)(f(it[l], l) ? 1 : 0) << l;
+        return m;
+    }
+    int at(int SmallItem::*v, int k) const { return it[k].*v; }
+    void move_to_rank(int SmallItem::*v) {
+        int old[64];
+        for (int l = 0; l < 64; ++l) old[l] = it[l].*v;
+        for (int l = 0; l < 64; ++l) it[it[l].rank].*v = old[l];
+    }
+    int from(int SmallItem::*v, int l, const SmallItem&) const { return it[l].*v; }
+    void from_below(int SmallItem::*v, int SmallItem::*to) { for (int l = 0; l < 64; ++l) it[l].*to = it[l > 0 ? l - 1 : 0].*v; }
+    void prefix(int SmallItem::*v, int SmallItem::*to) {
+        int x = 0;
+        for (int l = 0; l < 64; ++l) it[l].*to = (x += it[l].*v);
+    }
+};
+struct SmallMap {
+    unsigned long long gaps;         // items that leave a gap behind their predecessor in the group
+    int n_tiles;
+};
+template <class W>
+__host__ __device__ __forceinline__ SmallMap small_map(W& w, int nseg, int R, int n_local, int gather, int BM, int max_tiles) {
+    using U = unsigned long long;
+    using S = SmallItem;
+    w.each([&](S& s, int lane) {
+        s.lo = s.off0 > 0 ? s.off0 : 0;
+        s.len = (s.off1 < R ? s.off1 : R) - s.lo;
+        s.ok = lane < nseg && s.e >= 0 && s.e < n_local && s.len > 0;  // others are skipped
+    });
+    // items: the segments by (expert, index) - without gathering by index - first, the skipped ones behind them
+    const U okm = w.ballot([](const S& s, int) { return s.ok; });
+    const int ni = __builtin_popcountll(okm);
+    U bit[6];                                                          // MOE_MAX_LOCAL = 64 experts: six bits
+#pragma unroll
+    for (int b = 0; b < 6; ++b) bit[b] = w.ballot([&](const S& s, int) { return s.ok && ((s.e >> b) & 1); });
+    w.each([&](S& s, int lane) {
+        const U below = (1ull << lane) - 1ull;
+        U eq = okm, lt = 0;                                            // the items of this expert, of lower experts
+#pragma unroll
+        for (int b = 5; b >= 0; --b) {
+            if ((s.e >> b) & 1) { lt |= eq & ~bit[b]; eq &= bit[b]; }
+            else eq &= ~bit[b];
+        }
+        s.rank = gather ? __builtin_popcountll(lt) + __builtin_popcountll(eq & below) : __builtin_popcountll(okm & below);
+        if (!s.ok) { s.rank = ni + __builtin_popcountll(~okm & below); s.len = 0; s.e = -1; }
+    });
+    w.move_to_rank(&S::lo);
+    w.move_to_rank(&S::len);
+    w.move_to_rank(&S::e);
+    // groups: chains of items of one expert whose rows increase (without gathering: follow each other)
+    w.prefix(&S::len, &S::incl);
+    w.each([](S& s, int) { s.excl = s.incl - s.len; s.hi = s.lo + s.len; });
+    const int total = w.at(&S::incl, 63);
+    w.from_below(&S::e, &S::prev_e);
+    w.from_below(&S::hi, &S::prev_hi);
+    w.each([&](S& s, int lane) {
+        s.opens = lane < ni && (lane == 0 || s.e != s.prev_e || (gather ? s.lo < s.prev_hi : s.lo != s.prev_hi));
+    });
+    SmallMap m;
+    const U heads = w.ballot([](const S& s, int) { return s.opens; });
+    m.gaps = w.ballot([&](const S& s, int lane) { return lane < ni && !s.opens && s.lo != s.prev_hi; });
+    w.each([&](S& s, int lane) {
+        const U upto = (2ull << lane) - 1ull, above = heads & ~upto;
+        const int head = 63 - __builtin_clzll((heads & upto) | 1ull);  // bit 0 is set whenever there is an item
+        s.v0 = s.excl - w.from(&S::excl, head, s);
+        s.end = above ? __builtin_ctzll(above) : ni;
+        const int excl_end = w.from(&S::excl, s.end < 63 ? s.end : 63, s);
+        s.rows = (s.end < ni ? excl_end : total) - s.excl;
+        s.tiles = s.opens ? (s.rows + BM - 1) / BM : 0;
+    });
+    w.prefix(&S::tiles, &S::tincl);
+    // a well-formed list (non-decreasing offsets) stays below the bound; overlapping segments are cut off here
+    const int nt = w.at(&S::tincl, 63);
+    m.n_tiles = nt < max_tiles ? nt : max_tiles;
+    return m;
+}
+// tile t: its record, the items that have rows in it and its range of group rows
+struct SmallTile { int row0, nrows, expert, gather, v_lo; unsigned long long in; };
+template <class W> __host__ __device__ __forceinline__ SmallTile small_tile(const W& w, const SmallMap& m, int t, int BM) {
+    using S = SmallItem;
+    SmallTile r;
+    const int g = 63 - __builtin_clzll(w.ballot([&](const S& s, int) { return s.opens && s.tincl - s.tiles <= t; }));
+    const int v_lo = (t - (w.at(&S::tincl, g) - w.at(&S::tiles, g))) * BM, rows = w.at(&S::rows, g), g_end = w.at(&S::end, g);
+    const int v_hi = rows < v_lo + BM ? rows : v_lo + BM;
+    r.in = w.ballot([&](const S& s, int lane) { return lane >= g && lane < g_end && s.v0 < v_hi && s.v0 + s.len > v_lo; });
+    const int f = __builtin_ctzll(r.in);
+    r.row0 = w.at(&S::lo, f) + v_lo - w.at(&S::v0, f);
+    r.nrows = v_hi - v_lo;
+    r.expert = w.at(&S::e, f);
+    r.gather = (m.gaps & r.in & ~(1ull << f)) != 0 ? 1 : 0;            // a gap in front of an item that starts inside the tile
+    r.v_lo = v_lo;
+    return r;
+}
+// the table entries of item k of a gathered tile: rel[v] = val + v for lo <= v < hi
+struct SmallRun { int lo, hi, val; };
+template <class W> __host__ __device__ __forceinline__ SmallRun small_run(const W& w, const SmallTile& r, int k) {
+    using S = SmallItem;
+    const int v0 = w.at(&S::v0, k) - r.v_lo, hi = v0 + w.at(&S::len, k);
+    return SmallRun{v0 > 0 ? v0 : 0, hi < r.nrows ? hi : r.nrows, w.at(&S::lo, k) - v0 - r.row0};
+}
+
 __global__ __launch_bounds__(256) void tilemap_small_kernel(const int32_t* __restrict__ seg_offset,
                                                             const int32_t* __restrict__ seg_expert, int nseg, int R,
                                                             int n_local, int gather, MapJobs jobs) {
     const MapJob& job = jobs.job[blockIdx.y];
-    const int BM = job.bm;
     const TileMap m = job.m;
-    const int lane = threadIdx.x & 63, wave_id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int i = min(lane, nseg - 1);
-    const int off0 = seg_offset[i], off1 = seg_offset[i + 1];
-    int e = seg_expert[i];
+    const int wave_id = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    WaveLanes w;
+    w.lane = threadIdx.x & 63;
+    const int i = min(w.lane, nseg - 1);
+    w.mine.off0 = seg_offset[i];
+    w.mine.off1 = seg_offset[i + 1];
+    w.mine.e = seg_expert[i];
     if (blockIdx.x == 0 && blockIdx.y == 0) zero_done(jobs.done, threadIdx.x, 256);
-    const unsigned long long below = (1ull << lane) - 1ull;
-    int lo = max(off0, 0), len = min(off1, R) - lo;
-    const bool ok = lane < nseg && e >= 0 && e < n_local && len > 0;   // others are skipped
-    // items: the segments by (expert, index) - without gathering by index - first, the skipped ones behind them
-    const unsigned long long okm = __ballot(ok);
-    unsigned long long eq = okm, lt = 0;
-#pragma unroll
-    for (int b = 5; b >= 0; --b) {                                     // MOE_MAX_LOCAL = 64 experts: six bits
-        const bool one = (e >> b) & 1;
-        const unsigned long long mb = __ballot(ok && one);
-        if (one) { lt |= eq & ~mb; eq &= mb; }
-        else eq &= ~mb;
-    }
-    const int ni = __popcll(okm);
-    int rank = gather ? __popcll(lt) + __popcll(eq & below) : __popcll(okm & below);
-    if (!ok) { rank = ni + __popcll(~okm & below); len = 0; e = -1; }
-    lo = __builtin_amdgcn_ds_permute(rank * 4, lo);
-    len = __builtin_amdgcn_ds_permute(rank * 4, len);
-    e = __builtin_amdgcn_ds_permute(rank * 4, e);
-    // groups: chains of items of one expert whose rows increase (without gathering: follow each other)
-    const int incl = wave_prefix(len, lane), excl = incl - len, total = __builtin_amdgcn_readlane(incl, 63);
-    const int prev_e = __shfl_up(e, 1, 64), prev_hi = __shfl_up(lo + len, 1, 64);
-    const bool live = lane < ni;
-    const bool opens = live && (lane == 0 || e != prev_e || (gather ? lo < prev_hi : lo != prev_hi));
-    const unsigned long long heads = __ballot(opens), gaps = __ballot(live && !opens && lo != prev_hi);
-    const unsigned long long upto = below | (1ull << lane);
-    const int head = 63 - __clzll((heads & upto) | 1ull);              // bit 0 is set whenever there is an item
-    const int v0 = excl - __shfl(excl, head, 64);                      // position of the item's first row in its group
-    const unsigned long long above = heads & ~upto;
-    const int end = above ? __builtin_ctzll(above) : ni;               // one past the last item of the group
-    const int excl_end = __shfl(excl, min(end, 63), 64);
-    const int rows_g = (end < ni ? excl_end : total) - excl;           // of the group this item opens
-    const int tiles_g = opens ? (rows_g + BM - 1) / BM : 0;
-    const int tincl = wave_prefix(tiles_g, lane), tile0 = tincl - tiles_g;
-    // a well-formed list (non-decreasing offsets) stays below the bound; overlapping segments are cut off here
-    const int nt = min(__builtin_amdgcn_readlane(tincl, 63), job.max_tiles);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *m.n_tiles = nt;
-    for (int t = wave_id; t < nt; t += gridDim.x * 4) {
-        const int g = 63 - __clzll(__ballot(opens && tile0 <= t));
-        const int v_lo = (t - __builtin_amdgcn_readlane(tile0, g)) * BM;
-        const int v_hi = min(__builtin_amdgcn_readlane(rows_g, g), v_lo + BM), g_end = __builtin_amdgcn_readlane(end, g);
-        unsigned long long in = __ballot(lane >= g && lane < g_end && v0 < v_hi && v0 + len > v_lo);
-        const int f = __builtin_ctzll(in);
-        const int row0 = __builtin_amdgcn_readlane(lo, f) + v_lo - __builtin_amdgcn_readlane(v0, f);
-        const bool gat = (gaps & in & ~(1ull << f)) != 0;              // a gap in front of an item that starts inside the tile
-        if (lane == 0) {
-            m.row0[t] = row0;
-            m.nrows[t] = v_hi - v_lo;
-            m.expert[t] = __builtin_amdgcn_readlane(e, f);
-            m.gather[t] = gat ? 1 : 0;
+    const SmallMap sm = small_map(w, nseg, R, n_local, gather, job.bm, job.max_tiles);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *m.n_tiles = sm.n_tiles;
+    for (int t = wave_id; t < sm.n_tiles; t += gridDim.x * 4) {
+        const SmallTile r = small_tile(w, sm, t, job.bm);
+        if (w.lane == 0) {
+            m.row0[t] = r.row0;
+            m.nrows[t] = r.nrows;
+            m.expert[t] = r.expert;
+            m.gather[t] = r.gather;
         }
-        if (!gat) continue;
-        for (; in; in &= in - 1) {
-            const int k = __builtin_ctzll(in);
-            const int v0k = __builtin_amdgcn_readlane(v0, k), first = __builtin_amdgcn_readlane(lo, k) - v0k - row0;
-            const int b = min(v0k + __builtin_amdgcn_readlane(len, k), v_hi);
-            for (int v = max(v0k, v_lo) + lane; v < b; v += 64) m.rel[(size_t)t * kRelPitch + v - v_lo] = first + v;
+        if (!r.gather) continue;
+        for (unsigned long long in = r.in; in; in &= in - 1) {
+            const SmallRun run = small_run(w, r, __builtin_ctzll(in));
+            for (int v = run.lo + w.lane; v < run.hi; v += 64) m.rel[(size_t)t * kRelPitch + v] = run.val + v;
         }
     }
 }
@@ -1736,11 +1824,6 @@ extern "C" int moe_selfcheck_tile_order(int32_t tiles_m, int32_t tiles_n, int32_
     return p.parts;
 }
 
-// Host-side self check of the tile map (not part of the published interface; used by the CPU tests): runs
-// the steps that the device kernel runs, on the host, and verifies that every row of every non-empty
-// segment of a known expert lies in exactly one tile of that expert, that tile rows increase, that exactly
-// the tiles with gaps are marked as gathered and that their offset tables are complete.  Returns the
-// number of tiles, or a negative status.
 extern "C" int moe_selfcheck_tile_shape(int32_t R, int32_t n_used, int32_t N, int32_t K, int32_t act, int32_t ncu) {
     if (R < 1 || n_used < 1 || N < 1 || K < 64 || K % 64 != 0 || ncu < 1) return moe_set_error(MOE_EINVAL, "moe_selfcheck_tile_shape: bad argument");
     return kShapeRows[choose_shape(R, n_used, N, K, act, ncu)];
@@ -1758,6 +1841,61 @@ extern "C" int moe_selfcheck_skinny_plan(int32_t total, int32_t ncu, int32_t ns)
     return p.parts;
 }
 
+// A tile map on the host, and whether it is the one that the segment list asks for.
+struct MapArrays {
+    std::vector<int32_t> row0, nrows, expert, gather, rel;
+    int32_t n_tiles;
+    TileMap m;
+    explicit MapArrays(int nt) : row0(nt), nrows(nt), expert(nt), gather(nt), rel((size_t)nt * kRelPitch, -1), n_tiles(nt) {
+        m = TileMap{&n_tiles, row0.data(), nrows.data(), expert.data(), gather.data(), rel.data(), nullptr};
+    }
+    bool enter(size_t at, int32_t value) {
+        if (at >= rel.size() || rel[at] != -1) {
+            (void)moe_set_error(MOE_EINTERNAL, "offset table entry %zu is outside the table or written twice", at);
+            return false;
+        }
+        rel[at] = value;
+        return true;
+    }
+};
+static int check_map(const MapArrays& map, int nt, const int32_t* seg_offset, const int32_t* seg_expert, int nseg, int R, int bm, int n_local, int gather) {
+    const TileMap& m = map.m;
+    std::vector<int> owner((size_t)R, -1);
+    for (int i = 0; i < nseg; ++i) {
+        const int lo = std::max(seg_offset[i], 0), hi = std::min(seg_offset[i + 1], R);
+        if (hi > lo && seg_expert[i] >= 0 && seg_expert[i] < n_local)
+            for (int r = lo; r < hi; ++r) owner[r] = seg_expert[i];
+    }
+    std::vector<int> hits((size_t)R, 0);
+    for (int t = 0; t < nt; ++t) {
+        if (m.nrows[t] < 1 || m.nrows[t] > bm) return moe_set_error(MOE_EINTERNAL, "tile %d has %d rows", t, m.nrows[t]);
+        if (m.gather[t] && !gather) return moe_set_error(MOE_EINTERNAL, "tile %d is gathered but gathering is off", t);
+        int prev = -1;
+        bool gaps = false;
+        for (int r = 0; r < m.nrows[t]; ++r) {
+            const int off = m.gather[t] ? m.rel[(size_t)t * kRelPitch + r] : r;
+            if (!m.gather[t] && m.rel[(size_t)t * kRelPitch + r] != -1) return moe_set_error(MOE_EINTERNAL, "tile %d has no gaps but an offset table", t);
+            const int row = m.row0[t] + off;
+            if (off < 0 || row < 0 || row >= R) return moe_set_error(MOE_EINTERNAL, "tile %d row %d maps to %d", t, r, row);
+            if (r == 0 && off != 0) return moe_set_error(MOE_EINTERNAL, "tile %d does not start at its first row", t);
+            if (row <= prev) return moe_set_error(MOE_EINTERNAL, "tile %d: rows do not increase", t);
+            if (prev >= 0 && row != prev + 1) gaps = true;
+            if (owner[row] != m.expert[t]) return moe_set_error(MOE_EINTERNAL, "tile %d of expert %d holds row %d of expert %d", t, m.expert[t], row, owner[row]);
+            ++hits[row];
+            prev = row;
+        }
+        if (gaps != (m.gather[t] != 0)) return moe_set_error(MOE_EINTERNAL, "tile %d: gather flag %d but gaps %d", t, m.gather[t], (int)gaps);
+    }
+    for (int r = 0; r < R; ++r)
+        if (hits[r] != (owner[r] >= 0 ? 1 : 0)) return moe_set_error(MOE_EINTERNAL, "row %d is in %d tiles", r, hits[r]);
+    return MOE_OK;
+}
+
+// Host-side self check of the tile map (not part of the published interface; used by the CPU tests): runs
+// the steps that the device kernels run, on the host, and verifies that every row of every non-empty
+// segment of a known expert lies in exactly one tile of that expert, that tile rows increase, that exactly
+// the tiles with gaps are marked as gathered and that their offset tables are complete.  Returns the
+// number of tiles, or a negative status.  Up to 64 segments the same goes for the map that such lists take.
 extern "C" int moe_selfcheck_tile_map(const int32_t* seg_offset, const int32_t* seg_expert, int32_t nseg, int32_t R,
                                       int32_t bm, int32_t n_local, int32_t gather) {
     if (!seg_offset || !seg_expert || nseg < 0 || nseg > kMaxSeg || R < 0 || bm < 1 || bm > kRelPitch || n_local < 1 || n_local > MOE_MAX_LOCAL)
@@ -1776,53 +1914,48 @@ extern "C" int moe_selfcheck_tile_map(const int32_t* seg_offset, const int32_t* 
         tilemap_merge(w, nseg, R);
     }
     tilemap_groups_host(w, bm, gather != 0);
-    const int max_tiles = (R + bm - 1) / bm + nseg;
-    const int nt = w.n_tiles;
+    const int max_tiles = max_tiles_of(R, bm, nseg), nt = w.n_tiles;
     if (nt > max_tiles) return moe_set_error(MOE_EINTERNAL, "%d tiles exceed the bound %d", nt, max_tiles);
-    std::vector<int32_t> row0(nt), nrows(nt), expert(nt), gat(nt), rel((size_t)nt * kRelPitch, -1);
-    int32_t n_tiles = nt;
-    TileMap m{&n_tiles, row0.data(), nrows.data(), expert.data(), gat.data(), rel.data()};
-    for (int t = nt - 1; t >= 0; --t) tilemap_tile(w, t, bm, m);
+    MapArrays map(nt);
+    for (int t = nt - 1; t >= 0; --t) tilemap_tile(w, t, bm, map.m);
     if (gather)
         for (int k = 0; k < w.n_items; ++k) {
             RelJob job[2];
             tilemap_rel_jobs(w, k, bm, nt, job);
             for (int pass = 0; pass < 2; ++pass)
-                for (int r = 0; r < job[pass].cnt; ++r) {
-                    int32_t& slot = rel[(size_t)job[pass].dst + r];
-                    if (slot != -1) return moe_set_error(MOE_EINTERNAL, "offset table entry %d written twice", job[pass].dst + r);
-                    slot = job[pass].val + r;
-                }
+                for (int r = 0; r < job[pass].cnt; ++r)
+                    if (!map.enter((size_t)job[pass].dst + r, job[pass].val + r)) return MOE_EINTERNAL;
         }
-    std::vector<int> owner((size_t)R, -1);
-    for (int i = 0; i < nseg; ++i) {
-        const int lo = std::max(seg_offset[i], 0), hi = std::min(seg_offset[i + 1], R);
-        if (hi > lo && seg_expert[i] >= 0 && seg_expert[i] < n_local)
-            for (int r = lo; r < hi; ++r) owner[r] = seg_expert[i];
+    int rc = check_map(map, nt, seg_offset, seg_expert, nseg, R, bm, n_local, gather);
+    if (rc != MOE_OK || nseg < 1 || nseg > kSmallMapSegs) return rc != MOE_OK ? rc : nt;
+    // the map of up to 64 segments
+    std::vector<ArrayLanes> lanes(1);
+    ArrayLanes& l = lanes[0];
+    for (int k = 0; k < 64; ++k) {
+        const int i = std::min(k, nseg - 1);
+        l.it[k].off0 = seg_offset[i];
+        l.it[k].off1 = seg_offset[i + 1];
+        l.it[k].e = seg_expert[i];
     }
-    std::vector<int> hits((size_t)R, 0);
-    for (int t = 0; t < nt; ++t) {
-        if (nrows[t] < 1 || nrows[t] > bm) return moe_set_error(MOE_EINTERNAL, "tile %d has %d rows", t, nrows[t]);
-        if (gat[t] && !gather) return moe_set_error(MOE_EINTERNAL, "tile %d is gathered but gathering is off", t);
-        int prev = -1;
-        bool gaps = false;
-        for (int r = 0; r < nrows[t]; ++r) {
-            const int off = gat[t] ? rel[(size_t)t * kRelPitch + r] : r;
-            if (!gat[t] && rel[(size_t)t * kRelPitch + r] != -1) return moe_set_error(MOE_EINTERNAL, "tile %d has no gaps but an offset table", t);
-            const int row = row0[t] + off;
-            if (off < 0 || row < 0 || row >= R) return moe_set_error(MOE_EINTERNAL, "tile %d row %d maps to %d", t, r, row);
-            if (r == 0 && off != 0) return moe_set_error(MOE_EINTERNAL, "tile %d does not start at its first row", t);
-            if (row <= prev) return moe_set_error(MOE_EINTERNAL, "tile %d: rows do not increase", t);
-            if (prev >= 0 && row != prev + 1) gaps = true;
-            if (owner[row] != expert[t]) return moe_set_error(MOE_EINTERNAL, "tile %d of expert %d holds row %d of expert %d", t, expert[t], row, owner[row]);
-            ++hits[row];
-            prev = row;
+    const SmallMap sm = small_map(l, nseg, R, n_local, gather, bm, max_tiles);
+    // (without gathering an empty segment of no known expert ends a run above, but not here)
+    if (sm.n_tiles > nt || (gather && sm.n_tiles != nt)) return moe_set_error(MOE_EINTERNAL, "%d tiles, and %d from the map of few segments", nt, sm.n_tiles);
+    MapArrays small(sm.n_tiles);
+    for (int t = 0; t < sm.n_tiles; ++t) {
+        const SmallTile r = small_tile(l, sm, t, bm);
+        small.m.row0[t] = r.row0;
+        small.m.nrows[t] = r.nrows;
+        small.m.expert[t] = r.expert;
+        small.m.gather[t] = r.gather;
+        if (!r.gather) continue;
+        for (unsigned long long in = r.in; in; in &= in - 1) {
+            const SmallRun run = small_run(l, r, __builtin_ctzll(in));
+            for (int v = run.lo; v < run.hi; ++v)
+                if (!small.enter((size_t)t * kRelPitch + v, run.val + v)) return MOE_EINTERNAL;
         }
-        if (gaps != (gat[t] != 0)) return moe_set_error(MOE_EINTERNAL, "tile %d: gather flag %d but gaps %d", t, gat[t], (int)gaps);
     }
-    for (int r = 0; r < R; ++r)
-        if (hits[r] != (owner[r] >= 0 ? 1 : 0)) return moe_set_error(MOE_EINTERNAL, "row %d is in %d tiles", r, hits[r]);
-    return nt;
+    rc = check_map(small, sm.n_tiles, seg_offset, seg_expert, nseg, R, bm, n_local, gather);
+    return rc != MOE_OK ? rc : nt;
 }
 
 extern "C" size_t moe_ffn_workspace_bytes(int32_t R_max, int32_t H, int32_t F, int32_t act, int32_t dtype) {

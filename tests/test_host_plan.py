@@ -365,6 +365,16 @@ def test_tile_map_gathers_the_segments_of_an_expert():
         experts = [int(v) for v in r.integers(-1, n_local + 1, size=nseg)]       # -1 and n_local: skipped
         for gather in (0, 1):
             assert run(lens, experts, n_local, bm, gather) == need(lens, experts, n_local, bm, gather)
+    # lists of up to 64 segments are mapped by lanes of a wave: every tile height, both sides of the last lane
+    for nseg in (1, 2, 63, 64, 65):
+        for _ in range(60):
+            n_local = int(r.integers(1, 65))
+            bm = int(r.choice([32, 64, 128, 192, 256]))
+            lens = [int(v) for v in r.choice([0, 1, 31, 32, 33, 100, 191, 192, 193, 256, 257, 600], size=nseg)]
+            experts = [int(v) for v in r.integers(-2, n_local + 2, size=nseg)]
+            for gather in (0, 1):
+                assert run(lens, experts, n_local, bm, gather) == need(lens, experts, n_local, bm, gather)
+                run(lens, experts, n_local, bm, gather, R=max(1, sum(lens) - int(r.integers(0, 700))))
     # offsets past R are clamped; 1024 segments of one row each
     assert run([10, 10, 10], [0, 1, 0], 2, 256, 1, R=25) == 2
     assert run([1] * 1024, [i % 3 for i in range(1024)], 3, 256, 1) == 2 + 2 + 2
