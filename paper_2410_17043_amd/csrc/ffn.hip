@@ -345,7 +345,8 @@ __host__ __device__ __forceinline__ SmallMap small_map(W& w, int nseg, int R, in
     using S = SmallItem;
     w.each([&](S& s, int lane) {
         s.lo = s.off0 > 0 ? s.off0 : 0;
-        s.len = (s.off1 < R ? s.off1 : R) - s.lo;
+        const int hi = s.off1 < R ? s.off1 : R;
+        s.len = hi > s.lo ? hi - s.lo : 0;                             // (of offsets that fall by 2^31 the difference would wrap)
         s.ok = lane < nseg && s.e >= 0 && s.e < n_local && s.len > 0;  // others are skipped
     });
     // items: the segments by (expert, index) - without gathering by index - first, the skipped ones behind them

@@ -375,6 +375,19 @@ def test_tile_map_gathers_the_segments_of_an_expert():
             for gather in (0, 1):
                 assert run(lens, experts, n_local, bm, gather) == need(lens, experts, n_local, bm, gather)
                 run(lens, experts, n_local, bm, gather, R=max(1, sum(lens) - int(r.integers(0, 700))))
+    # lists that are no segment list: offsets that fall, far below zero or past every row.  No tile may leave [0, R)
+    def tiles(off, experts, R, gather):
+        off, ex = np.array(off, dtype=np.int32), np.array(experts, dtype=np.int32)
+        rc = fn(off.ctypes.data_as(C.POINTER(C.c_int32)), ex.ctypes.data_as(C.POINTER(C.c_int32)), len(ex), R, 64, 2, gather)
+        assert rc >= 0, lib.moe_last_error()
+        return rc
+
+    lowest, highest = -2 ** 31, 2 ** 31 - 1
+    for gather in (0, 1):
+        assert tiles([5, lowest, 10], [0, 1], 20, gather) == 1
+        assert tiles([highest, -5, 10], [0, 1], 20, gather) == 1
+        assert tiles([lowest, highest], [0], 20, gather) == 1
+        assert tiles([highest, lowest], [0], 20, gather) == 0
     # offsets past R are clamped; 1024 segments of one row each
     assert run([10, 10, 10], [0, 1, 0], 2, 256, 1, R=25) == 2
     assert run([1] * 1024, [i % 3 for i in range(1024)], 3, 256, 1) == 2 + 2 + 2
