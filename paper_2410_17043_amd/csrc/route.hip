@@ -15,6 +15,7 @@
 //   route_mfma_kernel   every token in fp64 on the fp64 matrix cores: fp32 inputs and any H.
 #include "common.h"
 #include <algorithm>
+#include <type_traits>
 
 namespace {
 
@@ -368,18 +369,27 @@ __global__ __launch_bounds__(MAXT) void route_bf16_kernel(const uint16_t* __rest
 #pragma unroll
                     for (int i = 0; i < 4; ++i) zpart[((size_t)(wave * NG + n - n0) * TP + m * 16 + 4 * g + i) * 16 + r] = acc[m][n][i];
             __syncthreads();
-            // the S parts of an element: all reads first (a loop over S would wait for each in turn), sum in wave order
-            for (int q = threadIdx.x; q < NG * TP * 16; q += blockDim.x) {
-                const int tt = (q >> 4) % TP, e = e0 + (n0 + (q >> 4) / TP) * 16 + (q & 15);
-                double part[kRouteMaxWaves];
+            // the S parts of an element: all reads first (a loop over S would wait for each in turn), sum in wave order.  S is
+            // a power of two; a copy for each, because the few waves of a short row walk through most elements one after
+            // the other (H = 32, E = 256: 30.9 us with the absent waves' parts read under conditions, 16.8 so)
+            auto add_parts = [&](auto waves) {
+                constexpr int NW = decltype(waves)::value;
+                for (int q = threadIdx.x; q < NG * TP * 16; q += blockDim.x) {
+                    const int tt = (q >> 4) % TP, e = e0 + (n0 + (q >> 4) / TP) * 16 + (q & 15);
+                    double part[NW];
 #pragma unroll
-                for (int w = 0; w < kRouteMaxWaves; ++w) part[w] = (w < S) ? zpart[(size_t)w * NG * TP * 16 + q] : 0.0;
-                double sum = part[0];
+                    for (int w = 0; w < NW; ++w) part[w] = zpart[(size_t)w * NG * TP * 16 + q];
+                    double sum = part[0];
 #pragma unroll
-                for (int w = 1; w < kRouteMaxWaves; ++w)
-                    if (w < S) sum += part[w];
-                if (e < E) zl[(size_t)tt * ZP + e] = sum + bias_l[e];
-            }
+                    for (int w = 1; w < NW; ++w) sum += part[w];
+                    if (e < E) zl[(size_t)tt * ZP + e] = sum + bias_l[e];
+                }
+            };
+            if (S == kRouteMaxWaves) add_parts(std::integral_constant<int, kRouteMaxWaves>{});
+            else if (S == 8) add_parts(std::integral_constant<int, 8>{});
+            else if (S == 4) add_parts(std::integral_constant<int, 4>{});
+            else if (S == 2) add_parts(std::integral_constant<int, 2>{});
+            else add_parts(std::integral_constant<int, 1>{});
             if (n0 == 0) {
                 for (int q = threadIdx.x; q < EP + (e0 == 0 ? TP : 0); q += blockDim.x) {
                     const bool is_w = q < EP;

@@ -52,6 +52,10 @@ ROUTE_CASES = [
     small("c5_finegrained", T=20, H=64, E=33, k=16, G=3),
     small("c2_mixtral", T=12801, H=32, E=18, k=16, G=6),
     small("c2_mixtral", T=12801, H=32, E=40, k=9, G=8),
+    # more than 64 experts: one, two and four waves per block
+    small("c2_mixtral", T=33, H=32, E=256, k=2, G=8),
+    small("c2_mixtral", T=18, H=96, E=65, k=4, G=5),
+    small("c2_mixtral", T=18, H=160, E=128, k=1, G=8),
 ]
 
 
