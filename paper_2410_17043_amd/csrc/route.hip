@@ -85,7 +85,7 @@ __device__ __forceinline__ int piece_slot(int r, int c) { return (r << 2) + (c ^
 // rounding of the norms.  A GPU test feeds adversarial operands to the same instruction and holds it to this bound.
 constexpr float kLogitErr = 1.05f * 3.814697265625e-6f;     // 1.05 * 2^-18, per MFMA of a chain
 
-// Exchanges inside a group of L = 4 or 16 neighbouring lanes by data-parallel-primitive moves (no trip through
+// Exchanges inside a group of L = 4 or 16 neighbouring lanes (or of a wave: two shuffles first) by data-parallel-primitive moves (no trip through
 // the LDS crossbar, unlike a general shuffle): for a quad the lane whose index differs in bit 0 or 1, for a
 // row of 16 the lane N places further round the row.  Combining a value with its partners at distances
 // L/2, ..., 2, 1 leaves every lane of the group with the combination over the whole group.
@@ -97,7 +97,8 @@ template <int CTRL> __device__ __forceinline__ double dpp_move(double v) {
 constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E;       // quad_perm [1,0,3,2] and [2,3,0,1]
 constexpr int kRowRor1 = 0x121, kRowRor2 = 0x122, kRowRor4 = 0x124, kRowRor8 = 0x128;
 template <int L> __device__ __forceinline__ float group_sum(float v) {
-    if (L == 16) { v += dpp_move<kRowRor8>(v); v += dpp_move<kRowRor4>(v); v += dpp_move<kRowRor2>(v); v += dpp_move<kRowRor1>(v); }
+    if (L == 64) { v += __shfl_xor(v, 32, 64); v += __shfl_xor(v, 16, 64); }
+    if (L >= 16) { v += dpp_move<kRowRor8>(v); v += dpp_move<kRowRor4>(v); v += dpp_move<kRowRor2>(v); v += dpp_move<kRowRor1>(v); }
     else { v += dpp_move<kQuadXor2>(v); v += dpp_move<kQuadXor1>(v); }
     return v;
 }
@@ -114,7 +115,7 @@ __device__ __forceinline__ void wave_lds_order() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Selection for one token by a group of L neighbouring lanes (sub = 0..L-1; lane `sub` looks after experts sub,
+// Selection for one token by a group of L = 4, 16 or 64 neighbouring lanes (sub = 0..L-1; lane `sub` looks after experts sub,
 // sub + L, ..., at most NC of them, read once from zr[0..E) in LDS): the k + 1 largest, ties to the lower index;
 // softmax weights; returns whether every gap between consecutive ones exceeds min_gap (a negative min_gap: only
 // the k largest are extracted and the answer means nothing), and the k-th largest in *kth.  sel: LDS scratch of this
@@ -139,7 +140,8 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
         cv[i] = live[i] ? zr[sub + L * i] : 0.0;
     }
     const int n_take = min(min_gap >= 0.0 ? k + 1 : k, E);   // a negative min_gap: no gaps wanted, the k largest only
-    double zmax = 0.0, prev = 0.0;
+    double zmax = 0.0, prev = 0.0, my_z = 0.0;
+    int my_e = 0;
     bool safe = true;
     for (int j = 0; j < n_take; ++j) {
         double best = 0.0;
@@ -147,22 +149,29 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
 #pragma unroll
         for (int i = 0; i < NC; ++i)
             if (live[i] && (best_e == 0x7fffffff || cv[i] > best)) { best = cv[i]; best_e = sub + L * i; }
-#define MOE_GROUP_STEP(CTRL)                                                                                    \
-        {                                                                                                       \
-            const double ob = dpp_move<CTRL>(best);                                                             \
-            const int oe = dpp_move<CTRL>(best_e);                                                              \
-            if ((oe != 0x7fffffff) && (best_e == 0x7fffffff || ob > best || (ob == best && oe < best_e))) { best = ob; best_e = oe; } \
+        auto step = [&](double ob, int oe) {
+            if (L == 64) {                                   // branch-free: nothing else runs beside the one wave of a token
+                const bool take = (oe != 0x7fffffff) & ((best_e == 0x7fffffff) | (ob > best) | ((ob == best) & (oe < best_e)));
+                best = take ? ob : best;
+                best_e = take ? oe : best_e;
+            } else if ((oe != 0x7fffffff) && (best_e == 0x7fffffff || ob > best || (ob == best && oe < best_e))) {
+                best = ob;
+                best_e = oe;
+            }
+        };
+        if (L == 64) {
+            step(__shfl_xor(best, 32, 64), __shfl_xor(best_e, 32, 64));
+            step(__shfl_xor(best, 16, 64), __shfl_xor(best_e, 16, 64));
         }
-        if (L == 16) {
-            MOE_GROUP_STEP(kRowRor8)
-            MOE_GROUP_STEP(kRowRor4)
-            MOE_GROUP_STEP(kRowRor2)
-            MOE_GROUP_STEP(kRowRor1)
+        if (L >= 16) {
+            step(dpp_move<kRowRor8>(best), dpp_move<kRowRor8>(best_e));
+            step(dpp_move<kRowRor4>(best), dpp_move<kRowRor4>(best_e));
+            step(dpp_move<kRowRor2>(best), dpp_move<kRowRor2>(best_e));
+            step(dpp_move<kRowRor1>(best), dpp_move<kRowRor1>(best_e));
         } else {
-            MOE_GROUP_STEP(kQuadXor2)
-            MOE_GROUP_STEP(kQuadXor1)
+            step(dpp_move<kQuadXor2>(best), dpp_move<kQuadXor2>(best_e));
+            step(dpp_move<kQuadXor1>(best), dpp_move<kQuadXor1>(best_e));
         }
-#undef MOE_GROUP_STEP
 #pragma unroll
         for (int i = 0; i < NC; ++i)
             if (sub + L * i == best_e) live[i] = false;
@@ -170,10 +179,15 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
         else if (!(prev - best > min_gap)) safe = false;
         prev = best;
         if (j == k - 1) *kth = best;
-        if (j < k && sub == 0) { sz[j] = best; se[j] = best_e; }
+        if (L == 64) {                                   // choice j stays in lane j
+            if (sub == j) { my_z = best; my_e = best_e; }
+        } else if (j < k && sub == 0) {
+            sz[j] = best;
+            se[j] = best_e;
+        }
     }
-    constexpr int NP = FP32_WEIGHTS ? 4 : 1;             // part q: lane sub + 16 q of the 64
-    static_assert(!FP32_WEIGHTS || L == 16, "");
+    constexpr int NP = FP32_WEIGHTS && L == 16 ? 4 : 1;  // part q: lane sub + 16 q of the 64
+    static_assert(!FP32_WEIGHTS || L >= 16, "");
     float part[NP];
 #pragma unroll
     for (int q = 0; q < NP; ++q) part[q] = 0.f;
@@ -182,14 +196,15 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
         if (sub + L * i < E) part[i % NP] += __expf((float)(cv[i] - zmax));
     const float den = group_sum<L>(NP == 1 ? part[0] : (part[0] + part[2 % NP]) + (part[1 % NP] + part[3 % NP]));
     wave_lds_order();                                    // the group lies inside one wave
-    float wj[MOE_MAX_K / L];
+    constexpr int PER = (MOE_MAX_K + L - 1) / L;
+    float wj[PER];
 #pragma unroll
-    for (int m = 0; m < MOE_MAX_K / L; ++m) {
+    for (int m = 0; m < PER; ++m) {
         const int j = sub + L * m;
         wj[m] = 0.f;
         if (j < k) {
-            wj[m] = __expf((float)(sz[j] - zmax)) / den;
-            topk_idx[(size_t)t * k + j] = se[j];
+            wj[m] = __expf((float)((L == 64 ? my_z : sz[j]) - zmax)) / den;
+            topk_idx[(size_t)t * k + j] = L == 64 ? my_e : se[j];
             sw[j] = wj[m];
         }
     }
@@ -203,7 +218,7 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
         scale = 1.f / wsum;
     }
 #pragma unroll
-    for (int m = 0; m < MOE_MAX_K / L; ++m)
+    for (int m = 0; m < PER; ++m)
         if (sub + L * m < k) topk_w[(size_t)t * k + sub + L * m] = wj[m] * scale;
     return safe;
 }
@@ -591,10 +606,17 @@ __global__ __launch_bounds__(NT == 1 ? 1024 : 512) void route_mfma_kernel(const 
         __syncthreads();
     }
     unsigned char* sel = reinterpret_cast<unsigned char*>(zpart);   // [16][kSelPitch]
-    for (int tt = threadIdx.x >> 4; tt < 16 && tok0 + tt < T; tt += blockDim.x >> 4) {
-        double kth = 0.0;
-        select_group<NC, 16, true>(zl + (size_t)tt * ZP, E, k, renorm, tok0 + tt, threadIdx.x & 15, -1.0, sel + tt * kSelPitch, topk_idx, topk_w, &kth);
+    // more than 64 experts: a wave per token while there is one for each (four candidates per lane, a shorter chain per
+    // extraction: one token of 128 experts, k = 11, 17.9 us with 16 lanes, 12.9 so), 16 lanes per token otherwise.  The results are the same bits
+    const int n_tok = min(16, T - tok0);
+    double kth = 0.0;
+    if (NC > 4 && n_tok <= S) {
+        if (wave < n_tok)
+            select_group<(NC + 3) / 4, 64, true>(zl + (size_t)wave * ZP, E, k, renorm, tok0 + wave, lane, -1.0, sel + wave * kSelPitch, topk_idx, topk_w, &kth);
+        return;
     }
+    for (int tt = threadIdx.x >> 4; tt < n_tok; tt += blockDim.x >> 4)
+        select_group<NC, 16, true>(zl + (size_t)tt * ZP, E, k, renorm, tok0 + tt, threadIdx.x & 15, -1.0, sel + tt * kSelPitch, topk_idx, topk_w, &kth);
 }
 
 template <int DT, int NT, int PF, int NC>

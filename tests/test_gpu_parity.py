@@ -56,6 +56,11 @@ ROUTE_CASES = [
     small("c2_mixtral", T=33, H=32, E=256, k=2, G=8),
     small("c2_mixtral", T=18, H=96, E=65, k=4, G=5),
     small("c2_mixtral", T=18, H=160, E=128, k=1, G=8),
+    # ... and in fp64: a wave per token while there is one for each, then 16 lanes
+    small("c1_tiny_fp32", T=1, H=100, E=65, k=16, G=5),
+    small("c1_tiny_fp32", T=8, H=512, E=256, k=7, G=8),
+    small("c1_tiny_fp32", T=9, H=512, E=256, k=7, G=8),
+    small("c1_tiny_fp32", T=18, H=512, E=130, k=2, G=2),
 ]
 
 
@@ -91,10 +96,11 @@ def lane_tree(v):
     return v
 
 
+@pytest.mark.parametrize("T", [333, 3])
 @pytest.mark.parametrize("E,k,dtype,H_", [(16, 4, "fp32", 64), (5, 5, "fp32", 36), (64, 16, "fp32", 100), (200, 9, "fp32", 36), (24, 3, "bf16", 40)])
-def test_renormalised_weights_of_the_fp32_gate_are_quotients_rounded_once(H, E, k, dtype, H_):
+def test_renormalised_weights_of_the_fp32_gate_are_quotients_rounded_once(H, T, E, k, dtype, H_):
     """With the probabilities p (renorm = 0) of the same inputs: w = fl(p / sum p), to the bit."""
-    cfg = small("c1_tiny_fp32", T=333, H=H_, E=E, k=k, G=1)
+    cfg = small("c1_tiny_fp32", T=T, H=H_, E=E, k=k, G=1)
     cfg = dataclasses.replace(cfg, dtype=dtype, renorm=0)
     r = np.random.default_rng(E)
     x, wg = H.dev(r.standard_normal((cfg.T, H_)), dtype), H.dev(0.2 * r.standard_normal((E, H_)), dtype)
