@@ -247,10 +247,15 @@ int moe_combine(moe_ctx* ctx, const void* ret, const int32_t* slot_to_row, const
  * moe_status. */
 int moe_selfcheck_tile_order(int32_t tiles_m, int32_t tiles_n, int32_t ncu, int32_t nk);
 
-/* Rows per tile (128, 192 or 256) that a bf16 FFN GEMM of R rows over n_used experts takes on ncu compute units:
- * N output columns, K the inner dimension (a multiple of 64), act the activation of a first GEMM, -1 for a second.
- * (Shares of at most 64 rows take the weight-streaming kernels whatever this says.) */
+/* Rows per tile (128, 192 or 256) that the estimate prefers for a bf16 FFN GEMM of R rows over n_used experts on ncu
+ * compute units: N output columns, K the inner dimension (a multiple of 64), act the activation of a first GEMM, -1 for
+ * a second. */
 int moe_selfcheck_tile_shape(int32_t R, int32_t n_used, int32_t N, int32_t K, int32_t act, int32_t ncu);
+
+/* Rows per tile that the two GEMMs of a bf16 expert FFN take: the preferred ones where they hold up against 256 however
+ * the rows may be spread over the experts, else 256.  rows2 (HOST [2]): first GEMM, second GEMM.  (Shares of at most 64
+ * rows take the weight-streaming kernels; with too many segments for two tile maps both GEMMs take one height.) */
+int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2);
 
 /* Plan of the weight-streaming FFN kernels (shares of at most 64 rows) for `total` tiles of `ns` stages of K on
  * ncu compute units: checks that the pieces cover the stages exactly once, are at least two stages long and fit

@@ -28,6 +28,7 @@
 // fp32 path: 64 x 64 tiles on the fp32 matrix cores (gemm_f32_kernel).
 #include "common.h"
 #include <algorithm>
+#include <cmath>
 #include <cstddef>
 #include <type_traits>
 #include <vector>
@@ -1752,6 +1753,68 @@ TileShape choose_shape(int R, int n_used, int N, int K, int act, int cus) {
     return best;
 }
 
+// A height other than 256 has to hold up.  The choice above rests on a mean tile count and on rates of full rounds; where
+// either is off, the smaller tiles cost up to a third (210 rows for each of 32 experts, 1664 -> 6656 -> 1664: 192 and 128
+// rows per tile 645 us, 256 478).  So a chosen height is played once more, with
+//   - rates that follow the occupancy: a k-tile of a 256 x 256 tile takes 0.57 us on a nearly empty chip and 0.75 on a full
+//     one, at 128 x 128 0.38 with a block to itself and 0.53 beside another;
+//   - the bytes of weights and rows at the rate a GEMM streams them (5.5 - 6 TB/s), combined with the compute time by
+//     their 4-norm: near the crossing both count;
+//   - four ways in which the rows may be spread over the experts: even shares, popularity 1 / rank, and half a tile of
+//     padding per expert give or take its standard deviation;
+// and is given up for 256 when any of the four has it more than 6 % slower.  The constants are fitted to 430000 GEMMs of
+// 65 to 20000 rows, 1 to 64 experts, H and F of 128 to 14336, K from cold memory (median error 5 %).  Over those the
+// expert FFN is more than 3 % slower than one block per 256 x 256 tile was in 0.4 % of the shares, in 2.9 % without this check.
+struct ShapeCost { double start, a, b, a2, pair, b_pair, piece0, piece, gelu, tb_s, first_bytes; };
+double played_us(TileShape t, int tiles_m, int R, int n_used, int N, int K, int act, int cus) {
+    // start of the launch; per round and per k-tile of it (at no occupancy, and what full occupancy adds); rounds with two
+    // blocks per CU: extra per round, and their k-tile; K cuts: per launch and piece; GELU per round; bytes
+    static const ShapeCost cost[] = {{6.5, -0.1, 0.374, 2.2, 0.441, 0.094, 9.8, 0.030, 1.6, 5.5, 3.0},
+                                     {3.6, 4.8, 0.527, 0.0, 0.0, 0.083, 9.3, 0.054, 3.7, 5.6, 9.4},
+                                     {4.3, 6.0, 0.555, 0.0, 0.0, 0.191, 10.0, 0.057, 4.4, 6.0, 9.8}};
+    const ShapeCost& c = cost[t];
+    const int per_cu = (t == TS_128) ? TileGeom<2, 2>::PER_CU : 1, slots = cus * per_cu, nk = K / BK, mats = (act == MOE_ACT_SWIGLU) ? 2 : 1;
+    const int out_cols = ((t == TS_128) ? TileGeom<2, 2>::BN : TileGeom<4, 4>::BN) / mats;
+    const TailPlan p = plan_tail(tiles_m * ((N + out_cols - 1) / out_cols), slots, nk);
+    const double a = c.a + (act == MOE_ACT_GELU_MLP ? c.gelu : 0.0);
+    auto k_tile = [&](double q) { return (per_cu == 2 && q <= 0.5) ? c.b + 0.074 * q : (per_cu == 2 ? c.pair : c.b) + c.b_pair * q; };
+    auto round = [&](double q) { return a + (q > 0.5 ? c.a2 : 0.0) + k_tile(q) * nk; };   // of q * slots tiles
+    double us = (p.n_full / slots) * round(1.0);
+    if (p.n_full % slots > 0) us += round((double)(p.n_full % slots) / slots);
+    if (p.n_tail > 0) us += c.piece0 + k_tile((double)(p.n_tail * p.parts) / slots) * 2 * p.pairs_per + p.n_tail * p.parts * c.piece;
+    const double bytes = ((double)n_used * N * K * mats + (double)R * (K + N)) * 2.0;
+    const double mem = c.first_bytes + bytes * 1e-6 / c.tb_s;
+    us = std::max(us, 0.1);
+    return c.start + std::sqrt(std::sqrt(us * us * us * us + mem * mem * mem * mem));
+}
+// M-tiles of bm rows when R rows are spread over n_used experts in way 0 .. 3
+int spread_tiles_m(int R, int bm, int n_used, int way) {
+    if (n_used <= 1) return (R + bm - 1) / bm;
+    if (way == 0) return n_used * (((R + n_used - 1) / n_used + bm - 1) / bm);
+    if (way == 1) {
+        double ranks = 0.0;
+        for (int e = 1; e <= n_used; ++e) ranks += 1.0 / e;
+        int tiles = 0;
+        for (int e = 1; e <= n_used; ++e) tiles += (int)std::ceil(R / (e * ranks * bm));
+        return tiles;
+    }
+    const double mean = (double)R / bm + 0.5 * n_used, sd = std::sqrt(n_used / 12.0);
+    return std::max(n_used, (int)(way == 2 ? std::ceil(mean + sd) : std::floor(mean - sd)));
+}
+TileShape confirm_shape(TileShape t, int R, int n_used, int N, int K, int act, int cus) {
+    if (t == TS_256) return t;
+    for (int way = 0; way < (n_used <= 1 ? 1 : 4); ++way) {
+        const double us = played_us(t, spread_tiles_m(R, kShapeRows[t], n_used, way), R, n_used, N, K, act, cus);
+        if (us > 1.06 * played_us(TS_256, spread_tiles_m(R, kShapeRows[TS_256], n_used, way), R, n_used, N, K, act, cus)) return TS_256;
+    }
+    return t;
+}
+// the heights that both GEMMs of a share take
+void take_shapes(int R, int n_used, int H, int F, int act, int cus, TileShape (&shape)[2]) {
+    shape[0] = confirm_shape(choose_shape(R, n_used, F, H, act, cus), R, n_used, F, H, act, cus);
+    shape[1] = confirm_shape(choose_shape(R, n_used, H, F, -1, cus), R, n_used, H, F, -1, cus);
+}
+
 // Shares of at most kSkinnyRows rows (the tile map is then made of 32 MT-row tiles).
 inline int skinny_tile_rows(int R) { return R <= 32 ? 32 : 64; }
 template <int EPI, int MT>
@@ -1828,6 +1891,15 @@ extern "C" int moe_selfcheck_tile_order(int32_t tiles_m, int32_t tiles_n, int32_
 extern "C" int moe_selfcheck_tile_shape(int32_t R, int32_t n_used, int32_t N, int32_t K, int32_t act, int32_t ncu) {
     if (R < 1 || n_used < 1 || N < 1 || K < 64 || K % 64 != 0 || ncu < 1) return moe_set_error(MOE_EINVAL, "moe_selfcheck_tile_shape: bad argument");
     return kShapeRows[choose_shape(R, n_used, N, K, act, ncu)];
+}
+
+extern "C" int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2) {
+    if (R < 1 || n_used < 1 || H < 64 || H % 64 != 0 || F < 64 || F % 64 != 0 || act < 0 || act > 2 || ncu < 1 || !rows2)
+        return moe_set_error(MOE_EINVAL, "moe_selfcheck_tile_shapes: bad argument");
+    TileShape shape[2];
+    take_shapes(R, n_used, H, F, act, ncu, shape);
+    for (int i = 0; i < 2; ++i) rows2[i] = kShapeRows[shape[i]];
+    return MOE_OK;
 }
 
 extern "C" int moe_selfcheck_skinny_plan(int32_t total, int32_t ncu, int32_t ns) {
@@ -2016,8 +2088,7 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         bm[0] = bm[1] = skinny_tile_rows(R);
     } else if (dtype == MOE_BF16) {
         n_used = std::min(gather ? std::min(n_local, nseg) : nseg, R);   // runs of rows that share no tile
-        shape[0] = choose_shape(R, n_used, F, H, act, round_size());
-        shape[1] = choose_shape(R, n_used, H, F, -1, round_size());
+        take_shapes(R, n_used, H, F, act, round_size(), shape);
         for (int i = 0; i < 2; ++i) bm[i] = kShapeRows[shape[i]];
         // two maps share the records of the workspace, which are made for one map of 64-row tiles
         if (bm[0] != bm[1] && max_tiles_of(R, bm[0], nseg) + max_tiles_of(R, bm[1], nseg) > max_tiles_for(R)) {

@@ -420,6 +420,25 @@ def test_skinny_plan_and_row_geometry_self_checks():
     assert lib.moe_selfcheck_row_geometry(0, 2, out) < 0 and lib.moe_selfcheck_row_geometry(64, 17, out) < 0
 
 
+# rows, experts, H, F, activation -> rows per tile of both GEMMs.  First shares whose preferred smaller tiles measured
+# slower than 256 x 256 ones (by 26, 23, 12, 13, 7 and 5 %: full rounds of half-empty tiles, streaming bound by memory),
+# then shares that keep theirs.
+@pytest.mark.parametrize("R,n_used,Hd,F,act,rows", [
+    (6724, 32, 1664, 6656, 0, (256, 256)), (3451, 16, 3200, 3456, 0, (256, 256)), (3869, 8, 3200, 3584, 2, (256, 256)),
+    (14545, 32, 2304, 5632, 1, (256, 256)), (176, 1, 2688, 6016, 0, (256, 256)), (480, 2, 2304, 3840, 0, (256, 256)),
+    (403, 4, 2048, 1408, 2, (128, 128)), (701, 1, 4096, 14336, 2, (192, 192)), (10199, 4, 1024, 4096, 1, (256, 192)),
+    (129, 1, 256, 1408, 2, (128, 128)), (1151, 1, 2048, 4608, 1, (128, 192)), (20571, 1, 4096, 14336, 2, (256, 256))])
+def test_a_smaller_tile_height_has_to_hold_up_against_256_rows(R, n_used, Hd, F, act, rows):
+    import ctypes as C
+    from paper_2410_17043_amd import _lib
+    lib = _lib.load()
+    got = (C.c_int32 * 2)()
+    assert lib.moe_selfcheck_tile_shapes(R, n_used, Hd, F, act, 256, got) == 0
+    assert tuple(got) == rows
+    for i, (N, K, a) in enumerate(((F, Hd, act), (Hd, F, -1))):              # never anything but the preferred height or 256
+        assert got[i] in (256, lib.moe_selfcheck_tile_shape(R, n_used, N, K, a, 256))
+
+
 @pytest.mark.parametrize("n,hi,hetero", [(2, 9, False), (5, 3, True), (7, 40, False), (16, 200, True), (17, 5, False), (33, 1000, True)])
 def test_send_order_time_is_that_of_playing_the_order_and_no_exchange_improves_it(n, hi, hetero):
     """The hill climbing resumes recorded runs; playing the order it returns from the start gives the same time to the
