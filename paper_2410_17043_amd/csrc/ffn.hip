@@ -44,7 +44,7 @@ struct TileMap {
     int32_t* expert;    // [max_tiles] local expert
     int32_t* gather;    // [max_tiles] 0: the tile is rows row0 .. row0 + nrows - 1; 1: row r is row0 + rel[tile][r]
     int32_t* rel;       // [max_tiles][kRelPitch] row offsets of the gathered tiles (written for those only)
-    int32_t* done;      // [kMaxSplitTiles] pieces that have arrived, per tile cut along K (zeroed with the map); NULL: no tile is cut
+    int32_t* done;      // [kMaxSplitTiles] pieces that have arrived, per tile cut along K (zeroed with the map; bf16)
 };
 constexpr int kMaxSplitTiles = 256;
 constexpr int kRelPitch = 256;
@@ -77,7 +77,7 @@ TileMap tilemap_at(void* ws, int R, int which = 0, int first = 0) {
     m.done = nullptr;
     return m;
 }
-inline int max_tiles_of(int R, int bm, int nseg) { return (R + bm - 1) / bm + nseg; }
+inline int max_tiles_of(int R, int bm, int nseg) { return std::min((R + bm - 1) / bm + nseg, R); }   // a tile has a row at least
 
 // Tile map.  The received rows come as segments (rows seg_offset[i] .. seg_offset[i+1] - 1 belong to local
 // expert seg_expert[i]); with several sources and several local experts the segments of one expert are not
@@ -1517,7 +1517,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_skinny_kernel(const uint16_t
     const int n_tiles_m = *m.n_tiles;
     const int total = n_tiles_m * tiles_n;
     const int ns_all = K / SKW;
-    const SkinnyPlan plan = m.done ? plan_skinny(total, ncu, ns_all) : SkinnyPlan{1, ns_all};
+    const SkinnyPlan plan = plan_skinny(total, ncu, ns_all);
     if ((int)blockIdx.x >= total * plan.parts) return;
     const int piece = blockIdx.x / total, tile_id = skinny_tile(blockIdx.x % total, total);
     const int tile_m = tile_id % n_tiles_m, tile_n = tile_id / n_tiles_m;
@@ -1682,9 +1682,8 @@ int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab
     // The tile count is only known on the device: the most tail tiles over every count that n_used runs of rows which
     // share no tile can give.  A list that leaves rows out may have fewer tiles; its tail is cut if it fits as well.
     int most_tail = 0;
-    if (!TG::SUM_IN_PLACE || m.done)
-        for (int t = (R + TG::BM - 1) / TG::BM, hi = (R + n_used * (TG::BM - 1)) / TG::BM; t <= hi; ++t)
-            most_tail = std::max(most_tail, plan_tail(t * tiles_n, ncu, K / BK).n_tail);
+    for (int t = (R + TG::BM - 1) / TG::BM, hi = (R + n_used * (TG::BM - 1)) / TG::BM; t <= hi; ++t)
+        most_tail = std::max(most_tail, plan_tail(t * tiles_n, ncu, K / BK).n_tail);
     hipLaunchKernelGGL((gemm_bf16_kernel<EPI, MI, NJ, TIMED>), dim3(ncu), dim3(256), TG::LDS, st,
                        reinterpret_cast<const uint16_t*>(A), lda, m, tab, which0, which1, N, K,
                        reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, most_tail, partial, marks,
@@ -1809,10 +1808,22 @@ TileShape confirm_shape(TileShape t, int R, int n_used, int N, int K, int act, i
     }
     return t;
 }
-// the heights that both GEMMs of a share take
-void take_shapes(int R, int n_used, int H, int F, int act, int cus, TileShape (&shape)[2]) {
+// The records that the maps of two heights take of the workspace, which has room for one map of 64-row tiles, and whether
+// two more stay free: the counters of the tiles that are cut along K (2 x 256) lie there.
+static_assert(2 * kMaxSplitTiles == 2 * kRelPitch, "two rows of the offset table");
+bool maps_fit(int R, int nseg, int bm0, int bm1) {
+    return max_tiles_of(R, bm0, nseg) + (bm0 == bm1 ? 0 : max_tiles_of(R, bm1, nseg)) + 2 <= max_tiles_for(R);
+}
+// The heights that both GEMMs of a share take.  With too many segments for two maps: one height, the first GEMM's if it
+// holds up for the second as well.  (The map of one height always fits: up to 255 rows there are fewer tiles than rows,
+// from 256 on at least two records more than ceil(R / 128) + 1024.)
+void take_shapes(int R, int n_used, int nseg, int H, int F, int act, int cus, TileShape (&shape)[2]) {
     shape[0] = confirm_shape(choose_shape(R, n_used, F, H, act, cus), R, n_used, F, H, act, cus);
     shape[1] = confirm_shape(choose_shape(R, n_used, H, F, -1, cus), R, n_used, H, F, -1, cus);
+    if (!maps_fit(R, nseg, kShapeRows[shape[0]], kShapeRows[shape[1]])) {
+        shape[0] = confirm_shape(shape[0], R, n_used, H, F, -1, cus);
+        shape[1] = shape[0];
+    }
 }
 
 // Shares of at most kSkinnyRows rows (the tile map is then made of 32 MT-row tiles).
@@ -1893,12 +1904,17 @@ extern "C" int moe_selfcheck_tile_shape(int32_t R, int32_t n_used, int32_t N, in
     return kShapeRows[choose_shape(R, n_used, N, K, act, ncu)];
 }
 
-extern "C" int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2) {
-    if (R < 1 || n_used < 1 || H < 64 || H % 64 != 0 || F < 64 || F % 64 != 0 || act < 0 || act > 2 || ncu < 1 || !rows2)
+extern "C" int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2) {
+    if (R < 1 || n_used < 1 || nseg < n_used || nseg > kMaxSeg || H < 64 || H % 64 != 0 || F < 64 || F % 64 != 0 || act < 0 || act > 2 || ncu < 1 || !rows2)
         return moe_set_error(MOE_EINVAL, "moe_selfcheck_tile_shapes: bad argument");
-    TileShape shape[2];
-    take_shapes(R, n_used, H, F, act, ncu, shape);
-    for (int i = 0; i < 2; ++i) rows2[i] = kShapeRows[shape[i]];
+    if (R <= kSkinnyRows) {
+        rows2[0] = rows2[1] = skinny_tile_rows(R);
+    } else {
+        TileShape shape[2];
+        take_shapes(R, n_used, nseg, H, F, act, ncu, shape);
+        for (int i = 0; i < 2; ++i) rows2[i] = kShapeRows[shape[i]];
+    }
+    if (!maps_fit(R, nseg, rows2[0], rows2[1])) return moe_set_error(MOE_EINTERNAL, "tile maps of %d and %d rows leave no room for the counters", rows2[0], rows2[1]);
     return MOE_OK;
 }
 
@@ -2088,23 +2104,15 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         bm[0] = bm[1] = skinny_tile_rows(R);
     } else if (dtype == MOE_BF16) {
         n_used = std::min(gather ? std::min(n_local, nseg) : nseg, R);   // runs of rows that share no tile
-        take_shapes(R, n_used, H, F, act, round_size(), shape);
+        take_shapes(R, n_used, nseg, H, F, act, round_size(), shape);
         for (int i = 0; i < 2; ++i) bm[i] = kShapeRows[shape[i]];
-        // two maps share the records of the workspace, which are made for one map of 64-row tiles
-        if (bm[0] != bm[1] && max_tiles_of(R, bm[0], nseg) + max_tiles_of(R, bm[1], nseg) > max_tiles_for(R)) {
-            shape[1] = shape[0];
-            bm[1] = bm[0];
-        }
     }
+    if (dtype == MOE_BF16 && !maps_fit(R, nseg, bm[0], bm[1])) return moe_set_error(MOE_EINTERNAL, "moe_expert_ffn: tile maps of %d rows in %d segments", R, nseg);
     if (ev) MOE_HIP(hipEventRecord(ev[0], st));
     MapJobs jobs;
     jobs.job[0] = MapJob{bm[0], max_tiles_of(R, bm[0], nseg), tilemap_at(workspace, R)};
     jobs.job[1] = (bm[1] == bm[0]) ? jobs.job[0] : MapJob{bm[1], max_tiles_of(R, bm[1], nseg), tilemap_at(workspace, R, 1, jobs.job[0].max_tiles)};
-    // the counters of the tiles that are cut along K lie behind the maps, in the room of two more tiles (2 x 256
-    // counters); with hundreds of segments for a handful of rows there is no such room and no tile is cut
-    const int n_records = jobs.job[0].max_tiles + (bm[1] == bm[0] ? 0 : jobs.job[1].max_tiles);
-    static_assert(2 * kMaxSplitTiles == 2 * kRelPitch, "two rows of the offset table");
-    jobs.done = (dtype == MOE_BF16 && n_records + 2 <= max_tiles_for(R)) ? tilemap_at(workspace, R, 0, max_tiles_for(R) - 2).rel : nullptr;
+    jobs.done = (dtype == MOE_BF16) ? tilemap_at(workspace, R, 0, max_tiles_for(R) - 2).rel : nullptr;
     if (jobs.done) {
         jobs.job[0].m.done = jobs.done;
         jobs.job[1].m.done = jobs.done + kMaxSplitTiles;

@@ -398,6 +398,8 @@ FFN_CASES = [
     ("bf16", 1, 2000, 256, 512, 4, 64),
     ("bf16", 2, 1500, 384, 256, 3, 200),
     ("bf16", 0, 900, 2048, 2304, 2, 31),                   # with pieces along K as well
+    ("bf16", 2, 200, 256, 2048, 3, 1024),                  # more segments than rows, pieces along K
+    ("bf16", 0, 60, 256, 2048, 3, 1024),
     ("bf16", 2, 3000, 256, 256, 64, 1024),                 # the limits: 64 local experts, 1024 segments (many of them empty)
     ("bf16", 1, 5000, 128, 256, 32, 300),
     # shares of at most 64 rows: the weight-streaming kernels (64-row tiles, tiles cut along K when they are few)

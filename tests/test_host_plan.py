@@ -433,10 +433,30 @@ def test_a_smaller_tile_height_has_to_hold_up_against_256_rows(R, n_used, Hd, F,
     from paper_2410_17043_amd import _lib
     lib = _lib.load()
     got = (C.c_int32 * 2)()
-    assert lib.moe_selfcheck_tile_shapes(R, n_used, Hd, F, act, 256, got) == 0
+    assert lib.moe_selfcheck_tile_shapes(R, n_used, max(n_used, 64), Hd, F, act, 256, got) == 0
     assert tuple(got) == rows
     for i, (N, K, a) in enumerate(((F, Hd, act), (Hd, F, -1))):              # never anything but the preferred height or 256
         assert got[i] in (256, lib.moe_selfcheck_tile_shape(R, n_used, N, K, a, 256))
+
+
+def test_tile_maps_leave_room_for_the_counters_of_cut_tiles():
+    """Tiles that are cut along K count their pieces behind the tile maps: there is room for every number of rows and
+    segments, with one height for both GEMMs where two maps do not fit."""
+    import ctypes as C
+    from paper_2410_17043_amd import _lib
+    lib = _lib.load()
+    got = (C.c_int32 * 2)()
+    one_height = 0
+    for R in list(range(1, 300)) + [511, 512, 513, 1000, 2048, 2500, 5000, 65536, 1000003]:
+        for nseg in (1, 2, 64, 65, 500, 511, 512, 700, 1022, 1023, 1024):
+            for Hd, F, n_used in ((1024, 4608, 3), (128, 9216, 1), (2048, 4608, 64), (3200, 3456, 16)):
+                n = min(n_used, nseg)
+                assert lib.moe_selfcheck_tile_shapes(R, n, nseg, Hd, F, 0, 256, got) == 0, (R, nseg, lib.moe_last_error())
+                few = (C.c_int32 * 2)()
+                assert lib.moe_selfcheck_tile_shapes(R, n, n, Hd, F, 0, 256, few) == 0
+                if few[0] != few[1] and got[0] == got[1]:
+                    one_height += 1
+    assert one_height > 0
 
 
 @pytest.mark.parametrize("n,hi,hetero", [(2, 9, False), (5, 3, True), (7, 40, False), (16, 200, True), (17, 5, False), (33, 1000, True)])
