@@ -252,9 +252,9 @@ int moe_selfcheck_tile_order(int32_t tiles_m, int32_t tiles_n, int32_t ncu, int3
  * a second. */
 int moe_selfcheck_tile_shape(int32_t R, int32_t n_used, int32_t N, int32_t K, int32_t act, int32_t ncu);
 
-/* Rows per tile that the two GEMMs of a bf16 expert FFN over nseg segments take: the preferred ones where they hold up
- * against 256 however the rows may be spread over the experts, else 256; one height for both where two tile maps would not
- * fit into the workspace; 32 or 64 for shares of at most 64 rows (the weight-streaming kernels).  rows2 (HOST [2]): first
+/* Rows per tile that the two GEMMs of a bf16 expert FFN over nseg segments take: the preferred ones unless they do not
+ * hold up against the others over the ways in which the rows may be spread over the experts; one height for both where two
+ * tile maps would not fit into the workspace; 32 or 64 for shares of at most 64 rows (the weight-streaming kernels).  rows2 (HOST [2]): first
  * GEMM, second GEMM.  Checks that the maps leave room for the counters of tiles that are cut along K. */
 int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2);
 

@@ -1759,11 +1759,13 @@ TileShape choose_shape(int R, int n_used, int N, int K, int act, int cus) {
 //     one, at 128 x 128 0.38 with a block to itself and 0.53 beside another;
 //   - the bytes of weights and rows at the rate a GEMM streams them (5.5 - 6 TB/s), combined with the compute time by
 //     their 4-norm: near the crossing both count;
-//   - four ways in which the rows may be spread over the experts: even shares, popularity 1 / rank, and half a tile of
-//     padding per expert give or take its standard deviation;
-// and is given up for 256 when any of the four has it more than 6 % slower.  The constants are fitted to 430000 GEMMs of
-// 65 to 20000 rows, 1 to 64 experts, H and F of 128 to 14336, K from cold memory (median error 5 %).  Over those the
-// expert FFN is more than 3 % slower than one block per 256 x 256 tile was in 0.4 % of the shares, in 2.9 % without this check.
+//   - five ways in which the rows may be spread over the experts: even shares, even popularity (shares that differ by
+//     chance), popularity 1 / rank, and half a tile of padding per expert give or take its standard deviation;
+// each against 256 x 256 tiles played the same way.  What counts is the mean of the five quotients and the worst of them,
+// half each; a height at which that exceeds 1.04 is given up for the one with the least (256 has 1).  The constants are
+// fitted to 430000 GEMMs of 65 to 20000 rows, 1 to 64 experts, H and F of 128 to 14336, weights from cold memory (median
+// error 5 %).  Over those the expert FFN is more than 3 % slower than one block per 256 x 256 tile was in 0.4 % of the
+// shares, in 2.9 % without this check; the mean gain is 1.249, 1.230 without.
 struct ShapeCost { double start, a, b, a2, pair, b_pair, piece0, piece, gelu, tb_s, first_bytes; };
 double played_us(TileShape t, int tiles_m, int R, int n_used, int N, int K, int act, int cus) {
     // start of the launch; per round and per k-tile of it (at no occupancy, and what full occupancy adds); rounds with two
@@ -1786,7 +1788,7 @@ double played_us(TileShape t, int tiles_m, int R, int n_used, int N, int K, int 
     us = std::max(us, 0.1);
     return c.start + std::sqrt(std::sqrt(us * us * us * us + mem * mem * mem * mem));
 }
-// M-tiles of bm rows when R rows are spread over n_used experts in way 0 .. 3
+// M-tiles of bm rows when R rows are spread over n_used experts in way 0 .. 4
 int spread_tiles_m(int R, int bm, int n_used, int way) {
     if (n_used <= 1) return (R + bm - 1) / bm;
     if (way == 0) return n_used * (((R + n_used - 1) / n_used + bm - 1) / bm);
@@ -1797,16 +1799,31 @@ int spread_tiles_m(int R, int bm, int n_used, int way) {
         for (int e = 1; e <= n_used; ++e) tiles += (int)std::ceil(R / (e * ranks * bm));
         return tiles;
     }
+    if (way == 2) {                                        // an expert has more than j tiles with the chance that its rows exceed j * bm
+        const double share = (double)R / n_used, sd = std::sqrt(share);
+        int j = std::max(1, (int)((share - 6.0 * sd) / bm));
+        double tiles = j;
+        for (; j * bm < share + 6.0 * sd; ++j) tiles += 0.5 * std::erfc((j * bm - share) / (sd * 1.4142135623730951));
+        return std::max(n_used, (int)std::lround(n_used * tiles));
+    }
     const double mean = (double)R / bm + 0.5 * n_used, sd = std::sqrt(n_used / 12.0);
-    return std::max(n_used, (int)(way == 2 ? std::ceil(mean + sd) : std::floor(mean - sd)));
+    return std::max(n_used, (int)(way == 3 ? std::ceil(mean + sd) : std::floor(mean - sd)));
+}
+double held_up(TileShape t, int R, int n_used, int N, int K, int act, int cus) {
+    const int ways = n_used <= 1 ? 1 : 5;
+    double sum = 0.0, worst = 0.0;
+    for (int way = 0; way < ways; ++way) {
+        const double q = played_us(t, spread_tiles_m(R, kShapeRows[t], n_used, way), R, n_used, N, K, act, cus) /
+                         played_us(TS_256, spread_tiles_m(R, kShapeRows[TS_256], n_used, way), R, n_used, N, K, act, cus);
+        sum += q;
+        worst = std::max(worst, q);
+    }
+    return 0.5 * (sum / ways + worst);
 }
 TileShape confirm_shape(TileShape t, int R, int n_used, int N, int K, int act, int cus) {
-    if (t == TS_256) return t;
-    for (int way = 0; way < (n_used <= 1 ? 1 : 4); ++way) {
-        const double us = played_us(t, spread_tiles_m(R, kShapeRows[t], n_used, way), R, n_used, N, K, act, cus);
-        if (us > 1.06 * played_us(TS_256, spread_tiles_m(R, kShapeRows[TS_256], n_used, way), R, n_used, N, K, act, cus)) return TS_256;
-    }
-    return t;
+    if (t == TS_256 || held_up(t, R, n_used, N, K, act, cus) <= 1.04) return t;
+    const TileShape other = t == TS_128 ? TS_192 : TS_128;
+    return held_up(other, R, n_used, N, K, act, cus) < 1.0 ? other : TS_256;
 }
 // The records that the maps of two heights take of the workspace, which has room for one map of 64-row tiles, and whether
 // two more stay free: the counters of the tiles that are cut along K (2 x 256) lie there.
@@ -1815,13 +1832,13 @@ bool maps_fit(int R, int nseg, int bm0, int bm1) {
     return max_tiles_of(R, bm0, nseg) + (bm0 == bm1 ? 0 : max_tiles_of(R, bm1, nseg)) + 2 <= max_tiles_for(R);
 }
 // The heights that both GEMMs of a share take.  With too many segments for two maps: one height, the first GEMM's if it
-// holds up for the second as well.  (The map of one height always fits: up to 255 rows there are fewer tiles than rows,
+// holds up for the second as well, else 256.  (The map of one height always fits: up to 255 rows there are fewer tiles than rows,
 // from 256 on at least two records more than ceil(R / 128) + 1024.)
 void take_shapes(int R, int n_used, int nseg, int H, int F, int act, int cus, TileShape (&shape)[2]) {
     shape[0] = confirm_shape(choose_shape(R, n_used, F, H, act, cus), R, n_used, F, H, act, cus);
     shape[1] = confirm_shape(choose_shape(R, n_used, H, F, -1, cus), R, n_used, H, F, -1, cus);
     if (!maps_fit(R, nseg, kShapeRows[shape[0]], kShapeRows[shape[1]])) {
-        shape[0] = confirm_shape(shape[0], R, n_used, H, F, -1, cus);
+        if (confirm_shape(shape[0], R, n_used, H, F, -1, cus) != shape[0]) shape[0] = TS_256;
         shape[1] = shape[0];
     }
 }
