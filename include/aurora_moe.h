@@ -288,12 +288,14 @@ int moe_selfcheck_tile_map(const int32_t* seg_offset, const int32_t* seg_expert,
  * accesses, a wave per 8 KB: the traffic shape of a top-2 send buffer without any indexing.  The kernel is
  * launched `reps` times (1..1000) back to back between the two events; ms_out is the average per launch. */
 /* moe_expert_ffn with one of its two GEMMs (which_gemm = 1 or 2) run as a second instantiation of the same kernel
- * template that reads the 100 MHz wall clock: marks[(b * 4 + w) * 4 + i] (DEVICE, zeroed by the caller) is the
- * clock of wave w of block b at 0 start, 1 first operands in LDS (loop about to start), 2 loop done, 3 end; a block
- * that found no tile writes mark 0 only.  marks_len >= (((R + 255) / 256 + nseg) * tiles_n + 256) * 16 elements with
- * tiles_n = ceil(N / 128) for the first GEMM of a SwiGLU expert (N = F), ceil(F / 256) for the other activations,
- * ceil(H / 256) for the second GEMM; MOE_ESHAPE otherwise, and for fp32 or shares of at most 64 rows (other
- * kernels).  Everything else as moe_expert_ffn. */
+ * template that reads the 100 MHz wall clock: marks[(i * 4 + w) * 4 + j] (DEVICE, zeroed by the caller) is the
+ * clock of wave w at 0 start, 1 first operands in LDS (loop about to start), 2 loop done, 3 end of item i, a tile or a
+ * piece of one; a block that found no tile writes mark 0 only.  marks_len >= (((R + 255) / 256 + nseg) * tiles_n + 256) * 16
+ * elements with tiles_n = ceil(N / 128) for the first GEMM of a SwiGLU expert (N = F), ceil(F / 256) for the other
+ * activations, ceil(H / 256) for the second GEMM; MOE_ESHAPE otherwise, and for fp32 or shares of at most 64 rows (other
+ * kernels).  The GEMM takes the tiles that moe_expert_ffn takes if marks has room for all of them:
+ * (((R + 127) / 128 + nseg) * ceil(N / 64 or 128) + 512) * 16 elements always do; with fewer it may take 256-row tiles.
+ * Everything else as moe_expert_ffn. */
 int moe_diag_ffn_phases(const void* recv, int32_t R, const int32_t* seg_offset, const int32_t* seg_expert, int32_t nseg,
                         const moe_expert_w* experts, int32_t n_local, int32_t H, int32_t F, int32_t act, int32_t dtype,
                         void* out, void* workspace, size_t workspace_bytes, int32_t which_gemm, int64_t* marks,

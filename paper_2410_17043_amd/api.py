@@ -241,8 +241,9 @@ def moe_expert_ffn_timed(recv, R, seg_offset, seg_expert, nseg, experts, H, F, a
 
 
 def ffn_phase_marks_len(R, nseg, H, F, act, which_gemm):
-    tiles_n = -(-F // (128 if act == ACT_SWIGLU else 256)) if which_gemm == 1 else -(-H // 256)
-    return (((R + 255) // 256 + nseg) * tiles_n + 256) * 16
+    """Elements that moe_diag_ffn_phases needs to mark every tile, whatever tiles the GEMM takes."""
+    tiles_n = -(-F // (64 if act == ACT_SWIGLU else 128)) if which_gemm == 1 else -(-H // 128)
+    return (((R + 127) // 128 + nseg) * tiles_n + 512) * 16
 
 
 def moe_diag_ffn_phases(recv, R, seg_offset, seg_expert, nseg, experts, H, F, act, dtype, out, workspace, which_gemm, marks):

@@ -1065,7 +1065,7 @@ __device__ __forceinline__ void sum_pieces(int unit_lo, int unit_hi, const float
 //
 // TIMED (diagnostics, moe_diag_ffn_phases): the same kernel with the 100 MHz wall clock read by lane 0 of every wave
 // into marks[item][wave][4]: 0 start, 1 first operands in LDS (loop about to start), 2 loop done, 3 end; an item is a
-// tile or a piece of one.  The ordinary instantiation contains none of it.
+// tile or a piece of one (there is room for all of them: see max_items).  The ordinary instantiation contains none of it.
 struct WorkItem {
     int tile_id, piece;      // piece < 0: the whole K range
     int nk;                  // k-tiles (even: K is a multiple of 64)
@@ -1674,11 +1674,6 @@ int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab
     }
     // one block per place: it walks through the tiles and pieces blockIdx, blockIdx + ncu, ... (the count is known on the
     // device), the pieces last
-    if (TIMED) {
-        const int out44 = EpiGeom<EPI, 4, 4>::NOUT;
-        const size_t need = ((size_t)max_tiles_of(R, TileGeom<4, 4>::BM, nseg) * ((N + out44 - 1) / out44) + round_size()) * 16;
-        if (marks_len < need) return moe_set_error(MOE_ESHAPE, "moe_diag_ffn_phases: marks needs %zu elements", need);
-    }
     // The tile count is only known on the device: the most tail tiles over every count that n_used runs of rows which
     // share no tile can give.  A list that leaves rows out may have fewer tiles; its tail is cut if it fits as well.
     int most_tail = 0;
@@ -1824,6 +1819,11 @@ TileShape confirm_shape(TileShape t, int R, int n_used, int N, int K, int act, i
     if (t == TS_256 || held_up(t, R, n_used, N, K, act, cus) <= 1.04) return t;
     const TileShape other = t == TS_128 ? TS_192 : TS_128;
     return held_up(other, R, n_used, N, K, act, cus) < 1.0 ? other : TS_256;
+}
+// Items (tiles and pieces) that a GEMM of N output columns over R rows in nseg segments can have at most.
+size_t max_items(TileShape t, int R, int nseg, int N, int act, int cus) {
+    const int out_cols = ((t == TS_128) ? TileGeom<2, 2>::BN : TileGeom<4, 4>::BN) / (act == MOE_ACT_SWIGLU ? 2 : 1);
+    return (size_t)max_tiles_of(R, kShapeRows[t], nseg) * ((N + out_cols - 1) / out_cols) + (size_t)cus * (t == TS_128 ? TileGeom<2, 2>::PER_CU : 1);
 }
 // The records that the maps of two heights take of the workspace, which has room for one map of 64-row tiles, and whether
 // two more stay free: the counters of the tiles that are cut along K (2 x 256) lie there.
@@ -2122,6 +2122,15 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     } else if (dtype == MOE_BF16) {
         n_used = std::min(gather ? std::min(n_local, nseg) : nseg, R);   // runs of rows that share no tile
         take_shapes(R, n_used, nseg, H, F, act, round_size(), shape);
+        if (timed_gemm != 0) {
+            const int g = timed_gemm - 1, N = g == 0 ? F : H, a = g == 0 ? act : -1;
+            const size_t need = max_items(TS_256, R, nseg, N, a, round_size()) * 16;
+            if (marks_len < need) return moe_set_error(MOE_ESHAPE, "moe_diag_ffn_phases: marks needs %zu elements", need);
+            if (marks_len < max_items(shape[g], R, nseg, N, a, round_size()) * 16) {   // no room for every tile of the smaller height
+                shape[g] = TS_256;
+                if (!maps_fit(R, nseg, kShapeRows[shape[0]], kShapeRows[shape[1]])) shape[0] = shape[1] = TS_256;
+            }
+        }
         for (int i = 0; i < 2; ++i) bm[i] = kShapeRows[shape[i]];
     }
     if (dtype == MOE_BF16 && !maps_fit(R, nseg, bm[0], bm[1])) return moe_set_error(MOE_EINTERNAL, "moe_expert_ffn: tile maps of %d rows in %d segments", R, nseg);

@@ -465,6 +465,37 @@ def test_ffn_phases_diag_gives_the_results_of_moe_expert_ffn_and_ordered_marks(H
                                 which, marks)
 
 
+@pytest.mark.parametrize("R,Hd,F,act,which,rows", [(1000, 256, 3712, 2, 1, 128), (8000, 256, 4736, 0, 1, 128), (2217, 512, 5248, 2, 2, 192)])
+def test_ffn_phases_diag_marks_every_tile(H, R, Hd, F, act, which, rows):
+    """Every tile has marks: of the height that moe_expert_ffn takes with marks of ffn_phase_marks_len elements, of 256
+    rows with as few as that height needs."""
+    import ctypes as C
+    from paper_2410_17043_amd import _lib
+    got = (C.c_int32 * 2)()
+    assert _lib.load().moe_selfcheck_tile_shapes(R, 1, 1, Hd, F, act, 256, got) == 0 and got[which - 1] == rows
+    cfg = small("c2_mixtral", H=Hd, F=F, act=act)
+    experts = [H.weights_to_dev(W.make_expert_weights(cfg, 0), "bf16")]
+    x = H.dev(W.round_to_dtype(np.random.default_rng(R).standard_normal((R, Hd)).astype(np.float32), "bf16"), "bf16")
+    ref = H.run_ffn(x, [0, R], [0], experts, Hd, F, act, "bf16")
+    i32 = dict(dtype=torch.int32, device=H.DEV)
+    so, se = torch.tensor([0, R], **i32), torch.tensor([0], **i32)
+    ws = torch.empty(H.P.moe_ffn_workspace_bytes(R, Hd, F, act, "bf16"), dtype=torch.uint8, device=H.DEV)
+    N, halved = (F, act == 2) if which == 1 else (Hd, False)
+    for bm in (rows, 256):
+        cols = (128 if bm == 128 else 256) // (2 if halved else 1)
+        tiles = -(-R // bm) * -(-N // cols)
+        n = H.P.ffn_phase_marks_len(R, 1, Hd, F, act, which) if bm == rows else ((-(-R // 256) + 1) * -(-N // cols) + 256) * 16
+        marks, out = torch.zeros(n, dtype=torch.int64, device=H.DEV), torch.full_like(ref, float("nan"))
+        H.P.moe_diag_ffn_phases(x, R, so, se, 1, experts, Hd, F, act, "bf16", out, ws, which, marks)
+        torch.cuda.synchronize()
+        a = marks.cpu().numpy().reshape(-1, 4, 4)
+        done = int((a[:, :, 3] > 0).all(axis=1).sum())
+        assert done >= tiles and (a[:tiles, :, 3] > 0).all()        # as many items as tiles, or more where some are cut
+        assert torch.equal(out, ref) if bm == rows else H.rel_err(H.host(out), H.host(ref)) < 2 ** -7
+    with pytest.raises(H.P.MoeError):
+        H.P.moe_diag_ffn_phases(x, R, so, se, 1, experts, Hd, F, act, "bf16", out, ws, which, marks[:((-(-R // 256)) * -(-N // cols) + 100) * 16])
+
+
 def test_expert_ffn_leaves_rows_outside_segments_untouched(H):
     cfg = small("c2_mixtral", H=128, F=256)
     r = np.random.default_rng(5)
