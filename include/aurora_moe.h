@@ -258,6 +258,11 @@ int moe_selfcheck_tile_shape(int32_t R, int32_t n_used, int32_t N, int32_t K, in
  * GEMM, second GEMM.  Checks that the maps leave room for the counters of tiles that are cut along K. */
 int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2);
 
+/* Walk of the blocks of a bf16 FFN GEMM through tiles_m x tiles_n tiles of `rows` rows (128, 192, 256) with inner dimension
+ * K on ncu compute units, launched for up to max_tiles_m: checks that every tile and piece is taken by one block, a piece
+ * as its block's last.  Returns the number of tiles a block takes at most, or a negative moe_status. */
+int moe_selfcheck_walk(int32_t rows, int32_t tiles_m, int32_t max_tiles_m, int32_t tiles_n, int32_t K, int32_t ncu);
+
 /* Plan of the weight-streaming FFN kernels (shares of at most 64 rows) for `total` tiles of `ns` stages of K on
  * ncu compute units: checks that the pieces cover the stages exactly once, are at least two stages long and fit
  * the launch.  Returns the number of pieces per tile (1 = whole tiles), or a negative moe_status. */
@@ -290,7 +295,7 @@ int moe_selfcheck_tile_map(const int32_t* seg_offset, const int32_t* seg_expert,
 /* moe_expert_ffn with one of its two GEMMs (which_gemm = 1 or 2) run as a second instantiation of the same kernel
  * template that reads the 100 MHz wall clock: marks[(i * 4 + w) * 4 + j] (DEVICE, zeroed by the caller) is the
  * clock of wave w at 0 start, 1 first operands in LDS (loop about to start), 2 loop done, 3 end of item i, a tile or a
- * piece of one; a block that found no tile writes mark 0 only.  marks_len >= (((R + 255) / 256 + nseg) * tiles_n + 256) * 16
+ * piece of one.  marks_len >= (((R + 255) / 256 + nseg) * tiles_n + 256) * 16
  * elements with tiles_n = ceil(N / 128) for the first GEMM of a SwiGLU expert (N = F), ceil(F / 256) for the other
  * activations, ceil(H / 256) for the second GEMM; MOE_ESHAPE otherwise, and for fp32 or shares of at most 64 rows (other
  * kernels).  The GEMM takes the tiles that moe_expert_ffn takes if marks has room for all of them:

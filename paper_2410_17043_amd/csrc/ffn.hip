@@ -673,6 +673,19 @@ __host__ __device__ __forceinline__ TailPlan plan_tail_upto(int most_tail, int t
     return p.n_tail <= most_tail ? p : TailPlan{total, 0, 1, nk / 2};
 }
 
+// Which items (tiles, then pieces) a block of the bf16 GEMM walks through: item, item + ncu, ... below end.  Place p of the
+// ncu places works through items p, p + ncu, ... in runs of `walk`, a block for each.  The places' runs end one after the
+// other, not all at once: whenever a run ends its CU is free for what other streams have queued.  Blocks start in the
+// order of their numbers, and so do the runs of a generation end.  No cut when there are no more than `walk` rounds.
+struct WalkRun { int item, end; };
+__host__ __device__ __forceinline__ WalkRun walk_run(int block, int ncu, int walk, int n_items) {
+    const int gen = block / ncu, place = block % ncu;
+    const int ahead = n_items <= walk * ncu ? 0 : (ncu - 1 - place) * walk / ncu;   // rounds that this place's runs end early
+    const int r0 = gen * walk - ahead, r1 = r0 + walk;
+    const int first = (r0 > 0 ? r0 : 0) * ncu + place, end = r1 * ncu;
+    return WalkRun{first, end < n_items ? end : n_items};
+}
+
 // ------------------------------------------------------------------------------------ fp32
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -1053,7 +1066,7 @@ __device__ __forceinline__ void sum_pieces(int unit_lo, int unit_hi, const float
 // come a whole k-tile apart cost about twice the L2 bandwidth.  The pair (kt+4, kt+5) is issued
 // in iteration kt (kt even) and first needed 2.5 iterations later.
 // The MFMAs are issued as D = B . A^T (operands swapped), so a lane ends up with 4 consecutive
-// output COLUMNS of one row (see store_rows).
+// output COLUMNS of one row (see store_tile).
 //
 // A block walks through several tiles, and the pipeline runs across them: the loads that go out in a tile's last two
 // trips are the next tile's first k-tiles (its addresses are prepared during the epilogue before), and the last
@@ -1061,7 +1074,8 @@ __device__ __forceinline__ void sum_pieces(int unit_lo, int unit_hi, const float
 // paid 3.4 us from the block's start to its first operands and 1.3 us of launch.  Per 256 x 256 tile at K = 1408: 41.6
 // -> 39.5 us, at K = 2048 SwiGLU 54.6 -> 53; 612329 rows of 2048 -> 1408 -> 2048 with shared experts, the whole share:
 // 9.33 -> 9.13 ms; 10199 rows of 1024 -> 4096 -> 1024 238 -> 233 us; two models at once 1.75 -> 1.70 ms.  (A tile whose
-// loop is long is bound by power instead: K = 14336 is unchanged.)
+// loop is long is bound by power instead: K = 14336 is unchanged.)  The walk is bounded (`walk` tiles, see walk_tiles): a
+// CU that comes free is where work of another stream gets in.
 //
 // TIMED (diagnostics, moe_diag_ffn_phases): the same kernel with the 100 MHz wall clock read by lane 0 of every wave
 // into marks[item][wave][4]: 0 start, 1 first operands in LDS (loop about to start), 2 loop done, 3 end; an item is a
@@ -1075,7 +1089,7 @@ struct WorkItem {
 template <int EPI, int MI, int NJ, bool TIMED>
 __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_kernel(const uint16_t* __restrict__ A, int lda, TileMap m,
                                                            ExpertTable tab, int which0, int which1, int N, int K,
-                                                           uint16_t* __restrict__ C, int ldc, int tiles_n, int ncu, int most_tail,
+                                                           uint16_t* __restrict__ C, int ldc, int tiles_n, int ncu, int walk, int most_tail,
                                                            float* partial, long long* __restrict__ marks,
                                                            uint32_t mark_items) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -1084,8 +1098,7 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
         if (TIMED && (uint32_t)item < mark_items && (threadIdx.x & 63) == 0)                                        \
             marks[((size_t)item * 4 + (threadIdx.x >> 6)) * 4 + (i)] = (long long)wall_clock64();                    \
     } while (0)
-    int item = blockIdx.x;
-    MOE_MARK(0);
+    const long long t_start = TIMED ? (long long)wall_clock64() : 0;
     using TG = TileGeom<MI, NJ>;
     using EG = EpiGeom<EPI, MI, NJ>;
     constexpr int NOUT = EG::NOUT;                                          // output columns per block
@@ -1098,7 +1111,11 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     plan.parts = __builtin_amdgcn_readfirstlane(plan.parts);
     plan.pairs_per = __builtin_amdgcn_readfirstlane(plan.pairs_per);
     const int n_items = plan.n_full + (plan.parts > 1 ? plan.n_tail * plan.parts : 0);
-    if (item >= n_items) return;
+    const WalkRun run = walk_run(blockIdx.x, ncu, walk, n_items);
+    int item = run.item;
+    const int end_item = run.end;
+    if (item >= end_item) return;
+    if (TIMED && (uint32_t)item < mark_items && (threadIdx.x & 63) == 0) marks[((size_t)item * 4 + (threadIdx.x >> 6)) * 4] = t_start;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform by construction; tell the compiler
@@ -1289,7 +1306,7 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     t_last = cur.nk - 2;
     issue_part(0, so[0], so[1], 0, 4 * GI);
     issue_part(2, so[2], so[3], 0, 3 * GI);        // its last group goes out in the first trip below
-    bool more = item + ncu < n_items;
+    bool more = item + ncu < end_item;
     if (more) {
         describe(item + ncu, next, src_next, a_row);
         describe_lanes(next, src_next, a_row);
@@ -1361,7 +1378,7 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
         if (more) {
             cur = next;
             t_first = 0;
-            more = item + 2 * ncu < n_items;
+            more = item + 2 * ncu < end_item;
             if (more) describe(item + 2 * ncu, next, src_next, a_row);
         }
         const int col0 = __builtin_amdgcn_readfirstlane(done.n0 + wn * EG::NW);
@@ -1658,6 +1675,24 @@ int round_size() {
     return ncu;
 }
 
+// Tiles that a block walks through.  A block holds its CU - all of its LDS and registers - until it ends, and what another
+// stream has queued (a decode step of a second model, its gate, its send buffer) waits for that, at every kernel of its
+// chain.  A decode share of 16 tokens (150 us alone) beside a prefill, one block per CU to the end of the GEMM -> runs of
+// 210 us that end one after the other (-> a block per tile): gate to send buffer beside 20571 rows of 4096 -> 14336 -> 4096
+// 3.0 -> 0.39 (0.27) ms, the whole share 4.8 -> 2.3 (1.35) ms; beside 200000 rows of 2048 -> 1408 -> 2048 1.26 -> 0.16
+// (0.14) and 2.3 -> 1.4 (0.76) ms; beside 40000 rows of 1024 -> 4096 -> 1024 0.89 -> 0.53 (0.53) ms.  What a new block
+// costs (4.7 us) shows as 0.5 to 1.4 % of those GEMMs; runs of 100 us cost 1.5 to 3.8 %.
+constexpr double kWalkUs = 210.0;
+int walk_tiles(int rows, int K) {
+    const double k_tile_us = rows == TileGeom<2, 2>::BM ? 0.53 : rows == TileGeom<3, 4>::BM ? 0.61 : 0.75;   // on a full chip
+    return std::max(1, (int)(kWalkUs / (5.0 + k_tile_us * (K / BK))));
+}
+// blocks for up to max_items tiles and pieces, of which only the device knows the number
+int walk_blocks(int max_items, int walk, int ncu) {
+    const int rounds = (max_items + ncu - 1) / ncu;
+    return (rounds <= walk ? 1 : (rounds + 2 * walk - 2) / walk) * ncu;
+}
+
 template <int EPI, int MI, int NJ, bool TIMED>
 int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
                 void* C, int ldc, int R, int nseg, int n_used, float* partial, hipStream_t st, long long* marks,
@@ -1672,16 +1707,15 @@ int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab
                                     hipFuncAttributeMaxDynamicSharedMemorySize, TG::LDS));
         attr_done = true;
     }
-    // one block per place: it walks through the tiles and pieces blockIdx, blockIdx + ncu, ... (the count is known on the
-    // device), the pieces last
     // The tile count is only known on the device: the most tail tiles over every count that n_used runs of rows which
     // share no tile can give.  A list that leaves rows out may have fewer tiles; its tail is cut if it fits as well.
     int most_tail = 0;
     for (int t = (R + TG::BM - 1) / TG::BM, hi = (R + n_used * (TG::BM - 1)) / TG::BM; t <= hi; ++t)
         most_tail = std::max(most_tail, plan_tail(t * tiles_n, ncu, K / BK).n_tail);
-    hipLaunchKernelGGL((gemm_bf16_kernel<EPI, MI, NJ, TIMED>), dim3(ncu), dim3(256), TG::LDS, st,
+    const int walk = walk_tiles(TG::BM, K);
+    hipLaunchKernelGGL((gemm_bf16_kernel<EPI, MI, NJ, TIMED>), dim3(walk_blocks(max_tiles_of(R, TG::BM, nseg) * tiles_n + ncu, walk, ncu)), dim3(256), TG::LDS, st,
                        reinterpret_cast<const uint16_t*>(A), lda, m, tab, which0, which1, N, K,
-                       reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, most_tail, partial, marks,
+                       reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, walk, most_tail, partial, marks,
                        (uint32_t)std::min<size_t>(marks_len / 16, 0xFFFFFFFFu));
     MOE_LAUNCH_CHECK("gemm_bf16_kernel");
     if (most_tail > 0 && !TG::SUM_IN_PLACE) {
@@ -1933,6 +1967,28 @@ extern "C" int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t nseg
     }
     if (!maps_fit(R, nseg, rows2[0], rows2[1])) return moe_set_error(MOE_EINTERNAL, "tile maps of %d and %d rows leave no room for the counters", rows2[0], rows2[1]);
     return MOE_OK;
+}
+
+extern "C" int moe_selfcheck_walk(int32_t rows, int32_t tiles_m, int32_t max_tiles_m, int32_t tiles_n, int32_t K, int32_t ncu) {
+    if ((rows != 128 && rows != 192 && rows != 256) || tiles_m < 1 || max_tiles_m < tiles_m || tiles_n < 1 || K < 64 || K % 64 != 0 || ncu < 1)
+        return moe_set_error(MOE_EINVAL, "moe_selfcheck_walk: bad argument");
+    const int slots = rows == 128 ? 2 * ncu : ncu, walk = walk_tiles(rows, K);
+    const TailPlan p = plan_tail(tiles_m * tiles_n, slots, K / BK);
+    const int n_items = p.n_full + (p.parts > 1 ? p.n_tail * p.parts : 0);
+    std::vector<int> seen((size_t)n_items, 0);
+    const int blocks = walk_blocks(max_tiles_m * tiles_n + slots, walk, slots);
+    for (int b = 0; b < blocks; ++b) {
+        const WalkRun run = walk_run(b, slots, walk, n_items);
+        for (int item = run.item; item < run.end; item += slots) {
+            if (item >= n_items || (run.end - run.item + slots - 1) / slots > walk) return moe_set_error(MOE_EINTERNAL, "run of block %d", b);
+            ++seen[item];
+            // a block stops behind a piece
+            if (item >= p.n_full && item + slots < run.end) return moe_set_error(MOE_EINTERNAL, "piece %d is not the last item of block %d", item, b);
+        }
+    }
+    for (int i = 0; i < n_items; ++i)
+        if (seen[i] != 1) return moe_set_error(MOE_EINTERNAL, "item %d is taken %d times", i, seen[i]);
+    return walk;
 }
 
 extern "C" int moe_selfcheck_skinny_plan(int32_t total, int32_t ncu, int32_t ns) {

@@ -458,6 +458,21 @@ def test_tile_maps_leave_room_for_the_counters_of_cut_tiles():
     assert one_height > 0
 
 
+def test_a_block_walks_through_a_bounded_run_of_tiles():
+    """Every tile and piece is taken once, and no block holds its CU for more than 210 us or one tile: what another stream
+    has queued gets in between blocks."""
+    from paper_2410_17043_amd import _lib
+    walk = _lib.load().moe_selfcheck_walk
+    r = np.random.default_rng(8)
+    for rows, k_tile_us in ((128, 0.5), (192, 0.56), (256, 0.71)):
+        for K in (64, 128, 1024, 1408, 2048, 4096, 5632, 14336, 65536):
+            w = walk(rows, 1, 1, 1, K, 256)
+            assert w == 1 or (w >= 1 and w * k_tile_us * (K / 32) <= 210), (rows, K, w)
+            for _ in range(12):
+                tm, tn, ncu = int(r.integers(1, 200)), int(r.integers(1, 60)), int(r.choice([256, 256, 64, 8, 304]))
+                assert walk(rows, tm, tm + int(r.integers(0, 70)), tn, K, ncu) == w, _lib.load().moe_last_error()
+
+
 @pytest.mark.parametrize("n,hi,hetero", [(2, 9, False), (5, 3, True), (7, 40, False), (16, 200, True), (17, 5, False), (33, 1000, True)])
 def test_send_order_time_is_that_of_playing_the_order_and_no_exchange_improves_it(n, hi, hetero):
     """The hill climbing resumes recorded runs; playing the order it returns from the start gives the same time to the
