@@ -1838,19 +1838,25 @@ int spread_tiles_m(int R, int bm, int n_used, int way) {
     const double mean = (double)R / bm + 0.5 * n_used, sd = std::sqrt(n_used / 12.0);
     return std::max(n_used, (int)(way == 3 ? std::ceil(mean + sd) : std::floor(mean - sd)));
 }
+// time of height t over that of 256 rows when the rows are spread in way `way`
+double against_256(TileShape t, int way, int R, int n_used, int N, int K, int act, int cus) {
+    return played_us(t, spread_tiles_m(R, kShapeRows[t], n_used, way), R, n_used, N, K, act, cus) /
+           played_us(TS_256, spread_tiles_m(R, kShapeRows[TS_256], n_used, way), R, n_used, N, K, act, cus);
+}
 double held_up(TileShape t, int R, int n_used, int N, int K, int act, int cus) {
     const int ways = n_used <= 1 ? 1 : 5;
     double sum = 0.0, worst = 0.0;
     for (int way = 0; way < ways; ++way) {
-        const double q = played_us(t, spread_tiles_m(R, kShapeRows[t], n_used, way), R, n_used, N, K, act, cus) /
-                         played_us(TS_256, spread_tiles_m(R, kShapeRows[TS_256], n_used, way), R, n_used, N, K, act, cus);
+        const double q = against_256(t, way, R, n_used, N, K, act, cus);
         sum += q;
         worst = std::max(worst, q);
     }
     return 0.5 * (sum / ways + worst);
 }
+// A height that is 12 % faster at even shares (57 % of those that are preferred to 256) is taken without the other four:
+// nothing is lost by it, and the call's host time stays (1.5 us of playing where a whole share of the layer takes 76).
 TileShape confirm_shape(TileShape t, int R, int n_used, int N, int K, int act, int cus) {
-    if (t == TS_256 || held_up(t, R, n_used, N, K, act, cus) <= 1.04) return t;
+    if (t == TS_256 || against_256(t, 0, R, n_used, N, K, act, cus) <= 0.88 || held_up(t, R, n_used, N, K, act, cus) <= 1.04) return t;
     const TileShape other = t == TS_128 ? TS_192 : TS_128;
     return held_up(other, R, n_used, N, K, act, cus) < 1.0 ? other : TS_256;
 }
