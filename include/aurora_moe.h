@@ -264,7 +264,8 @@ int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t nseg, int32_t H
 int moe_selfcheck_walk(int32_t rows, int32_t tiles_m, int32_t max_tiles_m, int32_t tiles_n, int32_t K, int32_t ncu);
 
 /* Plan of the weight-streaming FFN kernels (shares of at most 64 rows) for `total` tiles of `ns` stages of K on
- * ncu compute units: checks that the pieces cover the stages exactly once, are at least two stages long and fit
+ * ncu compute units: checks that the pieces cover the stages exactly once, are at least four stages long (the last may be
+ * shorter) and fit
  * the launch.  Returns the number of pieces per tile (1 = whole tiles), or a negative moe_status. */
 int moe_selfcheck_skinny_plan(int32_t total, int32_t ncu, int32_t ns);
 

@@ -2000,12 +2000,12 @@ extern "C" int moe_selfcheck_walk(int32_t rows, int32_t tiles_m, int32_t max_til
 extern "C" int moe_selfcheck_skinny_plan(int32_t total, int32_t ncu, int32_t ns) {
     if (total < 1 || ncu < 1 || ns < 1) return moe_set_error(MOE_EINVAL, "moe_selfcheck_skinny_plan: total, ncu and ns must be positive");
     const SkinnyPlan p = plan_skinny(total, ncu, ns);
-    // every stage in exactly one piece, no empty piece, no more blocks than max(total, ncu), pieces of at least 2 stages
+    // every stage in exactly one piece, no empty piece, no more blocks than max(total, ncu), pieces of at least 4 stages
     if (p.parts < 1 || p.per < 1 || (int64_t)p.parts * p.per < ns || (int64_t)(p.parts - 1) * p.per >= ns)
         return moe_set_error(MOE_EINTERNAL, "skinny plan: %d pieces of %d stages do not cover %d stages once", p.parts, p.per, ns);
     if ((int64_t)total * p.parts > std::max(total, ncu))
         return moe_set_error(MOE_EINTERNAL, "skinny plan: %d tiles x %d pieces exceed the launch", total, p.parts);
-    if (p.parts > 1 && (p.per < 2 || total >= ncu)) return moe_set_error(MOE_EINTERNAL, "skinny plan: pieces too short or not needed");
+    if (p.parts > 1 && (p.per < 4 || total >= ncu)) return moe_set_error(MOE_EINTERNAL, "skinny plan: pieces too short or not needed");
     return p.parts;
 }
 

@@ -408,6 +408,9 @@ def test_skinny_plan_and_row_geometry_self_checks():
     assert lib.moe_selfcheck_skinny_plan(224, 256, 32) == 1       # first GEMM of a Mixtral-shape expert, 32 rows
     assert lib.moe_selfcheck_skinny_plan(32, 256, 112) == 8       # second GEMM: K = 14336 in 8 pieces of 14 stages
     assert lib.moe_selfcheck_skinny_plan(0, 256, 8) < 0
+    # at least four stages per piece
+    assert [lib.moe_selfcheck_skinny_plan(16, 256, ns) for ns in (4, 7, 8, 11, 12, 16, 17)] == [1, 1, 2, 2, 3, 4, 4]
+    assert lib.moe_selfcheck_skinny_plan(1, 256, 1024) == 32
     out = (C.c_int32 * 3)()
     for row16 in list(range(1, 600)) + [1024, 1536, 4096, 65536]:
         for k in (1, 2, 3, 6, 8, 9, 16):
