@@ -265,8 +265,7 @@ int moe_selfcheck_walk(int32_t rows, int32_t tiles_m, int32_t max_tiles_m, int32
 
 /* Plan of the weight-streaming FFN kernels (shares of at most 64 rows) for `total` tiles of `ns` stages of K on
  * ncu compute units: checks that the pieces cover the stages exactly once, are at least four stages long (the last may be
- * shorter) and fit
- * the launch.  Returns the number of pieces per tile (1 = whole tiles), or a negative moe_status. */
+ * shorter) and fit the launch.  Returns the number of pieces per tile (1 = whole tiles), or a negative moe_status. */
 int moe_selfcheck_skinny_plan(int32_t total, int32_t ncu, int32_t ns);
 
 /* How the scatter kernels share rows of row16 16-byte units among waves for k slots per token: out3 (HOST) =

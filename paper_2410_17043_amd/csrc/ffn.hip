@@ -9,7 +9,7 @@
 // turns the segment list into a list of M-tiles (adjacent segments of the same
 // expert are merged, tiles never straddle experts), so nothing waits for the host.
 //
-// bf16 path: 256x256 block tile (192x256 or 128x128 where that fills the chip better, see choose_shape), 32-wide
+// bf16 path: 256x256 block tile (192x256 or 128x128 where that fills the chip better, see take_shapes), 32-wide
 // k-tiles, 4 waves in 2x2, each wave 128x128 = 4x4
 // tiles of v_mfma_f32_32x32x16_bf16 with fp32 accumulators (256 accumulator registers per
 // lane); operands go global -> LDS directly (no register staging) through a 5-stage ring that
@@ -642,9 +642,10 @@ __host__ __device__ __forceinline__ void tile_of_block(int id, int total, int ti
 // Tail splitting.  The grid runs in rounds of `ncu` tiles (one block per CU); the tiles of a last,
 // mostly empty round would leave most CUs idle for a whole tile time.  When that round has at most
 // ncu / 2 tiles, each of them is cut along K into `parts` pieces that run as separate blocks
-// (1/parts of a tile time) and write fp32 partial tiles; the last piece of a tile to arrive adds them
-// in piece order and applies the epilogue (see last_piece).  Everything here depends
-// only on the shapes, so results do not vary from run to run.
+// (1/parts of a tile time) and write fp32 partial tiles, which are added in piece order before the
+// epilogue - at 128 x 128 by the piece that arrives last (see last_piece), else by gemm_bf16_tail_kernel.
+// Everything here depends only on the shapes, so results do not vary from run to run; another tile
+// height or another cut adds the products of a row in another order, i.e. may round the last bit differently.
 struct TailPlan {
     int n_full;        // tiles handled whole: ids [0, n_full)
     int n_tail;        // tiles cut in pieces: ids [n_full, n_full + n_tail)
@@ -977,9 +978,10 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[MI][NJ], int lane
 // weight-streaming kernels) the block that arrives last (a counter per tile, nobody waits) adds all pieces in piece
 // order - its own is read back like the others, so the result does not depend on who was last - and finishes the
 // tile.  A kernel of its own for the sums costs 4.5 us where there is nothing to add and 5-16 us where there is, each
-// time behind a launch gap; the last block reads up to half a megabyte in about as long, without the gap.  The larger
-// tiles have 0.8 to 2 MB of pieces, which take one block 20 us and more (93 against 108 us for the second GEMM at 4096
-// -> 14336 -> 4096 and 701 rows): those are added by gemm_bf16_tail_kernel, spread over the chip.
+// time behind a launch gap; the last block reads up to half a megabyte (32 pieces of a weight-streaming tile: 1 MB) in
+// about as long, without the gap.  The larger tiles have 0.8 to 2 MB of pieces, which take one block 20 us and more (93
+// against 108 us for the second GEMM at 4096 -> 14336 -> 4096 and 701 rows): those are added by gemm_bf16_tail_kernel,
+// spread over the chip.
 // The writers may sit on other XCDs, whose L2s do not see each other: pieces are stored and read with accesses of
 // agent scope (sc1: written through, read past the L2), the counter is an agent-scope atomic, and a wave's stores have
 // completed (vmcnt(0)) before its block counts.  The same with plain accesses between __threadfence()s was far
@@ -1718,10 +1720,12 @@ int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab
                        reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, walk, most_tail, partial, marks,
                        (uint32_t)std::min<size_t>(marks_len / 16, 0xFFFFFFFFu));
     MOE_LAUNCH_CHECK("gemm_bf16_kernel");
-    if (most_tail > 0 && !TG::SUM_IN_PLACE) {
-        hipLaunchKernelGGL((gemm_bf16_tail_kernel<EPI, MI, NJ>), dim3(most_tail * MI * G::NJO), dim3(256), 0, st, m, N, K,
-                           reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, most_tail, partial);
-        MOE_LAUNCH_CHECK("gemm_bf16_tail_kernel");
+    if constexpr (!TG::SUM_IN_PLACE) {
+        if (most_tail > 0) {
+            hipLaunchKernelGGL((gemm_bf16_tail_kernel<EPI, MI, NJ>), dim3(most_tail * MI * G::NJO), dim3(256), 0, st, m, N, K,
+                               reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, most_tail, partial);
+            MOE_LAUNCH_CHECK("gemm_bf16_tail_kernel");
+        }
     }
     return MOE_OK;
 }
@@ -1740,7 +1744,7 @@ int launch_bf16_shape(TileShape t, const void* A, int lda, const TileMap& m, con
 // Which tiles a bf16 GEMM takes.  The number of tiles is only known on the device, so the choice is made from an
 // estimate of it: half a tile of padding per expert.  Every shape's time is modelled as rounds of the grid, a round
 // costing a + b * (k-tiles of 32), and a tail as plan_tail cuts it; the first round of the large shapes starts cold; the
-// shape with the least time is taken.  The
+// shape with the least time is preferred, and taken if it holds up (see confirm_shape).  The
 // constants (microseconds) are from GEMMs of K = 1024 ... 14336 with whole rounds: 256 x 256 100 us per round at
 // K = 4096, 37 at 1024; 192 x 256 80 us at 4096; 128 x 128, two blocks per CU, 66 us at 4096 and 36 at 2048, and
 // about two thirds of that when the round has one block per CU.  So 256 x 256 is the best rate (1.35 PFLOP/s against

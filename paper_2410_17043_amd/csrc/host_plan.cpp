@@ -2,7 +2,7 @@
 // Appendix A/B) and expert colocation by bottleneck matching (Sec. 6.2).
 // Plain C++; nothing here touches the GPU.  Planning is offline (Sec. 2.4), its
 // results are inputs of moe_dispatch.
-#include <emmintrin.h>
+#include <emmintrin.h>   // SSE2, which every x86-64 host has
 
 #include <algorithm>
 #include <cmath>

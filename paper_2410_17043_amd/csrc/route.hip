@@ -690,7 +690,7 @@ int route_dispatch(const moe_ctx* c, const void* x, const void* wg, const float*
     // other waits for its fragments; with many tokens four tiles per block (the gate rows are fetched from L2 once
     // per 64 tokens instead of once per 32) and one wave per SIMD
     const bool few = (s.T + 63) / 64 < 200;
-    // ... but while tiles of one token each find a CU, one per block: half the fragments, sums and selections behind each
+    // ... but while token tiles each find a CU (256 of them), one per block: half the fragments, sums and selections behind each
     // other, and the ring has room for all partial tiles at once.  E = 64, k = 6, H = 2048: 14.0 -> 11.0 us at 64 tokens,
     // 24.7 -> 21.8 at 4096; E = 24, k = 3, H = 1152: 7.9 -> 6.7 and 12.7 -> 10.8
     if ((s.T + 15) / 16 <= 256) {
