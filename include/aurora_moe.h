@@ -258,6 +258,10 @@ int moe_selfcheck_tile_shape(int32_t R, int32_t n_used, int32_t N, int32_t K, in
  * GEMM, second GEMM.  Checks that the maps leave room for the counters of tiles that are cut along K. */
 int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2);
 
+/* Rows per tile of the two GEMMs of an fp32 share of R rows in nseg segments of n_used experts: 64 (fp32 matrix cores) or
+ * 128 (pairs of halves on the fp16 ones).  Self check, runs on the host. */
+int moe_selfcheck_f32_kernels(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2);
+
 /* Walk of the blocks of a bf16 FFN GEMM through tiles_m x tiles_n tiles of `rows` rows (128, 192, 256) with inner dimension
  * K on ncu compute units, launched for up to max_tiles_m: checks that every tile and piece is taken by one block, a piece
  * as its block's last.  Returns the number of tiles a block takes at most, or a negative moe_status. */

@@ -25,7 +25,8 @@
 // Shares of at most 64 rows (bf16) take a pair of weight-streaming kernels instead (gemm_bf16_skinny_kernel):
 // 32- or 64-row tiles, 256-byte bursts per weight row, the LDS ring given to loads in flight.
 //
-// fp32 path: 64 x 64 tiles on the fp32 matrix cores (gemm_f32_kernel).
+// fp32 path: 128 x 128 tiles of pairs of halves on the fp16 matrix cores (gemm_f32_halves_kernel); where there are too few
+// of them, 64 x 64 tiles on the fp32 matrix cores (gemm_f32_kernel).
 #include "common.h"
 #include <algorithm>
 #include <cmath>
@@ -899,6 +900,319 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     const f32x2 v = {lo, hi};
     const bf16x2 b = __builtin_convertvector(v, bf16x2);      // round to nearest even in hardware
     return *reinterpret_cast<const uint32_t*>(&b);
+}
+
+// The same products on the fp16 matrix cores, for grids that fill the chip with 128 x 128 tiles (see f32_in_halves).
+//
+// A float, scaled by a power of two that its row has, is h + l / 2048 + a rest of at most 2^-23 of it, with h and l in fp16
+// (11 bits and a sign each), and x w = h_x h_w + (h_x l_w + l_x h_w) / 2048 + terms below 2^-22: three products of
+// v_mfma_f32_32x32x16_f16 in 96 clocks per 16 elements of K instead of 512 for v_mfma_f32_32x32x2_f32.  Products of
+// halves are exact, and the small ones are accumulated apart from h_x h_w, so that they are not rounded to its last bit:
+// against 64 bits the rms error is 0.36 to 0.9 of that of the fp32 instruction's chain over K = 64 ... 8192 of normal,
+// uniform, heavy-tailed and unevenly scaled operands (K = 128 / 1024 / 8192 of normal ones: 1.1e-7 / 2.2e-7 / 5.9e-7
+// against 2.1e-7 / 5.8e-7 / 1.6e-6).  (It is the sum's rounding that shrinks: a single product is off by up to 2^-21, where the
+// fp32 instruction rounds it to 2^-24.)  Three bf16 parts and six products, which have all 24 bits, took 1.5 times as long.
+//
+// The scale puts the largest of the row's first 32 elements at 4 to 8 (a row of zeros: 2^127).  Elements up to 2^13
+// times that one keep all their bits down to 2^-15 times it; the rest below is cut at 2^-39 times it.  A row with larger elements,
+// an infinity or a NaN leaves a sum that is not finite, and the block forms the tile again with v_mfma_f32_32x32x2_f32
+// (multiply_exactly: a third of the rate).
+//
+// 128 x 128 block tile, k-tiles of 32, 8 waves: two groups of 2 x 2 waves, 64 x 64 each, group g taking half g of every
+// k-tile; the groups' sums are exchanged through LDS at the end and each group finishes half of the rows: two waves per
+// SIMD on one tile per CU.  Every element is split once per block: loaded to registers three k-tiles
+// ahead, split between the products and written to LDS as two planes one ahead (two stages of 32 KB).
+// The pair of GEMMs of 3001 rows of 1024 -> 2816 -> 1024 SwiGLU: 407 us with gemm_f32_kernel, 216 here; 20000 rows, SiLU:
+// 1740 -> 861 (268 TFLOP/s).  The card is at its power limit then: leaving out the split, the loads or the LDS writes
+// gains a fifth each, at a higher clock.
+// Blocks walk through tiles like those of gemm_bf16_kernel: the loads run on into the next tile.
+//
+// Plane of an operand tile: 128 rows x 32 elements as blocks of 16 rows x 4 chunks of 16 bytes (tile_off, conflict-free).
+// The order of the sum over k is free: chunk c holds elements 4 c .. 4 c + 3 and 16 + 4 c .. + 3 of the k-tile, so that
+// four lanes fetch 64 contiguous bytes of a row per load.
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+constexpr int XM = 128, XN = 128, XK = 32;
+constexpr int kXPlane = XM * XK * 2;                     // 8 KB
+constexpr int kXOperand = 2 * kXPlane;
+constexpr int kXStage = 2 * kXOperand;                   // A, then B
+constexpr int kXGive = 32 * 1024;                        // sums of a group that the other one finishes
+constexpr int kXLds = 2 * kXStage + 2 * kXGive + 2 * (XM + XN) * 4 + 64;   // stages, sums, exponents of the rows of two tiles, votes
+constexpr int kXMinK = 4 * XK;                           // a walk reads three k-tiles ahead: at most into the next tile
+constexpr float kLowScale = 2048.f;
+
+// Power of two for the row that four neighbouring lanes hold in q0 and q1
+__device__ __forceinline__ int scale_exponent(const f32x4& q0, const f32x4& q1) {
+    float m = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m = fmaxf(m, fmaxf(fabsf(q0[e]), fabsf(q1[e])));
+    m = fmaxf(m, __shfl_xor(m, 1, 64));
+    m = fmaxf(m, __shfl_xor(m, 2, 64));
+    const int e = (int)(__float_as_uint(m) >> 23);         // (m >= 0)
+    return min(127 + 2 - e, 127);                          // e = 0: zeros (or below 2^-126)
+}
+__device__ __forceinline__ float power_of_two(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }   // -126 <= e <= 127
+
+// A lane's part of an operand pair on its way from floats to planes: 2 x 4 elements of A and of B, taken in pairs.
+struct Splitter {
+    u32x4 part[2][2];                                      // [A, B][h, l]
+    f16x2 h[8];
+    __device__ __forceinline__ void high(const f32x4 (&q)[4], const float (&scale)[2], int u) {
+        const f32x2 v = {q[u >> 1][2 * (u & 1)] * scale[u >> 2], q[u >> 1][2 * (u & 1) + 1] * scale[u >> 2]};
+        h[u] = __builtin_convertvector(v, f16x2);          // to nearest even
+        part[u >> 2][0][u & 3] = __builtin_bit_cast(uint32_t, h[u]);
+    }
+    __device__ __forceinline__ void low(const f32x4 (&q)[4], const float (&scale)[2], int u) {   // exact differences
+        const float s = scale[u >> 2] * kLowScale;
+        const f32x2 v = {__builtin_fmaf((float)h[u].x, -kLowScale, q[u >> 1][2 * (u & 1)] * s), __builtin_fmaf((float)h[u].y, -kLowScale, q[u >> 1][2 * (u & 1) + 1] * s)};
+        part[u >> 2][1][u & 3] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
+    }
+    __device__ __forceinline__ void store(unsigned char* st, int op, int n) const { *reinterpret_cast<u32x4*>(st + op * kXOperand + n * kXPlane) = part[op][n]; }
+};
+__device__ __forceinline__ void split_halves(const f32x4 (&q)[4], const float (&scale)[2], unsigned char* st) {
+    Splitter s;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) { s.high(q, scale, u); s.low(q, scale, u); }
+#pragma unroll
+    for (int n = 0; n < 4; ++n) s.store(st, n / 2, n % 2);
+}
+// 64 x 64 x 16 ([row tile][weight-row tile], D^T: rows n, columns m) while the next k-tile is split: a product, then a
+// handful of vector instructions, held together (the scheduler left to itself puts all products first)
+typedef f32x16 Acc22[2][2];
+__device__ __forceinline__ void multiply_halves(const unsigned char* pa, const unsigned char* pb, Acc22& hi, Acc22& lo, const f32x4 (&q)[4],
+                                                const float (&scale)[2], unsigned char* then) {
+    f16x8 a[2][2], b[2][2];
+    auto read = [&](f16x8 (&f)[2][2], const unsigned char* p, int n) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) f[n][i] = *reinterpret_cast<const f16x8*>(p + n * kXPlane + i * 2048);
+    };
+    read(a, pa, 0);
+    read(b, pb, 0);
+    read(a, pa, 1);
+    read(b, pb, 1);
+    Splitter s;
+    constexpr int term[3][2] = {{0, 0}, {1, 0}, {0, 1}};   // half of A, of B
+#pragma unroll
+    for (int t = 0; t < 12; ++t) {
+        const int i = (t >> 1) & 1, j = t & 1;
+        __builtin_amdgcn_sched_barrier(0);
+        f32x16& acc = t < 4 ? hi[i][j] : lo[i][j];
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(b[term[t >> 2][1]][j], a[term[t >> 2][0]][i], acc, 0, 0, 0);
+        if (t < 8) { s.high(q, scale, t); s.low(q, scale, t); }
+        if (t == 4 || t == 5) s.store(then, 0, t - 4);
+        if (t == 8 || t == 9) s.store(then, 1, t - 8);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+// one 32 x 32 tile and its neighbour (rows of b[1]) on the fp32 matrix cores, straight from memory
+__device__ __forceinline__ void multiply_exactly(const float* pa, const float* pb0, const float* pb1, int fk, int K, f32x16 (&acc)[2]) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[0][e] = acc[1][e] = 0.f;
+    for (int k = 4 * fk; k < K + 4 * fk; k += 8) {
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        const bool in = k < K;
+        const f32x4 a = in ? *reinterpret_cast<const f32x4*>(pa + k) : zero;
+        const f32x4 b0 = in ? *reinterpret_cast<const f32x4*>(pb0 + k) : zero;
+        const f32x4 b1 = in ? *reinterpret_cast<const f32x4*>(pb1 + k) : zero;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(b0[v], a[v], acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(b1[v], a[v], acc[1], 0, 0, 0);
+        }
+    }
+}
+
+template <int EPI>
+__global__ __launch_bounds__(512, 2) void gemm_f32_halves_kernel(const float* __restrict__ A, int lda, TileMap m, ExpertTable tab,
+                                                                int which0, int which1, int N, int K, float* __restrict__ C, int ldc,
+                                                                int tiles_n, int ncu, int walk) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    constexpr int NOUT = (EPI == EPI_SWIGLU) ? XN / 2 : XN;
+    const int n_tiles_m = *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(m.n_tiles));
+    const int total = n_tiles_m * tiles_n;
+    const WalkRun run = walk_run(blockIdx.x, ncu, walk, total);
+    int item = __builtin_amdgcn_readfirstlane(run.item);
+    const int end_item = __builtin_amdgcn_readfirstlane(run.end);
+    if (item >= end_item) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int grp = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+    const int fr = lane & 31, fk = lane >> 5;
+    const int nk = ((K + XK - 1) / XK + 1) & ~1;           // even; k-tiles past K count as zeros
+    const int k_full = K / XK;                             // k-tiles without an end of K in them
+
+    struct Tile { int row0, nrows, n0, ex; const int32_t* rel; };
+    struct Source { __amdgpu_buffer_rsrc_t a, b; uint32_t a_voff, b_voff; };
+    constexpr uint32_t kNoOffset = 0xFFFFFFF0u;               // past the end of the buffer (row offsets end below it, see ffn_impl)
+    // what this lane fetches: chunk `lc` of tile row 16 wave + lane / 4, of A and of B; it goes to slot `lane` of block `wave`
+    const int lc = (lane & 3) ^ (lane >> 4);
+    auto weights = [&](int which, int ex) { return reinterpret_cast<const char*>(which == 0 ? tab.w1[ex] : which == 1 ? tab.w_up[ex] : tab.w_down[ex]); };
+    auto describe = [&](int id, Tile& t, Source& s) {
+        int tile_m, tile_n;
+        tile_of_block(id, total, n_tiles_m, tiles_n, &tile_m, &tile_n);
+        tile_m = __builtin_amdgcn_readfirstlane(tile_m);
+        auto rec = [&](const int32_t* p) { return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p))[tile_m]; };
+        t.row0 = rec(m.row0);
+        t.nrows = rec(m.nrows);
+        t.ex = rec(m.expert);
+        t.rel = rec(m.gather) ? m.rel + (size_t)tile_m * kRelPitch : nullptr;
+        t.n0 = __builtin_amdgcn_readfirstlane(tile_n * NOUT);
+        const int r = 16 * wave + (lane >> 2);
+        int ar = min(r, t.nrows - 1);
+        if (t.rel) ar = t.rel[ar];                         // gathered tile: offsets below 2^32 bytes (checked on the host)
+        s.a = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(A + (size_t)t.row0 * lda), 0, kNoOffset, 0x00027000);
+        s.a_voff = (uint32_t)ar * (uint32_t)lda * 4u;
+        // SwiGLU: the 64 weight rows of a wave-column are 32 gate rows and the 32 up rows of the same columns
+        s.b = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(weights((EPI == EPI_SWIGLU && (wave & 2)) ? which1 : which0, t.ex) + (size_t)t.n0 * K * 4), 0, kNoOffset, 0x00027000);
+        const int col = (EPI == EPI_SWIGLU) ? (wave >> 2) * 32 + (r & 31) : r;
+        s.b_voff = (uint32_t)min(col, N - 1 - t.n0) * (uint32_t)K * 4u;
+        asm volatile("" : "+v"(s.a_voff), "+v"(s.b_voff));  // stay 32-bit lane offsets next to a scalar base
+    };
+    Tile cur, next;
+    Source src, src_next;
+    bool more = item + ncu < end_item;
+    // Byte offsets of the lane's two quads inside a k-tile.  Past K nothing counts: those lanes' offsets lie past the end of
+    // the buffer, which reads as zero.
+    const uint32_t quad0 = (uint32_t)lc * 16u, quad1 = quad0 + 64u;
+    auto fetch = [&](f32x4 (&q)[4], int kt) {
+        const int at = kt * (XK * 4);
+        const bool in0 = kt < k_full || kt * XK + lc * 4 < K, in1 = kt < k_full || kt * XK + 16 + lc * 4 < K;
+        auto load = [&](__amdgpu_buffer_rsrc_t r, uint32_t off, bool in) { return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, in ? off : kNoOffset, at, 0)); };
+        q[0] = load(src.a, src.a_voff + quad0, in0);
+        q[1] = load(src.a, src.a_voff + quad1, in1);
+        q[2] = load(src.b, src.b_voff + quad0, in0);
+        q[3] = load(src.b, src.b_voff + quad1, in1);
+    };
+    f32x4 even[4], odd[4];                                 // k-tiles in flight: two quads of A, two of B
+    float scale[2];                                        // of the rows that this lane splits
+    Acc22 hi, lo;
+    auto clear = [&] {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) hi[i][j][e] = lo[i][j][e] = 0.f;
+    };
+    const int a_off = tile_off(wm * 64 + fr, 2 * grp + fk), b_off = kXOperand + tile_off(wn * 64 + fr, 2 * grp + fk);
+    const int w_off = wave * 1024 + lane * 16;
+    int tile_parity = 0;
+    int32_t* exponents = reinterpret_cast<int32_t*>(lds + 2 * kXStage + 2 * kXGive);
+    auto rescale = [&](const f32x4 (&q)[4]) {              // scales of the tile whose first k-tile is in q; to LDS what undoes them
+        const int ea = scale_exponent(q[0], q[1]), eb = scale_exponent(q[2], q[3]);
+        scale[0] = power_of_two(ea);
+        scale[1] = power_of_two(eb);
+        int32_t* e = exponents + tile_parity * (XM + XN);
+        if ((lane & 3) == 0) { e[16 * wave + (lane >> 2)] = -ea; e[XM + 16 * wave + (lane >> 2)] = -eb; }
+        tile_parity ^= 1;
+    };
+    // k-tile kt is in `now`; the one behind it goes to `then`
+    auto step = [&](int kt, unsigned char* now, unsigned char* then, f32x4 (&q)[4]) {
+        if (kt + 3 == nk && more) src = src_next;
+        __builtin_amdgcn_sched_barrier(0);
+        if (kt + 1 == nk) rescale(q);                      // the next tile's first k-tile
+        __builtin_amdgcn_sched_barrier(0);
+        multiply_halves(now + a_off, now + b_off, hi, lo, q, scale, then + w_off);
+        fetch(q, kt + 3 >= nk ? kt + 3 - nk : kt + 3);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0): this wave has read `now` and written `then`
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+
+    describe(item, cur, src);
+    fetch(even, 0);
+    fetch(odd, 1);
+    if (more) describe(item + ncu, next, src_next);
+    clear();
+    unsigned char *st0 = lds, *st1 = lds + kXStage, *sums = lds + 2 * kXStage;
+    uint32_t* votes = reinterpret_cast<uint32_t*>(exponents + 2 * (XM + XN));
+    rescale(even);
+    split_halves(even, scale, st0 + w_off);
+    fetch(even, 2);
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    while (true) {
+        const int32_t* undo = exponents + (tile_parity ^ 1) * (XM + XN);
+        for (int kt = 0; kt < nk; kt += 2) {
+            step(kt, st0, st1, odd);
+            step(kt + 1, st1, st0, even);
+        }
+        // sums of the group, and what of them the other group finishes
+        float off = 0.f;                                   // 0, or NaN if a sum is not finite
+        unsigned char* give = sums + grp * kXGive + (wave & 3) * 8192 + lane * 16;
+        const unsigned char* take = sums + (grp ^ 1) * kXGive + (wave & 3) * 8192 + lane * 16;
+        f32x16 fin[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                f32x4 other;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int e = 4 * q + t;
+                    const float x0 = __builtin_fmaf(lo[0][j][e], 1.f / kLowScale, hi[0][j][e]), x1 = __builtin_fmaf(lo[1][j][e], 1.f / kLowScale, hi[1][j][e]);
+                    off = __builtin_fmaf(x0, 0.f, __builtin_fmaf(x1, 0.f, off));
+                    fin[j][e] = grp == 0 ? x0 : x1;
+                    other[t] = grp == 0 ? x1 : x0;
+                }
+                *reinterpret_cast<f32x4*>(give + (j * 4 + q) * 1024) = other;
+            }
+        const bool redo = __ballot(!(off == 0.f)) != 0;
+        if (lane == 0) votes[wave] = redo ? 1 : 0;
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        uint32_t any = 0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) any |= votes[w];
+        any = __builtin_amdgcn_readfirstlane(any);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 v = *reinterpret_cast<const f32x4*>(take + (j * 4 + q) * 1024);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) fin[j][4 * q + t] += v[t];
+            }
+        const int ea = undo[wm * 64 + grp * 32 + fr];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    fin[j][4 * q + t] = ldexpf(fin[j][4 * q + t], ea + undo[XM + wn * 64 + j * 32 + q * 8 + fk * 4 + t]);
+        const int gr = wm * 64 + grp * 32 + fr;
+        if (any) {
+            int ar = min(gr, cur.nrows - 1);
+            if (cur.rel) ar = cur.rel[ar];
+            const int c0 = cur.n0 + wn * (NOUT / 2) + fr;
+            const float* w0 = reinterpret_cast<const float*>(weights(which0, cur.ex));
+            const float* w1 = (EPI == EPI_SWIGLU) ? reinterpret_cast<const float*>(weights(which1, cur.ex)) : w0;
+            multiply_exactly(A + (size_t)(cur.row0 + ar) * lda, w0 + (size_t)min(c0, N - 1) * K,
+                             w1 + (size_t)min((EPI == EPI_SWIGLU) ? c0 : c0 + 32, N - 1) * K, fk, K, fin);
+        }
+        if (gr < cur.nrows) {
+            float* crow = C + (size_t)(cur.row0 + (cur.rel ? cur.rel[gr] : gr)) * ldc;
+#pragma unroll
+            for (int j = 0; j < ((EPI == EPI_SWIGLU) ? 1 : 2); ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    f32x4 v;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) v[t] = epilogue<EPI>(fin[j][4 * g + t], (EPI == EPI_SWIGLU) ? fin[1][4 * g + t] : 0.f);
+                    const int col = cur.n0 + wn * (NOUT / 2) + j * 32 + g * 8 + fk * 4;
+                    if (col < N) *reinterpret_cast<f32x4*>(crow + col) = v;     // N is a multiple of 4
+                }
+        }
+        if (!more) return;
+        item += ncu;
+        cur = next;
+        more = item + ncu < end_item;
+        if (more) describe(item + ncu, next, src_next);
+        clear();
+    }
 }
 
 template <int EPI, int MI, int NJ> struct EpiGeom {
@@ -1917,9 +2231,50 @@ int launch_bf16_skinny(const void* A, int lda, const TileMap& m, const ExpertTab
     return launch_bf16_skinny_mt<EPI, 2>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, partial, st);
 }
 
+// Tiles of the fp16 kernel that a block walks through (see kWalkUs).
+int halves_walk_tiles(int K) { return std::max(1, (int)(kWalkUs / (3.3 + 0.89 * (K / (double)XK)))); }
+// Which kernel an fp32 GEMM takes: the 64 x 64 tiles of gemm_f32_kernel keep more CUs busy where there are few tiles, the
+// 128 x 128 ones of gemm_f32_halves_kernel have twice the rate.  Both times are modelled from the estimated number of
+// tiles; the constants (us) are fitted to 250 shares of 20 to 20000 rows, 1 to 8 experts, H of 128 to 1024 and F of 128 to 2816
+// (median error 2 %, 19 of 20 within 7 %).  3 % are left to the older kernel: over those shares none is slower than with
+// it alone.  3001 rows of 1024 -> 2816 -> 1024 SwiGLU: 407 -> 216 us for the pair; 476 rows of 676 -> 2152 -> 676 for 8
+// experts: 95 with either; 64 rows of 640 -> 2424 -> 640: 61 against 77, so those keep the small tiles.
+double f32_us(bool in_halves, int R, int n_used, int N, int K, int act, int cus) {
+    const int side = in_halves ? XM : FM, cols = side / (act == MOE_ACT_SWIGLU ? 2 : 1);
+    const double per_cu = estimated_tiles_m(R, side, n_used) * ((N + cols - 1) / cols) / cus, rounds = std::ceil(per_cu);
+    const int nk = in_halves ? ((K + XK - 1) / XK + 1) / 2 * 2 : (K + FK - 1) / FK;
+    if (in_halves) return 6.7 + rounds * (2.35 + 0.59 * nk) + per_cu * (0.94 + 0.296 * nk);
+    return 5.5 + rounds * (0.8 + 0.515 * nk);
+}
+bool f32_in_halves(int R, int n_used, int N, int K, int act, int cus) {
+    return K >= kXMinK && f32_us(true, R, n_used, N, K, act, cus) < 0.97 * f32_us(false, R, n_used, N, K, act, cus);
+}
+// Both GEMMs of a share.  Without room for two maps the small tiles, unless the large ones win for both.
+void take_f32_kernels(int R, int n_used, int nseg, int H, int F, int act, int cus, bool (&in_halves)[2]) {
+    in_halves[0] = f32_in_halves(R, n_used, F, H, act, cus);
+    in_halves[1] = f32_in_halves(R, n_used, H, F, -1, cus);
+    if (in_halves[0] != in_halves[1] && !maps_fit(R, nseg, FM, XM)) in_halves[0] = in_halves[1] = false;
+}
 template <int EPI>
-int launch_f32(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
+int launch_f32_halves(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
+                     void* C, int ldc, int R, int nseg, hipStream_t st) {
+    const int nout = (EPI == EPI_SWIGLU) ? XN / 2 : XN;
+    const int tiles_n = (N + nout - 1) / nout, ncu = round_size(), walk = halves_walk_tiles(K);
+    static bool attr_done = false;
+    if (!attr_done) {
+        MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_halves_kernel<EPI>), hipFuncAttributeMaxDynamicSharedMemorySize, kXLds));
+        attr_done = true;
+    }
+    hipLaunchKernelGGL((gemm_f32_halves_kernel<EPI>), dim3(walk_blocks(max_tiles_of(R, XM, nseg) * tiles_n, walk, ncu)), dim3(512), kXLds, st,
+                       reinterpret_cast<const float*>(A), lda, m, tab, which0, which1, N, K, reinterpret_cast<float*>(C), ldc, tiles_n, ncu, walk);
+    MOE_LAUNCH_CHECK("gemm_f32_halves_kernel");
+    return MOE_OK;
+}
+
+template <int EPI>
+int launch_f32(bool in_halves, const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
                void* C, int ldc, int R, int nseg, hipStream_t st) {
+    if (in_halves) return launch_f32_halves<EPI>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, st);
     const int nout = (EPI == EPI_SWIGLU) ? FN / 2 : FN;
     const int tiles_n = (N + nout - 1) / nout;
     const int max_tiles_m = max_tiles_of(R, FM, nseg);
@@ -1976,6 +2331,16 @@ extern "C" int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t nseg
         for (int i = 0; i < 2; ++i) rows2[i] = kShapeRows[shape[i]];
     }
     if (!maps_fit(R, nseg, rows2[0], rows2[1])) return moe_set_error(MOE_EINTERNAL, "tile maps of %d and %d rows leave no room for the counters", rows2[0], rows2[1]);
+    return MOE_OK;
+}
+
+extern "C" int moe_selfcheck_f32_kernels(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2) {
+    if (R < 1 || n_used < 1 || nseg < n_used || nseg > kMaxSeg || H < 4 || H % 4 != 0 || F < 4 || F % 4 != 0 || act < 0 || act > 2 || ncu < 1 || !rows2)
+        return moe_set_error(MOE_EINVAL, "moe_selfcheck_f32_kernels: bad argument");
+    bool in_halves[2];
+    take_f32_kernels(R, n_used, nseg, H, F, act, ncu, in_halves);
+    for (int i = 0; i < 2; ++i) rows2[i] = in_halves[i] ? XM : FM;
+    if (rows2[0] != rows2[1] && !maps_fit(R, nseg, rows2[0], rows2[1])) return moe_set_error(MOE_EINTERNAL, "no room for tile maps of %d and %d rows", rows2[0], rows2[1]);
     return MOE_OK;
 }
 
@@ -2182,10 +2547,14 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     const int gather = (size_t)R * (size_t)std::max(H, F) * elem_size(dtype) <= 0xFFFFFFFFull ? 1 : 0;
     TileShape shape[2] = {TS_256, TS_256};
     int n_used = 1;
+    bool in_halves[2] = {false, false};
     int bm[2] = {FM, FM};
-    if (skinny) {
+    if (dtype == MOE_F32) {
+        take_f32_kernels(R, std::min(gather ? std::min(n_local, nseg) : nseg, R), nseg, H, F, act, round_size(), in_halves);
+        for (int i = 0; i < 2; ++i) bm[i] = in_halves[i] ? XM : FM;
+    } else if (skinny) {
         bm[0] = bm[1] = skinny_tile_rows(R);
-    } else if (dtype == MOE_BF16) {
+    } else {
         n_used = std::min(gather ? std::min(n_local, nseg) : nseg, R);   // runs of rows that share no tile
         take_shapes(R, n_used, nseg, H, F, act, round_size(), shape);
         if (timed_gemm != 0) {
@@ -2199,7 +2568,7 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         }
         for (int i = 0; i < 2; ++i) bm[i] = kShapeRows[shape[i]];
     }
-    if (dtype == MOE_BF16 && !maps_fit(R, nseg, bm[0], bm[1])) return moe_set_error(MOE_EINTERNAL, "moe_expert_ffn: tile maps of %d rows in %d segments", R, nseg);
+    if ((dtype == MOE_BF16 || bm[0] != bm[1]) && !maps_fit(R, nseg, bm[0], bm[1])) return moe_set_error(MOE_EINTERNAL, "moe_expert_ffn: tile maps of %d rows in %d segments", R, nseg);
     if (ev) MOE_HIP(hipEventRecord(ev[0], st));
     MapJobs jobs;
     jobs.job[0] = MapJob{bm[0], max_tiles_of(R, bm[0], nseg), tilemap_at(workspace, R)};
@@ -2238,12 +2607,12 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         if (ev) MOE_HIP(hipEventRecord(ev[2], st));
         rc = launch_bf16_shape<EPI_PLAIN>(shape[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, partial, st, timed_gemm == 2, marks, marks_len);
     } else {
-        if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, st);
-        else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, st);
-        else rc = launch_f32<EPI_SILU>(recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, st);
+        if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(in_halves[0], recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, st);
+        else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(in_halves[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, st);
+        else rc = launch_f32<EPI_SILU>(in_halves[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, st);
         if (rc != MOE_OK) return rc;
         if (ev) MOE_HIP(hipEventRecord(ev[2], st));
-        rc = launch_f32<EPI_PLAIN>(hmid, F, m, tab, 2, 2, H, F, out, H, R, nseg, st);
+        rc = launch_f32<EPI_PLAIN>(in_halves[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, st);
     }
     if (rc != MOE_OK) return rc;
     if (ev) MOE_HIP(hipEventRecord(ev[3], st));

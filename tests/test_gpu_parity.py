@@ -636,6 +636,55 @@ def test_expert_ffn_fp32_tiles(H, act, R, Hd, F, n_local, nseg):
     H.assert_close(H.host(out), O.expert_ffn(recv, off, exp, experts, act), "fp32")
 
 
+# fp32 GEMMs on pairs of halves (128-row tiles): a K that ends inside a k-tile and an odd number of them, gathered and
+# ragged tiles, N of no whole tile, several tiles per block, one kernel of each kind with a map of its own
+@pytest.mark.parametrize("act,R,Hd,F,n_local,nseg,rows", [(1, 1300, 1156, 1164, 2, 9, [128, 128]), (2, 4000, 132, 1012, 3, 40, [128, 64]),
+                                                          (0, 60000, 132, 292, 1, 1, [128, 128]), (0, 9000, 516, 772, 2, 700, [128, 128])])
+def test_expert_ffn_fp32_in_halves(H, act, R, Hd, F, n_local, nseg, rows):
+    assert f32_rows(R, n_local, nseg, Hd, F, act) == rows
+    test_expert_ffn_fp32_tiles(H, act, R, Hd, F, n_local, nseg)
+
+
+def f32_rows(R, n_local, nseg, Hd, F, act):
+    import ctypes
+    from paper_2410_17043_amd import _lib
+    got = (ctypes.c_int32 * 2)()
+    assert _lib.load().moe_selfcheck_f32_kernels(R, n_local, nseg, Hd, F, act, 256, got) == 0
+    return list(got)
+
+
+def test_expert_ffn_fp32_in_halves_takes_every_value(H):
+    """Rows and weight rows of any scale, zeros where the scale is taken from, elements far above it, infinities, NaN."""
+    R, Hd, F, n_local, nseg = 4000, 356, 1012, 2, 40
+    assert f32_rows(R, n_local, nseg, Hd, F, 0) == [128, 128]
+    cfg = small("c1_tiny_fp32", H=Hd, F=F, act=0)
+    r = np.random.default_rng(5)
+    recv = r.standard_normal((R, Hd)).astype(np.float32)
+    scale = 10.0 ** r.integers(-30, 20, size=R)
+    recv *= scale[:, None].astype(np.float32)
+    recv[100:103] = 0.0
+    recv[200, :64] = 0.0
+    recv[300, :32] *= np.float32(1e-9)                                # elements past the range of the row's scale: the tile is formed again
+    recv[301, 5] *= np.float32(1e6)
+    experts = [W.make_expert_weights(cfg, e) for e in range(n_local)]
+    experts[0]["w1"][7] *= np.float32(1e-25)
+    experts[1]["w_down"][3, :40] = 0.0
+    bad = [1000, 2500, 2501]
+    recv[bad[0], 350], recv[bad[1], 0], recv[bad[2], 40] = np.inf, np.nan, -np.inf
+    off, exp = make_segments(r, R, nseg, n_local)
+    out = H.host(H.run_ffn(H.dev(recv, "fp32"), off, exp, [H.weights_to_dev(w, "fp32") for w in experts], Hd, F, 0, "fp32"))
+    fine = np.ones(R, dtype=bool)
+    fine[bad] = False
+    with np.errstate(all="ignore"):
+        ref = O.expert_ffn(np.where(fine[:, None], recv, 0.0), off, exp, experts, 0)
+    assert (~np.isfinite(out[~fine])).any(axis=1).all()
+    assert np.isfinite(out[fine]).all() and (out[100:103] == 0).all()
+    # per row: two sums of up to 1012 terms, each within sqrt(K) 2^-24 of the norms of its factors, and their rounding;
+    # what lies below the normal range of fp32 (rows of 1e-30, squared by silu) rounds to multiples of 2^-149
+    err = np.linalg.norm(out - ref, axis=1)[fine]
+    assert (err <= 4e-6 * np.linalg.norm(ref, axis=1)[fine] + np.sqrt(Hd) * 1012 * 2.0 ** -149).all()
+
+
 @pytest.mark.parametrize("R,nseg", [(60, 5), (300, 63), (300, 64), (300, 65), (1000, 64)])
 def test_expert_ffn_tile_map_skips_what_it_must(H, R, nseg):
     """Empty segments, segments of no local expert, rows before the first and after the last segment, on both sides of
