@@ -258,6 +258,11 @@ int moe_selfcheck_tile_shape(int32_t R, int32_t n_used, int32_t N, int32_t K, in
  * GEMM, second GEMM.  Checks that the maps leave room for the counters of tiles that are cut along K. */
 int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2);
 
+/* The two forms of the planner's flow player (the wider one on hosts with AVX-512) on an order of n GPUs: the same bits, as
+ * they are played and after improving the order by exchanges.  Returns 1, 0 where there is only one form, or a negative
+ * moe_status. */
+int moe_selfcheck_flow_player(int32_t n, const int64_t* D, const double* B, const int32_t* order);
+
 /* Rows per tile of the two GEMMs of an fp32 share of R rows in nseg segments of n_used experts: 64 (fp32 matrix cores) or
  * 128 (pairs of halves on the fp16 ones).  Self check, runs on the host. */
 int moe_selfcheck_f32_kernels(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2);

@@ -495,3 +495,20 @@ def test_send_order_time_is_that_of_playing_the_order_and_no_exchange_improves_i
                 o = p["dest_order"].copy()
                 o[i, [q, q + 1]] = o[i, [q + 1, q]]
                 assert P.aurora_simulate(D, B, o) >= p["order_time"] * (1 - 1e-9)
+
+
+def test_both_forms_of_the_flow_player_give_the_same_bits():
+    """Either side of the lane counts at which the wide form takes another register more; unequal, extreme and equal rates,
+    many and few flows."""
+    import ctypes as C
+    from paper_2410_17043_amd import _lib
+    lib = _lib.load()
+    r = np.random.default_rng(11)
+    for n in (2, 3, 8, 9, 16, 17, 32, 33, 64):
+        for rates in ("equal", "unequal", "extreme"):
+            D = r.integers(0, 2 if rates == "extreme" else 5000, size=(n, n)).astype(np.int64)
+            B = None if rates == "equal" else r.uniform(0.5, 1.0, size=n) if rates == "unequal" else 10.0 ** r.uniform(-12, 12, size=n)
+            order = np.stack([r.permutation(n) for _ in range(n)]).astype(np.int32)
+            got = lib.moe_selfcheck_flow_player(n, D.ctypes.data_as(C.POINTER(C.c_int64)), None if B is None else B.ctypes.data_as(C.POINTER(C.c_double)),
+                                                order.ctypes.data_as(C.POINTER(C.c_int32)))
+            assert got in (0, 1), (n, rates, lib.moe_last_error())
