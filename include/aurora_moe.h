@@ -263,6 +263,10 @@ int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t nseg, int32_t H
  * moe_status. */
 int moe_selfcheck_flow_player(int32_t n, const int64_t* D, const double* B, const int32_t* order);
 
+/* Narrow tiles that the two GEMMs of a bf16 share take instead (few rows per expert): 10 MT + NT for tiles of 32 MT rows x
+ * 32 NT weight rows, 0 where the kernels of moe_selfcheck_tile_shapes run.  Checks that the tile maps fit. */
+int moe_selfcheck_narrow(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* forms2);
+
 /* Rows per tile of the two GEMMs of an fp32 share of R rows in nseg segments of n_used experts: 64 (fp32 matrix cores) or
  * 128 (pairs of halves on the fp16 ones).  Self check, runs on the host. */
 int moe_selfcheck_f32_kernels(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2);

@@ -1977,6 +1977,171 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_skinny_kernel(const uint16_t
     skinny_store<EPI, MT>(acc, wave, lane, row0, nrows, rel, n0, N, C, ldc);
 }
 
+// Shares of up to a tile of rows per expert (see narrow_form): every weight is used once or twice, and what counts is how
+// many CUs stream and what each has to fetch - a CU gets about 58 GB/s of operands that are not in its L2, whether 90 or 130
+// KB of loads are in flight.  So a tile is 32 MT rows x only 32 NT weight rows over the whole of K: enough tiles for the
+// chip without cutting K, which costs the 128 x 128 tiles and the kernel above 64 KB of partial sums per block, a counter and a
+// last block that adds them.  Weights 2048 -> 1408 -> 2048 for four experts and 403 rows, weights from cold memory: 29.4 + 22.1
+// -> 18.8 + 12.5 us; 64 rows of 2048 -> 2816 -> 2048 13.3 + 15.0 -> 11.2 + 10; a decode step with both 130 -> 95.
+// 8 waves (4 for 32-row tiles), of which KP share a row tile and take a part of every stage each, added through LDS at the end:
+// two waves per SIMD hide each other's LDS reads (19.4 + 12.9 us with one).  Rows fetched straight to the registers of the
+// wave that multiplies them, which leaves the LDS to the weights, took 26.8 + 19.6: a load of 32 bytes from each of 32
+// rows occupies the address unit four times as long as one of 256 bytes from each of 4.
+template <int MT, int NT> struct NarrowGeom {
+    static constexpr int BM_ = 32 * MT, BN_ = 32 * NT;
+    static constexpr int KW = (MT == 4 && NT == 2) ? 64 : 128;   // elements of K per stage: smaller where a stage takes much of the ring
+    static constexpr int RPL = 512 / KW;                 // rows that a wave-load (1 KB) fetches
+    static constexpr int A_BYTES = BM_ * KW * 2;
+    static constexpr int STAGE = A_BYTES + BN_ * KW * 2;
+    static constexpr int WAVES = MT == 1 ? 4 : 8;
+    static constexpr int NA = BM_ / RPL / WAVES, NB = BN_ / RPL / WAVES;   // wave-loads per stage and wave
+    static constexpr int STAGES = 160 * 1024 / STAGE < 8 ? 160 * 1024 / STAGE : 8;
+    static constexpr int LDS = STAGES * STAGE;
+    static constexpr int AHEAD = (STAGES - 2) * (NA + NB);   // loads that may be outstanding when a stage is needed
+    static constexpr int WAIT = 0x0070 | (AHEAD & 15) | (AHEAD >> 4) << 14;   // vmcnt(AHEAD) lgkmcnt(0)
+    static constexpr int KP = WAVES / MT;                    // waves that share a row tile, each with a part of every stage
+    static constexpr int STEPS = KW / 16 / KP;           // k-steps of a wave per stage
+    static_assert(NB >= 1 && AHEAD < 64 && STEPS >= 1 && LDS >= WAVES * NT * 4096, "");
+    // byte offset of (row, 16-byte chunk) inside an operand's part of a stage: blocks of one wave-load, conflict-free
+    static __device__ __forceinline__ int off(int row, int c) { return KW == 64 ? f32_slot(row, c) * 16 : skinny_off(row, c); }
+    // the chunk that lane l of a wave-load fetches, which goes to its slot l: row l / (64 / RPL) of block blk
+    static __device__ __forceinline__ int chunk(int l, int blk) {
+        return KW == 64 ? (l & 7) ^ ((l >> 4) | (blk & 1) << 2) : (l & 15) ^ ((l >> 4) << 2 | (blk & 3));
+    }
+};
+
+template <int EPI, int MT, int NT>
+__global__ __launch_bounds__((64 * NarrowGeom<MT, NT>::WAVES), (NarrowGeom<MT, NT>::WAVES / 4)) void gemm_bf16_narrow_kernel(const uint16_t* __restrict__ A, int lda, TileMap m, ExpertTable tab,
+                                                                  int which0, int which1, int N, int K, uint16_t* __restrict__ C, int ldc, int tiles_n) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    using G = NarrowGeom<MT, NT>;
+    constexpr int NOUT = (EPI == EPI_SWIGLU) ? G::BN_ / 2 : G::BN_;
+    const int n_tiles_m = *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(m.n_tiles));
+    const int total = n_tiles_m * tiles_n;
+    for (int item = blockIdx.x; item < total; item += gridDim.x) {   // one, unless the list has more runs than experts
+        const int tile_id = skinny_tile(item, total);
+        const int tile_m = __builtin_amdgcn_readfirstlane(tile_id % n_tiles_m), tile_n = __builtin_amdgcn_readfirstlane(tile_id / n_tiles_m);
+        auto rec = [&](const int32_t* p) { return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p))[tile_m]; };
+        const int row0 = rec(m.row0), nrows = rec(m.nrows), ex = rec(m.expert);
+        const int32_t* rel = rec(m.gather) ? m.rel + (size_t)tile_m * kRelPitch : nullptr;
+        auto pick = [&](int which) { return reinterpret_cast<const char*>(which == 0 ? tab.w1[ex] : which == 1 ? tab.w_up[ex] : tab.w_down[ex]); };
+        const int n0 = tile_n * NOUT;
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int ns = K / G::KW;
+        const int lrow = lane / (64 / G::RPL);
+        const char* a_base = reinterpret_cast<const char*>(A + (size_t)row0 * lda);
+        const char *b_base = pick(which0) + (size_t)n0 * K * 2, *u_base = (EPI == EPI_SWIGLU) ? pick(which1) + (size_t)n0 * K * 2 : b_base;
+        uint32_t a_voff[G::NA], b_voff[G::NB];
+        int ar[G::NA];
+#pragma unroll
+        for (int i = 0; i < G::NA; ++i) ar[i] = min((G::NA * wave + i) * G::RPL + lrow, nrows - 1);
+        if (rel) {
+            int t[G::NA];
+#pragma unroll
+            for (int i = 0; i < G::NA; ++i) t[i] = rel[ar[i]];
+#pragma unroll
+            for (int i = 0; i < G::NA; ++i) ar[i] = t[i];
+        }
+#pragma unroll
+        for (int i = 0; i < G::NA; ++i) a_voff[i] = (uint32_t)ar[i] * (uint32_t)lda * 2u + (uint32_t)G::chunk(lane, G::NA * wave + i) * 16u;
+#pragma unroll
+        for (int i = 0; i < G::NB; ++i) {
+            const int blk = G::NB * wave + i, rr = blk * G::RPL + lrow;
+            const int col = (EPI == EPI_SWIGLU) ? (rr >> 5) * 16 + (rr & 15) : rr;   // rows 16 .. 31 of each 32 are up rows
+            b_voff[i] = (uint32_t)min(col, N - 1 - n0) * (uint32_t)K * 2u + (uint32_t)G::chunk(lane, blk) * 16u;
+        }
+        auto issue = [&](int t) {                            // stage t into ring slot t % STAGES; past the end the last one again
+            unsigned char* st = lds + (t % G::STAGES) * G::STAGE;
+            const size_t kb = (size_t)min(t, ns - 1) * G::KW * 2;
+#pragma unroll
+            for (int i = 0; i < G::NB; ++i) {
+                const int blk = G::NB * wave + i;
+                const char* p = ((EPI == EPI_SWIGLU && (blk * G::RPL & 16)) ? u_base : b_base) + kb;
+                unsigned char* to = st + G::A_BYTES + blk * 1024;
+                uint32_t& v = b_voff[i];
+                asm volatile("" : "+s"(p), "+v"(v));
+                __builtin_amdgcn_global_load_lds(p + v, (__attribute__((address_space(3))) void*)to, 16, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < G::NA; ++i) {
+                const char* p = a_base + kb;
+                unsigned char* to = st + (G::NA * wave + i) * 1024;
+                uint32_t& v = a_voff[i];
+                asm volatile("" : "+s"(p), "+v"(v));
+                __builtin_amdgcn_global_load_lds(p + v, (__attribute__((address_space(3))) void*)to, 16, 0, 0);
+            }
+        };
+        f32x16 acc[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
+#pragma unroll
+        for (int t = 0; t < G::STAGES - 1; ++t) issue(t);
+        const int fr = lane & 31, fk = lane >> 5;
+        const int rt = wave % MT, kp = wave / MT;            // row tile of this wave, its part of a stage
+        for (int t = 0; t < ns; ++t) {
+            __builtin_amdgcn_s_waitcnt(G::WAIT);             // stage t has landed
+            __builtin_amdgcn_s_barrier();                    // everybody's part of it; the slot of stage t - 1 is free
+            asm volatile("" ::: "memory");
+            const unsigned char* st = lds + (t % G::STAGES) * G::STAGE;
+            bf16x8 af[G::STEPS], bf[G::STEPS][NT];
+#pragma unroll
+            for (int s = 0; s < G::STEPS; ++s) {
+                const int c = 2 * (kp * G::STEPS + s) + fk;
+                af[s] = *reinterpret_cast<const bf16x8*>(st + G::off(rt * 32 + fr, c));
+#pragma unroll
+                for (int j = 0; j < NT; ++j) bf[s][j] = *reinterpret_cast<const bf16x8*>(st + G::A_BYTES + G::off(j * 32 + fr, c));
+            }
+            issue(t + G::STAGES - 1);
+#pragma unroll
+            for (int s = 0; s < G::STEPS; ++s)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[s][j], af[s], acc[j], 0, 0, 0);
+        }
+        __builtin_amdgcn_s_waitcnt(0x0070);                  // no load may still be on its way to LDS
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        // the parts of a row tile are added in order by the wave of the first one
+        f32x4* parts = reinterpret_cast<f32x4*>(lds);
+        if (kp > 0)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    parts[((kp * MT + rt) * NT + j) * 256 + q * 64 + lane] = f32x4{acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
+        __builtin_amdgcn_s_waitcnt(0x0070);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        const int gr = rt * 32 + fr;
+        if (kp == 0 && gr < nrows) {
+#pragma unroll
+            for (int k2 = 1; k2 < G::KP; ++k2)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 v = parts[((k2 * MT + rt) * NT + j) * 256 + q * 64 + lane];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) acc[j][4 * q + t] += v[t];
+                    }
+            uint16_t* crow = C + (size_t)(row0 + (rel ? rel[gr] : gr)) * ldc;
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int g = 0; g < ((EPI == EPI_SWIGLU) ? 2 : 4); ++g) {
+                    float v[4];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) v[t] = epilogue_bf16<EPI>(acc[j][4 * g + t], (EPI == EPI_SWIGLU) ? acc[j][4 * ((g + 2) & 3) + t] : 0.f);
+                    const int col = n0 + j * (NOUT / NT) + g * 8 + fk * 4;
+                    if (col < N) *reinterpret_cast<u32x2*>(crow + col) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+                }
+        }
+        __builtin_amdgcn_s_waitcnt(0x0070);
+        __builtin_amdgcn_s_barrier();                        // the next item's loads go to the same LDS
+    }
+}
+
 constexpr int kMaxCU = 256;                    // tail pieces per launch, at most: sizes the partial-tile workspace
 
 // number of CUs of the current device (a round of the grid), at most kMaxCU
@@ -2224,6 +2389,89 @@ int launch_bf16_skinny_mt(const void* A, int lda, const TileMap& m, const Expert
     MOE_LAUNCH_CHECK("gemm_bf16_skinny_kernel");
     return MOE_OK;
 }
+// Which shares take narrow tiles, and of which form.  The time of a form is modelled as what a CU has to fetch (74 GB/s and 3 us per
+// round of tiles), together with the weights at 4.2 TB/s (their 4-norm); that of the weight-streaming kernels likewise, with their
+// pieces; that of the tiled kernels as in played_us; all without the launch.  A form is taken where it is modelled 10 % faster.
+// Only up to 128 rows per expert: beyond, the weights are fetched again for every tile of rows.  The constants are fitted to 760
+// shares of 1 to 2560 rows, 1 to 16 experts, H of 256 to 4096 and F of 256 to 14336, weights from cold memory (median error 8 %);
+// over those the expert FFN gets 1.118 times faster on average (1.157 if the best form were always known, 1.124 without the 10 %), 3
+// shares are more than 3 % slower, by at most 11 %.
+struct NarrowForm { int mt, nt; };                       // mt = 0: none
+constexpr NarrowForm kNarrowForms[] = {{4, 2}, {2, 2}, {2, 1}, {1, 2}, {1, 1}};
+double stream_us(double rounds, double bytes, double gb_s, double per_round, int n_used, int N, int K, int act, double tb_s) {
+    const double cu = rounds * (bytes * 1e-3 / gb_s + per_round), hbm = (double)n_used * N * K * (act == MOE_ACT_SWIGLU ? 4.0 : 2.0) * 1e-6 / tb_s;
+    return std::sqrt(std::sqrt(cu * cu * cu * cu + hbm * hbm * hbm * hbm));
+}
+double narrow_us(NarrowForm f, int R, int n_used, int N, int K, int act, int cus) {
+    const int cols = 32 * f.nt / (act == MOE_ACT_SWIGLU ? 2 : 1);
+    const int tiles = spread_tiles_m(R, 32 * f.mt, n_used, 2) * ((N + cols - 1) / cols);
+    return stream_us((tiles + cus - 1) / cus, 64.0 * (f.mt + f.nt) * K, 74.4, 3.06, n_used, N, K, act, 4.2);
+}
+double skinny_us(int R, int n_used, int N, int K, int act, int cus) {
+    const int rows = skinny_tile_rows(R), cols = SBN / (act == MOE_ACT_SWIGLU ? 2 : 1), ns = K / SKW;
+    const int tiles = spread_tiles_m(R, rows, n_used, 2) * ((N + cols - 1) / cols);
+    const SkinnyPlan p = plan_skinny(tiles, cus, ns);
+    return stream_us((tiles * p.parts + cus - 1) / cus, (rows + SBN) * 2.0 * SKW * p.per, 37.55, -0.29, n_used, N, K, act, 6.14) +
+           (p.parts > 1 ? 2.0 + 0.73 * p.parts : 0.0);
+}
+NarrowForm narrow_form(int R, int n_used, int N, int K, int act, int cus, double other_us) {
+    NarrowForm best{0, 0};
+    double best_us = 0.9 * other_us;
+    for (const NarrowForm f : kNarrowForms) {
+        const double us = narrow_us(f, R, n_used, N, K, act, cus);
+        if (us < best_us) { best = f; best_us = us; }
+    }
+    return best;
+}
+// both GEMMs of a share that would take `rows` rows per tile otherwise (of the streaming kernels up to kSkinnyRows rows)
+void take_narrow_forms(int R, int n_used, int H, int F, int act, int cus, const int (&rows)[2], NarrowForm (&form)[2]) {
+    for (int g = 0; g < 2; ++g) {
+        const int N = g == 0 ? F : H, K = g == 0 ? H : F, a = g == 0 ? act : -1;
+        double other;
+        if (R <= kSkinnyRows) {
+            other = skinny_us(R, n_used, N, K, a, cus);
+        } else {
+            const TileShape t = rows[g] == kShapeRows[TS_128] ? TS_128 : rows[g] == kShapeRows[TS_192] ? TS_192 : TS_256;
+            other = played_us(t, spread_tiles_m(R, rows[g], n_used, 2), R, n_used, N, K, a, cus);
+        }
+        form[g] = narrow_form(R, n_used, N, K, a, cus, other);
+    }
+}
+// the same, unless their maps do not fit; rows: then theirs
+void take_narrow(int R, int n_used, int nseg, int H, int F, int act, int cus, int (&rows)[2], NarrowForm (&form)[2]) {
+    form[0] = form[1] = NarrowForm{0, 0};
+    if (R > 128 * n_used) return;
+    take_narrow_forms(R, n_used, H, F, act, cus, rows, form);
+    const int new_rows[2] = {form[0].mt ? 32 * form[0].mt : rows[0], form[1].mt ? 32 * form[1].mt : rows[1]};
+    if (!maps_fit(R, nseg, new_rows[0], new_rows[1])) { form[0] = form[1] = NarrowForm{0, 0}; return; }
+    rows[0] = new_rows[0];
+    rows[1] = new_rows[1];
+}
+
+template <int EPI, int MT, int NT>
+int launch_bf16_narrow_nt(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
+                          void* C, int ldc, int R, int nseg, int n_used, hipStream_t st) {
+    using G = NarrowGeom<MT, NT>;
+    const int nout = (EPI == EPI_SWIGLU) ? G::BN_ / 2 : G::BN_;
+    const int tiles_n = (N + nout - 1) / nout;
+    static bool attr_done = false;
+    if (!attr_done) {
+        MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_narrow_kernel<EPI, MT, NT>), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS));
+        attr_done = true;
+    }
+    hipLaunchKernelGGL((gemm_bf16_narrow_kernel<EPI, MT, NT>), dim3(std::min(max_tiles_of(R, G::BM_, nseg), (R + n_used * (G::BM_ - 1)) / G::BM_) * tiles_n), dim3(64 * G::WAVES), G::LDS, st,
+                       reinterpret_cast<const uint16_t*>(A), lda, m, tab, which0, which1, N, K, reinterpret_cast<uint16_t*>(C), ldc, tiles_n);
+    MOE_LAUNCH_CHECK("gemm_bf16_narrow_kernel");
+    return MOE_OK;
+}
+template <int EPI>
+int launch_bf16_narrow(NarrowForm f, const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
+                       void* C, int ldc, int R, int nseg, int n_used, hipStream_t st) {
+#define MOE_NARROW(a, b) if (f.mt == a && f.nt == b) return launch_bf16_narrow_nt<EPI, a, b>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, n_used, st)
+    MOE_NARROW(4, 2); MOE_NARROW(2, 2); MOE_NARROW(2, 1); MOE_NARROW(1, 2); MOE_NARROW(1, 1);
+#undef MOE_NARROW
+    return moe_set_error(MOE_EINTERNAL, "no narrow tiles of %d x %d", f.mt, f.nt);
+}
 template <int EPI>
 int launch_bf16_skinny(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
                        void* C, int ldc, int R, int nseg, float* partial, hipStream_t st) {
@@ -2331,6 +2579,20 @@ extern "C" int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t nseg
         for (int i = 0; i < 2; ++i) rows2[i] = kShapeRows[shape[i]];
     }
     if (!maps_fit(R, nseg, rows2[0], rows2[1])) return moe_set_error(MOE_EINTERNAL, "tile maps of %d and %d rows leave no room for the counters", rows2[0], rows2[1]);
+    return MOE_OK;
+}
+
+extern "C" int moe_selfcheck_narrow(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* forms2) {
+    if (R < 1 || n_used < 1 || nseg < n_used || nseg > kMaxSeg || H < 128 || H % 128 != 0 || F < 128 || F % 128 != 0 || act < 0 || act > 2 || ncu < 1 || !forms2)
+        return moe_set_error(MOE_EINVAL, "moe_selfcheck_narrow: bad argument");
+    int32_t rows2[2];
+    const int rc = moe_selfcheck_tile_shapes(R, n_used, nseg, H, F, act, ncu, rows2);
+    if (rc != MOE_OK) return rc;
+    int rows[2] = {rows2[0], rows2[1]};
+    NarrowForm form[2];
+    take_narrow(R, n_used, nseg, H, F, act, ncu, rows, form);
+    for (int i = 0; i < 2; ++i) forms2[i] = 10 * form[i].mt + form[i].nt;
+    if (!maps_fit(R, nseg, rows[0], rows[1])) return moe_set_error(MOE_EINTERNAL, "no room for tile maps of %d and %d rows", rows[0], rows[1]);
     return MOE_OK;
 }
 
@@ -2546,16 +2808,15 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     // gathered tiles address their rows by 32-bit byte offsets from the tile's first row
     const int gather = (size_t)R * (size_t)std::max(H, F) * elem_size(dtype) <= 0xFFFFFFFFull ? 1 : 0;
     TileShape shape[2] = {TS_256, TS_256};
-    int n_used = 1;
+    const int n_used = std::min(gather ? std::min(n_local, nseg) : nseg, R);   // runs of rows that share no tile
     bool in_halves[2] = {false, false};
     int bm[2] = {FM, FM};
     if (dtype == MOE_F32) {
-        take_f32_kernels(R, std::min(gather ? std::min(n_local, nseg) : nseg, R), nseg, H, F, act, round_size(), in_halves);
+        take_f32_kernels(R, n_used, nseg, H, F, act, round_size(), in_halves);
         for (int i = 0; i < 2; ++i) bm[i] = in_halves[i] ? XM : FM;
     } else if (skinny) {
         bm[0] = bm[1] = skinny_tile_rows(R);
     } else {
-        n_used = std::min(gather ? std::min(n_local, nseg) : nseg, R);   // runs of rows that share no tile
         take_shapes(R, n_used, nseg, H, F, act, round_size(), shape);
         if (timed_gemm != 0) {
             const int g = timed_gemm - 1, N = g == 0 ? F : H, a = g == 0 ? act : -1;
@@ -2568,6 +2829,8 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         }
         for (int i = 0; i < 2; ++i) bm[i] = kShapeRows[shape[i]];
     }
+    NarrowForm form[2] = {{0, 0}, {0, 0}};
+    if (dtype == MOE_BF16 && timed_gemm == 0) take_narrow(R, n_used, nseg, H, F, act, round_size(), bm, form);
     if ((dtype == MOE_BF16 || bm[0] != bm[1]) && !maps_fit(R, nseg, bm[0], bm[1])) return moe_set_error(MOE_EINTERNAL, "moe_expert_ffn: tile maps of %d rows in %d segments", R, nseg);
     if (ev) MOE_HIP(hipEventRecord(ev[0], st));
     MapJobs jobs;
@@ -2588,14 +2851,15 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     }
     MOE_LAUNCH_CHECK("tilemap_kernel");
     if (ev) MOE_HIP(hipEventRecord(ev[1], st));
-    int rc;
-    if (skinny) {
+    int rc = MOE_OK;
+    if (form[0].mt) {
+        if (act == MOE_ACT_SWIGLU) rc = launch_bf16_narrow<EPI_SWIGLU>(form[0], recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, st);
+        else if (act == MOE_ACT_GELU_MLP) rc = launch_bf16_narrow<EPI_GELU>(form[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, st);
+        else rc = launch_bf16_narrow<EPI_SILU>(form[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, st);
+    } else if (skinny) {
         if (act == MOE_ACT_SWIGLU) rc = launch_bf16_skinny<EPI_SWIGLU>(recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, partial, st);
         else if (act == MOE_ACT_GELU_MLP) rc = launch_bf16_skinny<EPI_GELU>(recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, partial, st);
         else rc = launch_bf16_skinny<EPI_SILU>(recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, partial, st);
-        if (rc != MOE_OK) return rc;
-        if (ev) MOE_HIP(hipEventRecord(ev[2], st));
-        rc = launch_bf16_skinny<EPI_PLAIN>(hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, partial, st);
     } else if (dtype == MOE_BF16) {
         if (act == MOE_ACT_SWIGLU)
             rc = launch_bf16_shape<EPI_SWIGLU>(shape[0], recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
@@ -2603,17 +2867,17 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
             rc = launch_bf16_shape<EPI_GELU>(shape[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
         else
             rc = launch_bf16_shape<EPI_SILU>(shape[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
-        if (rc != MOE_OK) return rc;
-        if (ev) MOE_HIP(hipEventRecord(ev[2], st));
-        rc = launch_bf16_shape<EPI_PLAIN>(shape[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, partial, st, timed_gemm == 2, marks, marks_len);
     } else {
         if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(in_halves[0], recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, st);
         else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(in_halves[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, st);
         else rc = launch_f32<EPI_SILU>(in_halves[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, st);
-        if (rc != MOE_OK) return rc;
-        if (ev) MOE_HIP(hipEventRecord(ev[2], st));
-        rc = launch_f32<EPI_PLAIN>(in_halves[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, st);
     }
+    if (rc != MOE_OK) return rc;
+    if (ev) MOE_HIP(hipEventRecord(ev[2], st));
+    if (form[1].mt) rc = launch_bf16_narrow<EPI_PLAIN>(form[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, st);
+    else if (skinny) rc = launch_bf16_skinny<EPI_PLAIN>(hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, partial, st);
+    else if (dtype == MOE_BF16) rc = launch_bf16_shape<EPI_PLAIN>(shape[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, partial, st, timed_gemm == 2, marks, marks_len);
+    else rc = launch_f32<EPI_PLAIN>(in_halves[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, st);
     if (rc != MOE_OK) return rc;
     if (ev) MOE_HIP(hipEventRecord(ev[3], st));
     return MOE_OK;

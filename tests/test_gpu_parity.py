@@ -636,6 +636,27 @@ def test_expert_ffn_fp32_tiles(H, act, R, Hd, F, n_local, nseg):
     H.assert_close(H.host(out), O.expert_ffn(recv, off, exp, experts, act), "fp32")
 
 
+# Narrow tiles: every form in both GEMMs and every activation, one k-tile less than the ring and many more, tiles of one row,
+# gathered tiles, beside the weight-streaming kernels, and a map of more than 64 segments
+@pytest.mark.parametrize("R,Hd,F,n_local,nseg,act,forms", [
+    (45, 128, 512, 1, 4, 1, [0, 11]), (45, 512, 128, 1, 1, 2, [11, 0]), (120, 128, 128, 1, 4, 2, [11, 11]), (233, 1408, 128, 3, 3, 1, [11, 12]),
+    (278, 1280, 640, 4, 13, 2, [12, 12]), (485, 512, 256, 5, 16, 2, [21, 21]), (456, 1024, 256, 5, 5, 2, [21, 22]), (482, 512, 1024, 4, 65, 2, [42, 21]),
+    (360, 1408, 640, 3, 65, 2, [22, 22]), (403, 2048, 1408, 4, 64, 2, [42, 22]), (65, 2048, 2816, 1, 2, 0, None), (1, 1152, 256, 1, 1, 2, [11, 0])])
+def test_expert_ffn_narrow_tiles(H, R, Hd, F, n_local, nseg, act, forms):
+    import ctypes as C
+    from paper_2410_17043_amd import _lib
+    got = (C.c_int32 * 2)()
+    assert _lib.load().moe_selfcheck_narrow(R, min(n_local, nseg, R), nseg, Hd, F, act, 256, got) == 0
+    assert forms is None or list(got) == forms
+    cfg = small("c2_mixtral", H=Hd, F=F, act=act)
+    r = np.random.default_rng(R + nseg)
+    recv = W.to_bf16_grid(r.standard_normal((R, Hd)).astype(np.float32))
+    experts = [W.make_expert_weights(cfg, e) for e in range(n_local)]
+    off, exp = make_segments(r, R, nseg, n_local)
+    out = H.host(H.run_ffn(H.dev(recv, "bf16"), off, exp, [H.weights_to_dev(w, "bf16") for w in experts], Hd, F, act, "bf16"))
+    H.assert_close(out[off[0]:off[-1]], O.expert_ffn(recv, off, exp, experts, act)[off[0]:off[-1]], "bf16")
+
+
 # fp32 GEMMs on pairs of halves (128-row tiles): a K that ends inside a k-tile and an odd number of them, gathered and
 # ragged tiles, N of no whole tile, several tiles per block, one kernel of each kind with a map of its own
 @pytest.mark.parametrize("act,R,Hd,F,n_local,nseg,rows", [(1, 1300, 1156, 1164, 2, 9, [128, 128]), (2, 4000, 132, 1012, 3, 40, [128, 64]),
