@@ -305,14 +305,16 @@ struct WaveLanes {
     __device__ __forceinline__ int at(int SmallItem::*v, int k) const { return __builtin_amdgcn_readlane(mine.*v, k); }
     __device__ __forceinline__ void move_to_rank(int SmallItem::*v) { mine.*v = __builtin_amdgcn_ds_permute(mine.rank * 4, mine.*v); }
     __device__ __forceinline__ int from(int SmallItem::*v, int l, const SmallItem&) const { return __shfl(mine.*v, l, 64); }
-    __device__ __forceinline__ void from_below(int SmallItem::*v, int SmallItem::*to) { mine.*to = __shfl_up(mine.*v, 1, 64); }
+    // by data-parallel moves: a few clocks each, where a shuffle takes the way through the LDS crossbar
+    __device__ __forceinline__ void from_below(int SmallItem::*v, int SmallItem::*to) { mine.*to = __builtin_amdgcn_update_dpp(mine.*v, mine.*v, 0x138, 0xf, 0xf, false); }   // wave_shr:1
     __device__ __forceinline__ void prefix(int SmallItem::*v, int SmallItem::*to) {   // inclusive
         int x = mine.*v;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int up = __shfl_up(x, o, 64);
-            if (lane >= o) x += up;
-        }
+        x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8: inside rows of 16 lanes
+        x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+        x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+        x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+        x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15: the row below into rows 1 and 3
+        x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31: the lower half into rows 2 and 3
         mine.*to = x;
     }
 };
@@ -452,6 +454,36 @@ __global__ __launch_bounds__(256) void tilemap_small_kernel(const int32_t* __res
             for (int v = run.lo + w.lane; v < run.hi; v += 64) m.rel[(size_t)t * kRelPitch + v] = run.val + v;
         }
     }
+}
+
+// The segment list itself, for shares that take gemm_f32_kernel twice: its blocks take one tile each and every wave works it
+// out from the list, instead of a map by a launch of its own.  A small fp32 share (256 tokens, 517 rows of 64 -> 128 -> 64) is
+// bound by its launches: 32.1 -> 27.9 us with six instead of seven.  In the narrow tiles of decode steps the same gained
+// nothing: the list is cold in every kernel, and what the map's launches cost (2 x 4.7 us) the four GEMMs took longer.  Up to 64
+// segments.
+struct SegList { const int32_t *offset, *expert; int nseg, R, n_local, gather, max_tiles; };
+__device__ __forceinline__ SmallMap load_segments(const SegList& g, int bm, WaveLanes& w) {
+    w.lane = threadIdx.x & 63;
+    const int i = min(w.lane, g.nseg - 1);
+    w.mine.off0 = g.offset[i];
+    w.mine.off1 = g.offset[i + 1];
+    w.mine.e = g.expert[i];
+    return small_map(w, g.nseg, g.R, g.n_local, g.gather, bm, g.max_tiles);
+}
+// rows of a tile (in it: 0 .. nrows - 1) -> offsets from its first row
+template <int N> __device__ __forceinline__ void segment_rows(const WaveLanes& w, const SmallTile& r, int (&row)[N]) {
+    if (!r.gather) return;
+    int off[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) off[i] = 0;
+    for (unsigned long long in = r.in; in; in &= in - 1) {
+        const SmallRun run = small_run(w, r, __builtin_ctzll(in));
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if (row[i] >= run.lo && row[i] < run.hi) off[i] = run.val + row[i];
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) row[i] = off[i];
 }
 
 __global__ __launch_bounds__(kMapThreads) void tilemap_kernel(const int32_t* __restrict__ seg_offset,
@@ -713,129 +745,147 @@ constexpr int kF32TileBytes = FM * FK * 4;     // one operand tile: 8 KB
 constexpr int kF32Stages = 3;
 __device__ __forceinline__ int f32_slot(int r, int c) { return (r << 3) + (c ^ ((r >> 1) & 7)); }
 
-template <int EPI>
-__global__ __launch_bounds__(256, 3) void gemm_f32_kernel(const float* __restrict__ A, int lda, TileMap m,
+template <int EPI, bool SEG>
+__global__ __launch_bounds__(256, 3) void gemm_f32_kernel(const float* __restrict__ A, int lda, TileMap m, SegList seg,
                                                           ExpertTable tab, int which0, int which1, int N, int K,
                                                           float* __restrict__ C, int ldc, int tiles_n) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[kF32Stages * 2 * kF32TileBytes];
     constexpr int NOUT = (EPI == EPI_SWIGLU) ? FN / 2 : FN;                 // output columns per block
-    const int n_tiles_m = *m.n_tiles;
+    WaveLanes lanes;
+    SmallMap map;
+    if constexpr (SEG) map = load_segments(seg, FM, lanes);
+    const int n_tiles_m = SEG ? __builtin_amdgcn_readfirstlane(map.n_tiles) : *m.n_tiles;
     const int total = n_tiles_m * tiles_n;
-    if ((int)blockIdx.x >= total) return;
-    int tile_m, tile_n;
-    tile_of_block(blockIdx.x, total, n_tiles_m, tiles_n, &tile_m, &tile_n);
-    const int row0 = m.row0[tile_m], nrows = m.nrows[tile_m], ex = m.expert[tile_m];
-    const int32_t* rel = m.gather[tile_m] ? m.rel + (size_t)tile_m * kRelPitch : nullptr;
-    auto pick = [&](int which) -> const float* {
-        return reinterpret_cast<const float*>(which == 0 ? tab.w1[ex] : which == 1 ? tab.w_up[ex] : tab.w_down[ex]);
-    };
-    const float* B0 = pick(which0);
-    const float* B1 = (EPI == EPI_SWIGLU) ? pick(which1) : B0;
-    const int n0 = tile_n * NOUT;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave >> 1, wn = wave & 1;
-
-    // wave-load i (of 2 per operand) fills rows 8 (wave + 4 i) .. + 7: this lane fetches one chunk of one row.  Addresses
-    // are a scalar base plus a 32-bit offset per lane.  Chunks past K are fetched clamped to the row's last one and
-    // zeroed when they are read.
-    const int nchunk = K / 4, nk = (K + FK - 1) / FK;   // K is a multiple of 4
-    // byte offset of the lane's chunk inside a k-tile's 128 bytes: row r = 8 (wave + 4 i) + lane / 8, so (r >> 1) & 7 does not depend on i
-    const uint32_t chunk = (uint32_t)(((lane & 7) ^ (((wave & 1) << 2) + (lane >> 4))) * 16);
-    const uint32_t chunk_last = min(chunk, (uint32_t)((nchunk - 1) * 16 - (nk - 1) * (FK * 4)));
-    const char* a_base = reinterpret_cast<const char*>(A + (size_t)row0 * lda);
-    const char* b_base[2];
-    uint32_t a_voff[2], b_voff[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int r0 = (wave + 4 * i) * 8;         // wave-uniform
-        int ar = min(r0 + (lane >> 3), nrows - 1);
-        if (rel) ar = rel[ar];                     // gathered tile: offsets below 2^32 bytes (checked on the host)
-        a_voff[i] = (uint32_t)ar * (uint32_t)lda * 4u;
-        const int col0 = (EPI == EPI_SWIGLU) ? (r0 >> 5) * 16 + (r0 & 15) : r0;
-        b_base[i] = reinterpret_cast<const char*>(((EPI == EPI_SWIGLU && (r0 & 16)) ? B1 : B0) + (size_t)n0 * K);
-        b_voff[i] = (uint32_t)min(col0 + (lane >> 3), N - 1 - n0) * (uint32_t)K * 4u;
-        asm volatile("" : "+v"(a_voff[i]), "+v"(b_voff[i]));   // stay 32-bit lane offsets next to a scalar base
-    }
-    // loads [lo, hi) of the four of k-tile kt; past the end the last k-tile is fetched again: their count stays uniform
-    auto issue = [&](int kt, int stage, int lo, int hi) {
-        kt = min(kt, nk - 1);
-        const uint32_t ch = kt == nk - 1 ? chunk_last : chunk;
-        unsigned char* st = lds + stage * 2 * kF32TileBytes + wave * 1024;
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            if (it < lo || it >= hi) continue;
-            const bool is_a = it < 2;
-            const int i = it & 1;
-            const char* p = (is_a ? a_base : b_base[i]) + (size_t)kt * (FK * 4);
-            uint32_t v = (is_a ? a_voff[i] : b_voff[i]) + ch;
-            asm volatile("" : "+s"(p), "+v"(v));
-            __builtin_amdgcn_global_load_lds(p + v, (__attribute__((address_space(3))) void*)(st + (is_a ? 0 : kF32TileBytes) + i * 4096), 16, 0, 0);
+    for (int id = blockIdx.x; id < total; id += gridDim.x) {   // one, unless the list has more runs than experts
+        int tile_m, tile_n;
+        tile_of_block(id, total, n_tiles_m, tiles_n, &tile_m, &tile_n);
+        SmallTile t{};
+        const int32_t* rel = nullptr;
+        if constexpr (SEG) {
+            tile_m = __builtin_amdgcn_readfirstlane(tile_m);
+            t = small_tile(lanes, map, tile_m, FM);
+        } else {
+            t.row0 = m.row0[tile_m]; t.nrows = m.nrows[tile_m]; t.expert = m.expert[tile_m];
+            rel = m.gather[tile_m] ? m.rel + (size_t)tile_m * kRelPitch : nullptr;
         }
-    };
-    issue(0, 0, 0, 4);
-    issue(1, 1, 0, 3);                             // the fourth goes out in the first k-step below
-    const int fr = lane & 31, fk = lane >> 5;
-    int a_off[4], b_off[4];
+        const int row0 = t.row0, nrows = t.nrows, ex = t.expert;
+        auto pick = [&](int which) -> const float* {
+            return reinterpret_cast<const float*>(which == 0 ? tab.w1[ex] : which == 1 ? tab.w_up[ex] : tab.w_down[ex]);
+        };
+        const float* B0 = pick(which0);
+        const float* B1 = (EPI == EPI_SWIGLU) ? pick(which1) : B0;
+        const int n0 = tile_n * NOUT;
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int wm = wave >> 1, wn = wave & 1;
+
+        // wave-load i (of 2 per operand) fills rows 8 (wave + 4 i) .. + 7: this lane fetches one chunk of one row.  Addresses
+        // are a scalar base plus a 32-bit offset per lane.  Chunks past K are fetched clamped to the row's last one and
+        // zeroed when they are read.
+        const int nchunk = K / 4, nk = (K + FK - 1) / FK;   // K is a multiple of 4
+        // byte offset of the lane's chunk inside a k-tile's 128 bytes: row r = 8 (wave + 4 i) + lane / 8, so (r >> 1) & 7 does not depend on i
+        const uint32_t chunk = (uint32_t)(((lane & 7) ^ (((wave & 1) << 2) + (lane >> 4))) * 16);
+        const uint32_t chunk_last = min(chunk, (uint32_t)((nchunk - 1) * 16 - (nk - 1) * (FK * 4)));
+        const char* a_base = reinterpret_cast<const char*>(A + (size_t)row0 * lda);
+        const char* b_base[2];
+        uint32_t a_voff[2], b_voff[2];
+        // rows that this lane fetches, and the one whose products it ends up with
+        int rows[3] = {min(wave * 8 + (lane >> 3), nrows - 1), min((wave + 4) * 8 + (lane >> 3), nrows - 1), min(wm * 32 + (lane & 31), nrows - 1)};
+        if constexpr (SEG) segment_rows(lanes, t, rows);
+        else if (rel) {                                // gathered tile: offsets below 2^32 bytes (checked on the host)
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        a_off[s] = f32_slot(wm * 32 + fr, 2 * s + fk) * 16;
-        b_off[s] = kF32TileBytes + f32_slot(wn * 32 + fr, 2 * s + fk) * 16;
-    }
-    f32x16 acc;
+            for (int i = 0; i < 3; ++i) rows[i] = rel[rows[i]];
+        }
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-    f32x4 af[2], bf[2];
-    auto read = [&](const unsigned char* st, int s) {
-        af[s & 1] = *reinterpret_cast<const f32x4*>(st + a_off[s]);
-        bf[s & 1] = *reinterpret_cast<const f32x4*>(st + b_off[s]);
-    };
-    // the MFMAs of k-step s of k-tile kt; behind the first the fragments of the next k-step are read, behind the second
-    // load `it` of k-tile t_load goes out
-    auto step = [&](const unsigned char* st_next, int kt, int s, bool ragged, int t_load, int slot, int it) {
-        __builtin_amdgcn_sched_barrier(0);
-        if (ragged && kt * (FK / 4) + 2 * s + fk >= nchunk)   // zero in both: 0 * a stray infinity would be a NaN
-            af[s & 1] = bf[s & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
-        read(st_next, (s + 1) & 3);
-        issue(t_load, slot, it, it + 1);
+        for (int i = 0; i < 2; ++i) {
+            const int r0 = (wave + 4 * i) * 8;         // wave-uniform
+            a_voff[i] = (uint32_t)rows[i] * (uint32_t)lda * 4u;
+            const int col0 = (EPI == EPI_SWIGLU) ? (r0 >> 5) * 16 + (r0 & 15) : r0;
+            b_base[i] = reinterpret_cast<const char*>(((EPI == EPI_SWIGLU && (r0 & 16)) ? B1 : B0) + (size_t)n0 * K);
+            b_voff[i] = (uint32_t)min(col0 + (lane >> 3), N - 1 - n0) * (uint32_t)K * 4u;
+            asm volatile("" : "+v"(a_voff[i]), "+v"(b_voff[i]));   // stay 32-bit lane offsets next to a scalar base
+        }
+        // loads [lo, hi) of the four of k-tile kt; past the end the last k-tile is fetched again: their count stays uniform
+        auto issue = [&](int kt, int stage, int lo, int hi) {
+            kt = min(kt, nk - 1);
+            const uint32_t ch = kt == nk - 1 ? chunk_last : chunk;
+            unsigned char* st = lds + stage * 2 * kF32TileBytes + wave * 1024;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf[s & 1][v], af[s & 1][v], acc, 0, 0, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    int cur = 0;                                   // ring slot of k-tile kt
-    auto trip = [&](int kt, bool ragged) {
-        const int nxt = cur == kF32Stages - 1 ? 0 : cur + 1, prev = cur == 0 ? kF32Stages - 1 : cur - 1;
-        const unsigned char* st = lds + cur * 2 * kF32TileBytes;
-        // slot `prev` was last read in trip kt - 1, whose barrier every wave has passed: k-tile kt + 2 goes there
-        step(st, kt, 0, ragged, kt + 1, nxt, 3);
-        step(st, kt, 1, ragged, kt + 2, prev, 0);
-        step(st, kt, 2, ragged, kt + 2, prev, 1);
-        __builtin_amdgcn_s_waitcnt(0x0070 | 2);    // vmcnt(2) lgkmcnt(0): k-tile kt + 1 is in LDS, this wave has read all of kt
+            for (int it = 0; it < 4; ++it) {
+                if (it < lo || it >= hi) continue;
+                const bool is_a = it < 2;
+                const int i = it & 1;
+                const char* p = (is_a ? a_base : b_base[i]) + (size_t)kt * (FK * 4);
+                uint32_t v = (is_a ? a_voff[i] : b_voff[i]) + ch;
+                asm volatile("" : "+s"(p), "+v"(v));
+                __builtin_amdgcn_global_load_lds(p + v, (__attribute__((address_space(3))) void*)(st + (is_a ? 0 : kF32TileBytes) + i * 4096), 16, 0, 0);
+            }
+        };
+        issue(0, 0, 0, 4);
+        issue(1, 1, 0, 3);                             // the fourth goes out in the first k-step below
+        const int fr = lane & 31, fk = lane >> 5;
+        int a_off[4], b_off[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            a_off[s] = f32_slot(wm * 32 + fr, 2 * s + fk) * 16;
+            b_off[s] = kF32TileBytes + f32_slot(wn * 32 + fr, 2 * s + fk) * 16;
+        }
+        f32x16 acc;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+        f32x4 af[2], bf[2];
+        auto read = [&](const unsigned char* st, int s) {
+            af[s & 1] = *reinterpret_cast<const f32x4*>(st + a_off[s]);
+            bf[s & 1] = *reinterpret_cast<const f32x4*>(st + b_off[s]);
+        };
+        // the MFMAs of k-step s of k-tile kt; behind the first the fragments of the next k-step are read, behind the second
+        // load `it` of k-tile t_load goes out
+        auto step = [&](const unsigned char* st_next, int kt, int s, bool ragged, int t_load, int slot, int it) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (ragged && kt * (FK / 4) + 2 * s + fk >= nchunk)   // zero in both: 0 * a stray infinity would be a NaN
+                af[s & 1] = bf[s & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            read(st_next, (s + 1) & 3);
+            issue(t_load, slot, it, it + 1);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(bf[s & 1][v], af[s & 1][v], acc, 0, 0, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        int cur = 0;                                   // ring slot of k-tile kt
+        auto trip = [&](int kt, bool ragged) {
+            const int nxt = cur == kF32Stages - 1 ? 0 : cur + 1, prev = cur == 0 ? kF32Stages - 1 : cur - 1;
+            const unsigned char* st = lds + cur * 2 * kF32TileBytes;
+            // slot `prev` was last read in trip kt - 1, whose barrier every wave has passed: k-tile kt + 2 goes there
+            step(st, kt, 0, ragged, kt + 1, nxt, 3);
+            step(st, kt, 1, ragged, kt + 2, prev, 0);
+            step(st, kt, 2, ragged, kt + 2, prev, 1);
+            __builtin_amdgcn_s_waitcnt(0x0070 | 2);    // vmcnt(2) lgkmcnt(0): k-tile kt + 1 is in LDS, this wave has read all of kt
+            __builtin_amdgcn_s_barrier();
+            step(lds + nxt * 2 * kF32TileBytes, kt, 3, ragged, kt + 2, prev, 2);
+            cur = nxt;
+        };
+        __builtin_amdgcn_s_waitcnt(0x0F70 | 3);        // vmcnt(3): k-tile 0 is in LDS
         __builtin_amdgcn_s_barrier();
-        step(lds + nxt * 2 * kF32TileBytes, kt, 3, ragged, kt + 2, prev, 2);
-        cur = nxt;
-    };
-    __builtin_amdgcn_s_waitcnt(0x0F70 | 3);        // vmcnt(3): k-tile 0 is in LDS
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    read(lds, 0);
-    for (int kt = 0; kt < K / FK; ++kt) trip(kt, false);
-    if (K % FK != 0) trip(nk - 1, true);
-    __builtin_amdgcn_s_waitcnt(0x0070);            // no load may still target LDS when the block ends
-    const int gr = wm * 32 + fr;
-    if (gr >= nrows) return;
-    float* crow = C + (size_t)(row0 + (rel ? rel[gr] : gr)) * ldc;
+        asm volatile("" ::: "memory");
+        read(lds, 0);
+        for (int kt = 0; kt < K / FK; ++kt) trip(kt, false);
+        if (K % FK != 0) trip(nk - 1, true);
+        __builtin_amdgcn_s_waitcnt(0x0070);            // no load may still target LDS when the block ends
+        if (wm * 32 + fr < nrows) {
+            float* crow = C + (size_t)(row0 + rows[2]) * ldc;
 #pragma unroll
-    for (int g = 0; g < ((EPI == EPI_SWIGLU) ? 2 : 4); ++g) {
-        f32x4 v;
+            for (int g = 0; g < ((EPI == EPI_SWIGLU) ? 2 : 4); ++g) {
+                f32x4 v;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = epilogue<EPI>(acc[4 * g + t], (EPI == EPI_SWIGLU) ? acc[4 * (g & 1) + 8 + t] : 0.f);
-        const int col = n0 + wn * (NOUT / 2) + g * 8 + fk * 4;
-        if (col < N) *reinterpret_cast<f32x4*>(crow + col) = v;            // N is a multiple of 4
+                for (int t = 0; t < 4; ++t) v[t] = epilogue<EPI>(acc[4 * g + t], (EPI == EPI_SWIGLU) ? acc[4 * (g & 1) + 8 + t] : 0.f);
+                const int col = n0 + wn * (NOUT / 2) + g * 8 + fk * 4;
+                if (col < N) *reinterpret_cast<f32x4*>(crow + col) = v;            // N is a multiple of 4
+            }
+        }
+        __builtin_amdgcn_s_barrier();              // the next item's loads go to the same LDS
     }
 }
 
@@ -2520,15 +2570,18 @@ int launch_f32_halves(const void* A, int lda, const TileMap& m, const ExpertTabl
 }
 
 template <int EPI>
-int launch_f32(bool in_halves, const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
-               void* C, int ldc, int R, int nseg, hipStream_t st) {
+int launch_f32(bool in_halves, bool need_map, const void* A, int lda, const TileMap& m, SegList seg, const ExpertTable& tab, int which0, int which1,
+               int N, int K, void* C, int ldc, int R, int nseg, int n_used, hipStream_t st) {
     if (in_halves) return launch_f32_halves<EPI>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, st);
     const int nout = (EPI == EPI_SWIGLU) ? FN / 2 : FN;
     const int tiles_n = (N + nout - 1) / nout;
-    const int max_tiles_m = max_tiles_of(R, FM, nseg);
-    hipLaunchKernelGGL((gemm_f32_kernel<EPI>), dim3(max_tiles_m * tiles_n), dim3(256), 0, st,
-                       reinterpret_cast<const float*>(A), lda, m, tab, which0, which1, N, K,
-                       reinterpret_cast<float*>(C), ldc, tiles_n);
+    seg.max_tiles = max_tiles_of(R, FM, nseg);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(std::min(seg.max_tiles, (R + n_used * (FM - 1)) / FM) * tiles_n), dim3(256), 0, st,
+                           reinterpret_cast<const float*>(A), lda, m, seg, tab, which0, which1, N, K, reinterpret_cast<float*>(C), ldc, tiles_n);
+    };
+    if (need_map) launch(gemm_f32_kernel<EPI, false>);
+    else launch(gemm_f32_kernel<EPI, true>);
     MOE_LAUNCH_CHECK("gemm_f32_kernel");
     return MOE_OK;
 }
@@ -2843,13 +2896,16 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     }
     const TileMap &m = jobs.job[0].m, &m2 = jobs.job[1].m;
     const int n_maps = bm[1] == bm[0] ? 1 : 2;
-    if (nseg <= kSmallMapSegs) {                           // about a tile per wave
+    const bool need_map = dtype == MOE_BF16 || nseg > kSmallMapSegs || in_halves[0] || in_halves[1];   // else see SegList
+    const SegList seg = {seg_offset, seg_expert, nseg, R, n_local, gather, 0};
+    if (!need_map) {
+    } else if (nseg <= kSmallMapSegs) {                           // about a tile per wave
         const int blocks = std::min(64, (R / std::min(bm[0], bm[1]) + std::min(nseg, n_local) + 3) / 4);
         hipLaunchKernelGGL(tilemap_small_kernel, dim3(blocks, n_maps), dim3(256), 0, st, seg_offset, seg_expert, nseg, R, n_local, gather, jobs);
     } else {
         hipLaunchKernelGGL(tilemap_kernel, dim3(n_maps), dim3(kMapThreads), 0, st, seg_offset, seg_expert, nseg, R, n_local, gather, jobs);
     }
-    MOE_LAUNCH_CHECK("tilemap_kernel");
+    if (need_map) MOE_LAUNCH_CHECK("tilemap_kernel");
     if (ev) MOE_HIP(hipEventRecord(ev[1], st));
     int rc = MOE_OK;
     if (form[0].mt) {
@@ -2868,16 +2924,16 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         else
             rc = launch_bf16_shape<EPI_SILU>(shape[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
     } else {
-        if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(in_halves[0], recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, st);
-        else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(in_halves[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, st);
-        else rc = launch_f32<EPI_SILU>(in_halves[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, st);
+        if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(in_halves[0], need_map, recv, H, m, seg, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, st);
+        else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(in_halves[0], need_map, recv, H, m, seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, st);
+        else rc = launch_f32<EPI_SILU>(in_halves[0], need_map, recv, H, m, seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, st);
     }
     if (rc != MOE_OK) return rc;
     if (ev) MOE_HIP(hipEventRecord(ev[2], st));
     if (form[1].mt) rc = launch_bf16_narrow<EPI_PLAIN>(form[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, st);
     else if (skinny) rc = launch_bf16_skinny<EPI_PLAIN>(hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, partial, st);
     else if (dtype == MOE_BF16) rc = launch_bf16_shape<EPI_PLAIN>(shape[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, partial, st, timed_gemm == 2, marks, marks_len);
-    else rc = launch_f32<EPI_PLAIN>(in_halves[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, st);
+    else rc = launch_f32<EPI_PLAIN>(in_halves[1], need_map, hmid, F, m2, seg, tab, 2, 2, H, F, out, H, R, nseg, n_used, st);
     if (rc != MOE_OK) return rc;
     if (ev) MOE_HIP(hipEventRecord(ev[3], st));
     return MOE_OK;

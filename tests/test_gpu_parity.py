@@ -636,6 +636,29 @@ def test_expert_ffn_fp32_tiles(H, act, R, Hd, F, n_local, nseg):
     H.assert_close(H.host(out), O.expert_ffn(recv, off, exp, experts, act), "fp32")
 
 
+@pytest.mark.parametrize("nseg", [1, 63, 64, 65])
+def test_expert_ffn_fp32_tiles_from_the_segment_list(H, nseg):
+    """Gathered tiles, empty segments, segments of no local expert and rows outside all segments, on both sides of the
+    segment count up to which the blocks work out their tiles themselves."""
+    R, Hd, F, n_local = 300, 64, 96, 3
+    cfg = small("c1_tiny_fp32", H=Hd, F=F, act=2)
+    r = np.random.default_rng(nseg)
+    recv = r.standard_normal((R, Hd)).astype(np.float32)
+    experts = [W.make_expert_weights(cfg, e) for e in range(n_local)]
+    off = np.sort(r.integers(3, R - 4, size=nseg + 1))
+    exp = r.integers(-1, n_local + 1, size=nseg) if nseg > 1 else np.array([2])
+    assert f32_rows(R, min(n_local, nseg), nseg, Hd, F, 2) == [64, 64]
+    out = H.host(H.run_ffn(H.dev(recv, "fp32"), off, exp, [H.weights_to_dev(w, "fp32") for w in experts], Hd, F, 2, "fp32"))
+    done, ref = np.zeros(R, dtype=bool), np.zeros((R, Hd))
+    for i in range(nseg):
+        if 0 <= exp[i] < n_local and off[i + 1] > off[i]:
+            w = experts[exp[i]]
+            done[off[i]:off[i + 1]] = True
+            ref[off[i]:off[i + 1]] = O.ffn(recv[off[i]:off[i + 1]], w["w1"], w["w_up"], w["w_down"], 2)
+    assert np.isnan(out[~done]).all()
+    H.assert_close(out[done], ref[done], "fp32")
+
+
 # Narrow tiles: every form in both GEMMs and every activation, one k-tile less than the ring and many more, tiles of one row,
 # gathered tiles, beside the weight-streaming kernels, and a map of more than 64 segments
 @pytest.mark.parametrize("R,Hd,F,n_local,nseg,act,forms", [
