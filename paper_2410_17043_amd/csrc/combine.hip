@@ -95,15 +95,18 @@ __global__ __launch_bounds__(256) void combine_kernel(const u32x4* __restrict__ 
     }
 }
 
-// Any k: one token and 1 KB of its rows per wave, four source rows in flight at a time.  The loads are issued
-// unconditionally (a slot past k or a dropped one reads a valid row whose value is not used): with the loads of
+// One token and 1 KB of its rows per wave, all source rows of K slots in flight at a time (K = 0: any k, four at a time).  For any
+// k, and for the k of the kernel above where its one wave per token leaves the chip to a few waves that walk through their
+// rows (see kFewTokens).  The loads
+// are issued unconditionally (a slot past k or a dropped one reads a valid row whose value is not used): with the loads of
 // a 16-slot array under conditions the compiler kept the whole array in registers (217 of them) and waited
 // for each load in turn.
-template <int DT, bool STREAM>
-__global__ __launch_bounds__(256) void combine_any_k_kernel(const u32x4* __restrict__ ret, const int32_t* __restrict__ slot_to_row,
-                                                            const float* __restrict__ topk_w, const u32x4* __restrict__ shared_out,
-                                                            int T, int k, int row16, u32x4* __restrict__ y) {
-    constexpr int V = Pack<DT>::V;
+template <int DT, int K, bool STREAM>
+__global__ __launch_bounds__(256) void combine_pieces_kernel(const u32x4* __restrict__ ret, const int32_t* __restrict__ slot_to_row,
+                                                             const float* __restrict__ topk_w, const u32x4* __restrict__ shared_out,
+                                                             int T, int any_k, int row16, u32x4* __restrict__ y) {
+    constexpr int V = Pack<DT>::V, J = K > 0 ? K : 4;
+    const int k = K > 0 ? K : any_k;
     const int lane = threadIdx.x & 63;
     const int t = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
     if (t >= T) return;
@@ -112,20 +115,25 @@ __global__ __launch_bounds__(256) void combine_any_k_kernel(const u32x4* __restr
     float acc[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) acc[v] = 0.f;
-    for (int j0 = 0; j0 < k; j0 += 4) {
-        int rows[4];
-        float w[4];
-        u32x4 d[4];
+    u32x4 sh = {0, 0, 0, 0};
+    if (shared_out) sh = shared_out[(size_t)t * row16 + c];
+    for (int j0 = 0; j0 < k; j0 += J) {
+        int rows[J];
+        float w[J];
+        u32x4 d[J];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < J; ++i) {
             const int j = min(j0 + i, k - 1);
             rows[i] = (j0 + i < k) ? slot_to_row[(size_t)t * k + j] : -1;
             w[i] = topk_w[(size_t)t * k + j];
+        }
+#pragma unroll
+        for (int i = 0; i < J; ++i) {
             const u32x4* p = ret + (size_t)max(rows[i], 0) * row16 + c;
             d[i] = STREAM ? __builtin_nontemporal_load(p) : *p;
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < J; ++i) {
             if (rows[i] >= 0) {
                 float f[V];
                 Pack<DT>::unpack(d[i], f);
@@ -136,7 +144,7 @@ __global__ __launch_bounds__(256) void combine_any_k_kernel(const u32x4* __restr
     }
     if (shared_out) {
         float f[V];
-        Pack<DT>::unpack(shared_out[(size_t)t * row16 + c], f);
+        Pack<DT>::unpack(sh, f);
 #pragma unroll
         for (int v = 0; v < V; ++v) acc[v] += f[v];
     }
@@ -148,6 +156,13 @@ __global__ __launch_bounds__(256) void combine_any_k_kernel(const u32x4* __restr
 // cache plain loads only evict each other (103 against 86 us at 403 MB) and streaming loads are used.
 constexpr size_t kCombineCacheableBytes = (size_t)128 << 20;
 
+// A wave per token and piece of its rows up to this many tokens, or bytes read and written: the walk of one wave through its
+// rows is then what takes the time (us, bf16, H = 4096: 16 tokens, k = 2 4.9 -> 2.2; 64, k = 6 7.7 -> 2.5; 1024, k = 2 7.6 ->
+// 5.2; H = 1024, k = 1, 4096 tokens 4.1 -> 3.8).  Beyond, the memory system prefers waves that keep reading and writing (8192
+// tokens, k = 2, H = 4096: 39 against 44).
+constexpr int kFewTokens = 1024;
+constexpr size_t kFewBytes = (size_t)16 << 20;
+
 template <int DT, bool STREAM>
 int launch_combine(const moe_ctx* c, const void* ret, const int32_t* s2r, const float* w, const void* shared, void* y,
                    hipStream_t st) {
@@ -157,13 +172,16 @@ int launch_combine(const moe_ctx* c, const void* ret, const int32_t* s2r, const 
     const u32x4* r = reinterpret_cast<const u32x4*>(ret);
     const u32x4* sh = reinterpret_cast<const u32x4*>(shared);
     u32x4* yo = reinterpret_cast<u32x4*>(y);
-    if (s.k == 1) hipLaunchKernelGGL((combine_kernel<DT, 1, STREAM>), grid, dim3(256), 0, st, r, s2r, w, sh, s.T, row16, yo);
-    else if (s.k == 2) hipLaunchKernelGGL((combine_kernel<DT, 2, STREAM>), grid, dim3(256), 0, st, r, s2r, w, sh, s.T, row16, yo);
-    else if (s.k == 6) hipLaunchKernelGGL((combine_kernel<DT, 6, STREAM>), grid, dim3(256), 0, st, r, s2r, w, sh, s.T, row16, yo);
-    else {
-        const dim3 grid_any((s.T + 3) / 4, (row16 + 63) / 64);
-        hipLaunchKernelGGL((combine_any_k_kernel<DT, STREAM>), grid_any, dim3(256), 0, st, r, s2r, w, sh, s.T, s.k, row16, yo);
-    }
+    const dim3 pieces((s.T + 3) / 4, (row16 + 63) / 64);
+    const bool few = s.T <= kFewTokens || (size_t)s.T * (s.k + 1) * row16 * 16 <= kFewBytes;
+#define MOE_COMBINE(K)                                                                                                              \
+    if (few) hipLaunchKernelGGL((combine_pieces_kernel<DT, K, STREAM>), pieces, dim3(256), 0, st, r, s2r, w, sh, s.T, s.k, row16, yo); \
+    else hipLaunchKernelGGL((combine_kernel<DT, K, STREAM>), grid, dim3(256), 0, st, r, s2r, w, sh, s.T, row16, yo)
+    if (s.k == 1) { MOE_COMBINE(1); }
+    else if (s.k == 2) { MOE_COMBINE(2); }
+    else if (s.k == 6) { MOE_COMBINE(6); }
+    else hipLaunchKernelGGL((combine_pieces_kernel<DT, 0, STREAM>), pieces, dim3(256), 0, st, r, s2r, w, sh, s.T, s.k, row16, yo);
+#undef MOE_COMBINE
     MOE_LAUNCH_CHECK("combine_kernel");
     return MOE_OK;
 }

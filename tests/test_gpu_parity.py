@@ -594,6 +594,31 @@ def test_combine(H, cfg, with_shared):
     assert H.rel_err(H.host(sh.y), ref) < (1e-6 if cfg.dtype == "fp32" else 2 ** -8)
 
 
+@pytest.mark.parametrize("k", [1, 2, 6])
+@pytest.mark.parametrize("dtype,Hd", [("bf16", 4104), ("fp32", 2052)])
+def test_combine_of_few_and_of_many_tokens_gives_the_same_bits(H, dtype, Hd, k):
+    """1024 tokens (a wave per piece of a row) against the first 1024 of 1030 (a wave per token), rows that end inside a
+    piece, dropped slots, one token with all of them dropped; and both against a plain sum."""
+    P, T = H.P, 1030
+    r = np.random.default_rng(k)
+    ret = H.dev(W.round_to_dtype(r.standard_normal((T * k, Hd)).astype(np.float32), dtype), dtype)
+    shared = H.dev(W.round_to_dtype(r.standard_normal((T, Hd)).astype(np.float32), dtype), dtype)
+    rows = np.where(r.random(T * k) < 0.1, -1, r.integers(0, 1024 * k, size=T * k)).astype(np.int32)
+    rows[5 * k:6 * k] = -1
+    s2r, w = torch.from_numpy(rows).to(H.DEV), torch.from_numpy(r.random((T, k)).astype(np.float32)).to(H.DEV)
+    got = []
+    for n in (1024, T):
+        ctx, y = P.MoeCtx(n, Hd, 8, k, 8, dtype, 0, 0), torch.full((n, Hd), float("nan"), dtype=ret.dtype, device=H.DEV)
+        P.moe_combine(ctx, ret, s2r[:n * k], w[:n], shared[:n], y)
+        got.append(H.host(y))
+    assert np.array_equal(got[0], got[1][:1024])
+    ref = H.host(shared).astype(np.float64)
+    for j in range(k):
+        sl = rows.reshape(T, k)[:, j]
+        ref += np.where(sl[:, None] >= 0, H.host(w)[:, j:j + 1].astype(np.float64) * H.host(ret)[np.maximum(sl, 0)], 0.0)
+    assert H.rel_err(got[1], ref) < (1e-6 if dtype == "fp32" else 2 ** -8)
+
+
 # The tile heights (first GEMM, second GEMM) a share takes, with rows just past a tile edge, gathered tiles, two maps in
 # one workspace, and too many segments for two maps (then both GEMMs take the first one's height).
 TILE_SHAPE_CASES = [(129, 256, 1408, 1, 1, 2, (128, 128)), (385, 128, 9216, 1, 2, 2, (192, 128)), (513, 128, 9216, 2, 9, 2, (256, 128)),
