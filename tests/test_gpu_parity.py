@@ -754,6 +754,27 @@ def test_expert_ffn_fp32_in_halves_takes_every_value(H):
     assert (err <= 4e-6 * np.linalg.norm(ref, axis=1)[fine] + np.sqrt(Hd) * 1012 * 2.0 ** -149).all()
 
 
+def test_expert_ffn_fp32_in_halves_rows_of_zeros_leave_their_tile_to_the_halves(H):
+    """Rows and weight rows of zeros change no bit of the others (a tile formed again would), and rows below the largest
+    scale keep their precision."""
+    R, Hd, F = 4000, 356, 1012
+    assert f32_rows(R, 1, 1, Hd, F, 0) == [128, 128]
+    r = np.random.default_rng(6)
+    recv = r.standard_normal((R, Hd)).astype(np.float32)
+    tiny = np.arange(50, R, 500)
+    recv[tiny] *= np.float32(2.0 ** -117)
+    w = W.make_expert_weights(small("c1_tiny_fp32", H=Hd, F=F, act=0), 0)
+    whole = H.host(H.run_ffn(H.dev(recv, "fp32"), [0, R], [0], [H.weights_to_dev(w, "fp32")], Hd, F, 0, "fp32"))
+    rows, cols = np.arange(3, R, 90), np.arange(1, Hd, 60)
+    recv[rows], w["w_down"][cols] = 0.0, 0.0
+    out = H.host(H.run_ffn(H.dev(recv, "fp32"), [0, R], [0], [H.weights_to_dev(w, "fp32")], Hd, F, 0, "fp32"))
+    assert (out[rows] == 0).all() and (out[:, cols] == 0).all()
+    assert np.array_equal(np.delete(np.delete(out, rows, 0), cols, 1), np.delete(np.delete(whole, rows, 0), cols, 1))
+    ref = O.ffn(recv[tiny], w["w1"], w["w_up"], w["w_down"], 0)         # the bound of the test above
+    err = np.linalg.norm(out[tiny] - ref, axis=1)
+    assert (err <= 4e-6 * np.linalg.norm(ref, axis=1) + np.sqrt(Hd) * 1012 * 2.0 ** -149).all()
+
+
 @pytest.mark.parametrize("R,nseg", [(60, 5), (300, 63), (300, 64), (300, 65), (1000, 64)])
 def test_expert_ffn_tile_map_skips_what_it_must(H, R, nseg):
     """Empty segments, segments of no local expert, rows before the first and after the last segment, on both sides of
