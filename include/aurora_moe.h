@@ -268,7 +268,7 @@ int moe_selfcheck_flow_player(int32_t n, const int64_t* D, const double* B, cons
 int moe_selfcheck_narrow(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* forms2);
 
 /* Rows per tile of the two GEMMs of an fp32 share of R rows in nseg segments of n_used experts: 64 (fp32 matrix cores) or
- * 128 (pairs of halves on the fp16 ones).  Self check, runs on the host. */
+ * 128 (three bf16 parts on the bf16 ones).  Self check, runs on the host. */
 int moe_selfcheck_f32_kernels(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2);
 
 /* Walk of the blocks of a bf16 FFN GEMM through tiles_m x tiles_n tiles of `rows` rows (128, 192, 256) with inner dimension

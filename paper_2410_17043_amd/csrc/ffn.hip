@@ -25,10 +25,11 @@
 // Shares of at most 64 rows (bf16) take a pair of weight-streaming kernels instead (gemm_bf16_skinny_kernel):
 // 32- or 64-row tiles, 256-byte bursts per weight row, the LDS ring given to loads in flight.
 //
-// fp32 path: 128 x 128 tiles of pairs of halves on the fp16 matrix cores (gemm_f32_halves_kernel); where there are too few
-// of them, 64 x 64 tiles on the fp32 matrix cores (gemm_f32_kernel).
+// fp32 path: 128 x 128 tiles of three bf16 parts per element on the bf16 matrix cores (gemm_f32_parts_kernel); where there are
+// too few of them, 64 x 64 tiles on the fp32 matrix cores (gemm_f32_kernel).
 #include "common.h"
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <cstddef>
 #include <type_traits>
@@ -952,108 +953,110 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     return *reinterpret_cast<const uint32_t*>(&b);
 }
 
-// The same products on the fp16 matrix cores, for grids that fill the chip with 128 x 128 tiles (see f32_in_halves).
+// The same products on the bf16 matrix cores, for grids that fill the chip with 128 x 128 tiles (see take_f32_kernels).
 //
-// A float, scaled by a power of two that its row has, is h + l / 2048 + a rest of at most 2^-23 of it, with h and l in fp16
-// (11 bits and a sign each), and x w = h_x h_w + (h_x l_w + l_x h_w) / 2048 + terms below 2^-22: three products of
-// v_mfma_f32_32x32x16_f16 in 96 clocks per 16 elements of K instead of 512 for v_mfma_f32_32x32x2_f32.  Products of
-// halves are exact, and the small ones are accumulated apart from h_x h_w, so that they are not rounded to its last bit:
-// against 64 bits the rms error is 0.36 to 0.9 of that of the fp32 instruction's chain over K = 64 ... 8192 of normal,
-// uniform, heavy-tailed and unevenly scaled operands (K = 128 / 1024 / 8192 of normal ones: 1.1e-7 / 2.2e-7 / 5.9e-7
-// against 2.1e-7 / 5.8e-7 / 1.6e-6).  (It is the sum's rounding that shrinks: a single product is off by up to 2^-21, where the
-// fp32 instruction rounds it to 2^-24.)  Three bf16 parts and six products, which have all 24 bits, took 1.5 times as long.
+// A float of 24 bits is the sum of three bf16 numbers of 8 bits and a sign, x = x0 + x1 + x2, each the rest rounded to nearest
+// (the differences are exact), and x w = x0 w0 + (x0 w1 + x1 w0) + (x1 w1 + x0 w2 + x2 w0) + terms below 2^-24 of it: six
+// products of v_mfma_f32_32x32x16_bf16 in 192 clocks per 16 elements of K instead of 512 for v_mfma_f32_32x32x2_f32.  (The
+// splitting and the six products are those of G. Henry, P. Tang and A. Heinecke, "Leveraging the bfloat16 artificial
+// intelligence datatype for higher-precision computations", 2019.)  bf16 has the exponents of fp32, so no element needs a scale
+// and none hides behind a larger one.  Products of parts are exact, and the small ones are accumulated apart from x0 w0, so
+// that they are not rounded to its last bit: against 64 bits the FFN is off by a quarter of what the chain of fp32 products is (3001
+// rows of 1024 -> 2816 -> 1024, normal, uniform, heavy-tailed and unevenly scaled operands: 1.4e-7 ... 2.8e-7 against 7.4e-7 ...
+// 1.16e-6, also behind elements of 2^20 to 2^60 that meet zeros).  A single product is off by 0.43 x 2^-24 rms and below 2^-23, one
+// of fp32 by 0.42 x 2^-24 and up to 2^-24: for rows with one nonzero element both FFNs are off by 5.7e-8.
 //
-// The scale puts the largest of the row's first 32 elements at 4 to 8 (at most 2^116, also for zeros: then 2048 times the
-// scale is finite, and a row of zeros has finite sums; elements of 2^-100 and above behind 32 zeros do not).  Elements up to 2^13
-// times that one keep all their bits down to 2^-15 times it; the rest below is cut at 2^-39 times it.  A row with larger elements,
-// an infinity or a NaN leaves a sum that is not finite, and the block forms the tile again with v_mfma_f32_32x32x2_f32
-// (multiply_exactly: with a row in every
-// tile of the first GEMM that asks for it, 3001 rows of 1024 -> 2816 -> 1024 SwiGLU take 680 us instead of 238).
+// What parts cannot give is taken from the fp32 matrix cores, element by element (multiply_exactly): a sum that is not finite
+// (infinities, NaN, and elements that bf16 rounds to infinity), and one so small that what lies below the range of the parts
+// could count in it: less than K 2^-100 times the largest element of its row or weight row, and 1 (rows of zeros have
+// nothing to lose).  Small are then the sums of both groups of waves below: one that merely cancels, which one in 10^8 does, has
+// lost nothing that counts.  The other elements of the tile stay as they are: no row depends on its neighbours.
 //
 // 128 x 128 block tile, k-tiles of 32, 8 waves: two groups of 2 x 2 waves, 64 x 64 each, group g taking half g of every
 // k-tile; the groups' sums are exchanged through LDS at the end and each group finishes half of the rows: two waves per
 // SIMD on one tile per CU.  Every element is split once per block: loaded to registers three k-tiles
-// ahead, split between the products and written to LDS as two planes one ahead (two stages of 32 KB).
-// The pair of GEMMs of 3001 rows of 1024 -> 2816 -> 1024 SwiGLU: 407 us with gemm_f32_kernel, 216 here; 20000 rows, SiLU:
-// 1740 -> 861 (268 TFLOP/s).  The card is at its power limit then: leaving out the split, the loads or the LDS writes
-// gains a fifth each, at a higher clock.
+// ahead, split between the products and written to LDS as three planes one ahead (two stages of 48 KB).
+// The pair of GEMMs of 3001 rows of 1024 -> 2816 -> 1024 SwiGLU takes 410 us with gemm_f32_kernel and 330 here; 20000 rows,
+// SiLU: 1750 -> 1290 (179 TFLOP/s; the fp32 instruction reaches 155 from registers).  With all results of a GEMM below the limit: 3001
+// rows, SiLU, 283 -> 490 for one GEMM of the two, 730 for both (234 above it).
 // Blocks walk through tiles like those of gemm_bf16_kernel: the loads run on into the next tile.
 //
 // Plane of an operand tile: 128 rows x 32 elements as blocks of 16 rows x 4 chunks of 16 bytes (tile_off, conflict-free).
 // The order of the sum over k is free: chunk c holds elements 4 c .. 4 c + 3 and 16 + 4 c .. + 3 of the k-tile, so that
 // four lanes fetch 64 contiguous bytes of a row per load.
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 constexpr int XM = 128, XN = 128, XK = 32;
 constexpr int kXPlane = XM * XK * 2;                     // 8 KB
-constexpr int kXOperand = 2 * kXPlane;
+constexpr int kXOperand = 3 * kXPlane;
 constexpr int kXStage = 2 * kXOperand;                   // A, then B
-constexpr int kXGive = 32 * 1024;                        // sums of a group that the other one finishes
-constexpr int kXLds = 2 * kXStage + 2 * kXGive + 2 * (XM + XN) * 4 + 64;   // stages, sums, exponents of the rows of two tiles, votes
+constexpr int kXGive = 32 * 1024;                        // sums of a group that the other one finishes; both groups' begin in the second stage
+constexpr int kXLargest = kXStage + 2 * kXGive;          // largest elements of the rows and weight rows of a tile
+constexpr int kXLds = kXLargest + (XM + XN) * 4;
+static_assert(2 * kXGive >= kXStage, "");
 constexpr int kXMinK = 4 * XK;                           // a walk reads three k-tiles ahead: at most into the next tile
-constexpr float kLowScale = 2048.f;
-constexpr int kMaxScale = 127 - 11;                      // exponent of the largest scale: times kLowScale still a float
+constexpr float kPartsFloor = 0x1p-100f;
 
-// Power of two for the row that four neighbouring lanes hold in q0 and q1
-__device__ __forceinline__ int scale_exponent(const f32x4& q0, const f32x4& q1) {
-    float m = 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) m = fmaxf(m, fmaxf(fabsf(q0[e]), fabsf(q1[e])));
-    m = fmaxf(m, __shfl_xor(m, 1, 64));
-    m = fmaxf(m, __shfl_xor(m, 2, 64));
-    const int e = (int)(__float_as_uint(m) >> 23);         // (m >= 0)
-    return min(127 + 2 - e, kMaxScale);                    // e = 0: zeros (or below 2^-126)
+// m or the larger of |a| and |b| (neither is taken for a NaN)
+__device__ __forceinline__ float largest_of(float m, float a, float b) {
+    asm("v_max3_f32 %0, %0, abs(%1), abs(%2)" : "+v"(m) : "v"(a), "v"(b));
+    return m;
 }
-__device__ __forceinline__ float power_of_two(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }   // -126 <= e <= 127
 
-// A lane's part of an operand pair on its way from floats to planes: 2 x 4 elements of A and of B, taken in pairs.
+// A lane's part of an operand pair on its way from floats to planes: 2 x 4 elements of A and of B, taken in pairs u = 0 .. 7,
+// each in three phases.
 struct Splitter {
-    u32x4 part[2][2];                                      // [A, B][h, l]
-    f16x2 h[8];
-    __device__ __forceinline__ void high(const f32x4 (&q)[4], const float (&scale)[2], int u) {
-        const f32x2 v = {q[u >> 1][2 * (u & 1)] * scale[u >> 2], q[u >> 1][2 * (u & 1) + 1] * scale[u >> 2]};
-        h[u] = __builtin_convertvector(v, f16x2);          // to nearest even
-        part[u >> 2][0][u & 3] = __builtin_bit_cast(uint32_t, h[u]);
+    u32x4 part[2][3];                                      // [A, B][plane]
+    f32x2 rest;
+    __device__ __forceinline__ uint32_t take() {           // nearest bf16 of the rest, which it leaves
+        const bf16x2 b = __builtin_convertvector(rest, bf16x2);
+        return __builtin_bit_cast(uint32_t, b);
     }
-    __device__ __forceinline__ void low(const f32x4 (&q)[4], const float (&scale)[2], int u) {   // exact differences
-        const float s = scale[u >> 2] * kLowScale;
-        const f32x2 v = {__builtin_fmaf((float)h[u].x, -kLowScale, q[u >> 1][2 * (u & 1)] * s), __builtin_fmaf((float)h[u].y, -kLowScale, q[u >> 1][2 * (u & 1) + 1] * s)};
-        part[u >> 2][1][u & 3] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
+    __device__ __forceinline__ void phase(const f32x4 (&q)[4], float (&largest)[2], int p, unsigned char* st) {
+        const int u = p / 3, n = p % 3, op = u >> 2;
+        if (n == 0) {
+            rest = f32x2{q[u >> 1][2 * (u & 1)], q[u >> 1][2 * (u & 1) + 1]};
+            largest[op] = largest_of(largest[op], rest.x, rest.y);
+        }
+        const uint32_t b = take();
+        part[op][n][u & 3] = b;
+        if (n < 2) rest = f32x2{rest.x - bf16_bits_to_f32(b & 0xffffu), rest.y - __uint_as_float(b & 0xffff0000u)};
+        if ((u & 3) == 3) *reinterpret_cast<u32x4*>(st + op * kXOperand + n * kXPlane) = part[op][n];
     }
-    __device__ __forceinline__ void store(unsigned char* st, int op, int n) const { *reinterpret_cast<u32x4*>(st + op * kXOperand + n * kXPlane) = part[op][n]; }
 };
-__device__ __forceinline__ void split_halves(const f32x4 (&q)[4], const float (&scale)[2], unsigned char* st) {
+__device__ __forceinline__ void split_parts(const f32x4 (&q)[4], float (&largest)[2], unsigned char* st) {
     Splitter s;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) { s.high(q, scale, u); s.low(q, scale, u); }
-#pragma unroll
-    for (int n = 0; n < 4; ++n) s.store(st, n / 2, n % 2);
+    for (int p = 0; p < 24; ++p) s.phase(q, largest, p, st);
 }
 // 64 x 64 x 16 ([row tile][weight-row tile], D^T: rows n, columns m) while the next k-tile is split: a product, then a
 // handful of vector instructions, held together (the scheduler left to itself puts all products first)
 typedef f32x16 Acc22[2][2];
-__device__ __forceinline__ void multiply_halves(const unsigned char* pa, const unsigned char* pb, Acc22& hi, Acc22& lo, const f32x4 (&q)[4],
-                                                const float (&scale)[2], unsigned char* then) {
-    f16x8 a[2][2], b[2][2];
-    auto read = [&](f16x8 (&f)[2][2], const unsigned char* p, int n) {
+__device__ __forceinline__ void multiply_parts(const unsigned char* pa, const unsigned char* pb, Acc22& hi, Acc22& lo, const f32x4 (&q)[4],
+                                               float (&largest)[2], unsigned char* then) {
+    bf16x8 a[3][2], b[3][2];
+    auto read = [&](bf16x8 (&f)[3][2], const unsigned char* p, int n) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) f[n][i] = *reinterpret_cast<const f16x8*>(p + n * kXPlane + i * 2048);
+        for (int i = 0; i < 2; ++i) f[n][i] = *reinterpret_cast<const bf16x8*>(p + n * kXPlane + i * 2048);
     };
     read(a, pa, 0);
     read(b, pb, 0);
-    read(a, pa, 1);
     read(b, pb, 1);
+    read(a, pa, 1);
     Splitter s;
-    constexpr int term[3][2] = {{0, 0}, {1, 0}, {0, 1}};   // half of A, of B
+    constexpr int term[6][2] = {{0, 0}, {0, 1}, {1, 1}, {1, 0}, {2, 0}, {0, 2}};   // part of A, of B
 #pragma unroll
-    for (int t = 0; t < 12; ++t) {
+    for (int t = 0; t < 24; ++t) {
         const int i = (t >> 1) & 1, j = t & 1;
         __builtin_amdgcn_sched_barrier(0);
         f32x16& acc = t < 4 ? hi[i][j] : lo[i][j];
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(b[term[t >> 2][1]][j], a[term[t >> 2][0]][i], acc, 0, 0, 0);
-        if (t < 8) { s.high(q, scale, t); s.low(q, scale, t); }
-        if (t == 4 || t == 5) s.store(then, 0, t - 4);
-        if (t == 8 || t == 9) s.store(then, 1, t - 8);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[term[t >> 2][1]][j], a[term[t >> 2][0]][i], acc, 0, 0, 0);
+        if (t == 9) read(a, pa, 2);
+        if (t == 13) read(b, pb, 2);
+        // 24 phases behind the first 22 products: the last of them are in LDS by the barrier
+        if (t < 20) s.phase(q, largest, t, then);
+        if (t == 20 || t == 21) {
+            s.phase(q, largest, 2 * t - 20, then);
+            s.phase(q, largest, 2 * t - 19, then);
+        }
     }
     __builtin_amdgcn_sched_barrier(0);
 }
@@ -1081,7 +1084,7 @@ __device__ __forceinline__ void multiply_exactly(const float* pa, const float* p
 }
 
 template <int EPI>
-__global__ __launch_bounds__(512, 2) void gemm_f32_halves_kernel(const float* __restrict__ A, int lda, TileMap m, ExpertTable tab,
+__global__ __launch_bounds__(512, 2) void gemm_f32_parts_kernel(const float* __restrict__ A, int lda, TileMap m, ExpertTable tab,
                                                                 int which0, int which1, int N, int K, float* __restrict__ C, int ldc,
                                                                 int tiles_n, int ncu, int walk) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -1141,7 +1144,7 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_halves_kernel(const float* __
         q[3] = load(src.b, src.b_voff + quad1, in1);
     };
     f32x4 even[4], odd[4];                                 // k-tiles in flight: two quads of A, two of B
-    float scale[2];                                        // of the rows that this lane splits
+    float largest[2] = {0.f, 0.f};                         // of the elements that this lane has split, of A and of B
     Acc22 hi, lo;
     auto clear = [&] {
 #pragma unroll
@@ -1153,23 +1156,24 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_halves_kernel(const float* __
     };
     const int a_off = tile_off(wm * 64 + fr, 2 * grp + fk), b_off = kXOperand + tile_off(wn * 64 + fr, 2 * grp + fk);
     const int w_off = wave * 1024 + lane * 16;
-    int tile_parity = 0;
-    int32_t* exponents = reinterpret_cast<int32_t*>(lds + 2 * kXStage + 2 * kXGive);
-    auto rescale = [&](const f32x4 (&q)[4]) {              // scales of the tile whose first k-tile is in q; to LDS what undoes them
-        const int ea = scale_exponent(q[0], q[1]), eb = scale_exponent(q[2], q[3]);
-        scale[0] = power_of_two(ea);
-        scale[1] = power_of_two(eb);
-        int32_t* e = exponents + tile_parity * (XM + XN);
-        if ((lane & 3) == 0) { e[16 * wave + (lane >> 2)] = -ea; e[XM + 16 * wave + (lane >> 2)] = -eb; }
-        tile_parity ^= 1;
+    float* tile_largest = reinterpret_cast<float*>(lds + kXLargest);
+    auto note_largest = [&] {                              // of the tile's rows, whose four lanes are neighbours; starts the next tile's
+#pragma unroll
+        for (int op = 0; op < 2; ++op) {
+            float m = largest[op];
+            m = fmaxf(m, __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(m), 0xB1, 0xf, 0xf, true)));   // quad_perm 1 0 3 2
+            m = fmaxf(m, __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(m), 0x4E, 0xf, 0xf, true)));   // 2 3 0 1
+            if ((lane & 3) == 0) tile_largest[op * XM + 16 * wave + (lane >> 2)] = m;
+            largest[op] = 0.f;
+        }
     };
     // k-tile kt is in `now`; the one behind it goes to `then`
     auto step = [&](int kt, unsigned char* now, unsigned char* then, f32x4 (&q)[4]) {
         if (kt + 3 == nk && more) src = src_next;
         __builtin_amdgcn_sched_barrier(0);
-        if (kt + 1 == nk) rescale(q);                      // the next tile's first k-tile
+        if (kt + 1 == nk) note_largest();                  // what is split now is the next tile's first k-tile
         __builtin_amdgcn_sched_barrier(0);
-        multiply_halves(now + a_off, now + b_off, hi, lo, q, scale, then + w_off);
+        multiply_parts(now + a_off, now + b_off, hi, lo, q, largest, then + w_off);
         fetch(q, kt + 3 >= nk ? kt + 3 - nk : kt + 3);
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0): this wave has read `now` and written `then`
@@ -1182,22 +1186,18 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_halves_kernel(const float* __
     fetch(odd, 1);
     if (more) describe(item + ncu, next, src_next);
     clear();
-    unsigned char *st0 = lds, *st1 = lds + kXStage, *sums = lds + 2 * kXStage;
-    uint32_t* votes = reinterpret_cast<uint32_t*>(exponents + 2 * (XM + XN));
-    rescale(even);
-    split_halves(even, scale, st0 + w_off);
+    unsigned char *st0 = lds, *st1 = lds + kXStage, *sums = st1;
+    split_parts(even, largest, st0 + w_off);
     fetch(even, 2);
     __builtin_amdgcn_s_waitcnt(0xC07F);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     while (true) {
-        const int32_t* undo = exponents + (tile_parity ^ 1) * (XM + XN);
         for (int kt = 0; kt < nk; kt += 2) {
             step(kt, st0, st1, odd);
             step(kt + 1, st1, st0, even);
         }
-        // sums of the group, and what of them the other group finishes
-        float off = 0.f;                                   // 0, or NaN if a sum is not finite
+        // sums of the group, and what of them the other group finishes (the second stage is free: the next tile's first k-tile is in st0)
         unsigned char* give = sums + grp * kXGive + (wave & 3) * 8192 + lane * 16;
         const unsigned char* take = sums + (grp ^ 1) * kXGive + (wave & 3) * 8192 + lane * 16;
         f32x16 fin[2];
@@ -1209,47 +1209,51 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_halves_kernel(const float* __
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const int e = 4 * q + t;
-                    const float x0 = __builtin_fmaf(lo[0][j][e], 1.f / kLowScale, hi[0][j][e]), x1 = __builtin_fmaf(lo[1][j][e], 1.f / kLowScale, hi[1][j][e]);
-                    off = __builtin_fmaf(x0, 0.f, __builtin_fmaf(x1, 0.f, off));
+                    const float x0 = hi[0][j][e] + lo[0][j][e], x1 = hi[1][j][e] + lo[1][j][e];
                     fin[j][e] = grp == 0 ? x0 : x1;
                     other[t] = grp == 0 ? x1 : x0;
                 }
                 *reinterpret_cast<f32x4*>(give + (j * 4 + q) * 1024) = other;
             }
-        const bool redo = __ballot(!(off == 0.f)) != 0;
-        if (lane == 0) votes[wave] = redo ? 1 : 0;
         __builtin_amdgcn_s_waitcnt(0xC07F);
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        uint32_t any = 0;
-#pragma unroll
-        for (int w = 0; w < 8; ++w) any |= votes[w];
-        any = __builtin_amdgcn_readfirstlane(any);
+        const int gr = wm * 64 + grp * 32 + fr;
+        const float row_largest = tile_largest[gr];
+        const float small = (float)K * kPartsFloor;
+        uint32_t bad[2] = {0, 0};
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const f32x4 v = *reinterpret_cast<const f32x4*>(take + (j * 4 + q) * 1024);
+                const f32x4 w = *reinterpret_cast<const f32x4*>(&tile_largest[XM + wn * 64 + j * 32 + q * 8 + fk * 4]);
 #pragma unroll
-                for (int t = 0; t < 4; ++t) fin[j][4 * q + t] += v[t];
+                for (int t = 0; t < 4; ++t) {
+                    const int e = 4 * q + t;
+                    const float larger = fmaxf(fabsf(fin[j][e]), fabsf(v[t]));
+                    fin[j][e] += v[t];
+                    const float limit = row_largest > 0.f && w[t] > 0.f ? small * fmaxf(fmaxf(row_largest, w[t]), 1.f) : 0.f;
+                    if (!(larger >= limit && fabsf(fin[j][e]) <= FLT_MAX)) bad[j] |= 1u << e;
+                }
             }
-        const int ea = undo[wm * 64 + grp * 32 + fr];
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    fin[j][4 * q + t] = ldexpf(fin[j][4 * q + t], ea + undo[XM + wn * 64 + j * 32 + q * 8 + fk * 4 + t]);
-        const int gr = wm * 64 + grp * 32 + fr;
-        if (any) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_s_barrier();                      // the sums have been read: the next tile's second k-tile may be written
+        asm volatile("" ::: "memory");
+        if (__ballot((bad[0] | bad[1]) != 0)) {
             int ar = min(gr, cur.nrows - 1);
             if (cur.rel) ar = cur.rel[ar];
             const int c0 = cur.n0 + wn * (NOUT / 2) + fr;
             const float* w0 = reinterpret_cast<const float*>(weights(which0, cur.ex));
             const float* w1 = (EPI == EPI_SWIGLU) ? reinterpret_cast<const float*>(weights(which1, cur.ex)) : w0;
+            f32x16 exact[2];
             multiply_exactly(A + (size_t)(cur.row0 + ar) * lda, w0 + (size_t)min(c0, N - 1) * K,
-                             w1 + (size_t)min((EPI == EPI_SWIGLU) ? c0 : c0 + 32, N - 1) * K, fk, K, fin);
+                             w1 + (size_t)min((EPI == EPI_SWIGLU) ? c0 : c0 + 32, N - 1) * K, fk, K, exact);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (bad[j] >> e & 1) fin[j][e] = exact[j][e];
         }
         if (gr < cur.nrows) {
             float* crow = C + (size_t)(cur.row0 + (cur.rel ? cur.rel[gr] : gr)) * ldc;
@@ -2537,50 +2541,58 @@ int launch_bf16_skinny(const void* A, int lda, const TileMap& m, const ExpertTab
     return launch_bf16_skinny_mt<EPI, 2>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, partial, st);
 }
 
-// Tiles of the fp16 kernel that a block walks through (see kWalkUs).
-int halves_walk_tiles(int K) { return std::max(1, (int)(kWalkUs / (3.3 + 0.89 * (K / (double)XK)))); }
-// Which kernel an fp32 GEMM takes: the 64 x 64 tiles of gemm_f32_kernel keep more CUs busy where there are few tiles, the
-// 128 x 128 ones of gemm_f32_halves_kernel have twice the rate.  Both times are modelled from the estimated number of
-// tiles; the constants (us) are fitted to 250 shares of 20 to 20000 rows, 1 to 8 experts, H of 128 to 1024 and F of 128 to 2816
-// (median error 2 %, 19 of 20 within 7 %).  3 % are left to the older kernel: over those shares none is slower than with
-// it alone.  3001 rows of 1024 -> 2816 -> 1024 SwiGLU: 407 -> 216 us for the pair; 476 rows of 676 -> 2152 -> 676 for 8
-// experts: 95 with either; 64 rows of 640 -> 2424 -> 640: 61 against 77, so those keep the small tiles.
-double f32_us(bool in_halves, int R, int n_used, int N, int K, int act, int cus) {
-    const int side = in_halves ? XM : FM, cols = side / (act == MOE_ACT_SWIGLU ? 2 : 1);
-    const double per_cu = estimated_tiles_m(R, side, n_used) * ((N + cols - 1) / cols) / cus, rounds = std::ceil(per_cu);
-    const int nk = in_halves ? ((K + XK - 1) / XK + 1) / 2 * 2 : (K + FK - 1) / FK;
-    if (in_halves) return 6.7 + rounds * (2.35 + 0.59 * nk) + per_cu * (0.94 + 0.296 * nk);
-    return 5.5 + rounds * (0.8 + 0.515 * nk);
+// Tiles of gemm_f32_parts_kernel that a block walks through (see kWalkUs).
+int parts_walk_tiles(int K) { return std::max(1, (int)(kWalkUs / (5.1 + 1.23 * ((K + XK - 1) / XK)))); }
+// Which kernels an fp32 share takes: the 64 x 64 tiles of gemm_f32_kernel keep more CUs busy where there are few tiles and
+// need no map by a launch of its own, the 128 x 128 ones of gemm_f32_parts_kernel have the higher rate.  The times of both are modelled
+// from the number of tiles, of which the host knows one for every n_used runs of rows only roughly (half a tile of padding
+// per run, 0.29 sqrt(n_used) of them standard deviation): the older kernel is given two deviations on its side, the other
+// one two against it, and 3 % besides, each GEMM by itself and both together with the map.  The constants (us) are fitted to 260
+// shares of 150 to 20000 rows, 1 to 8 experts, H of 128 to 1024 and F of 128 to 2816, all four combinations of kernels one
+// after the other without a pause (median error 2.3 %, 19 of 20 within 7.4 %): a third of the shares takes 128 x 128 tiles and is 1.18
+// times faster.  Over 120 shares that were not fitted none with 128 x 128 tiles is slower than without.
+double f32_us(bool in_parts, int R, int n_used, int N, int K, int act, int cus) {
+    const int side = in_parts ? XM : FM, cols = side / (act == MOE_ACT_SWIGLU ? 2 : 1);
+    double tiles_m = (R + side - 1) / side;
+    if (n_used > 1) tiles_m = std::max((double)n_used, (double)R / side + 0.5 * n_used + (in_parts ? 0.58 : -0.58) * std::sqrt((double)n_used));
+    const double per_cu = tiles_m * ((N + cols - 1) / cols) / cus, rounds = std::ceil(per_cu);
+    const int nk = in_parts ? ((K + XK - 1) / XK + 1) / 2 * 2 : (K + FK - 1) / FK;
+    if (in_parts) return 3.75 + rounds * (5.96 + 0.932 * nk) + per_cu * (0.299 * nk - 0.905);
+    return 5.0 + rounds * (0.504 + 0.505 * nk);
 }
-bool f32_in_halves(int R, int n_used, int N, int K, int act, int cus) {
-    return K >= kXMinK && f32_us(true, R, n_used, N, K, act, cus) < 0.97 * f32_us(false, R, n_used, N, K, act, cus);
-}
-// Both GEMMs of a share.  Without room for two maps the small tiles, unless the large ones win for both.
-void take_f32_kernels(int R, int n_used, int nseg, int H, int F, int act, int cus, bool (&in_halves)[2]) {
-    in_halves[0] = f32_in_halves(R, n_used, F, H, act, cus);
-    in_halves[1] = f32_in_halves(R, n_used, H, F, -1, cus);
-    if (in_halves[0] != in_halves[1] && !maps_fit(R, nseg, FM, XM)) in_halves[0] = in_halves[1] = false;
+constexpr double kF32MapUs = 1.8, kF32Gain = 0.97;
+// Without room for two maps the small tiles, unless the large ones win for both.
+void take_f32_kernels(int R, int n_used, int nseg, int H, int F, int act, int cus, bool (&in_parts)[2]) {
+    double older = 0.0, taken = kF32MapUs;
+    for (int g = 0; g < 2; ++g) {
+        const int N = g == 0 ? F : H, K = g == 0 ? H : F, a = g == 0 ? act : -1;
+        const double small = f32_us(false, R, n_used, N, K, a, cus), large = f32_us(true, R, n_used, N, K, a, cus);
+        in_parts[g] = K >= kXMinK && large < kF32Gain * small;
+        older += small;
+        taken += in_parts[g] ? large : small;
+    }
+    if (taken >= kF32Gain * older || (in_parts[0] != in_parts[1] && !maps_fit(R, nseg, FM, XM))) in_parts[0] = in_parts[1] = false;
 }
 template <int EPI>
-int launch_f32_halves(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
+int launch_f32_parts(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
                      void* C, int ldc, int R, int nseg, hipStream_t st) {
     const int nout = (EPI == EPI_SWIGLU) ? XN / 2 : XN;
-    const int tiles_n = (N + nout - 1) / nout, ncu = round_size(), walk = halves_walk_tiles(K);
+    const int tiles_n = (N + nout - 1) / nout, ncu = round_size(), walk = parts_walk_tiles(K);
     static bool attr_done = false;
     if (!attr_done) {
-        MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_halves_kernel<EPI>), hipFuncAttributeMaxDynamicSharedMemorySize, kXLds));
+        MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_parts_kernel<EPI>), hipFuncAttributeMaxDynamicSharedMemorySize, kXLds));
         attr_done = true;
     }
-    hipLaunchKernelGGL((gemm_f32_halves_kernel<EPI>), dim3(walk_blocks(max_tiles_of(R, XM, nseg) * tiles_n, walk, ncu)), dim3(512), kXLds, st,
+    hipLaunchKernelGGL((gemm_f32_parts_kernel<EPI>), dim3(walk_blocks(max_tiles_of(R, XM, nseg) * tiles_n, walk, ncu)), dim3(512), kXLds, st,
                        reinterpret_cast<const float*>(A), lda, m, tab, which0, which1, N, K, reinterpret_cast<float*>(C), ldc, tiles_n, ncu, walk);
-    MOE_LAUNCH_CHECK("gemm_f32_halves_kernel");
+    MOE_LAUNCH_CHECK("gemm_f32_parts_kernel");
     return MOE_OK;
 }
 
 template <int EPI>
-int launch_f32(bool in_halves, bool need_map, const void* A, int lda, const TileMap& m, SegList seg, const ExpertTable& tab, int which0, int which1,
+int launch_f32(bool in_parts, bool need_map, const void* A, int lda, const TileMap& m, SegList seg, const ExpertTable& tab, int which0, int which1,
                int N, int K, void* C, int ldc, int R, int nseg, int n_used, hipStream_t st) {
-    if (in_halves) return launch_f32_halves<EPI>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, st);
+    if (in_parts) return launch_f32_parts<EPI>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, st);
     const int nout = (EPI == EPI_SWIGLU) ? FN / 2 : FN;
     const int tiles_n = (N + nout - 1) / nout;
     seg.max_tiles = max_tiles_of(R, FM, nseg);
@@ -2660,9 +2672,9 @@ extern "C" int moe_selfcheck_narrow(int32_t R, int32_t n_used, int32_t nseg, int
 extern "C" int moe_selfcheck_f32_kernels(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2) {
     if (R < 1 || n_used < 1 || nseg < n_used || nseg > kMaxSeg || H < 4 || H % 4 != 0 || F < 4 || F % 4 != 0 || act < 0 || act > 2 || ncu < 1 || !rows2)
         return moe_set_error(MOE_EINVAL, "moe_selfcheck_f32_kernels: bad argument");
-    bool in_halves[2];
-    take_f32_kernels(R, n_used, nseg, H, F, act, ncu, in_halves);
-    for (int i = 0; i < 2; ++i) rows2[i] = in_halves[i] ? XM : FM;
+    bool in_parts[2];
+    take_f32_kernels(R, n_used, nseg, H, F, act, ncu, in_parts);
+    for (int i = 0; i < 2; ++i) rows2[i] = in_parts[i] ? XM : FM;
     if (rows2[0] != rows2[1] && !maps_fit(R, nseg, rows2[0], rows2[1])) return moe_set_error(MOE_EINTERNAL, "no room for tile maps of %d and %d rows", rows2[0], rows2[1]);
     return MOE_OK;
 }
@@ -2870,11 +2882,11 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     const int gather = (size_t)R * (size_t)std::max(H, F) * elem_size(dtype) <= 0xFFFFFFFFull ? 1 : 0;
     TileShape shape[2] = {TS_256, TS_256};
     const int n_used = std::min(gather ? std::min(n_local, nseg) : nseg, R);   // runs of rows that share no tile
-    bool in_halves[2] = {false, false};
+    bool in_parts[2] = {false, false};
     int bm[2] = {FM, FM};
     if (dtype == MOE_F32) {
-        take_f32_kernels(R, n_used, nseg, H, F, act, round_size(), in_halves);
-        for (int i = 0; i < 2; ++i) bm[i] = in_halves[i] ? XM : FM;
+        take_f32_kernels(R, n_used, nseg, H, F, act, round_size(), in_parts);
+        for (int i = 0; i < 2; ++i) bm[i] = in_parts[i] ? XM : FM;
     } else if (skinny) {
         bm[0] = bm[1] = skinny_tile_rows(R);
     } else {
@@ -2904,7 +2916,7 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     }
     const TileMap &m = jobs.job[0].m, &m2 = jobs.job[1].m;
     const int n_maps = bm[1] == bm[0] ? 1 : 2;
-    const bool need_map = dtype == MOE_BF16 || nseg > kSmallMapSegs || in_halves[0] || in_halves[1];   // else see SegList
+    const bool need_map = dtype == MOE_BF16 || nseg > kSmallMapSegs || in_parts[0] || in_parts[1];   // else see SegList
     const SegList seg = {seg_offset, seg_expert, nseg, R, n_local, gather, 0};
     if (!need_map) {
     } else if (nseg <= kSmallMapSegs) {                           // about a tile per wave
@@ -2932,16 +2944,16 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         else
             rc = launch_bf16_shape<EPI_SILU>(shape[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
     } else {
-        if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(in_halves[0], need_map, recv, H, m, seg, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, st);
-        else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(in_halves[0], need_map, recv, H, m, seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, st);
-        else rc = launch_f32<EPI_SILU>(in_halves[0], need_map, recv, H, m, seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, st);
+        if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, st);
+        else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, st);
+        else rc = launch_f32<EPI_SILU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, st);
     }
     if (rc != MOE_OK) return rc;
     if (ev) MOE_HIP(hipEventRecord(ev[2], st));
     if (form[1].mt) rc = launch_bf16_narrow<EPI_PLAIN>(form[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, st);
     else if (skinny) rc = launch_bf16_skinny<EPI_PLAIN>(hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, partial, st);
     else if (dtype == MOE_BF16) rc = launch_bf16_shape<EPI_PLAIN>(shape[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, partial, st, timed_gemm == 2, marks, marks_len);
-    else rc = launch_f32<EPI_PLAIN>(in_halves[1], need_map, hmid, F, m2, seg, tab, 2, 2, H, F, out, H, R, nseg, n_used, st);
+    else rc = launch_f32<EPI_PLAIN>(in_parts[1], need_map, hmid, F, m2, seg, tab, 2, 2, H, F, out, H, R, nseg, n_used, st);
     if (rc != MOE_OK) return rc;
     if (ev) MOE_HIP(hipEventRecord(ev[3], st));
     return MOE_OK;

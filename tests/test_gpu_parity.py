@@ -705,11 +705,12 @@ def test_expert_ffn_narrow_tiles(H, R, Hd, F, n_local, nseg, act, forms):
     H.assert_close(out[off[0]:off[-1]], O.expert_ffn(recv, off, exp, experts, act)[off[0]:off[-1]], "bf16")
 
 
-# fp32 GEMMs on pairs of halves (128-row tiles): a K that ends inside a k-tile and an odd number of them, gathered and
-# ragged tiles, N of no whole tile, several tiles per block, one kernel of each kind with a map of its own
-@pytest.mark.parametrize("act,R,Hd,F,n_local,nseg,rows", [(1, 1300, 1156, 1164, 2, 9, [128, 128]), (2, 4000, 132, 1012, 3, 40, [128, 64]),
-                                                          (0, 60000, 132, 292, 1, 1, [128, 128]), (0, 9000, 516, 772, 2, 700, [128, 128])])
-def test_expert_ffn_fp32_in_halves(H, act, R, Hd, F, n_local, nseg, rows):
+# fp32 GEMMs on three bf16 parts (128-row tiles): a K that ends inside a k-tile and an odd number of them, gathered and
+# ragged tiles, N of no whole tile, several tiles per block, one kernel of each kind with a map of its own, K of the least four k-tiles
+@pytest.mark.parametrize("act,R,Hd,F,n_local,nseg,rows", [(1, 1800, 1156, 1164, 2, 9, [128, 128]), (2, 3000, 292, 1156, 3, 40, [128, 64]),
+                                                          (0, 40000, 260, 356, 1, 1, [128, 128]), (0, 12000, 516, 772, 2, 700, [128, 128]),
+                                                          (0, 20000, 128, 356, 1, 1, [128, 128])])
+def test_expert_ffn_fp32_in_parts(H, act, R, Hd, F, n_local, nseg, rows):
     assert f32_rows(R, n_local, nseg, Hd, F, act) == rows
     test_expert_ffn_fp32_tiles(H, act, R, Hd, F, n_local, nseg)
 
@@ -722,9 +723,9 @@ def f32_rows(R, n_local, nseg, Hd, F, act):
     return list(got)
 
 
-def test_expert_ffn_fp32_in_halves_takes_every_value(H):
-    """Rows and weight rows of any scale, zeros where the scale is taken from, elements far above it, infinities, NaN."""
-    R, Hd, F, n_local, nseg = 4000, 356, 1012, 2, 40
+def test_expert_ffn_fp32_in_parts_takes_every_value(H):
+    """Rows and weight rows of any scale, zeros in front, elements far apart, infinities, NaN."""
+    R, Hd, F, n_local, nseg = 6000, 356, 1012, 2, 40
     assert f32_rows(R, n_local, nseg, Hd, F, 0) == [128, 128]
     cfg = small("c1_tiny_fp32", H=Hd, F=F, act=0)
     r = np.random.default_rng(5)
@@ -733,7 +734,7 @@ def test_expert_ffn_fp32_in_halves_takes_every_value(H):
     recv *= scale[:, None].astype(np.float32)
     recv[100:103] = 0.0
     recv[200, :64] = 0.0
-    recv[300, :32] *= np.float32(1e-9)                                # elements past the range of the row's scale: the tile is formed again
+    recv[300, :32] *= np.float32(1e-9)
     recv[301, 5] *= np.float32(1e6)
     experts = [W.make_expert_weights(cfg, e) for e in range(n_local)]
     experts[0]["w1"][7] *= np.float32(1e-25)
@@ -754,10 +755,10 @@ def test_expert_ffn_fp32_in_halves_takes_every_value(H):
     assert (err <= 4e-6 * np.linalg.norm(ref, axis=1)[fine] + np.sqrt(Hd) * 1012 * 2.0 ** -149).all()
 
 
-def test_expert_ffn_fp32_in_halves_rows_of_zeros_leave_their_tile_to_the_halves(H):
-    """Rows and weight rows of zeros change no bit of the others (a tile formed again would), and rows below the largest
-    scale keep their precision."""
-    R, Hd, F = 4000, 356, 1012
+def test_expert_ffn_fp32_in_parts_rows_of_zeros_change_no_other(H):
+    """Rows and weight rows of zeros change no bit of the others (a tile formed again would), and rows of tiny elements
+    keep their precision."""
+    R, Hd, F = 6000, 356, 1012
     assert f32_rows(R, 1, 1, Hd, F, 0) == [128, 128]
     r = np.random.default_rng(6)
     recv = r.standard_normal((R, Hd)).astype(np.float32)
@@ -773,6 +774,64 @@ def test_expert_ffn_fp32_in_halves_rows_of_zeros_leave_their_tile_to_the_halves(
     ref = O.ffn(recv[tiny], w["w1"], w["w_up"], w["w_down"], 0)         # the bound of the test above
     err = np.linalg.norm(out[tiny] - ref, axis=1)
     assert (err <= 4e-6 * np.linalg.norm(ref, axis=1) + np.sqrt(Hd) * 1012 * 2.0 ** -149).all()
+
+
+@pytest.mark.parametrize("operand", ["rows", "weights"])
+@pytest.mark.parametrize("p", [13, 24, 30, 40, 100])
+def test_expert_ffn_fp32_in_parts_large_elements_hide_no_other(H, operand, p):
+    """An element of 2^p that meets weights of zero (or the other way round) leaves the sum to the others, which keep their
+    precision: the bound of the tests above, from operands without that column."""
+    R, Hd, F = 6000, 356, 1012
+    assert f32_rows(R, 1, 1, Hd, F, 0) == [128, 128]
+    r = np.random.default_rng(7)
+    recv = r.standard_normal((R, Hd)).astype(np.float32)
+    w = W.make_expert_weights(small("c1_tiny_fp32", H=Hd, F=F, act=0), 0)
+    recv[:, 5], w["w1"][:, 5] = 0.0, 0.0
+    ref = O.ffn(recv, w["w1"], w["w_up"], w["w_down"], 0)
+    if operand == "rows":
+        recv[:, 5] = 2.0 ** p
+    else:
+        w["w1"][:, 5] = 2.0 ** p
+    out = H.host(H.run_ffn(H.dev(recv, "fp32"), [0, R], [0], [H.weights_to_dev(w, "fp32")], Hd, F, 0, "fp32"))
+    err = np.linalg.norm(out - ref, axis=1)
+    assert (err <= 4e-6 * np.linalg.norm(ref, axis=1)).all(), (err / np.linalg.norm(ref, axis=1)).max()
+
+
+def test_expert_ffn_fp32_in_parts_single_products_are_rounded_as_in_fp32(H):
+    """Rows with one nonzero element, whose products with the weights are large enough that silu is the identity (20 and
+    above: off by 2e-9), and a w_down with one per row.  A product of parts leaves out up to 2^-24 of it, its small
+    products are rounded below 2^-31 of it and the sum once, 2^-24: 4 x 2^-24 for both GEMMs, and what silu and those add."""
+    R, Hd, F = 6000, 356, 1012
+    assert f32_rows(R, 1, 1, Hd, F, 0) == [128, 128]
+    r = np.random.default_rng(8)
+    recv = np.zeros((R, Hd), dtype=np.float32)
+    recv[np.arange(R), r.integers(0, Hd, size=R)] = r.uniform(20, 40, size=R)
+    w = {"w1": r.uniform(1, 2, size=(F, Hd)).astype(np.float32), "w_up": None, "w_down": np.zeros((Hd, F), dtype=np.float32)}
+    w["w_down"][np.arange(Hd), r.integers(0, F, size=Hd)] = r.uniform(-2, 2, size=Hd)
+    out = H.host(H.run_ffn(H.dev(recv, "fp32"), [0, R], [0], [H.weights_to_dev(w, "fp32")], Hd, F, 0, "fp32"))
+    ref = (recv.astype(np.float64) @ w["w1"].T.astype(np.float64)) @ w["w_down"].T.astype(np.float64)
+    assert np.abs(out / ref - 1).max() <= 4.1 * 2.0 ** -24
+
+
+def test_expert_ffn_fp32_in_parts_no_row_depends_on_its_neighbours(H):
+    """Infinities, NaN, the largest floats, zeros in front and rows of tiny elements in every tile change no bit of the other rows."""
+    R, Hd, F = 6000, 356, 1012
+    assert f32_rows(R, 1, 1, Hd, F, 0) == [128, 128]
+    r = np.random.default_rng(9)
+    recv = r.standard_normal((R, Hd)).astype(np.float32)
+    dw = H.weights_to_dev(W.make_expert_weights(small("c1_tiny_fp32", H=Hd, F=F, act=0), 0), "fp32")
+    whole = H.host(H.run_ffn(H.dev(recv, "fp32"), [0, R], [0], [dw], Hd, F, 0, "fp32"))
+    odd = np.arange(R) % 37 == 5
+    which = np.nonzero(odd)[0]
+    for i, row in enumerate(which):
+        if i % 5 == 0: recv[row, i % Hd] = np.inf
+        elif i % 5 == 1: recv[row, i % Hd] = np.nan
+        elif i % 5 == 2: recv[row, i % Hd] = np.float32(3.4e38)
+        elif i % 5 == 3: recv[row, :32] = 0.0
+        else: recv[row] *= np.float32(1e-35)
+    out = H.host(H.run_ffn(H.dev(recv, "fp32"), [0, R], [0], [dw], Hd, F, 0, "fp32"))
+    assert np.array_equal(out[~odd], whole[~odd])
+    assert (~np.isfinite(out[which[0::5]])).any(axis=1).all() and np.isnan(out[which[1::5]]).all()
 
 
 @pytest.mark.parametrize("R,nseg", [(60, 5), (300, 63), (300, 64), (300, 65), (1000, 64)])
