@@ -271,6 +271,10 @@ int moe_selfcheck_narrow(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int
  * 128 (three bf16 parts on the bf16 ones).  Self check, runs on the host. */
 int moe_selfcheck_f32_kernels(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2);
 
+/* 1 where such a share has its tile maps made by a launch of their own, 0 where the blocks work their tiles out from the
+ * segment list (few tiles of 64 rows in at most 64 segments), or a negative moe_status. */
+int moe_selfcheck_f32_map(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu);
+
 /* Walk of the blocks of a bf16 FFN GEMM through tiles_m x tiles_n tiles of `rows` rows (128, 192, 256) with inner dimension
  * K on ncu compute units, launched for up to max_tiles_m: checks that every tile and piece is taken by one block, a piece
  * as its block's last.  Returns the number of tiles a block takes at most, or a negative moe_status. */

@@ -461,7 +461,7 @@ __global__ __launch_bounds__(256) void tilemap_small_kernel(const int32_t* __res
 // out from the list, instead of a map by a launch of its own.  A small fp32 share (256 tokens, 517 rows of 64 -> 128 -> 64) is
 // bound by its launches: 32.1 -> 27.9 us with six instead of seven.  In the narrow tiles of decode steps the same gained
 // nothing: the list is cold in every kernel, and what the map's launches cost (2 x 4.7 us) the four GEMMs took longer.  Up to 64
-// segments.
+// segments, and few tiles (see kListTiles).
 struct SegList { const int32_t *offset, *expert; int nseg, R, n_local, gather, max_tiles; };
 __device__ __forceinline__ SmallMap load_segments(const SegList& g, int bm, WaveLanes& w) {
     w.lane = threadIdx.x & 63;
@@ -757,7 +757,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(const float* __restric
     if constexpr (SEG) map = load_segments(seg, FM, lanes);
     const int n_tiles_m = SEG ? __builtin_amdgcn_readfirstlane(map.n_tiles) : *m.n_tiles;
     const int total = n_tiles_m * tiles_n;
-    for (int id = blockIdx.x; id < total; id += gridDim.x) {   // one, unless the list has more runs than experts
+    for (int id = blockIdx.x; id < total; id += gridDim.x) {   // one: always with a map, else unless the list has more runs than experts
         int tile_m, tile_n;
         tile_of_block(id, total, n_tiles_m, tiles_n, &tile_m, &tile_n);
         SmallTile t{};
@@ -886,6 +886,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(const float* __restric
                 if (col < N) *reinterpret_cast<f32x4*>(crow + col) = v;            // N is a multiple of 4
             }
         }
+        if constexpr (!SEG) return;
         __builtin_amdgcn_s_barrier();              // the next item's loads go to the same LDS
     }
 }
@@ -2573,6 +2574,16 @@ void take_f32_kernels(int R, int n_used, int nseg, int H, int F, int act, int cu
     }
     if (taken >= kF32Gain * older || (in_parts[0] != in_parts[1] && !maps_fit(R, nseg, FM, XM))) in_parts[0] = in_parts[1] = false;
 }
+// Shares that take gemm_f32_kernel twice work their tiles out from the segment list (see SegList) up to this many tiles of both GEMMs
+// per CU: the launch of the map, 1.5 us, is saved once, working a tile out costs every block.  1200 tiles on 256 CUs 1.02 to 1.07
+// times faster, 2000 0.97 to 1.06, 4000 0.93 to 0.95, 9000 (20480 rows of 64 -> 1600 -> 64) 0.92.
+constexpr int kListTiles = 5;
+bool f32_needs_map(int R, int n_used, int nseg, int H, int F, int act, int cus, const bool (&in_parts)[2]) {
+    if (nseg > kSmallMapSegs || in_parts[0] || in_parts[1]) return true;
+    const int cols = act == MOE_ACT_SWIGLU ? FN / 2 : FN;
+    const int64_t tiles_m = std::min<int64_t>(max_tiles_of(R, FM, nseg), (R + (int64_t)n_used * (FM - 1)) / FM);
+    return tiles_m * ((F + cols - 1) / cols + (H + FN - 1) / FN) > (int64_t)kListTiles * cus;
+}
 template <int EPI>
 int launch_f32_parts(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
                      void* C, int ldc, int R, int nseg, hipStream_t st) {
@@ -2596,12 +2607,12 @@ int launch_f32(bool in_parts, bool need_map, const void* A, int lda, const TileM
     const int nout = (EPI == EPI_SWIGLU) ? FN / 2 : FN;
     const int tiles_n = (N + nout - 1) / nout;
     seg.max_tiles = max_tiles_of(R, FM, nseg);
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(std::min(seg.max_tiles, (R + n_used * (FM - 1)) / FM) * tiles_n), dim3(256), 0, st,
+    auto launch = [&](auto kernel, int tiles_m) {
+        hipLaunchKernelGGL(kernel, dim3(tiles_m * tiles_n), dim3(256), 0, st,
                            reinterpret_cast<const float*>(A), lda, m, seg, tab, which0, which1, N, K, reinterpret_cast<float*>(C), ldc, tiles_n);
     };
-    if (need_map) launch(gemm_f32_kernel<EPI, false>);
-    else launch(gemm_f32_kernel<EPI, true>);
+    if (need_map) launch(gemm_f32_kernel<EPI, false>, seg.max_tiles);
+    else launch(gemm_f32_kernel<EPI, true>, std::min(seg.max_tiles, (R + n_used * (FM - 1)) / FM));
     MOE_LAUNCH_CHECK("gemm_f32_kernel");
     return MOE_OK;
 }
@@ -2677,6 +2688,14 @@ extern "C" int moe_selfcheck_f32_kernels(int32_t R, int32_t n_used, int32_t nseg
     for (int i = 0; i < 2; ++i) rows2[i] = in_parts[i] ? XM : FM;
     if (rows2[0] != rows2[1] && !maps_fit(R, nseg, rows2[0], rows2[1])) return moe_set_error(MOE_EINTERNAL, "no room for tile maps of %d and %d rows", rows2[0], rows2[1]);
     return MOE_OK;
+}
+
+extern "C" int moe_selfcheck_f32_map(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu) {
+    int32_t rows2[2];
+    const int rc = moe_selfcheck_f32_kernels(R, n_used, nseg, H, F, act, ncu, rows2);
+    if (rc != MOE_OK) return rc;
+    const bool in_parts[2] = {rows2[0] == XM, rows2[1] == XM};
+    return f32_needs_map(R, n_used, nseg, H, F, act, ncu, in_parts) ? 1 : 0;
 }
 
 extern "C" int moe_selfcheck_walk(int32_t rows, int32_t tiles_m, int32_t max_tiles_m, int32_t tiles_n, int32_t K, int32_t ncu) {
@@ -2916,7 +2935,7 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     }
     const TileMap &m = jobs.job[0].m, &m2 = jobs.job[1].m;
     const int n_maps = bm[1] == bm[0] ? 1 : 2;
-    const bool need_map = dtype == MOE_BF16 || nseg > kSmallMapSegs || in_parts[0] || in_parts[1];   // else see SegList
+    const bool need_map = dtype == MOE_BF16 || f32_needs_map(R, n_used, nseg, H, F, act, round_size(), in_parts);   // else see SegList
     const SegList seg = {seg_offset, seg_expert, nseg, R, n_local, gather, 0};
     if (!need_map) {
     } else if (nseg <= kSmallMapSegs) {                           // about a tile per wave

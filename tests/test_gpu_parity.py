@@ -650,7 +650,8 @@ def test_expert_ffn_blocks_walk_through_tiles(H, R, Hd, F, n_local, nseg, act, r
 
 
 # fp32 tiles of 64 x 64: one row past a tile, a K that is no multiple of the 32-wide k-tile, gathered tiles, N below a tile
-@pytest.mark.parametrize("act,R,Hd,F,n_local,nseg", [(2, 65, 100, 68, 1, 1), (0, 129, 36, 260, 2, 9), (1, 64, 4, 4, 1, 1), (2, 300, 128, 96, 3, 64)])
+@pytest.mark.parametrize("act,R,Hd,F,n_local,nseg", [(2, 65, 100, 68, 1, 1), (0, 129, 36, 260, 2, 9), (1, 64, 4, 4, 1, 1), (2, 300, 128, 96, 3, 64),
+                                                     (0, 14900, 64, 320, 3, 64)])     # the last by a tile map, for its many tiles
 def test_expert_ffn_fp32_tiles(H, act, R, Hd, F, n_local, nseg):
     cfg = small("c1_tiny_fp32", H=Hd, F=F, act=act)
     r = np.random.default_rng(R + F)

@@ -461,6 +461,19 @@ def test_tile_maps_leave_room_for_the_counters_of_cut_tiles():
     assert one_height > 0
 
 
+def test_only_shares_of_few_fp32_tiles_are_spared_the_tile_map():
+    """Every block of gemm_f32_kernel that works its tile out from the segment list pays for it: beyond 5 tiles per CU in both
+    GEMMs together, more than 64 segments or with larger tiles in one of them the map is made once."""
+    from paper_2410_17043_amd import _lib
+    needs_map = _lib.load().moe_selfcheck_f32_map
+    for n in (1, 8):
+        for R, Hd, F, nseg in ((517, 64, 128, 8), (12800, 64, 320, 8), (1, 4, 4, 8)):
+            assert needs_map(R, n, nseg, Hd, F, 0, 256) == 0, (R, n)
+        for R, Hd, F, nseg in ((14300, 64, 320, 8), (20480, 64, 1600, 8), (300000, 64, 64, 8), (517, 64, 128, 65), (3001, 1024, 2816, 8)):
+            assert needs_map(R, n, nseg, Hd, F, 0, 256) == 1, (R, n)
+    assert needs_map(9000, 8, 8, 64, 320, 2, 256) == 1 and needs_map(6000, 8, 8, 64, 320, 2, 256) == 0      # SwiGLU: 32 columns per tile
+
+
 def test_a_block_walks_through_a_bounded_run_of_tiles():
     """Every tile and piece is taken once, and no block holds its CU for more than 210 us or one tile: what another stream
     has queued gets in between blocks."""
