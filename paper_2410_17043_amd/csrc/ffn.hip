@@ -2042,7 +2042,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_skinny_kernel(const uint16_t
 
 // Shares of up to a tile of rows per expert (see narrow_form): every weight is used once or twice, and what counts is how
 // many CUs stream and what each has to fetch - a CU gets about 58 GB/s of operands that are not in its L2, whether 90 or 130
-// KB of loads are in flight.  So a tile is 32 MT rows x only 32 NT weight rows over the whole of K: enough tiles for the
+// KB of loads are in flight, what a tile costs besides included (55 to 110 GB/s without it, see kNarrowForms).  So a tile is 32 MT rows x only 32 NT weight rows over the whole of K: enough tiles for the
 // chip without cutting K, which costs the 128 x 128 tiles and the kernel above 64 KB of partial sums per block, a counter and a
 // last block that adds them.  Weights 2048 -> 1408 -> 2048 for four experts and 403 rows, weights from cold memory: 29.4 + 22.1
 // -> 18.8 + 12.5 us; 64 rows of 2048 -> 2816 -> 2048 13.3 + 15.0 -> 11.2 + 10; a decode step with both 130 -> 95.
@@ -2452,52 +2452,79 @@ int launch_bf16_skinny_mt(const void* A, int lda, const TileMap& m, const Expert
     MOE_LAUNCH_CHECK("gemm_bf16_skinny_kernel");
     return MOE_OK;
 }
-// Which shares take narrow tiles, and of which form.  The time of a form is modelled as what a CU has to fetch (74 GB/s and 3 us per
-// round of tiles), together with the weights at 4.2 TB/s (their 4-norm); that of the weight-streaming kernels likewise, with their
-// pieces; that of the tiled kernels as in played_us; all without the launch.  A form is taken where it is modelled 10 % faster.
-// Only up to 128 rows per expert: beyond, the weights are fetched again for every tile of rows.  The constants are fitted to 760
-// shares of 1 to 2560 rows, 1 to 16 experts, H of 256 to 4096 and F of 256 to 14336, weights from cold memory (median error 8 %);
-// over those the expert FFN gets 1.118 times faster on average (1.157 if the best form were always known, 1.124 without the 10 %), 3
-// shares are more than 3 % slower, by at most 11 %.
+// Which shares take narrow tiles, and of which form.  The time of a form is modelled as what a CU has to fetch (per round of
+// tiles), together with the weights at the rate they stream and with all that is fetched, again and again for every tile, from caches (the
+// 4-norm of the three); that of the weight-streaming kernels likewise, with their pieces; that of the tiled kernels as in played_us; all
+// with what the start of a kernel costs.  A form has to be 15 % faster in the mean of the five ways in which rows spread over
+// experts (spread_tiles_m), 8 % beside the streaming kernels, whose times are better known; even popularity alone decides where it says less than 0.7 or more than the other kernel's time.
+// Only up to 128 rows per expert: beyond, the weights are fetched again for every tile of rows.  The constants are fitted to the
+// 5600 GEMMs of 2800 shares of 1 to 2000 rows, 1 to 16 experts, H of 128 to 4096 and F of 128 to 14336, rows in even shares, by
+// chance, by popularity and cut at random, weights from cold memory (median error 4 to 7 %).  Over 1200 others the expert FFN is 1.312 times
+// faster in the mean than without narrow tiles, one is more than 3 % slower (44.6 -> 47.4 us); with even popularity alone and 10 %
+// 39 of 900 were, by up to 20 %.
 struct NarrowForm { int mt, nt; };                       // mt = 0: none
-constexpr NarrowForm kNarrowForms[] = {{4, 2}, {2, 2}, {2, 1}, {1, 2}, {1, 1}};
-double stream_us(double rounds, double bytes, double gb_s, double per_round, int n_used, int N, int K, int act, double tb_s) {
+struct NarrowCost { NarrowForm form; double start, gb_s, per_round, tb_s, all_tb_s; };
+constexpr NarrowCost kNarrowForms[] = {{{4, 2}, 5.46, 67.4, 2.83, 3.79, 16.3}, {{2, 2}, 4.40, 61.3, 2.99, 4.47, 13.7}, {{2, 1}, 3.97, 82.3, 2.67, 3.27, 14.6},
+                                       {{1, 2}, 4.05, 54.7, 3.37, 4.93, 100.0}, {{1, 1}, 3.83, 109.8, 2.74, 4.38, 10.2}};
+constexpr double kNarrowGain = 0.85, kNarrowGainStreaming = 0.92;
+double stream_us(double rounds, double bytes, double gb_s, double per_round, int n_used, int N, int K, int act, double tb_s, double all_us = 0.0) {
     const double cu = rounds * (bytes * 1e-3 / gb_s + per_round), hbm = (double)n_used * N * K * (act == MOE_ACT_SWIGLU ? 4.0 : 2.0) * 1e-6 / tb_s;
-    return std::sqrt(std::sqrt(cu * cu * cu * cu + hbm * hbm * hbm * hbm));
+    return std::sqrt(std::sqrt(cu * cu * cu * cu + hbm * hbm * hbm * hbm + all_us * all_us * all_us * all_us));
 }
-double narrow_us(NarrowForm f, int R, int n_used, int N, int K, int act, int cus) {
-    const int cols = 32 * f.nt / (act == MOE_ACT_SWIGLU ? 2 : 1);
-    const int tiles = spread_tiles_m(R, 32 * f.mt, n_used, 2) * ((N + cols - 1) / cols);
-    return stream_us((tiles + cus - 1) / cus, 64.0 * (f.mt + f.nt) * K, 74.4, 3.06, n_used, N, K, act, 4.2);
+double narrow_us(const NarrowCost& c, int tiles_m, int n_used, int N, int K, int act, int cus) {
+    const int cols = 32 * c.form.nt / (act == MOE_ACT_SWIGLU ? 2 : 1);
+    const int tiles = tiles_m * ((N + cols - 1) / cols);
+    const double bytes = 64.0 * (c.form.mt + c.form.nt) * K;
+    return c.start + stream_us((tiles + cus - 1) / cus, bytes, c.gb_s, c.per_round, n_used, N, K, act, c.tb_s, tiles * bytes * 1e-6 / c.all_tb_s);
 }
 double skinny_us(int R, int n_used, int N, int K, int act, int cus) {
     const int rows = skinny_tile_rows(R), cols = SBN / (act == MOE_ACT_SWIGLU ? 2 : 1), ns = K / SKW;
     const int tiles = spread_tiles_m(R, rows, n_used, 2) * ((N + cols - 1) / cols);
     const SkinnyPlan p = plan_skinny(tiles, cus, ns);
-    return stream_us((tiles * p.parts + cus - 1) / cus, (rows + SBN) * 2.0 * SKW * p.per, 37.55, -0.29, n_used, N, K, act, 6.14) +
-           (p.parts > 1 ? 2.0 + 0.73 * p.parts : 0.0);
+    const double rounds = (tiles * p.parts + cus - 1) / cus, bytes = (rows + SBN) * 2.0 * SKW * p.per;
+    if (rows == 32) return 6.65 + stream_us(rounds, bytes, 69.0, -0.38, n_used, N, K, act, 5.76) + (p.parts > 1 ? 1.64 + 0.26 * p.parts : 0.0);
+    return 7.42 + stream_us(rounds, bytes, 49.3, -1.37, n_used, N, K, act, 5.21) + (p.parts > 1 ? 2.17 + 0.48 * p.parts : 0.0);
 }
-NarrowForm narrow_form(int R, int n_used, int N, int K, int act, int cus, double other_us) {
+// other_us(way): time of the kernel that would run otherwise; tiles_m(mt, way): tiles of 32 mt rows
+template <typename Other, typename Tiles>
+NarrowForm narrow_form(int n_used, int N, int K, int act, int cus, double gain, Other other_us, Tiles tiles_m) {
     NarrowForm best{0, 0};
-    double best_us = 0.9 * other_us;
-    for (const NarrowForm f : kNarrowForms) {
-        const double us = narrow_us(f, R, n_used, N, K, act, cus);
-        if (us < best_us) { best = f; best_us = us; }
+    double best_q = 1.0;
+    const int likely = n_used <= 1 ? 0 : 2;
+    const double other = other_us(likely);
+    for (const NarrowCost& c : kNarrowForms) {
+        const double q = narrow_us(c, tiles_m(c.form.mt, likely), n_used, N, K, act, cus) / other;
+        if (q < best_q) { best = c.form; best_q = q; }
+    }
+    if (best.mt == 0 || best_q < 0.7) return best;
+    if (n_used <= 1) return best_q < gain ? best : NarrowForm{0, 0};
+    double others[5];
+    for (int way = 0; way < 5; ++way) others[way] = other_us(way);
+    best = NarrowForm{0, 0};
+    best_q = gain;
+    for (const NarrowCost& c : kNarrowForms) {
+        double q = 0.0;
+        for (int way = 0; way < 5; ++way) q += 0.2 * narrow_us(c, tiles_m(c.form.mt, way), n_used, N, K, act, cus) / others[way];
+        if (q < best_q) { best = c.form; best_q = q; }
     }
     return best;
 }
 // both GEMMs of a share that would take `rows` rows per tile otherwise (of the streaming kernels up to kSkinnyRows rows)
 void take_narrow_forms(int R, int n_used, int H, int F, int act, int cus, const int (&rows)[2], NarrowForm (&form)[2]) {
+    int counted[5][5] = {};                              // [mt][way]
+    auto tiles_m = [&](int mt, int way) {
+        int& t = counted[mt][way];
+        if (t == 0) t = spread_tiles_m(R, 32 * mt, n_used, way);
+        return t;
+    };
     for (int g = 0; g < 2; ++g) {
         const int N = g == 0 ? F : H, K = g == 0 ? H : F, a = g == 0 ? act : -1;
-        double other;
-        if (R <= kSkinnyRows) {
-            other = skinny_us(R, n_used, N, K, a, cus);
-        } else {
-            const TileShape t = rows[g] == kShapeRows[TS_128] ? TS_128 : rows[g] == kShapeRows[TS_192] ? TS_192 : TS_256;
-            other = played_us(t, spread_tiles_m(R, rows[g], n_used, 2), R, n_used, N, K, a, cus);
-        }
-        form[g] = narrow_form(R, n_used, N, K, a, cus, other);
+        const TileShape t = rows[g] == kShapeRows[TS_128] ? TS_128 : rows[g] == kShapeRows[TS_192] ? TS_192 : TS_256;
+        auto other = [&](int way) {
+            if (R <= kSkinnyRows) return skinny_us(R, n_used, N, K, a, cus);
+            return std::max(1.0, 1.117 * played_us(t, t == TS_128 ? tiles_m(4, way) : spread_tiles_m(R, rows[g], n_used, way), R, n_used, N, K, a, cus) - 2.97);
+        };
+        form[g] = narrow_form(n_used, N, K, a, cus, R <= kSkinnyRows ? kNarrowGainStreaming : kNarrowGain, other, tiles_m);
     }
 }
 // the same, unless their maps do not fit; rows: then theirs

@@ -474,6 +474,28 @@ def test_only_shares_of_few_fp32_tiles_are_spared_the_tile_map():
     assert needs_map(9000, 8, 8, 64, 320, 2, 256) == 1 and needs_map(6000, 8, 8, 64, 320, 2, 256) == 0      # SwiGLU: 32 columns per tile
 
 
+def test_narrow_tiles_are_taken_where_they_were_measured_faster():
+    """GEMMs whose narrow tiles took longer than the kernel beside them (us, weights from cold memory) and some that gained."""
+    import ctypes as C
+    from paper_2410_17043_amd import _lib
+    got = (C.c_int32 * 2)()
+
+    def forms(R, n_used, nseg, Hd, F, act):
+        assert _lib.load().moe_selfcheck_narrow(R, n_used, nseg, Hd, F, act, 256, got) == 0
+        return list(got)
+    # rows evenly, by chance or by popularity over the experts; what the narrow tiles took: R, experts, segments, H, F, activation, GEMM
+    for R, n, nseg, Hd, F, act, g in ((938, 14, 33, 640, 9984, 0, 2),         # 71 -> 93
+                                      (1461, 16, 16, 256, 13568, 0, 2),       # 52 -> 75
+                                      (1655, 14, 33, 3584, 256, 2, 2),        # 19 -> 29
+                                      (964, 8, 8, 3200, 2560, 1, 2),          # 46 -> 55
+                                      (1142, 11, 11, 2176, 1280, 2, 2),       # 26 -> 31
+                                      (629, 16, 64, 2048, 2048, 0, 1),        # 40 -> 44
+                                      (811, 15, 15, 1024, 6400, 0, 2)):       # 67 -> 81
+        assert forms(R, n, nseg, Hd, F, act)[g - 1] == 0, (R, n, Hd, F)
+    for R, n, nseg, Hd, F, act in ((403, 4, 64, 2048, 1408, 2), (64, 1, 1, 2048, 2816, 2), (108, 1, 2, 2048, 5632, 0), (139, 4, 4, 2816, 4096, 0)):
+        assert all(forms(R, n, nseg, Hd, F, act)), (R, n, Hd, F)              # 1.3 to 1.9 times faster
+
+
 def test_a_block_walks_through_a_bounded_run_of_tiles():
     """Every tile and piece is taken once, and no block holds its CU for more than 210 us or one tile: what another stream
     has queued gets in between blocks."""
