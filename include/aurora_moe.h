@@ -290,6 +290,10 @@ int moe_selfcheck_skinny_plan(int32_t total, int32_t ncu, int32_t ns);
  * checks that the rows fit a wave's loads, that every slot has a lane and that the pieces cover the row. */
 int moe_selfcheck_row_geometry(int32_t row16, int32_t k, int32_t* out3);
 
+/* 1 where the combine of T tokens with k rows of row16 16-byte units each takes a wave per token and piece of its rows, 0
+ * where it takes a wave per token, or a negative moe_status. */
+int moe_selfcheck_combine_pieces(int32_t T, int32_t k, int32_t row16);
+
 /* Tile map of the FFN for a segment list (HOST seg_offset [nseg+1], seg_expert [nseg]; R rows, tiles of bm
  * rows, n_local experts; gather = chain the segments of an expert into full tiles): runs the steps of the
  * device kernel on the host and checks that every row of every non-empty segment of a known expert lies in

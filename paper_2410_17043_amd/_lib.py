@@ -67,6 +67,7 @@ SIGNATURES = {
     "moe_selfcheck_f32_map": (C.c_int, [_i32] * 7),
     "moe_selfcheck_walk": (C.c_int, [_i32] * 6),
     "moe_selfcheck_skinny_plan": (C.c_int, [_i32, _i32, _i32]),
+    "moe_selfcheck_combine_pieces": (C.c_int, [_i32] * 3),
     "moe_selfcheck_row_geometry": (C.c_int, [_i32, _i32, _pi32]),
     "moe_selfcheck_tile_map": (C.c_int, [_pi32, _pi32, _i32, _i32, _i32, _i32, _i32]),
     "aurora_order": (C.c_int, [_i32, C.POINTER(C.c_int64), C.POINTER(C.c_double), C.POINTER(aurora_schedule)]),

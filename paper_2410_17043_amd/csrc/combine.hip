@@ -163,9 +163,15 @@ constexpr size_t kCombineCacheableBytes = (size_t)128 << 20;
 // A wave per token and piece of its rows up to this many tokens, or bytes read and written: the walk of one wave through its
 // rows is then what takes the time (us, bf16, H = 4096: 16 tokens, k = 2 4.9 -> 2.2; 64, k = 6 7.7 -> 2.5; 1024, k = 2 7.6 ->
 // 5.2; H = 1024, k = 1, 4096 tokens 4.1 -> 3.8).  Beyond, the memory system prefers waves that keep reading and writing (8192
-// tokens, k = 2, H = 4096: 39 against 44).
+// tokens, k = 2, H = 4096: 39 against 44).  Rows of more than 96 KB are many pieces: up to half as many tokens (fp32, 1024
+// tokens, rows from cold memory: H = 24576, k = 1, 2 and 6 1.06, 1.04 and 1.03 times faster, H = 32768 0.97, 0.96 and 0.97; 512 tokens of those 1.16,
+// 1.16 and 1.10; bf16 up to 64 KB 1.08 to 5.0).
 constexpr int kFewTokens = 1024;
 constexpr size_t kFewBytes = (size_t)16 << 20;
+constexpr int kLongRow16 = 96 * 1024 / 16;
+bool few_tokens(int T, int k, int row16) {
+    return T <= (row16 > kLongRow16 ? kFewTokens / 2 : kFewTokens) || (size_t)T * (k + 1) * row16 * 16 <= kFewBytes;
+}
 
 template <int DT, bool STREAM>
 int launch_combine(const moe_ctx* c, const void* ret, const int32_t* s2r, const float* w, const void* shared, void* y,
@@ -177,7 +183,7 @@ int launch_combine(const moe_ctx* c, const void* ret, const int32_t* s2r, const 
     const u32x4* sh = reinterpret_cast<const u32x4*>(shared);
     u32x4* yo = reinterpret_cast<u32x4*>(y);
     const dim3 pieces((s.T + 3) / 4, (row16 + 63) / 64);
-    const bool few = s.T <= kFewTokens || (size_t)s.T * (s.k + 1) * row16 * 16 <= kFewBytes;
+    const bool few = few_tokens(s.T, s.k, row16);
 #define MOE_COMBINE(K)                                                                                                              \
     if (few) hipLaunchKernelGGL((combine_pieces_kernel<DT, K, STREAM>), pieces, dim3(256), 0, st, r, s2r, w, sh, s.T, s.k, row16, yo); \
     else hipLaunchKernelGGL((combine_kernel<DT, K, STREAM>), grid, dim3(256), 0, st, r, s2r, w, sh, s.T, row16, yo)
@@ -200,6 +206,11 @@ int launch_combine_dt(const moe_ctx* c, const void* ret, const int32_t* s2r, con
 }
 
 }  // namespace
+
+extern "C" int moe_selfcheck_combine_pieces(int32_t T, int32_t k, int32_t row16) {
+    if (T < 1 || k < 1 || k > MOE_MAX_K || row16 < 1) return moe_set_error(MOE_EINVAL, "moe_selfcheck_combine_pieces: bad argument");
+    return (k != 1 && k != 2 && k != 6) || few_tokens(T, k, row16) ? 1 : 0;
+}
 
 extern "C" int moe_combine(moe_ctx* ctx, const void* ret, const int32_t* slot_to_row, const float* topk_w,
                            const void* shared_out, void* y, void* stream) {

@@ -474,6 +474,17 @@ def test_only_shares_of_few_fp32_tiles_are_spared_the_tile_map():
     assert needs_map(9000, 8, 8, 64, 320, 2, 256) == 1 and needs_map(6000, 8, 8, 64, 320, 2, 256) == 0      # SwiGLU: 32 columns per tile
 
 
+def test_combine_takes_pieces_of_rows_for_few_tokens_fewer_with_long_rows():
+    """What was measured faster: up to 1024 tokens (512 with rows of more than 96 KB) or 16 MiB moved; k other than 1, 2, 6 always."""
+    from paper_2410_17043_amd import _lib
+    pieces = _lib.load().moe_selfcheck_combine_pieces
+    for k in (1, 2, 6):
+        for row16, few in ((16, 1024), (512, 1024), (6144, 1024), (6145, 512), (8192, 512)):
+            assert pieces(few, k, row16) == 1 and (row16 < 512 or pieces(few + 512, k, row16) == 0), (k, row16)
+        assert pieces(4096, k, 16) == 1
+    assert pieces(100000, 3, 8192) == 1
+
+
 def test_narrow_tiles_are_taken_where_they_were_measured_faster():
     """GEMMs whose narrow tiles took longer than the kernel beside them (us, weights from cold memory) and some that gained."""
     import ctypes as C
