@@ -25,7 +25,9 @@
  *   - Matrices are row-major.  A "slot" is a (token, choice) pair, id t*k + j.
  *   - dtype: MOE_F32 (0) = IEEE fp32 storage; MOE_BF16 (1) = bfloat16 storage.
  *     Accumulation is fp64 in the gate (indices must not depend on summation
- *     order) and fp32 elsewhere.
+ *     order) and fp32 elsewhere.  Products of fp32 operands have an error below
+ *     2^-23 (in large shares of moe_expert_ffn they are sums of products of bf16
+ *     parts that hold all 24 bits of an operand), and no result depends on other rows.
  *   - Arguments are validated before anything is launched: NULL where not
  *     allowed / non-positive sizes -> MOE_EINVAL; inconsistent sizes (k > E,
  *     limits exceeded, maps out of range, dest_order not a permutation)
@@ -275,6 +277,10 @@ int moe_selfcheck_f32_kernels(int32_t R, int32_t n_used, int32_t nseg, int32_t H
  * segment list (few tiles of 64 rows in at most 64 segments), or a negative moe_status. */
 int moe_selfcheck_f32_map(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu);
 
+/* Walk of the blocks of the fp32 kernel of 128-row tiles through tiles_m x tiles_n tiles, launched for up to max_tiles_m: checks
+ * that every tile is taken by one block.  Returns the number of tiles a block takes at most, or a negative moe_status. */
+int moe_selfcheck_f32_walk(int32_t tiles_m, int32_t max_tiles_m, int32_t tiles_n, int32_t K, int32_t ncu);
+
 /* Walk of the blocks of a bf16 FFN GEMM through tiles_m x tiles_n tiles of `rows` rows (128, 192, 256) with inner dimension
  * K on ncu compute units, launched for up to max_tiles_m: checks that every tile and piece is taken by one block, a piece
  * as its block's last.  Returns the number of tiles a block takes at most, or a negative moe_status. */
@@ -321,6 +327,9 @@ int moe_selfcheck_tile_map(const int32_t* seg_offset, const int32_t* seg_expert,
  * activations, ceil(H / 256) for the second GEMM; MOE_ESHAPE otherwise, and for fp32 or shares of at most 64 rows (other
  * kernels).  The GEMM takes the tiles that moe_expert_ffn takes if marks has room for all of them:
  * (((R + 127) / 128 + nseg) * ceil(N / 64 or 128) + 512) * 16 elements always do; with fewer it may take 256-row tiles.
+ * A share of few rows per expert, to which moe_expert_ffn may give narrow tiles (moe_selfcheck_narrow), is run with the tiles
+ * that it would take without them: there the marks are not those of the kernel that moe_expert_ffn runs, and the outputs
+ * agree with its up to the order of the sums.
  * Everything else as moe_expert_ffn. */
 int moe_diag_ffn_phases(const void* recv, int32_t R, const int32_t* seg_offset, const int32_t* seg_expert, int32_t nseg,
                         const moe_expert_w* experts, int32_t n_local, int32_t H, int32_t F, int32_t act, int32_t dtype,

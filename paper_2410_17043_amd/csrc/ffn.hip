@@ -23,7 +23,9 @@
 // tile_of_block); the tiles of a mostly empty last round are cut along K (see plan_tail).
 //
 // Shares of at most 64 rows (bf16) take a pair of weight-streaming kernels instead (gemm_bf16_skinny_kernel):
-// 32- or 64-row tiles, 256-byte bursts per weight row, the LDS ring given to loads in flight.
+// 32- or 64-row tiles, 256-byte bursts per weight row, the LDS ring given to loads in flight.  Either GEMM of a bf16 share of
+// up to 128 rows per expert, those of at most 64 rows included, takes narrow tiles where they are modelled faster
+// (gemm_bf16_narrow_kernel: 32 to 128 rows x 32 or 64 weight rows over the whole of K, see take_narrow).
 //
 // fp32 path: 128 x 128 tiles of three bf16 parts per element on the bf16 matrix cores (gemm_f32_parts_kernel); where there are
 // too few of them, 64 x 64 tiles on the fp32 matrix cores (gemm_f32_kernel).
@@ -2294,7 +2296,7 @@ int launch_bf16_shape(TileShape t, const void* A, int lda, const TileMap& m, con
 // and 400 rows 35 + 33 us against 27 + 18 for 128 x 128; at 1024 -> 4096 -> 1024 and 10199 rows the second GEMM 93
 // against 80 us for 192 x 256 (220 tiles for 256 CUs instead of 160).
 constexpr int kShapeRows[] = {TileGeom<2, 2>::BM, TileGeom<3, 4>::BM, TileGeom<4, 4>::BM};
-constexpr int kSkinnyRows = 64;                          // shares up to this many rows take the streaming kernels
+constexpr int kSkinnyRows = 64;                          // shares up to this many rows take the streaming kernels where narrow tiles do not win
 inline double estimated_tiles_m(int R, int bm, int n_used) {
     if (n_used <= 1) return (R + bm - 1) / bm;
     return std::max((double)n_used, (double)R / bm + 0.5 * n_used);
@@ -2723,6 +2725,24 @@ extern "C" int moe_selfcheck_f32_map(int32_t R, int32_t n_used, int32_t nseg, in
     if (rc != MOE_OK) return rc;
     const bool in_parts[2] = {rows2[0] == XM, rows2[1] == XM};
     return f32_needs_map(R, n_used, nseg, H, F, act, ncu, in_parts) ? 1 : 0;
+}
+
+extern "C" int moe_selfcheck_f32_walk(int32_t tiles_m, int32_t max_tiles_m, int32_t tiles_n, int32_t K, int32_t ncu) {
+    if (tiles_m < 0 || max_tiles_m < std::max(tiles_m, 1) || tiles_n < 1 || K < kXMinK || K % 4 != 0 || ncu < 1)
+        return moe_set_error(MOE_EINVAL, "moe_selfcheck_f32_walk: bad argument");
+    const int walk = parts_walk_tiles(K), total = tiles_m * tiles_n;
+    std::vector<int> seen((size_t)total, 0);
+    for (int b = 0; b < walk_blocks(max_tiles_m * tiles_n, walk, ncu); ++b) {
+        const WalkRun run = walk_run(b, ncu, walk, total);
+        int taken = 0;
+        for (int item = run.item; item < run.end; item += ncu, ++taken) {
+            if (item >= total || taken == walk) return moe_set_error(MOE_EINTERNAL, "run of block %d", b);
+            ++seen[item];
+        }
+    }
+    for (int i = 0; i < total; ++i)
+        if (seen[i] != 1) return moe_set_error(MOE_EINTERNAL, "tile %d is taken %d times", i, seen[i]);
+    return walk;
 }
 
 extern "C" int moe_selfcheck_walk(int32_t rows, int32_t tiles_m, int32_t max_tiles_m, int32_t tiles_n, int32_t K, int32_t ncu) {

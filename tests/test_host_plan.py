@@ -522,6 +522,41 @@ def test_a_block_walks_through_a_bounded_run_of_tiles():
                 assert walk(rows, tm, tm + int(r.integers(0, 70)), tn, K, ncu) == w, _lib.load().moe_last_error()
 
 
+def test_blocks_of_the_fp32_kernel_of_large_tiles_take_every_tile_once():
+    """Also with fewer tiles than the launch allows for, and with none."""
+    from paper_2410_17043_amd import _lib
+    walk = _lib.load().moe_selfcheck_f32_walk
+    r = np.random.default_rng(10)
+    for K in (128, 132, 356, 1024, 2816, 8192, 65536):
+        w = walk(1, 1, 1, K, 256)
+        assert w == 1 or (w >= 1 and w * 1.1 * (K / 32) <= 210), (K, w)
+        for _ in range(20):
+            tm, tn, ncu = int(r.integers(0, 200)), int(r.integers(1, 60)), int(r.choice([256, 256, 64, 8, 304]))
+            assert walk(tm, max(1, tm) + int(r.integers(0, 70)), tn, K, ncu) == w, _lib.load().moe_last_error()
+
+
+def test_kernels_of_a_share_are_chosen_within_the_workspace_for_every_size():
+    """Narrow tiles and the fp32 kernels over the sizes that the entry point takes: the maps fit, the forms are built, a share of
+    more rows keeps 128-row tiles where K allows them."""
+    import ctypes as C
+    from paper_2410_17043_amd import _lib
+    lib, r = _lib.load(), np.random.default_rng(12)
+    got = (C.c_int32 * 2)()
+    forms = set()
+    for _ in range(4000):
+        n = int(r.choice([1, 2, 3, 5, 8, 16, 64]))
+        R = int(np.exp(r.uniform(0, np.log(30000))))
+        nseg = int(r.choice([n, n + 1, max(n, 64), max(n, 65), max(n, 700), 1024]))
+        Hd, F = 128 * int(r.integers(1, 40)), 128 * int(r.integers(1, 112))
+        assert lib.moe_selfcheck_narrow(R, min(n, R), nseg, Hd, F, int(r.integers(0, 3)), 256, got) == 0, lib.moe_last_error()
+        assert R <= 128 * n or list(got) == [0, 0]
+        forms.update(got)
+        Hd, F = 4 * int(r.integers(1, 512)), 4 * int(r.integers(1, 1500))
+        assert lib.moe_selfcheck_f32_kernels(R, min(n, R), nseg, Hd, F, int(r.integers(0, 3)), 256, got) == 0, lib.moe_last_error()
+        assert (Hd >= 128 or got[0] == 64) and (F >= 128 or got[1] == 64)
+    assert forms == {0, 11, 12, 21, 22, 42}
+
+
 @pytest.mark.parametrize("n,hi,hetero", [(2, 9, False), (5, 3, True), (7, 40, False), (16, 200, True), (17, 5, False), (33, 1000, True)])
 def test_send_order_time_is_that_of_playing_the_order_and_no_exchange_improves_it(n, hi, hetero):
     """The hill climbing resumes recorded runs; playing the order it returns from the start gives the same time to the
