@@ -1067,21 +1067,32 @@ __device__ __forceinline__ void multiply_parts(const unsigned char* pa, const un
 __device__ __forceinline__ void multiply_exactly(const float* pa, const float* pb0, const float* pb1, int fk, int K, f32x16 (&acc)[2]) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[0][e] = acc[1][e] = 0.f;
-    // bound by the round trips of the loads: they stand under no condition (past K, a multiple of 4, the last quad again, which does
-    // not count), so that those of four steps go out at once (with one step at a time the 680 us above were 756)
-#pragma unroll 4
-    for (int k = 4 * fk; k < K + 4 * fk; k += 8) {
-        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-        const bool in = k < K;
-        const int kc = min(k, K - 4);
-        f32x4 a = *reinterpret_cast<const f32x4*>(pa + kc), b0 = *reinterpret_cast<const f32x4*>(pb0 + kc), b1 = *reinterpret_cast<const f32x4*>(pb1 + kc);
-        a = in ? a : zero;
-        b0 = in ? b0 : zero;
-        b1 = in ? b1 : zero;
+    // where few waves need it, bound by the round trips of the loads: those of four steps of 8 elements go out at once, under no
+    // condition (past K, a multiple of 4, the last quad again, which does not count).  3001 rows of 1024 -> 2816 -> 1024 with the largest
+    // floats in two rows 346 -> 327 us, without them 234; where all need it the 32-byte loads of each row count, not their latency.
+    constexpr int STEPS = 4;
+    for (int k0 = 0; k0 < K; k0 += 8 * STEPS) {
+        f32x4 a[STEPS], b0[STEPS], b1[STEPS];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(b0[v], a[v], acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(b1[v], a[v], acc[1], 0, 0, 0);
+        for (int s = 0; s < STEPS; ++s) {
+            const int kc = min(k0 + 8 * s + 4 * fk, K - 4);
+            a[s] = *reinterpret_cast<const f32x4*>(pa + kc);
+            b0[s] = *reinterpret_cast<const f32x4*>(pb0 + kc);
+            b1[s] = *reinterpret_cast<const f32x4*>(pb1 + kc);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            const bool in = k0 + 8 * s + 4 * fk < K;
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};       // in all three: 0 * a stray infinity would be a NaN
+            a[s] = in ? a[s] : zero;
+            b0[s] = in ? b0[s] : zero;
+            b1[s] = in ? b1[s] : zero;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(b0[s][v], a[s][v], acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(b1[s][v], a[s][v], acc[1], 0, 0, 0);
+            }
         }
     }
 }
