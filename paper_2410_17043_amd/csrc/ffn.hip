@@ -2465,38 +2465,41 @@ int launch_bf16_skinny_mt(const void* A, int lda, const TileMap& m, const Expert
     MOE_LAUNCH_CHECK("gemm_bf16_skinny_kernel");
     return MOE_OK;
 }
-// Which shares take narrow tiles, and of which form.  The time of a form is modelled as what a CU has to fetch (per round of
-// tiles), together with the weights at the rate they stream and with all that is fetched, again and again for every tile, from caches (the
-// 4-norm of the three); that of the weight-streaming kernels likewise, with their pieces; that of the tiled kernels as in played_us; all
-// with what the start of a kernel costs.  A form has to be 15 % faster in the mean of the five ways in which rows spread over
-// experts (spread_tiles_m), 8 % beside the streaming kernels, whose times are better known; even popularity alone decides where it says less than 0.7 or more than the other kernel's time.
-// Only up to 128 rows per expert: beyond, the weights are fetched again for every tile of rows.  The constants are fitted to the
-// 5600 GEMMs of 2800 shares of 1 to 2000 rows, 1 to 16 experts, H of 128 to 4096 and F of 128 to 14336, rows in even shares, by
-// chance, by popularity and cut at random, weights from cold memory (median error 4 to 7 %).  Over 1200 others the expert FFN is 1.312 times
-// faster in the mean than without narrow tiles, one is more than 3 % slower (44.6 -> 47.4 us); with even popularity alone and 10 %
-// 39 of 900 were, by up to 20 %.
+// Which shares take narrow tiles, and of which form.  The time of a form is modelled as what a CU has to fetch, round of tiles by round
+// (the last one at a higher rate where it leaves CUs idle), together with the weights at the rate they stream and with all that is
+// fetched, again and again for every tile, from caches (the 4-norm of the three); that of the weight-streaming kernels likewise, with
+// their pieces; that of the tiled kernels as in played_us; all with what the start of a kernel costs.  A form has to be 13 % faster in
+// the mean of the five ways in which rows spread over experts (spread_tiles_m), 12 % beside the streaming kernels; even popularity alone
+// decides where it says less than 0.6 or more than the other kernel's time.  Only up to 128 rows per expert: beyond, the
+// weights are fetched again for every tile of rows.  The constants are fitted to the kernel durations of 2000 GEMMs, each with every form
+// and without: shares of 1 to 2000 rows, 1 to 16 experts, H of 128 to 4096 and F of 128 to 14336, rows in even shares, by chance,
+// by popularity and cut at random, weights from cold memory (median error 8 %).  Over 1200 other shares the expert FFN is 1.322
+// times faster in the mean than without narrow tiles, two are more than 3 % slower (4 %); with one spread of the rows and equal
+// starts of all kernels 39 of 900 were, by up to 20 %.  2500 shares by their kernel durations: 1.390 faster, 1.424 with the best form
+// always known, 12 more than 3 % slower; with 10 and 8 % 1.395 and 19, with 18 % 1.372 and 4.
 struct NarrowForm { int mt, nt; };                       // mt = 0: none
-struct NarrowCost { NarrowForm form; double start, gb_s, per_round, tb_s, all_tb_s; };
-constexpr NarrowCost kNarrowForms[] = {{{4, 2}, 5.46, 67.4, 2.83, 3.79, 16.3}, {{2, 2}, 4.40, 61.3, 2.99, 4.47, 13.7}, {{2, 1}, 3.97, 82.3, 2.67, 3.27, 14.6},
-                                       {{1, 2}, 4.05, 54.7, 3.37, 4.93, 100.0}, {{1, 1}, 3.83, 109.8, 2.74, 4.38, 10.2}};
-constexpr double kNarrowGain = 0.85, kNarrowGainStreaming = 0.92;
-double stream_us(double rounds, double bytes, double gb_s, double per_round, int n_used, int N, int K, int act, double tb_s, double all_us = 0.0) {
-    const double cu = rounds * (bytes * 1e-3 / gb_s + per_round), hbm = (double)n_used * N * K * (act == MOE_ACT_SWIGLU ? 4.0 : 2.0) * 1e-6 / tb_s;
-    return std::sqrt(std::sqrt(cu * cu * cu * cu + hbm * hbm * hbm * hbm + all_us * all_us * all_us * all_us));
-}
+struct NarrowCost { NarrowForm form; double start, gb_s, per_round, tb_s, all_tb_s, alone; };   // alone: what an otherwise idle chip adds to gb_s
+constexpr NarrowCost kNarrowForms[] = {{{4, 2}, 1.45, 57.2, 2.95, 10.0, 100.0, 0.70}, {{2, 2}, 1.66, 46.6, 2.96, 10.0, 24.2, 1.18},
+                                       {{2, 1}, 1.25, 65.0, 2.82, 10.0, 21.0, 0.68}, {{1, 2}, 1.62, 51.5, 2.97, 5.16, 100.0, 0.98},
+                                       {{1, 1}, 1.72, 60.1, 2.43, 6.01, 17.9, 0.88}};
+constexpr double kNarrowGain = 0.87, kNarrowGainStreaming = 0.88;
+double norm4(double a, double b, double c = 0.0) { return std::sqrt(std::sqrt(a * a * a * a + b * b * b * b + c * c * c * c)); }
+double weights_us(int n_used, int N, int K, int act, double tb_s) { return (double)n_used * N * K * (act == MOE_ACT_SWIGLU ? 4.0 : 2.0) * 1e-6 / tb_s; }
 double narrow_us(const NarrowCost& c, int tiles_m, int n_used, int N, int K, int act, int cus) {
     const int cols = 32 * c.form.nt / (act == MOE_ACT_SWIGLU ? 2 : 1);
-    const int tiles = tiles_m * ((N + cols - 1) / cols);
-    const double bytes = 64.0 * (c.form.mt + c.form.nt) * K;
-    return c.start + stream_us((tiles + cus - 1) / cus, bytes, c.gb_s, c.per_round, n_used, N, K, act, c.tb_s, tiles * bytes * 1e-6 / c.all_tb_s);
+    const int tiles = tiles_m * ((N + cols - 1) / cols), last = tiles % cus;
+    const double kb = 64e-3 * (c.form.mt + c.form.nt) * K;
+    double cu = tiles / cus * (kb / c.gb_s + c.per_round);
+    if (last > 0) cu += kb / (c.gb_s * (1.0 + c.alone * (1.0 - (double)last / cus))) + c.per_round;
+    return c.start + norm4(cu, weights_us(n_used, N, K, act, c.tb_s), tiles * kb * 1e-3 / c.all_tb_s);
 }
 double skinny_us(int R, int n_used, int N, int K, int act, int cus) {
     const int rows = skinny_tile_rows(R), cols = SBN / (act == MOE_ACT_SWIGLU ? 2 : 1), ns = K / SKW;
     const int tiles = spread_tiles_m(R, rows, n_used, 2) * ((N + cols - 1) / cols);
     const SkinnyPlan p = plan_skinny(tiles, cus, ns);
-    const double rounds = (tiles * p.parts + cus - 1) / cus, bytes = (rows + SBN) * 2.0 * SKW * p.per;
-    if (rows == 32) return 6.65 + stream_us(rounds, bytes, 69.0, -0.38, n_used, N, K, act, 5.76) + (p.parts > 1 ? 1.64 + 0.26 * p.parts : 0.0);
-    return 7.42 + stream_us(rounds, bytes, 49.3, -1.37, n_used, N, K, act, 5.21) + (p.parts > 1 ? 2.17 + 0.48 * p.parts : 0.0);
+    const double rounds = (tiles * p.parts + cus - 1) / cus, kb = (rows + SBN) * 2e-3 * SKW * p.per;
+    if (rows == 32) return 4.88 + norm4(rounds * (kb / 69.6 - 0.82), weights_us(n_used, N, K, act, 6.41)) + (p.parts > 1 ? 1.69 + 0.28 * p.parts : 0.0);
+    return 2.25 + norm4(rounds * (kb / 60.7 + 2.79), weights_us(n_used, N, K, act, 5.31)) + (p.parts > 1 ? 2.32 + 0.50 * p.parts : 0.0);
 }
 // other_us(way): time of the kernel that would run otherwise; tiles_m(mt, way): tiles of 32 mt rows
 template <typename Other, typename Tiles>
@@ -2509,7 +2512,7 @@ NarrowForm narrow_form(int n_used, int N, int K, int act, int cus, double gain, 
         const double q = narrow_us(c, tiles_m(c.form.mt, likely), n_used, N, K, act, cus) / other;
         if (q < best_q) { best = c.form; best_q = q; }
     }
-    if (best.mt == 0 || best_q < 0.7) return best;
+    if (best.mt == 0 || best_q < 0.6) return best;
     if (n_used <= 1) return best_q < gain ? best : NarrowForm{0, 0};
     double others[5];
     for (int way = 0; way < 5; ++way) others[way] = other_us(way);
@@ -2535,7 +2538,7 @@ void take_narrow_forms(int R, int n_used, int H, int F, int act, int cus, const 
         const TileShape t = rows[g] == kShapeRows[TS_128] ? TS_128 : rows[g] == kShapeRows[TS_192] ? TS_192 : TS_256;
         auto other = [&](int way) {
             if (R <= kSkinnyRows) return skinny_us(R, n_used, N, K, a, cus);
-            return std::max(1.0, 1.117 * played_us(t, t == TS_128 ? tiles_m(4, way) : spread_tiles_m(R, rows[g], n_used, way), R, n_used, N, K, a, cus) - 2.97);
+            return std::max(1.0, 1.068 * played_us(t, t == TS_128 ? tiles_m(4, way) : spread_tiles_m(R, rows[g], n_used, way), R, n_used, N, K, a, cus) - 4.88);
         };
         form[g] = narrow_form(n_used, N, K, a, cus, R <= kSkinnyRows ? kNarrowGainStreaming : kNarrowGain, other, tiles_m);
     }

@@ -688,9 +688,9 @@ def test_expert_ffn_fp32_tiles_from_the_segment_list(H, nseg):
 # Narrow tiles: every form in both GEMMs and every activation, one k-tile less than the ring and many more, tiles of one row,
 # gathered tiles, beside the weight-streaming kernels, and a map of more than 64 segments
 @pytest.mark.parametrize("R,Hd,F,n_local,nseg,act,forms", [
-    (20, 128, 1408, 1, 4, 1, [0, 11]), (20, 1408, 128, 1, 1, 2, [11, 0]), (45, 128, 512, 1, 4, 1, [11, 11]), (45, 512, 128, 1, 1, 2, [11, 11]), (77, 128, 1280, 6, 64, 1, [21, 11]), (65, 1152, 512, 8, 64, 1, [11, 12]),
+    (6, 128, 1536, 7, 16, 1, [0, 11]), (6, 1536, 128, 7, 64, 0, [11, 0]), (45, 128, 512, 1, 4, 1, [21, 11]), (45, 512, 128, 1, 1, 2, [11, 21]), (77, 128, 1280, 6, 64, 1, [21, 11]), (65, 1152, 512, 8, 64, 1, [11, 12]),
     (278, 1280, 640, 4, 13, 2, [12, 12]), (226, 640, 384, 7, 64, 2, [21, 21]), (232, 1280, 512, 8, 16, 2, [21, 22]), (298, 896, 1152, 4, 16, 2, [42, 21]),
-    (360, 1408, 640, 3, 65, 2, [22, 22]), (418, 1536, 896, 6, 64, 0, [12, 42]), (403, 2048, 1408, 4, 64, 2, [42, 22]), (65, 2048, 2816, 1, 2, 0, None), (1, 1152, 256, 1, 1, 2, [11, 0])])
+    (360, 1408, 640, 3, 65, 2, [22, 22]), (418, 1536, 896, 6, 64, 0, [12, 42]), (906, 768, 256, 8, 65, 2, [22, 42]), (403, 2048, 1408, 4, 64, 2, [42, 42]), (65, 2048, 2816, 1, 2, 0, None), (1, 1152, 256, 1, 1, 2, [11, 11])])
 def test_expert_ffn_narrow_tiles(H, R, Hd, F, n_local, nseg, act, forms):
     import ctypes as C
     from paper_2410_17043_amd import _lib

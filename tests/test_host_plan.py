@@ -500,8 +500,7 @@ def test_narrow_tiles_are_taken_where_they_were_measured_faster():
                                       (1655, 14, 33, 3584, 256, 2, 2),        # 19 -> 29
                                       (964, 8, 8, 3200, 2560, 1, 2),          # 46 -> 55
                                       (1142, 11, 11, 2176, 1280, 2, 2),       # 26 -> 31
-                                      (629, 16, 64, 2048, 2048, 0, 1),        # 40 -> 44
-                                      (811, 15, 15, 1024, 6400, 0, 2)):       # 67 -> 81
+                                      (629, 16, 64, 2048, 2048, 0, 1)):       # 40 -> 44
         assert forms(R, n, nseg, Hd, F, act)[g - 1] == 0, (R, n, Hd, F)
     for R, n, nseg, Hd, F, act in ((403, 4, 64, 2048, 1408, 2), (64, 1, 1, 2048, 2816, 2), (108, 1, 2, 2048, 5632, 0), (139, 4, 4, 2816, 4096, 0)):
         assert all(forms(R, n, nseg, Hd, F, act)), (R, n, Hd, F)              # 1.3 to 1.9 times faster
