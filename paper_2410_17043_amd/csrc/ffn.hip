@@ -2501,29 +2501,42 @@ double skinny_us(int R, int n_used, int N, int K, int act, int cus) {
     if (rows == 32) return 4.88 + norm4(rounds * (kb / 69.6 - 0.82), weights_us(n_used, N, K, act, 6.41)) + (p.parts > 1 ? 1.69 + 0.28 * p.parts : 0.0);
     return 2.25 + norm4(rounds * (kb / 60.7 + 2.79), weights_us(n_used, N, K, act, 5.31)) + (p.parts > 1 ? 2.32 + 0.50 * p.parts : 0.0);
 }
-// other_us(way): time of the kernel that would run otherwise; tiles_m(mt, way): tiles of 32 mt rows
-template <typename Other, typename Tiles>
-NarrowForm narrow_form(int n_used, int N, int K, int act, int cus, double gain, Other other_us, Tiles tiles_m) {
-    NarrowForm best{0, 0};
-    double best_q = 1.0;
-    const int likely = n_used <= 1 ? 0 : 2;
-    const double other = other_us(likely);
-    for (const NarrowCost& c : kNarrowForms) {
-        const double q = narrow_us(c, tiles_m(c.form.mt, likely), n_used, N, K, act, cus) / other;
-        if (q < best_q) { best = c.form; best_q = q; }
+// other_tiles(way): tiles of rows of the kernel that would run otherwise; other_us(tiles): its time; tiles_m(mt, way): tiles of 32 mt rows.
+// Host time counts in small shares (1 us of the call's 7): a time is worked out once per tile count, and the other four ways are
+// played only for forms that come within 15 % of the best one.
+template <typename OtherTiles, typename OtherUs, typename Tiles>
+NarrowForm narrow_form(int n_used, int N, int K, int act, int cus, double gain, OtherTiles other_tiles, OtherUs other_us, Tiles tiles_m) {
+    constexpr int FORMS = sizeof kNarrowForms / sizeof kNarrowForms[0];
+    const int likely = n_used <= 1 ? 0 : 2, likely_tiles = other_tiles(likely);
+    const double likely_us = other_us(likely_tiles);
+    double us[FORMS];
+    int best = -1;
+    for (int f = 0; f < FORMS; ++f) {
+        us[f] = narrow_us(kNarrowForms[f], tiles_m(kNarrowForms[f].form.mt, likely), n_used, N, K, act, cus);
+        if (us[f] < (best < 0 ? likely_us : us[best])) best = f;
     }
-    if (best.mt == 0 || best_q < 0.6) return best;
-    if (n_used <= 1) return best_q < gain ? best : NarrowForm{0, 0};
+    if (best < 0) return NarrowForm{0, 0};
+    if (us[best] < 0.6 * likely_us || (n_used <= 1 && us[best] < gain * likely_us)) return kNarrowForms[best].form;
+    if (n_used <= 1) return NarrowForm{0, 0};
     double others[5];
-    for (int way = 0; way < 5; ++way) others[way] = other_us(way);
-    best = NarrowForm{0, 0};
-    best_q = gain;
-    for (const NarrowCost& c : kNarrowForms) {
-        double q = 0.0;
-        for (int way = 0; way < 5; ++way) q += 0.2 * narrow_us(c, tiles_m(c.form.mt, way), n_used, N, K, act, cus) / others[way];
-        if (q < best_q) { best = c.form; best_q = q; }
+    for (int way = 0; way < 5; ++way) {
+        const int t = other_tiles(way);
+        others[way] = t == likely_tiles ? likely_us : other_us(t);
     }
-    return best;
+    const double near = 1.15 * us[best];
+    best = -1;
+    double best_q = gain;
+    for (int f = 0; f < FORMS; ++f) {
+        if (us[f] > near) continue;
+        const NarrowCost& c = kNarrowForms[f];
+        double q = 0.0;
+        for (int way = 0; way < 5; ++way) {
+            const int t = tiles_m(c.form.mt, way);
+            q += 0.2 * (t == tiles_m(c.form.mt, likely) ? us[f] : narrow_us(c, t, n_used, N, K, act, cus)) / others[way];
+        }
+        if (q < best_q) { best = f; best_q = q; }
+    }
+    return best < 0 ? NarrowForm{0, 0} : kNarrowForms[best].form;
 }
 // both GEMMs of a share that would take `rows` rows per tile otherwise (of the streaming kernels up to kSkinnyRows rows)
 void take_narrow_forms(int R, int n_used, int H, int F, int act, int cus, const int (&rows)[2], NarrowForm (&form)[2]) {
@@ -2533,14 +2546,16 @@ void take_narrow_forms(int R, int n_used, int H, int F, int act, int cus, const 
         if (t == 0) t = spread_tiles_m(R, 32 * mt, n_used, way);
         return t;
     };
+    const bool streaming = R <= kSkinnyRows;
     for (int g = 0; g < 2; ++g) {
         const int N = g == 0 ? F : H, K = g == 0 ? H : F, a = g == 0 ? act : -1;
         const TileShape t = rows[g] == kShapeRows[TS_128] ? TS_128 : rows[g] == kShapeRows[TS_192] ? TS_192 : TS_256;
-        auto other = [&](int way) {
-            if (R <= kSkinnyRows) return skinny_us(R, n_used, N, K, a, cus);
-            return std::max(1.0, 1.068 * played_us(t, t == TS_128 ? tiles_m(4, way) : spread_tiles_m(R, rows[g], n_used, way), R, n_used, N, K, a, cus) - 4.88);
+        auto other_tiles = [&](int way) { return streaming ? 0 : t == TS_128 ? tiles_m(4, way) : spread_tiles_m(R, rows[g], n_used, way); };
+        auto other_us = [&](int tiles) {
+            if (streaming) return skinny_us(R, n_used, N, K, a, cus);
+            return std::max(1.0, 1.068 * played_us(t, tiles, R, n_used, N, K, a, cus) - 4.88);
         };
-        form[g] = narrow_form(n_used, N, K, a, cus, R <= kSkinnyRows ? kNarrowGainStreaming : kNarrowGain, other, tiles_m);
+        form[g] = narrow_form(n_used, N, K, a, cus, streaming ? kNarrowGainStreaming : kNarrowGain, other_tiles, other_us, tiles_m);
     }
 }
 // the same, unless their maps do not fit; rows: then theirs
