@@ -312,6 +312,61 @@ def test_dispatch_alone_and_after_in_place_index_rewrite(H, cfg):
     check(idx_a)
 
 
+@pytest.mark.parametrize("T,k,E,cap", [
+    (1, 1, 2, 0), (64, 1, 64, 1), (65, 3, 17, 9), (256, 2, 64, 0), (512, 1, 3, 100),        # lists that every wave of the scatter counts
+    (171, 3, 16, 0), (100, 2, 65, 0),                                                         # one slot or one expert too many for that
+    (16385, 1, 16, 900), (8200, 2, 17, 0), (8193, 2, 64, 0), (16400, 1, 65, 0),               # counts added up by every block of the rank kernel, or not
+    (131072, 2, 64, 0), (131073, 2, 64, 5000)])                                               # 256 of its blocks, and one more
+def test_ranks_of_dispatch_alone_after_traffic_and_without_allocation(H, T, k, E, cap):
+    """All three ways to a send buffer against a stable sort on the host; some indices name no expert and have no row."""
+    P = H.P
+    cfg = small("c1_tiny_fp32", T=T, H=4, E=E, k=k, G=1)
+    r = np.random.default_rng(T + E)
+    pop = 1.0 / np.arange(1, E + 1)
+    idx = r.choice(E, size=T * k, p=pop / pop.sum()).astype(np.int32)
+    idx[r.integers(0, T * k, size=T * k // 10)] = -1
+    idx[r.integers(0, T * k, size=T * k // 10)] = E
+    e2g = (np.arange(E) * 2 // E).astype(np.int32) if E > 1 else np.zeros(1, np.int32)
+    send_order = np.concatenate([np.nonzero(e2g == d)[0] for d in (1, 0)])
+    place = np.full(E, -1)
+    place[send_order] = np.arange(E)
+    ok = (idx >= 0) & (idx < E)
+    by_place = np.argsort(np.where(ok, place[np.clip(idx, 0, E - 1)], E), kind="stable")[:ok.sum()]   # experts in send order, slots ascending
+    counts = np.bincount(idx[ok], minlength=E)
+    kept = np.minimum(counts, cap) if cap else counts
+    start, off = np.cumsum(counts[send_order]) - counts[send_order], np.concatenate([[0], np.cumsum(kept[send_order])])
+    slot_to_row = np.full(T * k, -1)
+    for p in range(E):
+        rows = by_place[start[p]:start[p] + kept[send_order[p]]]
+        slot_to_row[rows] = off[p] + np.arange(len(rows))
+    shape = (T, 4, E, k, 2, "fp32", 0, cap)
+    x = torch.arange(T * 4, dtype=torch.float32, device=H.DEV).reshape(T, 4)
+    di = torch.from_numpy(idx.reshape(T, k)).to(H.DEV)
+    i32 = lambda n: torch.full((n,), -7, dtype=torch.int32, device=H.DEV)
+    for way in ("alone", "traffic", "noalloc"):
+        out = [torch.zeros((T * k, 4), device=H.DEV), i32(T * k), i32(T * k), i32(E + 1), i32(E)]
+        with_ctx = P.MoeCtx(*shape)
+        if way == "noalloc":
+            P.moe_dispatch_noalloc(shape, x, di, e2g, [1, 0], *out)
+        else:
+            if way == "traffic":
+                with_ctx.set_rank_reuse(True)
+                ec, dc, nd = i32(E), i32(2), i32(1)
+                P.moe_traffic(with_ctx, di, e2g, ec, dc, nd)
+            P.moe_dispatch(with_ctx, x, di, e2g, [1, 0], *out)
+        torch.cuda.synchronize()
+        if way == "traffic":
+            assert np.array_equal(H.host(ec), kept) and int(nd.item()) == counts.sum() - kept.sum()
+            assert np.array_equal(H.host(dc), [kept[e2g == d].sum() for d in (0, 1)])
+        send_buf, s2r, r2s, seg_off, seg_exp = [H.host(t) for t in out]
+        assert np.array_equal(seg_off, off) and np.array_equal(seg_exp, send_order), way
+        assert np.array_equal(s2r, slot_to_row), way
+        has = np.nonzero(slot_to_row >= 0)[0]
+        assert np.array_equal(r2s[slot_to_row[has]], has) and np.all(r2s[off[-1]:] == -7), way
+        assert np.array_equal(send_buf[slot_to_row[has], 0], 4.0 * (has // k)), way
+        with_ctx.close()
+
+
 CHUNK_CASES = [small("c2_mixtral", T=300, H=264), small("c3_switch", T=700, H=128), small("c5_finegrained", T=260, H=64),
                small("c3_switch", T=40, H=64),                 # most experts get no token at all
                small("c1_tiny_fp32", T=37, H=100, E=5, k=3, G=5), small("c5_finegrained", T=3000, H=64, E=160, k=9, G=16),
