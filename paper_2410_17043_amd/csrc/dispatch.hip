@@ -8,10 +8,10 @@
 // traffic call on the same indices came directly before):
 //   every slot gets its rank among the slots of its expert, in slot order, plus the
 //   per-expert totals.  Up to 16384 slots this is ONE block of 16 waves (a launch costs
-//   more than the whole count at that size); beyond, three kernels:
+//   more than the whole count at that size); beyond, two kernels:
 //     count_kernel   per block of 1024 consecutive slots: slots per expert (wave ballots)
-//     scan_kernel    one block: exclusive prefix over blocks per expert
-//     rank_kernel    the same ballots again: block prefix + rank inside the block
+//     rank_kernel    adds up the counts of the blocks before its own, then the same ballots again
+//   (three, with scan_kernel for the prefix over the blocks, where that would read too much).
 //   The capacity rule, the traffic row and the drop count follow from the totals.
 //
 // Scatter (moe_dispatch): one kernel.  Every wave first turns the per-expert totals into segment
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256) void count_kernel(const int32_t* __restrict__ 
 // Traffic row, drop count and per-expert kept counts from the raw totals.  Thread e < E adds its expert's kept
 // count to its destination and its dropped slots to the drop count with LDS atomics (integer sums: the result
 // does not depend on their order); a loop over the experts in one thread per destination cost 6 us at 64 experts.
-// Called by all threads of a block of at least max(E, G + 1) threads.
+// Called by all threads of a block of at least max(E, G + 1) threads; raw is in place for all of them.
 __device__ __forceinline__ void traffic_outputs(const int* raw, int* kept, int E, int G, int capacity, const SegMap& map,
                                                 int32_t* __restrict__ expert_count, int32_t* __restrict__ dest_count,
                                                 int32_t* __restrict__ n_dropped) {
@@ -151,15 +151,53 @@ __global__ __launch_bounds__(256) void scan_kernel(int32_t* __restrict__ block_h
     traffic_outputs(raw, kept, E, G, capacity, map, expert_count, dest_count, n_dropped);
 }
 
+// What the counts of all blocks add up to, in front of this block and in all: block_hist as count_kernel left it, PARTS threads
+// per expert (256 / PARTS experts), each with every PARTS-th block.
+struct BlockSums { int before, all; };
+template <int PARTS>
+__device__ __forceinline__ BlockSums sum_block_hist(const int32_t* __restrict__ block_hist, int n_blocks, int E, int (*part)[256]) {
+    const int e = threadIdx.x % (256 / PARTS), p = threadIdx.x / (256 / PARTS), es = min(e, E - 1);
+    BlockSums s = {0, 0};
+    for (int b0 = p; b0 < n_blocks; b0 += 8 * PARTS) {        // eight loads in flight, under no condition
+        int c[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) c[u] = block_hist[(size_t)min(b0 + u * PARTS, n_blocks - 1) * E + es];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int b = b0 + u * PARTS;
+            if (b < n_blocks) s.all += c[u];
+            if (b < (int)blockIdx.x) s.before += c[u];
+        }
+    }
+    part[0][threadIdx.x] = s.before;
+    part[1][threadIdx.x] = s.all;
+    __syncthreads();
+    s = BlockSums{0, 0};
+#pragma unroll
+    for (int q = 0; q < PARTS; ++q) {
+        s.before += part[0][q * (256 / PARTS) + e];
+        s.all += part[1][q * (256 / PARTS) + e];
+    }
+    return s;                                                 // of expert threadIdx.x % (256 / PARTS)
+}
+
+// SCAN_PARTS > 0: block_hist holds the blocks' own counts, which every block adds up for itself (and block 0 writes the totals
+// and the traffic row): one launch less than with scan_kernel, whose prefix it holds otherwise.
+template <int SCAN_PARTS>
 __global__ __launch_bounds__(256) void rank_kernel(const int32_t* __restrict__ idx, int n_slots, int E,
-                                                   const int32_t* __restrict__ block_base,
-                                                   int32_t* __restrict__ slot_rank) {
+                                                   const int32_t* __restrict__ block_hist, int n_blocks, int G, int capacity, SegMap map,
+                                                   int32_t* __restrict__ raw_count, int32_t* __restrict__ slot_rank,
+                                                   int32_t* __restrict__ expert_count, int32_t* __restrict__ dest_count,
+                                                   int32_t* __restrict__ n_dropped) {
     extern __shared__ int cnt[];      // [16][E], turned into an exclusive prefix over chunks
+    __shared__ int part[SCAN_PARTS > 0 ? 2 : 1][256];
     int my_e[4], lane_rank[4];
     block_chunk_counts<true>(idx, n_slots, E, cnt, my_e, lane_rank);
+    BlockSums sums = {0, 0};
+    if constexpr (SCAN_PARTS > 0) sums = sum_block_hist<SCAN_PARTS>(block_hist, n_blocks, E, part);
     __syncthreads();
     for (int e = threadIdx.x; e < E; e += 256) {
-        int run = block_base[(size_t)blockIdx.x * E + e];
+        int run = SCAN_PARTS > 0 ? sums.before : block_hist[(size_t)blockIdx.x * E + e];
 #pragma unroll
         for (int c = 0; c < kChunks; ++c) {
             const int v = cnt[c * E + e];
@@ -177,6 +215,17 @@ __global__ __launch_bounds__(256) void rank_kernel(const int32_t* __restrict__ i
             const int e = my_e[r];
             slot_rank[s] = (e >= 0 && e < E) ? cnt[(wave * 4 + r) * E + e] + lane_rank[r] : -1;
         }
+    }
+    if constexpr (SCAN_PARTS > 0) {
+        if (blockIdx.x != 0) return;
+        __syncthreads();                                      // part has been read
+        int *raw = part[0], *kept = part[1];
+        if ((int)threadIdx.x < E) {
+            raw[threadIdx.x] = sums.all;
+            raw_count[threadIdx.x] = sums.all;
+        }
+        __syncthreads();
+        traffic_outputs(raw, kept, E, G, capacity, map, expert_count, dest_count, n_dropped);
     }
 }
 
@@ -691,6 +740,11 @@ struct RankScratch {
     int32_t* slot_rank;    // [n_slots]
 };
 
+// What a block of rank_kernel adds up for itself: up to 1024 blocks' counts and 64 Ki of them.  Traffic call, three launches -> two:
+// 98304 slots of 64 experts 12.3 -> 8.0 us, 262144 18.7 -> 9.9, 1048576 (1024 blocks) 52.1 -> 28.2; of 8 experts 13.3 -> 8.3,
+// 18.9 -> 8.6, 50.5 -> 14.3.  Beyond, the counts would be read too many times over.
+constexpr int kScanBlocks = 1024, kScanCounts = 64 * 1024;
+
 // Rank pass; the three count outputs may be NULL.
 int launch_rank_pass(const moe_shape& s, const RankScratch& sc, const int32_t* idx, const SegMap& map, int32_t* expert_count,
                      int32_t* dest_count, int32_t* n_dropped, hipStream_t st) {
@@ -704,11 +758,20 @@ int launch_rank_pass(const moe_shape& s, const RankScratch& sc, const int32_t* i
         const size_t lds = (size_t)kChunks * s.E * sizeof(int);
         hipLaunchKernelGGL(count_kernel, dim3(n_blocks), dim3(256), lds, st, idx, n_slots, s.E, sc.block_hist);
         MOE_LAUNCH_CHECK("count_kernel");
-        hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(256), 0, st, sc.block_hist, n_blocks, s.E, s.G, s.capacity, map,
-                           sc.raw_count, expert_count, dest_count, n_dropped);
-        MOE_LAUNCH_CHECK("scan_kernel");
-        hipLaunchKernelGGL(rank_kernel, dim3(n_blocks), dim3(256), lds, st, idx, n_slots, s.E, sc.block_hist,
-                           sc.slot_rank);
+#define MOE_RANK(PARTS)                                                                                                    \
+    hipLaunchKernelGGL(rank_kernel<PARTS>, dim3(n_blocks), dim3(256), lds, st, idx, n_slots, s.E, sc.block_hist, n_blocks, s.G, \
+                       s.capacity, map, sc.raw_count, sc.slot_rank, expert_count, dest_count, n_dropped)
+        if (n_blocks <= kScanBlocks && n_blocks * s.E <= kScanCounts) {
+            if (s.E <= 16) MOE_RANK(16);
+            else if (s.E <= 64) MOE_RANK(4);
+            else MOE_RANK(1);
+        } else {
+            hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(256), 0, st, sc.block_hist, n_blocks, s.E, s.G, s.capacity, map,
+                               sc.raw_count, expert_count, dest_count, n_dropped);
+            MOE_LAUNCH_CHECK("scan_kernel");
+            MOE_RANK(0);
+        }
+#undef MOE_RANK
         MOE_LAUNCH_CHECK("rank_kernel");
     }
     return MOE_OK;
