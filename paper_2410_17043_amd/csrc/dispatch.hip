@@ -553,7 +553,7 @@ __global__ __launch_bounds__(256) void scatter_kernel(const u32x4* __restrict__ 
 constexpr int kMaxPlanChunks = 4096;
 constexpr int kMaxChunks = kMaxPlanChunks + MOE_MAX_G;      // plus one left-over chunk per destination
 constexpr int kLayoutThreads = 1024;
-constexpr int kChunksPerThread = (kMaxChunks + kLayoutThreads - 1) / kLayoutThreads;
+constexpr int kMaxChunksPerThread = (kMaxChunks + kLayoutThreads - 1) / kLayoutThreads;
 
 struct ChunkTables {                  // device pointers
     int nc;                           // chunks in all (plan + G left-over)
@@ -592,6 +592,10 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* excl_out, int* w
     return total;
 }
 
+// CPT: chunks per thread (CPT * 1024 >= tb.nc).  One block, bound by the round trips to memory behind each other: the plan's
+// entries are loaded together with the counts, the second pass finds them in registers, and a plan of up to 1024 chunks
+// has one per thread (five per thread, loaded one after the other in both passes: 12.5 us for 16 GPUs and 64 experts; 4.8 so).
+template <int CPT>
 __global__ __launch_bounds__(kLayoutThreads) void chunk_layout_kernel(ChunkTables tb, const int32_t* __restrict__ raw_count,
                                                                       int E, int G, int capacity, SegMap map,
                                                                       int32_t* __restrict__ chunk_offset,
@@ -601,6 +605,16 @@ __global__ __launch_bounds__(kLayoutThreads) void chunk_layout_kernel(ChunkTable
     __shared__ int kept[MOE_MAX_E], first[MOE_MAX_E], dest_cnt[MOE_MAX_G], wave_tot[kLayoutThreads / 64];
     __shared__ int d_exp[MOE_MAX_E], d_beg[MOE_MAX_G + 1];    // the plan's tables (which expert lives where), in LDS
     const int tid = threadIdx.x;
+    // thread t owns chunks [t * CPT, (t + 1) * CPT)
+    const int c0 = tid * CPT;
+    int dest[CPT], lo[CPT], hi[CPT];
+#pragma unroll
+    for (int u = 0; u < CPT; ++u) {                           // under no condition: past the end the last chunk again, which does not count
+        const int c = min(c0 + u, tb.nc - 1);
+        dest[u] = tb.c_dest[c];
+        lo[u] = tb.c_cumlo[c];
+        hi[u] = tb.c_cumhi[c];
+    }
     if (tid < E) {
         const int c = raw_count[tid];
         kept[tid] = (capacity > 0 && c > capacity) ? capacity : c;
@@ -619,50 +633,44 @@ __global__ __launch_bounds__(kLayoutThreads) void chunk_layout_kernel(ChunkTable
     }
     __syncthreads();
     if (tid < E) tb.expert_first[tid] = first[tid];
-    // thread t owns chunks [t * CPT, (t + 1) * CPT): sizes, then the block-wide prefix
-    const int c0 = tid * kChunksPerThread;
-    int size[kChunksPerThread], pieces[kChunksPerThread], sum = 0, psum = 0;
+    // sizes, then the block-wide prefix
+    int pieces[CPT], sum = 0, psum = 0;
 #pragma unroll
-    for (int u = 0; u < kChunksPerThread; ++u) {
-        const int c = c0 + u;
-        size[u] = 0; pieces[u] = 0;
-        if (c < tb.nc) {
-            const int d = tb.c_dest[c];
-            if (d >= 0) {
-                const int lo = min(tb.c_cumlo[c], dest_cnt[d]), hi = min(tb.c_cumhi[c], dest_cnt[d]);
-                size[u] = hi - lo;
-                if (hi > lo)
-                    for (int i = d_beg[d]; i < d_beg[d + 1]; ++i) {   // experts of d whose slots meet [lo, hi)
-                        const int e = d_exp[i];
-                        if (kept[e] > 0 && first[e] < hi && first[e] + kept[e] > lo) ++pieces[u];
-                    }
+    for (int u = 0; u < CPT; ++u) {
+        const int d = c0 + u < tb.nc ? dest[u] : -1;
+        const int rows = d >= 0 ? dest_cnt[d] : 0;
+        lo[u] = min(lo[u], rows);
+        hi[u] = d >= 0 ? min(hi[u], rows) : lo[u];            // the chunk is [lo, hi) of its destination's sequence
+        pieces[u] = 0;
+        if (hi[u] > lo[u])
+            for (int i = d_beg[d]; i < d_beg[d + 1]; ++i) {   // experts of d whose slots meet [lo, hi)
+                const int e = d_exp[i];
+                if (kept[e] > 0 && first[e] < hi[u] && first[e] + kept[e] > lo[u]) ++pieces[u];
             }
-        }
-        sum += size[u];
+        sum += hi[u] - lo[u];
         psum += pieces[u];
     }
     int row0, piece0;
     const int total = block_exclusive_scan(sum, &row0, wave_tot);
     const int total_pieces = block_exclusive_scan(psum, &piece0, wave_tot);
 #pragma unroll
-    for (int u = 0; u < kChunksPerThread; ++u) {
+    for (int u = 0; u < CPT; ++u) {
         const int c = c0 + u;
         if (c < tb.nc) {
             tb.c_row0[c] = row0;
             chunk_offset[c] = row0;
-            if (size[u] > 0) {
-                const int d = tb.c_dest[c];
-                const int lo = min(tb.c_cumlo[c], dest_cnt[d]), hi = lo + size[u];
+            if (hi[u] > lo[u]) {
+                const int d = dest[u];
                 for (int i = d_beg[d]; i < d_beg[d + 1]; ++i) {
                     const int e = d_exp[i];
-                    if (kept[e] > 0 && first[e] < hi && first[e] + kept[e] > lo) {
-                        piece_offset[piece0] = row0 + max(first[e], lo) - lo;
+                    if (kept[e] > 0 && first[e] < hi[u] && first[e] + kept[e] > lo[u]) {
+                        piece_offset[piece0] = row0 + max(first[e], lo[u]) - lo[u];
                         piece_expert[piece0] = e;
                         ++piece0;
                     }
                 }
             }
-            row0 += size[u];
+            row0 += hi[u] - lo[u];
         }
     }
     if (tid == 0) {
@@ -1034,8 +1042,12 @@ extern "C" int moe_dispatch_chunks(moe_ctx* ctx, const moe_chunk_plan* plan, con
         int rc = launch_rank_pass(s, scratch_of(ctx), topk_idx, plan->map, nullptr, nullptr, nullptr, st);
         if (rc != MOE_OK) return rc;
     }
-    hipLaunchKernelGGL(chunk_layout_kernel, dim3(1), dim3(kLayoutThreads), 0, st, plan->tb, ctx->raw_count, s.E, s.G,
-                       s.capacity, plan->map, chunk_offset, piece_offset, piece_expert, n_pieces);
+#define MOE_LAYOUT(CPT)                                                                                                     \
+    hipLaunchKernelGGL(chunk_layout_kernel<CPT>, dim3(1), dim3(kLayoutThreads), 0, st, plan->tb, ctx->raw_count, s.E, s.G, \
+                       s.capacity, plan->map, chunk_offset, piece_offset, piece_expert, n_pieces)
+    if (plan->tb.nc <= kLayoutThreads) MOE_LAYOUT(1);
+    else MOE_LAYOUT(kMaxChunksPerThread);
+#undef MOE_LAYOUT
     MOE_LAUNCH_CHECK("chunk_layout_kernel");
     const int row16 = (int)((int64_t)s.H * elem_size(s.dtype) / 16);
     const RowGeom g = row_geometry(row16, s.k);
