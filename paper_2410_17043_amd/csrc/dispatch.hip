@@ -7,7 +7,7 @@
 // Rank pass (moe_traffic; moe_dispatch runs it too unless the caller has switched rank reuse on and the
 // traffic call on the same indices came directly before):
 //   every slot gets its rank among the slots of its expert, in slot order, plus the
-//   per-expert totals.  Up to 16384 slots this is ONE block of 16 waves (a launch costs
+//   per-expert totals.  Up to 8192 slots this is ONE block of 16 waves (a launch costs
 //   more than the whole count at that size); beyond, two kernels:
 //     count_kernel   per block of 1024 consecutive slots: slots per expert (wave ballots)
 //     rank_kernel    adds up the counts of the blocks before its own, then the same ballots again
@@ -35,12 +35,13 @@ struct SegMap {                       // built on the host from expert_to_gpu an
 
 constexpr int kChunks = MOE_SLOTS_PER_BLOCK / 64;   // 16 chunks of 64 slots per block, in slot order
 
-// Lanes of the wave whose expert equals this lane's (0 <= e < 256; garbage for e < 0): the lanes that agree
+// Lanes of the wave whose expert equals this lane's (0 <= e < 2^BITS; garbage for e < 0): the lanes that agree
 // on every bit of e.
+template <int BITS = 8>                               // MOE_MAX_E = 256 experts: eight bits
 __device__ __forceinline__ unsigned long long same_expert_lanes(int e) {
     unsigned long long peers = __ballot(e >= 0);
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {                     // MOE_MAX_E = 256 experts: eight bits
+    for (int b = 0; b < BITS; ++b) {
         const unsigned long long mb = __ballot((e >> b) & 1);
         peers &= ((e >> b) & 1) ? mb : ~mb;
     }
@@ -49,48 +50,38 @@ __device__ __forceinline__ unsigned long long same_expert_lanes(int e) {
 
 // cnt[chunk][e] for this block's 16 chunks; lane_rank[r] = rank of this lane's slot inside its
 // chunk among the lanes with the same expert.
-template <bool WANT_RANK>
+template <int BITS, bool WANT_RANK>
 __device__ __forceinline__ void block_chunk_counts(const int32_t* __restrict__ idx, int n_slots, int E, int* cnt,
                                                    int (&my_e)[4], int (&lane_rank)[4]) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int base = blockIdx.x * MOE_SLOTS_PER_BLOCK + wave * 256;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int s = base + r * 64 + lane;
-        my_e[r] = (s < n_slots) ? idx[s] : -1;
+        my_e[r] = idx[min(base + r * 64 + lane, n_slots - 1)];   // under no condition: the loads go out together
         lane_rank[r] = 0;
     }
     const unsigned long long lt = (1ull << lane) - 1ull;
-    if (E <= 16) {
-        for (int e = 0; e < E; ++e) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const unsigned long long m = __ballot(my_e[r] == e);
-                if (WANT_RANK && my_e[r] == e) lane_rank[r] = __popcll(m & lt);
-                if (lane == 0) cnt[(wave * 4 + r) * E + e] = __popcll(m);
-            }
-        }
-        return;
-    }
-    // many experts: nine ballots per round instead of one per expert; the first lane of every group of equal
-    // experts writes the group's size, so the table starts from zero
+    // ballots over the bits of the expert id; the first lane of every group of equal experts writes the group's size, so
+    // the table starts from zero
     for (int i = threadIdx.x; i < kChunks * E; i += 256) cnt[i] = 0;
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int e = (my_e[r] >= 0 && my_e[r] < E) ? my_e[r] : -1;
-        const unsigned long long peers = same_expert_lanes(e);
+        const int e = (base + r * 64 + lane < n_slots && my_e[r] >= 0 && my_e[r] < E) ? my_e[r] : -1;
+        my_e[r] = e;
+        const unsigned long long peers = same_expert_lanes<BITS>(e);
         const int rk = __popcll(peers & lt);
         if (WANT_RANK) lane_rank[r] = rk;
         if (e >= 0 && rk == 0) cnt[(wave * 4 + r) * E + e] = __popcll(peers);
     }
 }
 
+template <int BITS>
 __global__ __launch_bounds__(256) void count_kernel(const int32_t* __restrict__ idx, int n_slots, int E,
                                                     int32_t* __restrict__ block_hist) {
     extern __shared__ int cnt[];      // [16][E]
     int my_e[4], lane_rank[4];
-    block_chunk_counts<false>(idx, n_slots, E, cnt, my_e, lane_rank);
+    block_chunk_counts<BITS, false>(idx, n_slots, E, cnt, my_e, lane_rank);
     __syncthreads();
     for (int e = threadIdx.x; e < E; e += 256) {
         int s = 0;
@@ -183,7 +174,7 @@ __device__ __forceinline__ BlockSums sum_block_hist(const int32_t* __restrict__ 
 
 // SCAN_PARTS > 0: block_hist holds the blocks' own counts, which every block adds up for itself (and block 0 writes the totals
 // and the traffic row): one launch less than with scan_kernel, whose prefix it holds otherwise.
-template <int SCAN_PARTS>
+template <int BITS, int SCAN_PARTS>
 __global__ __launch_bounds__(256) void rank_kernel(const int32_t* __restrict__ idx, int n_slots, int E,
                                                    const int32_t* __restrict__ block_hist, int n_blocks, int G, int capacity, SegMap map,
                                                    int32_t* __restrict__ raw_count, int32_t* __restrict__ slot_rank,
@@ -192,7 +183,7 @@ __global__ __launch_bounds__(256) void rank_kernel(const int32_t* __restrict__ i
     extern __shared__ int cnt[];      // [16][E], turned into an exclusive prefix over chunks
     __shared__ int part[SCAN_PARTS > 0 ? 2 : 1][256];
     int my_e[4], lane_rank[4];
-    block_chunk_counts<true>(idx, n_slots, E, cnt, my_e, lane_rank);
+    block_chunk_counts<BITS, true>(idx, n_slots, E, cnt, my_e, lane_rank);
     BlockSums sums = {0, 0};
     if constexpr (SCAN_PARTS > 0) sums = sum_block_hist<SCAN_PARTS>(block_hist, n_blocks, E, part);
     __syncthreads();
@@ -213,7 +204,7 @@ __global__ __launch_bounds__(256) void rank_kernel(const int32_t* __restrict__ i
         const int s = base + r * 64 + lane;
         if (s < n_slots) {
             const int e = my_e[r];
-            slot_rank[s] = (e >= 0 && e < E) ? cnt[(wave * 4 + r) * E + e] + lane_rank[r] : -1;
+            slot_rank[s] = (e >= 0) ? cnt[(wave * 4 + r) * E + e] + lane_rank[r] : -1;
         }
     }
     if constexpr (SCAN_PARTS > 0) {
@@ -229,13 +220,16 @@ __global__ __launch_bounds__(256) void rank_kernel(const int32_t* __restrict__ i
     }
 }
 
-constexpr int kSmallMaxSlots = 16384;
-constexpr int kSmallRounds = kSmallMaxSlots / (16 * 64);     // rounds of 64 slots per wave
+// Traffic call of 8192 slots with one block and of 16384 with two launches of many: 5.7 and 6.1 us (16 experts), 6.4 and 6.3
+// (64), 7.2 and 7.8 (200); 16384 slots with one block take 9.2 to 12.4.
+constexpr int kSmallMaxSlots = 8192;
 
-// The whole rank pass in one block of 1024 threads.  Wave w owns the slots [w*spw, (w+1)*spw),
-// round by round.  Few experts: one ballot per (expert, round), the running count is wave-uniform.
-// Many experts: ballots over the bits of the expert id give every lane the lanes of its round with
-// the same expert; the wave's running per-expert counts sit in LDS.
+// The whole rank pass in one block of 1024 threads.  Wave w owns the slots [w*spw, (w+1)*spw), round by round (at most
+// ROUNDS).  Ballots over the BITS bits of the expert id give every lane the lanes of its round with the same expert; the
+// wave's running per-expert counts sit in LDS.  Bound by what four waves per SIMD issue: a ballot per bit and not one per expert
+// (traffic call of 4096 slots of 16 experts 8.7 -> 4.0 us, of 8 6.2 -> 4.0, 32 slots of 16 6.5 -> 2.4; 4096 of 64, whose ids
+// have two bits less than the largest, 5.5 -> 4.4).
+template <int BITS, int ROUNDS>
 __global__ __launch_bounds__(1024) void small_rank_kernel(const int32_t* __restrict__ idx, int n_slots, int E, int G,
                                                           int capacity, SegMap map, int32_t* __restrict__ raw_count,
                                                           int32_t* __restrict__ slot_rank,
@@ -248,56 +242,32 @@ __global__ __launch_bounds__(1024) void small_rank_kernel(const int32_t* __restr
     const int rounds = (n_slots + 1023) / 1024;            // per wave
     const int base = wave * rounds * 64;
     const unsigned long long lt = (1ull << lane) - 1ull;
-    int my_e[kSmallRounds], my_rank[kSmallRounds];
+    int my_e[ROUNDS], my_rank[ROUNDS];
 #pragma unroll
-    for (int r = 0; r < kSmallRounds; ++r) {               // all index loads first
-        const int s = base + r * 64 + lane;
-        int e = (r < rounds && s < n_slots) ? idx[s] : -1;
-        my_e[r] = (e < E) ? e : -1;                         // out of range: no rank
-        my_rank[r] = -1;
-    }
-    int few_cnt = 0;                                       // few experts: lane e ends up with the wave's count of expert e
-    if (E <= 16) {
-        // few experts: one ballot per (expert, round); the running count is wave-uniform
-        for (int e = 0; e < E; ++e) {
-            int cnt = 0;
-#pragma unroll
-            for (int r = 0; r < kSmallRounds; ++r) {
-                if (r < rounds) {
-                    const unsigned long long m = __ballot(my_e[r] == e);
-                    if (my_e[r] == e) my_rank[r] = cnt + __popcll(m & lt);
-                    cnt += __popcll(m);
-                }
-            }
-            if (lane == e) few_cnt = cnt;
-        }
-    } else {
-        // many experts: nine ballots per round give every lane the lanes with the same expert; the wave's
-        // running counts sit in its row of wave_cnt (only this wave touches it until the barrier below)
-        for (int i = lane; i < E; i += 64) wave_cnt[wave][i] = 0;
+    for (int r = 0; r < ROUNDS; ++r) my_e[r] = idx[min(base + r * 64 + lane, n_slots - 1)];   // all index loads first, under no condition
+    auto in_order = [] {                                   // a lane reads what other lanes of its wave have written
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    // the wave's running counts sit in its row of wave_cnt (only this wave touches it until the barrier below)
+    for (int i = lane; i < E; i += 64) wave_cnt[wave][i] = 0;
+    in_order();
 #pragma unroll
-        for (int r = 0; r < kSmallRounds; ++r) {
-            if (r < rounds) {
-                const int e = my_e[r];
-                const unsigned long long peers = same_expert_lanes(e);
-                const int rk = __popcll(peers & lt);
-                if (e >= 0) {
-                    const int before = wave_cnt[wave][e];
-                    my_rank[r] = before + rk;
-                    if (rk == 0) wave_cnt[wave][e] = before + __popcll(peers);
-                }
-                // the next round's lanes read counts that other lanes of this wave wrote in this one
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int r = 0; r < ROUNDS; ++r) {
+        my_rank[r] = -1;
+        if (r < rounds) {
+            const int e = (base + r * 64 + lane < n_slots && my_e[r] < E) ? my_e[r] : -1;   // out of range: no rank
+            my_e[r] = e;
+            const unsigned long long peers = same_expert_lanes<BITS>(e);
+            const int rk = __popcll(peers & lt);
+            if (e >= 0) {
+                const int before = wave_cnt[wave][e];
+                my_rank[r] = before + rk;
+                if (rk == 0) wave_cnt[wave][e] = before + __popcll(peers);
             }
+            in_order();
         }
-    }
-    if (E <= 16) {
-        if (lane < E) wave_cnt[wave][lane] = few_cnt;
     }
     __syncthreads();
     if (threadIdx.x < E) {                                 // exclusive scan over the 16 waves
@@ -314,7 +284,7 @@ __global__ __launch_bounds__(1024) void small_rank_kernel(const int32_t* __restr
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kSmallRounds; ++r) {
+    for (int r = 0; r < ROUNDS; ++r) {
         const int s = base + r * 64 + lane;
         if (r < rounds && s < n_slots) slot_rank[s] = (my_e[r] >= 0) ? wave_cnt[wave][my_e[r]] + my_rank[r] : -1;
     }
@@ -418,7 +388,7 @@ struct OwnRanks {
         for (int c = 0; c < kOwnRankSlots / 64; ++c) {
             if (c * 64 >= n_slots) break;                     // wave-uniform
             const int e = (c * 64 + lane < n_slots && all[c] >= 0 && all[c] < E) ? all[c] : -1;
-            const unsigned long long peers = same_expert_lanes(e);
+            const unsigned long long peers = same_expert_lanes<6>(e);
             const unsigned long long before = first <= c * 64 ? 0ull : first >= c * 64 + 64 ? ~0ull : (1ull << (first - c * 64)) - 1ull;
             if (e >= 0 && (peers & lt) == 0) {                // the first lane of every group of equal experts
                 cnt[0][e] += __popcll(peers);
@@ -427,7 +397,7 @@ struct OwnRanks {
             in_order();
         }
         const int e = (lane < n && own >= 0 && own < E) ? own : -1;
-        const unsigned long long peers = same_expert_lanes(e);
+        const unsigned long long peers = same_expert_lanes<6>(e);
         *my_e = e;
         *total = cnt[0][lane];
         return e >= 0 ? cnt[1][e] + __popcll(peers & lt) : -1;
@@ -759,25 +729,41 @@ int launch_rank_pass(const moe_shape& s, const RankScratch& sc, const int32_t* i
     const int n_slots = s.T * s.k;
     const int n_blocks = (n_slots + MOE_SLOTS_PER_BLOCK - 1) / MOE_SLOTS_PER_BLOCK;
     if (n_slots <= kSmallMaxSlots) {
-        hipLaunchKernelGGL(small_rank_kernel, dim3(1), dim3(1024), 0, st, idx, n_slots, s.E, s.G, s.capacity, map,
-                           sc.raw_count, sc.slot_rank, expert_count, dest_count, n_dropped);
+#define MOE_SMALL(...)                                                                                                 \
+    hipLaunchKernelGGL((small_rank_kernel<__VA_ARGS__>), dim3(1), dim3(1024), 0, st, idx, n_slots, s.E, s.G, s.capacity, map, \
+                       sc.raw_count, sc.slot_rank, expert_count, dest_count, n_dropped)
+#define MOE_SMALL_BITS(BITS)                                                                                           \
+    do {                                                                                                               \
+        if (n_slots <= 1024) MOE_SMALL(BITS, 1);                                                                        \
+        else if (n_slots <= 4096) MOE_SMALL(BITS, 4);                                                                   \
+        else MOE_SMALL(BITS, 8);                                                                                        \
+    } while (0)
+        if (s.E <= 16) MOE_SMALL_BITS(4);
+        else if (s.E <= 64) MOE_SMALL_BITS(6);
+        else MOE_SMALL_BITS(8);
+#undef MOE_SMALL_BITS
+#undef MOE_SMALL
         MOE_LAUNCH_CHECK("small_rank_kernel");
     } else {
         const size_t lds = (size_t)kChunks * s.E * sizeof(int);
-        hipLaunchKernelGGL(count_kernel, dim3(n_blocks), dim3(256), lds, st, idx, n_slots, s.E, sc.block_hist);
+#define MOE_COUNT(BITS) hipLaunchKernelGGL(count_kernel<BITS>, dim3(n_blocks), dim3(256), lds, st, idx, n_slots, s.E, sc.block_hist)
+        if (s.E <= 16) MOE_COUNT(4);
+        else if (s.E <= 64) MOE_COUNT(6);
+        else MOE_COUNT(8);
+#undef MOE_COUNT
         MOE_LAUNCH_CHECK("count_kernel");
-#define MOE_RANK(PARTS)                                                                                                    \
-    hipLaunchKernelGGL(rank_kernel<PARTS>, dim3(n_blocks), dim3(256), lds, st, idx, n_slots, s.E, sc.block_hist, n_blocks, s.G, \
+#define MOE_RANK(...)                                                                                                            \
+    hipLaunchKernelGGL((rank_kernel<__VA_ARGS__>), dim3(n_blocks), dim3(256), lds, st, idx, n_slots, s.E, sc.block_hist, n_blocks, s.G, \
                        s.capacity, map, sc.raw_count, sc.slot_rank, expert_count, dest_count, n_dropped)
         if (n_blocks <= kScanBlocks && n_blocks * s.E <= kScanCounts) {
-            if (s.E <= 16) MOE_RANK(16);
-            else if (s.E <= 64) MOE_RANK(4);
-            else MOE_RANK(1);
+            if (s.E <= 16) MOE_RANK(4, 16);
+            else if (s.E <= 64) MOE_RANK(6, 4);
+            else MOE_RANK(8, 1);
         } else {
             hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(256), 0, st, sc.block_hist, n_blocks, s.E, s.G, s.capacity, map,
                                sc.raw_count, expert_count, dest_count, n_dropped);
             MOE_LAUNCH_CHECK("scan_kernel");
-            MOE_RANK(0);
+            MOE_RANK(8, 0);
         }
 #undef MOE_RANK
         MOE_LAUNCH_CHECK("rank_kernel");
