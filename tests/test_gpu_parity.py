@@ -312,6 +312,38 @@ def test_dispatch_alone_and_after_in_place_index_rewrite(H, cfg):
     check(idx_a)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("E,k,masked", [(8, 2, 3), (8, 2, 6), (24, 3, 20), (64, 6, 58), (200, 9, 150)])
+@pytest.mark.parametrize("T", [37, 13000])
+def test_route_leaves_out_experts_with_a_bias_of_minus_infinity(H, T, E, k, masked, dtype):
+    """Masked experts are as good as absent, also where exactly k are left; so is a bias that sets logits 1e-9 of themselves apart
+    (closer than fp32 numbers are): the same choice as that of fp64 logits of the experts that are left."""
+    P = H.P
+    Hd = 64 if T > 1000 else 96
+    r = np.random.default_rng(E + k)
+    x = W.round_to_dtype(r.standard_normal((T, Hd)).astype(np.float32), dtype)
+    wg = W.round_to_dtype((r.standard_normal((E, Hd)) * 0.02).astype(np.float32), dtype)
+    left = np.sort(r.permutation(E)[masked:])
+    wg[left[1::2]] = wg[left[0:2 * (len(left) // 2):2]]         # pairs of equal rows: only the bias tells them apart
+    bias = np.full(E, -np.inf, np.float32)
+    bias[left] = np.float32(1e-9) * r.permutation(len(left))
+    z = x.astype(np.float64) @ wg[left].astype(np.float64).T + bias[left].astype(np.float64)
+    idx_ref = left[np.argsort(-z, axis=1, kind="stable")[:, :k]]
+    zk = -np.sort(-z, axis=1)
+    clear = np.min(zk[:, :-1] - zk[:, 1:], axis=1) > 1e-12 if len(left) > 1 else np.ones(T, bool)
+    assert clear.mean() > 0.99
+    ctx = P.MoeCtx(T, Hd, E, k, 1, dtype, 0, 0)
+    idx = torch.zeros((T, k), dtype=torch.int32, device=H.DEV)
+    w = torch.zeros((T, k), device=H.DEV)
+    P.moe_route(ctx, H.dev(x, dtype), H.dev(wg, dtype), torch.from_numpy(bias).to(H.DEV), idx, w)
+    torch.cuda.synchronize()
+    assert np.array_equal(H.host(idx)[clear], idx_ref[clear])
+    p = np.exp(z - z.max(axis=1, keepdims=True))
+    p /= p.sum(axis=1, keepdims=True)
+    assert H.rel_err(H.host(w), -np.sort(-p, axis=1)[:, :k]) < 1e-5
+    ctx.close()
+
+
 @pytest.mark.parametrize("T,k,E,cap", [
     (1, 1, 2, 0), (64, 1, 64, 1), (65, 3, 17, 9), (256, 2, 64, 0), (512, 1, 3, 100),        # lists that every wave of the scatter counts
     (171, 3, 16, 0), (100, 2, 65, 0),                                                         # one slot or one expert too many for that
