@@ -2088,18 +2088,34 @@ template <int MT, int NT> struct NarrowGeom {
 
 template <int EPI, int MT, int NT>
 __global__ __launch_bounds__((64 * NarrowGeom<MT, NT>::WAVES), (NarrowGeom<MT, NT>::WAVES / 4)) void gemm_bf16_narrow_kernel(const uint16_t* __restrict__ A, int lda, TileMap m, ExpertTable tab,
-                                                                  int which0, int which1, int N, int K, uint16_t* __restrict__ C, int ldc, int tiles_n) {
+                                                                  int which0, int which1, int N, int K, uint16_t* __restrict__ C, int ldc, int tiles_n, SegList one) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     using G = NarrowGeom<MT, NT>;
     constexpr int NOUT = (EPI == EPI_SWIGLU) ? G::BN_ / 2 : G::BN_;
-    const int n_tiles_m = *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(m.n_tiles));
+    auto word = [](const int32_t* p, int i) { return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p))[i]; };
+    // `one`: the only segment of the list, whose tiles need no map (see ffn_impl); else its pointers are NULL
+    int n_tiles_m, one_lo = 0, one_len = 0, one_expert = 0;
+    if (one.offset) {
+        one_expert = word(one.expert, 0);
+        one_lo = max(word(one.offset, 0), 0);
+        const int hi = min(word(one.offset, 1), one.R);
+        one_len = one_expert >= 0 && one_expert < one.n_local && hi > one_lo ? hi - one_lo : 0;
+        n_tiles_m = (one_len + G::BM_ - 1) / G::BM_;
+    } else {
+        n_tiles_m = word(m.n_tiles, 0);
+    }
     const int total = n_tiles_m * tiles_n;
     for (int item = blockIdx.x; item < total; item += gridDim.x) {   // one, unless the list has more runs than experts
         const int tile_id = skinny_tile(item, total);
         const int tile_m = __builtin_amdgcn_readfirstlane(tile_id % n_tiles_m), tile_n = __builtin_amdgcn_readfirstlane(tile_id / n_tiles_m);
-        auto rec = [&](const int32_t* p) { return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p))[tile_m]; };
-        const int row0 = rec(m.row0), nrows = rec(m.nrows), ex = rec(m.expert);
-        const int32_t* rel = rec(m.gather) ? m.rel + (size_t)tile_m * kRelPitch : nullptr;
+        int row0 = one_lo + tile_m * G::BM_, nrows = min(G::BM_, one_len - tile_m * G::BM_), ex = one_expert;
+        const int32_t* rel = nullptr;
+        if (!one.offset) {
+            row0 = word(m.row0, tile_m);
+            nrows = word(m.nrows, tile_m);
+            ex = word(m.expert, tile_m);
+            if (word(m.gather, tile_m)) rel = m.rel + (size_t)tile_m * kRelPitch;
+        }
         auto pick = [&](int which) { return reinterpret_cast<const char*>(which == 0 ? tab.w1[ex] : which == 1 ? tab.w_up[ex] : tab.w_down[ex]); };
         const int n0 = tile_n * NOUT;
         const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -2571,7 +2587,7 @@ void take_narrow(int R, int n_used, int nseg, int H, int F, int act, int cus, in
 
 template <int EPI, int MT, int NT>
 int launch_bf16_narrow_nt(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
-                          void* C, int ldc, int R, int nseg, int n_used, hipStream_t st) {
+                          void* C, int ldc, int R, int nseg, int n_used, const SegList& one, hipStream_t st) {
     using G = NarrowGeom<MT, NT>;
     const int nout = (EPI == EPI_SWIGLU) ? G::BN_ / 2 : G::BN_;
     const int tiles_n = (N + nout - 1) / nout;
@@ -2581,14 +2597,14 @@ int launch_bf16_narrow_nt(const void* A, int lda, const TileMap& m, const Expert
         attr_done = true;
     }
     hipLaunchKernelGGL((gemm_bf16_narrow_kernel<EPI, MT, NT>), dim3(std::min(max_tiles_of(R, G::BM_, nseg), (R + n_used * (G::BM_ - 1)) / G::BM_) * tiles_n), dim3(64 * G::WAVES), G::LDS, st,
-                       reinterpret_cast<const uint16_t*>(A), lda, m, tab, which0, which1, N, K, reinterpret_cast<uint16_t*>(C), ldc, tiles_n);
+                       reinterpret_cast<const uint16_t*>(A), lda, m, tab, which0, which1, N, K, reinterpret_cast<uint16_t*>(C), ldc, tiles_n, one);
     MOE_LAUNCH_CHECK("gemm_bf16_narrow_kernel");
     return MOE_OK;
 }
 template <int EPI>
 int launch_bf16_narrow(NarrowForm f, const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
-                       void* C, int ldc, int R, int nseg, int n_used, hipStream_t st) {
-#define MOE_NARROW(a, b) if (f.mt == a && f.nt == b) return launch_bf16_narrow_nt<EPI, a, b>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, n_used, st)
+                       void* C, int ldc, int R, int nseg, int n_used, const SegList& one, hipStream_t st) {
+#define MOE_NARROW(a, b) if (f.mt == a && f.nt == b) return launch_bf16_narrow_nt<EPI, a, b>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, n_used, one, st)
     MOE_NARROW(4, 2); MOE_NARROW(2, 2); MOE_NARROW(2, 1); MOE_NARROW(1, 2); MOE_NARROW(1, 1);
 #undef MOE_NARROW
     return moe_set_error(MOE_EINTERNAL, "no narrow tiles of %d x %d", f.mt, f.nt);
@@ -3011,8 +3027,13 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     }
     const TileMap &m = jobs.job[0].m, &m2 = jobs.job[1].m;
     const int n_maps = bm[1] == bm[0] ? 1 : 2;
-    const bool need_map = dtype == MOE_BF16 || f32_needs_map(R, n_used, nseg, H, F, act, round_size(), in_parts);   // else see SegList
+    // A list of one segment (a dense MLP, shared experts) whose GEMMs both take narrow tiles needs no map either: a tile follows from the
+    // segment's two offsets, which cost the GEMMs one round trip instead of the two to the number of tiles and a record.
+    // Shared experts of a decode step, 64 rows of 2048 -> 2816 -> 2048: 24.7 -> 22.9 us, 16 rows 21.8 -> 19.8.
+    const bool one_segment = nseg == 1 && form[0].mt && form[1].mt;
+    const bool need_map = dtype == MOE_BF16 ? !one_segment : f32_needs_map(R, n_used, nseg, H, F, act, round_size(), in_parts);   // else see SegList
     const SegList seg = {seg_offset, seg_expert, nseg, R, n_local, gather, 0};
+    const SegList one = one_segment ? seg : SegList{};
     if (!need_map) {
     } else if (nseg <= kSmallMapSegs) {                           // about a tile per wave
         const int blocks = std::min(64, (R / std::min(bm[0], bm[1]) + std::min(nseg, n_local) + 3) / 4);
@@ -3024,9 +3045,9 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     if (ev) MOE_HIP(hipEventRecord(ev[1], st));
     int rc = MOE_OK;
     if (form[0].mt) {
-        if (act == MOE_ACT_SWIGLU) rc = launch_bf16_narrow<EPI_SWIGLU>(form[0], recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, st);
-        else if (act == MOE_ACT_GELU_MLP) rc = launch_bf16_narrow<EPI_GELU>(form[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, st);
-        else rc = launch_bf16_narrow<EPI_SILU>(form[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, st);
+        if (act == MOE_ACT_SWIGLU) rc = launch_bf16_narrow<EPI_SWIGLU>(form[0], recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, one, st);
+        else if (act == MOE_ACT_GELU_MLP) rc = launch_bf16_narrow<EPI_GELU>(form[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, one, st);
+        else rc = launch_bf16_narrow<EPI_SILU>(form[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, one, st);
     } else if (skinny) {
         if (act == MOE_ACT_SWIGLU) rc = launch_bf16_skinny<EPI_SWIGLU>(recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, partial, st);
         else if (act == MOE_ACT_GELU_MLP) rc = launch_bf16_skinny<EPI_GELU>(recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, partial, st);
@@ -3045,7 +3066,7 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     }
     if (rc != MOE_OK) return rc;
     if (ev) MOE_HIP(hipEventRecord(ev[2], st));
-    if (form[1].mt) rc = launch_bf16_narrow<EPI_PLAIN>(form[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, st);
+    if (form[1].mt) rc = launch_bf16_narrow<EPI_PLAIN>(form[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, one, st);
     else if (skinny) rc = launch_bf16_skinny<EPI_PLAIN>(hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, partial, st);
     else if (dtype == MOE_BF16) rc = launch_bf16_shape<EPI_PLAIN>(shape[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, partial, st, timed_gemm == 2, marks, marks_len);
     else rc = launch_f32<EPI_PLAIN>(in_parts[1], need_map, hmid, F, m2, seg, tab, 2, 2, H, F, out, H, R, nseg, n_used, st);

@@ -793,6 +793,24 @@ def test_expert_ffn_narrow_tiles(H, R, Hd, F, n_local, nseg, act, forms):
     H.assert_close(out[off[0]:off[-1]], O.expert_ffn(recv, off, exp, experts, act)[off[0]:off[-1]], "bf16")
 
 
+@pytest.mark.parametrize("R,lo,hi,expert", [(60, 5, 70, 0), (60, -3, 33, 0), (60, 0, 60, 1), (60, 0, 60, -1), (60, 40, 40, 0), (100, 1, 100, 0), (1, 0, 1, 0)])
+def test_expert_ffn_narrow_tiles_of_one_segment(H, R, lo, hi, expert):
+    """A list of one segment, whose tiles come from its offsets: clipped to the rows that there are, nothing of an unknown
+    expert, no other row is written."""
+    import ctypes as C
+    from paper_2410_17043_amd import _lib
+    got = (C.c_int32 * 2)()
+    assert _lib.load().moe_selfcheck_narrow(R, 1, 1, 512, 128, 2, 256, got) == 0 and got[0] and got[1]
+    cfg = small("c2_mixtral", H=512, F=128, act=2)
+    recv = W.to_bf16_grid(np.random.default_rng(R).standard_normal((R, 512)).astype(np.float32))
+    w = W.make_expert_weights(cfg, 0)
+    out = H.host(H.run_ffn(H.dev(recv, "bf16"), [lo, hi], [expert], [H.weights_to_dev(w, "bf16")], 512, 128, 2, "bf16"))
+    lo, hi = max(lo, 0), min(hi, R) if expert == 0 else max(lo, 0)
+    assert np.isnan(out[:lo]).all() and np.isnan(out[hi:]).all()
+    if hi > lo:
+        H.assert_close(out[lo:hi], O.ffn(recv[lo:hi], w["w1"], w["w_up"], w["w_down"], 2), "bf16")
+
+
 # fp32 GEMMs on three bf16 parts (128-row tiles): a K that ends inside a k-tile and an odd number of them, gathered and
 # ragged tiles, N of no whole tile, several tiles per block, one kernel of each kind with a map of its own, K of the least four k-tiles
 @pytest.mark.parametrize("act,R,Hd,F,n_local,nseg,rows", [(1, 1800, 1156, 1164, 2, 9, [128, 128]), (2, 3000, 292, 1156, 3, 40, [128, 64]),
