@@ -956,6 +956,38 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     return *reinterpret_cast<const uint32_t*>(&b);
 }
 
+// The pieces of a tile that is cut along K.  Every piece writes its fp32 accumulators; at 128 x 128 (and in the
+// weight-streaming kernels) the block that arrives last (a counter per tile, nobody waits) adds all pieces in piece
+// order - its own is read back like the others, so the result does not depend on who was last - and finishes the
+// tile.  A kernel of its own for the sums costs 4.5 us where there is nothing to add and 5-16 us where there is, each
+// time behind a launch gap; the last block reads up to half a megabyte (32 pieces of a weight-streaming tile: 1 MB) in
+// about as long, without the gap.  The larger tiles have 0.8 to 2 MB of pieces, which take one block 20 us and more (93
+// against 108 us for the second GEMM at 4096 -> 14336 -> 4096 and 701 rows): those are added by gemm_bf16_tail_kernel,
+// spread over the chip.
+// The writers may sit on other XCDs, whose L2s do not see each other: pieces are stored and read with accesses of
+// agent scope (sc1: written through, read past the L2), the counter is an agent-scope atomic, and a wave's stores have
+// completed (vmcnt(0)) before its block counts.  The same with plain accesses between __threadfence()s was far
+// slower: every fence writes back the whole L2 (54 against 17 us at 110 tiles of four pieces).
+constexpr int kAgentScope = 16;                              // cache policy bits of a buffer access: sc1
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t pieces_rsrc(const float* partial, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(partial), 0, bytes, 0x00027000);
+}
+__device__ __forceinline__ void store_piece(__amdgpu_buffer_rsrc_t r, int quad, const f32x4& v) {   // 16 bytes at quad * 16
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, quad * 16, 0, kAgentScope);
+}
+__device__ __forceinline__ f32x4 load_piece(__amdgpu_buffer_rsrc_t r, int quad) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, quad * 16, 0, kAgentScope));
+}
+__device__ __forceinline__ bool last_piece(int32_t* done, int parts, int* lds_flag) {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070);                        // vmcnt(0) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    if (threadIdx.x == 0) *lds_flag = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
+    __syncthreads();
+    asm volatile("" ::: "memory");
+    return *lds_flag != 0;
+}
+
 // The same products on the bf16 matrix cores, for grids that fill the chip with 128 x 128 tiles (see take_f32_kernels).
 //
 // A float of 24 bits is the sum of three bf16 numbers of 8 bits and a sign, x = x0 + x1 + x2, each the rest rounded to nearest
@@ -993,10 +1025,39 @@ constexpr int kXOperand = 3 * kXPlane;
 constexpr int kXStage = 2 * kXOperand;                   // A, then B
 constexpr int kXGive = 32 * 1024;                        // sums of a group that the other one finishes; both groups' begin in the second stage
 constexpr int kXLargest = kXStage + 2 * kXGive;          // largest elements of the rows and weight rows of a tile
-constexpr int kXLds = kXLargest + (XM + XN) * 4;
+constexpr int kXFlag = kXLargest + (XM + XN) * 4;        // whether this block adds the pieces of a tile
+constexpr int kXLds = kXFlag + 16;
 static_assert(2 * kXGive >= kXStage, "");
 constexpr int kXMinK = 4 * XK;                           // a walk reads three k-tiles ahead: at most into the next tile
 constexpr float kPartsFloor = 0x1p-100f;
+
+// The tiles of a last round that leaves most CUs idle are cut along K into `parts` pieces of at least kXCutMin k-tiles, one per
+// block.  A piece writes its sums (fp32, 64 KB) and the largest elements of its rows and weight rows; the block whose
+// piece of a tile arrives last adds them in order and finishes the tile.
+// A k-tile takes 0.93 us on an empty chip and 0.3 more on a full one, and pieces on all CUs cost 17 us (fit over 36 of 120
+// shares of 300 to 16000 rows); a round is cut where that leaves a gain: 8355 rows of 512 -> 2048 -> 512 (8 of 264 tiles in the second
+// GEMM's last round, K = 2048) 293 -> 252 us, 7064 of 768 -> 2304 -> 768 332 -> 301, 3001 of 1024 -> 2816 -> 1024 SwiGLU (32 of 1056
+// tiles, K = 1024) first GEMM 229 -> 218.  Shares that cross from one tile into the next, for rounds that are more than half full (192
+// tiles of K = 2816), gained nothing: the chip is slower by about what it is fuller.
+constexpr int kXCutMin = 8;
+constexpr size_t kXPiece = (size_t)(XM * XN + XM + XN) * sizeof(float);
+struct PartsCut {
+    int n_full;        // tiles taken whole: ids [0, n_full)
+    int n_cut;         // the others, each as
+    int parts, per;    // ... parts pieces of per k-tiles (the last one may be shorter)
+};
+__host__ __device__ __forceinline__ PartsCut plan_parts(int total, int ncu, int nk) {
+    const PartsCut whole{total, 0, 1, nk};
+    const int rest = total % ncu;
+    if (2 * rest > ncu || rest == 0) return whole;
+    const int most = min(ncu / rest, nk / kXCutMin);
+    if (most < 2) return whole;
+    const int per = ((nk + most - 1) / most + 1) & ~1;     // pieces begin at even k-tiles
+    const int parts = (nk + per - 1) / per, places = rest * parts;
+    // in nanoseconds: the round as it is, as pieces, and what those cost, half as much again
+    if (nk * (932 + 299 * rest / ncu) - per * (932 + 299 * places / ncu) < 26000 * places / ncu) return whole;
+    return PartsCut{total - rest, rest, parts, per};
+}
 
 // m or the larger of |a| and |b| (neither is taken for a NaN)
 __device__ __forceinline__ float largest_of(float m, float a, float b) {
@@ -1097,32 +1158,51 @@ __device__ __forceinline__ void multiply_exactly(const float* pa, const float* p
     }
 }
 
-template <int EPI>
+// CUT: the last round's tiles may be cut along K (see plan_parts).  The code for pieces costs short tiles 2 to 4 % (scalar registers
+// on their way from one tile to the next), so shares that have none run without it.
+template <int EPI, bool CUT>
 __global__ __launch_bounds__(512, 2) void gemm_f32_parts_kernel(const float* __restrict__ A, int lda, TileMap m, ExpertTable tab,
                                                                 int which0, int which1, int N, int K, float* __restrict__ C, int ldc,
-                                                                int tiles_n, int ncu, int walk) {
+                                                                int tiles_n, int ncu, int walk, float* partial) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     constexpr int NOUT = (EPI == EPI_SWIGLU) ? XN / 2 : XN;
     const int n_tiles_m = *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(m.n_tiles));
     const int total = n_tiles_m * tiles_n;
-    const WalkRun run = walk_run(blockIdx.x, ncu, walk, total);
+    const int nk_all = ((K + XK - 1) / XK + 1) & ~1;       // even; k-tiles past K count as zeros
+    PartsCut cut = {total, 0, 1, nk_all};
+    if (CUT) {
+        cut = plan_parts(total, ncu, nk_all);
+        cut.n_full = __builtin_amdgcn_readfirstlane(cut.n_full);
+        cut.n_cut = __builtin_amdgcn_readfirstlane(cut.n_cut);
+        cut.parts = __builtin_amdgcn_readfirstlane(cut.parts);
+        cut.per = __builtin_amdgcn_readfirstlane(cut.per);
+    }
+    const WalkRun run = walk_run(blockIdx.x, ncu, walk, cut.n_full + cut.n_cut * cut.parts);   // whole tiles, then pieces
     int item = __builtin_amdgcn_readfirstlane(run.item);
     const int end_item = __builtin_amdgcn_readfirstlane(run.end);
     if (item >= end_item) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
     const int fr = lane & 31, fk = lane >> 5;
-    const int nk = ((K + XK - 1) / XK + 1) & ~1;           // even; k-tiles past K count as zeros
     const int k_full = K / XK;                             // k-tiles without an end of K in them
 
-    struct Tile { int row0, nrows, n0, ex; const int32_t* rel; };
-    struct Source { __amdgpu_buffer_rsrc_t a, b; uint32_t a_voff, b_voff; };
+    struct Tile { int row0, nrows, n0, ex, nk, piece; const int32_t* rel; };   // nk: k-tiles of it that this block takes; piece < 0: all
+    struct Source { __amdgpu_buffer_rsrc_t a, b; uint32_t a_voff, b_voff; int k0; };
     constexpr uint32_t kNoOffset = 0xFFFFFFF0u;               // past the end of the buffer (row offsets end below it, see ffn_impl)
     // what this lane fetches: chunk `lc` of tile row 16 wave + lane / 4, of A and of B; it goes to slot `lane` of block `wave`
     const int lc = (lane & 3) ^ (lane >> 4);
     auto weights = [&](int which, int ex) { return reinterpret_cast<const char*>(which == 0 ? tab.w1[ex] : which == 1 ? tab.w_up[ex] : tab.w_down[ex]); };
     auto describe = [&](int id, Tile& t, Source& s) {
         int tile_m, tile_n;
+        s.k0 = 0;
+        t.nk = nk_all;
+        t.piece = -1;
+        if (CUT && id >= cut.n_full) {
+            t.piece = __builtin_amdgcn_readfirstlane((id - cut.n_full) / cut.n_cut);
+            id -= t.piece * cut.n_cut;
+            s.k0 = t.piece * cut.per;
+            t.nk = min(cut.per, nk_all - s.k0);
+        }
         tile_of_block(id, total, n_tiles_m, tiles_n, &tile_m, &tile_n);
         tile_m = __builtin_amdgcn_readfirstlane(tile_m);
         auto rec = [&](const int32_t* p) { return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p))[tile_m]; };
@@ -1149,6 +1229,7 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_parts_kernel(const float* __r
     // the buffer, which reads as zero.
     const uint32_t quad0 = (uint32_t)lc * 16u, quad1 = quad0 + 64u;
     auto fetch = [&](f32x4 (&q)[4], int kt) {
+        kt += src.k0;
         const int at = kt * (XK * 4);
         const bool in0 = kt < k_full || kt * XK + lc * 4 < K, in1 = kt < k_full || kt * XK + 16 + lc * 4 < K;
         auto load = [&](__amdgpu_buffer_rsrc_t r, uint32_t off, bool in) { return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, in ? off : kNoOffset, at, 0)); };
@@ -1183,12 +1264,12 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_parts_kernel(const float* __r
     };
     // k-tile kt is in `now`; the one behind it goes to `then`
     auto step = [&](int kt, unsigned char* now, unsigned char* then, f32x4 (&q)[4]) {
-        if (kt + 3 == nk && more) src = src_next;
+        if (kt + 3 == cur.nk && more) src = src_next;
         __builtin_amdgcn_sched_barrier(0);
-        if (kt + 1 == nk) note_largest();                  // what is split now is the next tile's first k-tile
+        if (kt + 1 == cur.nk) note_largest();                  // what is split now is the next tile's first k-tile
         __builtin_amdgcn_sched_barrier(0);
         multiply_parts(now + a_off, now + b_off, hi, lo, q, largest, then + w_off);
-        fetch(q, kt + 3 >= nk ? kt + 3 - nk : kt + 3);
+        fetch(q, kt + 3 >= cur.nk ? kt + 3 - cur.nk : kt + 3);
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0): this wave has read `now` and written `then`
         __builtin_amdgcn_s_barrier();
@@ -1207,7 +1288,7 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_parts_kernel(const float* __r
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     while (true) {
-        for (int kt = 0; kt < nk; kt += 2) {
+        for (int kt = 0; kt < cur.nk; kt += 2) {
             step(kt, st0, st1, odd);
             step(kt + 1, st1, st0, even);
         }
@@ -1233,28 +1314,86 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_parts_kernel(const float* __r
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         const int gr = wm * 64 + grp * 32 + fr;
-        const float row_largest = tile_largest[gr];
         const float small = (float)K * kPartsFloor;
+        float row_largest = tile_largest[gr];
         uint32_t bad[2] = {0, 0};
+        auto judge = [&](int e, int j, float larger, float w_largest) {
+            const float limit = row_largest > 0.f && w_largest > 0.f ? small * fmaxf(fmaxf(row_largest, w_largest), 1.f) : 0.f;
+            if (!(larger >= limit && fabsf(fin[j][e]) <= FLT_MAX)) bad[j] |= 1u << e;
+        };
+        const int w_at = wn * 64 + fk * 4;                 // the weight rows of fin[j][4 q + t]: w_at + 32 j + 8 q + t
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const f32x4 v = *reinterpret_cast<const f32x4*>(take + (j * 4 + q) * 1024);
-                const f32x4 w = *reinterpret_cast<const f32x4*>(&tile_largest[XM + wn * 64 + j * 32 + q * 8 + fk * 4]);
+                const f32x4 w = *reinterpret_cast<const f32x4*>(&tile_largest[XM + w_at + j * 32 + q * 8]);
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const int e = 4 * q + t;
                     const float larger = fmaxf(fabsf(fin[j][e]), fabsf(v[t]));
                     fin[j][e] += v[t];
-                    const float limit = row_largest > 0.f && w[t] > 0.f ? small * fmaxf(fmaxf(row_largest, w[t]), 1.f) : 0.f;
-                    if (!(larger >= limit && fabsf(fin[j][e]) <= FLT_MAX)) bad[j] |= 1u << e;
+                    judge(e, j, larger, w[t]);
                 }
             }
         __builtin_amdgcn_s_waitcnt(0xC07F);
         __builtin_amdgcn_s_barrier();                      // the sums have been read: the next tile's second k-tile may be written
         asm volatile("" ::: "memory");
-        if (__ballot((bad[0] | bad[1]) != 0)) {
+        bool finish = true;                                // this block writes the tile
+        if (CUT && cur.piece >= 0) {
+            const int tid = threadIdx.x, tile = (item - cut.n_full) % cut.n_cut;
+            auto slot = [&](int p) { return p * (int)(kXPiece / 16); };
+            const __amdgpu_buffer_rsrc_t pieces = pieces_rsrc(partial + (size_t)tile * cut.parts * (kXPiece / 4), (uint32_t)(cut.parts * kXPiece));
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    store_piece(pieces, slot(cur.piece) + (j * 4 + q) * 512 + tid, f32x4{fin[j][4 * q], fin[j][4 * q + 1], fin[j][4 * q + 2], fin[j][4 * q + 3]});
+            if (tid < (XM + XN) / 4) store_piece(pieces, slot(cur.piece) + XM * XN / 4 + tid, reinterpret_cast<const f32x4*>(tile_largest)[tid]);
+            finish = last_piece(m.done + tile, cut.parts, reinterpret_cast<int*>(lds + kXFlag));
+            if (finish) {
+                // all pieces in order, this one as well: the sum does not depend on who was last.  What counts as small is judged by the
+                // pieces' sums as by the groups' above; of the largest elements all pieces have their own.
+                f32x4 sum[8], w[8];
+                float top[2][16];                          // largest of the pieces' sums
+                row_largest = 0.f;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) sum[q] = w[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) top[j][e] = 0.f;
+                for (int i = 0; i < cut.parts; ++i) {
+                    const int from = slot(i), larg = from + XM * XN / 4;
+                    f32x4 v[8], u[8];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) v[q] = load_piece(pieces, from + q * 512 + tid);
+                    const f32x4 r = load_piece(pieces, larg + gr / 4);
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) u[q] = load_piece(pieces, larg + (XM + w_at + q / 4 * 32 + q % 4 * 8) / 4);
+                    row_largest = fmaxf(row_largest, r[gr & 3]);
+#pragma unroll
+                    for (int q = 0; q < 8; ++q)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            sum[q][t] += v[q][t];
+                            w[q][t] = fmaxf(w[q][t], u[q][t]);
+                            float& big = top[q / 4][q % 4 * 4 + t];
+                            big = fmaxf(big, fabsf(v[q][t]));
+                        }
+                }
+                bad[0] = bad[1] = 0;
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const int j = q / 4, e = q % 4 * 4 + t;
+                        fin[j][e] = sum[q][t];
+                        judge(e, j, top[j][e], w[q][t]);
+                    }
+            }
+        }
+        if (finish && __ballot((bad[0] | bad[1]) != 0)) {
             int ar = min(gr, cur.nrows - 1);
             if (cur.rel) ar = cur.rel[ar];
             const int c0 = cur.n0 + wn * (NOUT / 2) + fr;
@@ -1269,7 +1408,7 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_parts_kernel(const float* __r
                 for (int e = 0; e < 16; ++e)
                     if (bad[j] >> e & 1) fin[j][e] = exact[j][e];
         }
-        if (gr < cur.nrows) {
+        if (finish && gr < cur.nrows) {
             float* crow = C + (size_t)(cur.row0 + (cur.rel ? cur.rel[gr] : gr)) * ldc;
 #pragma unroll
             for (int j = 0; j < ((EPI == EPI_SWIGLU) ? 1 : 2); ++j)
@@ -1362,38 +1501,6 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[MI][NJ], int lane
             __builtin_amdgcn_raw_buffer_store_b128(q[it], dst, row_off[it] + p % PER_ROW * JP * 64, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
     }
-}
-
-// The pieces of a tile that is cut along K.  Every piece writes its fp32 accumulators; at 128 x 128 (and in the
-// weight-streaming kernels) the block that arrives last (a counter per tile, nobody waits) adds all pieces in piece
-// order - its own is read back like the others, so the result does not depend on who was last - and finishes the
-// tile.  A kernel of its own for the sums costs 4.5 us where there is nothing to add and 5-16 us where there is, each
-// time behind a launch gap; the last block reads up to half a megabyte (32 pieces of a weight-streaming tile: 1 MB) in
-// about as long, without the gap.  The larger tiles have 0.8 to 2 MB of pieces, which take one block 20 us and more (93
-// against 108 us for the second GEMM at 4096 -> 14336 -> 4096 and 701 rows): those are added by gemm_bf16_tail_kernel,
-// spread over the chip.
-// The writers may sit on other XCDs, whose L2s do not see each other: pieces are stored and read with accesses of
-// agent scope (sc1: written through, read past the L2), the counter is an agent-scope atomic, and a wave's stores have
-// completed (vmcnt(0)) before its block counts.  The same with plain accesses between __threadfence()s was far
-// slower: every fence writes back the whole L2 (54 against 17 us at 110 tiles of four pieces).
-constexpr int kAgentScope = 16;                              // cache policy bits of a buffer access: sc1
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t pieces_rsrc(const float* partial, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(partial), 0, bytes, 0x00027000);
-}
-__device__ __forceinline__ void store_piece(__amdgpu_buffer_rsrc_t r, int quad, const f32x4& v) {   // 16 bytes at quad * 16
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, quad * 16, 0, kAgentScope);
-}
-__device__ __forceinline__ f32x4 load_piece(__amdgpu_buffer_rsrc_t r, int quad) {
-    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, quad * 16, 0, kAgentScope));
-}
-__device__ __forceinline__ bool last_piece(int32_t* done, int parts, int* lds_flag) {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0x0070);                        // vmcnt(0) lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-    if (threadIdx.x == 0) *lds_flag = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == parts - 1;
-    __syncthreads();
-    asm volatile("" ::: "memory");
-    return *lds_flag != 0;
 }
 
 // Sum of the pieces of one tile and its epilogue for units [unit_lo, unit_hi) of 32 x 32 outputs per wave.  Four pieces are requested before
@@ -2658,26 +2765,39 @@ bool f32_needs_map(int R, int n_used, int nseg, int H, int F, int act, int cus, 
     const int64_t tiles_m = std::min<int64_t>(max_tiles_of(R, FM, nseg), (R + (int64_t)n_used * (FM - 1)) / FM);
     return tiles_m * ((F + cols - 1) / cols + (H + FN - 1) / FN) > (int64_t)kListTiles * cus;
 }
+// Whether most of the tile counts that n_used runs of R rows can have (the device knows which it is) leave tiles that are cut.
+bool cuts_parts(int R, int n_used, int N, int K, int act, int cus) {
+    const int cols = act == MOE_ACT_SWIGLU ? XN / 2 : XN, tiles_n = (N + cols - 1) / cols, nk = ((K + XK - 1) / XK + 1) & ~1;
+    const int lo = (R + XM - 1) / XM, hi = std::max(lo, (int)std::min<int64_t>(R, (R + (int64_t)n_used * (XM - 1)) / XM));
+    int cut = 0;
+    for (int t = lo; t <= hi; ++t) cut += plan_parts(t * tiles_n, cus, nk).n_cut > 0 ? 1 : -1;
+    return cut >= 0;
+}
 template <int EPI>
 int launch_f32_parts(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
-                     void* C, int ldc, int R, int nseg, hipStream_t st) {
+                     void* C, int ldc, int R, int nseg, float* partial, hipStream_t st) {
     const int nout = (EPI == EPI_SWIGLU) ? XN / 2 : XN;
     const int tiles_n = (N + nout - 1) / nout, ncu = round_size(), walk = parts_walk_tiles(K);
-    static bool attr_done = false;
-    if (!attr_done) {
-        MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_parts_kernel<EPI>), hipFuncAttributeMaxDynamicSharedMemorySize, kXLds));
-        attr_done = true;
-    }
-    hipLaunchKernelGGL((gemm_f32_parts_kernel<EPI>), dim3(walk_blocks(max_tiles_of(R, XM, nseg) * tiles_n, walk, ncu)), dim3(512), kXLds, st,
-                       reinterpret_cast<const float*>(A), lda, m, tab, which0, which1, N, K, reinterpret_cast<float*>(C), ldc, tiles_n, ncu, walk);
+    auto launch = [&](auto kernel, bool& attr_done, int more) -> int {
+        if (!attr_done) {
+            MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kXLds));
+            attr_done = true;
+        }
+        hipLaunchKernelGGL(kernel, dim3(walk_blocks(max_tiles_of(R, XM, nseg) * tiles_n + more, walk, ncu)), dim3(512), kXLds, st,
+                           reinterpret_cast<const float*>(A), lda, m, tab, which0, which1, N, K, reinterpret_cast<float*>(C), ldc, tiles_n, ncu, walk, partial);
+        return MOE_OK;
+    };
+    static bool attr_cut = false, attr_whole = false;
+    const int rc = partial ? launch(gemm_f32_parts_kernel<EPI, true>, attr_cut, ncu) : launch(gemm_f32_parts_kernel<EPI, false>, attr_whole, 0);
+    if (rc != MOE_OK) return rc;
     MOE_LAUNCH_CHECK("gemm_f32_parts_kernel");
     return MOE_OK;
 }
 
 template <int EPI>
 int launch_f32(bool in_parts, bool need_map, const void* A, int lda, const TileMap& m, SegList seg, const ExpertTable& tab, int which0, int which1,
-               int N, int K, void* C, int ldc, int R, int nseg, int n_used, hipStream_t st) {
-    if (in_parts) return launch_f32_parts<EPI>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, st);
+               int N, int K, void* C, int ldc, int R, int nseg, int n_used, float* partial, hipStream_t st) {
+    if (in_parts) return launch_f32_parts<EPI>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, partial, st);
     const int nout = (EPI == EPI_SWIGLU) ? FN / 2 : FN;
     const int tiles_n = (N + nout - 1) / nout;
     seg.max_tiles = max_tiles_of(R, FM, nseg);
@@ -2775,18 +2895,28 @@ extern "C" int moe_selfcheck_f32_map(int32_t R, int32_t n_used, int32_t nseg, in
 extern "C" int moe_selfcheck_f32_walk(int32_t tiles_m, int32_t max_tiles_m, int32_t tiles_n, int32_t K, int32_t ncu) {
     if (tiles_m < 0 || max_tiles_m < std::max(tiles_m, 1) || tiles_n < 1 || K < kXMinK || K % 4 != 0 || ncu < 1)
         return moe_set_error(MOE_EINVAL, "moe_selfcheck_f32_walk: bad argument");
-    const int walk = parts_walk_tiles(K), total = tiles_m * tiles_n;
-    std::vector<int> seen((size_t)total, 0);
-    for (int b = 0; b < walk_blocks(max_tiles_m * tiles_n, walk, ncu); ++b) {
-        const WalkRun run = walk_run(b, ncu, walk, total);
-        int taken = 0;
-        for (int item = run.item; item < run.end; item += ncu, ++taken) {
-            if (item >= total || taken == walk) return moe_set_error(MOE_EINTERNAL, "run of block %d", b);
-            ++seen[item];
+    const int walk = parts_walk_tiles(K), total = tiles_m * tiles_n, nk = ((K + XK - 1) / XK + 1) / 2 * 2;
+    const PartsCut cuts[2] = {PartsCut{total, 0, 1, nk}, plan_parts(total, ncu, nk)};
+    for (const PartsCut& c : cuts) {
+        const int n_items = c.n_full + c.n_cut * c.parts;
+        std::vector<int> seen((size_t)n_items, 0);
+        for (int b = 0; b < walk_blocks(max_tiles_m * tiles_n + ncu, walk, ncu); ++b) {
+            const WalkRun run = walk_run(b, ncu, walk, n_items);
+            int taken = 0;
+            for (int item = run.item; item < run.end; item += ncu, ++taken) {
+                if (item >= n_items || taken == walk) return moe_set_error(MOE_EINTERNAL, "run of block %d", b);
+                if (item >= c.n_full && c.n_cut > 0 && item + ncu < run.end) return moe_set_error(MOE_EINTERNAL, "piece %d is not the last item of block %d", item, b);
+                ++seen[item];
+            }
         }
+        for (int i = 0; i < n_items; ++i)
+            if (seen[i] != 1) return moe_set_error(MOE_EINTERNAL, "item %d is taken %d times", i, seen[i]);
+        if (c.n_cut == 0) continue;
+        if (c.n_full + c.n_cut != total || c.n_cut * c.parts > ncu)
+            return moe_set_error(MOE_EINTERNAL, "%d pieces of %d tiles", c.parts, c.n_cut);
+        if (c.parts < 2 || c.per % 2 != 0 || c.per < kXCutMin || c.parts * c.per < nk || (c.parts - 1) * c.per >= nk)
+            return moe_set_error(MOE_EINTERNAL, "%d pieces of %d k-tiles for %d", c.parts, c.per, nk);
     }
-    for (int i = 0; i < total; ++i)
-        if (seen[i] != 1) return moe_set_error(MOE_EINTERNAL, "tile %d is taken %d times", i, seen[i]);
     return walk;
 }
 
@@ -2941,10 +3071,13 @@ extern "C" int moe_selfcheck_tile_map(const int32_t* seg_offset, const int32_t* 
     return rc != MOE_OK ? rc : nt;
 }
 
+// without room for the pieces of cut tiles
+static size_t least_workspace(int R, int F, int dtype) { return tilemap_bytes(R) + align256((size_t)R * F * elem_size(dtype)) + 256; }
+
 extern "C" size_t moe_ffn_workspace_bytes(int32_t R_max, int32_t H, int32_t F, int32_t act, int32_t dtype) {
     if (R_max < 0 || H <= 0 || F <= 0 || act < 0 || act > 2 || (dtype != MOE_F32 && dtype != MOE_BF16)) return 0;
-    const size_t partial = (dtype == MOE_BF16) ? (size_t)kMaxCU * TileGeom<4, 4>::PARTIAL : 0;   // pieces of tail tiles
-    return tilemap_bytes(R_max) + align256((size_t)R_max * F * elem_size(dtype)) + partial + 256;
+    const size_t partial = (dtype == MOE_BF16) ? (size_t)kMaxCU * TileGeom<4, 4>::PARTIAL : (size_t)kMaxCU * kXPiece;   // pieces of cut tiles
+    return least_workspace(R_max, F, dtype) + partial;
 }
 
 // timed_gemm: 0 none, 1 / 2: that GEMM runs as its TIMED instantiation and writes marks (bf16, more than 64 rows)
@@ -2967,7 +3100,9 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         return moe_set_error(MOE_EALIGN, "moe_expert_ffn: fp32 needs H and F to be multiples of 4");
     if (!aligned16(recv) || !aligned16(out) || (reinterpret_cast<uintptr_t>(workspace) & 255u))
         return moe_set_error(MOE_EALIGN, "moe_expert_ffn: recv/out need 16-byte, workspace 256-byte alignment");
-    if (workspace_bytes < moe_ffn_workspace_bytes(R, H, F, act, dtype))
+    const bool pieces_fit = workspace_bytes >= moe_ffn_workspace_bytes(R, H, F, act, dtype);
+    // (fp32 tiles are not cut in a workspace that was sized for the tile map and the intermediate alone)
+    if (!pieces_fit && (dtype != MOE_F32 || workspace_bytes < least_workspace(R, F, dtype)))
         return moe_set_error(MOE_ESHAPE, "moe_expert_ffn: workspace too small (%zu < %zu)", workspace_bytes,
                              moe_ffn_workspace_bytes(R, H, F, act, dtype));
     ExpertTable tab;
@@ -3020,7 +3155,12 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     MapJobs jobs;
     jobs.job[0] = MapJob{bm[0], max_tiles_of(R, bm[0], nseg), tilemap_at(workspace, R)};
     jobs.job[1] = (bm[1] == bm[0]) ? jobs.job[0] : MapJob{bm[1], max_tiles_of(R, bm[1], nseg), tilemap_at(workspace, R, 1, jobs.job[0].max_tiles)};
-    jobs.done = (dtype == MOE_BF16) ? tilemap_at(workspace, R, 0, max_tiles_for(R) - 2).rel : nullptr;
+    float* f32_pieces[2] = {nullptr, nullptr};            // where an fp32 GEMM's tiles are cut
+    if (dtype == MOE_F32 && pieces_fit && maps_fit(R, nseg, bm[0], bm[1])) {
+        if (in_parts[0] && cuts_parts(R, n_used, F, H, act, round_size())) f32_pieces[0] = partial;
+        if (in_parts[1] && cuts_parts(R, n_used, H, F, -1, round_size())) f32_pieces[1] = partial;
+    }
+    jobs.done = (dtype == MOE_BF16 || f32_pieces[0] || f32_pieces[1]) ? tilemap_at(workspace, R, 0, max_tiles_for(R) - 2).rel : nullptr;
     if (jobs.done) {
         jobs.job[0].m.done = jobs.done;
         jobs.job[1].m.done = jobs.done + kMaxSplitTiles;
@@ -3060,16 +3200,16 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         else
             rc = launch_bf16_shape<EPI_SILU>(shape[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
     } else {
-        if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, st);
-        else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, st);
-        else rc = launch_f32<EPI_SILU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, st);
+        if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
+        else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
+        else rc = launch_f32<EPI_SILU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
     }
     if (rc != MOE_OK) return rc;
     if (ev) MOE_HIP(hipEventRecord(ev[2], st));
     if (form[1].mt) rc = launch_bf16_narrow<EPI_PLAIN>(form[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, one, st);
     else if (skinny) rc = launch_bf16_skinny<EPI_PLAIN>(hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, partial, st);
     else if (dtype == MOE_BF16) rc = launch_bf16_shape<EPI_PLAIN>(shape[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, partial, st, timed_gemm == 2, marks, marks_len);
-    else rc = launch_f32<EPI_PLAIN>(in_parts[1], need_map, hmid, F, m2, seg, tab, 2, 2, H, F, out, H, R, nseg, n_used, st);
+    else rc = launch_f32<EPI_PLAIN>(in_parts[1], need_map, hmid, F, m2, seg, tab, 2, 2, H, F, out, H, R, nseg, n_used, f32_pieces[1], st);
     if (rc != MOE_OK) return rc;
     if (ev) MOE_HIP(hipEventRecord(ev[3], st));
     return MOE_OK;

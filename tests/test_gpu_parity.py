@@ -829,6 +829,51 @@ def f32_rows(R, n_local, nseg, Hd, F, act):
     return list(got)
 
 
+@pytest.mark.parametrize("R,Hd,F,act,cut", [(8355, 512, 2048, 0, (0, 8)), (6600, 640, 1300, 1, (0, 5)), (3071, 1024, 2816, 2, (4, 0))])
+def test_expert_ffn_fp32_in_parts_tiles_cut_along_k(H, R, Hd, F, act, cut):
+    """Tiles of a last round in pieces, against the same tiles whole (a workspace without room for pieces) and the oracle: also for
+    rows of huge, tiny and infinite elements, NaN and zeros, whose sums no piece may judge alone."""
+    import ctypes as C
+    from paper_2410_17043_amd import _lib
+    P = H.P
+    rows2 = (C.c_int32 * 2)()
+    assert _lib.load().moe_selfcheck_f32_kernels(R, 1, 1, Hd, F, act, 256, rows2) == 0 and list(rows2) == [128, 128]
+    for g, (N, K) in enumerate(((F, Hd), (Hd, F))):            # pieces of a tile in either GEMM, if any
+        cols = 64 if g == 0 and act == 2 else 128
+        rest, nk = -(-R // 128) * -(-N // cols) % 256, (-(-K // 32) + 1) // 2 * 2
+        assert cut[g] == 0 or (0 < rest <= 128 and min(256 // rest, nk // 8) == cut[g])
+    cfg = small("c1_tiny_fp32", H=Hd, F=F, act=act, dtype="fp32")
+    r = np.random.default_rng(R)
+    recv = r.standard_normal((R, Hd)).astype(np.float32)
+    w = W.make_expert_weights(cfg, 0)
+    special = np.sort(r.permutation(R)[:12])
+    recv[special[0], 5] = np.inf
+    recv[special[1], 7] = np.nan
+    recv[special[2:4]] = 0.0
+    recv[special[4:6]] *= np.float32(2.0 ** -110)
+    recv[special[6:8], ::9] *= np.float32(2.0 ** 40)
+    recv[special[8]] *= np.float32(2.0 ** -140)
+    recv[special[9]] *= np.float32(2.0 ** 90)
+    x, dw = H.dev(recv, "fp32"), [H.weights_to_dev(w, "fp32")]
+    so, se = torch.tensor([0, R], dtype=torch.int32, device=H.DEV), torch.zeros(1, dtype=torch.int32, device=H.DEV)
+    full = P.moe_ffn_workspace_bytes(R, Hd, F, act, "fp32")
+    out = []
+    for room in (full, full, full - 1):
+        out.append(torch.full((R, Hd), -7.0, device=H.DEV))
+        P.moe_expert_ffn(x, R, so, se, 1, dw, Hd, F, act, "fp32", out[-1], torch.empty(room, dtype=torch.uint8, device=H.DEV))
+    torch.cuda.synchronize()
+    assert torch.equal(out[0].view(torch.int32), out[1].view(torch.int32))       # the same bits on every run
+    a, b = H.host(out[0]), H.host(out[2])
+    assert np.array_equal(np.isfinite(a), np.isfinite(b)) and np.array_equal(np.isnan(a), np.isnan(b))
+    plain = np.setdiff1d(np.arange(R), special)
+    H.assert_close(a[plain], O.ffn(recv[plain], w["w1"], w["w_up"], w["w_down"], act), "fp32")
+    assert H.rms_rel_err(a[plain], b[plain]) < 1e-6
+    for row in special:                                          # each row on its own scale (sums of up to F products in two orders)
+        fin = np.isfinite(a[row])
+        if fin.any() and np.abs(b[row][fin]).max() > 0:
+            assert H.rel_err(a[row][fin], b[row][fin]) < 1e-5, row
+
+
 def test_expert_ffn_fp32_in_parts_takes_every_value(H):
     """Rows and weight rows of any scale, zeros in front, elements far apart, infinities, NaN."""
     R, Hd, F, n_local, nseg = 6000, 356, 1012, 2, 40
