@@ -472,10 +472,12 @@ __global__ __launch_bounds__(MAXT) void route_bf16_kernel(const uint16_t* __rest
     MOE_MARK(3);
     // selection: L lanes per token
     const int sub = threadIdx.x & (L - 1);
+    float wmax = 0.f;                                    // the largest expert norm, once per wave
+    for (int e = lane; e < E; e += 64) wmax = fmaxf(wmax, wn2[e]);
+    wmax = group_max<16>(wmax);
+    wmax = fmaxf(wmax, __shfl_xor(wmax, 16, 64));
+    wmax = fmaxf(wmax, __shfl_xor(wmax, 32, 64));
     for (int tsel = threadIdx.x / L; tsel < TP && tok0 + tsel < T; tsel += blockDim.x / L) {
-        float wmax = 0.f;                                // the largest expert norm
-        for (int e = sub; e < E; e += L) wmax = fmaxf(wmax, wn2[e]);
-        wmax = group_max<L>(wmax);
         const double min_gap = 2.0 * (double)((float)RUN * kLogitErr * sqrtf(xn2[tsel] * wmax));
         double kth = 0.0;
         const bool safe = select_group<NC, L, false, true>(zl + (size_t)tsel * ZP, E, k, renorm, tok0 + tsel, sub, min_gap, lds + tsel * kSelPitch,
