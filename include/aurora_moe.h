@@ -192,8 +192,10 @@ typedef struct {
 } moe_expert_w;
 
 /* Bytes of device workspace moe_expert_ffn needs for up to R_max rows (the
- * [R,F] intermediate, a tile map of about 1 KiB per 64 rows plus 1 MiB and, for
- * bf16, 64 MiB of fp32 partial tiles); 0 if an argument is invalid. */
+ * [R,F] intermediate, a tile map of about 1 KiB per 64 rows plus 1 MiB and the
+ * partial tiles of cut tiles: 64 MiB for bf16, 16.25 MiB for fp32); 0 if an argument
+ * is invalid.  moe_expert_ffn takes an fp32 workspace without the room for partial
+ * tiles as well and then cuts none. */
 size_t moe_ffn_workspace_bytes(int32_t R_max, int32_t H, int32_t F, int32_t act, int32_t dtype);
 
 /* Expert FFN (Sec. 2.1) over the rows this GPU received: rows
@@ -261,7 +263,7 @@ int moe_selfcheck_tile_shape(int32_t R, int32_t n_used, int32_t N, int32_t K, in
 int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* rows2);
 
 /* The two forms of the planner's flow player (the wider one on hosts with AVX-512) on an order of n GPUs: the same bits, as
- * they are played and after improving the order by exchanges.  Returns 1, 0 where there is only one form, or a negative
+ * they are played and after improving the order by exchanges; and the same order whether exchanges are played at the port bound or not.  Returns 1, 0 where there is only one form, or a negative
  * moe_status. */
 int moe_selfcheck_flow_player(int32_t n, const int64_t* D, const double* B, const int32_t* order);
 
