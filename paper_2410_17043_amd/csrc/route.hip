@@ -118,8 +118,8 @@ __device__ __forceinline__ void wave_lds_order() {
 // Selection for one token by a group of L = 4, 16 or 64 neighbouring lanes (sub = 0..L-1; lane `sub` looks after experts sub,
 // sub + L, ..., at most NC of them, read once from zr[0..E) in LDS): the k + 1 largest, ties to the lower index;
 // softmax weights; returns whether every gap between consecutive ones exceeds min_gap (a negative min_gap: only
-// the k largest are extracted and the answer means nothing), and the k-th largest in *kth.  sel: LDS scratch of this
-// token, kSelPitch bytes.  The extraction is a chain of k + 1 reductions and only that; what follows from its result
+// the k largest are extracted and the answer means nothing), and the k-th largest (ROUNDED: where the answer is no, a
+// number that is at most that) in *kth.  sel: LDS scratch of this token, kSelPitch bytes.  The extraction is a chain of k + 1 reductions and only that; what follows from its result
 // (exponentials, divisions, stores) is done for all k at once behind it.
 // FP32_WEIGHTS: the gate of fp32 layers (and of bf16 rows that are no multiple of 64 bytes).  Its sums keep the order in
 // which a wave with an expert per lane adds them (a tree over 64 lanes), and a renormalised weight is the quotient itself,
@@ -162,7 +162,7 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
             c[i] = live[i] ? (float)cv[i] : NONE;
             is_nan |= c[i] != c[i];
         }
-        if (__ballot(is_nan) >> (lane & ~(L - 1)) & ((1ull << L) - 1ull)) safe = false;
+        bool all = (__ballot(is_nan) >> (lane & ~(L - 1)) & ((1ull << L) - 1ull)) != 0;   // the k largest are not known even roughly
         for (int j = 0; j < n_take; ++j) {
             float best = c[0];
 #pragma unroll
@@ -180,14 +180,21 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
             if (j < k) {
                 if (takes) se[j] = sub + L * mine;
                 if (holders == 0u && sub == 0) se[j] = 0;
-                if (holders == 0u) safe = false;
+                if (holders == 0u) all = true;
             }
             if (j > 0 && best > NONE && !(last - best > gap + 0x1p-22f * fmaxf(fabsf(last), fabsf(best)))) safe = false;
             last = best;
         }
         wave_lds_order();                                // the group lies inside one wave
         zmax = zr[se[0]];
-        *kth = zr[se[k - 1]];
+        if (all) safe = false;
+        if (!safe) {
+            // logits that round to one number came in any order: the last one may be the largest of them, but the smallest of
+            // k different ones is at most the k-th largest
+            double least = zmax;
+            for (int j = 1; j < k; ++j) least = fmin(least, zr[se[j]]);
+            *kth = all ? -__builtin_huge_val() : least;
+        }
     } else
     for (int j = 0; j < n_take; ++j) {
         double best = 0.0;
@@ -309,7 +316,7 @@ __global__ __launch_bounds__(MAXT) void route_bf16_kernel(const uint16_t* __rest
     const int ZP = E + 4;                                                         // row pitch of zl: spreads the rows over the banks
     double* zl = reinterpret_cast<double*>(lds + ring_bytes);                     // [TP][ZP]
     double* bias_l = zl + (size_t)TP * ZP;                                        // [E]
-    double* redo_thr = bias_l + E;                                                // [TP] (k-th largest logit) - 2B of a token
+    double* redo_thr = bias_l + E;                                                // [TP] 2B below the k-th largest logit of a token, or less
     float* xn2 = reinterpret_cast<float*>(redo_thr + TP);                         // [TP]
     float* wn2 = xn2 + TP;                                                        // [E]
     int* redo_tok = reinterpret_cast<int*>(wn2 + E);                              // [TP] tokens to evaluate again
@@ -489,8 +496,8 @@ __global__ __launch_bounds__(MAXT) void route_bf16_kernel(const uint16_t* __rest
     }
     __syncthreads();
     // Tokens that could not be certified.  Every logit is within B of its true value, so an expert whose
-    // logit is more than 2B below the k-th largest is truly below k experts and cannot be selected: the true
-    // logits of the others (usually k + 1 of them) are evaluated with fp64 FMAs - a wave per (token, expert)
+    // logit is more than 2B below the k-th largest (or anything below that) is truly below k experts and cannot be selected: the
+    // true logits of the others (usually k + 1 of them) are evaluated with fp64 FMAs - a wave per (token, expert)
     // pair, the lanes sharing the hidden dimension, lane sums added in a fixed butterfly order - and put in
     // place of the approximate ones; the selection on the patched row is exact.
     const int n_redo = counters[0];

@@ -344,6 +344,41 @@ def test_route_leaves_out_experts_with_a_bias_of_minus_infinity(H, T, E, k, mask
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("T,E,k", [(300, 8, 4), (300, 16, 5), (300, 24, 4), (5000, 24, 5), (14000, 30, 4), (300, 64, 6), (5000, 64, 6), (14000, 64, 4), (300, 160, 6)])
+@pytest.mark.parametrize("what", ["common bias", "too few left", "too few above the lowest"])
+def test_route_orders_logits_that_rounding_cannot_tell_apart(H, T, E, k, what, dtype):
+    """Pairs of logits that are 2^-26 apart, which the sum of 32 products next to 1 loses: all logits on one fp32 number by a common
+    bias, or fewer experts than choices left by the bias (the others follow by index).  Every logit is exact in fp64."""
+    P = H.P
+    r = np.random.default_rng(E * k)
+    x, wg = np.zeros((T, 128), np.float32), np.zeros((E, 128), np.float32)
+    x[:, 0] = x[:, 32] = 1.0
+    x[:, 1] = 2.0 ** -13
+    x[np.arange(T), 33 + r.integers(0, 95, size=T)] = r.choice([1.0, -1.0, 0.5], size=T)
+    wg[:, 0], wg[:, 32] = 1.0, -1.0
+    for h in range(33, 128):                                     # up to 2^-5: less than half a spacing of 2^20
+        wg[:, h] = 2.0 ** -13 * r.permutation(np.arange(E) // 2 * (256 // E) + 1)
+    wg[r.permutation(E)[:E // 2], 1] = 2.0 ** -13
+    wg[1], wg[0, 33:] = wg[E - 1], 2.0 ** -5
+    wg[1, 1], wg[E - 1, 1] = 0.0, 2.0 ** -13
+    bias = np.full(E, {"common bias": 2.0 ** 20, "too few left": -np.inf, "too few above the lowest": np.finfo(np.float32).min}[what], np.float32)
+    if what != "common bias":
+        bias[np.concatenate([[0, 1, E - 1], 2 + r.permutation(E - 3)])[:k - 1]] = 0.0
+    z = x.astype(np.float64) @ wg.astype(np.float64).T + bias.astype(np.float64)
+    idx_ref = np.argsort(-z, axis=1, kind="stable")[:, :k]
+    p = np.exp(z - z.max(axis=1, keepdims=True))
+    p /= p.sum(axis=1, keepdims=True)
+    ctx = P.MoeCtx(T, 128, E, k, 1, dtype, 0, 0)
+    idx = torch.zeros((T, k), dtype=torch.int32, device=H.DEV)
+    w = torch.zeros((T, k), device=H.DEV)
+    P.moe_route(ctx, H.dev(x, dtype), H.dev(wg, dtype), torch.from_numpy(bias).to(H.DEV), idx, w)
+    torch.cuda.synchronize()
+    assert np.array_equal(H.host(idx), idx_ref)
+    assert H.rel_err(H.host(w), np.take_along_axis(p, idx_ref, axis=1)) < 1e-5
+    ctx.close()
+
+
 @pytest.mark.parametrize("T,k,E,cap", [
     (1, 1, 2, 0), (64, 1, 64, 1), (65, 3, 17, 9), (256, 2, 64, 0), (512, 1, 3, 100),        # lists that every wave of the scatter counts
     (171, 3, 16, 0), (100, 2, 65, 0),                                                         # one slot or one expert too many for that
