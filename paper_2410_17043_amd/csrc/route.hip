@@ -15,6 +15,7 @@
 //   route_mfma_kernel   every token in fp64 on the fp64 matrix cores: fp32 inputs and any H.
 #include "common.h"
 #include <algorithm>
+#include <climits>
 #include <type_traits>
 
 namespace {
@@ -102,9 +103,12 @@ template <int L> __device__ __forceinline__ float group_sum(float v) {
     else { v += dpp_move<kQuadXor2>(v); v += dpp_move<kQuadXor1>(v); }
     return v;
 }
-template <int L> __device__ __forceinline__ float group_max(float v) {
-    if (L == 16) { v = fmaxf(v, dpp_move<kRowRor8>(v)); v = fmaxf(v, dpp_move<kRowRor4>(v)); v = fmaxf(v, dpp_move<kRowRor2>(v)); v = fmaxf(v, dpp_move<kRowRor1>(v)); }
-    else { v = fmaxf(v, dpp_move<kQuadXor2>(v)); v = fmaxf(v, dpp_move<kQuadXor1>(v)); }
+__device__ __forceinline__ float larger_of(float a, float b) { return fmaxf(a, b); }
+__device__ __forceinline__ int larger_of(int a, int b) { return max(a, b); }
+template <int L, typename V> __device__ __forceinline__ V group_max(V v) {
+    auto with = [&](V other) { v = larger_of(v, other); };
+    if (L == 16) { with(dpp_move<kRowRor8>(v)); with(dpp_move<kRowRor4>(v)); with(dpp_move<kRowRor2>(v)); with(dpp_move<kRowRor1>(v)); }
+    else { with(dpp_move<kQuadXor2>(v)); with(dpp_move<kQuadXor1>(v)); }
     return v;
 }
 
@@ -118,19 +122,20 @@ __device__ __forceinline__ void wave_lds_order() {
 // Selection for one token by a group of L = 4, 16 or 64 neighbouring lanes (sub = 0..L-1; lane `sub` looks after experts sub,
 // sub + L, ..., at most NC of them, read once from zr[0..E) in LDS): the k + 1 largest, ties to the lower index;
 // softmax weights; returns whether every gap between consecutive ones exceeds min_gap (a negative min_gap: only
-// the k largest are extracted and the answer means nothing), and the k-th largest (ROUNDED: where the answer is no, a
-// number that is at most that) in *kth.  sel: LDS scratch of this token, kSelPitch bytes.  The extraction is a chain of k + 1 reductions and only that; what follows from its result
+// the k largest are extracted and the answer means nothing), and where the answer is no the k-th largest in
+// *kth.  sel: LDS scratch of this token, kSelPitch bytes.  The extraction is a chain of k + 1 reductions and only that; what follows from its result
 // (exponentials, divisions, stores) is done for all k at once behind it.
 // FP32_WEIGHTS: the gate of fp32 layers (and of bf16 rows that are no multiple of 64 bytes).  Its sums keep the order in
 // which a wave with an expert per lane adds them (a tree over 64 lanes), and a renormalised weight is the quotient itself,
 // rounded once: the product with a rounded reciprocal of the sum has a tenth more error (rms 7.7e-8 against 7.0e-8 at k = 4).
 //
 // ROUNDED: the extractions compare the logits rounded to fp32: one instruction per exchange instead of a dozen (fp64 compares with
-// their index).  The answer is then whether every gap exceeds min_gap and what the rounding can hide, 2^-23 of the larger
-// one; ties are never safe, and nor is anything among the k largest that is not finite.  Weights come from the fp64 logits as
-// before.  A token that is not safe has to be selected again without it.  Gate of 64 tokens, E = 64,
-// k = 6: 10.8 -> 9.4 us; 16 tokens, E = 8, k = 2: 7.8 -> 7.3; 16384 tokens, E = 64, k = 6: 39.8 -> 37.9, 36.8 with the same for the
-// tokens that are evaluated again.
+// their index).  Rounding keeps the order of all that it does not make equal, and logits that round alike are compared in
+// fp64 (a branch of the wave, for that extraction), so the result is the same.  With a NaN among the logits the answer is no,
+// *kth is -inf and nothing has been selected: the caller selects again without ROUNDED.
+// Gate of 64 tokens, E = 64, k = 6, H = 2048: 17.4 -> 14.6 us; 16 tokens, E = 8, k = 2: 7.8 -> 7.3; 16384 tokens, E = 64, k = 6: 42.6 ->
+// 38.8, 40.4 where a bias of 1e4 on all experts makes some logits round alike (67.8 when their tokens were evaluated
+// again instead); fp32 gate of 16384 tokens of zeros, E = 64, k = 6: 83.9 -> 83.7 (89.7 when all were selected again).
 constexpr int kSelPitch = MOE_MAX_K * 16;                  // values, then indices and weights
 template <int NC, int L, bool FP32_WEIGHTS = false, bool ROUNDED = false>
 __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int E, int k, int renorm, int t, int sub,
@@ -152,48 +157,65 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
     bool safe = true;
     if constexpr (ROUNDED) {
         static_assert(L < 64, "");
-        constexpr float NONE = -__builtin_huge_valf();
         const int lane = threadIdx.x & 63;
-        const float gap = (float)min_gap * 1.000001f + 0x1p-120f;   // rounded up; what lies below the range of fp32
-        float c[NC], last = 0.f;
+        auto in_group = [&](bool v) { return (__ballot(v) >> (lane & ~(L - 1)) & ((1ull << L) - 1ull)) != 0; };   // in any of its lanes
+        const float taken = __builtin_nanf("");              // loses against every number
+        float c[NC];
         bool is_nan = false;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
-            c[i] = live[i] ? (float)cv[i] : NONE;
-            is_nan |= c[i] != c[i];
+            c[i] = live[i] ? (float)cv[i] : taken;
+            is_nan |= live[i] && c[i] != c[i];
         }
-        bool all = (__ballot(is_nan) >> (lane & ~(L - 1)) & ((1ull << L) - 1ull)) != 0;   // the k largest are not known even roughly
+        if (in_group(is_nan)) {
+            *kth = -__builtin_huge_val();
+            return false;
+        }
+        const int n_groups = __popcll(__ballot(true)) / L;
+        int* se_next = reinterpret_cast<int*>(sz);           // the one behind the k largest
         for (int j = 0; j < n_take; ++j) {
             float best = c[0];
 #pragma unroll
             for (int i = 1; i < NC; ++i) best = fmaxf(best, c[i]);
             best = group_max<L>(best);
-            int mine = -1;                               // the lane's first candidate of this value
+            int mine = 0, hits = 0;                          // the lane's first candidate of this value, and how many it has
 #pragma unroll
             for (int i = NC - 1; i >= 0; --i)
-                if (c[i] == best) mine = i;
-            const unsigned holders = (unsigned)(__ballot(mine >= 0 && best > NONE) >> (lane & ~(L - 1))) & ((1u << L) - 1u);
-            const bool takes = holders != 0u && (holders & ((2u << sub) - 1u)) == (1u << sub);   // the first lane that holds it
+                if (c[i] == best) { mine = i; ++hits; }
+            bool takes = hits != 0;
+            if (__popcll(__ballot(takes)) != n_groups || __ballot(hits > 1)) {   // several, in some group of the wave
+                double z = 0.0;
+                int e = -1;
+#pragma unroll
+                for (int i = 0; i < NC; ++i)
+                    if (c[i] == best && (e < 0 || cv[i] > z)) { z = cv[i]; e = sub + L * i; }
+                // as two numbers in the order of the fp64 ones (+0: zeros are equal), then the lower index
+                const long long bits = __double_as_longlong(z + 0.0), key = bits ^ (bits >> 63 & 0x7fffffffffffffffll);
+                const int hi = takes ? (int)(key >> 32) : INT_MIN, lo = (int)((uint32_t)key ^ 0x80000000u);
+                const int top_hi = group_max<L>(hi);             // (no exchange under a condition)
+                const int top_lo = group_max<L>(hi == top_hi ? lo : INT_MIN);
+                takes &= hi == top_hi && lo == top_lo;
+                const int first = group_max<L>(takes ? -e : INT_MIN);
+                takes &= -e == first;
+                mine = e / L;
+            }
+            if (takes) (j < k ? se + j : se_next)[0] = sub + L * mine;
 #pragma unroll
             for (int i = 0; i < NC; ++i)
-                if (takes && i == mine) c[i] = NONE;
-            if (j < k) {
-                if (takes) se[j] = sub + L * mine;
-                if (holders == 0u && sub == 0) se[j] = 0;
-                if (holders == 0u) all = true;
-            }
-            if (j > 0 && best > NONE && !(last - best > gap + 0x1p-22f * fmaxf(fabsf(last), fabsf(best)))) safe = false;
-            last = best;
+                if (takes && i == mine) c[i] = taken;
         }
-        wave_lds_order();                                // the group lies inside one wave
+        wave_lds_order();                                    // the group lies inside one wave
         zmax = zr[se[0]];
-        if (all) safe = false;
-        if (!safe) {
-            // logits that round to one number came in any order: the last one may be the largest of them, but the smallest of
-            // k different ones is at most the k-th largest
-            double least = zmax;
-            for (int j = 1; j < k; ++j) least = fmin(least, zr[se[j]]);
-            *kth = all ? -__builtin_huge_val() : least;
+        if (min_gap >= 0.0) {
+            bool close = false;
+#pragma unroll
+            for (int m = 0; m < (MOE_MAX_K + L - 1) / L; ++m) {
+                if (L * m >= n_take - 1) break;
+                const int j = min(sub + L * m, n_take - 2);   // past the last gap: that one again
+                close |= !(zr[se[j]] - zr[*(j + 1 < k ? se + j + 1 : se_next)] > min_gap);
+            }
+            safe = !in_group(close);
+            if (!safe) *kth = zr[se[k - 1]];
         }
     } else
     for (int j = 0; j < n_take; ++j) {
@@ -574,7 +596,7 @@ __global__ __launch_bounds__(MAXT) void route_bf16_kernel(const uint16_t* __rest
     for (int f = threadIdx.x >> 4; f < n_redo; f += blockDim.x >> 4) {
         const int tsel = redo_tok[f];
         double kth = 0.0;
-        if (!select_group<(NC * L + 15) / 16, 16, false, true>(zl + (size_t)tsel * ZP, E, k, renorm, tok0 + tsel, threadIdx.x & 15, 0.0,
+        if (!select_group<(NC * L + 15) / 16, 16, false, true>(zl + (size_t)tsel * ZP, E, k, renorm, tok0 + tsel, threadIdx.x & 15, -1.0,
                                                                lds + tsel * kSelPitch, topk_idx, topk_w, &kth))
             select_group<(NC * L + 15) / 16, 16>(zl + (size_t)tsel * ZP, E, k, renorm, tok0 + tsel, threadIdx.x & 15, -1.0, lds + tsel * kSelPitch,
                                                  topk_idx, topk_w, &kth);
@@ -694,7 +716,7 @@ __global__ __launch_bounds__(NT == 1 ? 1024 : 512) void route_mfma_kernel(const 
         return;
     }
     for (int tt = threadIdx.x >> 4; tt < n_tok; tt += blockDim.x >> 4) {
-        if (!select_group<NC, 16, true, true>(zl + (size_t)tt * ZP, E, k, renorm, tok0 + tt, threadIdx.x & 15, 0.0, sel + tt * kSelPitch, topk_idx, topk_w, &kth))
+        if (!select_group<NC, 16, true, true>(zl + (size_t)tt * ZP, E, k, renorm, tok0 + tt, threadIdx.x & 15, -1.0, sel + tt * kSelPitch, topk_idx, topk_w, &kth))
             select_group<NC, 16, true>(zl + (size_t)tt * ZP, E, k, renorm, tok0 + tt, threadIdx.x & 15, -1.0, sel + tt * kSelPitch, topk_idx, topk_w, &kth);
     }
 }

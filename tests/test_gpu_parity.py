@@ -362,7 +362,7 @@ def test_route_orders_logits_that_rounding_cannot_tell_apart(H, T, E, k, what, d
     wg[r.permutation(E)[:E // 2], 1] = 2.0 ** -13
     wg[1], wg[0, 33:] = wg[E - 1], 2.0 ** -5
     wg[1, 1], wg[E - 1, 1] = 0.0, 2.0 ** -13
-    bias = np.full(E, {"common bias": 2.0 ** 20, "too few left": -np.inf, "too few above the lowest": np.finfo(np.float32).min}[what], np.float32)
+    bias = np.full(E, {"common bias": (-1) ** k * 2.0 ** 20, "too few left": -np.inf, "too few above the lowest": np.finfo(np.float32).min}[what], np.float32)
     if what != "common bias":
         bias[np.concatenate([[0, 1, E - 1], 2 + r.permutation(E - 3)])[:k - 1]] = 0.0
     z = x.astype(np.float64) @ wg.astype(np.float64).T + bias.astype(np.float64)
