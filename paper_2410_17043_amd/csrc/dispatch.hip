@@ -7,7 +7,7 @@
 // Rank pass (moe_traffic; moe_dispatch runs it too unless the caller has switched rank reuse on and the
 // traffic call on the same indices came directly before):
 //   every slot gets its rank among the slots of its expert, in slot order, plus the
-//   per-expert totals.  Up to 8192 slots this is ONE block of 16 waves (a launch costs
+//   per-expert totals.  Up to 8192 slots (more of few experts) this is ONE block of 16 waves (a launch costs
 //   more than the whole count at that size); beyond, two kernels:
 //     count_kernel   per block of 1024 consecutive slots: slots per expert (wave ballots)
 //     rank_kernel    adds up the counts of the blocks before its own, then the same ballots again
@@ -222,13 +222,18 @@ __global__ __launch_bounds__(256) void rank_kernel(const int32_t* __restrict__ i
 
 // Traffic call of 8192 slots with one block and of 16384 with two launches of many: 5.7 and 6.1 us (16 experts), 6.4 and 6.3
 // (64), 7.2 and 7.8 (200); 16384 slots with one block take 9.2 to 12.4.
-constexpr int kSmallMaxSlots = 8192;
+// Up to four experts take a ballot each, without a trip to LDS per round, which is the faster way from about 1024 slots on (8192
+// slots of one expert 5.7 -> 3.7 us, of two 4.2, of four 5.1).  One block then holds out longer against two launches of 6.0 to
+// 6.4 us: two experts take 5.1 at 12288 slots and 6.1 at 16384, three 5.7 at 12288, four 5.9 at 10240.
+constexpr int kFewExperts = 4;
+inline int small_max_slots(int E) { return E <= 2 ? 16384 : E == 3 ? 12288 : E == 4 ? 10240 : 8192; }
 
 // The whole rank pass in one block of 1024 threads.  Wave w owns the slots [w*spw, (w+1)*spw), round by round (at most
 // ROUNDS).  Ballots over the BITS bits of the expert id give every lane the lanes of its round with the same expert; the
 // wave's running per-expert counts sit in LDS.  Bound by what four waves per SIMD issue: a ballot per bit and not one per expert
 // (traffic call of 4096 slots of 16 experts 8.7 -> 4.0 us, of 8 6.2 -> 4.0, 32 slots of 16 6.5 -> 2.4; 4096 of 64, whose ids
 // have two bits less than the largest, 5.5 -> 4.4).
+// BITS = 0: few experts (up to kFewExperts), a ballot for each; the counts stay in scalar registers.
 template <int BITS, int ROUNDS>
 __global__ __launch_bounds__(1024) void small_rank_kernel(const int32_t* __restrict__ idx, int n_slots, int E, int G,
                                                           int capacity, SegMap map, int32_t* __restrict__ raw_count,
@@ -250,15 +255,31 @@ __global__ __launch_bounds__(1024) void small_rank_kernel(const int32_t* __restr
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        if (r >= rounds || base + r * 64 + lane >= n_slots || my_e[r] >= E) my_e[r] = -1;   // out of range: no rank
+        my_rank[r] = -1;
+    }
+    if constexpr (BITS == 0) {
+        for (int e = 0; e < E; ++e) {
+            int cnt = 0;
+#pragma unroll
+            for (int r = 0; r < ROUNDS; ++r) {
+                if (r >= rounds) continue;
+                const unsigned long long m = __ballot(my_e[r] == e);
+                if (my_e[r] == e) my_rank[r] = cnt + __popcll(m & lt);
+                cnt += __popcll(m);
+            }
+            if (lane == 0) wave_cnt[wave][e] = cnt;
+        }
+    } else {
     // the wave's running counts sit in its row of wave_cnt (only this wave touches it until the barrier below)
     for (int i = lane; i < E; i += 64) wave_cnt[wave][i] = 0;
     in_order();
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) {
-        my_rank[r] = -1;
         if (r < rounds) {
-            const int e = (base + r * 64 + lane < n_slots && my_e[r] < E) ? my_e[r] : -1;   // out of range: no rank
-            my_e[r] = e;
+            const int e = my_e[r];
             const unsigned long long peers = same_expert_lanes<BITS>(e);
             const int rk = __popcll(peers & lt);
             if (e >= 0) {
@@ -268,6 +289,7 @@ __global__ __launch_bounds__(1024) void small_rank_kernel(const int32_t* __restr
             }
             in_order();
         }
+    }
     }
     __syncthreads();
     if (threadIdx.x < E) {                                 // exclusive scan over the 16 waves
@@ -728,7 +750,7 @@ int launch_rank_pass(const moe_shape& s, const RankScratch& sc, const int32_t* i
                      int32_t* dest_count, int32_t* n_dropped, hipStream_t st) {
     const int n_slots = s.T * s.k;
     const int n_blocks = (n_slots + MOE_SLOTS_PER_BLOCK - 1) / MOE_SLOTS_PER_BLOCK;
-    if (n_slots <= kSmallMaxSlots) {
+    if (n_slots <= small_max_slots(s.E)) {
 #define MOE_SMALL(...)                                                                                                 \
     hipLaunchKernelGGL((small_rank_kernel<__VA_ARGS__>), dim3(1), dim3(1024), 0, st, idx, n_slots, s.E, s.G, s.capacity, map, \
                        sc.raw_count, sc.slot_rank, expert_count, dest_count, n_dropped)
@@ -738,7 +760,12 @@ int launch_rank_pass(const moe_shape& s, const RankScratch& sc, const int32_t* i
         else if (n_slots <= 4096) MOE_SMALL(BITS, 4);                                                                   \
         else MOE_SMALL(BITS, 8);                                                                                        \
     } while (0)
-        if (s.E <= 16) MOE_SMALL_BITS(4);
+        if (s.E <= kFewExperts && n_slots > 1024) {
+            if (n_slots <= 4096) MOE_SMALL(0, 4);
+            else if (n_slots <= 8192) MOE_SMALL(0, 8);
+            else if (n_slots <= 12288) MOE_SMALL(0, 12);
+            else MOE_SMALL(0, 16);
+        } else if (s.E <= 16) MOE_SMALL_BITS(4);
         else if (s.E <= 64) MOE_SMALL_BITS(6);
         else MOE_SMALL_BITS(8);
 #undef MOE_SMALL_BITS

@@ -382,6 +382,8 @@ def test_route_orders_logits_that_rounding_cannot_tell_apart(H, T, E, k, what, d
 @pytest.mark.parametrize("T,k,E,cap", [
     (1, 1, 2, 0), (64, 1, 64, 1), (65, 3, 17, 9), (256, 2, 64, 0), (512, 1, 3, 100),        # lists that every wave of the scatter counts
     (171, 3, 16, 0), (100, 2, 65, 0),                                                         # one slot or one expert too many for that
+    (1025, 1, 2, 0), (2048, 2, 3, 700), (4097, 1, 4, 0), (4096, 2, 3, 0), (10240, 1, 4, 0), (10241, 1, 4, 0),   # a ballot per expert, and not
+    (6144, 2, 3, 0), (12289, 1, 3, 0), (8193, 2, 2, 9000), (16384, 1, 2, 0),
     (16385, 1, 16, 900), (8200, 2, 17, 0), (8193, 2, 64, 0), (16400, 1, 65, 0),               # counts added up by every block of the rank kernel, or not
     (131072, 2, 64, 0), (131073, 2, 64, 5000)])                                               # 256 of its blocks, and one more
 def test_ranks_of_dispatch_alone_after_traffic_and_without_allocation(H, T, k, E, cap):
