@@ -11,7 +11,7 @@
 //   more than the whole count at that size); beyond, two kernels:
 //     count_kernel   per block of 1024 consecutive slots: slots per expert (wave ballots)
 //     rank_kernel    adds up the counts of the blocks before its own, then the same ballots again
-//   (three, with scan_kernel for the prefix over the blocks, where that would read too much).
+//   (three, with scan_kernel for the prefix over the blocks, for very many slots).
 //   The capacity rule, the traffic row and the drop count follow from the totals.
 //
 // Scatter (moe_dispatch): one kernel.  Every wave first turns the per-expert totals into segment
@@ -740,10 +740,11 @@ struct RankScratch {
     int32_t* slot_rank;    // [n_slots]
 };
 
-// What a block of rank_kernel adds up for itself: up to 1024 blocks' counts and 64 Ki of them.  Traffic call, three launches -> two:
-// 98304 slots of 64 experts 12.3 -> 8.0 us, 262144 18.7 -> 9.9, 1048576 (1024 blocks) 52.1 -> 28.2; of 8 experts 13.3 -> 8.3,
-// 18.9 -> 8.6, 50.5 -> 14.3.  Beyond, the counts would be read too many times over.
-constexpr int kScanBlocks = 1024, kScanCounts = 64 * 1024;
+// Counts of how many blocks a block of rank_kernel adds up for itself.  Traffic call, three launches -> two: 98304 slots of 64
+// experts 12.3 -> 8.0 us, 262144 18.7 -> 9.9, 1048576 (1024 blocks) 52.1 -> 28.2; of 8 experts 13.3 -> 8.3, 18.9 -> 8.6, 50.5 -> 14.3.
+// Beyond 64 experts a thread adds up all blocks of its expert, and the scan kernel's one block does that with 32 loads in
+// flight: 98304 slots of 96 experts 12.8 -> 11.4, 262144 (256 blocks) 19.5 -> 18.7, 524288 30.2 -> 31.5, 786432 of 65 42.2 -> 51.4.
+inline int max_scan_blocks(int E) { return E <= 64 ? 1024 : 256; }
 
 // Rank pass; the three count outputs may be NULL.
 int launch_rank_pass(const moe_shape& s, const RankScratch& sc, const int32_t* idx, const SegMap& map, int32_t* expert_count,
@@ -782,7 +783,7 @@ int launch_rank_pass(const moe_shape& s, const RankScratch& sc, const int32_t* i
 #define MOE_RANK(...)                                                                                                            \
     hipLaunchKernelGGL((rank_kernel<__VA_ARGS__>), dim3(n_blocks), dim3(256), lds, st, idx, n_slots, s.E, sc.block_hist, n_blocks, s.G, \
                        s.capacity, map, sc.raw_count, sc.slot_rank, expert_count, dest_count, n_dropped)
-        if (n_blocks <= kScanBlocks && n_blocks * s.E <= kScanCounts) {
+        if (n_blocks <= max_scan_blocks(s.E)) {
             if (s.E <= 16) MOE_RANK(4, 16);
             else if (s.E <= 64) MOE_RANK(6, 4);
             else MOE_RANK(8, 1);
