@@ -2195,43 +2195,41 @@ template <int MT, int NT> struct NarrowGeom {
     }
 };
 
-template <int EPI, int MT, int NT>
+// ONE: the list has one segment, whose tiles need no map (see ffn_impl).  An instantiation of its own: as a branch on the pointers it
+// cost the lists that have a map 1.5 % (300 expert FFNs, from cold memory as from warm), and itself 1 %.
+struct OneSegment { const int32_t *offset, *expert; int R, n_local; };
+template <int EPI, int MT, int NT, bool ONE>
 __global__ __launch_bounds__((64 * NarrowGeom<MT, NT>::WAVES), (NarrowGeom<MT, NT>::WAVES / 4)) void gemm_bf16_narrow_kernel(const uint16_t* __restrict__ A, int lda, TileMap m, ExpertTable tab,
-                                                                  int which0, int which1, int N, int K, uint16_t* __restrict__ C, int ldc, SegList one) {
+                                                                  int which0, int which1, int N, int K, uint16_t* __restrict__ C, int ldc, int tiles_n, OneSegment one) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     using G = NarrowGeom<MT, NT>;
     constexpr int NOUT = (EPI == EPI_SWIGLU) ? G::BN_ / 2 : G::BN_;
     auto word = [](const int32_t* p, int i) { return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p))[i]; };
-    // `one`: the only segment of the list, whose tiles need no map (see ffn_impl); else its pointers are NULL
-    struct Record { int row0, nrows, expert, gather; };
-    auto record = [&](int t) { return Record{word(m.row0, t), word(m.nrows, t), word(m.expert, t), word(m.gather, t)}; };
-    Record first = {0, 0, 0, 0};
     int n_tiles_m, one_lo = 0, one_len = 0, one_expert = 0;
-    if (one.offset) {
+    if (ONE) {
         one_expert = word(one.expert, 0);
         one_lo = max(word(one.offset, 0), 0);
         const int hi = min(word(one.offset, 1), one.R);
         one_len = one_expert >= 0 && one_expert < one.n_local && hi > one_lo ? hi - one_lo : 0;
         n_tiles_m = (one_len + G::BM_ - 1) / G::BM_;
     } else {
-        // The record of this block's tile does not wait for the number of tiles (there is room for as many as the grid has): one
-        // round trip to memory less in front of the operands.  300 expert FFNs of such shares 1.018 times faster, up to 1.11 (319
-        // rows of 3840 -> 2048 -> 3840 for four experts 118 -> 107 us), none slower; a grid padded so that an N-tile's blocks sit on
-        // one XCD left the XCDs uneven (18 N-tiles of 12 experts 97 -> 108 us).
         n_tiles_m = word(m.n_tiles, 0);
-        first = record(blockIdx.y);
-        asm volatile("" : "+s"(first.row0), "+s"(first.nrows), "+s"(first.expert), "+s"(first.gather));
     }
-    const int tile_n = blockIdx.x;
-    for (int tile_m = blockIdx.y; tile_m < n_tiles_m; tile_m += gridDim.y) {   // one, unless the list has more runs than experts
+    // The row tiles of a column tile on one XCD.  A grid of row and column tiles would let a block read its record without waiting
+    // for the number of tiles, which gives nothing (300 expert FFNs from cold memory: 1.001), but where weights are still in
+    // the L2s, or an expert has several row tiles, they come to several L2s: up to 14 % slower (182 rows of 1920 -> 4096 -> 1920 for two experts 28.9 -> 33.2 us).
+    const int total = ONE ? n_tiles_m : n_tiles_m * tiles_n;
+    for (int item = ONE ? blockIdx.y : blockIdx.x; item < total; item += ONE ? gridDim.y : gridDim.x) {   // one, unless the list has more runs than experts
+        const int tile_id = ONE ? 0 : skinny_tile(item, total);
+        const int tile_m = ONE ? item : __builtin_amdgcn_readfirstlane(tile_id % n_tiles_m);
+        const int tile_n = ONE ? blockIdx.x : __builtin_amdgcn_readfirstlane(tile_id / n_tiles_m);
         int row0 = one_lo + tile_m * G::BM_, nrows = min(G::BM_, one_len - tile_m * G::BM_), ex = one_expert;
         const int32_t* rel = nullptr;
-        if (!one.offset) {
-            const Record r = tile_m == (int)blockIdx.y ? first : record(tile_m);
-            row0 = r.row0;
-            nrows = r.nrows;
-            ex = r.expert;
-            if (r.gather) rel = m.rel + (size_t)tile_m * kRelPitch;
+        if (!ONE) {
+            row0 = word(m.row0, tile_m);
+            nrows = word(m.nrows, tile_m);
+            ex = word(m.expert, tile_m);
+            if (word(m.gather, tile_m)) rel = m.rel + (size_t)tile_m * kRelPitch;
         }
         auto pick = [&](int which) { return reinterpret_cast<const char*>(which == 0 ? tab.w1[ex] : which == 1 ? tab.w_up[ex] : tab.w_down[ex]); };
         const int n0 = tile_n * NOUT;
@@ -2702,21 +2700,28 @@ void take_narrow(int R, int n_used, int nseg, int H, int F, int act, int cus, in
     rows[1] = new_rows[1];
 }
 
-template <int EPI, int MT, int NT>
-int launch_bf16_narrow_nt(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
+template <int EPI, int MT, int NT, bool ONE>
+int launch_bf16_narrow_one(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
                           void* C, int ldc, int R, int nseg, int n_used, const SegList& one, hipStream_t st) {
     using G = NarrowGeom<MT, NT>;
     const int nout = (EPI == EPI_SWIGLU) ? G::BN_ / 2 : G::BN_;
     const int tiles_n = (N + nout - 1) / nout;
     static bool attr_done = false;
     if (!attr_done) {
-        MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_narrow_kernel<EPI, MT, NT>), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS));
+        MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_narrow_kernel<EPI, MT, NT, ONE>), hipFuncAttributeMaxDynamicSharedMemorySize, G::LDS));
         attr_done = true;
     }
-    hipLaunchKernelGGL((gemm_bf16_narrow_kernel<EPI, MT, NT>), dim3(tiles_n, std::min(max_tiles_of(R, G::BM_, nseg), (R + n_used * (G::BM_ - 1)) / G::BM_)), dim3(64 * G::WAVES), G::LDS, st,
-                       reinterpret_cast<const uint16_t*>(A), lda, m, tab, which0, which1, N, K, reinterpret_cast<uint16_t*>(C), ldc, one);
+    const int tiles_m = std::min(max_tiles_of(R, G::BM_, nseg), (R + n_used * (G::BM_ - 1)) / G::BM_);
+    hipLaunchKernelGGL((gemm_bf16_narrow_kernel<EPI, MT, NT, ONE>), ONE ? dim3(tiles_n, tiles_m) : dim3(tiles_m * tiles_n), dim3(64 * G::WAVES), G::LDS, st,
+                       reinterpret_cast<const uint16_t*>(A), lda, m, tab, which0, which1, N, K, reinterpret_cast<uint16_t*>(C), ldc, tiles_n, OneSegment{one.offset, one.expert, one.R, one.n_local});
     MOE_LAUNCH_CHECK("gemm_bf16_narrow_kernel");
     return MOE_OK;
+}
+template <int EPI, int MT, int NT>
+int launch_bf16_narrow_nt(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
+                          void* C, int ldc, int R, int nseg, int n_used, const SegList& one, hipStream_t st) {
+    return one.offset ? launch_bf16_narrow_one<EPI, MT, NT, true>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, n_used, one, st)
+                      : launch_bf16_narrow_one<EPI, MT, NT, false>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, n_used, one, st);
 }
 template <int EPI>
 int launch_bf16_narrow(NarrowForm f, const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
