@@ -2788,22 +2788,24 @@ bool cuts_parts(int R, int n_used, int N, int K, int act, int cus) {
     for (int t = lo; t <= hi; ++t) cut += plan_parts(t * tiles_n, cus, nk).n_cut > 0 ? 1 : -1;
     return cut >= 0;
 }
+// What is launched for up to max_items tiles; pieces of a last round take one round more at most.
+int parts_blocks(int max_items, int walk, int ncu, bool may_cut) { return walk_blocks(max_items + (may_cut ? ncu : 0), walk, ncu); }
 template <int EPI>
 int launch_f32_parts(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
                      void* C, int ldc, int R, int nseg, float* partial, hipStream_t st) {
     const int nout = (EPI == EPI_SWIGLU) ? XN / 2 : XN;
     const int tiles_n = (N + nout - 1) / nout, ncu = round_size(), walk = parts_walk_tiles(K);
-    auto launch = [&](auto kernel, bool& attr_done, int more) -> int {
+    auto launch = [&](auto kernel, bool& attr_done) -> int {
         if (!attr_done) {
             MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kXLds));
             attr_done = true;
         }
-        hipLaunchKernelGGL(kernel, dim3(walk_blocks(max_tiles_of(R, XM, nseg) * tiles_n + more, walk, ncu)), dim3(512), kXLds, st,
+        hipLaunchKernelGGL(kernel, dim3(parts_blocks(max_tiles_of(R, XM, nseg) * tiles_n, walk, ncu, partial != nullptr)), dim3(512), kXLds, st,
                            reinterpret_cast<const float*>(A), lda, m, tab, which0, which1, N, K, reinterpret_cast<float*>(C), ldc, tiles_n, ncu, walk, partial);
         return MOE_OK;
     };
     static bool attr_cut = false, attr_whole = false;
-    const int rc = partial ? launch(gemm_f32_parts_kernel<EPI, true>, attr_cut, ncu) : launch(gemm_f32_parts_kernel<EPI, false>, attr_whole, 0);
+    const int rc = partial ? launch(gemm_f32_parts_kernel<EPI, true>, attr_cut) : launch(gemm_f32_parts_kernel<EPI, false>, attr_whole);
     if (rc != MOE_OK) return rc;
     MOE_LAUNCH_CHECK("gemm_f32_parts_kernel");
     return MOE_OK;
@@ -2912,10 +2914,11 @@ extern "C" int moe_selfcheck_f32_walk(int32_t tiles_m, int32_t max_tiles_m, int3
         return moe_set_error(MOE_EINVAL, "moe_selfcheck_f32_walk: bad argument");
     const int walk = parts_walk_tiles(K), total = tiles_m * tiles_n, nk = ((K + XK - 1) / XK + 1) / 2 * 2;
     const PartsCut cuts[2] = {PartsCut{total, 0, 1, nk}, plan_parts(total, ncu, nk)};
-    for (const PartsCut& c : cuts) {
+    for (int may_cut = 0; may_cut < 2; ++may_cut) {       // either instantiation, by the grid that it is launched with
+        const PartsCut& c = cuts[may_cut];
         const int n_items = c.n_full + c.n_cut * c.parts;
         std::vector<int> seen((size_t)n_items, 0);
-        for (int b = 0; b < walk_blocks(max_tiles_m * tiles_n + ncu, walk, ncu); ++b) {
+        for (int b = 0; b < parts_blocks(max_tiles_m * tiles_n, walk, ncu, may_cut != 0); ++b) {
             const WalkRun run = walk_run(b, ncu, walk, n_items);
             int taken = 0;
             for (int item = run.item; item < run.end; item += ncu, ++taken) {
