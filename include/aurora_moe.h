@@ -279,6 +279,11 @@ int moe_selfcheck_f32_kernels(int32_t R, int32_t n_used, int32_t nseg, int32_t H
  * segment list (few tiles of 64 rows in at most 64 segments), or a negative moe_status. */
 int moe_selfcheck_f32_map(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu);
 
+/* Pieces along K into which the two GEMMs of such a share cut the tiles of their last round if its rows lie in tiles_m tiles of 128
+ * rows: 1 where none is cut at that number, 0 where the GEMM never cuts any.  parts2: HOST [2]. */
+int moe_selfcheck_f32_cuts(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t tiles_m,
+                           int32_t* parts2);
+
 /* Walk of the blocks of the fp32 kernel of 128-row tiles through tiles_m x tiles_n tiles, launched for up to max_tiles_m: checks
  * that every tile is taken by one block.  Returns the number of tiles a block takes at most, or a negative moe_status. */
 int moe_selfcheck_f32_walk(int32_t tiles_m, int32_t max_tiles_m, int32_t tiles_n, int32_t K, int32_t ncu);

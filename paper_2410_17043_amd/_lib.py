@@ -65,6 +65,7 @@ SIGNATURES = {
     "moe_selfcheck_narrow": (C.c_int, [_i32] * 7 + [_pi32]),
     "moe_selfcheck_f32_kernels": (C.c_int, [_i32] * 7 + [_pi32]),
     "moe_selfcheck_f32_map": (C.c_int, [_i32] * 7),
+    "moe_selfcheck_f32_cuts": (C.c_int, [_i32] * 8 + [_pi32]),
     "moe_selfcheck_f32_walk": (C.c_int, [_i32] * 5),
     "moe_selfcheck_walk": (C.c_int, [_i32] * 6),
     "moe_selfcheck_skinny_plan": (C.c_int, [_i32, _i32, _i32]),

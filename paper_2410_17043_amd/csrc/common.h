@@ -33,7 +33,7 @@ struct moe_ctx {
     moe_shape s;
     int32_t n_slots;      // T * k
     int32_t n_blocks;     // ceil(n_slots / MOE_SLOTS_PER_BLOCK)
-    int32_t* block_hist;  // device [n_blocks][E]: slots per expert in each block, later its exclusive prefix
+    int32_t* block_hist;  // device [n_blocks][E]: slots per expert in each block (where scan_kernel runs, later their exclusive prefix)
     int32_t* raw_count;   // device [E]: slots per expert before the capacity rule
     int32_t* slot_rank;   // device [n_slots]: rank of a slot among the slots of its expert (-1: index out of range)
     const void* rank_src; // host: the topk_idx pointer the LAST call on this context (a moe_traffic) ranked, else NULL

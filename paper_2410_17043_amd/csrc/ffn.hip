@@ -2788,6 +2788,12 @@ bool cuts_parts(int R, int n_used, int N, int K, int act, int cus) {
     for (int t = lo; t <= hi; ++t) cut += plan_parts(t * tiles_n, cus, nk).n_cut > 0 ? 1 : -1;
     return cut >= 0;
 }
+// The GEMMs of a share whose tiles may be cut; the counters of the pieces lie behind the tile maps.
+void take_cuts(int R, int n_used, int nseg, int H, int F, int act, int cus, const bool (&in_parts)[2], bool (&cuts)[2]) {
+    const bool fit = maps_fit(R, nseg, in_parts[0] ? XM : FM, in_parts[1] ? XM : FM);
+    cuts[0] = fit && in_parts[0] && cuts_parts(R, n_used, F, H, act, cus);
+    cuts[1] = fit && in_parts[1] && cuts_parts(R, n_used, H, F, -1, cus);
+}
 // What is launched for up to max_items tiles; pieces of a last round take one round more at most.
 int parts_blocks(int max_items, int walk, int ncu, bool may_cut) { return walk_blocks(max_items + (may_cut ? ncu : 0), walk, ncu); }
 template <int EPI>
@@ -2907,6 +2913,21 @@ extern "C" int moe_selfcheck_f32_map(int32_t R, int32_t n_used, int32_t nseg, in
     if (rc != MOE_OK) return rc;
     const bool in_parts[2] = {rows2[0] == XM, rows2[1] == XM};
     return f32_needs_map(R, n_used, nseg, H, F, act, ncu, in_parts) ? 1 : 0;
+}
+
+extern "C" int moe_selfcheck_f32_cuts(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t tiles_m, int32_t* parts2) {
+    int32_t rows2[2];
+    const int rc = moe_selfcheck_f32_kernels(R, n_used, nseg, H, F, act, ncu, rows2);
+    if (rc != MOE_OK) return rc;
+    if (tiles_m < 0 || !parts2) return moe_set_error(MOE_EINVAL, "moe_selfcheck_f32_cuts: bad argument");
+    const bool in_parts[2] = {rows2[0] == XM, rows2[1] == XM};
+    bool cuts[2];
+    take_cuts(R, n_used, nseg, H, F, act, ncu, in_parts, cuts);
+    for (int g = 0; g < 2; ++g) {
+        const int N = g == 0 ? F : H, K = g == 0 ? H : F, cols = g == 0 && act == MOE_ACT_SWIGLU ? XN / 2 : XN;
+        parts2[g] = cuts[g] ? plan_parts(tiles_m * ((N + cols - 1) / cols), ncu, ((K + XK - 1) / XK + 1) & ~1).parts : 0;
+    }
+    return MOE_OK;
 }
 
 extern "C" int moe_selfcheck_f32_walk(int32_t tiles_m, int32_t max_tiles_m, int32_t tiles_n, int32_t K, int32_t ncu) {
@@ -3173,11 +3194,9 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     MapJobs jobs;
     jobs.job[0] = MapJob{bm[0], max_tiles_of(R, bm[0], nseg), tilemap_at(workspace, R)};
     jobs.job[1] = (bm[1] == bm[0]) ? jobs.job[0] : MapJob{bm[1], max_tiles_of(R, bm[1], nseg), tilemap_at(workspace, R, 1, jobs.job[0].max_tiles)};
-    float* f32_pieces[2] = {nullptr, nullptr};            // where an fp32 GEMM's tiles are cut
-    if (dtype == MOE_F32 && pieces_fit && maps_fit(R, nseg, bm[0], bm[1])) {
-        if (in_parts[0] && cuts_parts(R, n_used, F, H, act, round_size())) f32_pieces[0] = partial;
-        if (in_parts[1] && cuts_parts(R, n_used, H, F, -1, round_size())) f32_pieces[1] = partial;
-    }
+    bool cuts[2] = {false, false};
+    if (dtype == MOE_F32 && pieces_fit) take_cuts(R, n_used, nseg, H, F, act, round_size(), in_parts, cuts);
+    float* const f32_pieces[2] = {cuts[0] ? partial : nullptr, cuts[1] ? partial : nullptr};   // where an fp32 GEMM's tiles are cut
     jobs.done = (dtype == MOE_BF16 || f32_pieces[0] || f32_pieces[1]) ? tilemap_at(workspace, R, 0, max_tiles_for(R) - 2).rel : nullptr;
     if (jobs.done) {
         jobs.job[0].m.done = jobs.done;

@@ -193,11 +193,13 @@ DISPATCH_CASES = [
     (small("c3_switch", T=2100, H=64), 7),
     (small("c5_finegrained", T=1111, H=136), 0),
     (small("c5_finegrained", T=700, H=64, E=160, k=9, G=16), 30),
-    # more than 16384 slots: the multi-block counting path
+    # more than 8192 slots: many blocks count
     (small("c5_finegrained", T=3100, H=64), 0),
     (small("c3_switch", T=20011, H=32), None),
-    (small("c2_mixtral", T=8193, H=64), 0),               # 16386 slots, just over the single-block limit
-    (small("c2_mixtral", T=8192, H=64), 0),               # 16384 slots, the single-block limit itself
+    (small("c2_mixtral", T=8193, H=64), 0),               # 16386 slots, the last block of 1024 nearly empty
+    (small("c2_mixtral", T=8192, H=64), 0),               # 16384 slots, the last one full
+    (small("c2_mixtral", T=4097, H=64), 0),               # 8194 slots, just over the single-block limit
+    (small("c2_mixtral", T=4096, H=64), 0),               # 8192 slots, the single-block limit itself
     # row lengths that pick the other copy geometries: several short rows per wave (1, 2, 4 KB rows; a ragged
     # last wave), rows longer than a wave's 8 KB cut into pieces (a whole number of pieces and a ragged one)
     (small("c2_mixtral", T=203, H=512), 0),               # 1 KB rows: 8 tokens per wave
@@ -377,6 +379,31 @@ def test_route_orders_logits_that_rounding_cannot_tell_apart(H, T, E, k, what, d
     assert np.array_equal(H.host(idx), idx_ref)
     assert H.rel_err(H.host(w), np.take_along_axis(p, idx_ref, axis=1)) < 1e-5
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("T,E,k", [(40, 8, 2), (300, 24, 4), (5000, 64, 6), (14000, 30, 3), (14000, 64, 6), (40, 160, 6)])
+def test_route_rows_with_nan_or_infinities_change_no_other(H, T, E, k, dtype):
+    """A few tokens whose logits are no numbers, among tokens of zeros (all logits equal: the first k experts) and ordinary ones."""
+    r = np.random.default_rng(T + E)
+    x, wg = W.round_to_dtype(r.standard_normal((T, 96)).astype(np.float32), dtype), W.round_to_dtype(r.standard_normal((E, 96)).astype(np.float32), dtype)
+    kind = r.integers(0, 6, size=T)
+    x[kind == 0] = 0.0
+    odd = x.copy()
+    odd[kind == 1, 3], odd[kind == 2, 50], odd[kind == 3, 7] = np.nan, np.inf, -np.inf
+    got = []
+    for rows in (x, odd):
+        ctx = H.P.MoeCtx(T, 96, E, k, 1, dtype, 1, 0)
+        idx, w = torch.full((T, k), -7, dtype=torch.int32, device=H.DEV), torch.full((T, k), -7.0, device=H.DEV)
+        H.P.moe_route(ctx, H.dev(rows, dtype), H.dev(wg, dtype), None, idx, w)
+        torch.cuda.synchronize()
+        got.append((H.host(idx), H.host(w)))
+        ctx.close()
+    same = (kind == 0) | (kind > 3)
+    assert np.array_equal(got[0][0][same], got[1][0][same]) and np.array_equal(got[0][1][same], got[1][1][same])
+    assert np.array_equal(got[1][0][kind == 0], np.tile(np.arange(k), (int((kind == 0).sum()), 1)))
+    z = x.astype(np.float64) @ wg.astype(np.float64).T
+    assert np.array_equal(got[0][0], np.argsort(-z, axis=1, kind="stable")[:, :k])
 
 
 @pytest.mark.parametrize("T,k,E,cap", [
@@ -870,24 +897,29 @@ def f32_rows(R, n_local, nseg, Hd, F, act):
     return list(got)
 
 
-@pytest.mark.parametrize("R,Hd,F,act,cut", [(8355, 512, 2048, 0, (0, 8)), (6600, 640, 1300, 1, (0, 5)), (3071, 1024, 2816, 2, (4, 0))])
-def test_expert_ffn_fp32_in_parts_tiles_cut_along_k(H, R, Hd, F, act, cut):
+@pytest.mark.parametrize("R,Hd,F,n_local,nseg,act,cut", [
+    (8355, 512, 2048, 1, 1, 0, [2, 8]), (6600, 640, 1300, 1, 1, 1, [0, 5]), (3071, 1024, 2816, 1, 1, 2, [4, 0]),
+    # several experts in ragged runs (rows of a cut tile from all over), both map kernels, and one that may cut but has nothing to
+    (6619, 952, 296, 4, 9, 2, [3, 0]), (8499, 512, 1012, 2, 9, 0, [2, 4]), (8301, 452, 1016, 2, 90, 1, [2, 4]), (8142, 984, 472, 4, 65, 2, [4, 2]),
+    (6238, 476, 656, 2, 9, 2, [1, 0])])
+def test_expert_ffn_fp32_in_parts_tiles_cut_along_k(H, R, Hd, F, n_local, nseg, act, cut):
     """Tiles of a last round in pieces, against the same tiles whole (a workspace without room for pieces) and the oracle: also for
     rows of huge, tiny and infinite elements, NaN and zeros, whose sums no piece may judge alone."""
     import ctypes as C
     from paper_2410_17043_amd import _lib
-    P = H.P
-    rows2 = (C.c_int32 * 2)()
-    assert _lib.load().moe_selfcheck_f32_kernels(R, 1, 1, Hd, F, act, 256, rows2) == 0 and list(rows2) == [128, 128]
-    for g, (N, K) in enumerate(((F, Hd), (Hd, F))):            # pieces of a tile in either GEMM, if any
-        cols = 64 if g == 0 and act == 2 else 128
-        rest, nk = -(-R // 128) * -(-N // cols) % 256, (-(-K // 32) + 1) // 2 * 2
-        assert cut[g] == 0 or (0 < rest <= 128 and min(256 // rest, nk // 8) == cut[g])
+    P, lib = H.P, _lib.load()
+    r = np.random.default_rng(R + nseg)
+    off, exp = make_segments(r, R, nseg, n_local)
+    c_off, c_exp, parts2 = (C.c_int32 * (nseg + 1))(*off), (C.c_int32 * nseg)(*exp), (C.c_int32 * 2)()
+    tiles_m = lib.moe_selfcheck_tile_map(c_off, c_exp, nseg, R, 128, n_local, 1)
+    assert tiles_m > 0 and lib.moe_selfcheck_f32_cuts(R, min(n_local, nseg), nseg, Hd, F, act, 256, tiles_m, parts2) == 0
+    assert list(parts2) == cut                                   # pieces of a tile in either GEMM; 1: none, but it could
     cfg = small("c1_tiny_fp32", H=Hd, F=F, act=act, dtype="fp32")
-    r = np.random.default_rng(R)
     recv = r.standard_normal((R, Hd)).astype(np.float32)
-    w = W.make_expert_weights(cfg, 0)
+    experts = [W.make_expert_weights(cfg, e) for e in range(n_local)]
     special = np.sort(r.permutation(R)[:12])
+    plain = np.setdiff1d(np.arange(R), special)
+    ref = O.expert_ffn(recv, off, exp, experts, act)[plain]
     recv[special[0], 5] = np.inf
     recv[special[1], 7] = np.nan
     recv[special[2:4]] = 0.0
@@ -895,20 +927,20 @@ def test_expert_ffn_fp32_in_parts_tiles_cut_along_k(H, R, Hd, F, act, cut):
     recv[special[6:8], ::9] *= np.float32(2.0 ** 40)
     recv[special[8]] *= np.float32(2.0 ** -140)
     recv[special[9]] *= np.float32(2.0 ** 90)
-    x, dw = H.dev(recv, "fp32"), [H.weights_to_dev(w, "fp32")]
-    so, se = torch.tensor([0, R], dtype=torch.int32, device=H.DEV), torch.zeros(1, dtype=torch.int32, device=H.DEV)
+    x, dw = H.dev(recv, "fp32"), [H.weights_to_dev(w, "fp32") for w in experts]
+    so, se = torch.tensor(off, dtype=torch.int32, device=H.DEV), torch.tensor(exp, dtype=torch.int32, device=H.DEV)
     full = P.moe_ffn_workspace_bytes(R, Hd, F, act, "fp32")
     out = []
     for room in (full, full, full - 1):
         out.append(torch.full((R, Hd), -7.0, device=H.DEV))
-        P.moe_expert_ffn(x, R, so, se, 1, dw, Hd, F, act, "fp32", out[-1], torch.empty(room, dtype=torch.uint8, device=H.DEV))
+        P.moe_expert_ffn(x, R, so, se, nseg, dw, Hd, F, act, "fp32", out[-1], torch.empty(room, dtype=torch.uint8, device=H.DEV))
     torch.cuda.synchronize()
     assert torch.equal(out[0].view(torch.int32), out[1].view(torch.int32))       # the same bits on every run
     a, b = H.host(out[0]), H.host(out[2])
     assert np.array_equal(np.isfinite(a), np.isfinite(b)) and np.array_equal(np.isnan(a), np.isnan(b))
-    plain = np.setdiff1d(np.arange(R), special)
-    H.assert_close(a[plain], O.ffn(recv[plain], w["w1"], w["w_up"], w["w_down"], act), "fp32")
+    H.assert_close(a[plain], ref, "fp32")
     assert H.rms_rel_err(a[plain], b[plain]) < 1e-6
+    assert (max(cut) > 1) != np.array_equal(a[plain], b[plain])                 # sums in another order, or the same
     for row in special:                                          # each row on its own scale (sums of up to F products in two orders)
         fin = np.isfinite(a[row])
         if fin.any() and np.abs(b[row][fin]).max() > 0:

@@ -41,7 +41,7 @@ def one_call(H, cfg, seed):
 def test_noalloc_dispatch_matches_dispatch_twice_in_a_row():
     from tests import harness as H
     assert torch.cuda.is_available()
-    big = W.scaled(W.get_config("c5_finegrained"), T=3500, H=64)          # 21000 slots, 64 experts: three-kernel rank pass
+    big = W.scaled(W.get_config("c5_finegrained"), T=3500, H=64)          # 21000 slots, 64 experts: two-kernel rank pass
     small = W.scaled(W.get_config("c3_switch"), T=700, H=128)             # 700 slots, capacity drops: one-block rank pass
     one_call(H, big, 1)
     one_call(H, small, 2)
