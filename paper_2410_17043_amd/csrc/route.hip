@@ -167,7 +167,7 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
             c[i] = live[i] ? (float)cv[i] : taken;
             is_nan |= live[i] && c[i] != c[i];
         }
-        if (in_group(is_nan)) {
+        if (__builtin_expect(in_group(is_nan), 0)) {
             *kth = -__builtin_huge_val();
             return false;
         }
@@ -183,7 +183,7 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
             for (int i = NC - 1; i >= 0; --i)
                 if (c[i] == best) { mine = i; ++hits; }
             bool takes = hits != 0;
-            if (__popcll(__ballot(takes)) != n_groups || __ballot(hits > 1)) {   // several, in some group of the wave
+            if (__builtin_expect(__popcll(__ballot(takes)) != n_groups || __ballot(hits > 1), 0)) {   // several, in some group of the wave
                 double z = 0.0;
                 int e = -1;
 #pragma unroll
