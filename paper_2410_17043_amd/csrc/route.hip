@@ -521,14 +521,15 @@ __global__ __launch_bounds__(MAXT) void route_bf16_kernel(const uint16_t* __rest
     // logit is more than 2B below the k-th largest (or anything below that) is truly below k experts and cannot be selected: the
     // true logits of the others (usually k + 1 of them) are evaluated with fp64 FMAs - a wave per (token, expert)
     // pair, the lanes sharing the hidden dimension, lane sums added in a fixed butterfly order - and put in
-    // place of the approximate ones; the selection on the patched row is exact.
+    // place of the approximate ones; the selection on the patched row is exact.  A logit that the bias makes -inf is exact as it is:
+    // 16384 tokens of which it leaves 5 of 64 experts for k = 6 take 108 us with it, 862 with all 64 evaluated.
     const int n_redo = counters[0];
     MOE_MARK(4);
     if (TIMED && threadIdx.x == 0) marks[(size_t)blockIdx.x * 16 * 8 + 6] = n_redo;
     if (n_redo == 0) return;                             // block-uniform
     for (int q = threadIdx.x; q < n_redo * E; q += blockDim.x) {
         const int tsel = redo_tok[q / E], e = q % E;
-        if (zl[(size_t)tsel * ZP + e] >= redo_thr[tsel]) pairs[atomicAdd(&counters[1], 1)] = (tsel << 16) | e;
+        if (zl[(size_t)tsel * ZP + e] >= redo_thr[tsel] && bias_l[e] > -__builtin_huge_val()) pairs[atomicAdd(&counters[1], 1)] = (tsel << 16) | e;
     }
     __syncthreads();
     const int n_pairs = counters[1];
