@@ -135,7 +135,8 @@ __device__ __forceinline__ void wave_lds_order() {
 // *kth is -inf and nothing has been selected: the caller selects again without ROUNDED.
 // Gate of 64 tokens, E = 64, k = 6, H = 2048: 17.4 -> 14.6 us; 16 tokens, E = 8, k = 2: 7.8 -> 7.3; 16384 tokens, E = 64, k = 6: 42.6 ->
 // 38.8, 40.4 where a bias of 1e4 on all experts makes some logits round alike (67.8 when their tokens were evaluated
-// again instead); fp32 gate of 16384 tokens of zeros, E = 64, k = 6: 83.9 -> 83.7 (89.7 when all were selected again).
+// again instead); fp32 gate of 16384 tokens of zeros, E = 64, k = 6: 83.9 -> 83.7 (89.7 when all were selected again).  Gaps are
+// checked behind the chain, in fp64: a check of the rounded ones inside it gains 0.5 us where k = 1 and loses as much at k = 8.
 constexpr int kSelPitch = MOE_MAX_K * 16;                  // values, then indices and weights
 template <int NC, int L, bool FP32_WEIGHTS = false, bool ROUNDED = false>
 __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int E, int k, int renorm, int t, int sub,
@@ -167,7 +168,7 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
             c[i] = live[i] ? (float)cv[i] : taken;
             is_nan |= live[i] && c[i] != c[i];
         }
-        if (__builtin_expect(in_group(is_nan), 0)) {
+        if (in_group(is_nan)) {
             *kth = -__builtin_huge_val();
             return false;
         }
@@ -183,7 +184,9 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
             for (int i = NC - 1; i >= 0; --i)
                 if (c[i] == best) { mine = i; ++hits; }
             bool takes = hits != 0;
-            if (__builtin_expect(__popcll(__ballot(takes)) != n_groups || __ballot(hits > 1), 0)) {   // several, in some group of the wave
+            // several, in some group of the wave (out of the way in the 16-lane kernels, whose code is cold in decode steps)
+            const bool several = __popcll(__ballot(takes)) != n_groups || __ballot(hits > 1);
+            if (L == 16 ? __builtin_expect(several, 0) : several) {
                 double z = 0.0;
                 int e = -1;
 #pragma unroll
@@ -198,11 +201,15 @@ __device__ __forceinline__ bool select_group(const double* __restrict__ zr, int 
                 const int first = group_max<L>(takes ? -e : INT_MIN);
                 takes &= -e == first;
                 mine = e / L;
+#pragma unroll
+                for (int i = 0; i < NC; ++i)
+                    if (takes && i == mine) c[i] = taken;
+            } else {
+#pragma unroll
+                for (int i = 0; i < NC; ++i)
+                    if (c[i] == best) c[i] = taken;
             }
             if (takes) (j < k ? se + j : se_next)[0] = sub + L * mine;
-#pragma unroll
-            for (int i = 0; i < NC; ++i)
-                if (takes && i == mine) c[i] = taken;
         }
         wave_lds_order();                                    // the group lies inside one wave
         zmax = zr[se[0]];
