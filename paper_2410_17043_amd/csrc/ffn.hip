@@ -10,8 +10,8 @@
 // expert are merged, tiles never straddle experts), so nothing waits for the host.
 //
 // bf16 path: 256x256 block tile (192x256 or 128x128 where that fills the chip better, see take_shapes), 32-wide
-// k-tiles, 4 waves in 2x2, each wave 128x128 = 4x4
-// tiles of v_mfma_f32_32x32x16_bf16 with fp32 accumulators (256 accumulator registers per
+// k-tiles, 4 waves in 2x2, each wave 128x128 = 8x8
+// tiles of v_mfma_f32_16x16x32_bf16 with fp32 accumulators (256 accumulator registers per
 // lane); operands go global -> LDS directly (no register staging) through a 5-stage ring that
 // fills the whole 160 KB LDS, in an XOR-swizzled layout that makes every ds_read_b128 of an
 // MFMA operand conflict-free on the 64 LDS banks.  Loads, LDS reads and MFMAs are software
@@ -900,7 +900,7 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int BK = 32, STAGES = 5;
-// Block tile of MI x NJ: the 4 waves are 2 x 2, a wave holds MI x NJ tiles of 32 x 32.
+// Block tile of MI x NJ: the 4 waves are 2 x 2, a wave holds 32 MI rows by 32 NJ weight rows.
 //   4 x 4  256 x 256, all 160 KB of LDS, one block per CU: the fewest operand bytes per flop
 //   3 x 4  192 x 256, 140 KB, one block per CU
 //   2 x 2  128 x 128, 80 KB, two blocks per CU
@@ -920,16 +920,17 @@ constexpr int BM = TileGeom<4, 4>::BM;         // rows of the largest tile
 // 16 bytes and is filled by ONE wave-wide direct-to-LDS load (lane l fills slot l).
 // Inside a block the rows are kept row-major (4 slots per row, so 4 neighbouring
 // lanes fetch 64 contiguous bytes of one row from memory), with the 16-byte chunk
-// index XOR-ed by row/4:
-//     slot(r, c) = 4*r + (c ^ (r >> 2)),   r = 0..15, c = 0..3.
-// The LDS has 64 banks and serves a ds_read_b128 sixteen lanes at a time; the 16
-// lanes of one MFMA operand read (16 consecutive rows, same chunk) then fall on
-// slots with 16 different values of slot % 16, i.e. on all 64 banks once.
-__device__ __forceinline__ int slot_of(int r, int c) { return (r << 2) + (c ^ (r >> 2)); }
+// index XOR-ed by -row/4:
+//     slot(r, c) = 4*r + (c ^ (-(r >> 2) & 3)),   r = 0..15, c = 0..3.
+// The LDS has 64 banks and serves a ds_read_b128 sixteen lanes at a time: lanes 0-3, 12-15 and 20-27 of the
+// lower half, its others, and the same of the upper half.  Those of an MFMA operand read - one chunk of 16 rows, or chunk l / 16
+// of row l % 16 - fall on 16 different values of slot % 16, i.e. on all 64 banks once.  (With r >> 2 in place of its
+// negative the second kind of read takes twice as long: 256 x 256 tiles 5 % slower.)
+__device__ __forceinline__ int slot_of(int r, int c) { return (r << 2) + (c ^ (-(r >> 2) & 3)); }
 // inverse for the loading lane: which (row, chunk) of the block lane l must fetch
 __device__ __forceinline__ void rc_of_slot(int l, int* r, int* c) {
     *r = l >> 2;
-    *c = (l & 3) ^ (l >> 4);
+    *c = (l & 3) ^ (-(l >> 4) & 3);
 }
 // byte offset of (row, chunk) inside an operand tile
 __device__ __forceinline__ int tile_off(int row, int c) { return ((row >> 4) << 10) + (slot_of(row & 15, c) << 4); }
@@ -1192,7 +1193,7 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_parts_kernel(const float* __r
     struct Source { __amdgpu_buffer_rsrc_t a, b; uint32_t a_voff, b_voff; int k0; };
     constexpr uint32_t kNoOffset = 0xFFFFFFF0u;               // past the end of the buffer (row offsets end below it, see ffn_impl)
     // what this lane fetches: chunk `lc` of tile row 16 wave + lane / 4, of A and of B; it goes to slot `lane` of block `wave`
-    const int lc = (lane & 3) ^ (lane >> 4);
+    const int lc = (lane & 3) ^ (-(lane >> 4) & 3);
     auto weights = [&](int which, int ex) { return reinterpret_cast<const char*>(which == 0 ? tab.w1[ex] : which == 1 ? tab.w_up[ex] : tab.w_down[ex]); };
     auto describe = [&](int id, Tile& t, Source& s) {
         int tile_m, tile_n;
@@ -1438,12 +1439,12 @@ template <int EPI, int MI, int NJ> struct EpiGeom {
     static constexpr int NJO = NW / 32;                            // 32-wide output column tiles per wave
     static constexpr int ROWS = 32 * MI;                           // rows per wave
 };
-// Activation and store of a wave's part of a tile: acc[i][j][e] is output row 32 i + lane % 32 and output column
-// j * 32 + (e / 4) * 8 + (lane / 32) * 4 + e % 4.  Up to 64 columns at a time are packed to bf16, transposed through
+// Activation and store of a wave's part of a tile: acc[i][j][e] is output row 16 i + lane % 16 and output column
+// 16 j + lane / 16 * 4 + e.  32 rows of up to 64 columns at a time are packed to bf16, transposed through
 // `region` (4 KB of LDS of this wave's own; LDS accesses of a wave execute in order) and stored as whole lines: stores
 // of 32 bytes per row straight from the registers took 13 us per 256 x 256 tile instead of 4.
-// Region: rows of CH 16-byte chunks, chunk c of row r at slot c ^ (r / (16 / CH)) % CH, the 8-byte halves of a chunk
-// exchanged in rows 16-31: both the 8-byte writes (32 rows, one chunk) and the 16-byte reads touch all 64 banks once.
+// Region: rows of CH 16-byte chunks, chunk c of row r at slot c ^ (r / (16 / CH)) % CH: both the 8-byte writes (half a wave:
+// 16 rows, one chunk) and the 16-byte reads touch all 64 banks once.
 // An accumulator element on its way to the vector unit.  The large tiles' accumulators fill the accumulation registers;
 // left to itself the register allocator moves whole 16-element tuples out of them at every use and spills.
 template <bool IN_AGPR> __device__ __forceinline__ float read_acc(float a) {
@@ -1453,7 +1454,7 @@ template <bool IN_AGPR> __device__ __forceinline__ float read_acc(float a) {
     return v;
 }
 template <int EPI, int MI, int NJ, bool IN_AGPR, bool GATHER>
-__device__ __forceinline__ void store_tile(const f32x16 (&acc)[MI][NJ], int lane0, unsigned char* region, __amdgpu_buffer_rsrc_t dst,
+__device__ __forceinline__ void store_tile(const f32x4 (&acc)[2 * MI][2 * NJ], int lane0, unsigned char* region, __amdgpu_buffer_rsrc_t dst,
                                            int first_row, int nrows, const int32_t* __restrict__ rel, int ldc) {
     constexpr int NJO = EpiGeom<EPI, MI, NJ>::NJO;
     constexpr int JP = NJO == 1 ? 1 : 2, CH = 4 * JP, RPI = 64 / CH, STEPS = 32 / RPI;   // column tiles per pass, chunks per row, rows per store
@@ -1461,21 +1462,21 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[MI][NJ], int lane
     static_assert(TileGeom<MI, NJ>::STAGE / 4 >= 32 * CH * 16, "32 rows of a pass");
     int lane = lane0;                                        // opaque: what follows from it is not worth registers during the loop
     asm volatile("" : "+v"(lane));
-    const int fr = lane & 31, fk = lane >> 5;
-    unsigned char* wr = region + fr * (CH * 16) + ((fk ^ (fr >> 4)) * 8);
-    const int w_swz = (fr / (16 / CH)) % CH;
+    const int fr = lane & 15;
+    unsigned char* wr = region + fr * (CH * 16) + (lane >> 4 & 1) * 8;
+    const int w_swz = (fr / (16 / CH)) % CH;                 // (the same 16 rows further)
     auto write = [&](int p) {
-        const int i = p / PER_ROW, j0 = p % PER_ROW * JP;
+        const int i0 = p / PER_ROW * 2, j0 = p % PER_ROW * JP * 2;
 #pragma unroll
-        for (int j = j0; j < j0 + JP; ++j)
+        for (int i = i0; i < i0 + 2; ++i)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
+            for (int j = j0; j < j0 + 2 * JP; ++j) {
                 float v[4];
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
-                    v[t] = epilogue_bf16<EPI>(read_acc<IN_AGPR>(acc[i][j][4 * g + t]),
-                                              (EPI == EPI_SWIGLU) ? read_acc<IN_AGPR>(acc[i][(j + NJ / 2) % NJ][4 * g + t]) : 0.f);
-                *reinterpret_cast<u32x2*>(wr + (((j - j0) * 4 + g) ^ w_swz) * 16) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+                    v[t] = epilogue_bf16<EPI>(read_acc<IN_AGPR>(acc[i][j][t]),
+                                              (EPI == EPI_SWIGLU) ? read_acc<IN_AGPR>(acc[i][(j + NJ) % (2 * NJ)][t]) : 0.f);
+                *reinterpret_cast<u32x2*>(wr + (i - i0) * (16 * CH * 16) + ((((j - j0) * 2) + (lane >> 5)) ^ w_swz) * 16) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
             }
     };
     write(0);
@@ -1489,8 +1490,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[MI][NJ], int lane
 #pragma unroll
         for (int it = 0; it < STEPS; ++it) {
             const int r = it * RPI + lane / CH;
-            const u32x4 v = *reinterpret_cast<const u32x4*>(region + r * (CH * 16) + ((lane % CH) ^ ((r / (16 / CH)) % CH)) * 16);
-            q[it] = it >= STEPS / 2 ? u32x4{v.z, v.w, v.x, v.y} : v;
+            q[it] = *reinterpret_cast<const u32x4*>(region + r * (CH * 16) + ((lane % CH) ^ ((r / (16 / CH)) % CH)) * 16);
             const int gr = first_row + p / PER_ROW * 32 + r;
             const int mr = GATHER ? rel[min(gr, nrows - 1)] : gr;
             row_off[it] = gr < nrows ? (uint32_t)mr * (uint32_t)ldc * 2u + (uint32_t)(lane % CH) * 16u : 0xFFFFFF00u;   // else past the end of dst: not stored
@@ -1532,7 +1532,7 @@ __device__ __forceinline__ void sum_pieces(int unit_lo, int unit_hi, const float
                 for (int n = 0; n < NP; ++n)
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
-                        v[u][n][q] = load_piece(src, min(p0 + u, parts - 1) * (int)(TG::PARTIAL / 16) + ((i * NJ + jo + n * (NJ / 2)) * 4 + q) * 256 + (int)threadIdx.x);
+                        v[u][n][q] = load_piece(src, min(p0 + u, parts - 1) * (int)(TG::PARTIAL / 16) + ((2 * i + (q >> 1)) * (2 * NJ) + 2 * jo + (q & 1) + n * NJ) * 256 + (int)threadIdx.x);
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 if (p0 + u < parts) {
@@ -1542,16 +1542,19 @@ __device__ __forceinline__ void sum_pieces(int unit_lo, int unit_hi, const float
                         for (int q = 0; q < 4; ++q) sum[n][q] += v[u][n][q];
                 }
         }
-        const int gr = (wave >> 1) * G::ROWS + i * 32 + (lane & 31);
-        if (gr >= nrows) continue;
-        uint16_t* crow = C + (size_t)(row0 + (rel ? rel[gr] : gr)) * ldc;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            float v[4];
+        for (int h = 0; h < 2; ++h) {
+            const int gr = (wave >> 1) * G::ROWS + i * 32 + h * 16 + (lane & 15);
+            if (gr >= nrows) continue;
+            uint16_t* crow = C + (size_t)(row0 + (rel ? rel[gr] : gr)) * ldc;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) v[t] = epilogue_bf16<EPI>(sum[0][q][t], sum[NP - 1][q][t]);
-            const int col = n0 + (wave & 1) * G::NW + jo * 32 + q * 8 + (lane >> 5) * 4;
-            if (col < N) *reinterpret_cast<u32x2*>(crow + col) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+            for (int q = 2 * h; q < 2 * h + 2; ++q) {
+                float v[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) v[t] = epilogue_bf16<EPI>(sum[0][q][t], sum[NP - 1][q][t]);
+                const int col = n0 + (wave & 1) * G::NW + jo * 32 + (q & 1) * 16 + (lane >> 4) * 4;
+                if (col < N) *reinterpret_cast<u32x2*>(crow + col) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+            }
         }
     }
 }
@@ -1581,6 +1584,10 @@ __device__ __forceinline__ void sum_pieces(int unit_lo, int unit_hi, const float
 // TIMED (diagnostics, moe_diag_ffn_phases): the same kernel with the 100 MHz wall clock read by lane 0 of every wave
 // into marks[item][wave][4]: 0 start, 1 first operands in LDS (loop about to start), 2 loop done, 3 end; an item is a
 // tile or a piece of one (there is room for all of them: see max_items).  The ordinary instantiation contains none of it.
+// 16 bytes per lane, from lane_off + off on, into the KB of LDS at `to`
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, unsigned char* to, uint32_t lane_off, int off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)to, 16, lane_off, off, 0, 0);
+}
 struct WorkItem {
     int tile_id, piece;      // piece < 0: the whole K range
     int nk;                  // k-tiles (even: K is a multiple of 64)
@@ -1623,10 +1630,9 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     const int wm = wave >> 1, wn = wave & 1;
 
     // Direct-to-LDS staging.  A stage is 4 (MI + NJ) blocks of 1 KB (4 MI of A, 4 NJ of B); wave w
-    // fills blocks w, w+4, ...: MI of A and NJ of B per stage.  Addresses are kept as a wave-uniform
-    // 64-bit base (advanced with k by scalar adds) plus a fixed 32-bit byte offset per lane, so a
-    // load costs no vector address arithmetic.
-    struct Source { const char *a, *b0, *b1; uint32_t a_voff[MI], b_voff[NJ]; };
+    // fills blocks w, w+4, ...: MI of A and NJ of B per stage.  A load's address is a buffer descriptor per operand, a
+    // fixed 32-bit byte offset per lane and the byte offset of the k-tile in one scalar register, so it costs no address arithmetic.
+    struct Source { __amdgpu_buffer_rsrc_t a, b0, b1; uint32_t a_voff[MI], b_voff[NJ]; };
     // in two parts, so that the loads of the first are under way during an epilogue
     auto describe = [&](int id, WorkItem& w, Source& src, int (&a_row)[MI]) {
         int lr, lc, ln = lane;
@@ -1656,11 +1662,13 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
         auto pick = [&](int which) -> const char* {
             return reinterpret_cast<const char*>(which == 0 ? tab.w1[ex] : which == 1 ? tab.w_up[ex] : tab.w_down[ex]) + (size_t)kt_lo * BK * 2;
         };
-        src.b0 = pick(which0);
-        src.b1 = (EPI == EPI_SWIGLU) ? pick(which1) : src.b0;
+        const char *b0 = pick(which0), *b1 = (EPI == EPI_SWIGLU) ? pick(which1) : b0;
         // SwiGLU: the second half of a wave-column's 2 NJ 16-row blocks are up rows; this wave fetches blocks wave + 4 i
-        if (NJ == 2 && (wave & 2)) src.b0 = src.b1;
-        src.a = reinterpret_cast<const char*>(A + (size_t)w.row0 * lda) + (size_t)kt_lo * BK * 2;
+        if (NJ == 2 && (wave & 2)) b0 = b1;
+        auto rsrc = [](const char* p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(p), 0, 0xFFFFFFFFu, 0x00027000); };
+        src.b0 = rsrc(b0);
+        src.b1 = rsrc(b1);
+        src.a = rsrc(reinterpret_cast<const char*>(A + (size_t)w.row0 * lda) + (size_t)kt_lo * BK * 2);
 #pragma unroll
         for (int i = 0; i < MI; ++i) a_row[i] = min((wave + 4 * i) * 16 + lr, w.nrows - 1);   // row (relative to row0) of the tile rows this lane fetches
         if (w.rel) {                                         // gathered tile: offsets from row0, below 2^32 bytes (checked
@@ -1687,168 +1695,115 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
             }
             src.b_voff[i] = (uint32_t)min(col, N - 1) * (uint32_t)K * 2u + (uint32_t)lc * 16u;
         }
-        // opaque to the optimiser from here on: these must stay 32-bit lane offsets next to scalar bases
-#pragma unroll
-        for (int i = 0; i < MI; ++i) asm volatile("" : "+v"(src.a_voff[i]));
-#pragma unroll
-        for (int i = 0; i < NJ; ++i) asm volatile("" : "+v"(src.b_voff[i]));
     };
     WorkItem cur, next;
     Source src, src_next;
     int t_first = 0, t_last = 0;                             // loads: the k-tile number at which `src` starts, and the last pair it has
-    // The loads of k-tiles t and t+1 (t even) into the stages at LDS byte offsets so0 and so1, items [i_lo, i_hi): the
-    // MI + NJ 16-row blocks this wave fetches, A and B in turn, each for both k-tiles.  Past the end of the last tile its
-    // last pair is fetched again (into stages nobody reads any more) so that the count of outstanding loads stays uniform.
-    auto issue_part = [&](int t, int so0, int so1, int i_lo, int i_hi) {
-        t = min(t - t_first, t_last);
-        unsigned char* s0 = lds + so0;
-        unsigned char* s1 = lds + so1;
-        const size_t kb = (size_t)t * BK * 2;                // byte offset of k-tile t inside a row
-#pragma unroll
-        for (int it = 0; it < MI + NJ; ++it) {
-            if (it < i_lo || it >= i_hi) continue;
-            static_assert(MI <= NJ, "A and B blocks alternate while there are A blocks");
-            const bool is_a = it < 2 * MI && (it & 1) == 0;
-            const int i = it < 2 * MI ? it >> 1 : it - MI;
-            const int blk = (wave + 4 * i) * 1024 + (is_a ? 0 : TG::A_BYTES);
-            const char* b = (EPI == EPI_SWIGLU && (i & (NJ / 4))) ? src.b1 : src.b0;
-            const char* p = (is_a ? src.a : b) + kb;
-            uint32_t& v = is_a ? src.a_voff[i] : src.b_voff[i];
-            // opaque here, so that scalar base + zero-extended 32-bit lane offset is still visible when the
-            // load is selected (saddr form: half the address registers, no 64-bit vector add per load)
-            const char* p1 = p + BK * 2;
-            asm volatile("" : "+s"(p), "+s"(p1), "+v"(v));
-            __builtin_amdgcn_global_load_lds(p + v, (__attribute__((address_space(3))) void*)(s0 + blk), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds(p1 + v, (__attribute__((address_space(3))) void*)(s1 + blk), 16, 0, 0);
-        }
+    // byte offset inside a row of the pair of k-tiles t and t+1 (t even).  Past the end of the last tile its last pair is fetched
+    // again (into stages nobody reads any more) so that the count of outstanding loads stays uniform.
+    auto pair_offset = [&](int t) { return min(t - t_first, t_last) * (BK * 2); };
+    // Load l of the 2 (MI + NJ) by which this wave fetches its 16-row blocks of such a pair, A and B in turn, each for both
+    // k-tiles, into the stages at LDS byte offsets so0 and so1
+    auto issue_one = [&](int kb, int so0, int so1, int l) {
+        static_assert(MI <= NJ, "A and B blocks alternate while there are A blocks");
+        const int it = l >> 1;
+        if (it >= MI + NJ) return;
+        const bool is_a = it < 2 * MI && (it & 1) == 0;
+        const int i = it < 2 * MI ? it >> 1 : it - MI;
+        unsigned char* to = lds + ((l & 1) ? so1 : so0) + (wave + 4 * i) * 1024 + (is_a ? 0 : TG::A_BYTES);
+        const __amdgpu_buffer_rsrc_t r = is_a ? src.a : (EPI == EPI_SWIGLU && (i & (NJ / 4))) ? src.b1 : src.b0;
+        load_to_lds(r, to, is_a ? src.a_voff[i] : src.b_voff[i], kb + (l & 1) * (BK * 2));
     };
-    constexpr int GI = (MI + NJ + 3) / 4;                    // items per group (the last may have fewer): four groups per pair of k-tiles
-    constexpr int LAST = MI + NJ - 3 * GI;
-    static_assert(LAST >= 1, "");
+    constexpr int GI = (MI + NJ + 3) / 4;                    // 16-row blocks per quarter of a pair (the last may have fewer)
 
-    const int fr = lane & 31, fk = lane >> 5;      // fragment row within a 32-row tile, which k-half
-    int a_off[2], b_off[2];                        // byte offsets inside a stage of 32-row tile 0, per k-step;
-#pragma unroll                                     // tile i lies 2 KB further (two 16-row blocks)
-    for (int s = 0; s < 2; ++s) {
-        a_off[s] = tile_off(wm * 32 * MI + fr, 2 * s + fk);
-        b_off[s] = TG::A_BYTES + tile_off(wn * 32 * NJ + fr, 2 * s + fk);
-    }
-    f32x16 acc[MI][NJ];                                      // [m-tile i][n-tile j], holds D^T: rows n, columns m
-    auto load_frags = [&](bf16x8 (&af)[MI], bf16x8 (&bfr)[NJ], const unsigned char* st, int s) {
-        const unsigned char* pa = st + a_off[s];
-        const unsigned char* pb = st + b_off[s];
-#pragma unroll
-        for (int i = 0; i < MI; ++i) af[i] = *reinterpret_cast<const bf16x8*>(pa + i * 2048);
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) bfr[j] = *reinterpret_cast<const bf16x8*>(pb + j * 2048);
+    // A fragment is 16 rows x 32 elements, one 16-row block of the stage; block i of the wave lies i KB further
+    const int a_off = tile_off(wm * 32 * MI + (lane & 15), lane >> 4), b_off = TG::A_BYTES + tile_off(wn * 32 * NJ + (lane & 15), lane >> 4);
+    f32x4 acc[2 * MI][2 * NJ];                               // [16 rows i][16 columns j], holds D^T: rows n, columns m
+    // Fragment r of the 2 MI + 2 NJ of a k-tile, in the order in which the products need them
+    auto read = [&](bf16x8 (&af)[2 * MI], bf16x8 (&bfr)[2 * NJ], const unsigned char* st, int r) {
+        if (r == 0) bfr[0] = *reinterpret_cast<const bf16x8*>(st + b_off);
+        else if (r <= 2 * MI) af[r - 1] = *reinterpret_cast<const bf16x8*>(st + a_off + (r - 1) * 1024);
+        else bfr[r - 2 * MI] = *reinterpret_cast<const bf16x8*>(st + b_off + (r - 2 * MI) * 1024);
     };
-    auto mma = [&](const bf16x8 (&af)[MI], const bf16x8 (&bfr)[NJ], auto from_zero) {
-        f32x16 zero;
+    // The MFMAs of a k-tile, with the reads of the next one's fragments and `load` 0 .. 4 GI - 1 spread between them.
+    // Power bounds the large tiles, so the instruction is the one that takes the least of it per product: from registers alone
+    // v_mfma_f32_16x16x32_bf16 sustains 2.06 PFLOP/s on a whole chip (1.96 GHz), v_mfma_f32_32x32x16_bf16 1.81 (1.73 GHz) - and in
+    // runs that have the weight fragment in common (1.66 to 1.79 PFLOP/s where both operands change from product to product).
+    // The results are the same bits.  The order is that of the source (see the barriers): the scheduler left to itself
+    // moves all reads together and mixes the runs.  20571 rows of 4096 -> 14336 -> 4096: 3590 + 1780 -> 3360 + 1650 us.
+    auto k_tile = [&](auto from_zero, const bf16x8 (&af)[2 * MI], const bf16x8 (&bfr)[2 * NJ], bf16x8 (&an)[2 * MI], bf16x8 (&bn)[2 * NJ], const unsigned char* next_stage, auto load) {
+        constexpr int READS = 2 * MI + 2 * NJ, LOADS = 4 * GI, M = 4 * MI * NJ, EVERY = M >= 48 ? 3 : 1;
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int e = 0; e < 16; ++e) zero[e] = 0.f;
+        for (int j = 0; j < 2 * NJ; ++j)
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], decltype(from_zero)::value ? zero : acc[i][j], 0, 0, 0);
+            for (int i = 0; i < 2 * MI; ++i) {
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j], af[i], decltype(from_zero)::value ? zero : acc[i][j], 0, 0, 0);
+                const int n = j * 2 * MI + i + 1;            // products so far
+                const bool reads_now = n % EVERY == 0 && n / EVERY <= READS, loads_now = (n + 1) * LOADS / M > n * LOADS / M;
+                if (reads_now || loads_now) __builtin_amdgcn_sched_barrier(0);
+                if (reads_now) read(an, bn, next_stage, n / EVERY - 1);
+                if (loads_now) load(n * LOADS / M);
+                if (reads_now || loads_now) __builtin_amdgcn_sched_barrier(0);
+            }
     };
 
-    // Software pipeline, two k-tiles per trip, four phases of MI x NJ MFMAs each:
-    //   A(kt)   read fragments (kt, k-step 1)     | MFMAs (kt, step 0)   | load group 3 of pair (kt+2, kt+3)
-    //   barrier: every wave is done with the stages of tiles kt-1 and kt
-    //   B(kt)   read fragments (kt+1, step 0)     | MFMAs (kt, step 1)   | load group 0 of pair (kt+4, kt+5)
-    //   A(kt+1) read fragments (kt+1, step 1)     | MFMAs (kt+1, step 0) | load group 1
-    //   wait until only groups 0 and 1 (4 GI loads per wave) are outstanding: pair (kt+2, kt+3) is in LDS; barrier
-    //   B(kt+1) read fragments (kt+2, step 0)     | MFMAs (kt+1, step 1) | load group 2
-    // A group is GI 16-row blocks, both k-tiles of the pair: 4 loads per wave at 4 x 4, 2 at 2 x 2.  The
-    // loads are spread evenly, at 4 x 4 one per four MFMAs: a CU sustains roughly one wave-load per 40 clocks
+    // Software pipeline, two k-tiles per trip; the fragments of a k-tile are read during the one before it:
+    //   barrier: every wave has read the fragments of kt, so the stages of kt-1 and kt are free
+    //   MFMAs of kt   | read the fragments of kt+1 | load the first half of pair (kt+4, kt+5)
+    //   wait until only that half (4 GI loads per wave) is outstanding: pair (kt+2, kt+3) is in LDS; barrier
+    //   MFMAs of kt+1 | read the fragments of kt+2 | load the second half
+    // A half is 2 GI 16-row blocks, both k-tiles of the pair: 8 loads per wave at 4 x 4, 4 at 2 x 2.  The
+    // loads are spread evenly, at 4 x 4 one per eight MFMAs: a CU sustains roughly one wave-load per 40 clocks
     // when the lines come from HBM, and a load that cannot be accepted stalls the wave's MFMA issue too.
     // A bare s_barrier is used: __syncthreads() would add a fence that waits for ALL outstanding loads.  In front of it a
     // wave waits for its own LDS reads: a read that is only issued is not ordered against what other waves write behind
-    // the barrier.  The phase behind it starts with MFMAs on those fragments, so the wait costs nothing.
-#define MOE_PHASE_SCHED()                                                                      \
-    if (MI * NJ == 12) {                                                                       \
-    _Pragma("unroll") for (int q = 0; q < 7; ++q) {   /* (MFMA, LDS read) x 7 */                \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                     \
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                     \
-    }                                                                                          \
-    _Pragma("unroll") for (int q = 0; q < 4; ++q) {   /* (MFMA, global->LDS load) x 4, MFMA */  \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                     \
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                     \
-    }                                                                                          \
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                         \
-    } else if (MI * NJ == 16) {                                                                \
-    _Pragma("unroll") for (int q = 0; q < 8; ++q) {   /* (MFMA, LDS read) x 8 */                \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                     \
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                                     \
-    }                                                                                          \
-    _Pragma("unroll") for (int q = 0; q < 4; ++q) {   /* (MFMA, MFMA, global->LDS load) x 4 */  \
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                                     \
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                     \
-    }                                                                                          \
-    } else {                                                                                   \
-    _Pragma("unroll") for (int q = 0; q < 2; ++q) {   /* (MFMA, 2 LDS reads, MFMA, load) x 2 */ \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                     \
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);                                     \
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                     \
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                     \
-    }                                                                                          \
-    }
+    // the barrier.  They are the first fragments that the MFMAs behind it need.
     // so[j] is the LDS byte offset of the stage that holds k-tile kt + j; the five values rotate by two per
     // trip, which keeps modulo arithmetic out of the instruction stream
     int so[STAGES];
 #pragma unroll
     for (int j = 0; j < STAGES; ++j) so[j] = j * TG::STAGE;
-    bf16x8 a0[MI], b0[NJ], a1[MI], b1[NJ];
+    bf16x8 a0[2 * MI], a1[2 * MI], b0[2 * NJ], b1[2 * NJ];   // of even and odd k-tiles
 
     int a_row[MI];
     describe(item, cur, src, a_row);
     describe_lanes(cur, src, a_row);
     t_last = cur.nk - 2;
-    issue_part(0, so[0], so[1], 0, 4 * GI);
-    issue_part(2, so[2], so[3], 0, 3 * GI);        // its last group goes out in the first trip below
+#pragma unroll
+    for (int l = 0; l < 8 * GI; ++l) issue_one(0, so[0], so[1], l);
+#pragma unroll
+    for (int l = 0; l < 8 * GI; ++l) issue_one(2 * BK * 2, so[2], so[3], l);
     bool more = item + ncu < end_item;
     if (more) {
         describe(item + ncu, next, src_next, a_row);
         describe_lanes(next, src_next, a_row);
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (6 * GI)); // vmcnt(three groups): pair (0, 1) is in LDS
+    // vmcnt(2 (MI + NJ)): pair (0, 1) is in LDS
+    __builtin_amdgcn_s_waitcnt(0x0F70 | ((2 * (MI + NJ)) & 15) | ((2 * (MI + NJ)) >> 4) << 14);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    load_frags(a0, b0, lds + so[0], 0);
+#pragma unroll
+    for (int r = 0; r < 2 * (MI + NJ); ++r) read(a0, b0, lds + so[0], r);
     // One trip.  FIRST: of a tile (the products start from zero); SWITCH: the loads of this tile end with phase A, those
     // of the next one follow.
     auto trip = [&](int kt, auto first, auto switches) {
         constexpr bool FIRST = decltype(first)::value, SWITCH = decltype(switches)::value;
-        __builtin_amdgcn_sched_barrier(0);
-        load_frags(a1, b1, lds + so[0], 1);
-        issue_part(kt + 2, so[2], so[3], 3 * GI, 4 * GI);
-        mma(a0, b0, first);
-        MOE_PHASE_SCHED()
+        const unsigned char *s1 = lds + so[1], *s2 = lds + so[2];
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_waitcnt(0xC07F);                  // lgkmcnt(0): this wave has read stage so[0], which is refilled below
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         if ((SWITCH || (FIRST && cur.nk == 4)) && more) { src = src_next; t_first = cur.nk; t_last = next.nk - 2; }
-        load_frags(a0, b0, lds + so[1], 0);
-        issue_part(kt + 4, so[4], so[0], 0, GI);
-        mma(a1, b1, std::false_type{});
-        MOE_PHASE_SCHED()
+        const int kb = pair_offset(kt + 4);
+        k_tile(first, a0, b0, a1, b1, s1, [&](int l) { issue_one(kb, so[4], so[0], l); });
         __builtin_amdgcn_sched_barrier(0);
-        load_frags(a1, b1, lds + so[1], 1);
-        issue_part(kt + 4, so[4], so[0], GI, 2 * GI);
-        mma(a0, b0, std::false_type{});
-        MOE_PHASE_SCHED()
-        __builtin_amdgcn_sched_barrier(0);
-        // vmcnt(4 GI): only groups 0 and 1 of the next pair may be outstanding; lgkmcnt(0): this wave has read stage so[1],
+        // vmcnt(4 GI): only the first half of the next pair may be outstanding; lgkmcnt(0): this wave has read stage so[1],
         // which the epilogue writes behind a tile's last trip
         __builtin_amdgcn_s_waitcnt(0x0070 | (4 * GI));
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        load_frags(a0, b0, lds + so[2], 0);
-        issue_part(kt + 4, so[4], so[0], 2 * GI, 3 * GI);
-        mma(a1, b1, std::false_type{});
-        MOE_PHASE_SCHED()
+        k_tile(std::false_type{}, a1, b1, a0, b0, s2, [&](int l) { issue_one(kb, so[4], so[0], 4 * GI + l); });
         __builtin_amdgcn_sched_barrier(0);
         const int t0 = so[0], t1 = so[1];
         so[0] = so[2]; so[1] = so[3]; so[2] = so[4]; so[3] = t0; so[4] = t1;
@@ -1868,9 +1823,9 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
         if (TG::PER_CU == 1) {                               // the accumulators stay where they are until they are stored
             asm volatile("s_nop 15\n\ts_nop 15");            // the last product has left the matrix core before read_acc
 #pragma unroll
-            for (int i = 0; i < MI; ++i)
+            for (int i = 0; i < 2 * MI; ++i)
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) asm volatile("" : "+a"(acc[i][j]));
+                for (int j = 0; j < 2 * NJ; ++j) asm volatile("" : "+a"(acc[i][j]));
         }
         MOE_MARK(2);
         if (cur.piece >= 0) break;                           // the last item of its block: a round holds all pieces
@@ -1899,21 +1854,15 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
         item += ncu;
         MOE_MARK(0);
     }
-#undef MOE_PHASE_SCHED
     // a piece of a tail tile: the raw accumulators, 16 bytes per lane and store (whole 4 KB per store)
     __builtin_amdgcn_s_waitcnt(0x0070);                      // vmcnt(0) lgkmcnt(0): no load may still target LDS below
     const int tail = __builtin_amdgcn_readfirstlane(cur.tile_id - plan.n_full), piece = __builtin_amdgcn_readfirstlane(cur.piece);
     float* pieces = partial + (size_t)tail * plan.parts * (TG::PARTIAL / 4);   // of this tile
     const __amdgpu_buffer_rsrc_t dst = pieces_rsrc(pieces, (uint32_t)(plan.parts * TG::PARTIAL));
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+    for (int i = 0; i < 2 * MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                store_piece(dst, piece * (int)(TG::PARTIAL / 16) + ((i * NJ + j) * 4 + q) * 256 + tid, v);
-            }
+        for (int j = 0; j < 2 * NJ; ++j) store_piece(dst, piece * (int)(TG::PARTIAL / 16) + (i * 2 * NJ + j) * 256 + tid, acc[i][j]);
     if (TG::SUM_IN_PLACE && last_piece(m.done + tail, plan.parts, reinterpret_cast<int*>(lds)))
         sum_pieces<EPI, MI, NJ>(0, MI * EG::NJO, pieces, plan.parts, cur.row0, cur.nrows, cur.rel, cur.n0, N, C, ldc);
     MOE_MARK(3);
