@@ -49,6 +49,7 @@ struct TileMap {
     int32_t* gather;    // [max_tiles] 0: the tile is rows row0 .. row0 + nrows - 1; 1: row r is row0 + rel[tile][r]
     int32_t* rel;       // [max_tiles][kRelPitch] row offsets of the gathered tiles (written for those only)
     int32_t* done;      // [kMaxSplitTiles] pieces that have arrived, per tile cut along K (zeroed with the map)
+    int32_t* strips;    // [2] numbering of the GEMM's tiles (see Strips), or NULL: bands
 };
 constexpr int kMaxSplitTiles = 256;
 constexpr int kRelPitch = 256;
@@ -71,6 +72,7 @@ TileMap tilemap_at(void* ws, int R, int which = 0, int first = 0) {
     char* p = reinterpret_cast<char*>(ws);
     const size_t n = (size_t)max_tiles_for(R);
     m.n_tiles = reinterpret_cast<int32_t*>(p) + which;
+    m.strips = reinterpret_cast<int32_t*>(p) + 4 + 2 * which;
     m.row0 = reinterpret_cast<int32_t*>(p + 256);
     m.nrows = m.row0 + n;
     m.expert = m.nrows + n;
@@ -274,12 +276,30 @@ __device__ __forceinline__ Int3 block_scan3(Int3 v, Int3* excl, int* wave_tot /*
     return total;
 }
 
+// How the tiles of a GEMM are numbered over the XCDs (see tile_of_block)
+constexpr int kFewestStripTiles = 192, kStripTiles = 3000;
+struct Strips { int wide, more; };                           // `more` strips of wide + 1 columns, then strips of `wide`; wide = 0: bands
+__host__ __device__ __forceinline__ Strips plan_strips(int tiles_m, int tiles_n) {
+    const int total = tiles_m * tiles_n;
+    if (total < kFewestStripTiles || total > kStripTiles || (tiles_m / 8 < 4 && tiles_n / 8 > tiles_m / 8)) return Strips{0, 0};
+    const float patch = fminf(total * 0.125f, 32.f), width = fmaxf(sqrtf(patch), patch / tiles_m);
+    const int strips = max(1, min(tiles_n, (int)(tiles_n / width + 0.5f)));
+    return Strips{tiles_n / strips, tiles_n % strips};
+}
 // One block per map, a thread per segment.  The segment list is read into LDS in one round trip; the stable order
 // by expert comes from wave ballots (segments of the same expert inside a wave) plus a scan over the 16
 // waves; groups, positions inside the groups and the tiles of the groups come from two block-wide prefix
 // sums; then one thread per tile writes the tile records and the items fill the offset tables.
 struct MapJob { int bm, max_tiles; TileMap m; };
-struct MapJobs { MapJob job[2]; int32_t* done; };   // the two GEMMs may take tiles of different heights; done: both GEMMs' counters or NULL
+struct MapJobs { MapJob job[2]; int32_t* done; int tiles_n[2]; };   // the two GEMMs may take tiles of different heights; done: both GEMMs' counters or NULL; tiles_n: column tiles of the GEMMs that are numbered by tile_of_block, else 0
+// lane g < 2 writes the strips of GEMM g if map `job` of `maps` is its map
+__device__ __forceinline__ void write_strips(const MapJobs& jobs, int job, int maps, int n_tiles, int lane) {
+    if (lane >= 2 || (maps == 2 && lane != job) || jobs.tiles_n[lane] == 0) return;
+    const Strips p = plan_strips(n_tiles, jobs.tiles_n[lane]);
+    int32_t* to = jobs.job[0].m.strips + 2 * lane;
+    to[0] = p.wide;
+    to[1] = p.more;
+}
 __device__ __forceinline__ void zero_done(int32_t* done, int tid, int nth) {
     if (done)
         for (int i = tid; i < 2 * kMaxSplitTiles; i += nth) done[i] = 0;
@@ -428,6 +448,8 @@ template <class W> __host__ __device__ __forceinline__ SmallRun small_run(const 
     return SmallRun{v0 > 0 ? v0 : 0, hi < r.nrows ? hi : r.nrows, w.at(&S::lo, k) - v0 - r.row0};
 }
 
+// STRIPS: a GEMM may be numbered in strips.  Without, the kernel is 0.5 us shorter, which shows in shares of 17 to 40 us.
+template <bool STRIPS>
 __global__ __launch_bounds__(256) void tilemap_small_kernel(const int32_t* __restrict__ seg_offset,
                                                             const int32_t* __restrict__ seg_expert, int nseg, int R,
                                                             int n_local, int gather, MapJobs jobs) {
@@ -443,6 +465,7 @@ __global__ __launch_bounds__(256) void tilemap_small_kernel(const int32_t* __res
     if (blockIdx.x == 0 && blockIdx.y == 0) zero_done(jobs.done, threadIdx.x, 256);
     const SmallMap sm = small_map(w, nseg, R, n_local, gather, job.bm, job.max_tiles);
     if (blockIdx.x == 0 && threadIdx.x == 0) *m.n_tiles = sm.n_tiles;
+    if (STRIPS && wave_id == (int)gridDim.x * 4 - 1) write_strips(jobs, blockIdx.y, gridDim.y, sm.n_tiles, w.lane);   // often without a tile
     for (int t = wave_id; t < sm.n_tiles; t += gridDim.x * 4) {
         const SmallTile r = small_tile(w, sm, t, job.bm);
         if (w.lane == 0) {
@@ -575,6 +598,7 @@ __global__ __launch_bounds__(kMapThreads) void tilemap_kernel(const int32_t* __r
     // a well-formed list (non-decreasing offsets) stays below the bound; overlapping segments are cut off here
     const int nt = tot2.a < max_tiles ? tot2.a : max_tiles;
     if (tid == 0) { w.g_tile0[ng] = tot2.a; w.n_tiles = nt; *m.n_tiles = nt; }
+    write_strips(jobs, blockIdx.x, gridDim.x, nt, tid);
     lds_barrier();
     for (int t = tid; t < nt; t += nth) tilemap_tile(w, t, BM, m);
     if (!gather) return;
@@ -669,9 +693,25 @@ __host__ __device__ __forceinline__ void tile_of_block_bands(int id, int tiles_m
 // the M-tiles in step.  Measured at the 4096 -> 14336 -> 4096 shape: +7 % on both GEMMs at 2000 rows (bands
 // of one row), +2.5 % at 6745 and 7900 rows (three rows), +1 % at 4147 and 5000 (two rows); with bands of
 // four to seven rows the exchange gains or loses less than 1 %, so those keep the M bands.
-__host__ __device__ __forceinline__ void tile_of_block(int id, int total, int tiles_m, int tiles_n, int* tm, int* tn) {
-    (void)total;
-    if (tiles_m / 8 < 4 && tiles_n / 8 > tiles_m / 8) tile_of_block_bands(id, tiles_n, tiles_m, tn, tm);
+//
+// Grids of kFewestStripTiles to kStripTiles tiles whose N side has no thicker bands are mostly left-over M-tiles or low bands: those are numbered
+// in strips.  XCD x gets the x-th eighth of the tiles in an order that cuts N into strips and goes through a strip row by
+// row, so that the tiles resident on an XCD form a patch about as high as it is wide.  (Where N has the thicker bands, each
+// XCD reads weights of its own, which strips do not keep up: up to 7 % slower.)  FFN of 2741 rows of 1152 -> 2304 -> 1152 for four
+// experts 64.9 -> 61.0 us, 12000 of 1408 -> 2048 -> 1408 SwiGLU for eight 230 -> 217, 9000 of 2048 -> 1408 -> 2048 for four 163 -> 157, 16000 241 -> 236.
+// Working the numbers below out in every block costs 0.4 us of a GEMM that takes 12 to 17, so the tile map holds them.
+__host__ __device__ __forceinline__ void tile_of_block_strips(int id, int total, int tiles_m, Strips p, int* tm, int* tn) {
+    const int x = id % 8, base = total / 8, extra = total % 8;
+    const int v = x * base + min(x, extra) + id / 8;         // place in the order
+    const int head = p.more * (p.wide + 1) * tiles_m;        // tiles of the wider strips
+    const unsigned w = p.wide + (v < head ? 1 : 0), u = v < head ? v : v - head;
+    const unsigned row = u / w, strip = row / (unsigned)tiles_m;
+    *tm = (int)(row - strip * (unsigned)tiles_m);
+    *tn = (v < head ? 0 : p.more * (p.wide + 1)) + (int)(strip * w + (u - row * w));
+}
+__host__ __device__ __forceinline__ void tile_of_block(int id, int total, int tiles_m, int tiles_n, Strips strips, int* tm, int* tn) {
+    if (strips.wide > 0) tile_of_block_strips(id, total, tiles_m, strips, tm, tn);
+    else if (tiles_m / 8 < 4 && tiles_n / 8 > tiles_m / 8) tile_of_block_bands(id, tiles_n, tiles_m, tn, tm);
     else tile_of_block_bands(id, tiles_m, tiles_n, tm, tn);
 }
 
@@ -761,7 +801,7 @@ __global__ __launch_bounds__(256, 3) void gemm_f32_kernel(const float* __restric
     const int total = n_tiles_m * tiles_n;
     for (int id = blockIdx.x; id < total; id += gridDim.x) {   // one: always with a map, else unless the list has more runs than experts
         int tile_m, tile_n;
-        tile_of_block(id, total, n_tiles_m, tiles_n, &tile_m, &tile_n);
+        tile_of_block(id, total, n_tiles_m, tiles_n, Strips{0, 0}, &tile_m, &tile_n);
         SmallTile t{};
         const int32_t* rel = nullptr;
         if constexpr (SEG) {
@@ -1169,7 +1209,9 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_parts_kernel(const float* __r
                                                                 int tiles_n, int ncu, int walk, float* partial) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     constexpr int NOUT = (EPI == EPI_SWIGLU) ? XN / 2 : XN;
-    const int n_tiles_m = *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(m.n_tiles));
+    auto word = [](const int32_t* p) { return *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p)); };
+    const int n_tiles_m = word(m.n_tiles);
+    const Strips strips = m.strips ? Strips{word(m.strips), word(m.strips + 1)} : Strips{0, 0};
     const int total = n_tiles_m * tiles_n;
     const int nk_all = ((K + XK - 1) / XK + 1) & ~1;       // even; k-tiles past K count as zeros
     PartsCut cut = {total, 0, 1, nk_all};
@@ -1206,7 +1248,7 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_parts_kernel(const float* __r
             s.k0 = t.piece * cut.per;
             t.nk = min(cut.per, nk_all - s.k0);
         }
-        tile_of_block(id, total, n_tiles_m, tiles_n, &tile_m, &tile_n);
+        tile_of_block(id, total, n_tiles_m, tiles_n, strips, &tile_m, &tile_n);
         tile_m = __builtin_amdgcn_readfirstlane(tile_m);
         auto rec = [&](const int32_t* p) { return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p))[tile_m]; };
         t.row0 = rec(m.row0);
@@ -1610,7 +1652,9 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     using TG = TileGeom<MI, NJ>;
     using EG = EpiGeom<EPI, MI, NJ>;
     constexpr int NOUT = EG::NOUT;                                          // output columns per block
-    const int n_tiles_m = *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(m.n_tiles));
+    auto word = [](const int32_t* p) { return *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p)); };
+    const int n_tiles_m = word(m.n_tiles);
+    const Strips strips = m.strips ? Strips{word(m.strips), word(m.strips + 1)} : Strips{0, 0};
     const int total = n_tiles_m * tiles_n;
     TailPlan plan = plan_tail_upto(most_tail, total, ncu, K / BK);
     // the same for all blocks; the compiler does not see it through the divisions
@@ -1650,7 +1694,7 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
             w.nk = min(plan.pairs_per * 2, K / BK - kt_lo);
         }
         int tile_m, tile_n;
-        tile_of_block(w.tile_id, total, n_tiles_m, tiles_n, &tile_m, &tile_n);
+        tile_of_block(w.tile_id, total, n_tiles_m, tiles_n, strips, &tile_m, &tile_n);
         tile_m = __builtin_amdgcn_readfirstlane(tile_m);
         // the same for the whole block, written by an earlier kernel: scalar loads, which do not queue behind the operands
         auto rec = [&](const int32_t* p) { return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p))[tile_m]; };
@@ -1882,7 +1926,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_tail_kernel(TileMap m, int N, i
     const int tt = blockIdx.x / UNITS, unit = blockIdx.x % UNITS;
     if (tt >= plan.n_tail) return;
     int tile_m, tile_n;
-    tile_of_block(plan.n_full + tt, total, n_tiles_m, tiles_n, &tile_m, &tile_n);
+    tile_of_block(plan.n_full + tt, total, n_tiles_m, tiles_n, m.strips ? Strips{m.strips[0], m.strips[1]} : Strips{0, 0}, &tile_m, &tile_n);
     const int32_t* rel = m.gather[tile_m] ? m.rel + (size_t)tile_m * kRelPitch : nullptr;
     sum_pieces<EPI, MI, NJ>(unit, unit + 1, partial + (size_t)tt * plan.parts * (TileGeom<MI, NJ>::PARTIAL / 4), plan.parts, m.row0[tile_m],
                             m.nrows[tile_m], rel, tile_n * G::NOUT, N, C, ldc);
@@ -2499,6 +2543,15 @@ TileShape confirm_shape(TileShape t, int R, int n_used, int N, int K, int act, i
     const TileShape other = t == TS_128 ? TS_192 : TS_128;
     return held_up(other, R, n_used, N, K, act, cus) < 1.0 ? other : TS_256;
 }
+// column tiles of a GEMM of N output columns and tiles of bn weight rows
+int tiled_columns(int N, bool swiglu, int bn) { return swiglu ? (2 * N + bn - 1) / bn : (N + bn - 1) / bn; }
+// tiles_n, or 0 if none of the tile counts that n_used runs of R rows can have is numbered in strips
+int columns_in_strips(int R, int bm, int n_used, int tiles_n) {
+    const int hi = (int)((R + (int64_t)n_used * (bm - 1)) / bm);
+    for (int t = (R + bm - 1) / bm; t <= hi; ++t)
+        if (plan_strips(t, tiles_n).wide > 0) return tiles_n;
+    return 0;
+}
 // Items (tiles and pieces) that a GEMM of N output columns over R rows in nseg segments can have at most.
 size_t max_items(TileShape t, int R, int nseg, int N, int act, int cus) {
     const int out_cols = ((t == TS_128) ? TileGeom<2, 2>::BN : TileGeom<4, 4>::BN) / (act == MOE_ACT_SWIGLU ? 2 : 1);
@@ -2794,7 +2847,7 @@ extern "C" int moe_selfcheck_tile_order(int32_t tiles_m, int32_t tiles_n, int32_
     std::vector<int> seen((size_t)total, 0);
     for (int id = 0; id < total; ++id) {
         int tm = -1, tn = -1;
-        tile_of_block(id, total, tiles_m, tiles_n, &tm, &tn);
+        tile_of_block(id, total, tiles_m, tiles_n, plan_strips(tiles_m, tiles_n), &tm, &tn);
         if (tm < 0 || tm >= tiles_m || tn < 0 || tn >= tiles_n) return moe_set_error(MOE_EINTERNAL, "tile %d maps outside the grid", id);
         if (seen[(size_t)tm * tiles_n + tn]++) return moe_set_error(MOE_EINTERNAL, "tile (%d, %d) is produced twice", tm, tn);
     }
@@ -3147,11 +3200,16 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     if (dtype == MOE_F32 && pieces_fit) take_cuts(R, n_used, nseg, H, F, act, round_size(), in_parts, cuts);
     float* const f32_pieces[2] = {cuts[0] ? partial : nullptr, cuts[1] ? partial : nullptr};   // where an fp32 GEMM's tiles are cut
     jobs.done = (dtype == MOE_BF16 || f32_pieces[0] || f32_pieces[1]) ? tilemap_at(workspace, R, 0, max_tiles_for(R) - 2).rel : nullptr;
+    for (int g = 0; g < 2; ++g)
+        jobs.tiles_n[g] = form[g].mt || skinny || (dtype == MOE_F32 && !in_parts[g]) ? 0 : columns_in_strips(R, bm[g], n_used,
+            tiled_columns(g == 0 ? F : H, g == 0 && act == MOE_ACT_SWIGLU, dtype == MOE_F32 ? XN : shape[g] == TS_128 ? TileGeom<2, 2>::BN : TileGeom<4, 4>::BN));
     if (jobs.done) {
         jobs.job[0].m.done = jobs.done;
         jobs.job[1].m.done = jobs.done + kMaxSplitTiles;
     }
-    const TileMap &m = jobs.job[0].m, &m2 = jobs.job[1].m;
+    TileMap m = jobs.job[0].m, m2 = jobs.job[1].m;
+    m2.strips = jobs.tiles_n[1] ? m.strips + 2 : nullptr;
+    if (!jobs.tiles_n[0]) m.strips = nullptr;
     const int n_maps = bm[1] == bm[0] ? 1 : 2;
     // A list of one segment (a dense MLP, shared experts) whose GEMMs both take narrow tiles needs no map either: a tile follows from the
     // segment's two offsets, which cost the GEMMs one round trip instead of the two to the number of tiles and a record.
@@ -3163,7 +3221,8 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     if (!need_map) {
     } else if (nseg <= kSmallMapSegs) {                           // about a tile per wave
         const int blocks = std::min(64, (R / std::min(bm[0], bm[1]) + std::min(nseg, n_local) + 3) / 4);
-        hipLaunchKernelGGL(tilemap_small_kernel, dim3(blocks, n_maps), dim3(256), 0, st, seg_offset, seg_expert, nseg, R, n_local, gather, jobs);
+        if (jobs.tiles_n[0] || jobs.tiles_n[1]) hipLaunchKernelGGL(tilemap_small_kernel<true>, dim3(blocks, n_maps), dim3(256), 0, st, seg_offset, seg_expert, nseg, R, n_local, gather, jobs);
+        else hipLaunchKernelGGL(tilemap_small_kernel<false>, dim3(blocks, n_maps), dim3(256), 0, st, seg_offset, seg_expert, nseg, R, n_local, gather, jobs);
     } else {
         hipLaunchKernelGGL(tilemap_kernel, dim3(n_maps), dim3(kMapThreads), 0, st, seg_offset, seg_expert, nseg, R, n_local, gather, jobs);
     }
