@@ -1759,6 +1759,8 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
         load_to_lds(r, to, is_a ? src.a_voff[i] : src.b_voff[i], kb + (l & 1) * (BK * 2));
     };
     constexpr int GI = (MI + NJ + 3) / 4;                    // 16-row blocks per quarter of a pair (the last may have fewer)
+    constexpr bool SOON = TG::PER_CU > 1;                    // loads as early as they can go out, else evenly spread (see below)
+    constexpr int FIRST_LOADS = SOON ? 8 * GI : 4 * GI;      // of the loads of a pair, 4 or 8 GI go out during the first k-tile of a trip
 
     // A fragment is 16 rows x 32 elements, one 16-row block of the stage; block i of the wave lies i KB further
     const int a_off = tile_off(wm * 32 * MI + (lane & 15), lane >> 4), b_off = TG::A_BYTES + tile_off(wn * 32 * NJ + (lane & 15), lane >> 4);
@@ -1769,14 +1771,14 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
         else if (r <= 2 * MI) af[r - 1] = *reinterpret_cast<const bf16x8*>(st + a_off + (r - 1) * 1024);
         else bfr[r - 2 * MI] = *reinterpret_cast<const bf16x8*>(st + b_off + (r - 2 * MI) * 1024);
     };
-    // The MFMAs of a k-tile, with the reads of the next one's fragments and `load` 0 .. 4 GI - 1 spread between them.
+    // The MFMAs of a k-tile, with the reads of the next one's fragments and `load` 0 .. LOADS - 1 between them.
     // Power bounds the large tiles, so the instruction is the one that takes the least of it per product: from registers alone
     // v_mfma_f32_16x16x32_bf16 sustains 2.06 PFLOP/s on a whole chip (1.96 GHz), v_mfma_f32_32x32x16_bf16 1.81 (1.73 GHz) - and in
     // runs that have the weight fragment in common (1.66 to 1.79 PFLOP/s where both operands change from product to product).
     // The results are the same bits.  The order is that of the source (see the barriers): the scheduler left to itself
     // moves all reads together and mixes the runs.  20571 rows of 4096 -> 14336 -> 4096: 3590 + 1780 -> 3360 + 1650 us.
-    auto k_tile = [&](auto from_zero, const bf16x8 (&af)[2 * MI], const bf16x8 (&bfr)[2 * NJ], bf16x8 (&an)[2 * MI], bf16x8 (&bn)[2 * NJ], const unsigned char* next_stage, auto load) {
-        constexpr int READS = 2 * MI + 2 * NJ, LOADS = 4 * GI, M = 4 * MI * NJ, EVERY = M >= 48 ? 3 : 1;
+    auto k_tile = [&](auto from_zero, const bf16x8 (&af)[2 * MI], const bf16x8 (&bfr)[2 * NJ], bf16x8 (&an)[2 * MI], bf16x8 (&bn)[2 * NJ], const unsigned char* next_stage, auto n_loads, auto load) {
+        constexpr int READS = 2 * MI + 2 * NJ, LOADS = decltype(n_loads)::value, M = 4 * MI * NJ, EVERY = 3;
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < 2 * NJ; ++j)
@@ -1784,22 +1786,27 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
             for (int i = 0; i < 2 * MI; ++i) {
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j], af[i], decltype(from_zero)::value ? zero : acc[i][j], 0, 0, 0);
                 const int n = j * 2 * MI + i + 1;            // products so far
-                const bool reads_now = n % EVERY == 0 && n / EVERY <= READS, loads_now = (n + 1) * LOADS / M > n * LOADS / M;
+                const int r = SOON ? n - 2 : n % EVERY == 0 ? n / EVERY - 1 : -1, l = SOON ? n - 1 : (n + 1) * LOADS / M > n * LOADS / M ? n * LOADS / M : -1;
+                const bool reads_now = r >= 0 && r < READS, loads_now = l >= 0 && l < LOADS;
                 if (reads_now || loads_now) __builtin_amdgcn_sched_barrier(0);
-                if (reads_now) read(an, bn, next_stage, n / EVERY - 1);
-                if (loads_now) load(n * LOADS / M);
+                if (loads_now) load(l);
+                if (reads_now) read(an, bn, next_stage, r);
                 if (reads_now || loads_now) __builtin_amdgcn_sched_barrier(0);
             }
     };
 
     // Software pipeline, two k-tiles per trip; the fragments of a k-tile are read during the one before it:
     //   barrier: every wave has read the fragments of kt, so the stages of kt-1 and kt are free
-    //   MFMAs of kt   | read the fragments of kt+1 | load the first half of pair (kt+4, kt+5)
-    //   wait until only that half (4 GI loads per wave) is outstanding: pair (kt+2, kt+3) is in LDS; barrier
+    //   MFMAs of kt   | read the fragments of kt+1 | load the first half of pair (kt+4, kt+5), or all of it
+    //   wait until only those loads (4 or 8 GI per wave) are outstanding: pair (kt+2, kt+3) is in LDS; barrier
     //   MFMAs of kt+1 | read the fragments of kt+2 | load the second half
-    // A half is 2 GI 16-row blocks, both k-tiles of the pair: 8 loads per wave at 4 x 4, 4 at 2 x 2.  The
+    // A half is 2 GI 16-row blocks, both k-tiles of the pair: 8 loads per wave at 4 x 4.  These
     // loads are spread evenly, at 4 x 4 one per eight MFMAs: a CU sustains roughly one wave-load per 40 clocks
-    // when the lines come from HBM, and a load that cannot be accepted stalls the wave's MFMA issue too.
+    // when the lines come from HBM, and a load that cannot be accepted stalls the wave's MFMA issue too (loads one after the
+    // other, in front of the reads: 2 to 5 % slower).  128 x 128 tiles (SOON) are bound by what is in flight instead: a k-tile of a
+    // block is 0.12 us of products, a round trip 0.7, and the other block of the CU fills a stall.  There the whole pair goes out in
+    // the first k-tile as soon as its stages are free, in front of the reads: 2741 rows of 1152 -> 2304 -> 1152 for four experts 59.9
+    // -> 56.9 us, 800 of 2048 -> 1408 -> 2048 SwiGLU 53.1 -> 46.9 (in halves, one after the other: 59.2 and 51.9).
     // A bare s_barrier is used: __syncthreads() would add a fence that waits for ALL outstanding loads.  In front of it a
     // wave waits for its own LDS reads: a read that is only issued is not ordered against what other waves write behind
     // the barrier.  They are the first fragments that the MFMAs behind it need.
@@ -1840,14 +1847,15 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
         __builtin_amdgcn_sched_barrier(0);
         if ((SWITCH || (FIRST && cur.nk == 4)) && more) { src = src_next; t_first = cur.nk; t_last = next.nk - 2; }
         const int kb = pair_offset(kt + 4);
-        k_tile(first, a0, b0, a1, b1, s1, [&](int l) { issue_one(kb, so[4], so[0], l); });
+        k_tile(first, a0, b0, a1, b1, s1, std::integral_constant<int, FIRST_LOADS>{}, [&](int l) { issue_one(kb, so[4], so[0], l); });
         __builtin_amdgcn_sched_barrier(0);
-        // vmcnt(4 GI): only the first half of the next pair may be outstanding; lgkmcnt(0): this wave has read stage so[1],
+        // vmcnt(FIRST_LOADS): only what has gone out of the next pair may be outstanding; lgkmcnt(0): this wave has read stage so[1],
         // which the epilogue writes behind a tile's last trip
-        __builtin_amdgcn_s_waitcnt(0x0070 | (4 * GI));
+        static_assert(FIRST_LOADS < 16, "");
+        __builtin_amdgcn_s_waitcnt(0x0070 | FIRST_LOADS);
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        k_tile(std::false_type{}, a1, b1, a0, b0, s2, [&](int l) { issue_one(kb, so[4], so[0], 4 * GI + l); });
+        k_tile(std::false_type{}, a1, b1, a0, b0, s2, std::integral_constant<int, 8 * GI - FIRST_LOADS>{}, [&](int l) { issue_one(kb, so[4], so[0], FIRST_LOADS + l); });
         __builtin_amdgcn_sched_barrier(0);
         const int t0 = so[0], t1 = so[1];
         so[0] = so[2]; so[1] = so[3]; so[2] = so[4]; so[3] = t0; so[4] = t1;
