@@ -49,7 +49,6 @@ struct TileMap {
     int32_t* gather;    // [max_tiles] 0: the tile is rows row0 .. row0 + nrows - 1; 1: row r is row0 + rel[tile][r]
     int32_t* rel;       // [max_tiles][kRelPitch] row offsets of the gathered tiles (written for those only)
     int32_t* done;      // [kMaxSplitTiles] pieces that have arrived, per tile cut along K (zeroed with the map)
-    int32_t* strips;    // [2] numbering of the GEMM's tiles (see Strips), or NULL: bands
 };
 constexpr int kMaxSplitTiles = 256;
 constexpr int kRelPitch = 256;
@@ -72,7 +71,6 @@ TileMap tilemap_at(void* ws, int R, int which = 0, int first = 0) {
     char* p = reinterpret_cast<char*>(ws);
     const size_t n = (size_t)max_tiles_for(R);
     m.n_tiles = reinterpret_cast<int32_t*>(p) + which;
-    m.strips = reinterpret_cast<int32_t*>(p) + 4 + 2 * which;
     m.row0 = reinterpret_cast<int32_t*>(p + 256);
     m.nrows = m.row0 + n;
     m.expert = m.nrows + n;
@@ -291,12 +289,12 @@ __host__ __device__ __forceinline__ Strips plan_strips(int tiles_m, int tiles_n)
 // waves; groups, positions inside the groups and the tiles of the groups come from two block-wide prefix
 // sums; then one thread per tile writes the tile records and the items fill the offset tables.
 struct MapJob { int bm, max_tiles; TileMap m; };
-struct MapJobs { MapJob job[2]; int32_t* done; int tiles_n[2]; };   // the two GEMMs may take tiles of different heights; done: both GEMMs' counters or NULL; tiles_n: column tiles of the GEMMs that are numbered by tile_of_block, else 0
+struct MapJobs { MapJob job[2]; int32_t* done; int32_t* strips; int tiles_n[2]; };   // the two GEMMs may take tiles of different heights; done: both GEMMs' counters or NULL; strips: two numbers per GEMM (see Strips); tiles_n: column tiles of the GEMMs that are numbered by tile_of_block, else 0
 // lane g < 2 writes the strips of GEMM g if map `job` of `maps` is its map
 __device__ __forceinline__ void write_strips(const MapJobs& jobs, int job, int maps, int n_tiles, int lane) {
     if (lane >= 2 || (maps == 2 && lane != job) || jobs.tiles_n[lane] == 0) return;
     const Strips p = plan_strips(n_tiles, jobs.tiles_n[lane]);
-    int32_t* to = jobs.job[0].m.strips + 2 * lane;
+    int32_t* to = jobs.strips + 2 * lane;
     to[0] = p.wide;
     to[1] = p.more;
 }
@@ -1206,12 +1204,12 @@ __device__ __forceinline__ void multiply_exactly(const float* pa, const float* p
 template <int EPI, bool CUT>
 __global__ __launch_bounds__(512, 2) void gemm_f32_parts_kernel(const float* __restrict__ A, int lda, TileMap m, ExpertTable tab,
                                                                 int which0, int which1, int N, int K, float* __restrict__ C, int ldc,
-                                                                int tiles_n, int ncu, int walk, float* partial) {
+                                                                int tiles_n, const int32_t* __restrict__ strips_at, int ncu, int walk, float* partial) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     constexpr int NOUT = (EPI == EPI_SWIGLU) ? XN / 2 : XN;
     auto word = [](const int32_t* p) { return *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p)); };
     const int n_tiles_m = word(m.n_tiles);
-    const Strips strips = m.strips ? Strips{word(m.strips), word(m.strips + 1)} : Strips{0, 0};
+    const Strips strips = strips_at ? Strips{word(strips_at), word(strips_at + 1)} : Strips{0, 0};
     const int total = n_tiles_m * tiles_n;
     const int nk_all = ((K + XK - 1) / XK + 1) & ~1;       // even; k-tiles past K count as zeros
     PartsCut cut = {total, 0, 1, nk_all};
@@ -1639,7 +1637,7 @@ struct WorkItem {
 template <int EPI, int MI, int NJ, bool TIMED>
 __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_kernel(const uint16_t* __restrict__ A, int lda, TileMap m,
                                                            ExpertTable tab, int which0, int which1, int N, int K,
-                                                           uint16_t* __restrict__ C, int ldc, int tiles_n, int ncu, int walk, int most_tail,
+                                                           uint16_t* __restrict__ C, int ldc, int tiles_n, const int32_t* __restrict__ strips_at, int ncu, int walk, int most_tail,
                                                            float* partial, long long* __restrict__ marks,
                                                            uint32_t mark_items) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
@@ -1654,7 +1652,7 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     constexpr int NOUT = EG::NOUT;                                          // output columns per block
     auto word = [](const int32_t* p) { return *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p)); };
     const int n_tiles_m = word(m.n_tiles);
-    const Strips strips = m.strips ? Strips{word(m.strips), word(m.strips + 1)} : Strips{0, 0};
+    const Strips strips = strips_at ? Strips{word(strips_at), word(strips_at + 1)} : Strips{0, 0};
     const int total = n_tiles_m * tiles_n;
     TailPlan plan = plan_tail_upto(most_tail, total, ncu, K / BK);
     // the same for all blocks; the compiler does not see it through the divisions
@@ -1925,7 +1923,7 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
 // hundreds of blocks.
 template <int EPI, int MI, int NJ>
 __global__ __launch_bounds__(256) void gemm_bf16_tail_kernel(TileMap m, int N, int K, uint16_t* __restrict__ C, int ldc,
-                                                             int tiles_n, int ncu, int most_tail, const float* __restrict__ partial) {
+                                                             int tiles_n, const int32_t* __restrict__ strips_at, int ncu, int most_tail, const float* __restrict__ partial) {
     using G = EpiGeom<EPI, MI, NJ>;
     constexpr int UNITS = MI * G::NJO;
     const int n_tiles_m = *m.n_tiles;
@@ -1934,7 +1932,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_tail_kernel(TileMap m, int N, i
     const int tt = blockIdx.x / UNITS, unit = blockIdx.x % UNITS;
     if (tt >= plan.n_tail) return;
     int tile_m, tile_n;
-    tile_of_block(plan.n_full + tt, total, n_tiles_m, tiles_n, m.strips ? Strips{m.strips[0], m.strips[1]} : Strips{0, 0}, &tile_m, &tile_n);
+    tile_of_block(plan.n_full + tt, total, n_tiles_m, tiles_n, strips_at ? Strips{strips_at[0], strips_at[1]} : Strips{0, 0}, &tile_m, &tile_n);
     const int32_t* rel = m.gather[tile_m] ? m.rel + (size_t)tile_m * kRelPitch : nullptr;
     sum_pieces<EPI, MI, NJ>(unit, unit + 1, partial + (size_t)tt * plan.parts * (TileGeom<MI, NJ>::PARTIAL / 4), plan.parts, m.row0[tile_m],
                             m.nrows[tile_m], rel, tile_n * G::NOUT, N, C, ldc);
@@ -2383,7 +2381,7 @@ int walk_blocks(int max_items, int walk, int ncu) {
 }
 
 template <int EPI, int MI, int NJ, bool TIMED>
-int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
+int launch_bf16(const void* A, int lda, const TileMap& m, const int32_t* strips, const ExpertTable& tab, int which0, int which1, int N, int K,
                 void* C, int ldc, int R, int nseg, int n_used, float* partial, hipStream_t st, long long* marks,
                 size_t marks_len) {
     using TG = TileGeom<MI, NJ>;
@@ -2404,13 +2402,13 @@ int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab
     const int walk = walk_tiles(TG::BM, K);
     hipLaunchKernelGGL((gemm_bf16_kernel<EPI, MI, NJ, TIMED>), dim3(walk_blocks(max_tiles_of(R, TG::BM, nseg) * tiles_n + ncu, walk, ncu)), dim3(256), TG::LDS, st,
                        reinterpret_cast<const uint16_t*>(A), lda, m, tab, which0, which1, N, K,
-                       reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, walk, most_tail, partial, marks,
+                       reinterpret_cast<uint16_t*>(C), ldc, tiles_n, strips, ncu, walk, most_tail, partial, marks,
                        (uint32_t)std::min<size_t>(marks_len / 16, 0xFFFFFFFFu));
     MOE_LAUNCH_CHECK("gemm_bf16_kernel");
     if constexpr (!TG::SUM_IN_PLACE) {
         if (most_tail > 0) {
             hipLaunchKernelGGL((gemm_bf16_tail_kernel<EPI, MI, NJ>), dim3(most_tail * MI * G::NJO), dim3(256), 0, st, m, N, K,
-                               reinterpret_cast<uint16_t*>(C), ldc, tiles_n, ncu, most_tail, partial);
+                               reinterpret_cast<uint16_t*>(C), ldc, tiles_n, strips, ncu, most_tail, partial);
             MOE_LAUNCH_CHECK("gemm_bf16_tail_kernel");
         }
     }
@@ -2419,9 +2417,9 @@ int launch_bf16(const void* A, int lda, const TileMap& m, const ExpertTable& tab
 
 enum TileShape { TS_128, TS_192, TS_256 };
 template <int EPI>
-int launch_bf16_shape(TileShape t, const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
+int launch_bf16_shape(TileShape t, const void* A, int lda, const TileMap& m, const int32_t* strips, const ExpertTable& tab, int which0, int which1, int N, int K,
                       void* C, int ldc, int R, int nseg, int n_used, float* partial, hipStream_t st, bool timed, long long* marks, size_t marks_len) {
-#define MOE_GEMM(...) launch_bf16<EPI, __VA_ARGS__>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, n_used, partial, st, marks, marks_len)
+#define MOE_GEMM(...) launch_bf16<EPI, __VA_ARGS__>(A, lda, m, strips, tab, which0, which1, N, K, C, ldc, R, nseg, n_used, partial, st, marks, marks_len)
     if (t == TS_128) return timed ? MOE_GEMM(2, 2, true) : MOE_GEMM(2, 2, false);
     if (t == TS_192) return timed ? MOE_GEMM(3, 4, true) : MOE_GEMM(3, 4, false);
     return timed ? MOE_GEMM(4, 4, true) : MOE_GEMM(4, 4, false);
@@ -2807,7 +2805,7 @@ void take_cuts(int R, int n_used, int nseg, int H, int F, int act, int cus, cons
 // What is launched for up to max_items tiles; pieces of a last round take one round more at most.
 int parts_blocks(int max_items, int walk, int ncu, bool may_cut) { return walk_blocks(max_items + (may_cut ? ncu : 0), walk, ncu); }
 template <int EPI>
-int launch_f32_parts(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
+int launch_f32_parts(const void* A, int lda, const TileMap& m, const int32_t* strips, const ExpertTable& tab, int which0, int which1, int N, int K,
                      void* C, int ldc, int R, int nseg, float* partial, hipStream_t st) {
     const int nout = (EPI == EPI_SWIGLU) ? XN / 2 : XN;
     const int tiles_n = (N + nout - 1) / nout, ncu = round_size(), walk = parts_walk_tiles(K);
@@ -2817,7 +2815,7 @@ int launch_f32_parts(const void* A, int lda, const TileMap& m, const ExpertTable
             attr_done = true;
         }
         hipLaunchKernelGGL(kernel, dim3(parts_blocks(max_tiles_of(R, XM, nseg) * tiles_n, walk, ncu, partial != nullptr)), dim3(512), kXLds, st,
-                           reinterpret_cast<const float*>(A), lda, m, tab, which0, which1, N, K, reinterpret_cast<float*>(C), ldc, tiles_n, ncu, walk, partial);
+                           reinterpret_cast<const float*>(A), lda, m, tab, which0, which1, N, K, reinterpret_cast<float*>(C), ldc, tiles_n, strips, ncu, walk, partial);
         return MOE_OK;
     };
     static bool attr_cut = false, attr_whole = false;
@@ -2828,9 +2826,9 @@ int launch_f32_parts(const void* A, int lda, const TileMap& m, const ExpertTable
 }
 
 template <int EPI>
-int launch_f32(bool in_parts, bool need_map, const void* A, int lda, const TileMap& m, SegList seg, const ExpertTable& tab, int which0, int which1,
+int launch_f32(bool in_parts, bool need_map, const void* A, int lda, const TileMap& m, const int32_t* strips, SegList seg, const ExpertTable& tab, int which0, int which1,
                int N, int K, void* C, int ldc, int R, int nseg, int n_used, float* partial, hipStream_t st) {
-    if (in_parts) return launch_f32_parts<EPI>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, partial, st);
+    if (in_parts) return launch_f32_parts<EPI>(A, lda, m, strips, tab, which0, which1, N, K, C, ldc, R, nseg, partial, st);
     const int nout = (EPI == EPI_SWIGLU) ? FN / 2 : FN;
     const int tiles_n = (N + nout - 1) / nout;
     seg.max_tiles = max_tiles_of(R, FM, nseg);
@@ -3215,9 +3213,9 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         jobs.job[0].m.done = jobs.done;
         jobs.job[1].m.done = jobs.done + kMaxSplitTiles;
     }
-    TileMap m = jobs.job[0].m, m2 = jobs.job[1].m;
-    m2.strips = jobs.tiles_n[1] ? m.strips + 2 : nullptr;
-    if (!jobs.tiles_n[0]) m.strips = nullptr;
+    const TileMap &m = jobs.job[0].m, &m2 = jobs.job[1].m;
+    jobs.strips = jobs.job[0].m.n_tiles + 4;                  // behind the two tile counts
+    const int32_t* const strips[2] = {jobs.tiles_n[0] ? jobs.strips : nullptr, jobs.tiles_n[1] ? jobs.strips + 2 : nullptr};
     const int n_maps = bm[1] == bm[0] ? 1 : 2;
     // A list of one segment (a dense MLP, shared experts) whose GEMMs both take narrow tiles needs no map either: a tile follows from the
     // segment's two offsets, which cost the GEMMs one round trip instead of the two to the number of tiles and a record.
@@ -3247,22 +3245,22 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         else rc = launch_bf16_skinny<EPI_SILU>(recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, partial, st);
     } else if (dtype == MOE_BF16) {
         if (act == MOE_ACT_SWIGLU)
-            rc = launch_bf16_shape<EPI_SWIGLU>(shape[0], recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
+            rc = launch_bf16_shape<EPI_SWIGLU>(shape[0], recv, H, m, strips[0], tab, 0, 1, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
         else if (act == MOE_ACT_GELU_MLP)
-            rc = launch_bf16_shape<EPI_GELU>(shape[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
+            rc = launch_bf16_shape<EPI_GELU>(shape[0], recv, H, m, strips[0], tab, 0, 0, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
         else
-            rc = launch_bf16_shape<EPI_SILU>(shape[0], recv, H, m, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
+            rc = launch_bf16_shape<EPI_SILU>(shape[0], recv, H, m, strips[0], tab, 0, 0, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
     } else {
-        if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
-        else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
-        else rc = launch_f32<EPI_SILU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
+        if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(in_parts[0], need_map, recv, H, m, strips[0], seg, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
+        else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(in_parts[0], need_map, recv, H, m, strips[0], seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
+        else rc = launch_f32<EPI_SILU>(in_parts[0], need_map, recv, H, m, strips[0], seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
     }
     if (rc != MOE_OK) return rc;
     if (ev) MOE_HIP(hipEventRecord(ev[2], st));
     if (form[1].mt) rc = launch_bf16_narrow<EPI_PLAIN>(form[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, one, st);
     else if (skinny) rc = launch_bf16_skinny<EPI_PLAIN>(hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, partial, st);
-    else if (dtype == MOE_BF16) rc = launch_bf16_shape<EPI_PLAIN>(shape[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, partial, st, timed_gemm == 2, marks, marks_len);
-    else rc = launch_f32<EPI_PLAIN>(in_parts[1], need_map, hmid, F, m2, seg, tab, 2, 2, H, F, out, H, R, nseg, n_used, f32_pieces[1], st);
+    else if (dtype == MOE_BF16) rc = launch_bf16_shape<EPI_PLAIN>(shape[1], hmid, F, m2, strips[1], tab, 2, 2, H, F, out, H, R, nseg, n_used, partial, st, timed_gemm == 2, marks, marks_len);
+    else rc = launch_f32<EPI_PLAIN>(in_parts[1], need_map, hmid, F, m2, strips[1], seg, tab, 2, 2, H, F, out, H, R, nseg, n_used, f32_pieces[1], st);
     if (rc != MOE_OK) return rc;
     if (ev) MOE_HIP(hipEventRecord(ev[3], st));
     return MOE_OK;
