@@ -220,7 +220,8 @@ int moe_expert_ffn(const void* recv, int32_t R, const int32_t* seg_offset, const
                    int32_t act, int32_t dtype, void* out, void* workspace, size_t workspace_bytes,
                    void* stream);
 
-/* Diagnostic twin of moe_expert_ffn (same arguments, same result): records HIP
+/* Diagnostic twin of moe_expert_ffn (same arguments, same result; to rounding where moe_expert_ffn runs both GEMMs
+ * in one kernel, see moe_selfcheck_small): records HIP
  * events on `stream` around each of its kernels, WAITS for the last one, and
  * returns the durations in milliseconds in ms_out (HOST [3]): tile map, first GEMM
  * with the activation (Sec. 2.1's FFN up-projection), second GEMM.  For measurement
@@ -267,6 +268,9 @@ int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t nseg, int32_t H
  * moe_status. */
 int moe_selfcheck_flow_player(int32_t n, const int64_t* D, const double* B, const int32_t* order);
 
+/* 1: a share of R rows for n_used experts in nseg segments runs both GEMMs in one kernel on a device of ncu compute units (0: not).
+ * moe_expert_ffn_timed, which reports the GEMMs one by one, always runs them apart. */
+int moe_selfcheck_small(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t dtype, int32_t ncu);
 /* Narrow tiles that the two GEMMs of a bf16 share take instead (few rows per expert): 10 MT + NT for tiles of 32 MT rows x
  * 32 NT weight rows, 0 where the kernels of moe_selfcheck_tile_shapes run.  Checks that the tile maps fit. */
 int moe_selfcheck_narrow(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* forms2);

@@ -27,6 +27,8 @@
 // up to 128 rows per expert, those of at most 64 rows included, takes narrow tiles where they are modelled faster
 // (gemm_bf16_narrow_kernel: 32 to 128 rows x 32 or 64 weight rows over the whole of K, see take_narrow).
 //
+// Experts of up to 192 KB (bf16; fp32: 128 KB) and few rows: both GEMMs in one kernel, without a tile map (ffn_small_kernel).
+//
 // fp32 path: 128 x 128 tiles of three bf16 parts per element on the bf16 matrix cores (gemm_f32_parts_kernel); where there are
 // too few of them, 64 x 64 tiles on the fp32 matrix cores (gemm_f32_kernel).
 #include "common.h"
@@ -2348,6 +2350,120 @@ __global__ __launch_bounds__((64 * NarrowGeom<MT, NT>::WAVES), (NarrowGeom<MT, N
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// Experts of a few hundred KB (see takes_small): both GEMMs of 32 rows by one block, in one launch and without a tile map.  Such a
+// share is bound by its launches - 2 to 3 us each at their shortest, where the products take one - so a block works its tile
+// out from the segment list (see SegList), takes the weights straight from the caches to registers and keeps its rows of the
+// intermediate in LDS.  Rows of operands are read as fragments of 16 rows x 64 bytes: 32 elements of bf16 for one
+// v_mfma_f32_16x16x32_bf16, 16 of fp32 for four v_mfma_f32_16x16x4_f32 (lane group g has elements 4 g .. 4 g + 3 and feeds one to
+// each: the order of the sum over k is free).  D = B . A^T: a lane ends with 4 consecutive columns of a row.
+constexpr int kSmallRows = 32, kSmallSteps = 4;              // rows per block; fragments of K that are loaded together
+template <int DT> __device__ __forceinline__ f32x4 small_mma(const u32x4& w, const u32x4& a, f32x4 acc) {
+    if (DT == MOE_BF16) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, a), acc, 0, 0, 0);
+    const f32x4 wf = __builtin_bit_cast(f32x4, w), af = __builtin_bit_cast(f32x4, a);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[v], af[v], acc, 0, 0, 0);
+    return acc;
+}
+// CT column tiles of 16, from column c0 on, of both row tiles: acc[m] += W_m[c0 + 16 c + ..] . rows over `steps` fragments of K, for
+// NM matrices at once.  a(i, s): fragment s of row tile i
+template <int DT, int NM, int CT, typename Rows>
+__device__ __forceinline__ void small_product(const char* (&w)[NM], size_t w_pitch, int c0, int steps, Rows a, f32x4 (&acc)[NM][CT][2]) {
+    const int lane = threadIdx.x & 63;
+    const size_t w_off = (size_t)(c0 + (lane & 15)) * w_pitch + (lane >> 4) * 16;
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) acc[m][c][0] = acc[m][c][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < steps; s0 += kSmallSteps) {
+        u32x4 wf[NM][CT][kSmallSteps], af[2][kSmallSteps];
+#pragma unroll
+        for (int s = 0; s < kSmallSteps; ++s) {
+#pragma unroll
+            for (int m = 0; m < NM; ++m)
+#pragma unroll
+                for (int c = 0; c < CT; ++c) wf[m][c][s] = *reinterpret_cast<const u32x4*>(w[m] + w_off + c * 16 * w_pitch + (s0 + s) * 64);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) af[i][s] = a(i, s0 + s);
+        }
+#pragma unroll
+        for (int s = 0; s < kSmallSteps; ++s)
+#pragma unroll
+            for (int m = 0; m < NM; ++m)
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) acc[m][c][i] = small_mma<DT>(wf[m][c][s], af[i][s], acc[m][c][i]);
+    }
+}
+template <int DT> __device__ __forceinline__ void small_store(char* p, const float (&v)[4]) {
+    if (DT == MOE_BF16) *reinterpret_cast<u32x2*>(p) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+    else *reinterpret_cast<f32x4*>(p) = f32x4{v[0], v[1], v[2], v[3]};
+}
+template <int DT, int EPI>
+__global__ __launch_bounds__(256) void ffn_small_kernel(const char* __restrict__ x, SegList seg, ExpertTable tab, int H, int F, char* __restrict__ out) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
+    constexpr int ES = DT == MOE_BF16 ? 2 : 4;
+    WaveLanes wl;
+    const SmallMap map = load_segments(seg, kSmallRows, wl);
+    const int n_tiles = __builtin_amdgcn_readfirstlane(map.n_tiles);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), fr = lane & 15, g = lane >> 4;
+    for (int item = blockIdx.x; item < n_tiles; item += gridDim.x) {   // one, unless the list has more runs than experts
+        const SmallTile t = small_tile(wl, map, item, kSmallRows);
+        int row[2] = {min(fr, t.nrows - 1), min(16 + fr, t.nrows - 1)};
+        segment_rows(wl, t, row);
+        const char* xr[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) xr[i] = x + (size_t)(t.row0 + row[i]) * H * ES + g * 16;
+        const int ex = __builtin_amdgcn_readfirstlane(t.expert);
+        const char *w1 = reinterpret_cast<const char*>(tab.w1[ex]), *wu = reinterpret_cast<const char*>(tab.w_up[ex]), *wd = reinterpret_cast<const char*>(tab.w_down[ex]);
+        const int pitch = F * ES + 16;                           // of a row of the intermediate: spreads the rows over the banks
+        auto first = [&](auto tiles) {
+            constexpr int CT = decltype(tiles)::value;
+            for (int ct = wave * CT; ct < F / 16; ct += 4 * CT) {
+                constexpr int NM = EPI == EPI_SWIGLU ? 2 : 1;
+                const char* w[NM];
+                w[0] = w1;
+                if (NM == 2) w[NM - 1] = wu;
+                f32x4 acc[NM][CT][2];
+                auto rows = [&](int i, int s) { return *reinterpret_cast<const u32x4*>(xr[i] + s * 64); };
+                small_product<DT, NM, CT>(w, (size_t)H * ES, ct * 16, H * ES / 64, rows, acc);
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        float v[4];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) v[q] = DT == MOE_BF16 ? epilogue_bf16<EPI>(acc[0][c][i][q], acc[NM - 1][c][i][q]) : epilogue<EPI>(acc[0][c][i][q], acc[NM - 1][c][i][q]);
+                        small_store<DT>(reinterpret_cast<char*>(lds) + (i * 16 + fr) * pitch + ((ct + c) * 16 + g * 4) * ES, v);
+                    }
+            }
+        };
+        auto second = [&](auto tiles) {
+            constexpr int CT = decltype(tiles)::value;
+            for (int ct = wave * CT; ct < H / 16; ct += 4 * CT) {
+                const char* w[1] = {wd};
+                f32x4 acc[1][CT][2];
+                auto rows = [&](int i, int s) { return *reinterpret_cast<const u32x4*>(lds + (i * 16 + fr) * pitch + s * 64 + g * 16); };
+                small_product<DT, 1, CT>(w, (size_t)F * ES, ct * 16, F * ES / 64, rows, acc);
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const float v[4] = {acc[0][c][i][0], acc[0][c][i][1], acc[0][c][i][2], acc[0][c][i][3]};
+                        if (i * 16 + fr < t.nrows) small_store<DT>(out + ((size_t)(t.row0 + row[i]) * H + (ct + c) * 16 + g * 4) * ES, v);
+                    }
+            }
+        };
+        if (F % 128 == 0) first(std::integral_constant<int, 2>{});
+        else first(std::integral_constant<int, 1>{});
+        __syncthreads();
+        if (H % 256 == 0) second(std::integral_constant<int, 4>{});
+        else second(std::integral_constant<int, 1>{});
+        __syncthreads();                                     // the next tile's intermediate goes to the same LDS
+    }
+}
+
 constexpr int kMaxCU = 256;                    // tail pieces per launch, at most: sizes the partial-tile workspace
 
 // number of CUs of the current device (a round of the grid), at most kMaxCU
@@ -2842,6 +2958,28 @@ int launch_f32(bool in_parts, bool need_map, const void* A, int lda, const TileM
     return MOE_OK;
 }
 
+// Which shares take ffn_small_kernel: weights of an expert that a CU fetches in about the time of the launches that are saved - up to
+// 192 KB in bf16, 128 KB in fp32, whose products take longer - and at most two blocks per CU, since every block fetches them
+// again.  One call with its map and two GEMMs -> in one kernel (us): fp32, 64 -> 128 -> 64 517 rows 12.3 -> 7.8, 16000 rows SwiGLU
+// 19.5 -> 13.4, 128 -> 128 -> 128 13.3 -> 11.0 (SwiGLU, 192 KB: 13.4 -> 13.9); bf16, 256 -> 128 -> 256 300 rows 16.0 -> 10.0, SwiGLU 15.0 -> 11.8,
+// 8000 rows GELU 16.7 -> 10.7, 16000 rows 17.6 -> 16.8, 30000 rows SwiGLU 24.0 -> 45 (SwiGLU of 256 -> 256 -> 256, 384 KB: 16.1 -> 25).
+constexpr int kSmallBytesBf16 = 192 << 10, kSmallBytesF32 = 128 << 10, kSmallPerCU = 2;
+bool takes_small(int R, int n_used, int nseg, int H, int F, int act, int dtype, int cus) {
+    const int es = elem_size(dtype), mats = act == MOE_ACT_SWIGLU ? 3 : 2;
+    return nseg <= kSmallMapSegs && (int64_t)H * es % (64 * kSmallSteps) == 0 && (int64_t)F * es % (64 * kSmallSteps) == 0 &&
+           (double)mats * H * F * es <= (dtype == MOE_BF16 ? kSmallBytesBf16 : kSmallBytesF32) &&
+           R + (int64_t)n_used * (kSmallRows - 1) <= (int64_t)kSmallPerCU * cus * kSmallRows;
+}
+template <int DT, int EPI>
+int launch_small(const void* x, const ExpertTable& tab, SegList seg, int R, int n_used, int H, int F, void* out, hipStream_t st) {
+    seg.max_tiles = max_tiles_of(R, kSmallRows, seg.nseg);
+    const int tiles = std::min<int64_t>(seg.max_tiles, (R + (int64_t)n_used * (kSmallRows - 1)) / kSmallRows);
+    hipLaunchKernelGGL((ffn_small_kernel<DT, EPI>), dim3(tiles), dim3(256), kSmallRows * (F * (DT == MOE_BF16 ? 2 : 4) + 16), st,
+                       reinterpret_cast<const char*>(x), seg, tab, H, F, reinterpret_cast<char*>(out));
+    MOE_LAUNCH_CHECK("ffn_small_kernel");
+    return MOE_OK;
+}
+
 }  // namespace
 
 // Host-side self check of the tile numbering and of the tail plan for a tiles_m x tiles_n grid with nk k-tiles
@@ -2889,6 +3027,13 @@ extern "C" int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t nseg
     }
     if (!maps_fit(R, nseg, rows2[0], rows2[1])) return moe_set_error(MOE_EINTERNAL, "tile maps of %d and %d rows leave no room for the counters", rows2[0], rows2[1]);
     return MOE_OK;
+}
+
+// 1: the share takes the kernel of both GEMMs at once
+extern "C" int moe_selfcheck_small(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t dtype, int32_t ncu) {
+    if (R < 1 || n_used < 1 || nseg < n_used || H < 1 || F < 1 || act < 0 || act > 2 || (dtype != MOE_F32 && dtype != MOE_BF16) || ncu < 1)
+        return moe_set_error(MOE_EINVAL, "moe_selfcheck_small: bad argument");
+    return takes_small(R, n_used, nseg, H, F, act, dtype, ncu) ? 1 : 0;
 }
 
 extern "C" int moe_selfcheck_narrow(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* forms2) {
@@ -3173,8 +3318,15 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         return moe_set_error(MOE_ESHAPE, "moe_diag_ffn_phases: bf16 and more than %d rows needed", kSkinnyRows);
     // gathered tiles address their rows by 32-bit byte offsets from the tile's first row
     const int gather = (size_t)R * (size_t)std::max(H, F) * elem_size(dtype) <= 0xFFFFFFFFull ? 1 : 0;
-    TileShape shape[2] = {TS_256, TS_256};
     const int n_used = std::min(gather ? std::min(n_local, nseg) : nseg, R);   // runs of rows that share no tile
+    if (timed_gemm == 0 && !ev && takes_small(R, n_used, nseg, H, F, act, dtype, round_size())) {   // (with events: the GEMMs, which they time)
+        const SegList list = {seg_offset, seg_expert, nseg, R, n_local, gather, 0};
+#define MOE_SMALL(DT, EPI) launch_small<DT, EPI>(recv, tab, list, R, n_used, H, F, out, st)
+        if (dtype == MOE_BF16) return act == MOE_ACT_SWIGLU ? MOE_SMALL(MOE_BF16, EPI_SWIGLU) : act == MOE_ACT_GELU_MLP ? MOE_SMALL(MOE_BF16, EPI_GELU) : MOE_SMALL(MOE_BF16, EPI_SILU);
+        return act == MOE_ACT_SWIGLU ? MOE_SMALL(MOE_F32, EPI_SWIGLU) : act == MOE_ACT_GELU_MLP ? MOE_SMALL(MOE_F32, EPI_GELU) : MOE_SMALL(MOE_F32, EPI_SILU);
+#undef MOE_SMALL
+    }
+    TileShape shape[2] = {TS_256, TS_256};
     bool in_parts[2] = {false, false};
     int bm[2] = {FM, FM};
     if (dtype == MOE_F32) {

@@ -879,6 +879,50 @@ def test_expert_ffn_narrow_tiles_of_one_segment(H, R, lo, hi, expert):
         H.assert_close(out[lo:hi], O.ffn(recv[lo:hi], w["w1"], w["w_up"], w["w_down"], 2), "bf16")
 
 
+# Both GEMMs in one kernel (32-row tiles): one row, a row less and more than a tile, several tiles; one column tile per wave and
+# several, in either GEMM; rows from all over, experts in falling order (more runs than experts), segments without rows, of unknown
+# experts and outside the rows.  Against the oracle, and against the GEMMs by themselves, which moe_expert_ffn_timed runs.
+@pytest.mark.parametrize("dtype,act,R,Hd,F,n_local,off,exp", [
+    ("fp32", 0, 517, 64, 128, 2, None, 8), ("fp32", 2, 33, 64, 64, 1, [0, 33], [0]), ("fp32", 1, 31, 256, 64, 3, None, 5), ("fp32", 0, 1, 128, 128, 1, [0, 1], [0]),
+    ("fp32", 2, 700, 64, 128, 2, [0, 90, 90, 200, 333, 700], [1, 0, 0, 1, 0]), ("fp32", 0, 300, 64, 192, 4, None, 64),
+    ("bf16", 2, 300, 256, 128, 2, None, 8), ("bf16", 1, 32, 128, 128, 1, [0, 32], [0]), ("bf16", 0, 1029, 128, 256, 4, None, 64), ("bf16", 2, 8000, 128, 256, 2, None, 3),
+    ("bf16", 0, 260, 256, 128, 3, [5, 60, 70, 130, 130, 300], [2, -1, 0, 1, 2]), ("bf16", 2, 65, 256, 128, 2, [0, 1, 33, 65], [1, 5, 0]),
+    # overlapping segments: more runs of one expert than experts, and more tiles than rows
+    ("fp32", 0, 64, 64, 64, 1, [0, 64, 10, 64, 20, 64, 30], [0, 0, 0, 0, 0, 0])])
+def test_expert_ffn_small(H, dtype, act, R, Hd, F, n_local, off, exp):
+    import torch
+    from paper_2410_17043_amd import _lib
+    r = np.random.default_rng(R + Hd)
+    if off is None:
+        off, exp = make_segments(r, R, exp, n_local)
+    assert _lib.load().moe_selfcheck_small(R, min(n_local, len(exp), R), len(exp), Hd, F, act, 1 if dtype == "bf16" else 0, 256) == 1
+    cfg = small("c2_mixtral", H=Hd, F=F, act=act)
+    experts = [W.make_expert_weights(cfg, e) for e in range(n_local)]
+    recv = r.standard_normal((R, Hd)).astype(np.float32)
+    if dtype == "bf16":
+        recv = W.to_bf16_grid(recv)
+    dev = [H.weights_to_dev(w, dtype) for w in experts]
+    x = H.dev(recv, dtype)
+    out = H.host(H.run_ffn(x, off, exp, dev, Hd, F, act, dtype))
+    apart = torch.full((R, Hd), float("nan"), dtype=H.P.TORCH_DTYPE[dtype], device="cuda")
+    ws = torch.empty(H.P.moe_ffn_workspace_bytes(R, Hd, F, act, dtype), dtype=torch.uint8, device="cuda")
+    i32 = dict(dtype=torch.int32, device="cuda")
+    H.P.moe_expert_ffn_timed(x, R, torch.tensor(off, **i32), torch.tensor(exp, **i32), len(exp), dev, Hd, F, act, dtype, apart, ws)
+    apart = H.host(apart)
+    written = np.zeros(R, dtype=bool)
+    for i, e in enumerate(exp):
+        if 0 <= e < n_local:
+            written[max(off[i], 0):max(min(off[i + 1], R), 0)] = True
+    assert np.isnan(out[~written]).all() and np.isnan(apart[~written]).all()
+    H.assert_close(out[written], apart[written], dtype)
+    ref = np.full((R, Hd), np.nan)
+    for i, e in enumerate(exp):
+        lo, hi = max(off[i], 0), min(off[i + 1], R)
+        if 0 <= e < n_local and hi > lo:
+            ref[lo:hi] = O.ffn(recv[lo:hi], experts[e]["w1"], experts[e]["w_up"], experts[e]["w_down"], act)
+    H.assert_close(out[written], ref[written], dtype)
+
+
 # fp32 GEMMs on three bf16 parts (128-row tiles): a K that ends inside a k-tile and an odd number of them, gathered and
 # ragged tiles, N of no whole tile, several tiles per block, one kernel of each kind with a map of its own, K of the least four k-tiles
 @pytest.mark.parametrize("act,R,Hd,F,n_local,nseg,rows", [(1, 1800, 1156, 1164, 2, 9, [128, 128]), (2, 3000, 292, 1156, 3, 40, [128, 64]),

@@ -592,3 +592,18 @@ def test_both_forms_of_the_flow_player_give_the_same_bits():
             got = lib.moe_selfcheck_flow_player(n, D.ctypes.data_as(C.POINTER(C.c_int64)), None if B is None else B.ctypes.data_as(C.POINTER(C.c_double)),
                                                 order.ctypes.data_as(C.POINTER(C.c_int32)))
             assert got in (0, 1), (n, rates, lib.moe_last_error())
+
+
+def test_both_gemms_in_one_kernel_only_for_small_experts_and_few_rows():
+    """What was measured faster: up to 192 KB of weights per expert in bf16 (fp32: 128 KB), two blocks of 32 rows per CU and 64 segments;
+    widths of whole 256 bytes."""
+    from paper_2410_17043_amd import _lib
+    takes = _lib.load().moe_selfcheck_small
+    F32, BF16 = 0, 1
+    for R, n, nseg, Hd, F, act, dt in ((517, 2, 8, 64, 128, 0, F32), (16000, 2, 8, 64, 128, 2, F32), (1000, 2, 4, 128, 128, 0, F32), (1, 1, 1, 64, 64, 1, F32),
+                                       (300, 2, 8, 256, 128, 2, BF16), (16384 - 31, 1, 64, 128, 256, 0, BF16)):
+        assert takes(R, n, nseg, Hd, F, act, dt, 256) == 1, (R, Hd, F)
+    for R, n, nseg, Hd, F, act, dt in ((517, 2, 8, 128, 128, 2, F32), (517, 2, 8, 68, 128, 0, F32), (517, 2, 8, 64, 132, 0, F32), (517, 2, 65, 64, 128, 0, F32),
+                                       (16384, 1, 1, 64, 128, 0, F32), (16384, 2, 8, 256, 128, 0, BF16), (300, 2, 8, 256, 256, 2, BF16), (517, 2, 8, 1 << 30, 1 << 30, 0, F32)):
+        assert takes(R, n, nseg, Hd, F, act, dt, 256) == 0, (R, Hd, F)
+    assert takes(0, 1, 1, 64, 64, 0, F32, 256) < 0
