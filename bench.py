@@ -26,7 +26,7 @@ PEAK_HBM_GBS = 8000.0         # MI355X HBM3E
 # HBM-side bytes per launch of the first FFN GEMM at c2_mixtral from rocprofv3 counters (FETCH_SIZE x 2.0 +
 # WRITE_SIZE x 1.0, see profiles/bench_c2_mixtral_layer_share.md), valid for the kernel source whose SHA-256
 # starts with the digest below; reported as null as soon as ffn.hip differs from what the counters saw.
-GEMM1_TRAFFIC = {"c2_mixtral": {"bytes": 3.9034e+06 * 1024 * 2.0 + 6.3078e+05 * 1024, "ffn_hip_sha256": "2f838d7c26705e87"}}
+GEMM1_TRAFFIC = {"c2_mixtral": {"bytes": 3.9048e+06 * 1024 * 2.0 + 6.3078e+05 * 1024, "ffn_hip_sha256": "75f724fe2537c030"}}
 
 
 def gemm1_traffic_bytes(name):
@@ -233,8 +233,8 @@ def box_reference(torch, wl, cfg, P):
     library's reference kernel that reads the token block of this workload once and writes it twice with
     streaming 16-byte accesses (the send buffer's traffic without indexing).  mfma_only_TFLOPs: the
     library's register-only loop of independent v_mfma_f32_32x32x16_bf16 on one wave per SIMD of every compute
-    unit, about 5 ms long (no LDS, no memory traffic: the ceiling of the matrix cores at the clock this box
-    grants them).  vendor_gemm_bf16_TFLOPs: hipBLASLt's GEMM of one projection of the first FFN GEMM."""
+    unit, about 5 ms long (no LDS, no memory traffic: what the matrix cores reach with that instruction at the clock
+    this box grants them; the large FFN tiles use v_mfma_f32_16x16x32_bf16, which takes less power).  vendor_gemm_bf16_TFLOPs: hipBLASLt's GEMM of one projection of the first FFN GEMM."""
     dev = wl["recv"].device
     ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
     src = torch.empty(256 << 20, dtype=torch.uint8, device=dev)

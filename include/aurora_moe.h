@@ -322,8 +322,8 @@ int moe_selfcheck_tile_map(const int32_t* seg_offset, const int32_t* seg_expert,
  * around their one kernel, WAIT for it and return its duration in milliseconds in ms_out, HOST [1]).
  *
  * moe_diag_mfma_only: n_blocks blocks of 4 waves, every wave issues iters x 16 independent
- * v_mfma_f32_32x32x16_bf16 (the FFN kernel's 4 x 4 register blocking) on operands that stay in registers: what
- * the matrix cores sustain with no operand traffic at all.  sink: device [n_blocks*256] fp32 out (sums, so
+ * v_mfma_f32_32x32x16_bf16 (as many accumulators as the FFN's large tiles) on operands that stay in registers: what
+ * the matrix cores sustain with that instruction and no operand traffic at all.  sink: device [n_blocks*256] fp32 out (sums, so
  * that the work cannot be dropped).  flop_out HOST [1]: the floating-point operations issued.
  * iters a multiple of 4 in [4, 2^24], 1 <= n_blocks <= 65536.
  *

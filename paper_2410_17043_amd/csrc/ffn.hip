@@ -1610,7 +1610,7 @@ __device__ __forceinline__ void sum_pieces(int unit_lo, int unit_hi, const float
 // issued in PAIRS of k-tiles (2q, 2q+1) every second iteration, interleaved so that the two
 // halves of every 128-byte memory line are requested back to back: half-line requests that
 // come a whole k-tile apart cost about twice the L2 bandwidth.  The pair (kt+4, kt+5) is issued
-// in iteration kt (kt even) and first needed 2.5 iterations later.
+// from iteration kt on (kt even) and has to be there before iteration kt+3.
 // The MFMAs are issued as D = B . A^T (operands swapped), so a lane ends up with 4 consecutive
 // output COLUMNS of one row (see store_tile).
 //
@@ -2599,7 +2599,9 @@ TileShape choose_shape(int R, int n_used, int N, int K, int act, int cus) {
 // half each; a height at which that exceeds 1.04 is given up for the one with the least (256 has 1).  The constants are
 // fitted to 430000 GEMMs of 65 to 20000 rows, 1 to 64 experts, H and F of 128 to 14336, weights from cold memory (median
 // error 5 %).  Over those the expert FFN is more than 3 % slower than one block per 256 x 256 tile was in 0.4 % of the
-// shares, in 2.9 % without this check; the mean gain is 1.249, 1.230 without.
+// shares, in 2.9 % without this check; the mean gain is 1.249, 1.230 without.  (All constants are of the loops with 32 x 32 x 16
+// products, 2 to 9 % slower than today's.  Fitted again to 68000 GEMMs of today's the rule would be 0.5 % faster in the mean and more
+// than 3 % slower in 4 % of them; tiles of 192 x 128 beside the three, 2.2 % faster and 1.1 %.)
 struct ShapeCost { double start, a, b, a2, pair, b_pair, piece0, piece, gelu, tb_s, first_bytes; };
 double played_us(TileShape t, int tiles_m, int R, int n_used, int N, int K, int act, int cus) {
     // start of the launch; per round and per k-tile of it (at no occupancy, and what full occupancy adds); rounds with two

@@ -879,6 +879,26 @@ def test_expert_ffn_narrow_tiles_of_one_segment(H, R, lo, hi, expert):
         H.assert_close(out[lo:hi], O.ffn(recv[lo:hi], w["w1"], w["w_up"], w["w_down"], 2), "bf16")
 
 
+# Grids that are numbered in strips (192 to 3000 tiles, no thicker bands of N): the numbers come from either map kernel, for one GEMM, the
+# other or both, with one height and with two; strips of two widths, a last round that is cut along K behind whole tiles.
+@pytest.mark.parametrize("R,Hd,F,n_local,nseg,act", [(3300, 128, 1024, 3, 12, 0), (3300, 1024, 128, 3, 100, 1), (4000, 1152, 1408, 4, 9, 2), (2741, 1152, 2304, 4, 24, 0),
+                                                     (8500, 2048, 768, 2, 5, 0)])
+def test_expert_ffn_grids_in_strips(H, R, Hd, F, n_local, nseg, act):
+    import ctypes as C
+    from paper_2410_17043_amd import _lib
+    got = (C.c_int32 * 2)()
+    assert _lib.load().moe_selfcheck_tile_shapes(R, n_local, nseg, Hd, F, act, 256, got) == 0
+    grids = [(-(-R // got[0]), -(-F // ((64 if got[0] == 128 else 128) if act == 2 else (128 if got[0] == 128 else 256)))), (-(-R // got[1]), -(-Hd // (128 if got[1] == 128 else 256)))]
+    assert any(192 <= m * n <= 3000 and not (m // 8 < 4 and n // 8 > m // 8) for m, n in grids), grids
+    cfg = small("c2_mixtral", H=Hd, F=F, act=act)
+    r = np.random.default_rng(R + nseg)
+    recv = W.to_bf16_grid(r.standard_normal((R, Hd)).astype(np.float32))
+    experts = [W.make_expert_weights(cfg, e) for e in range(n_local)]
+    off, exp = make_segments(r, R, nseg, n_local)
+    out = H.host(H.run_ffn(H.dev(recv, "bf16"), off, exp, [H.weights_to_dev(w, "bf16") for w in experts], Hd, F, act, "bf16"))
+    H.assert_close(out, O.expert_ffn(recv, off, exp, experts, act), "bf16")
+
+
 # Both GEMMs in one kernel (32-row tiles): one row, a row less and more than a tile, several tiles; one column tile per wave and
 # several, in either GEMM; rows from all over, experts in falling order (more runs than experts), segments without rows, of unknown
 # experts and outside the rows.  Against the oracle, and against the GEMMs by themselves, which moe_expert_ffn_timed runs.
