@@ -2972,6 +2972,11 @@ bool takes_small(int R, int n_used, int nseg, int H, int F, int act, int dtype, 
            (double)mats * H * F * es <= (dtype == MOE_BF16 ? kSmallBytesBf16 : kSmallBytesF32) &&
            R + (int64_t)n_used * (kSmallRows - 1) <= (int64_t)kSmallPerCU * cus * kSmallRows;
 }
+// whether two arrays of `bytes` have a byte in common
+bool share_memory(const void* a, const void* b, size_t bytes) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y ? y - x < bytes : x - y < bytes;
+}
 template <int DT, int EPI>
 int launch_small(const void* x, const ExpertTable& tab, SegList seg, int R, int n_used, int H, int F, void* out, hipStream_t st) {
     seg.max_tiles = max_tiles_of(R, kSmallRows, seg.nseg);
@@ -3321,7 +3326,8 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     // gathered tiles address their rows by 32-bit byte offsets from the tile's first row
     const int gather = (size_t)R * (size_t)std::max(H, F) * elem_size(dtype) <= 0xFFFFFFFFull ? 1 : 0;
     const int n_used = std::min(gather ? std::min(n_local, nseg) : nseg, R);   // runs of rows that share no tile
-    if (timed_gemm == 0 && !ev && takes_small(R, n_used, nseg, H, F, act, dtype, round_size())) {   // (with events: the GEMMs, which they time)
+    // a block of the kernel of both GEMMs writes its rows of `out` while others still read theirs of `recv`; the GEMMs apart do not
+    if (timed_gemm == 0 && !ev && !share_memory(recv, out, (size_t)R * H * elem_size(dtype)) && takes_small(R, n_used, nseg, H, F, act, dtype, round_size())) {   // (with events: the GEMMs, which they time)
         const SegList list = {seg_offset, seg_expert, nseg, R, n_local, gather, 0};
 #define MOE_SMALL(DT, EPI) launch_small<DT, EPI>(recv, tab, list, R, n_used, H, F, out, st)
         if (dtype == MOE_BF16) return act == MOE_ACT_SWIGLU ? MOE_SMALL(MOE_BF16, EPI_SWIGLU) : act == MOE_ACT_GELU_MLP ? MOE_SMALL(MOE_BF16, EPI_GELU) : MOE_SMALL(MOE_BF16, EPI_SILU);

@@ -943,6 +943,29 @@ def test_expert_ffn_small(H, dtype, act, R, Hd, F, n_local, off, exp):
     H.assert_close(out[written], ref[written], dtype)
 
 
+# The outputs may lie over the received rows, in place or some rows further: each output still comes from the rows as they were.
+@pytest.mark.parametrize("dtype,Hd,F,act", [("fp32", 64, 128, 0), ("bf16", 256, 128, 2)])
+@pytest.mark.parametrize("shift", [0, 1, 40, -40, -1])
+def test_expert_ffn_small_experts_over_their_own_rows(H, dtype, Hd, F, act, shift):
+    from paper_2410_17043_amd import _lib
+    R, n_local, nseg = 700, 2, 9
+    assert _lib.load().moe_selfcheck_small(R, n_local, nseg, Hd, F, act, 1 if dtype == "bf16" else 0, 256) == 1
+    r = np.random.default_rng(shift + 50)
+    recv = r.standard_normal((R, Hd)).astype(np.float32)
+    if dtype == "bf16":
+        recv = W.to_bf16_grid(recv)
+    off, exp = make_segments(r, R, nseg, n_local)
+    experts = [W.make_expert_weights(small("c2_mixtral", H=Hd, F=F, act=act), e) for e in range(n_local)]
+    both = torch.zeros((R + 40, Hd), dtype=H.P.TORCH_DTYPE[dtype], device=H.DEV)
+    x = both[max(-shift, 0):][:R]
+    out = both[max(shift, 0):][:R]
+    x.copy_(H.dev(recv, dtype))
+    i32 = dict(dtype=torch.int32, device=H.DEV)
+    ws = torch.empty(H.P.moe_ffn_workspace_bytes(R, Hd, F, act, dtype), dtype=torch.uint8, device=H.DEV)
+    H.P.moe_expert_ffn(x, R, torch.tensor(off, **i32), torch.tensor(exp, **i32), nseg, [H.weights_to_dev(w, dtype) for w in experts], Hd, F, act, dtype, out, ws)
+    H.assert_close(H.host(out), O.expert_ffn(recv, off, exp, experts, act), dtype)
+
+
 # fp32 GEMMs on three bf16 parts (128-row tiles): a K that ends inside a k-tile and an odd number of them, gathered and
 # ragged tiles, N of no whole tile, several tiles per block, one kernel of each kind with a map of its own, K of the least four k-tiles
 @pytest.mark.parametrize("act,R,Hd,F,n_local,nseg,rows", [(1, 1800, 1156, 1164, 2, 9, [128, 128]), (2, 3000, 292, 1156, 3, 40, [128, 64]),
