@@ -27,7 +27,7 @@
 // up to 128 rows per expert, those of at most 64 rows included, takes narrow tiles where they are modelled faster
 // (gemm_bf16_narrow_kernel: 32 to 128 rows x 32 or 64 weight rows over the whole of K, see take_narrow).
 //
-// Experts of up to 192 KB (bf16; fp32: 128 KB) and few rows: both GEMMs in one kernel, without a tile map (ffn_small_kernel).
+// Experts of up to 192 KB (bf16; fp32: 128 KB) and few blocks: both GEMMs in one kernel, without a tile map (ffn_small_kernel, see takes_small).
 //
 // fp32 path: 128 x 128 tiles of three bf16 parts per element on the bf16 matrix cores (gemm_f32_parts_kernel); where there are
 // too few of them, 64 x 64 tiles on the fp32 matrix cores (gemm_f32_kernel).
@@ -2960,17 +2960,28 @@ int launch_f32(bool in_parts, bool need_map, const void* A, int lda, const TileM
     return MOE_OK;
 }
 
-// Which shares take ffn_small_kernel: weights of an expert that a CU fetches in about the time of the launches that are saved - up to
-// 192 KB in bf16, 128 KB in fp32, whose products take longer - and at most two blocks per CU, since every block fetches them
-// again.  One call with its map and two GEMMs -> in one kernel (us): fp32, 64 -> 128 -> 64 517 rows 12.3 -> 7.8, 16000 rows SwiGLU
-// 19.5 -> 13.4, 128 -> 128 -> 128 13.3 -> 11.0 (SwiGLU, 192 KB: 13.4 -> 13.9); bf16, 256 -> 128 -> 256 300 rows 16.0 -> 10.0, SwiGLU 15.0 -> 11.8,
-// 8000 rows GELU 16.7 -> 10.7, 16000 rows 17.6 -> 16.8, 30000 rows SwiGLU 24.0 -> 45 (SwiGLU of 256 -> 256 -> 256, 384 KB: 16.1 -> 25).
-constexpr int kSmallBytesBf16 = 192 << 10, kSmallBytesF32 = 128 << 10, kSmallPerCU = 2;
+// Which shares take ffn_small_kernel: those whose weights a block fetches in about the time of the launches that are saved.  The figures are
+// one call with its map and two GEMMs over one call in one kernel, called again and again / with the caches flushed before each call.
+// - Up to one block per CU: 192 KB of weights per expert in bf16, 128 KB in fp32, whose products take longer.  bf16 192 KB SwiGLU
+//   1.10 to 1.29 / 1.10 to 1.25, GELU 1.11 to 1.34 (256 KB 0.90 to 1.14); fp32 128 KB 1.10 to 1.44 / 0.98 to 1.37 (192 KB 0.92 to 1.4).
+// - bf16 with at most kSmallFewRows rows per expert, where narrow tiles of few weight rows spread the weights over more CUs: 128 KB
+//   (1.16 to 1.45 / 0.95 to 1.19; 192 KB 0.91 to 1.25 / 0.72 to 0.98), and 64 KB for a list of one segment, which needs no map there
+//   (1.16 to 1.30 / 1.06 to 1.26; 96 KB 1.00 to 1.09 / 0.86 to 1.04, 192 KB 0.61 to 0.77 / 0.54 to 0.66).
+// - A second block per CU fetches the weights again, and its rows are then a good part of what it moves: weights, rows and outputs
+//   together at most 144 KB in bf16, 160 KB in fp32.  bf16 128 -> 256 (144 KB) 1.02 to 1.13 / 1.16 to 1.28, 256 -> 128 (160 KB) 0.91 to
+//   1.03, SwiGLU of 128 -> 128 (112 KB) 1.18 to 1.31, of 256 -> 128 (224 KB) 0.71 to 0.80; fp32 128 -> 128 (160 KB) 1.06 to 1.14, SwiGLU of
+//   64 -> 192 (160 KB) 1.12 to 1.21, 256 -> 64 (192 KB) 0.85 to 1.02.  With a third one 96 KB of bf16 are at 0.80.
+constexpr int kSmallBytesBf16 = 192 << 10, kSmallBytesF32 = 128 << 10;
+constexpr int kSmallFewRows = 128, kSmallFewBytes = 128 << 10, kSmallOneSegmentBytes = 64 << 10;
+constexpr int kSmallMovedBf16 = 144 << 10, kSmallMovedF32 = 160 << 10, kSmallPerCU = 2;
 bool takes_small(int R, int n_used, int nseg, int H, int F, int act, int dtype, int cus) {
     const int es = elem_size(dtype), mats = act == MOE_ACT_SWIGLU ? 3 : 2;
-    return nseg <= kSmallMapSegs && (int64_t)H * es % (64 * kSmallSteps) == 0 && (int64_t)F * es % (64 * kSmallSteps) == 0 &&
-           (double)mats * H * F * es <= (dtype == MOE_BF16 ? kSmallBytesBf16 : kSmallBytesF32) &&
-           R + (int64_t)n_used * (kSmallRows - 1) <= (int64_t)kSmallPerCU * cus * kSmallRows;
+    if (nseg > kSmallMapSegs || (int64_t)H * es % (64 * kSmallSteps) != 0 || (int64_t)F * es % (64 * kSmallSteps) != 0) return false;
+    const bool bf16 = dtype == MOE_BF16, few = bf16 && R <= (int64_t)kSmallFewRows * n_used;
+    const double weights = (double)mats * H * F * es, rows = 2.0 * kSmallRows * H * es;   // bytes
+    if (weights > (!bf16 ? kSmallBytesF32 : !few ? kSmallBytesBf16 : nseg == 1 ? kSmallOneSegmentBytes : kSmallFewBytes)) return false;
+    const int64_t tile_rows = R + (int64_t)n_used * (kSmallRows - 1), round = (int64_t)cus * kSmallRows;
+    return tile_rows <= round || (tile_rows <= kSmallPerCU * round && weights + rows <= (bf16 ? kSmallMovedBf16 : kSmallMovedF32));
 }
 // whether two arrays of `bytes` have a byte in common
 bool share_memory(const void* a, const void* b, size_t bytes) {

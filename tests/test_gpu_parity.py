@@ -906,7 +906,8 @@ def test_expert_ffn_grids_in_strips(H, R, Hd, F, n_local, nseg, act):
     ("fp32", 0, 517, 64, 128, 2, None, 8), ("fp32", 2, 33, 64, 64, 1, [0, 33], [0]), ("fp32", 1, 31, 256, 64, 3, None, 5), ("fp32", 0, 1, 128, 128, 1, [0, 1], [0]),
     ("fp32", 2, 700, 64, 128, 2, [0, 90, 90, 200, 333, 700], [1, 0, 0, 1, 0]), ("fp32", 0, 300, 64, 192, 4, None, 64),
     ("bf16", 2, 300, 256, 128, 2, None, 8), ("bf16", 1, 32, 128, 128, 1, [0, 32], [0]), ("bf16", 0, 1029, 128, 256, 4, None, 64), ("bf16", 2, 8000, 128, 256, 2, None, 3),
-    ("bf16", 0, 260, 256, 128, 3, [5, 60, 70, 130, 130, 300], [2, -1, 0, 1, 2]), ("bf16", 2, 65, 256, 128, 2, [0, 1, 33, 65], [1, 5, 0]),
+    ("bf16", 0, 260, 256, 128, 3, [5, 60, 70, 130, 130, 300], [2, -1, 0, 1, 2]), ("bf16", 2, 65, 128, 128, 2, [0, 1, 33, 65], [1, 5, 0]),
+    ("bf16", 1, 1, 128, 128, 1, [0, 1], [0]),
     # overlapping segments: more runs of one expert than experts, and more tiles than rows
     ("fp32", 0, 64, 64, 64, 1, [0, 64, 10, 64, 20, 64, 30], [0, 0, 0, 0, 0, 0])])
 def test_expert_ffn_small(H, dtype, act, R, Hd, F, n_local, off, exp):

@@ -607,3 +607,22 @@ def test_both_gemms_in_one_kernel_only_for_small_experts_and_few_rows():
                                        (16384, 1, 1, 64, 128, 0, F32), (16384, 2, 8, 256, 128, 0, BF16), (300, 2, 8, 256, 256, 2, BF16), (517, 2, 8, 1 << 30, 1 << 30, 0, F32)):
         assert takes(R, n, nseg, Hd, F, act, dt, 256) == 0, (R, Hd, F)
     assert takes(0, 1, 1, 64, 64, 0, F32, 256) < 0
+
+
+def test_no_share_runs_both_gemms_in_one_kernel_that_was_measured_slower_so():
+    """Few rows per expert beside narrow tiles, one segment beside narrow tiles without a map, a second block per CU of heavier experts;
+    and the shares next to them that were measured faster."""
+    from paper_2410_17043_amd import _lib
+    takes = _lib.load().moe_selfcheck_small
+    F32, BF16 = 0, 1
+    slower = [(1, 1, 1, 128, 256, 0, BF16), (64, 1, 1, 256, 128, 2, BF16), (16, 1, 1, 128, 128, 2, BF16), (100, 1, 1, 128, 256, 1, BF16),
+              (64, 2, 8, 256, 128, 2, BF16), (100, 4, 16, 128, 384, 0, BF16),
+              (9000, 2, 8, 256, 128, 2, BF16), (16000, 2, 8, 256, 128, 2, BF16), (12000, 2, 8, 128, 384, 0, BF16), (10000, 1, 1, 256, 128, 0, BF16),
+              (12000, 2, 8, 256, 64, 0, F32), (9000, 2, 8, 256, 64, 1, F32)]
+    faster = [(1, 1, 1, 128, 128, 0, BF16), (64, 1, 1, 128, 128, 1, BF16), (64, 2, 8, 128, 256, 0, BF16), (300, 1, 1, 256, 128, 2, BF16), (8000, 2, 8, 256, 128, 2, BF16),
+              (12000, 2, 8, 128, 256, 1, BF16), (16000, 2, 8, 128, 128, 2, BF16), (1, 1, 1, 256, 64, 0, F32), (8000, 1, 1, 256, 64, 0, F32),
+              (12000, 2, 8, 128, 128, 0, F32), (16000, 2, 8, 64, 128, 2, F32)]
+    for share in slower:
+        assert takes(*share, 256) == 0, share
+    for share in faster:
+        assert takes(*share, 256) == 1, share
