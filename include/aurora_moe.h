@@ -220,11 +220,11 @@ int moe_expert_ffn(const void* recv, int32_t R, const int32_t* seg_offset, const
                    int32_t act, int32_t dtype, void* out, void* workspace, size_t workspace_bytes,
                    void* stream);
 
-/* Diagnostic twin of moe_expert_ffn (same arguments, same result; to rounding where moe_expert_ffn runs both GEMMs
- * in one kernel, see moe_selfcheck_small): records HIP
+/* Diagnostic twin of moe_expert_ffn (same arguments, same kernels, same result): records HIP
  * events on `stream` around each of its kernels, WAITS for the last one, and
  * returns the durations in milliseconds in ms_out (HOST [3]): tile map, first GEMM
- * with the activation (Sec. 2.1's FFN up-projection), second GEMM.  For measurement
+ * with the activation (Sec. 2.1's FFN up-projection), second GEMM; 0, the one kernel's, 0 where
+ * both GEMMs run in one (moe_selfcheck_small).  For measurement
  * only: unlike every other device entry point it synchronises with the host. */
 int moe_expert_ffn_timed(const void* recv, int32_t R, const int32_t* seg_offset, const int32_t* seg_expert,
                          int32_t nseg, const moe_expert_w* experts, int32_t n_local, int32_t H, int32_t F,
@@ -269,7 +269,7 @@ int moe_selfcheck_tile_shapes(int32_t R, int32_t n_used, int32_t nseg, int32_t H
 int moe_selfcheck_flow_player(int32_t n, const int64_t* D, const double* B, const int32_t* order);
 
 /* 1: a share of R rows for n_used experts in nseg segments runs both GEMMs in one kernel on a device of ncu compute units (0: not).
- * moe_expert_ffn_timed, which reports the GEMMs one by one, always runs them apart. */
+ * Only where the outputs share no memory with the received rows. */
 int moe_selfcheck_small(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t dtype, int32_t ncu);
 /* Narrow tiles that the two GEMMs of a bf16 share take instead (few rows per expert): 10 MT + NT for tiles of 32 MT rows x
  * 32 NT weight rows, 0 where the kernels of moe_selfcheck_tile_shapes run.  Checks that the tile maps fit. */
@@ -338,8 +338,8 @@ int moe_selfcheck_tile_map(const int32_t* seg_offset, const int32_t* seg_expert,
  * activations, ceil(H / 256) for the second GEMM; MOE_ESHAPE otherwise, and for fp32 or shares of at most 64 rows (other
  * kernels).  The GEMM takes the tiles that moe_expert_ffn takes if marks has room for all of them:
  * (((R + 127) / 128 + nseg) * ceil(N / 64 or 128) + 512) * 16 elements always do; with fewer it may take 256-row tiles.
- * A share of few rows per expert, to which moe_expert_ffn may give narrow tiles (moe_selfcheck_narrow), is run with the tiles
- * that it would take without them: there the marks are not those of the kernel that moe_expert_ffn runs, and the outputs
+ * A share of few rows per expert, to which moe_expert_ffn may give narrow tiles (moe_selfcheck_narrow), and one whose GEMMs it
+ * runs in one kernel (moe_selfcheck_small) are run with the tiles that they would take without: there the marks are not those of the kernel that moe_expert_ffn runs, and the outputs
  * agree with its up to the order of the sums.
  * Everything else as moe_expert_ffn. */
 int moe_diag_ffn_phases(const void* recv, int32_t R, const int32_t* seg_offset, const int32_t* seg_expert, int32_t nseg,

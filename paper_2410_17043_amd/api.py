@@ -231,7 +231,8 @@ def moe_expert_ffn(recv, R, seg_offset, seg_expert, nseg, experts, H, F, act, dt
 
 
 def moe_expert_ffn_timed(recv, R, seg_offset, seg_expert, nseg, experts, H, F, act, dtype, out, workspace):
-    """Measurement twin of moe_expert_ffn; returns (ms_tilemap, ms_gemm1, ms_gemm2) and synchronises."""
+    """Measurement twin of moe_expert_ffn; returns (ms_tilemap, ms_gemm1, ms_gemm2) and synchronises; (0, ms, 0) where both
+    GEMMs run in one kernel."""
     tab = experts if isinstance(experts, C.Array) else expert_table(experts)
     ms = (C.c_float * 3)()
     _check("moe_expert_ffn_timed", _lib.load().moe_expert_ffn_timed(

@@ -3290,10 +3290,12 @@ extern "C" size_t moe_ffn_workspace_bytes(int32_t R_max, int32_t H, int32_t F, i
     return least_workspace(R_max, F, dtype) + partial;
 }
 
+// around the kernels: in front of the tile map, the first GEMM, the second, and behind it; at[1] and at[2] around one kernel of both GEMMs
+struct FfnEvents { hipEvent_t at[4]; bool one_kernel; };
 // timed_gemm: 0 none, 1 / 2: that GEMM runs as its TIMED instantiation and writes marks (bf16, more than 64 rows)
 static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, const int32_t* seg_expert, int32_t nseg,
                     const moe_expert_w* experts, int32_t n_local, int32_t H, int32_t F, int32_t act, int32_t dtype,
-                    void* out, void* workspace, size_t workspace_bytes, hipStream_t st, hipEvent_t* ev,
+                    void* out, void* workspace, size_t workspace_bytes, hipStream_t st, FfnEvents* ev,
                     int timed_gemm = 0, long long* marks = nullptr, size_t marks_len = 0) {
     if (!recv || !seg_offset || !seg_expert || !experts || !out || !workspace)
         return moe_set_error(MOE_EINVAL, "moe_expert_ffn: NULL argument");
@@ -3326,7 +3328,7 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         tab.w_down[e] = experts[e].w_down;
     }
     if (R == 0 || nseg == 0) {
-        if (ev) for (int i = 0; i < 4; ++i) MOE_HIP(hipEventRecord(ev[i], st));
+        if (ev) for (int i = 0; i < 4; ++i) MOE_HIP(hipEventRecord(ev->at[i], st));
         return MOE_OK;
     }
     void* hmid = reinterpret_cast<char*>(workspace) + tilemap_bytes(R);
@@ -3338,12 +3340,18 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     const int gather = (size_t)R * (size_t)std::max(H, F) * elem_size(dtype) <= 0xFFFFFFFFull ? 1 : 0;
     const int n_used = std::min(gather ? std::min(n_local, nseg) : nseg, R);   // runs of rows that share no tile
     // a block of the kernel of both GEMMs writes its rows of `out` while others still read theirs of `recv`; the GEMMs apart do not
-    if (timed_gemm == 0 && !ev && !share_memory(recv, out, (size_t)R * H * elem_size(dtype)) && takes_small(R, n_used, nseg, H, F, act, dtype, round_size())) {   // (with events: the GEMMs, which they time)
+    if (timed_gemm == 0 && !share_memory(recv, out, (size_t)R * H * elem_size(dtype)) && takes_small(R, n_used, nseg, H, F, act, dtype, round_size())) {
         const SegList list = {seg_offset, seg_expert, nseg, R, n_local, gather, 0};
+        if (ev) MOE_HIP(hipEventRecord(ev->at[1], st));
+        int rc;
 #define MOE_SMALL(DT, EPI) launch_small<DT, EPI>(recv, tab, list, R, n_used, H, F, out, st)
-        if (dtype == MOE_BF16) return act == MOE_ACT_SWIGLU ? MOE_SMALL(MOE_BF16, EPI_SWIGLU) : act == MOE_ACT_GELU_MLP ? MOE_SMALL(MOE_BF16, EPI_GELU) : MOE_SMALL(MOE_BF16, EPI_SILU);
-        return act == MOE_ACT_SWIGLU ? MOE_SMALL(MOE_F32, EPI_SWIGLU) : act == MOE_ACT_GELU_MLP ? MOE_SMALL(MOE_F32, EPI_GELU) : MOE_SMALL(MOE_F32, EPI_SILU);
+        if (dtype == MOE_BF16) rc = act == MOE_ACT_SWIGLU ? MOE_SMALL(MOE_BF16, EPI_SWIGLU) : act == MOE_ACT_GELU_MLP ? MOE_SMALL(MOE_BF16, EPI_GELU) : MOE_SMALL(MOE_BF16, EPI_SILU);
+        else rc = act == MOE_ACT_SWIGLU ? MOE_SMALL(MOE_F32, EPI_SWIGLU) : act == MOE_ACT_GELU_MLP ? MOE_SMALL(MOE_F32, EPI_GELU) : MOE_SMALL(MOE_F32, EPI_SILU);
 #undef MOE_SMALL
+        if (rc != MOE_OK || !ev) return rc;
+        ev->one_kernel = true;
+        MOE_HIP(hipEventRecord(ev->at[2], st));
+        return MOE_OK;
     }
     TileShape shape[2] = {TS_256, TS_256};
     bool in_parts[2] = {false, false};
@@ -3369,7 +3377,7 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     NarrowForm form[2] = {{0, 0}, {0, 0}};
     if (dtype == MOE_BF16 && timed_gemm == 0) take_narrow(R, n_used, nseg, H, F, act, round_size(), bm, form);
     if ((dtype == MOE_BF16 || bm[0] != bm[1]) && !maps_fit(R, nseg, bm[0], bm[1])) return moe_set_error(MOE_EINTERNAL, "moe_expert_ffn: tile maps of %d rows in %d segments", R, nseg);
-    if (ev) MOE_HIP(hipEventRecord(ev[0], st));
+    if (ev) MOE_HIP(hipEventRecord(ev->at[0], st));
     MapJobs jobs;
     jobs.job[0] = MapJob{bm[0], max_tiles_of(R, bm[0], nseg), tilemap_at(workspace, R)};
     jobs.job[1] = (bm[1] == bm[0]) ? jobs.job[0] : MapJob{bm[1], max_tiles_of(R, bm[1], nseg), tilemap_at(workspace, R, 1, jobs.job[0].max_tiles)};
@@ -3404,7 +3412,7 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         hipLaunchKernelGGL(tilemap_kernel, dim3(n_maps), dim3(kMapThreads), 0, st, seg_offset, seg_expert, nseg, R, n_local, gather, jobs);
     }
     if (need_map) MOE_LAUNCH_CHECK("tilemap_kernel");
-    if (ev) MOE_HIP(hipEventRecord(ev[1], st));
+    if (ev) MOE_HIP(hipEventRecord(ev->at[1], st));
     int rc = MOE_OK;
     if (form[0].mt) {
         if (act == MOE_ACT_SWIGLU) rc = launch_bf16_narrow<EPI_SWIGLU>(form[0], recv, H, m, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, one, st);
@@ -3427,13 +3435,13 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         else rc = launch_f32<EPI_SILU>(in_parts[0], need_map, recv, H, m, strips[0], seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
     }
     if (rc != MOE_OK) return rc;
-    if (ev) MOE_HIP(hipEventRecord(ev[2], st));
+    if (ev) MOE_HIP(hipEventRecord(ev->at[2], st));
     if (form[1].mt) rc = launch_bf16_narrow<EPI_PLAIN>(form[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, one, st);
     else if (skinny) rc = launch_bf16_skinny<EPI_PLAIN>(hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, partial, st);
     else if (dtype == MOE_BF16) rc = launch_bf16_shape<EPI_PLAIN>(shape[1], hmid, F, m2, strips[1], tab, 2, 2, H, F, out, H, R, nseg, n_used, partial, st, timed_gemm == 2, marks, marks_len);
     else rc = launch_f32<EPI_PLAIN>(in_parts[1], need_map, hmid, F, m2, strips[1], seg, tab, 2, 2, H, F, out, H, R, nseg, n_used, f32_pieces[1], st);
     if (rc != MOE_OK) return rc;
-    if (ev) MOE_HIP(hipEventRecord(ev[3], st));
+    if (ev) MOE_HIP(hipEventRecord(ev->at[3], st));
     return MOE_OK;
 }
 
@@ -3451,18 +3459,20 @@ extern "C" int moe_expert_ffn_timed(const void* recv, int32_t R, const int32_t* 
                                     void* stream, float* ms_out) {
     if (!ms_out) return moe_set_error(MOE_EINVAL, "moe_expert_ffn_timed: ms_out is NULL");
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
+    FfnEvents ev = {{nullptr, nullptr, nullptr, nullptr}, false};
     int rc = MOE_OK;
     for (int i = 0; i < 4 && rc == MOE_OK; ++i)
-        if (hipEventCreate(&ev[i]) != hipSuccess) rc = moe_set_error(MOE_EHIP, "hipEventCreate failed");
+        if (hipEventCreate(&ev.at[i]) != hipSuccess) rc = moe_set_error(MOE_EHIP, "hipEventCreate failed");
     if (rc == MOE_OK)
         rc = ffn_impl(recv, R, seg_offset, seg_expert, nseg, experts, n_local, H, F, act, dtype, out, workspace,
-                      workspace_bytes, st, ev);
-    if (rc == MOE_OK && hipEventSynchronize(ev[3]) != hipSuccess) rc = moe_set_error(MOE_EHIP, "hipEventSynchronize failed");
-    for (int i = 0; i < 3 && rc == MOE_OK; ++i)
-        if (hipEventElapsedTime(&ms_out[i], ev[i], ev[i + 1]) != hipSuccess) rc = moe_set_error(MOE_EHIP, "hipEventElapsedTime failed");
+                      workspace_bytes, st, &ev);
+    if (rc == MOE_OK && hipEventSynchronize(ev.at[ev.one_kernel ? 2 : 3]) != hipSuccess) rc = moe_set_error(MOE_EHIP, "hipEventSynchronize failed");
+    for (int i = 0; i < 3 && rc == MOE_OK; ++i) {
+        if (ev.one_kernel && i != 1) ms_out[i] = 0.f;
+        else if (hipEventElapsedTime(&ms_out[i], ev.at[i], ev.at[i + 1]) != hipSuccess) rc = moe_set_error(MOE_EHIP, "hipEventElapsedTime failed");
+    }
     for (int i = 0; i < 4; ++i)
-        if (ev[i]) (void)hipEventDestroy(ev[i]);
+        if (ev.at[i]) (void)hipEventDestroy(ev.at[i]);
     return rc;
 }
 

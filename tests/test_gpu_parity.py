@@ -901,7 +901,8 @@ def test_expert_ffn_grids_in_strips(H, R, Hd, F, n_local, nseg, act):
 
 # Both GEMMs in one kernel (32-row tiles): one row, a row less and more than a tile, several tiles; one column tile per wave and
 # several, in either GEMM; rows from all over, experts in falling order (more runs than experts), segments without rows, of unknown
-# experts and outside the rows.  Against the oracle, and against the GEMMs by themselves, which moe_expert_ffn_timed runs.
+# experts and outside the rows.  Against the oracle, against the GEMMs by themselves (of
+# the same list with empty segments behind it, more than that kernel takes), and against moe_expert_ffn_timed, which runs and times it.
 @pytest.mark.parametrize("dtype,act,R,Hd,F,n_local,off,exp", [
     ("fp32", 0, 517, 64, 128, 2, None, 8), ("fp32", 2, 33, 64, 64, 1, [0, 33], [0]), ("fp32", 1, 31, 256, 64, 3, None, 5), ("fp32", 0, 1, 128, 128, 1, [0, 1], [0]),
     ("fp32", 2, 700, 64, 128, 2, [0, 90, 90, 200, 333, 700], [1, 0, 0, 1, 0]), ("fp32", 0, 300, 64, 192, 4, None, 64),
@@ -911,7 +912,6 @@ def test_expert_ffn_grids_in_strips(H, R, Hd, F, n_local, nseg, act):
     # overlapping segments: more runs of one expert than experts, and more tiles than rows
     ("fp32", 0, 64, 64, 64, 1, [0, 64, 10, 64, 20, 64, 30], [0, 0, 0, 0, 0, 0])])
 def test_expert_ffn_small(H, dtype, act, R, Hd, F, n_local, off, exp):
-    import torch
     from paper_2410_17043_amd import _lib
     r = np.random.default_rng(R + Hd)
     if off is None:
@@ -928,7 +928,13 @@ def test_expert_ffn_small(H, dtype, act, R, Hd, F, n_local, off, exp):
     apart = torch.full((R, Hd), float("nan"), dtype=H.P.TORCH_DTYPE[dtype], device="cuda")
     ws = torch.empty(H.P.moe_ffn_workspace_bytes(R, Hd, F, act, dtype), dtype=torch.uint8, device="cuda")
     i32 = dict(dtype=torch.int32, device="cuda")
-    H.P.moe_expert_ffn_timed(x, R, torch.tensor(off, **i32), torch.tensor(exp, **i32), len(exp), dev, Hd, F, act, dtype, apart, ws)
+    timed = torch.full_like(apart, float("nan"))
+    ms = H.P.moe_expert_ffn_timed(x, R, torch.tensor(off, **i32), torch.tensor(exp, **i32), len(exp), dev, Hd, F, act, dtype, timed, ws)
+    assert ms[0] == 0.0 and ms[1] > 0.0 and ms[2] == 0.0
+    assert np.array_equal(H.host(timed), out, equal_nan=True)
+    more = 65 - len(exp)
+    assert _lib.load().moe_selfcheck_small(R, min(n_local, 65, R), 65, Hd, F, act, 1 if dtype == "bf16" else 0, 256) == 0
+    H.P.moe_expert_ffn(x, R, torch.tensor(list(off) + [off[-1]] * more, **i32), torch.tensor(list(exp) + [0] * more, **i32), 65, dev, Hd, F, act, dtype, apart, ws)
     apart = H.host(apart)
     written = np.zeros(R, dtype=bool)
     for i, e in enumerate(exp):
