@@ -694,11 +694,14 @@ __host__ __device__ __forceinline__ void tile_of_block_bands(int id, int tiles_m
 // of one row), +2.5 % at 6745 and 7900 rows (three rows), +1 % at 4147 and 5000 (two rows); with bands of
 // four to seven rows the exchange gains or loses less than 1 %, so those keep the M bands.
 //
-// Grids of kFewestStripTiles to kStripTiles tiles whose N side has no thicker bands are mostly left-over M-tiles or low bands: those are numbered
-// in strips.  XCD x gets the x-th eighth of the tiles in an order that cuts N into strips and goes through a strip row by
-// row, so that the tiles resident on an XCD form a patch about as high as it is wide.  (Where N has the thicker bands, each
-// XCD reads weights of its own, which strips do not keep up: up to 7 % slower.)  FFN of 2741 rows of 1152 -> 2304 -> 1152 for four
-// experts 64.9 -> 61.0 us, 12000 of 1408 -> 2048 -> 1408 SwiGLU for eight 230 -> 217, 9000 of 2048 -> 1408 -> 2048 for four 163 -> 157, 16000 241 -> 236.
+// bf16 grids of kFewestStripTiles to kStripTiles tiles that N does not band (see plan_strips) are numbered in strips instead: XCD x gets
+// the x-th eighth of the tiles in an order that cuts N into strips and goes through a strip row by row, so that the tiles resident
+// on an XCD form a patch about as high as it is wide.  Bands -> strips on the kernels as they are, one FFN after the other: left-over
+// M-tiles and low bands, 2741 rows of 1152 -> 2304 -> 1152 for four experts 48.1 -> 47.2 us, 12000 of 1408 -> 2048 -> 1408 SwiGLU for
+// eight 208.3 -> 205.3, 2476 of 3584 -> 2560 -> 3584 111.2 -> 105.2; thick M bands, 16384 of 2048 -> 2816 -> 2048 SwiGLU 420.8 -> 409.8, 16318 of
+// 1664 -> 2816 -> 1664 253.0 -> 249.8, 20571 of 4096 -> 14336 -> 4096 (second GEMM) the same.  33 shares 1.009 in the geometric mean, three of
+// them 0.984 to 0.991.  (Where N has the thicker bands, each XCD reads weights of its own, which strips do not keep up: up to 7 %
+// slower.  Outside the two limits nothing was gained.)  fp32: 11 shares of 128 x 128 tiles 0.997 to 1.005, so those keep the bands.
 // Working the numbers below out in every block costs 0.4 us of a GEMM that takes 12 to 17, so the tile map holds them.
 __host__ __device__ __forceinline__ void tile_of_block_strips(int id, int total, int tiles_m, Strips p, int* tm, int* tn) {
     const int x = id % 8, base = total / 8, extra = total % 8;
@@ -1206,12 +1209,10 @@ __device__ __forceinline__ void multiply_exactly(const float* pa, const float* p
 template <int EPI, bool CUT>
 __global__ __launch_bounds__(512, 2) void gemm_f32_parts_kernel(const float* __restrict__ A, int lda, TileMap m, ExpertTable tab,
                                                                 int which0, int which1, int N, int K, float* __restrict__ C, int ldc,
-                                                                int tiles_n, const int32_t* __restrict__ strips_at, int ncu, int walk, float* partial) {
+                                                                int tiles_n, int ncu, int walk, float* partial) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     constexpr int NOUT = (EPI == EPI_SWIGLU) ? XN / 2 : XN;
-    auto word = [](const int32_t* p) { return *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p)); };
-    const int n_tiles_m = word(m.n_tiles);
-    const Strips strips = strips_at ? Strips{word(strips_at), word(strips_at + 1)} : Strips{0, 0};
+    const int n_tiles_m = *reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(m.n_tiles));
     const int total = n_tiles_m * tiles_n;
     const int nk_all = ((K + XK - 1) / XK + 1) & ~1;       // even; k-tiles past K count as zeros
     PartsCut cut = {total, 0, 1, nk_all};
@@ -1248,7 +1249,7 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_parts_kernel(const float* __r
             s.k0 = t.piece * cut.per;
             t.nk = min(cut.per, nk_all - s.k0);
         }
-        tile_of_block(id, total, n_tiles_m, tiles_n, strips, &tile_m, &tile_n);
+        tile_of_block(id, total, n_tiles_m, tiles_n, Strips{0, 0}, &tile_m, &tile_n);
         tile_m = __builtin_amdgcn_readfirstlane(tile_m);
         auto rec = [&](const int32_t* p) { return reinterpret_cast<const __attribute__((address_space(4))) int32_t*>(reinterpret_cast<uintptr_t>(p))[tile_m]; };
         t.row0 = rec(m.row0);
@@ -2923,7 +2924,7 @@ void take_cuts(int R, int n_used, int nseg, int H, int F, int act, int cus, cons
 // What is launched for up to max_items tiles; pieces of a last round take one round more at most.
 int parts_blocks(int max_items, int walk, int ncu, bool may_cut) { return walk_blocks(max_items + (may_cut ? ncu : 0), walk, ncu); }
 template <int EPI>
-int launch_f32_parts(const void* A, int lda, const TileMap& m, const int32_t* strips, const ExpertTable& tab, int which0, int which1, int N, int K,
+int launch_f32_parts(const void* A, int lda, const TileMap& m, const ExpertTable& tab, int which0, int which1, int N, int K,
                      void* C, int ldc, int R, int nseg, float* partial, hipStream_t st) {
     const int nout = (EPI == EPI_SWIGLU) ? XN / 2 : XN;
     const int tiles_n = (N + nout - 1) / nout, ncu = round_size(), walk = parts_walk_tiles(K);
@@ -2933,7 +2934,7 @@ int launch_f32_parts(const void* A, int lda, const TileMap& m, const int32_t* st
             attr_done = true;
         }
         hipLaunchKernelGGL(kernel, dim3(parts_blocks(max_tiles_of(R, XM, nseg) * tiles_n, walk, ncu, partial != nullptr)), dim3(512), kXLds, st,
-                           reinterpret_cast<const float*>(A), lda, m, tab, which0, which1, N, K, reinterpret_cast<float*>(C), ldc, tiles_n, strips, ncu, walk, partial);
+                           reinterpret_cast<const float*>(A), lda, m, tab, which0, which1, N, K, reinterpret_cast<float*>(C), ldc, tiles_n, ncu, walk, partial);
         return MOE_OK;
     };
     static bool attr_cut = false, attr_whole = false;
@@ -2944,9 +2945,9 @@ int launch_f32_parts(const void* A, int lda, const TileMap& m, const int32_t* st
 }
 
 template <int EPI>
-int launch_f32(bool in_parts, bool need_map, const void* A, int lda, const TileMap& m, const int32_t* strips, SegList seg, const ExpertTable& tab, int which0, int which1,
+int launch_f32(bool in_parts, bool need_map, const void* A, int lda, const TileMap& m, SegList seg, const ExpertTable& tab, int which0, int which1,
                int N, int K, void* C, int ldc, int R, int nseg, int n_used, float* partial, hipStream_t st) {
-    if (in_parts) return launch_f32_parts<EPI>(A, lda, m, strips, tab, which0, which1, N, K, C, ldc, R, nseg, partial, st);
+    if (in_parts) return launch_f32_parts<EPI>(A, lda, m, tab, which0, which1, N, K, C, ldc, R, nseg, partial, st);
     const int nout = (EPI == EPI_SWIGLU) ? FN / 2 : FN;
     const int tiles_n = (N + nout - 1) / nout;
     seg.max_tiles = max_tiles_of(R, FM, nseg);
@@ -3006,12 +3007,15 @@ int launch_small(const void* x, const ExpertTable& tab, SegList seg, int R, int 
 extern "C" int moe_selfcheck_tile_order(int32_t tiles_m, int32_t tiles_n, int32_t ncu, int32_t nk) {
     if (tiles_m < 1 || tiles_n < 1 || ncu < 1 || nk < 2 || (nk & 1)) return moe_set_error(MOE_EINVAL, "moe_selfcheck_tile_order: bad argument");
     const int total = tiles_m * tiles_n;
-    std::vector<int> seen((size_t)total, 0);
-    for (int id = 0; id < total; ++id) {
-        int tm = -1, tn = -1;
-        tile_of_block(id, total, tiles_m, tiles_n, plan_strips(tiles_m, tiles_n), &tm, &tn);
-        if (tm < 0 || tm >= tiles_m || tn < 0 || tn >= tiles_n) return moe_set_error(MOE_EINTERNAL, "tile %d maps outside the grid", id);
-        if (seen[(size_t)tm * tiles_n + tn]++) return moe_set_error(MOE_EINTERNAL, "tile (%d, %d) is produced twice", tm, tn);
+    const Strips numberings[2] = {Strips{0, 0}, plan_strips(tiles_m, tiles_n)};   // fp32, bf16
+    for (const Strips& strips : numberings) {
+        std::vector<int> seen((size_t)total, 0);
+        for (int id = 0; id < total; ++id) {
+            int tm = -1, tn = -1;
+            tile_of_block(id, total, tiles_m, tiles_n, strips, &tm, &tn);
+            if (tm < 0 || tm >= tiles_m || tn < 0 || tn >= tiles_n) return moe_set_error(MOE_EINTERNAL, "tile %d maps outside the grid", id);
+            if (seen[(size_t)tm * tiles_n + tn]++) return moe_set_error(MOE_EINTERNAL, "tile (%d, %d) is produced twice", tm, tn);
+        }
     }
     const TailPlan p = plan_tail(total, ncu, nk);
     if (p.n_full + p.n_tail != total || p.n_full % ncu != 0 && p.n_tail != 0) return moe_set_error(MOE_EINTERNAL, "tail plan does not partition the tiles");
@@ -3386,8 +3390,8 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     float* const f32_pieces[2] = {cuts[0] ? partial : nullptr, cuts[1] ? partial : nullptr};   // where an fp32 GEMM's tiles are cut
     jobs.done = (dtype == MOE_BF16 || f32_pieces[0] || f32_pieces[1]) ? tilemap_at(workspace, R, 0, max_tiles_for(R) - 2).rel : nullptr;
     for (int g = 0; g < 2; ++g)
-        jobs.tiles_n[g] = form[g].mt || skinny || (dtype == MOE_F32 && !in_parts[g]) ? 0 : columns_in_strips(R, bm[g], n_used,
-            tiled_columns(g == 0 ? F : H, g == 0 && act == MOE_ACT_SWIGLU, dtype == MOE_F32 ? XN : shape[g] == TS_128 ? TileGeom<2, 2>::BN : TileGeom<4, 4>::BN));
+        jobs.tiles_n[g] = form[g].mt || skinny || dtype == MOE_F32 ? 0 : columns_in_strips(R, bm[g], n_used,
+            tiled_columns(g == 0 ? F : H, g == 0 && act == MOE_ACT_SWIGLU, shape[g] == TS_128 ? TileGeom<2, 2>::BN : TileGeom<4, 4>::BN));
     if (jobs.done) {
         jobs.job[0].m.done = jobs.done;
         jobs.job[1].m.done = jobs.done + kMaxSplitTiles;
@@ -3430,16 +3434,16 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
         else
             rc = launch_bf16_shape<EPI_SILU>(shape[0], recv, H, m, strips[0], tab, 0, 0, F, H, hmid, F, R, nseg, n_used, partial, st, timed_gemm == 1, marks, marks_len);
     } else {
-        if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(in_parts[0], need_map, recv, H, m, strips[0], seg, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
-        else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(in_parts[0], need_map, recv, H, m, strips[0], seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
-        else rc = launch_f32<EPI_SILU>(in_parts[0], need_map, recv, H, m, strips[0], seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
+        if (act == MOE_ACT_SWIGLU) rc = launch_f32<EPI_SWIGLU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 1, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
+        else if (act == MOE_ACT_GELU_MLP) rc = launch_f32<EPI_GELU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
+        else rc = launch_f32<EPI_SILU>(in_parts[0], need_map, recv, H, m, seg, tab, 0, 0, F, H, hmid, F, R, nseg, n_used, f32_pieces[0], st);
     }
     if (rc != MOE_OK) return rc;
     if (ev) MOE_HIP(hipEventRecord(ev->at[2], st));
     if (form[1].mt) rc = launch_bf16_narrow<EPI_PLAIN>(form[1], hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, n_used, one, st);
     else if (skinny) rc = launch_bf16_skinny<EPI_PLAIN>(hmid, F, m2, tab, 2, 2, H, F, out, H, R, nseg, partial, st);
     else if (dtype == MOE_BF16) rc = launch_bf16_shape<EPI_PLAIN>(shape[1], hmid, F, m2, strips[1], tab, 2, 2, H, F, out, H, R, nseg, n_used, partial, st, timed_gemm == 2, marks, marks_len);
-    else rc = launch_f32<EPI_PLAIN>(in_parts[1], need_map, hmid, F, m2, strips[1], seg, tab, 2, 2, H, F, out, H, R, nseg, n_used, f32_pieces[1], st);
+    else rc = launch_f32<EPI_PLAIN>(in_parts[1], need_map, hmid, F, m2, seg, tab, 2, 2, H, F, out, H, R, nseg, n_used, f32_pieces[1], st);
     if (rc != MOE_OK) return rc;
     if (ev) MOE_HIP(hipEventRecord(ev->at[3], st));
     return MOE_OK;
