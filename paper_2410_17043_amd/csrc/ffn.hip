@@ -737,7 +737,8 @@ __host__ __device__ __forceinline__ TailPlan plan_tail(int total, int ncu, int n
     const int rem = total % ncu;
     const int npairs = nk / 2;
     if (rem == 0) return p;
-    // up to 8 pieces of at least 16 k-tiles (more only add partial tiles); 2 or 3 pieces pay for the extra
+    // up to 8 pieces of at least 16 k-tiles (more only add partial tiles) but for the last one, which has four at least: of p <= 8
+    // pieces of ceil(npairs / p) pairs, npairs >= 8 p, the last has (npairs - (p - 1)^2) / p > 1 of them.  2 or 3 pieces pay for the extra
     // pass only when a piece is still long (64 k-tiles)
     const int parts = min(min(ncu / rem, npairs / 8), 8);
     if (parts < 2 || (parts < 4 && npairs / parts < 32)) return p;
@@ -1825,7 +1826,7 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
 #pragma unroll
     for (int l = 0; l < 8 * GI; ++l) issue_one(0, so[0], so[1], l);
 #pragma unroll
-    for (int l = 0; l < 8 * GI; ++l) issue_one(2 * BK * 2, so[2], so[3], l);
+    for (int l = 0; l < 8 * GI; ++l) issue_one(pair_offset(2), so[2], so[3], l);
     bool more = item + ncu < end_item;
     if (more) {
         describe(item + ncu, next, src_next, a_row);
@@ -3024,7 +3025,7 @@ extern "C" int moe_selfcheck_tile_order(int32_t tiles_m, int32_t tiles_n, int32_
         int covered = 0;
         for (int piece = 0; piece < p.parts; ++piece) {
             const int lo = piece * p.pairs_per * 2, n = std::min(p.pairs_per * 2, nk - lo);
-            if (lo != covered || n < 2) return moe_set_error(MOE_EINTERNAL, "pieces do not tile the k range");
+            if (lo != covered || n < 4) return moe_set_error(MOE_EINTERNAL, "pieces do not tile the k range by four k-tiles at least");
             covered += n;
         }
         if (covered != nk) return moe_set_error(MOE_EINTERNAL, "pieces do not cover the k range");

@@ -312,6 +312,10 @@ def test_tile_order_and_tail_plan_cover_every_tile_once():
                     assert 0 < rem <= 128 and rem * parts <= 256 and nk // parts >= 16
                     assert parts >= 4 or nk // parts >= 64
     assert split > 100
+    # every piece has two pairs of k-tiles at least, which a block loads before its loop: all K up to 65536, all sizes of a last round that are cut
+    for nk in range(32, 2050, 2):
+        for tiles in [t for t in range(1, 129) if 256 // t != 256 // (t + 1)]:
+            assert lib.moe_selfcheck_tile_order(tiles, 1, 256, nk) >= 1, lib.moe_last_error()
     assert lib.moe_selfcheck_tile_order(81, 112, 256, 128) == 2       # first GEMM of the Mixtral-shape share
     assert lib.moe_selfcheck_tile_order(81, 16, 256, 448) == 8        # second GEMM
     assert lib.moe_selfcheck_tile_order(0, 4, 256, 8) < 0
