@@ -557,6 +557,10 @@ FFN_CASES = [
     ("bf16", 0, 60, 256, 2048, 3, 1024),
     ("bf16", 2, 3000, 256, 256, 64, 1024),                 # the limits: 64 local experts, 1024 segments (many of them empty)
     ("bf16", 1, 5000, 128, 256, 32, 300),
+    # experts that are too large for the kernel of both GEMMs: as a small one of the same kind, on the tiles
+    ("fp32", 0, 300, 64, 320, 2, 5),
+    ("fp32", 2, 130, 64, 192, 2, 6),
+    ("bf16", 0, 300, 128, 512, 2, 3),
     # shares of at most 64 rows: the weight-streaming kernels (64-row tiles, tiles cut along K when they are few)
     ("bf16", 2, 16, 2048, 2048, 1, 1),
     ("bf16", 2, 64, 1024, 1408, 2, 3),
@@ -571,8 +575,18 @@ FFN_CASES = [
 ]
 
 
+def takes_small(R, n_local, nseg, Hd, F, act, dtype):
+    """Whether a share runs both GEMMs in one kernel."""
+    from paper_2410_17043_amd import _lib
+    got = _lib.load().moe_selfcheck_small(R, min(n_local, nseg, R), nseg, Hd, F, act, 1 if dtype == "bf16" else 0, 256)
+    assert got in (0, 1)
+    return got == 1
+
+
 @pytest.mark.parametrize("dtype,act,R,Hd,F,n_local,nseg", FFN_CASES)
 def test_expert_ffn(H, dtype, act, R, Hd, F, n_local, nseg):
+    case = (dtype, act, R, Hd, F, n_local, nseg)
+    assert takes_small(R, n_local, nseg, Hd, F, act, dtype) == (case in (("fp32", 0, 300, 64, 128, 2, 5), ("fp32", 2, 130, 64, 128, 2, 6), ("bf16", 0, 300, 128, 256, 2, 3)))
     cfg = small("c2_mixtral" if dtype == "bf16" else "c1_tiny_fp32", H=Hd, F=F, act=act, dtype=dtype)
     r = np.random.default_rng(R * 7 + F)
     recv = W.round_to_dtype(r.standard_normal((R, Hd)).astype(np.float32), dtype)
@@ -651,12 +665,14 @@ def test_ffn_phases_diag_marks_every_tile(H, R, Hd, F, act, which, rows):
         H.P.moe_diag_ffn_phases(x, R, so, se, 1, experts, Hd, F, act, "bf16", out, ws, which, marks[:((-(-R // 256)) * -(-N // cols) + 100) * 16])
 
 
-def test_expert_ffn_leaves_rows_outside_segments_untouched(H):
-    cfg = small("c2_mixtral", H=128, F=256)
+@pytest.mark.parametrize("F,one_kernel", [(256, True), (384, False)])
+def test_expert_ffn_leaves_rows_outside_segments_untouched(H, F, one_kernel):
+    assert takes_small(400, 1, 2, 128, F, 2, "bf16") == one_kernel
+    cfg = small("c2_mixtral", H=128, F=F)
     r = np.random.default_rng(5)
     recv = W.to_bf16_grid(r.standard_normal((400, 128)).astype(np.float32))
     experts = [W.make_expert_weights(cfg, 0)]
-    out = H.run_ffn(H.dev(recv, "bf16"), [10, 10, 300], [0, 0], [H.weights_to_dev(experts[0], "bf16")], 128, 256, 2, "bf16")
+    out = H.run_ffn(H.dev(recv, "bf16"), [10, 10, 300], [0, 0], [H.weights_to_dev(experts[0], "bf16")], 128, F, 2, "bf16")
     got = H.host(out)
     assert np.isnan(got[:10]).all() and np.isnan(got[300:]).all() and np.isfinite(got[10:300]).all()
     ref = O.expert_ffn(recv[10:300], [0, 290], [0], experts, 2)
@@ -1152,11 +1168,13 @@ def test_expert_ffn_fp32_in_parts_no_row_depends_on_its_neighbours(H):
     assert (~np.isfinite(out[which[0::5]])).any(axis=1).all() and np.isnan(out[which[1::5]]).all()
 
 
-@pytest.mark.parametrize("R,nseg", [(60, 5), (300, 63), (300, 64), (300, 65), (1000, 64)])
-def test_expert_ffn_tile_map_skips_what_it_must(H, R, nseg):
+@pytest.mark.parametrize("R,nseg,F,one_kernel", [(60, 5, 384, False), (300, 63, 384, False), (300, 64, 384, False), (300, 65, 384, False), (1000, 64, 384, False),
+                                                 (60, 5, 256, False), (300, 63, 256, False), (300, 64, 256, False), (300, 65, 256, False), (500, 64, 256, True), (1000, 64, 256, True)])
+def test_expert_ffn_tile_map_skips_what_it_must(H, R, nseg, F, one_kernel):
     """Empty segments, segments of no local expert, rows before the first and after the last segment, on both sides of
-    the segment count where the map kernel changes."""
-    Hd, F, n_local = 128, 256, 3
+    the segment count where the map kernel changes, and in the kernel that works its tiles out without a map."""
+    Hd, n_local = 128, 3
+    assert takes_small(R, n_local, nseg, Hd, F, 2, "bf16") == one_kernel
     cfg = small("c2_mixtral", H=Hd, F=F)
     r = np.random.default_rng(nseg)
     recv = W.to_bf16_grid(r.standard_normal((R, Hd)).astype(np.float32))
