@@ -694,7 +694,8 @@ __host__ __device__ __forceinline__ void tile_of_block_bands(int id, int tiles_m
 // of one row), +2.5 % at 6745 and 7900 rows (three rows), +1 % at 4147 and 5000 (two rows); with bands of
 // four to seven rows the exchange gains or loses less than 1 %, so those keep the M bands.
 //
-// bf16 grids of kFewestStripTiles to kStripTiles tiles that N does not band (see plan_strips) are numbered in strips instead: XCD x gets
+// bf16 grids of kFewestStripTiles to kStripTiles tiles that N does not band (see plan_strips), of GEMMs with K of least_strip_k and more, are
+// numbered in strips instead: XCD x gets
 // the x-th eighth of the tiles in an order that cuts N into strips and goes through a strip row by row, so that the tiles resident
 // on an XCD form a patch about as high as it is wide.  Bands -> strips on the kernels as they are, one FFN after the other: left-over
 // M-tiles and low bands, 2741 rows of 1152 -> 2304 -> 1152 for four experts 48.1 -> 47.2 us, 12000 of 1408 -> 2048 -> 1408 SwiGLU for
@@ -2671,8 +2672,13 @@ TileShape confirm_shape(TileShape t, int R, int n_used, int N, int K, int act, i
 }
 // column tiles of a GEMM of N output columns and tiles of bn weight rows
 int tiled_columns(int N, bool swiglu, int bn) { return swiglu ? (2 * N + bn - 1) / bn : (N + bn - 1) / bn; }
+// Short loops gain nothing from operands that an XCD's tiles share and lose more than that.  First GEMMs with bands / with strips, 128 x 128
+// tiles: at K = 128 and 256 0.78 to 1.04, 0.94 in the geometric mean of 41 (4065 rows of 256 -> 1664 14.5 -> 17.7 us), at 384 and 512 0.99,
+// from 640 on 1.01 to 1.03.  Larger tiles: at 256 and 384 FFNs of 0.99 to 1.00, at 512 1.013 and 1.016.
+int least_strip_k(int bm) { return bm == TileGeom<2, 2>::BM ? 640 : 512; }
 // tiles_n, or 0 if none of the tile counts that n_used runs of R rows can have is numbered in strips
-int columns_in_strips(int R, int bm, int n_used, int tiles_n) {
+int columns_in_strips(int R, int bm, int n_used, int tiles_n, int K) {
+    if (K < least_strip_k(bm)) return 0;
     const int hi = (int)((R + (int64_t)n_used * (bm - 1)) / bm);
     for (int t = (R + bm - 1) / bm; t <= hi; ++t)
         if (plan_strips(t, tiles_n).wide > 0) return tiles_n;
@@ -3059,6 +3065,17 @@ extern "C" int moe_selfcheck_small(int32_t R, int32_t n_used, int32_t nseg, int3
     return takes_small(R, n_used, nseg, H, F, act, dtype, ncu) ? 1 : 0;
 }
 
+// strips2: 1 where a GEMM that takes tiles of rows2 rows (see moe_selfcheck_tile_shapes) may be numbered in strips
+extern "C" int moe_selfcheck_strips(int32_t R, int32_t n_used, int32_t H, int32_t F, int32_t act, const int32_t* rows2, int32_t* strips2) {
+    if (R < 1 || n_used < 1 || H < 64 || F < 64 || act < 0 || act > 2 || !rows2 || !strips2) return moe_set_error(MOE_EINVAL, "moe_selfcheck_strips: bad argument");
+    for (int g = 0; g < 2; ++g) {
+        if (rows2[g] != 128 && rows2[g] != 192 && rows2[g] != 256) return moe_set_error(MOE_EINVAL, "moe_selfcheck_strips: no tiles of %d rows", rows2[g]);
+        const int tiles_n = tiled_columns(g == 0 ? F : H, g == 0 && act == MOE_ACT_SWIGLU, rows2[g] == 128 ? TileGeom<2, 2>::BN : TileGeom<4, 4>::BN);
+        strips2[g] = columns_in_strips(R, rows2[g], n_used, tiles_n, g == 0 ? H : F) > 0;
+    }
+    return MOE_OK;
+}
+
 extern "C" int moe_selfcheck_narrow(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t ncu, int32_t* forms2) {
     if (R < 1 || n_used < 1 || nseg < n_used || nseg > kMaxSeg || H < 128 || H % 128 != 0 || F < 128 || F % 128 != 0 || act < 0 || act > 2 || ncu < 1 || !forms2)
         return moe_set_error(MOE_EINVAL, "moe_selfcheck_narrow: bad argument");
@@ -3392,7 +3409,7 @@ static int ffn_impl(const void* recv, int32_t R, const int32_t* seg_offset, cons
     jobs.done = (dtype == MOE_BF16 || f32_pieces[0] || f32_pieces[1]) ? tilemap_at(workspace, R, 0, max_tiles_for(R) - 2).rel : nullptr;
     for (int g = 0; g < 2; ++g)
         jobs.tiles_n[g] = form[g].mt || skinny || dtype == MOE_F32 ? 0 : columns_in_strips(R, bm[g], n_used,
-            tiled_columns(g == 0 ? F : H, g == 0 && act == MOE_ACT_SWIGLU, shape[g] == TS_128 ? TileGeom<2, 2>::BN : TileGeom<4, 4>::BN));
+            tiled_columns(g == 0 ? F : H, g == 0 && act == MOE_ACT_SWIGLU, shape[g] == TS_128 ? TileGeom<2, 2>::BN : TileGeom<4, 4>::BN), g == 0 ? H : F);
     if (jobs.done) {
         jobs.job[0].m.done = jobs.done;
         jobs.job[1].m.done = jobs.done + kMaxSplitTiles;

@@ -895,17 +895,21 @@ def test_expert_ffn_narrow_tiles_of_one_segment(H, R, lo, hi, expert):
         H.assert_close(out[lo:hi], O.ffn(recv[lo:hi], w["w1"], w["w_up"], w["w_down"], 2), "bf16")
 
 
-# Grids that are numbered in strips (192 to 3000 tiles, no thicker bands of N): the numbers come from either map kernel, for one GEMM, the
+# Grids that are numbered in strips (192 to 3000 tiles, no thicker bands of N, K of 640 and more; the first two have a K of 128 and stay in bands): the numbers come from either map kernel, for one GEMM, the
 # other or both, with one height and with two; strips of two widths, a last round that is cut along K behind whole tiles.
-@pytest.mark.parametrize("R,Hd,F,n_local,nseg,act", [(3300, 128, 1024, 3, 12, 0), (3300, 1024, 128, 3, 100, 1), (4000, 1152, 1408, 4, 9, 2), (2741, 1152, 2304, 4, 24, 0),
-                                                     (8500, 2048, 768, 2, 5, 0)])
-def test_expert_ffn_grids_in_strips(H, R, Hd, F, n_local, nseg, act):
+@pytest.mark.parametrize("R,Hd,F,n_local,nseg,act,strips", [(3300, 128, 1024, 3, 12, 0, (0, 0)), (3300, 1024, 128, 3, 100, 1, (0, 0)), (3300, 640, 1024, 3, 12, 0, (1, 0)),
+                                                            (3300, 1024, 768, 3, 100, 1, (0, 1)), (4000, 1152, 1408, 4, 9, 2, (1, 1)), (2741, 1152, 2304, 4, 24, 0, (1, 1)),
+                                                            (8500, 2048, 768, 2, 5, 0, (1, 1))])
+def test_expert_ffn_grids_in_strips(H, R, Hd, F, n_local, nseg, act, strips):
     import ctypes as C
     from paper_2410_17043_amd import _lib
     got = (C.c_int32 * 2)()
     assert _lib.load().moe_selfcheck_tile_shapes(R, n_local, nseg, Hd, F, act, 256, got) == 0
     grids = [(-(-R // got[0]), -(-F // ((64 if got[0] == 128 else 128) if act == 2 else (128 if got[0] == 128 else 256)))), (-(-R // got[1]), -(-Hd // (128 if got[1] == 128 else 256)))]
     assert any(192 <= m * n <= 3000 and not (m // 8 < 4 and n // 8 > m // 8) for m, n in grids), grids
+    numbered = (C.c_int32 * 2)()
+    assert _lib.load().moe_selfcheck_strips(R, n_local, Hd, F, act, got, numbered) == 0
+    assert tuple(numbered) == strips
     cfg = small("c2_mixtral", H=Hd, F=F, act=act)
     r = np.random.default_rng(R + nseg)
     recv = W.to_bf16_grid(r.standard_normal((R, Hd)).astype(np.float32))

@@ -630,3 +630,18 @@ def test_no_share_runs_both_gemms_in_one_kernel_that_was_measured_slower_so():
         assert takes(*share, 256) == 0, share
     for share in faster:
         assert takes(*share, 256) == 1, share
+
+
+def test_only_gemms_of_long_loops_are_numbered_in_strips():
+    """K of 640 and more (512 in the larger tiles), 192 to 3000 tiles, no thicker bands of N."""
+    import ctypes as C
+    from paper_2410_17043_amd import _lib
+    strips = (C.c_int32 * 2)()
+    for R, n, H, F, act, rows, want in ((4065, 1, 256, 1664, 1, (128, 128), (0, 0)), (5703, 2, 128, 1152, 0, (128, 128), (0, 0)), (4302, 1, 512, 1792, 0, (128, 128), (0, 0)),
+                                        (4302, 1, 640, 1792, 0, (128, 128), (1, 0)), (2741, 4, 1152, 2304, 0, (128, 128), (1, 1)), (16384, 1, 2048, 2816, 2, (256, 256), (1, 1)),
+                                        (3300, 3, 1024, 640, 1, (128, 128), (0, 1)), (3300, 3, 1024, 512, 1, (128, 128), (0, 0)), (701, 1, 4096, 14336, 2, (192, 192), (0, 0)),
+                                        (20000, 4, 512, 2048, 2, (256, 128), (1, 1)), (40000, 4, 384, 3072, 1, (256, 128), (0, 1)),
+                                        (20571, 1, 4096, 14336, 2, (256, 256), (0, 1))):
+        assert _lib.load().moe_selfcheck_strips(R, n, H, F, act, (C.c_int32 * 2)(*rows), strips) == 0
+        assert tuple(strips) == want, (R, H, F, tuple(strips))
+    assert _lib.load().moe_selfcheck_strips(1, 1, 128, 128, 0, (C.c_int32 * 2)(64, 128), strips) < 0
