@@ -271,6 +271,9 @@ int moe_selfcheck_flow_player(int32_t n, const int64_t* D, const double* B, cons
 /* 1: a share of R rows for n_used experts in nseg segments runs both GEMMs in one kernel on a device of ncu compute units (0: not).
  * Only where the outputs share no memory with the received rows. */
 int moe_selfcheck_small(int32_t R, int32_t n_used, int32_t nseg, int32_t H, int32_t F, int32_t act, int32_t dtype, int32_t ncu);
+/* 1: a bf16 GEMM in tiles of `rows` rows with an inner dimension of K loads a pair of k-tiles as soon as its stages are free (0: spread
+ * over two k-tiles). */
+int moe_selfcheck_early_loads(int32_t rows, int32_t K);
 /* strips2 (HOST [2]): 1 where a bf16 GEMM in tiles of rows2 (HOST [2]) rows may be numbered in strips, by the tile counts that R rows
  * for n_used experts can have and by K; 0: in bands. */
 int moe_selfcheck_strips(int32_t R, int32_t n_used, int32_t H, int32_t F, int32_t act, const int32_t* rows2, int32_t* strips2);

@@ -63,6 +63,7 @@ SIGNATURES = {
     "moe_selfcheck_tile_shapes": (C.c_int, [_i32] * 7 + [_pi32]),
     "moe_selfcheck_flow_player": (C.c_int, [_i32, C.POINTER(C.c_int64), C.POINTER(C.c_double), _pi32]),
     "moe_selfcheck_small": (C.c_int, [_i32] * 8),
+    "moe_selfcheck_early_loads": (C.c_int, [_i32] * 2),
     "moe_selfcheck_strips": (C.c_int, [_i32] * 5 + [_pi32] * 2),
     "moe_selfcheck_narrow": (C.c_int, [_i32] * 7 + [_pi32]),
     "moe_selfcheck_f32_kernels": (C.c_int, [_i32] * 7 + [_pi32]),

@@ -1639,7 +1639,7 @@ struct WorkItem {
     int row0, nrows, n0;     // output rows and first output column
     const int32_t* rel;      // row offsets of a gathered tile, else NULL
 };
-template <int EPI, int MI, int NJ, bool TIMED>
+template <int EPI, int MI, int NJ, bool SOON, bool TIMED>
 __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_kernel(const uint16_t* __restrict__ A, int lda, TileMap m,
                                                            ExpertTable tab, int which0, int which1, int N, int K,
                                                            uint16_t* __restrict__ C, int ldc, int tiles_n, const int32_t* __restrict__ strips_at, int ncu, int walk, int most_tail,
@@ -1762,7 +1762,7 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
         load_to_lds(r, to, is_a ? src.a_voff[i] : src.b_voff[i], kb + (l & 1) * (BK * 2));
     };
     constexpr int GI = (MI + NJ + 3) / 4;                    // 16-row blocks per quarter of a pair (the last may have fewer)
-    constexpr bool SOON = TG::PER_CU > 1;                    // loads as early as they can go out, else evenly spread (see below)
+    // SOON: loads as early as they can go out, else evenly spread (see below)
     constexpr int FIRST_LOADS = SOON ? 8 * GI : 4 * GI;      // of the loads of a pair, 4 or 8 GI go out during the first k-tile of a trip
 
     // A fragment is 16 rows x 32 elements, one 16-row block of the stage; block i of the wave lies i KB further
@@ -1781,7 +1781,7 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     // The results are the same bits.  The order is that of the source (see the barriers): the scheduler left to itself
     // moves all reads together and mixes the runs.  20571 rows of 4096 -> 14336 -> 4096: 3590 + 1780 -> 3360 + 1650 us.
     auto k_tile = [&](auto from_zero, const bf16x8 (&af)[2 * MI], const bf16x8 (&bfr)[2 * NJ], bf16x8 (&an)[2 * MI], bf16x8 (&bn)[2 * NJ], const unsigned char* next_stage, auto n_loads, auto load) {
-        constexpr int READS = 2 * MI + 2 * NJ, LOADS = decltype(n_loads)::value, M = 4 * MI * NJ, EVERY = 3;
+        constexpr int READS = 2 * MI + 2 * NJ, LOADS = decltype(n_loads)::value, M = 4 * MI * NJ, EVERY = M >= 48 ? 3 : 1;
         const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < 2 * NJ; ++j)
@@ -1806,10 +1806,10 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     // A half is 2 GI 16-row blocks, both k-tiles of the pair: 8 loads per wave at 4 x 4.  These
     // loads are spread evenly, at 4 x 4 one per eight MFMAs: a CU sustains roughly one wave-load per 40 clocks
     // when the lines come from HBM, and a load that cannot be accepted stalls the wave's MFMA issue too (loads one after the
-    // other, in front of the reads: 2 to 5 % slower).  128 x 128 tiles (SOON) are bound by what is in flight instead: a k-tile of a
-    // block is 0.12 us of products, a round trip 0.7, and the other block of the CU fills a stall.  There the whole pair goes out in
-    // the first k-tile as soon as its stages are free, in front of the reads: 2741 rows of 1152 -> 2304 -> 1152 for four experts 59.9
-    // -> 56.9 us, 800 of 2048 -> 1408 -> 2048 SwiGLU 53.1 -> 46.9 (in halves, one after the other: 59.2 and 51.9).
+    // other, in front of the reads: 2 to 5 % slower).  128 x 128 tiles of long loops (SOON, see kSoonK) are bound by what is in flight
+    // instead: a k-tile of a block is 0.12 us of products, a round trip 0.7, and the other block of the CU fills a stall.  There the whole
+    // pair goes out in the first k-tile as soon as its stages are free, in front of the reads: 2741 rows of 1152 -> 2304 -> 1152 for four
+    // experts 59.9 -> 56.9 us, 800 of 2048 -> 1408 -> 2048 SwiGLU 53.1 -> 46.9 (in halves, one after the other: 59.2 and 51.9).
     // A bare s_barrier is used: __syncthreads() would add a fence that waits for ALL outstanding loads.  In front of it a
     // wave waits for its own LDS reads: a read that is only issued is not ordered against what other waves write behind
     // the barrier.  They are the first fragments that the MFMAs behind it need.
@@ -2499,7 +2499,16 @@ int walk_blocks(int max_items, int walk, int ncu) {
     return (rounds <= walk ? 1 : (rounds + 2 * walk - 2) / walk) * ncu;
 }
 
-template <int EPI, int MI, int NJ, bool TIMED>
+enum TileShape { TS_128, TS_192, TS_256 };
+// When the loads of 128 x 128 tiles go out as early as they can.  Time with spread loads over time with early ones, operands in the caches /
+// from memory, by the number of tiles, 1000 GEMMs of 100 to 14000 rows, K and N up to 2048: K up to 384 0.94 to 0.99 / 0.97 to 1.01, 512 to 1024
+// 0.96 to 1.01 / 0.97 to 1.05, from 1152 on 0.98 to 1.03 / 0.99 to 1.05; 235 of K from 512 to 7168 1.016 / 1.038.  Between 512 and 1024 it depends
+// on where the operands are, and the spread loads are the ones that lose less (early ones: 7 to 10 % of a GEMM of 12 to 20 us).
+// From 1152 on, grids of 257 to 450 tiles, where some CUs have two blocks and others one, take 1.01 to 1.04 times as long as with the
+// 32 x 32 x 16 loop before this one, up to 1.16 times; with one block per CU, or two on all, early loads are 1.02 to 1.08 times as fast.
+constexpr int kSoonK = 1152;
+bool loads_soon(TileShape t, int K) { return t == TS_128 && K >= kSoonK; }
+template <int EPI, int MI, int NJ, bool SOON, bool TIMED>
 int launch_bf16(const void* A, int lda, const TileMap& m, const int32_t* strips, const ExpertTable& tab, int which0, int which1, int N, int K,
                 void* C, int ldc, int R, int nseg, int n_used, float* partial, hipStream_t st, long long* marks,
                 size_t marks_len) {
@@ -2509,7 +2518,7 @@ int launch_bf16(const void* A, int lda, const TileMap& m, const int32_t* strips,
     const int ncu = round_size() * TG::PER_CU;             // tiles per round of the grid
     static bool attr_done = false;
     if (!attr_done) {
-        MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<EPI, MI, NJ, TIMED>),
+        MOE_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<EPI, MI, NJ, SOON, TIMED>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, TG::LDS));
         attr_done = true;
     }
@@ -2519,7 +2528,7 @@ int launch_bf16(const void* A, int lda, const TileMap& m, const int32_t* strips,
     for (int t = (R + TG::BM - 1) / TG::BM, hi = (R + n_used * (TG::BM - 1)) / TG::BM; t <= hi; ++t)
         most_tail = std::max(most_tail, plan_tail(t * tiles_n, ncu, K / BK).n_tail);
     const int walk = walk_tiles(TG::BM, K);
-    hipLaunchKernelGGL((gemm_bf16_kernel<EPI, MI, NJ, TIMED>), dim3(walk_blocks(max_tiles_of(R, TG::BM, nseg) * tiles_n + ncu, walk, ncu)), dim3(256), TG::LDS, st,
+    hipLaunchKernelGGL((gemm_bf16_kernel<EPI, MI, NJ, SOON, TIMED>), dim3(walk_blocks(max_tiles_of(R, TG::BM, nseg) * tiles_n + ncu, walk, ncu)), dim3(256), TG::LDS, st,
                        reinterpret_cast<const uint16_t*>(A), lda, m, tab, which0, which1, N, K,
                        reinterpret_cast<uint16_t*>(C), ldc, tiles_n, strips, ncu, walk, most_tail, partial, marks,
                        (uint32_t)std::min<size_t>(marks_len / 16, 0xFFFFFFFFu));
@@ -2534,14 +2543,14 @@ int launch_bf16(const void* A, int lda, const TileMap& m, const int32_t* strips,
     return MOE_OK;
 }
 
-enum TileShape { TS_128, TS_192, TS_256 };
 template <int EPI>
 int launch_bf16_shape(TileShape t, const void* A, int lda, const TileMap& m, const int32_t* strips, const ExpertTable& tab, int which0, int which1, int N, int K,
                       void* C, int ldc, int R, int nseg, int n_used, float* partial, hipStream_t st, bool timed, long long* marks, size_t marks_len) {
 #define MOE_GEMM(...) launch_bf16<EPI, __VA_ARGS__>(A, lda, m, strips, tab, which0, which1, N, K, C, ldc, R, nseg, n_used, partial, st, marks, marks_len)
-    if (t == TS_128) return timed ? MOE_GEMM(2, 2, true) : MOE_GEMM(2, 2, false);
-    if (t == TS_192) return timed ? MOE_GEMM(3, 4, true) : MOE_GEMM(3, 4, false);
-    return timed ? MOE_GEMM(4, 4, true) : MOE_GEMM(4, 4, false);
+    if (loads_soon(t, K)) return timed ? MOE_GEMM(2, 2, true, true) : MOE_GEMM(2, 2, true, false);
+    if (t == TS_128) return timed ? MOE_GEMM(2, 2, false, true) : MOE_GEMM(2, 2, false, false);
+    if (t == TS_192) return timed ? MOE_GEMM(3, 4, false, true) : MOE_GEMM(3, 4, false, false);
+    return timed ? MOE_GEMM(4, 4, false, true) : MOE_GEMM(4, 4, false, false);
 #undef MOE_GEMM
 }
 
@@ -3063,6 +3072,13 @@ extern "C" int moe_selfcheck_small(int32_t R, int32_t n_used, int32_t nseg, int3
     if (R < 1 || n_used < 1 || nseg < n_used || H < 1 || F < 1 || act < 0 || act > 2 || (dtype != MOE_F32 && dtype != MOE_BF16) || ncu < 1)
         return moe_set_error(MOE_EINVAL, "moe_selfcheck_small: bad argument");
     return takes_small(R, n_used, nseg, H, F, act, dtype, ncu) ? 1 : 0;
+}
+
+// 1: the loads of a pair of k-tiles go out together as soon as its stages are free
+extern "C" int moe_selfcheck_early_loads(int32_t rows, int32_t K) {
+    for (const TileShape t : {TS_128, TS_192, TS_256})
+        if (kShapeRows[t] == rows && K > 0) return loads_soon(t, K) ? 1 : 0;
+    return moe_set_error(MOE_EINVAL, "moe_selfcheck_early_loads: bad argument");
 }
 
 // strips2: 1 where a GEMM that takes tiles of rows2 rows (see moe_selfcheck_tile_shapes) may be numbered in strips

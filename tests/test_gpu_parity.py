@@ -919,6 +919,26 @@ def test_expert_ffn_grids_in_strips(H, R, Hd, F, n_local, nseg, act, strips):
     H.assert_close(out, O.expert_ffn(recv, off, exp, experts, act), "bf16")
 
 
+# 128 x 128 tiles by the two orders of their loads: the shortest loops (four and six k-tiles), the last K of the spread loads beside the first of the
+# early ones, more tiles than run at a time (a block goes on to another tile behind a loop of four and of eight k-tiles), gathered tiles.
+@pytest.mark.parametrize("R,Hd,F,n_local,nseg,act,early", [(300, 128, 512, 1, 1, 0, (0, 0)), (700, 256, 384, 2, 100, 2, (0, 0)), (500, 1024, 1152, 1, 3, 1, (0, 1)),
+                                                           (500, 1152, 1024, 2, 80, 2, (1, 0)), (2907, 128, 1792, 5, 90, 2, (0, 1)), (2907, 256, 1792, 5, 30, 2, (0, 1))])
+def test_expert_ffn_128_row_tiles_of_short_and_long_loops(H, R, Hd, F, n_local, nseg, act, early):
+    import ctypes as C
+    from paper_2410_17043_amd import _lib
+    lib, rows, forms = _lib.load(), (C.c_int32 * 2)(), (C.c_int32 * 2)()
+    assert lib.moe_selfcheck_tile_shapes(R, n_local, nseg, Hd, F, act, 256, rows) == 0 and lib.moe_selfcheck_narrow(R, n_local, nseg, Hd, F, act, 256, forms) == 0
+    assert not takes_small(R, n_local, nseg, Hd, F, act, "bf16") and not any(forms) and 128 in rows
+    assert [lib.moe_selfcheck_early_loads(128, K) for K in (Hd, F)] == list(early)
+    cfg = small("c2_mixtral", H=Hd, F=F, act=act)
+    r = np.random.default_rng(R + nseg)
+    recv = W.to_bf16_grid(r.standard_normal((R, Hd)).astype(np.float32))
+    experts = [W.make_expert_weights(cfg, e) for e in range(n_local)]
+    off, exp = make_segments(r, R, nseg, n_local)
+    out = H.host(H.run_ffn(H.dev(recv, "bf16"), off, exp, [H.weights_to_dev(w, "bf16") for w in experts], Hd, F, act, "bf16"))
+    H.assert_close(out, O.expert_ffn(recv, off, exp, experts, act), "bf16")
+
+
 # Both GEMMs in one kernel (32-row tiles): one row, a row less and more than a tile, several tiles; one column tile per wave and
 # several, in either GEMM; rows from all over, experts in falling order (more runs than experts), segments without rows, of unknown
 # experts and outside the rows.  Against the oracle, against the GEMMs by themselves (of

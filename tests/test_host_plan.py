@@ -645,3 +645,10 @@ def test_only_gemms_of_long_loops_are_numbered_in_strips():
         assert _lib.load().moe_selfcheck_strips(R, n, H, F, act, (C.c_int32 * 2)(*rows), strips) == 0
         assert tuple(strips) == want, (R, H, F, tuple(strips))
     assert _lib.load().moe_selfcheck_strips(1, 1, 128, 128, 0, (C.c_int32 * 2)(64, 128), strips) < 0
+
+
+def test_only_128_row_tiles_of_long_loops_load_early():
+    from paper_2410_17043_amd import _lib
+    early = _lib.load().moe_selfcheck_early_loads
+    assert [early(128, K) for K in (128, 256, 896, 1024, 1152, 4096)] == [0, 0, 0, 0, 1, 1]
+    assert early(192, 4096) == early(256, 4096) == 0 and early(64, 4096) < 0
