@@ -19,8 +19,8 @@ __device__ __forceinline__ __bf16 weyl_bf16(uint32_t n) {
 // One wave per SIMD (256 accumulator registers per lane leave room for no second one), 4 x 4 independent
 // 32x32x16 bf16 MFMA tiles per trip, as many accumulators as the large tiles of the FFN, but no LDS and no
 // memory traffic inside the loop.  Operand registers rotate from trip to trip so that consecutive MFMAs
-// never read the same pair.  (The large tiles use v_mfma_f32_16x16x32_bf16 in runs with one operand in common, which sustain
-// 2.06 PFLOP/s from registers where this loop sustains 1.81: the card is limited by power.)
+// never read the same pair.  (The large tiles use v_mfma_f32_16x16x32_bf16 in runs with one operand in common: the card is
+// limited by power, and a loop of those, which is not in the library, sustained 2.06 PFLOP/s from registers where this one sustains 1.81.)
 __global__ __launch_bounds__(256, 1) void mfma_only_kernel(int iters, float* __restrict__ sink) {
     const uint32_t id = (blockIdx.x * 256u + threadIdx.x) * 64u;
     bf16x8 a[4], b[4];

@@ -1604,6 +1604,11 @@ __device__ __forceinline__ void sum_pieces(int unit_lo, int unit_hi, const float
     }
 }
 
+// 16 bytes per lane, from lane_off + off on, into the KB of LDS at `to`
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, unsigned char* to, uint32_t lane_off, int off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)to, 16, lane_off, off, 0, 0);
+}
+
 // C[r, n] = epi(sum_k A[r,k] B0[n,k] , sum_k A[r,k] B1[n,k]) for one M-tile of 64 MI rows and one
 // N-tile of 64 NJ weight rows.  SwiGLU: the B tile's rows are, per wave-column wn (16 NJ output columns), 16 NJ rows
 // of W1 followed by the 16 NJ rows of Wu for the same columns, so the gate and the up product of
@@ -1611,8 +1616,8 @@ __device__ __forceinline__ void sum_pieces(int unit_lo, int unit_hi, const float
 //
 // Pipeline: 5 LDS stages of one 32-wide k-tile each (160 KB at 4 x 4).  Loads are direct-to-LDS and
 // issued in PAIRS of k-tiles (2q, 2q+1) every second iteration, interleaved so that the two
-// halves of every 128-byte memory line are requested back to back: half-line requests that
-// come a whole k-tile apart cost about twice the L2 bandwidth.  The pair (kt+4, kt+5) is issued
+// halves of every 128-byte memory line are requested close together (a few products apart): half-line requests
+// that come a whole k-tile apart cost about twice the L2 bandwidth.  The pair (kt+4, kt+5) is issued
 // from iteration kt on (kt even) and has to be there before iteration kt+3.
 // The MFMAs are issued as D = B . A^T (operands swapped), so a lane ends up with 4 consecutive
 // output COLUMNS of one row (see store_tile).
@@ -1629,10 +1634,6 @@ __device__ __forceinline__ void sum_pieces(int unit_lo, int unit_hi, const float
 // TIMED (diagnostics, moe_diag_ffn_phases): the same kernel with the 100 MHz wall clock read by lane 0 of every wave
 // into marks[item][wave][4]: 0 start, 1 first operands in LDS (loop about to start), 2 loop done, 3 end; an item is a
 // tile or a piece of one (there is room for all of them: see max_items).  The ordinary instantiation contains none of it.
-// 16 bytes per lane, from lane_off + off on, into the KB of LDS at `to`
-__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, unsigned char* to, uint32_t lane_off, int off) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)to, 16, lane_off, off, 0, 0);
-}
 struct WorkItem {
     int tile_id, piece;      // piece < 0: the whole K range
     int nk;                  // k-tiles (even: K is a multiple of 64)
@@ -1776,8 +1777,9 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     };
     // The MFMAs of a k-tile, with the reads of the next one's fragments and `load` 0 .. LOADS - 1 between them.
     // Power bounds the large tiles, so the instruction is the one that takes the least of it per product: from registers alone
-    // v_mfma_f32_16x16x32_bf16 sustains 2.06 PFLOP/s on a whole chip (1.96 GHz), v_mfma_f32_32x32x16_bf16 1.81 (1.73 GHz) - and in
-    // runs that have the weight fragment in common (1.66 to 1.79 PFLOP/s where both operands change from product to product).
+    // v_mfma_f32_16x16x32_bf16 sustained 2.06 PFLOP/s on a whole chip (1.96 GHz), v_mfma_f32_32x32x16_bf16 1.81 (1.73 GHz) - and in
+    // runs that have the weight fragment in common (1.66 to 1.79 PFLOP/s where both operands change from product to product).  (The first
+    // and the last of these by a loop that is not in the library: moe_diag_mfma_only runs the larger instruction.)
     // The results are the same bits.  The order is that of the source (see the barriers): the scheduler left to itself
     // moves all reads together and mixes the runs.  20571 rows of 4096 -> 14336 -> 4096: 3590 + 1780 -> 3360 + 1650 us.
     auto k_tile = [&](auto from_zero, const bf16x8 (&af)[2 * MI], const bf16x8 (&bfr)[2 * NJ], bf16x8 (&an)[2 * MI], bf16x8 (&bn)[2 * NJ], const unsigned char* next_stage, auto n_loads, auto load) {
@@ -1839,8 +1841,8 @@ __global__ __launch_bounds__(256, (TileGeom<MI, NJ>::PER_CU)) void gemm_bf16_ker
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int r = 0; r < 2 * (MI + NJ); ++r) read(a0, b0, lds + so[0], r);
-    // One trip.  FIRST: of a tile (the products start from zero); SWITCH: the loads of this tile end with phase A, those
-    // of the next one follow.
+    // One trip.  FIRST: of a tile (the products start from zero); SWITCH: the loads of this tile have all
+    // gone out, those of the next one follow.
     auto trip = [&](int kt, auto first, auto switches) {
         constexpr bool FIRST = decltype(first)::value, SWITCH = decltype(switches)::value;
         const unsigned char *s1 = lds + so[1], *s2 = lds + so[2];
@@ -2487,7 +2489,8 @@ int round_size() {
 // 210 us that end one after the other (-> a block per tile): gate to send buffer beside 20571 rows of 4096 -> 14336 -> 4096
 // 3.0 -> 0.39 (0.27) ms, the whole share 4.8 -> 2.3 (1.35) ms; beside 200000 rows of 2048 -> 1408 -> 2048 1.26 -> 0.16
 // (0.14) and 2.3 -> 1.4 (0.76) ms; beside 40000 rows of 1024 -> 4096 -> 1024 0.89 -> 0.53 (0.53) ms.  What a new block
-// costs (4.7 us) shows as 0.5 to 1.4 % of those GEMMs; runs of 100 us cost 1.5 to 3.8 %.
+// costs (4.7 us) shows as 0.5 to 1.4 % of those GEMMs; runs of 100 us cost 1.5 to 3.8 %.  (The k-tiles below are of loops with 32 x 32 x 16
+// products; those of 256 rows take 0.69 to 0.75 us today.)
 constexpr double kWalkUs = 210.0;
 int walk_tiles(int rows, int K) {
     const double k_tile_us = rows == TileGeom<2, 2>::BM ? 0.53 : rows == TileGeom<3, 4>::BM ? 0.61 : 0.75;   // on a full chip
@@ -2558,7 +2561,8 @@ int launch_bf16_shape(TileShape t, const void* A, int lda, const TileMap& m, con
 // estimate of it: half a tile of padding per expert.  Every shape's time is modelled as rounds of the grid, a round
 // costing a + b * (k-tiles of 32), and a tail as plan_tail cuts it; the first round of the large shapes starts cold; the
 // shape with the least time is preferred, and taken if it holds up (see confirm_shape).  The
-// constants (microseconds) are from GEMMs of K = 1024 ... 14336 with whole rounds: 256 x 256 100 us per round at
+// constants (microseconds) are from GEMMs of K = 1024 ... 14336 with whole rounds, in loops of 32 x 32 x 16 products (2 to 9 % slower
+// than today's, 5 to 12 at 128 x 128; see below for how the choice does on today's): 256 x 256 100 us per round at
 // K = 4096, 37 at 1024; 192 x 256 80 us at 4096; 128 x 128, two blocks per CU, 66 us at 4096 and 36 at 2048, and
 // about two thirds of that when the round has one block per CU.  So 256 x 256 is the best rate (1.35 PFLOP/s against
 // 1.3 and 1.0) and the others win where it leaves CUs idle or rows empty: at 2048 -> 1408 -> 2048 with four experts
@@ -2611,9 +2615,11 @@ TileShape choose_shape(int R, int n_used, int N, int K, int act, int cus) {
 // half each; a height at which that exceeds 1.04 is given up for the one with the least (256 has 1).  The constants are
 // fitted to 430000 GEMMs of 65 to 20000 rows, 1 to 64 experts, H and F of 128 to 14336, weights from cold memory (median
 // error 5 %).  Over those the expert FFN is more than 3 % slower than one block per 256 x 256 tile was in 0.4 % of the
-// shares, in 2.9 % without this check; the mean gain is 1.249, 1.230 without.  (All constants are of the loops with 32 x 32 x 16
-// products, 2 to 9 % slower than today's.  Fitted again to 68000 GEMMs of today's the rule would be 0.5 % faster in the mean and more
-// than 3 % slower in 4 % of them; tiles of 192 x 128 beside the three, 2.2 % faster and 1.1 %.)
+// shares, in 2.9 % without this check; the mean gain is 1.249, 1.230 without.  (All of this is of the loops with 32 x 32 x 16
+// products.  On today's, 460 shares of 65 to 20000 rows that take another height than 256 and no narrow tiles, one after the other with operands
+// in the caches where they fit: 1.37 times as fast in the geometric mean as with 256 x 256 tiles, three more than 3 % slower.  Fitted again to
+// 68000 GEMMs of today's the rule would be 0.5 % faster in the mean and more than 3 % slower in 4 % of them; tiles of 192 x 128 beside the three,
+// 2.2 % faster and 1.1 %.)
 struct ShapeCost { double start, a, b, a2, pair, b_pair, piece0, piece, gelu, tb_s, first_bytes; };
 double played_us(TileShape t, int tiles_m, int R, int n_used, int N, int K, int act, int cus) {
     // start of the launch; per round and per k-tile of it (at no occupancy, and what full occupancy adds); rounds with two
@@ -2750,7 +2756,9 @@ int launch_bf16_skinny_mt(const void* A, int lda, const TileMap& m, const Expert
 // by popularity and cut at random, weights from cold memory (median error 8 %).  Over 1200 other shares the expert FFN is 1.322
 // times faster in the mean than without narrow tiles, two are more than 3 % slower (4 %); with one spread of the rows and equal
 // starts of all kernels 39 of 900 were, by up to 20 %.  2500 shares by their kernel durations: 1.390 faster, 1.424 with the best form
-// always known, 12 more than 3 % slower; with 10 and 8 % 1.395 and 19, with 18 % 1.372 and 4.
+// always known, 12 more than 3 % slower; with 10 and 8 % 1.395 and 19, with 18 % 1.372 and 4.  (All beside tiled kernels of 32 x 32 x 16 products.
+// Beside today's, 260 shares with narrow tiles, of up to 32 experts and with operands in the caches where they fit: 1.34 times as fast as
+// without, eleven more than 3 % slower, ten of them by 3 to 9 %, shares of 14 experts and more.)
 struct NarrowForm { int mt, nt; };                       // mt = 0: none
 struct NarrowCost { NarrowForm form; double start, gb_s, per_round, tb_s, all_tb_s, alone; };   // alone: what an otherwise idle chip adds to gb_s
 constexpr NarrowCost kNarrowForms[] = {{{4, 2}, 1.45, 57.2, 2.95, 10.0, 100.0, 0.70}, {{2, 2}, 1.66, 46.6, 2.96, 10.0, 24.2, 1.18},
